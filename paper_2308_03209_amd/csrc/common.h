@@ -314,7 +314,16 @@ int32_t launch_wgrad(int32_t dtype, const void* A, int64_t lda, int32_t N1, cons
 // shared by the float32 and bfloat16 paths; resident = workgroups of the kernel the chip holds at once
 // (three per CU for the float32 kernel, two for the bfloat16 one)
 constexpr int32_t WGRAD_RESIDENT_F32 = 768, WGRAD_RESIDENT_BF16 = 512;
-int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident);
+// float32 products on the bfloat16 matrix cores: 256x128 tiles at two workgroups per CU, 128x128 at three
+constexpr int32_t WGRAD_RESIDENT_SPLIT_TALL = 512, WGRAD_RESIDENT_SPLIT = 768;
+int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident, int32_t tile_rows = 128);
+// float32 products on the bfloat16 matrix cores (gemm_split.hip): which shapes they take, and their launchers
+bool gemm_split_fits(const GemmArgs& a);
+int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream);
+bool wgrad_split_fits(int32_t N1, int32_t N2a, int32_t N2b, int64_t lda, int64_t ldb, int64_t ldb2);
+int32_t launch_wgrad_split(const float* A, int64_t lda, int32_t N1, const float* B, int64_t ldb, int32_t N2a, int64_t M,
+                           float* C, int64_t ldc, int32_t accumulate, float* workspace, hipStream_t stream,
+                           float* colsum_out, const float* B2, int64_t ldb2, int32_t N2b);
 int32_t launch_split_reduce(const float* partials, int64_t split_stride, int32_t splits, float* C, int64_t ldc,
                             int32_t rows, int32_t cols, int32_t accumulate, hipStream_t stream);
 int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream);

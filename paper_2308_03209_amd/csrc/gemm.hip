@@ -1,5 +1,6 @@
 // Dense feature transforms of the layers (the W and U products of the GraphSAGE layer in
-// Section 3 and their gradients) on the fp32 matrix cores of gfx950.
+// Section 3 and their gradients) on the fp32 matrix cores of gfx950: results of at most 64 columns (weight
+// gradients: 64 rows or columns) and the shapes that gemm_split.hip leaves out.
 //
 // One kernel computes a 128x128 tile of  C = sum_k Aop(i,k) * Bop(j,k)  per 256-thread block:
 // four 64-wide wavefronts in a 2x2 grid, each holding a 64x64 sub-tile as 2x2 blocks of
@@ -582,7 +583,11 @@ int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(a.K2 == 0 || a.A2, "dense: second segment is NULL");
   COFREE_REQUIRE(a.lda1 >= a.K1 && (a.K2 == 0 || a.lda2 >= a.K2), "dense: lda too small");
   COFREE_REQUIRE(a.ldc >= a.N, "dense: ldc too small");
+  COFREE_REQUIRE(!(a.K2 > 0 && a.B2) ? a.ldb >= (a.b_kmajor ? (int64_t)a.N : (int64_t)a.K1 + a.K2)
+                                     : (a.b_kmajor ? (a.ldb >= a.N && a.ldb2 >= a.N) : (a.ldb >= a.K1 && a.ldb2 >= a.K2)),
+                 "dense: ldb too small");
   if (a.M == 0) return COFREE_OK;
+  if (gemm_split_fits(a)) return launch_gemm_split(a, stream);
   GemmK p{};
   p.A1 = (const float*)a.A1;
   p.lda1 = a.lda1;
@@ -623,7 +628,6 @@ int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
            a.b_kmajor && a.N < 4 ? "true" : "false", (a.b_kmajor && a.N < 4) || narrow ? 1 : 0, (int)a.N, (int)p.K);
   ProfScope prof(pname, stream, bytes, flops);
   if (a.b_kmajor) {
-    COFREE_REQUIRE(a.ldb >= a.N && (!p.B2 || a.ldb2 >= a.N), "dense: ldb too small");
     if (a.N < 4)
       gemm_kernel<false, true, true, 1><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
     else if (narrow)
@@ -631,7 +635,6 @@ int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
     else
       gemm_kernel<false, true, false, 0><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
   } else {
-    COFREE_REQUIRE(p.B2 ? (a.ldb >= a.K1 && a.ldb2 >= a.K2) : a.ldb >= p.K, "dense: ldb too small");
     if (narrow)
       gemm_kernel<false, false, false, 1><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
     else
@@ -647,8 +650,8 @@ int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
 // CU, 77 chunks x 10 tiles = 770 workgroups ran 1.5 rounds in the time of 2); and as many rounds as it takes
 // to have at least 128 chunks, since few long chunks measured slower (256x602 over 230k nodes: 51 chunks
 // 73 TFLOP/s, 102 chunks 91, 153 chunks 98).  At least 512 reduction steps per chunk, at most 512 chunks.
-int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident) {
-  const int64_t tiles = (int64_t)((N1 + BM - 1) / BM) * ((N2 + BN - 1) / BN);
+int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident, int32_t tile_rows) {
+  const int64_t tiles = (int64_t)((N1 + tile_rows - 1) / tile_rows) * ((N2 + BN - 1) / BN);
   int64_t rounds = 1;
   while (rounds < 8 && resident * rounds / tiles < 128) ++rounds;
   int64_t s = resident * rounds / tiles;
@@ -669,7 +672,8 @@ int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident) {
 // enough for either storage type
 size_t wgrad_workspace_floats(int32_t N1, int32_t N2, int64_t M) {
   const int32_t s32 = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_F32), s16 = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_BF16);
-  return (size_t)(s32 > s16 ? s32 : s16) * ((size_t)N1 * (size_t)N2 + (size_t)N1);
+  const int32_t tall = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_SPLIT_TALL, 256);
+  return (size_t)std::max(std::max(s32, s16), tall) * ((size_t)N1 * (size_t)N2 + (size_t)N1);
 }
 
 int32_t launch_split_reduce(const float* partials, int64_t split_stride, int32_t splits, float* C, int64_t ldc,
@@ -696,6 +700,9 @@ int32_t launch_wgrad(int32_t dtype, const void* Av, int64_t lda, int32_t N1, con
   COFREE_REQUIRE(dtype == COFREE_F32, "wgrad: unknown dtype");
   const float* A = (const float*)Av;
   const float* B = (const float*)Bv;
+  if (wgrad_split_fits(N1, N2a, B2v ? N2b : 0, lda, ldb, ldb2))
+    return launch_wgrad_split(A, lda, N1, B, ldb, N2a, M, C, ldc, accumulate, workspace, stream, colsum_out,
+                              (const float*)B2v, ldb2, N2b);
   const int32_t S = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_F32);
   GemmK p{};
   p.A1 = A;

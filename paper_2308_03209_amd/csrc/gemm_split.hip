@@ -1,0 +1,726 @@
+// Float32 products of the layers on the bfloat16 matrix cores, with float32 operands, sums and results.
+//
+// A float32 has 24 significant bits and a bfloat16 eight, over the same exponent range, so every float32 is the
+// exact sum of three bfloat16: x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m (both differences are
+// exact in float32, and the second has at most eight bits left).  A product of two float32 is then nine products
+// of bfloat16, each exact in float32; the six that reach 2^-24 of it (l h, h l, m m, m h, h m, h h) are accumulated
+// in float32, smallest first - the three-way split of Henry, Tang and Heinecke ("Leveraging the bfloat16 artificial
+// intelligence datatype for higher-precision computations", ARITH 2019).  What is left out is below 2^-23 of a
+// product at worst and around 2^-27 of it on average, less than the rounding of the running sum.
+//
+// Which shapes: results of more than 64 columns (weight gradients: more than 64 rows and columns) and ranges of at
+// least eight k.  Narrower ones are bound by their bytes and stay on the float32 instructions (gemm.hip).
+//
+// What bounds it: a 32x32x16 bfloat16 matrix instruction takes 32 cycles, eight 32x32x2 float32 ones 512, so six of
+// the former could be 2.7 times as fast; but a loop of nothing but matrix instructions on random data already lowers
+// the shader clock from 2.4 to 1.8 GHz (1,860 TFLOP/s in bfloat16), and this kernel runs at about 1.6 GHz with the
+// matrix units 65 % busy: power, not issue slots, is the limit (128x128 tiles with half the reuse are only 4 %
+// slower).  Measured against the float32 instructions, in TFLOP/s of the product: 470k x 512 x 512 125 -> 206 (A B^T),
+// 122 -> 188 (A B), 124 -> 214 (A^T B); 529k x 512 x 1024 132 -> 220 and 128 -> 239; 230k x 256 x 602 112 -> 158 and
+// 99 -> 155.  The error against float64 is below that of the float32 instructions (230k-node and 529k-node sums:
+// 6.3e-8 against 7.6e-8; K = 602: 3.7e-7 against 4.4e-7) because the running sum is rounded six times per 16 k
+// instead of eight.
+//
+// Tiling: four wavefronts 2x2 per workgroup, each 32 RM x 32 RN of the result (64x128 or 128x64: 18 operand reads
+// from LDS per 48 matrix instructions), two workgroups per CU; see run_split for the pipeline.
+//
+// LDS plane of an operand of R rows: [k-group of 8][row][8 bfloat16].  A matrix operand - 8 consecutive k of 32
+// consecutive rows per half wavefront - is then 512 contiguous bytes.  Neighbouring rows are swapped in every other
+// group of eight and the second k-group is 64 bytes further than its rows take, so that all ways of filling a plane
+// (eight lanes = four rows of both k-groups, every row or every other row of one) write 128 distinct bytes: no bank
+// conflicts by the counter.
+//
+// Non-finite values: an infinity (or a magnitude that rounds to one in bfloat16) makes x - h, and with it every
+// result it reaches, NaN.  A workgroup that finds a non-finite result computes its tile again with float32 matrix
+// instructions, which treat infinities and NaN as IEEE arithmetic does.
+#include <cstdio>
+
+#include "common.h"
+
+namespace cofree {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+
+constexpr int SBK = 16;  // k per step: one matrix instruction deep
+
+struct SplitK {
+  const float* A1;
+  const float* A2;
+  const float* B1;
+  const float* B2;
+  int64_t lda1, lda2, ldb1, ldb2;
+  int64_t K1, K2;  // lengths of the two k-segments (K2 = 0: one); weight gradients: K1 = all nodes
+  float* C;
+  int64_t ldc;
+  int64_t M;
+  int32_t N;
+  int64_t k_chunk;         // weight gradients: nodes per chunk
+  int64_t c_split_stride;  // weight gradients: floats between the chunks' partials
+  int32_t tiles_m, tiles_n;
+  int64_t n_groups;
+  int32_t n_split;     // weight gradients: columns n_split .. of the result come from B2 (0: all from B1)
+  float* colsum_part;  // weight gradients: [chunks][M] partial column sums of operand A, or null
+  const float* bias;
+  int32_t relu;
+  const float* row_scale;
+  const float* gate;
+  int64_t ldg;
+  int32_t accumulate, relu_last, gate_last;
+  float gate_scale;
+};
+
+template <int ROWS>
+struct Plane {
+  static constexpr int KG = ROWS * 16 + 64;  // bytes of a k-group
+  static constexpr int SIZE = 2 * KG;        // bytes of a plane (16 k)
+  static constexpr int BYTES = 3 * SIZE;     // the three planes of an operand
+};
+__device__ inline int plane_row(int row) { return (row ^ ((row >> 3) & 1)) * 16; }
+
+// x0, x1 -> their high, middle and low parts, packed (x0 in the low half of each dword)
+__device__ inline void split_pair(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l) {
+  h = pack_bf16x2(x0, x1);
+  const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
+  m = pack_bf16x2(r0, r1);
+  const float s0 = r0 - __uint_as_float(m << 16), s1 = r1 - __uint_as_float(m & 0xffff0000u);
+  l = pack_bf16x2(s0, s1);
+}
+
+// eight consecutive k of one row, split and written to the three planes at d
+template <int ROWS>
+__device__ inline void store_group(unsigned char* d, const float (&x)[8]) {
+  uint4 h, m, l;
+  split_pair(x[0], x[1], h.x, m.x, l.x);
+  split_pair(x[2], x[3], h.y, m.y, l.y);
+  split_pair(x[4], x[5], h.z, m.z, l.z);
+  split_pair(x[6], x[7], h.w, m.w, l.w);
+  *reinterpret_cast<uint4*>(d) = h;
+  *reinterpret_cast<uint4*>(d + Plane<ROWS>::SIZE) = m;
+  *reinterpret_cast<uint4*>(d + 2 * Plane<ROWS>::SIZE) = l;
+}
+
+// ---- operand movers: ROWS rows x 16 k of an operand from memory to registers to LDS ---------------------------
+// A thread's share is UNITS groups of eight consecutive k of one row.  Loads are unconditional vector loads at a
+// block-uniform base plus 32-bit offsets.  Rows past the matrix edge repeat its last row (they feed results that are
+// never stored); k past the end of the range are read inside it and become zero on the way to LDS.
+
+// k-contiguous source: thread t holds k-group t%2 of rows t/2 + 128 u.  The range has at least eight k: a group that
+// would cross its end is read eight from the end and moved into place (three select stages).
+template <int ROWS>
+struct SplitKContig {
+  static constexpr int UNITS = ROWS / 128;
+  struct Raw {
+    float4u x[UNITS][2];
+  };
+  const float* base;
+  uint32_t off[UNITS];
+  int kq, k_len;
+  __device__ void init(const float* P, int64_t ld, int64_t extent, int64_t i0, int64_t k_len_, int tid) {
+    base = P + i0 * ld;
+    kq = (tid & 1) * 8;
+    k_len = (int)k_len_;
+    const int64_t last = extent - 1 - i0;
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      const int64_t r = (tid >> 1) + 128 * u;
+      off[u] = (uint32_t)((r < last ? r : last) * ld);
+    }
+  }
+  __device__ void load(int k0, Raw& w) const {
+    const int k = k0 + kq < k_len - 8 ? k0 + kq : k_len - 8;
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      w.x[u][0] = *reinterpret_cast<const float4u*>(base + (off[u] + (uint32_t)k));
+      w.x[u][1] = *reinterpret_cast<const float4u*>(base + (off[u] + (uint32_t)k + 4));
+    }
+  }
+  __device__ void store(unsigned char* lds, int tid, int k0, int u, const Raw& w, float) const {
+    float e[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) e[c] = w.x[u][c >> 2][c & 3];
+    if (k0 + SBK > k_len) {  // uniform: the last step of a ragged range
+      const int sh = k0 + kq - (k_len - 8);  // how far the group was moved; eight and more: nothing of it exists
+      if (sh > 0) {
+#pragma unroll
+        for (int s = 4; s > 0; s >>= 1) {
+#pragma unroll
+          for (int c = 0; c < 8; ++c) e[c] = (sh & s) ? (c + s < 8 ? e[c + s < 8 ? c + s : 7] : 0.f) : e[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) e[c] = sh > 7 ? 0.f : e[c];
+      }
+    }
+    store_group<ROWS>(lds + (tid & 1) * Plane<ROWS>::KG + plane_row((tid >> 1) + 128 * u), e);
+  }
+  __device__ void add_rows(int, const Raw&, float (&)[2]) const {}
+};
+
+// k-major source (element (i, k) at P[k ld + i]): thread t holds UNITS consecutive columns of the eight k of group
+// t / 128 (the same for a whole wavefront, so rows are addressed with scalars), one or two elements per load.  A pair
+// that would cross the matrix edge is read one column further left; the matrix has at least UNITS columns.
+template <int ROWS>
+struct SplitKMajor {
+  static constexpr int UNITS = ROWS / 128, T = 128;  // T threads per k-group
+  struct Raw {
+    float x[8][UNITS];
+  };
+  const float* base;
+  int64_t ld;
+  uint32_t off;   // first column of the thread
+  int kq, k_len;  // kq: first k of the thread's group
+  bool moved;     // the thread's pair was moved left: its first column is the pair's second
+  __device__ void init(const float* P, int64_t ld_, int64_t extent, int64_t i0, int64_t k_len_, int tid) {
+    base = P;
+    ld = ld_;
+    kq = __builtin_amdgcn_readfirstlane((tid / T) * 8);
+    k_len = (int)k_len_;
+    const int64_t i = i0 + (tid % T) * UNITS;
+    const int64_t start = i < extent - UNITS ? i : extent - UNITS;
+    moved = UNITS == 2 && start < i;
+    off = (uint32_t)start;
+  }
+  __device__ void load(int k0, Raw& w) const {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int k = k0 + kq + c < k_len ? k0 + kq + c : k_len - 1;
+      const float* const row = base + k * ld;
+      if constexpr (UNITS == 2) {
+        typedef float float2u __attribute__((ext_vector_type(2), aligned(4)));
+        const float2u t = *reinterpret_cast<const float2u*>(row + off);
+        w.x[c][0] = t[0];
+        w.x[c][1] = t[1];
+      } else {
+        w.x[c][0] = row[off];
+      }
+    }
+  }
+  __device__ float value(int k0, int c, int u, const Raw& w) const {
+    const float v = moved ? w.x[c][UNITS - 1] : w.x[c][u];
+    return k0 + kq + c < k_len ? v : 0.f;
+  }
+  // sign: 1 or -1 on every element
+  __device__ void store(unsigned char* lds, int tid, int k0, int u, const Raw& w, float sign) const {
+    float e[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) e[c] = sign * value(k0, c, u, w);
+    store_group<ROWS>(lds + (tid / T) * Plane<ROWS>::KG + plane_row((tid % T) * UNITS + u), e);
+  }
+  // s[u] += the thread's eight k of its column u (weight gradients: column sums of operand A)
+  __device__ void add_rows(int k0, const Raw& w, float (&s)[2]) const {
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      float t = 0.f;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) t += value(k0, c, u, w);
+      s[u] += t;
+    }
+  }
+};
+
+// 16 k of a wavefront's RM x RN blocks: 6 RM RN matrix instructions.  The operand with fewer blocks stays in
+// registers, the other one streams; between(o) is called in front of the o-th of its blocks.
+template <int TM, int TN, int RM, int RN, typename F>
+__device__ inline void multiply_step(const unsigned char* as, const unsigned char* bs, floatx16 (&acc)[RM][RN],
+                                     F between) {
+  constexpr bool STREAM_A = RM > RN;
+  constexpr int RK = STREAM_A ? RN : RM, RS = STREAM_A ? RM : RN;  // kept, streamed
+  const unsigned char* const kp = STREAM_A ? bs : as;
+  const unsigned char* const sp = STREAM_A ? as : bs;
+  constexpr int KS = Plane<STREAM_A ? TN : TM>::SIZE, SS = Plane<STREAM_A ? TM : TN>::SIZE;
+  bf16x8 kept[3][RK], st[2][3];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+#pragma unroll
+    for (int m = 0; m < RK; ++m) kept[p][m] = *reinterpret_cast<const bf16x8*>(kp + p * KS + m * 512);
+    st[0][p] = *reinterpret_cast<const bf16x8*>(sp + p * SS);
+  }
+#pragma unroll
+  for (int o = 0; o < RS; ++o) {
+    if (o + 1 < RS) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) st[(o + 1) & 1][p] = *reinterpret_cast<const bf16x8*>(sp + p * SS + (o + 1) * 512);
+    }
+    between(o);
+    constexpr int PK[6] = {2, 0, 1, 1, 0, 0}, PS[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+      for (int m = 0; m < RK; ++m) {
+        floatx16& c = STREAM_A ? acc[o][m] : acc[m][o];
+        c = STREAM_A ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(st[o & 1][PS[q]], kept[PK[q]][m], c, 0, 0, 0)
+                     : __builtin_amdgcn_mfma_f32_32x32x16_bf16(kept[PK[q]][m], st[o & 1][PS[q]], c, 0, 0, 0);
+      }
+  }
+}
+
+// One k-range of length k_len >= 1.  csum: column sums of operand A (only where the caller wants them).
+//
+// LDS holds two steps, one barrier per step: while step t is multiplied, step t+1 is split and written to the other
+// half in between the matrix instructions (a wavefront's vector instructions issue while its matrix instructions
+// run), and step t+2 is requested from memory into the registers that this frees.
+//
+// FLIP (weight gradients: thousands of k in one sum, partial sums added over many chunks): the matrix instructions cut
+// off (towards minus infinity) what of a small product lies far below the running sum, which over 2.7k k of one sign
+// comes to 6e-8 of the result - little, but it does not average out over the chunks.  So the sign of the sum and of
+// operand B changes every FLIP_STEPS steps, and what is cut off cancels.
+constexpr int FLIP_STEPS = 16;
+template <int TM, int TN, int RM, int RN, bool FLIP, typename MA, typename MB>
+__device__ inline void run_split(const MA& ma, const MB& mb, int k_len, unsigned char* smem, int a_off, int b_off,
+                                 floatx16 (&acc)[RM][RN], int tid, bool colsum, float (&csum)[2]) {
+  constexpr int HALF = Plane<TM>::BYTES + Plane<TN>::BYTES;  // bytes of one step's operands
+  constexpr int RS = RM > RN ? RM : RN;
+  const int n = (k_len + SBK - 1) / SBK;
+  typename MA::Raw ra;
+  typename MB::Raw rb;
+  auto put = [&](int t, int u) {  // unit u of the thread's share of step t
+    unsigned char* const d = smem + (t & 1) * HALF;
+    const int k0 = t * SBK;
+    if (u < MA::UNITS) {
+      ma.store(d, tid, k0, u, ra, 1.f);
+      if (u == 0 && colsum) ma.add_rows(k0, ra, csum);
+    } else {
+      mb.store(d + Plane<TM>::BYTES, tid, k0, u - MA::UNITS, rb, FLIP && (t / FLIP_STEPS) % 2 ? -1.f : 1.f);
+    }
+  };
+  constexpr int UNITS = MA::UNITS + MB::UNITS;
+  ma.load(0, ra);
+  mb.load(0, rb);
+  __syncthreads();  // whoever used the LDS before is done
+#pragma unroll
+  for (int u = 0; u < UNITS; ++u) put(0, u);
+  if (n > 1) {
+    ma.load(SBK, ra);
+    mb.load(SBK, rb);
+  }
+  __syncthreads();
+  auto flip = [&]() {
+#pragma unroll
+    for (int m = 0; m < RM; ++m)
+#pragma unroll
+      for (int q = 0; q < RN; ++q)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[m][q][v] = -acc[m][q][v];
+  };
+#pragma nounroll
+  for (int t = 0; t + 1 < n; ++t) {
+    if (FLIP && t > 0 && t % FLIP_STEPS == 0) flip();
+    const unsigned char* const d = smem + (t & 1) * HALF;
+    multiply_step<TM, TN, RM, RN>(d + a_off, d + Plane<TM>::BYTES + b_off, acc, [&](int o) {
+#pragma unroll
+      for (int u = 0; u < UNITS; ++u)
+        if (u % RS == o) put(t + 1, u);
+      if (o == RS - 1) {
+        const int t2 = t + 2 < n ? t + 2 : n - 1;
+        ma.load(t2 * SBK, ra);
+        mb.load(t2 * SBK, rb);
+      }
+    });
+    __syncthreads();
+  }
+  if (FLIP && n > 1 && (n - 1) % FLIP_STEPS == 0) flip();
+  const unsigned char* const d = smem + ((n - 1) & 1) * HALF;
+  multiply_step<TM, TN, RM, RN>(d + a_off, d + Plane<TM>::BYTES + b_off, acc, [](int) {});
+  if (FLIP && ((n - 1) / FLIP_STEPS) % 2) flip();
+}
+
+// One 32x32 block of the result over the same range on the float32 matrix instructions, operands straight from
+// memory (tiles with non-finite results).  Element (i, k) of an operand is at P[i si + k sk]; i, j: this lane's row of
+// each, inside the matrix.
+__device__ inline void run_plain(const float* A, int64_t sia, int64_t ska, const float* B, int64_t sib, int64_t skb,
+                                 int64_t i, int64_t j, int64_t k_len, int g, floatx16& acc) {
+#pragma nounroll
+  for (int64_t k0 = 0; k0 < k_len; k0 += 2) {
+    const bool in = k0 + g < k_len;
+    const int64_t k = in ? k0 + g : k_len - 1;
+    const float a = A[i * sia + k * ska], b = B[j * sib + k * skb];
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? a : 0.f, in ? b : 0.f, acc, 0, 0, 0);
+  }
+}
+
+// A_KMAJOR: weight gradient C = A^T B over graph nodes, float32 partials per chunk; else C = sum of segments A op(B).
+template <bool A_KMAJOR, bool B_KMAJOR, int RM, int RN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 ? 2 : 3))) void gemm_split_kernel(
+    const SplitK p) {
+  constexpr int TM = 64 * RM, TN = 64 * RN;
+  constexpr int STAGE_LD = 32 * RN + 4, STAGE_WAVE = 32 * STAGE_LD;  // result staging: floats
+  constexpr int OPERANDS = 2 * (Plane<TM>::BYTES + Plane<TN>::BYTES);
+  constexpr int STAGING = A_KMAJOR ? 0 : 4 * STAGE_WAVE * 4;
+  __shared__ __attribute__((aligned(128))) unsigned char smem[OPERANDS > STAGING ? OPERANDS : STAGING];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int g = lane >> 5, r = lane & 31;
+  // XCD-aware linear id -> (group, member): the tiles that share an operand panel are adjacent on one XCD
+  int64_t i0, j0, z = 0;
+  {
+    const int64_t L = blockIdx.x;
+    const int64_t per_group = A_KMAJOR ? p.tiles_m * p.tiles_n : p.tiles_n;
+    const int64_t group = (L / (8 * per_group)) * 8 + (L & 7);
+    const int64_t member = (L >> 3) % per_group;
+    if (group >= p.n_groups) return;  // padding of the last group octet (uniform over the block)
+    if constexpr (A_KMAJOR) {
+      z = group;
+      i0 = (member / p.tiles_n) * TM;
+      j0 = (member % p.tiles_n) * TN;
+    } else {
+      i0 = group * TM;
+      j0 = member * TN;
+    }
+  }
+  const int a_off = g * Plane<TM>::KG + wm * RM * 512 + plane_row(r);
+  const int b_off = g * Plane<TN>::KG + wn * RN * 512 + plane_row(r);
+  floatx16 acc[RM][RN];
+#pragma unroll
+  for (int m = 0; m < RM; ++m)
+#pragma unroll
+    for (int n = 0; n < RN; ++n)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[m][n][v] = 0.f;
+
+  // weight gradients: this block's chunk of nodes and its matrix of operand B
+  int64_t k_beg = 0, k_len = 0;
+  const float* Bw = p.B1;
+  int64_t ldbw = p.ldb1, extent_b = p.N, jw = j0;
+  if constexpr (A_KMAJOR) {
+    k_beg = z * p.k_chunk;
+    const int64_t k_end = k_beg + p.k_chunk < p.K1 ? k_beg + p.k_chunk : p.K1;
+    k_len = k_end > k_beg ? k_end - k_beg : 0;
+    if (p.n_split > 0) extent_b = p.n_split;
+    if (p.n_split > 0 && j0 >= p.n_split) {  // a column tile of the second matrix
+      Bw = p.B2;
+      ldbw = p.ldb2;
+      extent_b = p.N - p.n_split;
+      jw = j0 - p.n_split;
+    }
+  }
+  const int n_seg = !A_KMAJOR && p.K2 > 0 ? 2 : 1;
+  float csum[2] = {0.f, 0.f};
+  if constexpr (A_KMAJOR) {
+    if (k_len > 0) {
+      SplitKMajor<TM> ma;
+      SplitKMajor<TN> mb;
+      ma.init(p.A1 + k_beg * p.lda1, p.lda1, p.M, i0, k_len, tid);
+      mb.init(Bw + k_beg * ldbw, ldbw, extent_b, jw, k_len, tid);
+      run_split<TM, TN, RM, RN, true>(ma, mb, (int)k_len, smem, a_off, b_off, acc, tid, p.colsum_part != nullptr && j0 == 0,
+                                csum);
+    }
+  } else {
+    // one loop body for both segments (two inlined copies would each claim their own accumulators)
+#pragma nounroll
+    for (int seg = 0; seg < n_seg; ++seg) {
+      const int k_seg = (int)(seg ? p.K2 : p.K1);
+      SplitKContig<TM> ma;
+      ma.init(seg ? p.A2 : p.A1, seg ? p.lda2 : p.lda1, p.M, i0, k_seg, tid);
+      if constexpr (B_KMAJOR) {
+        SplitKMajor<TN> mb;
+        mb.init(seg ? p.B2 : p.B1, seg ? p.ldb2 : p.ldb1, p.N, j0, k_seg, tid);
+        run_split<TM, TN, RM, RN, false>(ma, mb, k_seg, smem, a_off, b_off, acc, tid, false, csum);
+      } else {
+        SplitKContig<TN> mb;
+        mb.init(seg ? p.B2 : p.B1, seg ? p.ldb2 : p.ldb1, p.N, j0, k_seg, tid);
+        run_split<TM, TN, RM, RN, false>(ma, mb, k_seg, smem, a_off, b_off, acc, tid, false, csum);
+      }
+    }
+  }
+  bool tile_done = false;  // uniform over the block
+  {
+    float bad = 0.f;  // stays zero while every result is finite
+#pragma unroll
+    for (int m = 0; m < RM; ++m)
+#pragma unroll
+      for (int n = 0; n < RN; ++n)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) bad = fmaf(acc[m][n][v], 0.f, bad);
+    if (__syncthreads_or(!(bad == 0.f))) {
+#pragma nounroll
+      for (int blk = 0; blk < RM * RN; ++blk) {
+        const int64_t ib = i0 + (wm * RM + blk / RN) * 32, jb = (wn * RN + blk % RN) * 32;
+        const int64_t ia = ib + r < p.M ? ib + r : p.M - 1, ja = jw + jb + r < extent_b ? jw + jb + r : extent_b - 1;
+        floatx16 c;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) c[v] = 0.f;
+        if constexpr (A_KMAJOR) {
+          run_plain(p.A1 + k_beg * p.lda1, 1, p.lda1, Bw + k_beg * ldbw, 1, ldbw, ia, ja, k_len, g, c);
+        } else {
+#pragma nounroll
+          for (int seg = 0; seg < n_seg; ++seg) {
+            const int64_t ldb = seg ? p.ldb2 : p.ldb1;
+            run_plain(seg ? p.A2 : p.A1, seg ? p.lda2 : p.lda1, 1, seg ? p.B2 : p.B1, B_KMAJOR ? 1 : ldb,
+                      B_KMAJOR ? ldb : 1, ia, ja, seg ? p.K2 : p.K1, g, c);
+          }
+        }
+        const int64_t j = j0 + jb + r;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int64_t i = ib + 8 * (v >> 2) + 4 * g + (v & 3);
+          if (i >= p.M || j >= p.N) continue;
+          float* dst = p.C + z * p.c_split_stride + i * p.ldc + j;
+          float y = c[v];
+          if constexpr (!A_KMAJOR) {
+            if (p.bias) y += p.bias[j];
+            if (p.relu) y = fmaxf(y, 0.f);
+            if (p.row_scale) y *= p.row_scale[i];
+            const bool shut = p.gate && !(p.gate[i * p.ldg + j] > 0.f);
+            if (!p.gate_last) y = shut ? 0.f : y * p.gate_scale;
+            if (p.accumulate) y += *dst;
+            if (p.gate_last) y = shut ? 0.f : y * p.gate_scale;
+            if (p.relu_last) y = fmaxf(y, 0.f);
+          }
+          *dst = y;
+        }
+      }
+      if (!A_KMAJOR) return;
+      tile_done = true;
+    }
+  }
+
+  // accumulator register v of lane (g, r) is element [8 (v/4) + 4 g + v%4][r] of its 32x32 block
+  if constexpr (A_KMAJOR) {
+    float* Cz = p.C + z * p.c_split_stride;
+    if (!tile_done) {
+#pragma unroll
+      for (int m = 0; m < RM; ++m) {
+#pragma unroll
+        for (int n = 0; n < RN; ++n) {
+          const int64_t j = j0 + wn * (32 * RN) + n * 32 + r;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const int64_t i = i0 + wm * (32 * RM) + m * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
+            if (j < p.N && i < p.M) Cz[i * p.ldc + j] = acc[m][n][v];
+          }
+        }
+      }
+    }
+    if (p.colsum_part != nullptr && j0 == 0) {
+      // the two k-groups of a column are added in order through LDS
+      using MA = SplitKMajor<TM>;
+      float* const red = reinterpret_cast<float*>(smem);
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < MA::UNITS; ++u) red[(tid / MA::T) * TM + (tid % MA::T) * MA::UNITS + u] = csum[u];
+      __syncthreads();
+      if (tid < TM && i0 + tid < p.M) {
+        p.colsum_part[z * p.M + i0 + tid] = red[tid] + red[TM + tid];
+      }
+    }
+  } else {
+    // Each wavefront passes its result through LDS in 32-row blocks, after which a lane holds four consecutive
+    // columns of one row: gate and accumulate operands are read, and the result is written, 16 bytes at a time.
+    // Those operands and the row scales do not depend on the product, so they are requested for four passes at a
+    // time, unconditionally at clamped addresses, the first four of a block before its staging barriers.
+    constexpr int LPR = 8 * RN;       // lanes per staged row
+    constexpr int RPP = 64 / LPR;     // rows per pass
+    constexpr int PASSES = 32 / RPP;  // passes per 32-row block
+    float* const st = reinterpret_cast<float*>(smem) + wave * STAGE_WAVE;
+    const int er = lane / LPR, ec = (lane % LPR) * 4;
+    const int64_t jv = j0 + wn * (32 * RN) + ec;
+    const bool wide_lane = jv + 4 <= p.N;   // the lane's four columns all exist
+    const int64_t jl = wide_lane ? jv : 0;  // where its 16-byte operand loads go (in range: N >= 4)
+    const bool extras = p.gate || p.accumulate || p.row_scale;  // uniform over the launch
+    struct Extra {
+      float4u g, c;
+      float rs;
+    };
+    auto request = [&](int m, int s, Extra& e) {
+      int64_t il = i0 + wm * (32 * RM) + m * 32 + s * RPP + er;
+      if (il > p.M - 1) il = p.M - 1;
+      e.g = float4u{1.f, 1.f, 1.f, 1.f};
+      e.c = float4u{0.f, 0.f, 0.f, 0.f};
+      e.rs = 1.f;
+      if (p.gate) e.g = *reinterpret_cast<const float4u*>(p.gate + il * p.ldg + jl);
+      if (p.accumulate) e.c = *reinterpret_cast<const float4u*>(p.C + il * p.ldc + jl);
+      if (p.row_scale) e.rs = p.row_scale[il];
+    };
+    auto pass = [&](int m, int s, bool have, const Extra& e) {
+      const int row = s * RPP + er;
+      const int64_t i = i0 + wm * (32 * RM) + m * 32 + row;
+      if (i < p.M && jv < p.N) {
+        const float4 t = *reinterpret_cast<const float4*>(st + row * STAGE_LD + ec);
+        float x[4] = {t.x, t.y, t.z, t.w};
+        float* dst = p.C + i * p.ldc + jv;
+        if (wide_lane) {
+          if (have) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              float y = x[c] * e.rs;
+              const bool shut = !(e.g[c] > 0.f);
+              if (!p.gate_last) y = shut ? 0.f : y * p.gate_scale;
+              y += e.c[c];
+              if (p.gate_last) y = shut ? 0.f : y * p.gate_scale;
+              x[c] = y;
+            }
+          }
+          if (p.relu_last) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[c] = fmaxf(x[c], 0.f);
+          }
+          float4u out;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) out[c] = x[c];
+          *reinterpret_cast<float4u*>(dst) = out;
+        } else {
+          const float sc = p.row_scale ? p.row_scale[i] : 1.f;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            if (jv + c < p.N) {
+              float y = x[c] * sc;
+              const bool shut = p.gate && !(p.gate[i * p.ldg + jv + c] > 0.f);
+              if (!p.gate_last) y = shut ? 0.f : y * p.gate_scale;
+              if (p.accumulate) y += dst[c];
+              if (p.gate_last) y = shut ? 0.f : y * p.gate_scale;
+              if (p.relu_last) y = fmaxf(y, 0.f);
+              dst[c] = y;
+            }
+          }
+        }
+      }
+    };
+#pragma unroll
+    for (int m = 0; m < RM; ++m) {
+      Extra e[4] = {};
+      if (extras) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) request(m, q, e[q]);
+      }
+      __syncthreads();  // operand planes (m = 0) / previous block no longer read
+#pragma unroll
+      for (int n = 0; n < RN; ++n) {
+        const int64_t j = j0 + wn * (32 * RN) + n * 32 + r;
+        const float bj = (p.bias && j < p.N) ? p.bias[j] : 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          float x = acc[m][n][v] + bj;
+          if (p.relu) x = fmaxf(x, 0.f);
+          st[(8 * (v >> 2) + 4 * g + (v & 3)) * STAGE_LD + n * 32 + r] = x;
+        }
+      }
+      __syncthreads();
+      if (extras) {
+#pragma nounroll
+        for (int q0 = 0; q0 < PASSES; q0 += 4) {
+          if (q0 > 0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) request(m, q0 + q, e[q]);
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q) pass(m, q0 + q, true, e[q]);
+        }
+      } else {
+#pragma nounroll
+        for (int q0 = 0; q0 < PASSES; q0 += 4)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) pass(m, q0 + q, false, e[0]);
+      }
+    }
+  }
+}
+
+// 32-bit element offsets inside a tile: 256 rows of a k-contiguous operand, 32 k-rows of a k-major one
+static bool split_strides_ok(int64_t lda, int64_t ldb) { return lda < ((int64_t)1 << 22) && ldb < ((int64_t)1 << 22); }
+
+bool gemm_split_fits(const GemmArgs& a) {
+  return a.dtype == COFREE_F32 && a.N > 64 && a.K1 >= 8 && (a.K2 == 0 || a.K2 >= 8) && split_strides_ok(a.lda1, a.ldb) &&
+         (a.K2 == 0 || split_strides_ok(a.lda2, a.B2 ? a.ldb2 : 0));
+}
+
+int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
+  SplitK p{};
+  p.A1 = (const float*)a.A1;
+  p.lda1 = a.lda1;
+  p.K1 = a.K1;
+  p.A2 = (const float*)a.A2;
+  p.lda2 = a.lda2;
+  p.K2 = a.K2;
+  p.B1 = a.B;
+  p.ldb1 = a.ldb;
+  p.B2 = a.B2 ? a.B2 : a.B + (a.b_kmajor ? (int64_t)a.K1 * a.ldb : (int64_t)a.K1);
+  p.ldb2 = a.B2 ? a.ldb2 : a.ldb;
+  p.C = (float*)a.C;
+  p.ldc = a.ldc;
+  p.M = a.M;
+  p.N = a.N;
+  p.bias = a.bias;
+  p.relu = a.relu;
+  p.row_scale = a.row_scale;
+  p.gate = (const float*)a.gate;
+  p.ldg = a.ldg;
+  p.accumulate = a.accumulate;
+  p.relu_last = a.relu_last;
+  p.gate_last = a.gate_last;
+  p.gate_scale = a.gate ? a.gate_scale : 1.f;
+  const int64_t K = (int64_t)a.K1 + a.K2;
+  // 128x256 tiles where they fit the columns as well as 128x128 ones and give every CU its two workgroups (half
+  // the reads of operand A; the rates are equal within 4 %), else 128x128 (20k x 256 x 256: 27.5 against 30.9 us)
+  p.n_groups = (a.M + 127) / 128;
+  const int32_t tiles128 = (a.N + 127) / 128;
+  const bool wide = tiles128 % 2 == 0 && p.n_groups * (tiles128 / 2) >= 512;
+  p.tiles_n = wide ? tiles128 / 2 : tiles128;
+  const int64_t blocks = ((p.n_groups + 7) / 8) * 8 * p.tiles_n;
+  COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "dense: grid too large");
+  char pname[96];
+  snprintf(pname, sizeof(pname), "gemm_split_kernel<false,%s,2,%d> N=%d K=%d", a.b_kmajor ? "true" : "false", wide ? 4 : 2,
+           (int)a.N, (int)K);
+  ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + (double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1)),
+                 2.0 * (double)a.M * a.N * (double)K);
+  const dim3 grid((unsigned)blocks);
+  if (wide) {
+    if (a.b_kmajor) gemm_split_kernel<false, true, 2, 4><<<grid, 256, 0, stream>>>(p);
+    else gemm_split_kernel<false, false, 2, 4><<<grid, 256, 0, stream>>>(p);
+  } else {
+    if (a.b_kmajor) gemm_split_kernel<false, true, 2, 2><<<grid, 256, 0, stream>>>(p);
+    else gemm_split_kernel<false, false, 2, 2><<<grid, 256, 0, stream>>>(p);
+  }
+  COFREE_HIP_CHECK(hipGetLastError());
+  return COFREE_OK;
+}
+
+bool wgrad_split_fits(int32_t N1, int32_t N2a, int32_t N2b, int64_t lda, int64_t ldb, int64_t ldb2) {
+  return N1 > 64 && N2a > 64 && (N2b == 0 || N2b >= 4) && split_strides_ok(lda, ldb) && split_strides_ok(0, ldb2);
+}
+
+int32_t launch_wgrad_split(const float* A, int64_t lda, int32_t N1, const float* B, int64_t ldb, int32_t N2a, int64_t M,
+                           float* C, int64_t ldc, int32_t accumulate, float* workspace, hipStream_t stream,
+                           float* colsum_out, const float* B2, int64_t ldb2, int32_t N2b) {
+  const int32_t N2 = N2a + (B2 ? N2b : 0);
+  const bool tall = ((N1 + 127) / 128) % 2 == 0;  // 256x128 tiles where they fit the rows as well as 128x128 ones
+  const int32_t S = wgrad_splits(N1, N2, M, tall ? WGRAD_RESIDENT_SPLIT_TALL : WGRAD_RESIDENT_SPLIT, tall ? 256 : 128);
+  SplitK p{};
+  p.A1 = A;
+  p.lda1 = lda;
+  p.B1 = B;
+  p.ldb1 = ldb;
+  p.B2 = B2;
+  p.ldb2 = ldb2;
+  p.n_split = B2 ? N2a : 0;
+  p.K1 = M;
+  p.C = workspace;
+  p.ldc = N2;
+  p.M = N1;
+  p.N = N2;
+  int64_t chunk = (M + S - 1) / S;
+  p.k_chunk = ((chunk + SBK - 1) / SBK) * SBK;
+  if (p.k_chunk < SBK) p.k_chunk = SBK;
+  p.c_split_stride = (int64_t)N1 * N2;
+  p.tiles_m = (N1 + (tall ? 255 : 127)) / (tall ? 256 : 128);
+  p.tiles_n = (N2 + 127) / 128;
+  p.n_groups = S;
+  float* colsum_part = workspace + (size_t)S * N1 * N2;
+  p.colsum_part = colsum_out ? colsum_part : nullptr;
+  const int64_t blocks = (int64_t)((S + 7) / 8) * 8 * p.tiles_m * p.tiles_n;
+  COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "wgrad: grid too large");
+  {
+    char pname[96];
+    snprintf(pname, sizeof(pname), "gemm_split_kernel<true,true,%d,2> N=%dx%d", tall ? 4 : 2, (int)N1, (int)N2);
+    ProfScope prof(pname, stream, 4.0 * ((double)M * N1 + (double)M * N2 + (double)N1 * N2), 2.0 * (double)M * N1 * N2);
+    if (tall) gemm_split_kernel<true, true, 4, 2><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
+    else gemm_split_kernel<true, true, 2, 2><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
+  }
+  COFREE_HIP_CHECK(hipGetLastError());
+  COFREE_TRY(launch_split_reduce(workspace, p.c_split_stride, S, C, ldc, N1, N2, accumulate, stream));
+  if (colsum_out) COFREE_TRY(launch_split_reduce(colsum_part, N1, S, colsum_out, N1, 1, N1, accumulate, stream));
+  return COFREE_OK;
+}
+
+}  // namespace cofree

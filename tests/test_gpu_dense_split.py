@@ -1,0 +1,89 @@
+"""Float32 products on the bfloat16 matrix cores (three-way split of every operand) against float64, at the edges
+of their tiles and steps, with infinities, and as weight and input gradients of a layer."""
+import numpy as np
+import pytest
+
+from oracle import dropedge as o_dropedge
+from oracle import layers as o_layers
+from oracle import partition as o_partition
+from paper_2308_03209_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2308_03209_amd import binding as B
+    wl = inputs.WORKLOADS[0]
+    src, dst = inputs.workload_graph(wl)
+    return dict(B=B, torch=torch, P=B.build_partition(wl.n_nodes, src, dst, 4, 0, inputs.SEED_CUT),
+                O=o_partition.build_partition(wl.n_nodes, src, dst, 4, 0, inputs.SEED_CUT))
+
+
+def assert_rounding(got, ref, mag, K, what):
+    """Every element within the bound of a float32 sum of K products, K 2^-24 of the sum of magnitudes, plus the
+    2^-23 of each product that the split leaves out and the result's own rounding."""
+    err = np.abs(got.astype(np.float64) - ref)
+    bound = (K + 4.0) * 2.0 ** -24 * mag
+    assert np.all(err <= bound), f"{what}: error {np.max(err / np.maximum(bound, 1e-300)):.2f} of its bound"
+
+
+# tiles are 128 x 128 or (from 512 of them) 128 x 256, k steps 16 with groups of 8
+@pytest.mark.parametrize("M,N,K", [(1, 65, 8), (127, 128, 9), (129, 129, 15), (300, 255, 16), (128, 256, 17), (130, 300, 31),
+                                   (257, 100, 33), (64, 384, 602), (65_600, 256, 24), (33_000, 512, 41)])
+def test_product_edges(env, M, N, K):
+    B, torch = env["B"], env["torch"]
+    print(f"[case] split product M={M} N={N} K={K}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn(M, K, generator=gen, device="cuda") * torch.exp2(torch.randint(-20, 21, (M, 1), generator=gen, device="cuda").float())
+    W, b = torch.randn(N, K, generator=gen, device="cuda"), torch.zeros(N, device="cuda")
+    C = torch.full((M, N), float("nan"), device="cuda")
+    B.dense_nt_f32(A, W, b, C, False)
+    ref, mag = A.double() @ W.double().T, A.double().abs() @ W.double().abs().T
+    assert_rounding(C.cpu().numpy(), ref.cpu().numpy(), mag.cpu().numpy(), K, "product")
+
+
+def test_non_finite_operands_follow_float32_arithmetic(env):
+    """An infinity or a value next to the largest float32 has no finite split: its tile is computed in plain float32."""
+    B, torch = env["B"], env["torch"]
+    rng = np.random.default_rng(5)
+    A, W = rng.standard_normal((200, 40)).astype(np.float32), (0.1 + rng.random((130, 40))).astype(np.float32)
+    A[7, 3], A[9, 5] = np.inf, np.nan
+    A[150], A[151, :] = 0.0, 0.0
+    A[150, 11] = np.float32(3.4e38)
+    A[151, 39] = -np.inf
+    C = torch.empty(200, 130, device="cuda")
+    B.dense_nt_f32(torch.from_numpy(A).cuda(), torch.from_numpy(W).cuda(), torch.zeros(130, device="cuda"), C, False)
+    got = C.cpu().numpy()
+    assert np.all(np.isposinf(got[7])) and np.all(np.isnan(got[9])) and np.all(np.isneginf(got[151]))
+    np.testing.assert_array_equal(got[150], np.float32(3.4e38) * W[:, 11])
+    rest = np.setdiff1d(np.arange(200), [7, 9, 150, 151])
+    a, w = A[rest].astype(np.float64), W.astype(np.float64)
+    assert_rounding(got[rest], a @ w.T, np.abs(a) @ np.abs(w).T, 40, "rows beside non-finite ones")
+
+
+@pytest.mark.parametrize("d_in,d_out", [(65, 66), (66, 129), (127, 128), (128, 200), (100, 256), (257, 300), (384, 512)])
+def test_weight_and_input_gradients(env, d_in, d_out):
+    """Backward of an aggregate-first GCN layer without activation: dW = dH^T A with any saved A, db = column sums,
+    dH_in = Ahat (dH W).  The node count is no multiple of the k step."""
+    B, torch, P, O = env["B"], env["torch"], env["P"], env["O"]
+    print(f"[case] split gradients {d_in} -> {d_out}", flush=True)
+    n = P.num_nodes
+    assert n % 16 != 0
+    gen = torch.Generator(device="cuda").manual_seed(d_in)
+    A, dH = torch.randn(n, d_in, generator=gen, device="cuda"), torch.randn(n, d_out, generator=gen, device="cuda")
+    W = torch.randn(d_out, d_in, generator=gen, device="cuda")
+    d = B.layer_desc(B.GCN, d_in, 0, d_out)
+    ws = torch.empty(B.layer_workspace_bytes(d, n, True), dtype=torch.uint8, device="cuda")
+    g = {"W": torch.full_like(W, float("nan")), "bW": torch.full((d_out,), float("nan"), device="cuda")}
+    dX = torch.full((n, d_in), float("nan"), device="cuda")
+    B.layer_bwd(P, None, 0, d, A, dH, {"W": W, "bW": torch.zeros(d_out, device="cuda")}, {"A": A}, dH, dX, g, False, ws)
+    a, h, w = (x.cpu().numpy().astype(np.float64) for x in (A, dH, W))
+    assert_rounding(g["W"].cpu().numpy(), h.T @ a, np.abs(h).T @ np.abs(a), n, "dW")
+    assert_rounding(g["bW"].cpu().numpy(), h.sum(0), np.abs(h).sum(0), n, "db")
+    full = o_dropedge.full_graph(O)
+    ref, mag = o_layers.gcn_aggregate(full, h @ w), o_layers.gcn_aggregate(full, np.abs(h) @ np.abs(w))
+    # on top of the product: three roundings of scales and a sum over at most max-degree neighbours
+    assert_rounding(dX.cpu().numpy(), ref, mag, d_out + 4 + int(np.max(np.diff(O["rowptr"]))), "dH_in")
