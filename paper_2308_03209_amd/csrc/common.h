@@ -118,9 +118,9 @@ struct DeviceGraph {
   const float* s_gcn_norm = nullptr;        // [n]  gcn_norm[order[i]]
   int64_t n = 0;
   int64_t nnz = 0;
-  // `order` starts with the hub rows: its first n_hub rows have at least AGG_HUB_MIN neighbours, nnz_hub
-  // adjacency entries in all
-  int64_t n_hub = 0, nnz_hub = 0;
+  // `order` starts with the longest rows: its first n_hub rows have at least AGG_HUB_MIN neighbours (nnz_hub adjacency
+  // entries in all), the first n_block at least AGG_BLOCK_MIN, the first n_wave at least AGG_WAVE_MIN
+  int64_t n_hub = 0, nnz_hub = 0, n_block = 0, n_wave = 0;
 };
 
 // Rows of at least AGG_HUB_MIN neighbours are split over the wavefronts of a whole workgroup (hub rows: the
@@ -129,11 +129,18 @@ struct DeviceGraph {
 // million-row graph (0.4-0.5 ms), below that the descending-degree order of the launches hides it.
 // AGG_ENTRY_SCALE_MIN_NODES: from this many nodes on (a per-node vector of 2 MB, half of one XCD's L2) the
 // per-source factors of an aggregation are read per adjacency entry instead of gathered per neighbour.
-// AGG_LONG_MIN: graphs of at least this average degree spread a row's neighbours over the lane groups of a
-// wavefront; below it a row gets one lane group.
+// AGG_LONG_MIN: graphs of at least this average degree give every row a wavefront.
+// AGG_BLOCK_MIN, AGG_WAVE_MIN: rows that the row kernel gives to a workgroup / a wavefront (measured in spmm.hip).
 constexpr int64_t AGG_HUB_MIN = 4096, AGG_LONG_MIN = 16, AGG_ENTRY_SCALE_MIN_NODES = 1 << 19;
+constexpr int64_t AGG_BLOCK_MIN = 128, AGG_WAVE_MIN = 32;
 struct DegreeBuckets {
-  int64_t n_hub = 0, nnz_hub = 0;
+  int64_t n_hub = 0, nnz_hub = 0, n_block = 0, n_wave = 0;
+  void attach(DeviceGraph* g) const {
+    g->n_hub = n_hub;
+    g->nnz_hub = nnz_hub;
+    g->n_block = n_block;
+    g->n_wave = n_wave;
+  }
 };
 
 // device storage of the processing-order copy (see DeviceGraph)
@@ -199,8 +206,7 @@ struct cofree_partition {
     d_slots.attach(&g);
     g.n = n_nodes;
     g.nnz = nnz;
-    g.n_hub = buckets.n_hub;
-    g.nnz_hub = buckets.nnz_hub;
+    buckets.attach(&g);
     return g;
   }
 };

@@ -142,27 +142,30 @@ __global__ __launch_bounds__(256) void order_keys_kernel(const int64_t* __restri
   key[v] = (uint32_t)deg[v];
   row[v] = (int32_t)v;
 }
-// out[0], out[1] += number of rows with deg >= hub_min and their adjacency entries (out zeroed beforehand;
-// integer sums, so the order in which the workgroups add their counts does not matter)
+// out[0 .. 3] += number of rows of at least AGG_HUB_MIN neighbours, their adjacency entries, and the numbers of rows of
+// at least AGG_BLOCK_MIN and AGG_WAVE_MIN (out zeroed beforehand; integer sums, so the order in which the workgroups
+// add their counts does not matter)
 __global__ __launch_bounds__(256) void degree_buckets_kernel(const int64_t* __restrict__ deg, int64_t n,
-                                                             int64_t hub_min, unsigned long long* __restrict__ out) {
-  __shared__ unsigned long long s[2][256];
-  unsigned long long c0 = 0, c1 = 0;
+                                                             unsigned long long* __restrict__ out) {
+  __shared__ unsigned long long s[4][256];
+  unsigned long long c[4] = {0, 0, 0, 0};
   for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (int64_t)gridDim.x * 256) {
     const int64_t d = deg[v];
-    if (d >= hub_min) c0 += 1, c1 += (unsigned long long)d;
+    if (d >= AGG_HUB_MIN) c[0] += 1, c[1] += (unsigned long long)d;
+    if (d >= AGG_BLOCK_MIN) c[2] += 1;
+    if (d >= AGG_WAVE_MIN) c[3] += 1;
   }
-  s[0][threadIdx.x] = c0;
-  s[1][threadIdx.x] = c1;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) s[q][threadIdx.x] = c[q];
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) {
-      s[0][threadIdx.x] += s[0][threadIdx.x + o];
-      s[1][threadIdx.x] += s[1][threadIdx.x + o];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q][threadIdx.x] += s[q][threadIdx.x + o];
     }
     __syncthreads();
   }
-  if (threadIdx.x < 2 && s[threadIdx.x][0] != 0) atomicAdd(&out[threadIdx.x], s[threadIdx.x][0]);
+  if (threadIdx.x < 4 && s[threadIdx.x][0] != 0) atomicAdd(&out[threadIdx.x], s[threadIdx.x][0]);
 }
 
 // (3) kept neighbour ids of every row, in order
@@ -329,7 +332,7 @@ static int32_t build_masks(const cofree_partition* P, int32_t K, double p_drop, 
   size_t sort_tmp_bytes = 0;
   COFREE_TRY(dev_alloc(&d_deg, (size_t)N));
   int32_t rc = dev_alloc(&d_sums, (size_t)n_chunks + 1);
-  if (rc == COFREE_OK) rc = dev_alloc(&d_buckets, 2);
+  if (rc == COFREE_OK) rc = dev_alloc(&d_buckets, 4);
   if (rc == COFREE_OK) rc = dev_alloc(&d_key, (size_t)N);
   if (rc == COFREE_OK) rc = dev_alloc(&d_key_sorted, (size_t)N);
   if (rc == COFREE_OK) rc = dev_alloc(&d_row, (size_t)N);
@@ -358,20 +361,22 @@ static int32_t build_masks(const cofree_partition* P, int32_t K, double p_drop, 
       scan_sums_kernel<<<1, 256, 0, stream>>>(d_sums, n_chunks, d.rowptr + N);  // total -> rowptr[N]
       scan_chunks_kernel<<<dim3((unsigned)n_chunks), 256, 0, stream>>>(d_deg, N, d_sums, d.rowptr);
       order_keys_kernel<<<dim3((unsigned)((N + 255) / 256)), 256, 0, stream>>>(d_deg, N, d_key, d_row);
-      e = hipMemsetAsync(d_buckets, 0, 2 * sizeof(int64_t), stream);
+      e = hipMemsetAsync(d_buckets, 0, 4 * sizeof(int64_t), stream);
       degree_buckets_kernel<<<dim3((unsigned)std::min<int64_t>((N + 255) / 256, 1024)), 256, 0, stream>>>(
-          d_deg, N, AGG_HUB_MIN, (unsigned long long*)d_buckets);
+          d_deg, N, (unsigned long long*)d_buckets);
       if (e == hipSuccess) e = hipGetLastError();
       if (e == hipSuccess)
         e = rocprim::radix_sort_pairs_desc(d_sort_tmp, sort_tmp_bytes, d_key, d_key_sorted, d_row, d.order, (size_t)N,
                                            0, 32, stream);
-      int64_t hb[2] = {0, 0};
+      int64_t hb[4] = {0, 0, 0, 0};
       if (e == hipSuccess)
         e = hipMemcpyAsync(&nnz, d.rowptr + N, sizeof(int64_t), hipMemcpyDeviceToHost, stream);
       if (e == hipSuccess) e = hipMemcpyAsync(hb, d_buckets, sizeof(hb), hipMemcpyDeviceToHost, stream);
       if (e == hipSuccess) e = hipStreamSynchronize(stream);
       d.buckets.n_hub = hb[0];
       d.buckets.nnz_hub = hb[1];
+      d.buckets.n_block = hb[2];
+      d.buckets.n_wave = hb[3];
     } else {
       const int64_t zero = 0;
       e = hipMemcpy(d.rowptr, &zero, sizeof(int64_t), hipMemcpyHostToDevice);

@@ -345,6 +345,8 @@ static int32_t to_device(cofree_partition* P) {
     for (int64_t v = 0; v < P->n_nodes; ++v) {
       const int64_t d = P->deg_local[v];
       if (d >= AGG_HUB_MIN) P->buckets.n_hub++, P->buckets.nnz_hub += d;
+      if (d >= AGG_BLOCK_MIN) P->buckets.n_block++;
+      if (d >= AGG_WAVE_MIN) P->buckets.n_wave++;
     }
   }
   {
@@ -382,8 +384,7 @@ int32_t select_graph(const cofree_partition* part, const cofree_masks* masks, in
   d.slots.attach(out);
   out->n = part->n_nodes;
   out->nnz = d.nnz;
-  out->n_hub = d.buckets.n_hub;
-  out->nnz_hub = d.buckets.nnz_hub;
+  d.buckets.attach(out);
   return COFREE_OK;
 }
 

@@ -8,23 +8,15 @@
 // with the roles of the two scale vectors exchanged - no atomics, fixed summation order.
 // Rows are stored as float32 or bfloat16; sums are always float32.
 //
-// Three kernels.  Every graph carries its rows sorted by descending degree, hub rows first:
+// Three kernels.  Every graph carries its rows sorted by descending degree:
+//  * aggregate_kernel: rows by teams of lanes - long rows a workgroup each, middling ones a wavefront each, short ones
+//    a group of 16 to 64 lanes - in one launch, longest rows first.
 //  * aggregate_hub_kernel (hub rows, AGG_HUB_MIN neighbours and more - the nodes that keep a high degree after
 //    the cut, Theorem 2): a workgroup of sixteen wavefronts per (row, column panel); every wavefront sums a
 //    strided share of the neighbours, the sixteen partial rows are staged in LDS and added in wavefront order.
 //    A launch of its own over the head of the order, when the graph has such rows.
-//  All other rows go through one of two kernels, chosen on the host by the graph's average degree:
-//  * aggregate_group_kernel (average degree of AGG_LONG_MIN and more): one wavefront per (row, column
-//    slice); the 64 lanes form 64/LPS neighbour groups that fetch different neighbours in the same load
-//    instruction.
-//  * aggregate_kernel (short rows): a group of LANES lanes of a 64-wide wavefront owns one row;
-//    one neighbour row is fetched by the group as one contiguous segment of 16 bytes per lane.
-//    Column indices are fetched LANES at a time with one coalesced load and handed out by
-//    cross-lane reads.
-// Rows are handed out by descending degree, so the lane groups of a wavefront get rows of similar length and
-// the longest rows start first: below the hub threshold a long row finishes well inside the launch.  (Cutting
-// the order further - rows of 16 neighbours and more through the group kernel, the rest through the row
-// kernel, each in a launch of its own - was measured and lost 5-8 % to the extra launches on every workload.)
+//  * aggregate_sliced_kernel (high average degree, wide float32 rows): a wavefront per (row, column slice), slices
+//    bound to XCDs.
 // Which wavefront sums which neighbours is fixed by the launch shape, so results are run-to-run identical.
 #include <climits>
 #include <cstdio>
@@ -149,23 +141,6 @@ __device__ inline void store_elems(T* p, int avail, const float (&v)[VEC]) {
   }
 }
 
-template <int LANES>
-__device__ inline int group_read_i(int x, int grp_base, int j) {
-  if constexpr (LANES == 64) {
-    return __builtin_amdgcn_readlane(x, j);
-  } else {
-    return __shfl(x, grp_base + j, 64);
-  }
-}
-template <int LANES>
-__device__ inline float group_read_f(float x, int grp_base, int j) {
-  if constexpr (LANES == 64) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j));
-  } else {
-    return __shfl(x, grp_base + j, 64);
-  }
-}
-
 template <typename T>
 struct AggK {
   const int64_t* rowptr;
@@ -176,11 +151,11 @@ struct AggK {
   int64_t ldy;
   int width;  // columns of this launch
   int64_t n;
-  const int32_t* order;  // short-row kernel: the i-th lane group works on row order[i] (null: row i)
-  const int32_t* order_long;  // the same for the long-row kernel's wavefronts
+  const int32_t* order;  // the i-th team works on row order[slot0 + i] (null: row i)
+  int64_t n_block, n_wave;  // row kernel: the first n_block rows get a workgroup each, the next n_wave a wavefront each
   int64_t slot0;      // first entry of `order` this launch covers (its bucket); n counts the entries from there
   int64_t skip_from;  // rows of at least this many neighbours belong to another launch (natural-order launches)
-  // short-row kernel on the processing-order copy of the graph: rowptr, col and in_vals are that copy's, indexed by
+  // row kernel on the processing-order copy of the graph: rowptr, col and in_vals are that copy's, indexed by
   // slot, and the row's own factors come per slot too (null: none, or read by row id from in_scale / out_scale)
   int by_slot;
   const float* in_scale_slot;
@@ -305,34 +280,133 @@ __device__ inline void finish_row(const AggK<T>& p, int64_t row, int c0, int fir
   }
 }
 
-// ---- short rows ---------------------------------------------------------------------------------
-// VEC = RowIO<T>::WIDE.  Rows need only element alignment (see LaneCols for the ragged end of a row).
-template <typename T, int VEC, int LANES, int NCH, bool TINY>
-__global__ __launch_bounds__(256) void aggregate_kernel(const AggK<T> p) {
-  const int64_t* __restrict__ rowptr = p.rowptr;
+// ---- rows by teams of lanes -----------------------------------------------------------------------
+// A row belongs to a team: TL lanes of a wavefront (short rows), a whole wavefront, or a workgroup (long rows).
+// Inside a team LPS lanes hold the row's columns (NCH pieces of 16 bytes each) and the team's NG = lanes / LPS
+// neighbour groups fetch different neighbours in the same load instruction; the groups are added in a fixed butterfly
+// order at the end, a workgroup's four wavefronts in ascending order through LDS.  Neighbour ids (and factors) are
+// fetched one per team lane with one coalesced load and handed out by cross-lane reads.
+// Rows come in descending degree: the workgroups of the grid's front take the n_block longest rows, then come n_wave
+// rows of a wavefront each, then the short rows, 64 / TL per wavefront.  A short team walks a row at 0.115 us per
+// neighbour (four in flight), so without the larger teams one row outlasted everything else on graphs of up to a few
+// million entries: 100k nodes, 600k entries, 128-wide bfloat16 80 -> 30 us a launch; 600k nodes, 4M entries, 100-wide
+// float32 470 -> 350 us.  It is one launch because launches of their own for the long rows cost more than they saved.
+// The lines (32 and 128 neighbours, common.h) are flat: 16 to 64 and 64 to 512 measured within 4 % on every workload,
+// the smaller workgroup line ahead on 20k nodes (14 -> 11 us a launch).  At most 64 registers in float32 and 72 in
+// bfloat16 are what the occupancy of the gather needs: 73 and 76 cost 3-8 % of every large launch, and bfloat16 in 64
+// goes to scratch memory (30 % slower).
+template <int LANES>
+__device__ inline int team_read_i(int x, int base, int j) {
+  if constexpr (LANES == 64) return __builtin_amdgcn_readlane(x, j);
+  else return __shfl(x, base + j, 64);
+}
+template <int LANES>
+__device__ inline float team_read_f(float x, int base, int j) {
+  if constexpr (LANES == 64) return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j));
+  else return __shfl(x, base + j, 64);
+}
+
+// Adds the neighbours of a row that fall to this wavefront (entries first .. of every `stride`, TL of them at a time).
+template <typename T, int TL, int LPS, int NCH, bool TINY>
+__device__ inline void gather_row(const AggK<T>& p, int64_t beg, int64_t end, int64_t first, int64_t stride, int lane,
+                                  const LaneCols (&lc)[NCH], const int (&cread)[NCH],
+                                  float (&acc)[NCH][RowIO<T>::WIDE]) {
+  constexpr int VEC = RowIO<T>::WIDE, NG = TL / LPS;
+  constexpr int UNR = 4;
   const int32_t* __restrict__ col = p.col;
   const T* __restrict__ X = p.X;
   const float* __restrict__ in_scale = p.in_scale;
   const float* __restrict__ in_vals = p.in_vals;
-  constexpr int RPW = 64 / LANES;  // rows per wavefront
-  constexpr int UNR = 4;
-  const int lane = threadIdx.x & 63;
-  const int sub = lane % LANES;
-  const int grp_base = (lane / LANES) * LANES;
-  const int64_t slot = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * RPW + lane / LANES;
-  if (slot >= p.n) return;
+  const int tl = lane % TL, base = lane - tl, grp = tl / LPS;
+  for (int64_t e0 = beg + first; e0 < end; e0 += stride) {
+    const int64_t e = e0 + tl < end ? e0 + tl : end - 1;
+    const int my_col = col[e];
+    float my_s = 1.f;
+    if (in_vals) my_s = in_vals[e];
+    else if (in_scale) my_s = in_scale[my_col];
+    const int cnt = (int)((end - e0) < (int64_t)TL ? (end - e0) : (int64_t)TL);
+    for (int j = 0; j < cnt; j += UNR * NG) {
+      int u[UNR];
+      float s[UNR];
+      bool ok[UNR];
+#pragma unroll
+      for (int t = 0; t < UNR; ++t) {
+        // slot of this group; a slot past the row's end repeats the last neighbour (see RowIO) and is left out
+        const int q = j + t * NG + (NG == 1 ? 0 : grp);
+        ok[t] = q < cnt;
+        const int qc = ok[t] ? q : cnt - 1;
+        u[t] = team_read_i<LPS>(my_col, base, qc);
+        s[t] = team_read_f<LPS>(my_s, base, qc);
+      }
+      if constexpr (TINY) {
+        float v[UNR][VEC];
+#pragma unroll
+        for (int t = 0; t < UNR; ++t) load_elems<T, VEC>(X + (int64_t)u[t] * p.ldx, p.width, v[t]);
+#pragma unroll
+        for (int t = 0; t < UNR; ++t)
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) acc[0][i] = ok[t] ? fmaf(s[t], v[t][i], acc[0][i]) : acc[0][i];
+      } else {
+        typename RowIO<T>::Raw v[UNR][NCH];
+#pragma unroll
+        for (int t = 0; t < UNR; ++t) {
+          const T* const src = X + (int64_t)u[t] * p.ldx;
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) v[t][c] = RowIO<T>::load_raw(src + cread[c]);
+        }
+#pragma unroll
+        for (int t = 0; t < UNR; ++t)
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) RowIO<T>::fma_raw(acc[c], s[t], RowIO<T>::keep_if(ok[t], v[t][c]));
+      }
+    }
+  }
+#pragma unroll
+  for (int off = LPS; off < TL; off <<= 1) {
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) acc[c][i] += __shfl_xor(acc[c][i], off, 64);
+  }
+}
+
+// TINY: rows narrower than one 16-byte access (element accesses; LPS = 1).
+// Rows need only element alignment (see LaneCols for the ragged end of a row).
+template <typename T, int TL, int LPS, int NCH, bool TINY>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4 : (sizeof(T) == 4 ? 8 : 7)))) void aggregate_kernel(const AggK<T> p) {
+  constexpr int VEC = RowIO<T>::WIDE;
+  constexpr int RPW = 64 / TL;  // short rows per wavefront
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int sub = lane % LPS;
+  const int64_t b = blockIdx.x;
+  const int64_t wave_blocks = (p.n_wave + 3) / 4;
+  int team;  // 0 short rows, 1 a wavefront per row, 2 a workgroup per row (uniform over the block)
+  int64_t slot, limit;
+  if (b < p.n_block) {
+    team = 2;
+    slot = b;
+    limit = p.n_block;
+  } else if (b < p.n_block + wave_blocks) {
+    team = 1;
+    slot = p.n_block + (b - p.n_block) * 4 + wave;
+    limit = p.n_block + p.n_wave;
+  } else {
+    team = 0;
+    slot = p.n_block + p.n_wave + ((b - p.n_block - wave_blocks) * 4 + wave) * RPW + lane / TL;
+    limit = p.n;
+  }
+  if (slot >= limit) return;  // never in a workgroup that shares a row
   const int64_t s = p.slot0 + slot;
   const int64_t row = p.order ? (int64_t)p.order[s] : slot;
   const int64_t at = p.by_slot ? s : row;
-  const int64_t beg = rowptr[at], end = rowptr[at + 1];
-  if (end - beg >= p.skip_from) return;  // a hub row met in natural order: the hub launch owns it
+  const int64_t beg = p.rowptr[at], end = p.rowptr[at + 1];
 
   float acc[NCH][VEC];
   LaneCols lc[NCH];
-  int cread[NCH];  // first column a lane reads in the gather loop (lanes past the end: the row's last window)
+  int cread[NCH];  // first column a lane reads (lanes past the end: the row's last window)
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-    lc[c] = lane_cols<VEC>(p.width, (sub + c * LANES) * VEC);
+    lc[c] = lane_cols<VEC>(p.width, (sub + c * LPS) * VEC);
     cread[c] = lc[c].avail > 0 ? lc[c].c0 : (p.width >= VEC ? p.width - VEC : 0);
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[c][i] = 0.f;
@@ -341,164 +415,96 @@ __global__ __launch_bounds__(256) void aggregate_kernel(const AggK<T> p) {
 #pragma unroll
   for (int c = 0; c < NCH; ++c) tail[c].request(p, row, s, cread[c]);
 
-  for (int64_t e0 = beg; e0 < end; e0 += LANES) {
-    int my_col = -1;
-    float my_s = 1.f;
-    if (e0 + sub < end) {
-      my_col = col[e0 + sub];
-      if (in_vals) my_s = in_vals[e0 + sub];
-      else if (in_scale) my_s = in_scale[my_col];
-    }
-    const int cnt = (int)((end - e0) < (int64_t)LANES ? (end - e0) : (int64_t)LANES);
-    for (int j = 0; j < cnt; j += UNR) {
-      int u[UNR];
-      float s[UNR];
+  if (team == 0) {
+    gather_row<T, TL, LPS, NCH, TINY>(p, beg, end, 0, TL, lane, lc, cread, acc);
+  } else {
+    gather_row<T, 64, LPS, NCH, TINY>(p, beg, end, team == 2 ? wave * 64 : 0, team == 2 ? 256 : 64, lane, lc, cread, acc);
+    if (team == 2) {
+      __shared__ float partial[3][NCH * LPS * VEC];
+      if (wave > 0 && lane < LPS) {
 #pragma unroll
-      for (int t = 0; t < UNR; ++t) {
-        const int jj = (j + t) % LANES;
-        u[t] = group_read_i<LANES>(my_col, grp_base, jj);
-        s[t] = group_read_f<LANES>(my_s, grp_base, jj);
-        if (j + t >= cnt) u[t] = -1;
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) partial[wave - 1][(c * VEC + i) * LPS + sub] = acc[c][i];
       }
-      if constexpr (TINY) {
-        float v[UNR][NCH][VEC];
+      __syncthreads();
+      if (wave > 0) return;
 #pragma unroll
-        for (int t = 0; t < UNR; ++t) {
+      for (int w = 0; w < 3; ++w)
 #pragma unroll
-          for (int c = 0; c < NCH; ++c) {
+        for (int c = 0; c < NCH; ++c)
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) v[t][c][i] = 0.f;
-            if (u[t] >= 0 && lc[c].avail > 0)
-              load_elems<T, VEC>(X + (int64_t)u[t] * p.ldx + lc[c].c0, lc[c].avail, v[t][c]);
-          }
-        }
-#pragma unroll
-        for (int t = 0; t < UNR; ++t)
-#pragma unroll
-          for (int c = 0; c < NCH; ++c)
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) acc[c][i] = fmaf(s[t], v[t][c][i], acc[c][i]);
-      } else {
-        typename RowIO<T>::Raw v[UNR][NCH];
-        const int u_first = group_read_i<LANES>(my_col, grp_base, j % LANES);  // exists: j < cnt
-#pragma unroll
-        for (int t = 0; t < UNR; ++t) {
-          const int64_t src = (int64_t)(u[t] >= 0 ? u[t] : u_first) * p.ldx;
-#pragma unroll
-          for (int c = 0; c < NCH; ++c) v[t][c] = RowIO<T>::load_raw(X + src + cread[c]);
-        }
-#pragma unroll
-        for (int t = 0; t < UNR; ++t)
-#pragma unroll
-          for (int c = 0; c < NCH; ++c) RowIO<T>::fma_raw(acc[c], s[t], RowIO<T>::keep_if(u[t] >= 0, v[t][c]));
-      }
+          for (int i = 0; i < VEC; ++i) acc[c][i] += partial[w][(c * VEC + i) * LPS + sub];
     }
   }
+  if ((lane % (team == 0 ? TL : 64)) >= LPS) return;  // the first neighbour group of the team writes
 #pragma unroll
   for (int c = 0; c < NCH; ++c)
     if (lc[c].avail > 0) finish_row<T, VEC, TINY>(p, row, lc[c].c0, lc[c].first, lc[c].avail, acc[c], tail[c]);
 }
 
-// ---- long rows ----------------------------------------------------------------------------------
-// One wavefront per (row, column slice).  A slice is LPS lanes x VEC elements wide (VEC = 16 bytes
-// of elements); the 64 lanes form 64/LPS neighbour groups that fetch different neighbours in the
-// same load instruction and are added together at the end in a fixed butterfly order, so a row
-// of degree d costs d*LPS/64 load instructions however narrow the matrix is.
-// SLICES = 8 is the XCD-aware launch for matrices far larger than one XCD's 4 MB L2: workgroups
-// are dealt round-robin to the 8 XCDs, so workgroup b works on column slice b % 8 of row group
-// b / 8, and each XCD's L2 only ever holds one eighth of every row - eight times as many (hot)
-// rows.  SLICES = 1 covers the whole width (<= LPS*VEC columns) with one slice.
-// Rows need only element alignment (see LaneCols for the ragged end of a row).
-template <typename T, int LPS, int SLICES, bool TINY>
-__global__ __launch_bounds__(256) void aggregate_group_kernel(const AggK<T> p) {
+// ---- XCD-affine column slices ---------------------------------------------------------------------
+// For graphs of high average degree whose matrix is far larger than one XCD's 4 MB L2: one wavefront per (row, column
+// slice of LPS lanes x 16 bytes).  Workgroups are dealt round-robin to the 8 XCDs, so workgroup b works on column
+// slice b % 8 of row group b / 8, and each XCD's L2 only ever holds one eighth of every row - eight times as many
+// (hot) rows.  The launcher sends only widths that divide into eight slices.
+template <typename T, int LPS>
+__global__ __launch_bounds__(256) void aggregate_sliced_kernel(const AggK<T> p) {
   constexpr int VEC = RowIO<T>::WIDE;
   constexpr int NG = 64 / LPS;
   constexpr int UNR = 4;
   const int lane = threadIdx.x & 63;
   const int sub = lane % LPS, grp = lane / LPS;
-  const int slice = SLICES == 1 ? 0 : (int)(blockIdx.x % (unsigned)SLICES);
-  const int64_t slot = (int64_t)(blockIdx.x / (unsigned)SLICES) * 4 + (threadIdx.x >> 6);
-  if (slot >= p.n) return;
-  const int64_t row = p.order_long ? (int64_t)p.order_long[p.slot0 + slot] : slot;
-  const LaneCols lc = lane_cols<VEC>(p.width, slice * (LPS * VEC) + sub * VEC);
-  const int c0 = lc.c0, avail = lc.avail;
+  const int64_t row = (int64_t)(blockIdx.x / 8u) * 4 + (threadIdx.x >> 6);  // natural order, which measured better
+  if (row >= p.n) return;
+  const int c0 = ((int)(blockIdx.x % 8u) * LPS + sub) * VEC;
   const T* __restrict__ X = p.X + c0;
   const int32_t* __restrict__ col = p.col;
   const float* __restrict__ in_scale = p.in_scale;
   const float* __restrict__ in_vals = p.in_vals;
   const int64_t beg = p.rowptr[row], end = p.rowptr[row + 1];
-  if (end - beg >= p.skip_from) return;  // a hub row met in natural order: the hub launch owns it
+  if (end - beg >= p.skip_from) return;  // a hub row: the hub launch owns it
   float acc[VEC];
 #pragma unroll
   for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
-  RowTail<T, VEC, TINY> tail;
-  tail.request(p, row, 0, avail > 0 ? c0 : (p.width >= VEC ? p.width - VEC : 0));
-  if constexpr (TINY) {
+  RowTail<T, VEC, false> tail;
+  tail.request(p, row, 0, c0);
+  // every load of the loop is unconditional (see RowIO): ids past the end of the row repeat its last id and are
+  // zeroed after the load.  scale_mode: 0 no per-source factor, 1 gathered from the per-node vector, 2 per entry
+  auto gather = [&](auto scale_mode) {
+    constexpr int MODE = decltype(scale_mode)::value;
+    const int64_t last = end - 1;
     for (int64_t e = beg + grp; e < end; e += NG * UNR) {
       int u[UNR];
       float s[UNR];
-      float v[UNR][VEC];
+      typename RowIO<T>::Raw v[UNR];
 #pragma unroll
       for (int t = 0; t < UNR; ++t) {
         const int64_t ee = e + t * NG;
-        u[t] = ee < end ? col[ee] : -1;
+        const int64_t ec = ee < last ? ee : last;
+        u[t] = col[ec];
+        if constexpr (MODE == 2) s[t] = in_vals[ec];
       }
 #pragma unroll
       for (int t = 0; t < UNR; ++t) {
-        s[t] = 1.f;
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) v[t][i] = 0.f;
-        if (u[t] >= 0 && avail > 0) {
-          if (in_vals) s[t] = in_vals[e + t * NG];
-          else if (in_scale) s[t] = in_scale[u[t]];
-          load_elems<T, VEC>(X + (int64_t)u[t] * p.ldx, avail, v[t]);
-        }
+        if constexpr (MODE == 1) s[t] = in_scale[u[t]];
+        if constexpr (MODE == 0) s[t] = 1.f;
+        v[t] = RowIO<T>::load_raw(X + (int64_t)u[t] * p.ldx);
       }
 #pragma unroll
-      for (int t = 0; t < UNR; ++t)
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(s[t], v[t][i], acc[i]);
+      for (int t = 0; t < UNR; ++t) RowIO<T>::fma_raw(acc, s[t], RowIO<T>::keep_if(e + t * NG < end, v[t]));
     }
-  } else {
-    // every load of the loop is unconditional (see RowIO): ids past the end of the row repeat its last id
-    // and are zeroed after the load; lanes past the end of the matrix row re-read its last window
-    const T* __restrict__ Xread = p.X + (avail > 0 ? c0 : p.width - VEC);
-    // scale_mode: 0 no per-source factor, 1 gathered from the per-node vector, 2 read per entry next to col
-    auto gather = [&](auto scale_mode) {
-      constexpr int MODE = decltype(scale_mode)::value;
-      const int64_t last = end - 1;
-      for (int64_t e = beg + grp; e < end; e += NG * UNR) {
-        int u[UNR];
-        float s[UNR];
-        typename RowIO<T>::Raw v[UNR];
-#pragma unroll
-        for (int t = 0; t < UNR; ++t) {
-          const int64_t ee = e + t * NG;
-          const int64_t ec = ee < last ? ee : last;
-          u[t] = col[ec];
-          if constexpr (MODE == 2) s[t] = in_vals[ec];
-        }
-#pragma unroll
-        for (int t = 0; t < UNR; ++t) {
-          if constexpr (MODE == 1) s[t] = in_scale[u[t]];
-          if constexpr (MODE == 0) s[t] = 1.f;
-          v[t] = RowIO<T>::load_raw(Xread + (int64_t)u[t] * p.ldx);
-        }
-#pragma unroll
-        for (int t = 0; t < UNR; ++t) RowIO<T>::fma_raw(acc, s[t], RowIO<T>::keep_if(e + t * NG < end, v[t]));
-      }
-    };
-    if (in_vals) gather(std::integral_constant<int, 2>{});
-    else if (in_scale) gather(std::integral_constant<int, 1>{});
-    else gather(std::integral_constant<int, 0>{});
-  }
+  };
+  if (in_vals) gather(std::integral_constant<int, 2>{});
+  else if (in_scale) gather(std::integral_constant<int, 1>{});
+  else gather(std::integral_constant<int, 0>{});
 #pragma unroll
   for (int off = LPS; off < 64; off <<= 1) {
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
   }
-  if (grp != 0 || avail <= 0) return;
-  finish_row<T, VEC, TINY>(p, row, c0, lc.first, avail, acc, tail);
+  if (grp != 0) return;
+  finish_row<T, VEC, false>(p, row, c0, 0, VEC, acc, tail);
 }
 
 // ---- hub rows -----------------------------------------------------------------------------------
@@ -595,58 +601,53 @@ struct LaunchCost {
   double flops(int64_t nnz) const { return 2.0 * (double)nnz * a.width; }
 };
 
-template <typename T, int VEC, int LANES, int NCH>
-static void launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
-  constexpr int rows_per_block = 4 * (64 / LANES);
-  const int64_t blocks = (k.n + rows_per_block - 1) / rows_per_block;
-  const bool tiny = LANES == 16 && NCH == 1 && k.width < VEC;  // rows narrower than one wide access
+// One launch of the row kernel: k.n rows, of which the first k.n_block take a workgroup and the next k.n_wave a
+// wavefront each.  Column lanes: the smallest power of two that covers the row in 16-byte pieces.  Short rows come
+// four to a wavefront, where the columns leave that many lanes: with more rows, narrow rows measured slower (8 rows
+// of 6 pieces: 0.50 ms, 4 rows 0.41 ms on 1.9M rows of 47 bfloat16); lanes that the columns leave free fetch further
+// neighbours of the row.
+template <typename T>
+static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
+  constexpr int WIDE = RowIO<T>::WIDE;
+  const int chunks = (k.width + WIDE - 1) / WIDE;
+  const bool tiny = k.width < WIDE;
+  int lps = 1;
+  while (lps < chunks && lps < 64) lps *= 2;
+  const int tl = lps < 16 ? 16 : lps;
+  const int nch = chunks > 64 ? 2 : 1;
+  const int64_t short_rows = k.n - k.n_block - k.n_wave, per_block = 4 * (64 / tl);
+  const int64_t blocks = k.n_block + (k.n_wave + 3) / 4 + (short_rows + per_block - 1) / per_block;
+  COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
   char pname[96];
-  snprintf(pname, sizeof(pname), "aggregate_kernel<%s,%d,%d,%d,%s> width=%d", type_name<T>(), VEC, LANES, NCH,
+  snprintf(pname, sizeof(pname), "aggregate_kernel<%s,%d,%d,%d,%s> width=%d", type_name<T>(), tl, lps, nch,
            tiny ? "true" : "false", (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
-  if constexpr (LANES == 16 && NCH == 1) {
-    if (tiny) {
-      aggregate_kernel<T, VEC, LANES, NCH, true><<<dim3((unsigned)blocks), 256, 0, stream>>>(k);
-      return;
-    }
-  }
-  aggregate_kernel<T, VEC, LANES, NCH, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(k);
-}
-
-template <typename T, int VEC>
-static int32_t dispatch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
-  const int chunks = (k.width + VEC - 1) / VEC;
-  // at most four rows per wavefront: with more, narrow rows measured slower (8 rows of 6 chunks: 0.50 ms,
-  // 4 rows with idle lanes: 0.41 ms on the 47-wide bf16 launches of cfg2)
-  if (chunks <= 16) launch_rows<T, VEC, 16, 1>(k, stream, cost, nnz);
-  else if (chunks <= 32) launch_rows<T, VEC, 32, 1>(k, stream, cost, nnz);
-  else if (chunks <= 64) launch_rows<T, VEC, 64, 1>(k, stream, cost, nnz);
-  else if (chunks <= 128) launch_rows<T, VEC, 64, 2>(k, stream, cost, nnz);
-  else return fail(COFREE_EINVAL, "internal: aggregate panel too wide");
+  const dim3 grid((unsigned)blocks);
+  if (tiny) aggregate_kernel<T, 16, 1, 1, true><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 1) aggregate_kernel<T, 16, 1, 1, false><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 2) aggregate_kernel<T, 16, 2, 1, false><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 4) aggregate_kernel<T, 16, 4, 1, false><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 8) aggregate_kernel<T, 16, 8, 1, false><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 16) aggregate_kernel<T, 16, 16, 1, false><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 32) aggregate_kernel<T, 32, 32, 1, false><<<grid, 256, 0, stream>>>(k);
+  else if (nch == 1) aggregate_kernel<T, 64, 64, 1, false><<<grid, 256, 0, stream>>>(k);
+  else aggregate_kernel<T, 64, 64, 2, false><<<grid, 256, 0, stream>>>(k);
   return COFREE_OK;
 }
 
-template <typename T, int SLICES>
-static int32_t launch_group(const AggK<T>& k, int lps, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
-  const int64_t blocks = ((k.n + 3) / 4) * SLICES;
+template <typename T>
+static int32_t launch_sliced(const AggK<T>& k, int lps, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
+  const int64_t blocks = ((k.n + 3) / 4) * 8;
   COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
   const dim3 grid((unsigned)blocks);
-  const bool tiny = lps == 1 && k.width < RowIO<T>::WIDE;
   char pname[96];
-  snprintf(pname, sizeof(pname), "aggregate_group_kernel<%s,%d,%d,%s> width=%d", type_name<T>(), lps, SLICES,
-           tiny ? "true" : "false", (int)cost.a.width);
+  snprintf(pname, sizeof(pname), "aggregate_sliced_kernel<%s,%d> width=%d", type_name<T>(), lps, (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   switch (lps) {
-    case 1:
-      if (tiny) aggregate_group_kernel<T, 1, SLICES, true><<<grid, 256, 0, stream>>>(k);
-      else aggregate_group_kernel<T, 1, SLICES, false><<<grid, 256, 0, stream>>>(k);
-      break;
-    case 2: aggregate_group_kernel<T, 2, SLICES, false><<<grid, 256, 0, stream>>>(k); break;
-    case 4: aggregate_group_kernel<T, 4, SLICES, false><<<grid, 256, 0, stream>>>(k); break;
-    case 8: aggregate_group_kernel<T, 8, SLICES, false><<<grid, 256, 0, stream>>>(k); break;
-    case 16: aggregate_group_kernel<T, 16, SLICES, false><<<grid, 256, 0, stream>>>(k); break;
-    case 32: aggregate_group_kernel<T, 32, SLICES, false><<<grid, 256, 0, stream>>>(k); break;
-    case 64: aggregate_group_kernel<T, 64, SLICES, false><<<grid, 256, 0, stream>>>(k); break;
+    case 8: aggregate_sliced_kernel<T, 8><<<grid, 256, 0, stream>>>(k); break;
+    case 16: aggregate_sliced_kernel<T, 16><<<grid, 256, 0, stream>>>(k); break;
+    case 32: aggregate_sliced_kernel<T, 32><<<grid, 256, 0, stream>>>(k); break;
+    case 64: aggregate_sliced_kernel<T, 64><<<grid, 256, 0, stream>>>(k); break;
     default: return fail(COFREE_EINVAL, "internal: bad lanes-per-slice");
   }
   return COFREE_OK;
@@ -713,38 +714,33 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   k.skip_from = INT64_MAX;
   const LaunchCost<T> cost{a, R};
 
-  // Hub rows (the head of the sorted row order) get a launch of their own.  COFREE_AGG_BUCKETS = 0 leaves
-  // them to the kernel that takes every other row.
-  bool buckets = a.g.order != nullptr && a.width >= WIDE;
+  // Hub rows (the head of the sorted row order) get a launch of their own.  COFREE_AGG_BUCKETS = 0 leaves them - and
+  // all other long rows - to the teams of the row kernel that take every other row.
+  bool buckets = a.g.order != nullptr;
   if (const char* env = getenv("COFREE_AGG_BUCKETS")) buckets = buckets && atoi(env) != 0;
-  const int64_t n_hub = buckets ? a.g.n_hub : 0;
+  const int64_t n_hub = buckets && a.width >= WIDE ? a.g.n_hub : 0;
   const int64_t hub_nnz = n_hub > 0 ? a.g.nnz_hub : 0;
 
-  // High average degree: the neighbour-group kernel.  Additionally cut into 8 XCD-affine column
-  // slices when the matrix is far larger than one XCD's 4 MB L2 and the width divides evenly into
-  // slices of at least one 128-byte cache line of float32: a gather costs a compute unit about the same
-  // per line request whatever part of the line is used, so narrower slices only multiply the requests
-  // (230k x 128 float32, average degree 61: 1.35 ms in 64-byte slices, 0.87 ms unsliced), and for
-  // bfloat16 rows the unsliced kernel measured faster at every width (512 wide: 1.73 against 2.13 ms).
+  // High average degree: a wavefront for every row.  Additionally cut into 8 XCD-affine column slices when the
+  // matrix is far larger than one XCD's 4 MB L2 and the width divides evenly into slices of at least one 128-byte
+  // cache line of float32: a gather costs a compute unit about the same per line request whatever part of the line
+  // is used, so narrower slices only multiply the requests (230k x 128 float32, average degree 61: 1.35 ms in
+  // 64-byte slices, 0.87 ms unsliced), and for bfloat16 rows the unsliced kernel measured faster at every width
+  // (512 wide: 1.73 against 2.13 ms).
   const int slice_unit = 8 * WIDE;  // 8 slices of at least one 16-byte lane each
   const bool dense_rows = a.g.nnz / a.g.n >= AGG_LONG_MIN;
-  const bool sliceable = a.width % slice_unit == 0 && a.width / slice_unit <= 64 &&
-                         ((a.width / slice_unit) & (a.width / slice_unit - 1)) == 0 &&
-                         sizeof(T) == 4 && a.width / slice_unit >= 8;
-  const bool groupable = a.width <= 64 * WIDE;
-  bool grouped = dense_rows && groupable;
+  const bool sliceable = sizeof(T) == 4 && a.width % slice_unit == 0 && a.width / slice_unit <= 64 &&
+                         ((a.width / slice_unit) & (a.width / slice_unit - 1)) == 0 && a.width / slice_unit >= 8;
+  bool waves = dense_rows;
   bool sliced = dense_rows && sliceable && (double)a.g.n * a.width * sizeof(T) > 32e6;
-  if (const char* env = getenv("COFREE_AGG_SLICES")) {  // tuning override: 0 = row kernel, 1 = grouped, 8 = sliced
+  if (const char* env = getenv("COFREE_AGG_SLICES")) {  // 0 = teams by degree, 1 = a wavefront per row, 8 = sliced
     const int v = atoi(env);
-    if (v == 0) grouped = sliced = false;
-    if (v == 1) {
-      grouped = groupable;
+    if (v == 0 || v == 1) {
+      waves = v == 1;
       sliced = false;
     }
     if (v == 8) sliced = sliceable;
   }
-  int lps = 1;
-  while (lps * WIDE < a.width && lps < 64) lps *= 2;
 
   // 1. hub rows
   if (n_hub > 0) {
@@ -753,54 +749,50 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
     k.n = n_hub;
     COFREE_TRY(launch_hub<T>(k, stream, cost, a.g.nnz_hub));
   }
-  if (sliced) {
-    // 2a. every other row in natural order (which measured better for the sliced launch): hub rows are met
-    //     and skipped
-    k.order = k.order_long = nullptr;
-    k.slot0 = 0;
-    k.n = a.g.n;
-    k.skip_from = n_hub > 0 ? AGG_HUB_MIN : INT64_MAX;
-    COFREE_TRY((launch_group<T, 8>(k, a.width / slice_unit, stream, cost, a.g.nnz - hub_nnz)));
-    COFREE_HIP_CHECK(hipGetLastError());
-    return COFREE_OK;
+  if constexpr (sizeof(T) == 4) {
+    if (sliced) {
+      // 2a. every other row in natural order: hub rows are met and skipped
+      k.order = nullptr;
+      k.slot0 = 0;
+      k.n = a.g.n;
+      k.skip_from = n_hub > 0 ? AGG_HUB_MIN : INT64_MAX;
+      COFREE_TRY(launch_sliced<T>(k, a.width / slice_unit, stream, cost, a.g.nnz - hub_nnz));
+      COFREE_HIP_CHECK(hipGetLastError());
+      return COFREE_OK;
+    }
   }
-  // 2b. every other row, order[n_hub ..): the neighbour-group kernel or the row kernel
+  // 2b. every other row, order[n_hub ..)
   if (n_hub == a.g.n) {
     COFREE_HIP_CHECK(hipGetLastError());
     return COFREE_OK;
   }
+  k.order = a.g.order;
   k.slot0 = n_hub;
   k.n = a.g.n - n_hub;
-  if (grouped) {
-    k.order = nullptr;
-    k.order_long = a.g.order;
-    COFREE_TRY((launch_group<T, 1>(k, lps, stream, cost, a.g.nnz - hub_nnz)));
-  } else {
-    k.order_long = nullptr;
-    k.order = a.g.order;
-    // The row kernel walks the processing-order copy of the graph (1.9M-node partition, 512-wide float32: 3.00 ms
-    // by row id, 2.8 ms in natural order with its worse balance).  COFREE_AGG_SLOTS = 0 reads by row id.
-    bool slots = a.g.order != nullptr && a.g.s_rowptr != nullptr;
-    if (const char* env = getenv("COFREE_AGG_SLOTS")) slots = slots && atoi(env) != 0;
-    if (slots) {
-      k.by_slot = 1;
-      k.rowptr = a.g.s_rowptr;
-      k.col = a.g.s_col;
-      if (k.in_vals) k.in_vals = a.in_scale == a.g.inv_deg ? a.g.s_val_inv_deg : a.g.s_val_gcn_norm;
-      if (a.in_scale == a.g.inv_deg) k.in_scale_slot = a.g.s_inv_deg;
-      if (a.in_scale == a.g.gcn_norm) k.in_scale_slot = a.g.s_gcn_norm;
-      if (a.out_scale == a.g.inv_deg) k.out_scale_slot = a.g.s_inv_deg;
-      if (a.out_scale == a.g.gcn_norm) k.out_scale_slot = a.g.s_gcn_norm;
-    }
-    const int panel = 128 * WIDE;  // columns one launch covers
-    for (int c0 = 0; c0 < a.width; c0 += panel) {
-      k.width = a.width - c0 < panel ? a.width - c0 : panel;
-      k.col0 = c0;
-      k.X = X + c0;
-      k.Y = Y + c0;
-      k.relu_src = R ? R + c0 : nullptr;
-      COFREE_TRY((dispatch_rows<T, WIDE>(k, stream, cost, a.g.nnz - hub_nnz)));
-    }
+  k.n_block = buckets ? a.g.n_block - n_hub : 0;
+  k.n_wave = waves ? k.n - k.n_block : (buckets ? a.g.n_wave - a.g.n_block : 0);
+  // The row kernel walks the processing-order copy of the graph (1.9M-node partition, 512-wide float32: 3.00 ms
+  // by row id, 2.8 ms in natural order with its worse balance).  COFREE_AGG_SLOTS = 0 reads by row id.
+  bool slots = a.g.order != nullptr && a.g.s_rowptr != nullptr;
+  if (const char* env = getenv("COFREE_AGG_SLOTS")) slots = slots && atoi(env) != 0;
+  if (slots) {
+    k.by_slot = 1;
+    k.rowptr = a.g.s_rowptr;
+    k.col = a.g.s_col;
+    if (k.in_vals) k.in_vals = a.in_scale == a.g.inv_deg ? a.g.s_val_inv_deg : a.g.s_val_gcn_norm;
+    if (a.in_scale == a.g.inv_deg) k.in_scale_slot = a.g.s_inv_deg;
+    if (a.in_scale == a.g.gcn_norm) k.in_scale_slot = a.g.s_gcn_norm;
+    if (a.out_scale == a.g.inv_deg) k.out_scale_slot = a.g.s_inv_deg;
+    if (a.out_scale == a.g.gcn_norm) k.out_scale_slot = a.g.s_gcn_norm;
+  }
+  const int panel = 128 * WIDE;  // columns one launch covers
+  for (int c0 = 0; c0 < a.width; c0 += panel) {
+    k.width = a.width - c0 < panel ? a.width - c0 : panel;
+    k.col0 = c0;
+    k.X = X + c0;
+    k.Y = Y + c0;
+    k.relu_src = R ? R + c0 : nullptr;
+    COFREE_TRY(launch_rows<T>(k, stream, cost, a.g.nnz - hub_nnz));
   }
   COFREE_HIP_CHECK(hipGetLastError());
   return COFREE_OK;

@@ -1,0 +1,45 @@
+"""The aggregation's teams of lanes: rows just below, at and above the degrees at which a row gets a wavefront, a
+workgroup or a hub launch, for every lane layout (width) of the row kernel, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import dropedge as o_dropedge
+from oracle import layers as o_layers
+from oracle import partition as o_partition
+from paper_2308_03209_amd import inputs
+from util import assert_close
+
+pytestmark = pytest.mark.gpu
+
+DEGREES = [4097, 4095, 1000, 257, 256, 255, 129, 128, 127, 65, 64, 63, 33, 32, 31, 17, 16, 15]
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2308_03209_amd import binding as B
+    src, dst = inputs.hub_graph(5001, DEGREES, 6000, 21)
+    P = B.build_partition(5001, src, dst, 1, 0, 1)
+    return dict(B=B, torch=torch, P=P, O=o_partition.build_partition(5001, src, dst, 1, 0, 1), M=B.dropedge_k(P, 1, 0.5, 3))
+
+
+# columns per 16-byte piece: 4 in float32, 8 in bfloat16; lane layouts change at 1, 2, 4, ... 64 and 128 pieces
+@pytest.mark.parametrize("dtype,width", [("f32", w) for w in (1, 4, 7, 13, 31, 41, 100, 255, 300, 514)] +
+                         [("bf16", w) for w in (3, 8, 15, 30, 47, 128, 172, 500, 1000)])
+@pytest.mark.parametrize("masked", [False, True])
+def test_rows_at_the_team_limits(env, dtype, width, masked):
+    B, torch, P, O = env["B"], env["torch"], env["P"], env["O"]
+    print(f"[case] row teams dtype={dtype} width={width} masked={masked}", flush=True)
+    g = o_dropedge.full_graph(O)
+    masks = None
+    if masked:
+        masks = env["M"]
+        g = o_dropedge.masked_graph(O, o_dropedge.masks(O["n_edges"], 1, 0.5, 3)[0])
+    td, code, tol = (torch.float32, B.F32, 1e-4) if dtype == "f32" else (torch.bfloat16, B.BF16, 5e-3)
+    X = torch.from_numpy(np.random.default_rng(width).standard_normal((P.num_nodes, width)).astype(np.float32)).to(td).cuda()
+    X64, Y = X.float().cpu().numpy().astype(np.float64), torch.empty_like(X)
+    for mode, ref in [(B.AGG_MEAN, o_layers.mean_aggregate), (B.AGG_GCN, o_layers.gcn_aggregate)]:
+        Y.fill_(float("nan"))
+        B.aggregate(P, masks, 0, mode, X, Y, width, code)
+        assert_close(Y.float().cpu().numpy(), ref(g, X64), tol, f"mode {mode} width {width}")
