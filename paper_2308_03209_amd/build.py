@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcofree.so")
 GATHER_CEILING = os.path.join(HERE, "gather_ceiling")   # stand-alone micro-benchmark (csrc/gather_ceiling.hip)
 SOURCES = ["partition.cpp", "dropedge.hip", "spmm.hip", "gemm.hip", "gemm_split.hip", "gemm_bf16.hip", "loss_step.hip", "layers.cpp", "profile.cpp"]
-HEADERS = [os.path.join(CSRC, "common.h"), os.path.join(HERE, "..", "include", "cofree.h")]
+HEADERS = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "colsum.h"), os.path.join(HERE, "..", "include", "cofree.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-Wno-unknown-warning-option"]

@@ -33,6 +33,7 @@ int32_t fail(int32_t code, const std::string& msg);
 // ---- optional kernel timing (profile.cpp) -------------------------------------------------
 // Brackets one kernel launch with HIP events on its stream when profiling is enabled, and
 // books the launch's algorithmic bytes / flops under `name`.
+bool profiling();  // whether launches are being timed (only then does a launch need its name)
 class ProfScope {
  public:
   ProfScope(const char* name, hipStream_t stream, double alg_bytes, double alg_flops);
@@ -308,39 +309,68 @@ struct GemmArgs {
 int32_t launch_gemm(const GemmArgs& a, hipStream_t stream);
 size_t gemm_param_scratch_bytes(int32_t N, int64_t K);
 
-// C[N1,N2] (+)= A^T B with A [M, N1] (lda), B [M, N2] (ldb) of `dtype`, C float32: reduction over
-// the long dimension M in fixed-order split chunks.  workspace: wgrad_workspace_floats(N1, N2 + N2b, M).
+// Sums of partial results in a fixed order: C[i, j] (+)= sum over z of part[z * stride + i * cols + j].  The weight and
+// bias gradients of a layer leave partials behind and are summed by one launch at its end.
+struct SplitSum {
+  const float* part;
+  int64_t stride;
+  float* C;
+  int64_t ldc;
+  int32_t splits, rows, cols;
+  int32_t block0;  // first workgroup of this job (set by the launcher)
+};
+struct SplitSums {
+  static constexpr int MAX = 8;
+  SplitSum job[MAX];
+  int32_t n = 0;
+  int32_t accumulate = 0;
+};
+int32_t add_split_sum(SplitSums* sums, const float* part, int64_t stride, int32_t splits, float* C, int64_t ldc,
+                      int32_t rows, int32_t cols);
+int32_t launch_split_sums(SplitSums sums, hipStream_t stream);
+
+// Weight gradient C[N1, N2 + N2b] = A^T [B | B2] with A [M, N1], B [M, N2], B2 [M, N2b] of `dtype`, C float32: reduction
+// over the long dimension M in fixed-order split chunks, whose partials go to `workspace`
+// (wgrad_workspace_floats(N1, N2 + N2b, M)) and are added to the sums.
+struct WgradArgs {
+  int32_t dtype = COFREE_F32;
+  int64_t M = 0;
+  const void* A = nullptr;
+  int64_t lda = 0;
+  int32_t N1 = 0;
+  const void* B = nullptr;
+  int64_t ldb = 0;
+  int32_t N2 = 0;
+  // optional second matrix (N2 must be a multiple of 128): two weight gradients that share A read it once
+  const void* B2 = nullptr;
+  int64_t ldb2 = 0;
+  int32_t N2b = 0;
+  float* C = nullptr;
+  int64_t ldc = 0;
+  float* workspace = nullptr;
+  // optional [N1]: the bias gradient that goes with C - column sums of A, computed on the way, or of colsum_src
+  // (same shape and leading dimension as A), by extra workgroups of the launch with colsum_workspace_floats(N1) of scratch
+  float* colsum_out = nullptr;
+  const void* colsum_src = nullptr;
+  float* colsum_workspace = nullptr;
+};
+int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
 size_t wgrad_workspace_floats(int32_t N1, int32_t N2, int64_t M);
-// colsum_out (optional, [N1]) (+)= column sums of A, computed on the way (the bias gradient that goes with C).
-// B2 (optional): a second matrix [M, N2b] (ldb2) whose product with the same A fills the columns N2 .. of C -
-// two weight gradients that share the incoming gradient read it once; N2 must be a multiple of 128.
-int32_t launch_wgrad(int32_t dtype, const void* A, int64_t lda, int32_t N1, const void* B, int64_t ldb, int32_t N2,
-                     int64_t M, float* C, int64_t ldc, int32_t accumulate, float* workspace, hipStream_t stream,
-                     float* colsum_out = nullptr, const void* B2 = nullptr, int64_t ldb2 = 0, int32_t N2b = 0);
-// shared by the float32 and bfloat16 paths; resident = workgroups of the kernel the chip holds at once
-// (three per CU for the float32 kernel, two for the bfloat16 one)
+size_t colsum_workspace_floats(int32_t N);
+// shared by the kernels; resident = workgroups of the kernel the chip holds at once (float32: three per CU; bfloat16:
+// two; float32 on the bfloat16 matrix cores: 256x128 tiles at two per CU, 128x128 at three)
 constexpr int32_t WGRAD_RESIDENT_F32 = 768, WGRAD_RESIDENT_BF16 = 512;
-// float32 products on the bfloat16 matrix cores: 256x128 tiles at two workgroups per CU, 128x128 at three
 constexpr int32_t WGRAD_RESIDENT_SPLIT_TALL = 512, WGRAD_RESIDENT_SPLIT = 768;
 int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident, int32_t tile_rows = 128);
+struct ColsumK;
+int32_t plan_colsum(const WgradArgs& a, ColsumK* k, SplitSums* sums);  // extra workgroups of a launch, if any
 // float32 products on the bfloat16 matrix cores (gemm_split.hip): which shapes they take, and their launchers
 bool gemm_split_fits(const GemmArgs& a);
 int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream);
-bool wgrad_split_fits(int32_t N1, int32_t N2a, int32_t N2b, int64_t lda, int64_t ldb, int64_t ldb2);
-int32_t launch_wgrad_split(const float* A, int64_t lda, int32_t N1, const float* B, int64_t ldb, int32_t N2a, int64_t M,
-                           float* C, int64_t ldc, int32_t accumulate, float* workspace, hipStream_t stream,
-                           float* colsum_out, const float* B2, int64_t ldb2, int32_t N2b);
-int32_t launch_split_reduce(const float* partials, int64_t split_stride, int32_t splits, float* C, int64_t ldc,
-                            int32_t rows, int32_t cols, int32_t accumulate, hipStream_t stream);
+bool wgrad_split_fits(const WgradArgs& a);
+int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
 int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream);
-int32_t launch_wgrad_bf16(const bf16_t* A, int64_t lda, int32_t N1, const bf16_t* B, int64_t ldb, int32_t N2,
-                          int64_t M, float* C, int64_t ldc, int32_t accumulate, float* workspace,
-                          hipStream_t stream, float* colsum_out, const bf16_t* B2, int64_t ldb2, int32_t N2b);
-
-// out[N] (+)= column sums of X [M, N] (ld) of `dtype`; workspace floats: colsum_workspace_floats(N)
-size_t colsum_workspace_floats(int32_t N);
-int32_t launch_colsum(int32_t dtype, const void* X, int64_t ld, int64_t M, int32_t N, float* out,
-                      int32_t accumulate, float* workspace, hipStream_t stream);
+int32_t launch_wgrad_bf16(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
 
 // dst[r,c] = src[r,c] * [gate[r,c] > 0 if gate] * keep(r,c)/(1-q) if q > 0   (`dtype`, contiguous [M,N];
 // dst may be src)

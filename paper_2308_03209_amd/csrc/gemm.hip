@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <cstdio>
 
+#include "colsum.h"
 #include "common.h"
 
 namespace cofree {
@@ -59,6 +60,7 @@ struct GemmK {
   int64_t n_groups;  // row panels (forward / input gradients) or k-chunks (weight gradients)
   float* colsum_part;  // weight gradients: [chunks][M] partial column sums of operand A, or null
   int32_t n_split;     // weight gradients: columns n_split .. of the result come from B2 (0: everything from B)
+  ColsumK extra;       // weight gradients: workgroups behind the others that sum columns of another matrix
 };
 
 // ---- operand tile movers: 128 (i) x 16 (k) floats per tile, 8 floats per thread -----------
@@ -336,6 +338,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
   int64_t i0, j0, z;
   {
     const int64_t L = blockIdx.x;
+    if constexpr (A_KMAJOR) {
+      if (L >= (int64_t)gridDim.x - p.extra.blocks) {
+        colsum_block<float>(p.extra, L - ((int64_t)gridDim.x - p.extra.blocks), smem);
+        return;
+      }
+    }
     const int64_t per_group = A_KMAJOR ? p.tiles_m * p.tiles_n : p.tiles_n;
     const int64_t group = (L / (8 * per_group)) * 8 + (L & 7);
     const int64_t member = (L >> 3) % per_group;
@@ -543,21 +551,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
   }
 }
 
-// fixed-order sum of split partials: C[i, j] (+)= sum_z part[z][i][j].  A block owns 32 consecutive
-// outputs; eight thread groups each add up every eighth partial (independent loads, batched by the
-// unrolling), and the eight group sums are added in order.
+// Fixed-order sums of split partials.  A block owns 32 consecutive outputs of one job; eight thread groups each add up
+// every eighth partial (independent loads, batched by the unrolling), and the eight group sums are added in order.
 constexpr int SR_IDX = 32, SR_ZG = 8;
-__global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restrict__ part, int64_t split_stride,
-                                                           int32_t splits, float* __restrict__ C, int64_t ldc,
-                                                           int32_t rows, int32_t cols, int32_t accumulate) {
+__global__ __launch_bounds__(256) void split_sums_kernel(const SplitSums p) {
   __shared__ float red[SR_ZG][SR_IDX];
+  int q = 0;  // this block's job (uniform)
+  while (q + 1 < p.n && (int)blockIdx.x >= p.job[q + 1].block0) ++q;
+  const SplitSum& jb = p.job[q];
   const int ii = threadIdx.x % SR_IDX, zg = threadIdx.x / SR_IDX;
-  const int64_t idx = (int64_t)blockIdx.x * SR_IDX + ii;
-  const bool ok = idx < (int64_t)rows * cols;
+  const int64_t idx = (int64_t)((int)blockIdx.x - jb.block0) * SR_IDX + ii;
+  const bool ok = idx < (int64_t)jb.rows * jb.cols;
   float s = 0.f;
   if (ok) {
+    const float* part = jb.part + idx;
 #pragma unroll 8
-    for (int z = zg; z < splits; z += SR_ZG) s += part[(int64_t)z * split_stride + idx];
+    for (int z = zg; z < jb.splits; z += SR_ZG) s += part[(int64_t)z * jb.stride];
   }
   red[zg][ii] = s;
   __syncthreads();
@@ -565,9 +574,54 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restri
     float t = red[0][ii];
 #pragma unroll
     for (int g = 1; g < SR_ZG; ++g) t += red[g][ii];
-    float* dst = C + (idx / cols) * ldc + (idx % cols);
-    *dst = accumulate ? *dst + t : t;
+    float* dst = jb.C + (idx / jb.cols) * jb.ldc + (idx % jb.cols);
+    *dst = p.accumulate ? *dst + t : t;
   }
+}
+
+int32_t add_split_sum(SplitSums* sums, const float* part, int64_t stride, int32_t splits, float* C, int64_t ldc,
+                      int32_t rows, int32_t cols) {
+  if (sums->n >= SplitSums::MAX) return fail(COFREE_EINVAL, "internal: too many split sums");
+  sums->job[sums->n++] = SplitSum{part, stride, C, ldc, splits, rows, cols, 0};
+  return COFREE_OK;
+}
+
+int32_t launch_split_sums(SplitSums sums, hipStream_t stream) {
+  if (sums.n == 0) return COFREE_OK;
+  int64_t blocks = 0;
+  double bytes = 0.0, flops = 0.0;
+  for (int q = 0; q < sums.n; ++q) {
+    SplitSum& j = sums.job[q];
+    const int64_t total = (int64_t)j.rows * j.cols;
+    j.block0 = (int32_t)blocks;
+    blocks += (total + SR_IDX - 1) / SR_IDX;
+    bytes += 4.0 * (double)total * (j.splits + 1);
+    flops += (double)total * j.splits;
+    COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "split sums: grid too large");
+  }
+  ProfScope prof("split_sums_kernel", stream, bytes, flops);
+  split_sums_kernel<<<dim3((unsigned)blocks), 256, 0, stream>>>(sums);
+  COFREE_HIP_CHECK(hipGetLastError());
+  return COFREE_OK;
+}
+
+// Column sums by extra workgroups: at least 32 rows each, at most COLSUM_MAX_SPLITS chunks of rows.
+constexpr int COLSUM_MAX_SPLITS = 1024;
+size_t colsum_workspace_floats(int32_t N) { return (size_t)COLSUM_MAX_SPLITS * (size_t)N; }
+int32_t plan_colsum(const WgradArgs& a, ColsumK* k, SplitSums* sums) {
+  *k = ColsumK{};
+  if (!a.colsum_out || !a.colsum_src) return COFREE_OK;
+  COFREE_REQUIRE(a.colsum_workspace, "colsum: no workspace");
+  k->X = a.colsum_src;
+  k->ld = a.lda;
+  k->M = a.M;
+  k->N = a.N1;
+  k->splits = (int32_t)std::max<int64_t>(1, std::min<int64_t>((a.M + 31) / 32, COLSUM_MAX_SPLITS));
+  k->panels = (a.N1 + 255) / 256;
+  k->blocks = k->splits * k->panels;
+  k->rows_per_split = (a.M + k->splits - 1) / k->splits;
+  k->partial = a.colsum_workspace;
+  return add_split_sum(sums, k->partial, a.N1, k->splits, a.colsum_out, a.N1, 1, a.N1);
 }
 
 static int32_t check_grid(int64_t blocks) {
@@ -623,8 +677,8 @@ int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
   COFREE_TRY(check_grid(blocks));
   const double flops = 2.0 * (double)a.M * a.N * (double)p.K;
   const double bytes = 4.0 * ((double)a.M * p.K + (double)a.N * p.K + (double)a.M * a.N * (a.accumulate ? 2 : 1));
-  char pname[96];  // the template instance launched below, then the shape
-  snprintf(pname, sizeof(pname), "gemm_kernel<false,%s,%s,%d> N=%d K=%d", a.b_kmajor ? "true" : "false",
+  char pname[96] = "";  // the template instance launched below, then the shape
+  if (profiling()) snprintf(pname, sizeof(pname), "gemm_kernel<false,%s,%s,%d> N=%d K=%d", a.b_kmajor ? "true" : "false",
            a.b_kmajor && a.N < 4 ? "true" : "false", (a.b_kmajor && a.N < 4) || narrow ? 1 : 0, (int)a.N, (int)p.K);
   ProfScope prof(pname, stream, bytes, flops);
   if (a.b_kmajor) {
@@ -663,7 +717,8 @@ int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident, int32_
   // therefore get more, shorter splits.
   const int64_t by_walk = std::min<int64_t>(M / 16384, 2048);
   if (s < by_walk) s = by_walk;
-  const int64_t max_by_len = (M + 511) / 512;
+  // Where chunks of 512 would leave CUs without a workgroup, chunks go down to 64 (2,000 nodes, 16 x 64: 30 -> 9 us).
+  const int64_t max_by_len = std::max<int64_t>((M + 511) / 512, std::min<int64_t>((M + 63) / 64, (512 + tiles - 1) / tiles));
   if (s > max_by_len) s = max_by_len;
   if (s < 1) s = 1;
   return (int32_t)s;
@@ -676,44 +731,27 @@ size_t wgrad_workspace_floats(int32_t N1, int32_t N2, int64_t M) {
   return (size_t)std::max(std::max(s32, s16), tall) * ((size_t)N1 * (size_t)N2 + (size_t)N1);
 }
 
-int32_t launch_split_reduce(const float* partials, int64_t split_stride, int32_t splits, float* C, int64_t ldc,
-                            int32_t rows, int32_t cols, int32_t accumulate, hipStream_t stream) {
-  const int64_t total = (int64_t)rows * cols;
-  ProfScope prof("split_reduce_kernel", stream, 4.0 * (double)total * (splits + 1), (double)total * splits);
-  split_reduce_kernel<<<dim3((unsigned)((total + SR_IDX - 1) / SR_IDX)), 256, 0, stream>>>(partials, split_stride, splits, C,
-                                                                                 ldc, rows, cols, accumulate);
-  COFREE_HIP_CHECK(hipGetLastError());
-  return COFREE_OK;
-}
-
-int32_t launch_wgrad(int32_t dtype, const void* Av, int64_t lda, int32_t N1, const void* Bv, int64_t ldb, int32_t N2a,
-                     int64_t M, float* C, int64_t ldc, int32_t accumulate, float* workspace, hipStream_t stream,
-                     float* colsum_out, const void* B2v, int64_t ldb2, int32_t N2b) {
-  COFREE_REQUIRE(Av && Bv && C && workspace, "wgrad: NULL operand");
-  COFREE_REQUIRE(N1 >= 1 && N2a >= 1 && M >= 0, "wgrad: bad shape");
-  COFREE_REQUIRE(!B2v || (N2b >= 1 && N2a % BN == 0 && ldb2 >= N2b), "wgrad: bad second matrix");
-  const int32_t N2 = N2a + (B2v ? N2b : 0);  // columns of the result
-  COFREE_REQUIRE(lda >= N1 && ldb >= N2a && ldc >= N2, "wgrad: leading dimension too small");
-  if (dtype == COFREE_BF16)
-    return launch_wgrad_bf16((const bf16_t*)Av, lda, N1, (const bf16_t*)Bv, ldb, N2a, M, C, ldc, accumulate, workspace,
-                             stream, colsum_out, (const bf16_t*)B2v, ldb2, N2b);
-  COFREE_REQUIRE(dtype == COFREE_F32, "wgrad: unknown dtype");
-  const float* A = (const float*)Av;
-  const float* B = (const float*)Bv;
-  if (wgrad_split_fits(N1, N2a, B2v ? N2b : 0, lda, ldb, ldb2))
-    return launch_wgrad_split(A, lda, N1, B, ldb, N2a, M, C, ldc, accumulate, workspace, stream, colsum_out,
-                              (const float*)B2v, ldb2, N2b);
+int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
+  COFREE_REQUIRE(a.A && a.B && a.C && a.workspace, "wgrad: NULL operand");
+  COFREE_REQUIRE(a.N1 >= 1 && a.N2 >= 1 && a.M >= 0, "wgrad: bad shape");
+  COFREE_REQUIRE(!a.B2 || (a.N2b >= 1 && a.N2 % BN == 0 && a.ldb2 >= a.N2b), "wgrad: bad second matrix");
+  const int32_t N1 = a.N1, N2 = a.N2 + (a.B2 ? a.N2b : 0);  // rows and columns of the result
+  const int64_t M = a.M;
+  COFREE_REQUIRE(a.lda >= N1 && a.ldb >= a.N2 && a.ldc >= N2, "wgrad: leading dimension too small");
+  if (a.dtype == COFREE_BF16) return launch_wgrad_bf16(a, sums, stream);
+  COFREE_REQUIRE(a.dtype == COFREE_F32, "wgrad: unknown dtype");
+  if (wgrad_split_fits(a)) return launch_wgrad_split(a, sums, stream);
   const int32_t S = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_F32);
   GemmK p{};
-  p.A1 = A;
-  p.lda1 = lda;
+  p.A1 = (const float*)a.A;
+  p.lda1 = a.lda;
   p.K1 = 0;  // unused by k-major loaders
-  p.B = B;
-  p.ldb = ldb;
-  p.B2 = (const float*)B2v;
-  p.ldb2 = ldb2;
-  p.n_split = B2v ? N2a : 0;
-  p.C = workspace;
+  p.B = (const float*)a.B;
+  p.ldb = a.ldb;
+  p.B2 = (const float*)a.B2;
+  p.ldb2 = a.ldb2;
+  p.n_split = a.B2 ? a.N2 : 0;
+  p.C = a.workspace;
   p.ldc = N2;
   p.M = N1;
   p.N = N2;
@@ -728,16 +766,17 @@ int32_t launch_wgrad(int32_t dtype, const void* Av, int64_t lda, int32_t N1, con
   p.tiles_n = narrow == 1 ? 1 : (N2 + BN - 1) / BN;
   p.tiles_m = narrow == 2 ? 1 : (N1 + BM - 1) / BM;
   p.n_groups = S;
-  float* colsum_part = workspace + (size_t)S * N1 * N2;
-  p.colsum_part = colsum_out ? colsum_part : nullptr;
-  const int64_t blocks = (int64_t)((S + 7) / 8) * 8 * p.tiles_m * p.tiles_n;
+  float* colsum_part = a.workspace + (size_t)S * N1 * N2;
+  p.colsum_part = a.colsum_out && !a.colsum_src ? colsum_part : nullptr;
+  COFREE_TRY(plan_colsum(a, &p.extra, sums));
+  const int64_t blocks = (int64_t)((S + 7) / 8) * 8 * p.tiles_m * p.tiles_n + p.extra.blocks;
   COFREE_TRY(check_grid(blocks));
   {
-    const bool tiny = N1 < 4 || (B2v ? N2b < 4 : N2 < 4);
-    char pname[96];
-    snprintf(pname, sizeof(pname), "gemm_kernel<true,true,%s,%d> N=%dx%d", tiny && narrow ? "true" : "false", narrow,
+    const bool tiny = N1 < 4 || (a.B2 ? a.N2b < 4 : N2 < 4);
+    char pname[96] = "";
+    if (profiling()) snprintf(pname, sizeof(pname), "gemm_kernel<true,true,%s,%d> N=%dx%d", tiny && narrow ? "true" : "false", narrow,
              (int)N1, (int)N2);
-    ProfScope prof(pname, stream, 4.0 * ((double)M * N1 + (double)M * N2 + (double)N1 * N2),
+    ProfScope prof(pname, stream, 4.0 * ((double)M * N1 * (p.extra.X ? 2 : 1) + (double)M * N2 + (double)N1 * N2),
                    2.0 * (double)M * N1 * N2);
     const dim3 grid((unsigned)blocks);
     if (narrow == 2) {
@@ -751,8 +790,8 @@ int32_t launch_wgrad(int32_t dtype, const void* Av, int64_t lda, int32_t N1, con
     }
   }
   COFREE_HIP_CHECK(hipGetLastError());
-  COFREE_TRY(launch_split_reduce(workspace, p.c_split_stride, S, C, ldc, N1, N2, accumulate, stream));
-  if (colsum_out) COFREE_TRY(launch_split_reduce(colsum_part, N1, S, colsum_out, N1, 1, N1, accumulate, stream));
+  COFREE_TRY(add_split_sum(sums, a.workspace, p.c_split_stride, S, a.C, a.ldc, N1, N2));
+  if (p.colsum_part) COFREE_TRY(add_split_sum(sums, colsum_part, N1, S, a.colsum_out, N1, 1, N1));
   return COFREE_OK;
 }
 

@@ -11,6 +11,7 @@
 #include <cstdio>
 #include <cstdlib>
 
+#include "colsum.h"
 #include "common.h"
 
 namespace cofree {
@@ -60,6 +61,7 @@ struct GemmHK {
   const bf16_t* B2;
   int64_t ldb2;
   int32_t n_split;
+  ColsumK extra;  // weight gradients: workgroups behind the others that sum columns of another matrix
 };
 
 // Movers bring one 128 x 32 operand tile from global memory to LDS in two steps: load() fills a
@@ -410,6 +412,12 @@ __global__ __launch_bounds__(64 * WM * WN)
   int64_t i0, j0, z;
   {
     const int64_t L = blockIdx.x;
+    if constexpr (WGRAD) {
+      if (L >= (int64_t)gridDim.x - p.extra.blocks) {
+        colsum_block<bf16_t>(p.extra, L - ((int64_t)gridDim.x - p.extra.blocks), reinterpret_cast<float*>(smem));
+        return;
+      }
+    }
     const int64_t per_group = WGRAD ? p.tiles_m * p.tiles_n : p.tiles_n;
     const int64_t group = (L / (8 * per_group)) * 8 + (L & 7);
     const int64_t member = (L >> 3) % per_group;
@@ -689,8 +697,8 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
     if (atoi(e) == 256) big = !narrow && a.N > HBN;
     if (atoi(e) == 128) big = false;
   }
-  char pname[96];  // the template instance launched below, then the shape
-  snprintf(pname, sizeof(pname), "gemm_bf16_kernel<false,false,%s> N=%d K=%d", big ? "false,4,4" : (narrow ? "true,2,2" : "false,2,2"),
+  char pname[96] = "";  // the template instance launched below, then the shape
+  if (profiling()) snprintf(pname, sizeof(pname), "gemm_bf16_kernel<false,false,%s> N=%d K=%d", big ? "false,4,4" : (narrow ? "true,2,2" : "false,2,2"),
            (int)a.N, (int)K);
   ProfScope prof(pname, stream, bytes, flops);
   if (big) {
@@ -707,20 +715,19 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
   return COFREE_OK;
 }
 
-int32_t launch_wgrad_bf16(const bf16_t* A, int64_t lda, int32_t N1, const bf16_t* B, int64_t ldb, int32_t N2a,
-                          int64_t M, float* C, int64_t ldc, int32_t accumulate, float* workspace,
-                          hipStream_t stream, float* colsum_out, const bf16_t* B2, int64_t ldb2, int32_t N2b) {
-  const int32_t N2 = N2a + (B2 ? N2b : 0);  // columns of the result
+int32_t launch_wgrad_bf16(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
+  const int32_t N1 = a.N1, N2 = a.N2 + (a.B2 ? a.N2b : 0);
+  const int64_t M = a.M;
   const int32_t S = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_BF16);
   GemmHK p{};
-  p.A1 = A;
-  p.lda1 = lda;
-  p.B = B;
-  p.ldb = ldb;
-  p.B2 = B2;
-  p.ldb2 = ldb2;
-  p.n_split = B2 ? N2a : 0;
-  p.C = workspace;
+  p.A1 = (const bf16_t*)a.A;
+  p.lda1 = a.lda;
+  p.B = (const bf16_t*)a.B;
+  p.ldb = a.ldb;
+  p.B2 = (const bf16_t*)a.B2;
+  p.ldb2 = a.ldb2;
+  p.n_split = a.B2 ? a.N2 : 0;
+  p.C = a.workspace;
   p.ldc = N2;
   p.c_f32 = 1;
   p.M = N1;
@@ -734,15 +741,16 @@ int32_t launch_wgrad_bf16(const bf16_t* A, int64_t lda, int32_t N1, const bf16_t
   p.tiles_n = (N2 + HBN - 1) / HBN;
   p.tiles_m = (N1 + HBM - 1) / HBM;
   p.n_groups = S;
-  float* colsum_part = workspace + (size_t)S * N1 * N2;
-  p.colsum_part = colsum_out ? colsum_part : nullptr;
-  const int64_t blocks = (int64_t)((S + 7) / 8) * 8 * p.tiles_m * p.tiles_n;
+  float* colsum_part = a.workspace + (size_t)S * N1 * N2;
+  p.colsum_part = a.colsum_out && !a.colsum_src ? colsum_part : nullptr;
+  COFREE_TRY(plan_colsum(a, &p.extra, sums));
+  const int64_t blocks = (int64_t)((S + 7) / 8) * 8 * p.tiles_m * p.tiles_n + p.extra.blocks;
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "wgrad: grid too large");
   {
-    const bool single = N1 % HBM == 1 || N2a % HBN == 1 || (B2 && N2b % HBN == 1);
-    char pname[96];
-    snprintf(pname, sizeof(pname), "gemm_bf16_kernel<true,%s,false,2,2> N=%dx%d", single ? "true" : "false", (int)N1, (int)N2);
-    ProfScope prof(pname, stream, 2.0 * ((double)M * N1 + (double)M * N2) + 4.0 * (double)N1 * N2,
+    const bool single = N1 % HBM == 1 || a.N2 % HBN == 1 || (a.B2 && a.N2b % HBN == 1);
+    char pname[96] = "";
+    if (profiling()) snprintf(pname, sizeof(pname), "gemm_bf16_kernel<true,%s,false,2,2> N=%dx%d", single ? "true" : "false", (int)N1, (int)N2);
+    ProfScope prof(pname, stream, 2.0 * ((double)M * N1 * (p.extra.X ? 2 : 1) + (double)M * N2) + 4.0 * (double)N1 * N2,
                    2.0 * (double)M * N1 * N2);
     if (single)
       gemm_bf16_kernel<true, true, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
@@ -750,8 +758,8 @@ int32_t launch_wgrad_bf16(const bf16_t* A, int64_t lda, int32_t N1, const bf16_t
       gemm_bf16_kernel<true, false, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
   }
   COFREE_HIP_CHECK(hipGetLastError());
-  COFREE_TRY(launch_split_reduce(workspace, p.c_split_stride, S, C, ldc, N1, N2, accumulate, stream));
-  if (colsum_out) COFREE_TRY(launch_split_reduce(colsum_part, N1, S, colsum_out, N1, 1, N1, accumulate, stream));
+  COFREE_TRY(add_split_sum(sums, a.workspace, p.c_split_stride, S, a.C, a.ldc, N1, N2));
+  if (p.colsum_part) COFREE_TRY(add_split_sum(sums, colsum_part, N1, S, a.colsum_out, N1, 1, N1));
   return COFREE_OK;
 }
 

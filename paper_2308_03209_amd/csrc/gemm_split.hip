@@ -35,6 +35,7 @@
 // instructions, which treat infinities and NaN as IEEE arithmetic does.
 #include <cstdio>
 
+#include "colsum.h"
 #include "common.h"
 
 namespace cofree {
@@ -62,6 +63,7 @@ struct SplitK {
   int64_t n_groups;
   int32_t n_split;     // weight gradients: columns n_split .. of the result come from B2 (0: all from B1)
   float* colsum_part;  // weight gradients: [chunks][M] partial column sums of operand A, or null
+  ColsumK extra;       // weight gradients: workgroups behind the others that sum columns of another matrix
   const float* bias;
   int32_t relu;
   const float* row_scale;
@@ -356,6 +358,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
   int64_t i0, j0, z = 0;
   {
     const int64_t L = blockIdx.x;
+    if constexpr (A_KMAJOR) {
+      if (L >= (int64_t)gridDim.x - p.extra.blocks) {
+        colsum_block<float>(p.extra, L - ((int64_t)gridDim.x - p.extra.blocks), reinterpret_cast<float*>(smem));
+        return;
+      }
+    }
     const int64_t per_group = A_KMAJOR ? p.tiles_m * p.tiles_n : p.tiles_n;
     const int64_t group = (L / (8 * per_group)) * 8 + (L & 7);
     const int64_t member = (L >> 3) % per_group;
@@ -659,8 +667,8 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   p.tiles_n = wide ? tiles128 / 2 : tiles128;
   const int64_t blocks = ((p.n_groups + 7) / 8) * 8 * p.tiles_n;
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "dense: grid too large");
-  char pname[96];
-  snprintf(pname, sizeof(pname), "gemm_split_kernel<false,%s,2,%d> N=%d K=%d", a.b_kmajor ? "true" : "false", wide ? 4 : 2,
+  char pname[96] = "";
+  if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<false,%s,2,%d> N=%d K=%d", a.b_kmajor ? "true" : "false", wide ? 4 : 2,
            (int)a.N, (int)K);
   ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + (double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1)),
                  2.0 * (double)a.M * a.N * (double)K);
@@ -676,50 +684,51 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   return COFREE_OK;
 }
 
-bool wgrad_split_fits(int32_t N1, int32_t N2a, int32_t N2b, int64_t lda, int64_t ldb, int64_t ldb2) {
-  return N1 > 64 && N2a > 64 && (N2b == 0 || N2b >= 4) && split_strides_ok(lda, ldb) && split_strides_ok(0, ldb2);
+bool wgrad_split_fits(const WgradArgs& a) {
+  return a.N1 > 64 && a.N2 > 64 && (!a.B2 || a.N2b >= 4) && split_strides_ok(a.lda, a.ldb) &&
+         split_strides_ok(0, a.B2 ? a.ldb2 : 0);
 }
 
-int32_t launch_wgrad_split(const float* A, int64_t lda, int32_t N1, const float* B, int64_t ldb, int32_t N2a, int64_t M,
-                           float* C, int64_t ldc, int32_t accumulate, float* workspace, hipStream_t stream,
-                           float* colsum_out, const float* B2, int64_t ldb2, int32_t N2b) {
-  const int32_t N2 = N2a + (B2 ? N2b : 0);
+int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
+  const int32_t N1 = a.N1, N2 = a.N2 + (a.B2 ? a.N2b : 0);
   const bool tall = ((N1 + 127) / 128) % 2 == 0;  // 256x128 tiles where they fit the rows as well as 128x128 ones
-  const int32_t S = wgrad_splits(N1, N2, M, tall ? WGRAD_RESIDENT_SPLIT_TALL : WGRAD_RESIDENT_SPLIT, tall ? 256 : 128);
+  const int32_t S = wgrad_splits(N1, N2, a.M, tall ? WGRAD_RESIDENT_SPLIT_TALL : WGRAD_RESIDENT_SPLIT, tall ? 256 : 128);
   SplitK p{};
-  p.A1 = A;
-  p.lda1 = lda;
-  p.B1 = B;
-  p.ldb1 = ldb;
-  p.B2 = B2;
-  p.ldb2 = ldb2;
-  p.n_split = B2 ? N2a : 0;
-  p.K1 = M;
-  p.C = workspace;
+  p.A1 = (const float*)a.A;
+  p.lda1 = a.lda;
+  p.B1 = (const float*)a.B;
+  p.ldb1 = a.ldb;
+  p.B2 = (const float*)a.B2;
+  p.ldb2 = a.ldb2;
+  p.n_split = a.B2 ? a.N2 : 0;
+  p.K1 = a.M;
+  p.C = a.workspace;
   p.ldc = N2;
   p.M = N1;
   p.N = N2;
-  int64_t chunk = (M + S - 1) / S;
+  int64_t chunk = (a.M + S - 1) / S;
   p.k_chunk = ((chunk + SBK - 1) / SBK) * SBK;
   if (p.k_chunk < SBK) p.k_chunk = SBK;
   p.c_split_stride = (int64_t)N1 * N2;
   p.tiles_m = (N1 + (tall ? 255 : 127)) / (tall ? 256 : 128);
   p.tiles_n = (N2 + 127) / 128;
   p.n_groups = S;
-  float* colsum_part = workspace + (size_t)S * N1 * N2;
-  p.colsum_part = colsum_out ? colsum_part : nullptr;
-  const int64_t blocks = (int64_t)((S + 7) / 8) * 8 * p.tiles_m * p.tiles_n;
+  float* colsum_part = a.workspace + (size_t)S * N1 * N2;
+  p.colsum_part = a.colsum_out && !a.colsum_src ? colsum_part : nullptr;
+  COFREE_TRY(plan_colsum(a, &p.extra, sums));
+  const int64_t blocks = (int64_t)((S + 7) / 8) * 8 * p.tiles_m * p.tiles_n + p.extra.blocks;
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "wgrad: grid too large");
   {
-    char pname[96];
-    snprintf(pname, sizeof(pname), "gemm_split_kernel<true,true,%d,2> N=%dx%d", tall ? 4 : 2, (int)N1, (int)N2);
-    ProfScope prof(pname, stream, 4.0 * ((double)M * N1 + (double)M * N2 + (double)N1 * N2), 2.0 * (double)M * N1 * N2);
+    char pname[96] = "";
+    if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<true,true,%d,2> N=%dx%d", tall ? 4 : 2, (int)N1, (int)N2);
+    ProfScope prof(pname, stream, 4.0 * ((double)a.M * N1 * (p.extra.X ? 2 : 1) + (double)a.M * N2 + (double)N1 * N2),
+                   2.0 * (double)a.M * N1 * N2);
     if (tall) gemm_split_kernel<true, true, 4, 2><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
     else gemm_split_kernel<true, true, 2, 2><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
   }
   COFREE_HIP_CHECK(hipGetLastError());
-  COFREE_TRY(launch_split_reduce(workspace, p.c_split_stride, S, C, ldc, N1, N2, accumulate, stream));
-  if (colsum_out) COFREE_TRY(launch_split_reduce(colsum_part, N1, S, colsum_out, N1, 1, N1, accumulate, stream));
+  COFREE_TRY(add_split_sum(sums, a.workspace, p.c_split_stride, S, a.C, a.ldc, N1, N2));
+  if (p.colsum_part) COFREE_TRY(add_split_sum(sums, colsum_part, N1, S, a.colsum_out, N1, 1, N1));
   return COFREE_OK;
 }
 

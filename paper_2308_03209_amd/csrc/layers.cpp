@@ -93,6 +93,16 @@ static bool conv_transform_first(const cofree_layer_desc& d) { return d.d_out < 
 // than the messages the mean is taken after U_a (on d_out columns instead of d_msg).
 static bool sage_combine_first(const cofree_layer_desc& d) { return d.d_out < d.d_msg; }
 
+// Two weight gradients of a layer that share the incoming gradient are one launch when both blocks are whole numbers of
+// 128-column tiles: the incoming gradient is read once (the products are memory bound in bf16; 256x512 over 1.9M nodes
+// 0.72 ms against 2 x 0.40; with a ragged second block the merged launch measured slower).
+static bool sage_merged(const cofree_layer_desc& d) {
+  return !sage_combine_first(d) && d.d_msg % 128 == 0 && d.d_in % 128 == 0;
+}
+static bool conv_merged(const cofree_layer_desc& d) {
+  return d.kind == COFREE_SAGE_CONV && !conv_transform_first(d) && d.d_in % 128 == 0;
+}
+
 static size_t max2(size_t a, size_t b) { return a > b ? a : b; }
 static size_t max3(size_t a, size_t b, size_t c) { return max2(a, max2(b, c)); }
 
@@ -128,8 +138,8 @@ static FwdPlan plan_fwd(const cofree_layer_desc& d, int64_t n, void* ws) {
 
 struct BwdPlan {
   void *dP = nullptr, *dA = nullptr, *dZ = nullptr, *T = nullptr, *params = nullptr;
-  float *wg = nullptr, *cs = nullptr;    // split-k / column-sum partials of the caller's stream
-  float *wg2 = nullptr, *cs2 = nullptr;  // the same for the work on the side stream
+  // partials of up to three weight gradients (they stay until the layer's last launch sums them), of one bias gradient
+  float *wg[3] = {nullptr, nullptr, nullptr}, *cs = nullptr;
   size_t bytes = 0;
 };
 
@@ -141,25 +151,20 @@ static BwdPlan plan_bwd(const cofree_layer_desc& d, int64_t n, void* ws) {
     if (d.dropout_q > 0.f) p.dP = c.take(N * d.d_out * es);
     p.dA = c.take(N * d.d_msg * es);
     p.dZ = c.take(N * d.d_msg * es);
-    const size_t wg_bytes = 4 * max3(wgrad_workspace_floats(d.d_out, d.d_msg + d.d_in, n),
-                                     max2(wgrad_workspace_floats(d.d_out, d.d_msg, n),
-                                          wgrad_workspace_floats(d.d_out, d.d_in, n)),
-                                     wgrad_workspace_floats(d.d_msg, d.d_in, n));
-    const size_t cs_bytes = 4 * colsum_workspace_floats(d.d_out > d.d_msg ? d.d_out : d.d_msg);
-    p.wg = (float*)c.take(wg_bytes);
-    p.cs = (float*)c.take(cs_bytes);
-    p.wg2 = (float*)c.take(wg_bytes);
-    p.cs2 = (float*)c.take(cs_bytes);
+    if (sage_merged(d)) {
+      p.wg[0] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_msg + d.d_in, n));
+    } else {
+      p.wg[0] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
+      p.wg[1] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_msg, n));
+    }
+    p.wg[2] = (float*)c.take(4 * wgrad_workspace_floats(d.d_msg, d.d_in, n));
   } else {
     if (d.dropout_q > 0.f || d.act) p.dP = c.take(N * d.d_out * es);
     // transform first: T = Ahat dPre [n, d_out]; aggregate first: T = norm * (dPre W) [n, d_in]
     p.T = c.take(N * (gcn_transform_first(d) ? d.d_out : d.d_in) * es);
-    const int32_t wg_cols = d.kind == COFREE_SAGE_CONV ? 2 * d.d_in : d.d_in;  // both halves of W in one launch
-    p.wg = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
-    p.cs = (float*)c.take(4 * colsum_workspace_floats(d.d_out));
-    p.wg2 = (float*)c.take(4 * max2(wgrad_workspace_floats(d.d_out, d.d_in, n),
-                                    wgrad_workspace_floats(d.d_out, wg_cols, n)));
-    p.cs2 = (float*)c.take(4 * colsum_workspace_floats(d.d_out));
+    p.wg[0] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, conv_merged(d) ? 2 * d.d_in : d.d_in, n));
+    if (d.kind == COFREE_SAGE_CONV && !conv_merged(d)) p.wg[1] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
+    if (d.kind == COFREE_GCN && gcn_transform_first(d)) p.cs = (float*)c.take(4 * colsum_workspace_floats(d.d_out));
   }
   if (d.dtype == COFREE_BF16) p.params = c.take(param_scratch_bytes(d));
   p.bytes = c.used;
@@ -363,7 +368,6 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
   if (workspace_bytes < p.bytes) return fail(COFREE_ENOMEM, "layer_bwd: workspace too small");
   hipStream_t s = (hipStream_t)stream;
   const int32_t dt = d.dtype;
-  accumulate = accumulate ? 1 : 0;
   auto gemm = [&]() {
     GemmArgs a;
     a.dtype = dt;
@@ -375,6 +379,19 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
     AggArgs a;
     a.g = g;
     a.dtype = dt;
+    return a;
+  };
+  // the weight and bias gradients leave partials, which the layer's last launch sums
+  SplitSums sums;
+  sums.accumulate = accumulate ? 1 : 0;
+  auto wgrad = [&](const void* A, int32_t N1, const void* B, int32_t N2, float* C, int64_t ldc, float* ws) {
+    WgradArgs a;
+    a.dtype = dt;
+    a.M = n;
+    a.A = A; a.lda = N1; a.N1 = N1;
+    a.B = B; a.ldb = N2; a.N2 = N2;
+    a.C = C; a.ldc = ldc;
+    a.workspace = ws;
     return a;
   };
 
@@ -394,16 +411,13 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
     SideStream* side = nullptr;
     hipStream_t s2 = fork_side(s, &side);
     SideJoin joiner{s, side};
-    // dU = dP^T [A | H]: when both blocks are whole numbers of 128-column tiles the two halves are one launch
-    // that reads dP once (the products are memory bound in bf16; 256x512 over 1.9M nodes: 0.72 ms against
-    // 2 x 0.40); else two launches (with a ragged second block the merged launch measured slower)
-    const bool merged_dU = !sage_combine_first(d) && d.d_msg % 128 == 0 && d.d_in % 128 == 0;
-    if (merged_dU)
-      COFREE_TRY(launch_wgrad(dt, dP, d.d_out, d.d_out, A, d.d_msg, d.d_msg, n, grads->U, ldu, accumulate, p.wg2, s2,
-                              grads->bU, H_in, d.d_in, d.d_in));
-    else
-      COFREE_TRY(launch_wgrad(dt, dP, d.d_out, d.d_out, H_in, d.d_in, d.d_in, n, grads->U + d.d_msg, ldu, accumulate,
-                              p.wg2, s2, grads->bU));
+    // dU = dP^T [A | H], in one launch or two
+    const bool merged_dU = sage_merged(d);
+    WgradArgs u = merged_dU ? wgrad(dP, d.d_out, A, d.d_msg, grads->U, ldu, p.wg[0])
+                            : wgrad(dP, d.d_out, H_in, d.d_in, grads->U + d.d_msg, ldu, p.wg[0]);
+    if (merged_dU) u.B2 = H_in, u.ldb2 = u.N2b = d.d_in;
+    u.colsum_out = grads->bU;
+    COFREE_TRY(launch_wgrad(u, &sums, s2));
     if (sage_combine_first(d)) {
       // forward was mean(Z U_a^T): dT = mean^T(dP) on d_out columns, dU_a = dT^T Z,
       // dZ = [Z > 0] * (dT U_a)
@@ -411,8 +425,7 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
       t.X = dP; t.Y = p.dA; t.width = d.d_out; t.ldx = t.ldy = d.d_out;
       t.in_scale = g.inv_deg;
       COFREE_TRY(launch_aggregate(t, s));
-      COFREE_TRY(launch_wgrad(dt, p.dA, d.d_out, d.d_out, Z, d.d_msg, d.d_msg, n, grads->U, ldu, accumulate, p.wg,
-                              s));
+      COFREE_TRY(launch_wgrad(wgrad(p.dA, d.d_out, Z, d.d_msg, grads->U, ldu, p.wg[1]), &sums, s));
       GemmArgs z = gemm();
       z.A1 = p.dA; z.lda1 = d.d_out; z.K1 = d.d_out;
       z.B = params->U; z.ldb = ldu; z.b_kmajor = 1;
@@ -422,7 +435,7 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
     } else {
       // dU_a = dP^T A (side stream as well)
       if (!merged_dU)
-        COFREE_TRY(launch_wgrad(dt, dP, d.d_out, d.d_out, A, d.d_msg, d.d_msg, n, grads->U, ldu, accumulate, p.wg2, s2));
+        COFREE_TRY(launch_wgrad(wgrad(dP, d.d_out, A, d.d_msg, grads->U, ldu, p.wg[1]), &sums, s2));
       // dA / deg = (dP U_a) scaled per destination row, so that the transposed mean is a plain pull
       GemmArgs a = gemm();
       a.A1 = dP; a.lda1 = d.d_out; a.K1 = d.d_out;
@@ -437,8 +450,9 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
       COFREE_TRY(launch_aggregate(t, s));
     }
     // dW = dZ^T H, dbW = column sums of dZ
-    COFREE_TRY(launch_wgrad(dt, p.dZ, d.d_msg, d.d_msg, H_in, d.d_in, d.d_in, n, grads->W, d.d_in, accumulate, p.wg,
-                            s, grads->bW));
+    WgradArgs w = wgrad(p.dZ, d.d_msg, H_in, d.d_in, grads->W, d.d_in, p.wg[2]);
+    w.colsum_out = grads->bW;
+    COFREE_TRY(launch_wgrad(w, &sums, s));
     if (dH_in) {
       // dH = dP U_s + dZ W: one product over the two k-segments [dP | dZ], each with its own parameters
       GemmArgs h = gemm();
@@ -449,7 +463,8 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
       h.C = dH_in; h.ldc = d.d_in; h.N = d.d_in;
       COFREE_TRY(launch_gemm(h, s));
     }
-    return joiner.finish();
+    COFREE_TRY(joiner.finish());
+    return launch_split_sums(sums, s);
   }
 
   // GCN and conventional GraphSAGE: dPre = dH_out gated by the activation and the dropout mask
@@ -469,24 +484,22 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
   if (d.kind == COFREE_SAGE_CONV) {
     const int64_t ldw = 2 * (int64_t)d.d_in;
     // dW_self = dPre^T H and db = column sums of dPre need only dPre: side stream.  Aggregate-first layers
-    // also have dW_neigh = dPre^T M: one launch for both when d_in is a whole number of 128-column tiles
-    const bool merged_dW = !conv_transform_first(d) && d.d_in % 128 == 0;
+    // also have dW_neigh = dPre^T M, in the same launch where the widths allow it
+    const bool merged_dW = conv_merged(d);
+    WgradArgs w = wgrad(dPre, d.d_out, H_in, d.d_in, grads->W, ldw, p.wg[0]);
     if (merged_dW) {
       COFREE_REQUIRE(saved->A, "layer_bwd: saved.A is NULL");
-      COFREE_TRY(launch_wgrad(dt, dPre, d.d_out, d.d_out, H_in, d.d_in, d.d_in, n, grads->W, ldw, accumulate, p.wg2, s2,
-                              grads->bW, saved->A, d.d_in, d.d_in));
-    } else {
-      COFREE_TRY(launch_wgrad(dt, dPre, d.d_out, d.d_out, H_in, d.d_in, d.d_in, n, grads->W, ldw, accumulate, p.wg2, s2,
-                              grads->bW));
+      w.B2 = saved->A, w.ldb2 = w.N2b = d.d_in;
     }
+    w.colsum_out = grads->bW;
+    COFREE_TRY(launch_wgrad(w, &sums, s2));
     if (conv_transform_first(d)) {
       // forward was mean(H W_neigh^T): dT = mean^T(dPre), dW_neigh = dT^T H, dH = dPre W_self + dT W_neigh
       AggArgs t = agg();
       t.X = dPre; t.Y = p.T; t.width = d.d_out; t.ldx = t.ldy = d.d_out;
       t.in_scale = g.inv_deg;
       COFREE_TRY(launch_aggregate(t, s));
-      COFREE_TRY(launch_wgrad(dt, p.T, d.d_out, d.d_out, H_in, d.d_in, d.d_in, n, grads->W + d.d_in, ldw, accumulate,
-                              p.wg, s));
+      COFREE_TRY(launch_wgrad(wgrad(p.T, d.d_out, H_in, d.d_in, grads->W + d.d_in, ldw, p.wg[1]), &sums, s));
       if (dH_in) {
         GemmArgs h = gemm();
         // W_self and W_neigh are column blocks of W: dH = dPre W_self + dT W_neigh is one product over the
@@ -504,8 +517,7 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
       // dH = dPre W_self + mean^T(dPre W_neigh)
       COFREE_REQUIRE(saved->A, "layer_bwd: saved.A is NULL");
       if (!merged_dW)
-        COFREE_TRY(launch_wgrad(dt, dPre, d.d_out, d.d_out, saved->A, d.d_in, d.d_in, n, grads->W + d.d_in, ldw,
-                                accumulate, p.wg2, s2));
+        COFREE_TRY(launch_wgrad(wgrad(dPre, d.d_out, saved->A, d.d_in, grads->W + d.d_in, ldw, p.wg[1]), &sums, s2));
       if (dH_in) {
         GemmArgs h = gemm();
         h.A1 = dPre; h.lda1 = d.d_out; h.K1 = d.d_out;
@@ -516,27 +528,29 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
         AggArgs a = agg();
         a.X = p.T; a.Y = dH_in; a.width = d.d_in; a.ldx = a.ldy = d.d_in;
         COFREE_TRY(launch_aggregate(a, s));
-        GemmArgs w = gemm();
-        w.A1 = dPre; w.lda1 = d.d_out; w.K1 = d.d_out;
-        w.B = params->W; w.ldb = ldw; w.b_kmajor = 1;
-        w.C = dH_in; w.ldc = d.d_in; w.N = d.d_in;
-        w.accumulate = 1;
-        w.gate = in_gate; w.ldg = d.d_in; w.gate_last = 1; w.gate_scale = in_scale;
-        COFREE_TRY(launch_gemm(w, s));
+        GemmArgs self = gemm();
+        self.A1 = dPre; self.lda1 = d.d_out; self.K1 = d.d_out;
+        self.B = params->W; self.ldb = ldw; self.b_kmajor = 1;
+        self.C = dH_in; self.ldc = d.d_in; self.N = d.d_in;
+        self.accumulate = 1;
+        self.gate = in_gate; self.ldg = d.d_in; self.gate_last = 1; self.gate_scale = in_scale;
+        COFREE_TRY(launch_gemm(self, s));
       }
     }
-    return joiner.finish();
+    COFREE_TRY(joiner.finish());
+    return launch_split_sums(sums, s);
   }
-  // db = column sums of dPre: on the way of dW when dPre is its operand, else a kernel of its own
-  if (gcn_transform_first(d)) COFREE_TRY(launch_colsum(dt, dPre, d.d_out, n, d.d_out, grads->bW, accumulate, p.cs2, s2));
   if (gcn_transform_first(d)) {
     // forward was Ahat (H W^T): dT = Ahat dPre, dW = dT^T H, dH = dT W
     AggArgs a = agg();
     a.X = dPre; a.Y = p.T; a.width = d.d_out; a.ldx = a.ldy = d.d_out;
     a.in_scale = g.gcn_norm; a.out_scale = g.gcn_norm; a.self_loop = 1;
     COFREE_TRY(launch_aggregate(a, s));
-    COFREE_TRY(launch_wgrad(dt, p.T, d.d_out, d.d_out, H_in, d.d_in, d.d_in, n, grads->W, d.d_in, accumulate, p.wg,
-                            s));
+    WgradArgs w = wgrad(p.T, d.d_out, H_in, d.d_in, grads->W, d.d_in, p.wg[0]);
+    w.colsum_out = grads->bW;  // db = column sums of dPre, which dW does not read
+    w.colsum_src = dPre;
+    w.colsum_workspace = p.cs;
+    COFREE_TRY(launch_wgrad(w, &sums, s));
     if (dH_in) {
       GemmArgs h = gemm();
       h.A1 = p.T; h.lda1 = d.d_out; h.K1 = d.d_out;
@@ -548,8 +562,9 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
   } else {
     // forward was (Ahat H) W^T: dW = dPre^T (Ahat H), dH = Ahat (dPre W)
     COFREE_REQUIRE(saved->A, "layer_bwd: saved.A is NULL");
-    COFREE_TRY(launch_wgrad(dt, dPre, d.d_out, d.d_out, saved->A, d.d_in, d.d_in, n, grads->W, d.d_in, accumulate,
-                            p.wg2, s2, grads->bW));
+    WgradArgs w = wgrad(dPre, d.d_out, saved->A, d.d_in, grads->W, d.d_in, p.wg[0]);
+    w.colsum_out = grads->bW;
+    COFREE_TRY(launch_wgrad(w, &sums, s2));
     if (dH_in) {
       GemmArgs h = gemm();
       h.A1 = dPre; h.lda1 = d.d_out; h.K1 = d.d_out;
@@ -564,7 +579,8 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
       COFREE_TRY(launch_aggregate(a, s));
     }
   }
-  return joiner.finish();
+  COFREE_TRY(joiner.finish());
+  return launch_split_sums(sums, s);
 }
 
 }  // extern "C"

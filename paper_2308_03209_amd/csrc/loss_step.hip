@@ -420,87 +420,6 @@ __global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ theta, co
   theta[i] -= lr * (mi * inv_c1) / (sqrtf(vi * inv_c2) + eps);
 }
 
-// ---- column sums (bias gradients): fixed-order two-stage reduction --------------------------
-// Stage 1: block s sums its contiguous chunk of rows.  Within a block, lane l of every wavefront
-// owns columns l, l+64, ... (of the block's 256-column panel, blockIdx.y) and wavefront w takes
-// rows w, w+4, ... of the chunk; the four wavefront sums are then added in order through LDS.
-// Stage 2: the per-chunk partials are added in a fixed order (split_reduce_kernel).  No atomics anywhere.
-constexpr int COLSUM_MAX_SPLITS = 1024;
-constexpr int COLSUM_PANEL = 256;
-
-static int colsum_splits(int64_t M) {
-  int64_t s = (M + 31) / 32;  // at least 32 rows per block
-  if (s > COLSUM_MAX_SPLITS) s = COLSUM_MAX_SPLITS;
-  if (s < 1) s = 1;
-  return (int)s;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict__ X, int64_t ld, int64_t M,
-                                                             int32_t N, int64_t rows_per_split,
-                                                             float* __restrict__ partial) {
-  __shared__ float sm[4][COLSUM_PANEL];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int c0 = blockIdx.y * COLSUM_PANEL;
-  const int64_t r0 = (int64_t)blockIdx.x * rows_per_split;
-  int64_t r1 = r0 + rows_per_split;
-  if (r1 > M) r1 = M;
-  // lane l owns the four consecutive columns c0 + 4l .. +3: one wide access per row
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  const int avail = N - (c0 + 4 * lane);
-  if (avail > 0) {
-    // eight rows requested before the first is added (one dependent load per iteration left the loop
-    // waiting on memory latency); the additions keep their row order
-    const T* src = X + c0 + 4 * lane;
-    int64_t r = r0 + wave;
-    if (avail >= 4) {  // all but the lane at a ragged end of the row: plain wide loads, nothing in between
-      for (; r + 28 < r1; r += 32) {
-        float v[8][4];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) ld4(src + (r + 4 * u) * ld, 4, v[u], 0.f);
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) acc[q] += v[u][q];
-      }
-    }
-    for (; r < r1; r += 4) {
-      float v[4];
-      ld4(src + r * ld, avail, v, 0.f);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) acc[q] += v[q];
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) sm[wave][4 * lane + q] = acc[q];
-  __syncthreads();
-  const int c = threadIdx.x;
-  if (c0 + c < N)
-    partial[(int64_t)blockIdx.x * N + c0 + c] = ((sm[0][c] + sm[1][c]) + sm[2][c]) + sm[3][c];
-}
-
-size_t colsum_workspace_floats(int32_t N) { return (size_t)COLSUM_MAX_SPLITS * (size_t)N; }
-
-int32_t launch_colsum(int32_t dtype, const void* X, int64_t ld, int64_t M, int32_t N, float* out,
-                      int32_t accumulate, float* workspace, hipStream_t stream) {
-  COFREE_REQUIRE(X && out && workspace, "colsum: NULL argument");
-  COFREE_REQUIRE(dtype == COFREE_F32 || dtype == COFREE_BF16, "colsum: unknown dtype");
-  COFREE_REQUIRE(N >= 1 && M >= 0 && ld >= N, "colsum: bad shape");
-  const int splits = colsum_splits(M);
-  const int64_t rows_per_split = (M + splits - 1) / splits;
-  const dim3 grid((unsigned)splits, (unsigned)((N + COLSUM_PANEL - 1) / COLSUM_PANEL));
-  {
-    ProfScope prof("colsum_kernels", stream, (dtype == COFREE_F32 ? 4.0 : 2.0) * (double)M * N, (double)M * N);
-    if (dtype == COFREE_F32)
-      colsum_partial_kernel<float><<<grid, 256, 0, stream>>>((const float*)X, ld, M, N, rows_per_split, workspace);
-    else
-      colsum_partial_kernel<bf16_t><<<grid, 256, 0, stream>>>((const bf16_t*)X, ld, M, N, rows_per_split, workspace);
-  }
-  COFREE_HIP_CHECK(hipGetLastError());
-  // stage 2: the same fixed-order reduction over partials as for the weight gradients
-  return launch_split_reduce(workspace, N, splits, out, N, 1, N, accumulate, stream);
-}
-
 // ---- gradient gates: ReLU of the forward output and/or the dropout keep mask ----------------
 template <typename T>
 __global__ __launch_bounds__(256) void mask_grad_kernel(const T* src, const T* __restrict__ gate, T* dst,

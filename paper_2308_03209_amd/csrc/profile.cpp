@@ -38,6 +38,8 @@ hipEvent_t get_event() {
 }
 }  // namespace
 
+bool profiling() { return g_enabled.load(std::memory_order_relaxed) != 0; }
+
 ProfScope::ProfScope(const char* name, hipStream_t stream, double alg_bytes, double alg_flops) {
   if (!g_enabled.load(std::memory_order_relaxed)) return;
   std::lock_guard<std::mutex> lk(g_mu);

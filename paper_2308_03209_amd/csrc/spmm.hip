@@ -618,8 +618,8 @@ static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCos
   const int64_t short_rows = k.n - k.n_block - k.n_wave, per_block = 4 * (64 / tl);
   const int64_t blocks = k.n_block + (k.n_wave + 3) / 4 + (short_rows + per_block - 1) / per_block;
   COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
-  char pname[96];
-  snprintf(pname, sizeof(pname), "aggregate_kernel<%s,%d,%d,%d,%s> width=%d", type_name<T>(), tl, lps, nch,
+  char pname[96] = "";
+  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_kernel<%s,%d,%d,%d,%s> width=%d", type_name<T>(), tl, lps, nch,
            tiny ? "true" : "false", (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   const dim3 grid((unsigned)blocks);
@@ -640,8 +640,8 @@ static int32_t launch_sliced(const AggK<T>& k, int lps, hipStream_t stream, cons
   const int64_t blocks = ((k.n + 3) / 4) * 8;
   COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
   const dim3 grid((unsigned)blocks);
-  char pname[96];
-  snprintf(pname, sizeof(pname), "aggregate_sliced_kernel<%s,%d> width=%d", type_name<T>(), lps, (int)cost.a.width);
+  char pname[96] = "";
+  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_sliced_kernel<%s,%d> width=%d", type_name<T>(), lps, (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   switch (lps) {
     case 8: aggregate_sliced_kernel<T, 8><<<grid, 256, 0, stream>>>(k); break;
@@ -662,8 +662,8 @@ static int32_t launch_hub(const AggK<T>& k, hipStream_t stream, const LaunchCost
   const int panels = (k.width + lps * WIDE - 1) / (lps * WIDE);
   COFREE_REQUIRE(k.n < ((int64_t)1 << 31) && panels < 65536, "aggregate: hub grid too large");
   const dim3 grid((unsigned)k.n, (unsigned)panels);
-  char pname[96];
-  snprintf(pname, sizeof(pname), "aggregate_hub_kernel<%s,%d> width=%d", type_name<T>(), lps, (int)cost.a.width);
+  char pname[96] = "";
+  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_hub_kernel<%s,%d> width=%d", type_name<T>(), lps, (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   switch (lps) {
     case 1: aggregate_hub_kernel<T, 1><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
