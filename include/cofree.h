@@ -277,6 +277,28 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
                          void* dH_in, const cofree_layer_grads* grads, int32_t accumulate, void* workspace,
                          size_t workspace_bytes, void* stream);
 
+/* The layers of a model in one call (Algorithm 1 line 10), for callers whose iteration is bound by the host: the same
+ * work as n_layers calls of cofree_layer_fwd in ascending order, or of cofree_layer_bwd in descending order, on one
+ * workspace that is large enough for each of them.  A layer's H_in is normally the H_out of the layer before, its dH_in
+ * the dH_out of the layer before.  The forward call does not read dH_out, dH_in and grads.  An error of one layer ends the
+ * call; what was enqueued before it runs. */
+typedef struct cofree_layer_call {
+  cofree_layer_desc desc;
+  const void* H_in;
+  void* H_out;
+  cofree_layer_params params;
+  cofree_layer_saved saved;
+  const void* dH_out;
+  void* dH_in;
+  cofree_layer_grads grads;
+} cofree_layer_call;
+int32_t cofree_layers_fwd(const cofree_partition* part, const cofree_masks* masks, int32_t mask_id,
+                          const cofree_layer_call* layers, int32_t n_layers, void* workspace, size_t workspace_bytes,
+                          void* stream);
+int32_t cofree_layers_bwd(const cofree_partition* part, const cofree_masks* masks, int32_t mask_id,
+                          const cofree_layer_call* layers, int32_t n_layers, int32_t accumulate, void* workspace,
+                          size_t workspace_bytes, void* stream);
+
 /* ---------------------------------------------------------------------------------------
  * Reweighted loss (Eq. 3):  L = c * sum_{j in V[i]} w_j * CE(softmax(logits_j), labels_j)
  * with w = Degree-Aware Reweighting weights (COFREE_W_DAR), ones (COFREE_W_NONE) or a device

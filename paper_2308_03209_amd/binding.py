@@ -42,7 +42,7 @@ EXPORTS = [
     "cofree_dropedge_k", "cofree_masks_free", "cofree_masks_count", "cofree_masks_host_bits",
     "cofree_masks_host_graph", "cofree_dropedge_pick",
     "cofree_aggregate",
-    "cofree_layer_workspace_bytes", "cofree_layer_fwd", "cofree_layer_bwd",
+    "cofree_layer_workspace_bytes", "cofree_layer_fwd", "cofree_layer_bwd", "cofree_layers_fwd", "cofree_layers_bwd",
     "cofree_loss_workspace_bytes", "cofree_loss_weighted", "cofree_loss_weighted_static", "cofree_loss_bce_weighted",
     "cofree_grad_gap", "cofree_step", "cofree_dense_nt_f32",
     "cofree_profile_enable", "cofree_profile_read",
@@ -76,6 +76,11 @@ class LayerGrads(C.Structure):
 
 class LayerSaved(C.Structure):
     _fields_ = [("Z", C.c_void_p), ("A", C.c_void_p)]
+
+
+class LayerCall(C.Structure):
+    _fields_ = [("desc", LayerDesc), ("H_in", C.c_void_p), ("H_out", C.c_void_p), ("params", LayerParams),
+                ("saved", LayerSaved), ("dH_out", C.c_void_p), ("dH_in", C.c_void_p), ("grads", LayerGrads)]
 
 
 def _load() -> C.CDLL:
@@ -113,6 +118,8 @@ def _load() -> C.CDLL:
         "cofree_layer_fwd": (i32, [vp, vp, i32, P(LayerDesc), vp, P(LayerParams), vp, P(LayerSaved), vp, sz, vp]),
         "cofree_layer_bwd": (i32, [vp, vp, i32, P(LayerDesc), vp, vp, P(LayerParams), P(LayerSaved), vp, vp,
                                    P(LayerGrads), i32, vp, sz, vp]),
+        "cofree_layers_fwd": (i32, [vp, vp, i32, vp, i32, vp, sz, vp]),
+        "cofree_layers_bwd": (i32, [vp, vp, i32, vp, i32, i32, vp, sz, vp]),
         "cofree_loss_workspace_bytes": (sz, []),
         "cofree_loss_weighted": (i32, [vp, i32, vp, vp, i32, vp, vp, i32, f32, vp, vp, vp, sz, vp]),
         "cofree_loss_weighted_static": (i32, [vp, i32, vp, vp, i32, vp, vp, i32, f32, vp, vp, vp]),
@@ -161,7 +168,8 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream() -> Optional[int]:
-    return torch.cuda.current_stream().cuda_stream or None
+    # the handle alone: building torch.cuda.current_stream()'s object costs as much as a kernel launch
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
 
 
 class Partition:
@@ -346,6 +354,17 @@ def layer_bwd(part: Partition, masks: Optional[Masks], mask_id: int, desc: Layer
     _check(lib.cofree_layer_bwd(part.handle, _mh(masks), mask_id, C.byref(desc), _ptr(H_in), _ptr(H_out),
                                 C.byref(prm), C.byref(sv), _ptr(dH_out), _ptr(dH_in), C.byref(gr),
                                 1 if accumulate else 0, _ptr(workspace), ws_bytes, _stream()))
+
+
+def layers_fwd(part: Partition, masks: Optional[Masks], mask_id: int, calls, workspace) -> None:
+    """calls: a ctypes array of LayerCall, one per layer."""
+    _check(lib.cofree_layers_fwd(part.handle, _mh(masks), mask_id, calls, len(calls), workspace.data_ptr(),
+                                 workspace.nbytes, _stream()))
+
+
+def layers_bwd(part: Partition, masks: Optional[Masks], mask_id: int, calls, accumulate: bool, workspace) -> None:
+    _check(lib.cofree_layers_bwd(part.handle, _mh(masks), mask_id, calls, len(calls), 1 if accumulate else 0,
+                                 workspace.data_ptr(), workspace.nbytes, _stream()))
 
 
 def loss_workspace_bytes() -> int:

@@ -583,4 +583,28 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
   return launch_split_sums(sums, s);
 }
 
+int32_t cofree_layers_fwd(const cofree_partition* part, const cofree_masks* masks, int32_t mask_id,
+                          const cofree_layer_call* layers, int32_t n_layers, void* workspace, size_t workspace_bytes,
+                          void* stream) {
+  COFREE_REQUIRE(n_layers >= 0 && (n_layers == 0 || layers), "layers_fwd: bad layer list");
+  for (int32_t l = 0; l < n_layers; ++l) {
+    const cofree_layer_call& c = layers[l];
+    COFREE_TRY(cofree_layer_fwd(part, masks, mask_id, &c.desc, c.H_in, &c.params, c.H_out, &c.saved, workspace,
+                                workspace_bytes, stream));
+  }
+  return COFREE_OK;
+}
+
+int32_t cofree_layers_bwd(const cofree_partition* part, const cofree_masks* masks, int32_t mask_id,
+                          const cofree_layer_call* layers, int32_t n_layers, int32_t accumulate, void* workspace,
+                          size_t workspace_bytes, void* stream) {
+  COFREE_REQUIRE(n_layers >= 0 && (n_layers == 0 || layers), "layers_bwd: bad layer list");
+  for (int32_t l = n_layers - 1; l >= 0; --l) {
+    const cofree_layer_call& c = layers[l];
+    COFREE_TRY(cofree_layer_bwd(part, masks, mask_id, &c.desc, c.H_in, c.H_out, &c.params, &c.saved, c.dH_out, c.dH_in,
+                                &c.grads, accumulate, workspace, workspace_bytes, stream));
+  }
+  return COFREE_OK;
+}
+
 }  // extern "C"

@@ -49,6 +49,8 @@ class Model:
             self.slices.append(sl)
         self.theta = torch.zeros(total, dtype=torch.float32, device=device)
         self.grad = torch.zeros(total, dtype=torch.float32, device=device)
+        # byte offset of every tensor in the flat buffers, per layer (W, bW, U, bU; None where the kind has none)
+        self.offsets = [tuple(4 * sl[k][0] if k in sl else None for k in ("W", "bW", "U", "bU")) for sl in self.slices]
         self.m = None
         self.v = None
         self.t = 0
@@ -140,6 +142,8 @@ class PartitionRunner:
         # a layer's input gradient is dead once the layer below has consumed it, so two buffers alternate
         self.dH = [None] + [buf(("dH", l % 2), d_in) for l, (d_in, _, _) in enumerate(model.dims[1:], start=1)]
         self.dlogits = buf(("dlogits", 0), model.dims[-1][2])
+        self._calls = (B.LayerCall * L)()
+        self._calls_for = None   # settings the descriptors in _calls were made from
         self.loss = torch.zeros(1, dtype=torch.float32, device=device)
         ws = B.loss_workspace_bytes()
         for l in range(L):
@@ -163,14 +167,39 @@ class PartitionRunner:
         return B.layer_desc(_KIND[self.model.kind], d_in, d_msg, d_out, act, q, l, self.dseed, epoch, self.dtype_code,
                             flags, q_below)
 
+    def _layer_calls(self):
+        settings = (self.q, self.dseed, self.fuse_gates, self.dtype_code)
+        if settings != self._calls_for:
+            for l, c in enumerate(self._calls):
+                c.desc = self.desc(l, 0)
+            self._calls_for = settings
+        return self._calls
+
+    def _fill(self, c: B.LayerCall, l: int, epoch: int) -> None:
+        """Addresses of layer l's buffers and parameters, taken anew for every call."""
+        c.desc.epoch = epoch
+        c.H_in, c.H_out = self.H[l].data_ptr(), self.H[l + 1].data_ptr()
+        saved = self.saved[l]
+        if "Z" in saved:
+            c.saved.Z = saved["Z"].data_ptr()
+        if "A" in saved:
+            c.saved.A = saved["A"].data_ptr()
+        W, bW, U, bU = self.model.offsets[l]
+        theta, p = self.model.theta.data_ptr(), c.params
+        p.W, p.bW = theta + W, theta + bW
+        if U is not None:
+            p.U, p.bU = theta + U, theta + bU
+
     def forward(self, X: torch.Tensor, mask_id: int = 0, epoch: int = 0) -> torch.Tensor:
         if X.dtype != self.torch_dtype:
             raise ValueError(f"features must be {self.torch_dtype}")
+        if not X.is_contiguous():
+            raise ValueError("tensor must be contiguous")
         self.H[0] = X
-        prm = self.model.params
-        for l in range(len(self.model.dims)):
-            B.layer_fwd(self.part, self.masks, mask_id, self.desc(l, epoch), self.H[l], prm[l], self.H[l + 1],
-                        self.saved[l], self.workspace)
+        calls = self._layer_calls()
+        for l, c in enumerate(calls):
+            self._fill(c, l, epoch)
+        B.layers_fwd(self.part, self.masks, mask_id, calls, self.workspace)
         return self.H[-1]
 
     def loss_backward(self, labels: torch.Tensor, weight_kind: int = B.W_DAR, scale_c: float = 1.0,
@@ -180,13 +209,20 @@ class PartitionRunner:
         loss_fn = B.loss_weighted if self.loss_kind == "softmax_ce" else B.loss_bce_weighted
         loss_fn(self.part, weight_kind, custom_w, self.H[-1], labels, train_mask, C, scale_c, self.loss,
                 self.dlogits, self.workspace, self.dtype_code)
-        prm, grd = self.model.params, self.model.grads
-        d_out = self.dlogits
-        for l in range(len(self.model.dims) - 1, -1, -1):
-            d_in = self.dH[l] if l > 0 else None
-            B.layer_bwd(self.part, self.masks, mask_id, self.desc(l, epoch), self.H[l], self.H[l + 1], prm[l],
-                        self.saved[l], d_out, d_in, grd[l], accumulate, self.workspace)
-            d_out = d_in
+        grad = self.model.grad.data_ptr()
+        d_out = self.dlogits.data_ptr()
+        calls = self._layer_calls()
+        for l in range(len(calls) - 1, -1, -1):
+            c = calls[l]
+            self._fill(c, l, epoch)
+            c.dH_out = d_out
+            c.dH_in = d_out = self.dH[l].data_ptr() if l > 0 else None
+            W, bW, U, bU = self.model.offsets[l]
+            g = c.grads
+            g.W, g.bW = grad + W, grad + bW
+            if U is not None:
+                g.U, g.bU = grad + U, grad + bU
+        B.layers_bwd(self.part, self.masks, mask_id, calls, accumulate, self.workspace)
 
     def iteration(self, X, labels, epoch: int, mask_seed: int = 0, weight_kind: int = B.W_DAR,
                   scale_c: float = 1.0, accumulate: bool = False, custom_w=None) -> int:
