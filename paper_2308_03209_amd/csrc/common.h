@@ -370,6 +370,9 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream);
 bool wgrad_split_fits(const WgradArgs& a);
 int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
 int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream);
+// bfloat16 products whose parameters fit LDS (gemm_bf16_resident.hip)
+bool gemm_resident_fits(const GemmArgs& a);
+int32_t launch_gemm_resident(const GemmArgs& a, hipStream_t stream);
 int32_t launch_wgrad_bf16(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
 
 // dst[r,c] = src[r,c] * [gate[r,c] > 0 if gate] * keep(r,c)/(1-q) if q > 0   (`dtype`, contiguous [M,N];

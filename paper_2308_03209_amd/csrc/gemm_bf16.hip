@@ -1,5 +1,6 @@
 // Dense feature transforms for bfloat16-stored activations: bf16 operands on the matrix cores
-// (v_mfma_f32_32x32x16_bf16), float32 accumulation, bf16 or float32 results.
+// (v_mfma_f32_32x32x16_bf16), float32 accumulation, bf16 or float32 results.  Weight gradients, and the products with
+// parameters that gemm_bf16_resident.h does not take.
 //
 // Same tiling as the float32 kernel (128x128 block tile, four wavefronts 2x2, each 64x64 as 2x2
 // MFMA accumulators) with k-tiles of 32; large A B^T products use a 256x256 tile of sixteen wavefronts.  LDS tiles are stored row-major [i][k] with rows padded
@@ -641,6 +642,7 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
                    "dense: ldb too small");
   else
     COFREE_REQUIRE(a.b_kmajor ? a.ldb >= a.N : a.ldb >= K, "dense: ldb too small");
+  if (gemm_resident_fits(a) && !getenv("COFREE_BF16_TILE")) return launch_gemm_resident(a, stream);
   const int64_t ldd = pad8(K);
   bf16_t* Wb = (bf16_t*)a.param_scratch;
   {
