@@ -259,9 +259,22 @@ __device__ inline void finish_row(const AggK<T>& p, int64_t row, int c0, int fir
     }
   }
   if (p.bias) {
+    // A window of a row that is not TINY exists whole, so its biases are wide loads without a condition: eight
+    // conditional ones, each with its own wait, held a launch back by half (2.35M rows of 172 bfloat16 1615 -> 1222 us,
+    // 100k rows of 128 43.8 -> 27.0).
+    const float* const b = p.bias + (p.col0 + c0);
+    if constexpr (TINY) {
 #pragma unroll
-    for (int i = 0; i < VEC; ++i)
-      if (i < avail) acc[i] += p.bias[p.col0 + c0 + i];
+      for (int i = 0; i < VEC; ++i)
+        if (i < avail) acc[i] += b[i];
+    } else {
+#pragma unroll
+      for (int q = 0; q < VEC / 4; ++q) {
+        const f32x4u t = reinterpret_cast<const f32x4u*>(b)[q];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[4 * q + i] += t[i];
+      }
+    }
   }
   if (p.relu_out) {
 #pragma unroll
