@@ -702,17 +702,6 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   k.ldx = a.ldx;
   k.ldy = a.ldy;
   k.in_scale = a.in_scale;
-  // Per-source factors of a large graph are read per entry: the per-node vector no longer stays in L2 there, and
-  // every neighbour's factor would cost a memory access of its own beside the row it scales (28M-node partition,
-  // 256-wide bfloat16 launch: 16.7 ms with the per-node gather, 15.9 ms with the per-entry stream; no difference
-  // at 1.9M nodes).  COFREE_AGG_ENTRY_SCALE = 0 / 1 forces one or the other.
-  k.in_vals = nullptr;
-  if (a.in_scale) {
-    bool per_entry = a.g.n >= AGG_ENTRY_SCALE_MIN_NODES;
-    if (const char* env = getenv("COFREE_AGG_ENTRY_SCALE")) per_entry = atoi(env) != 0;
-    if (per_entry && a.in_scale == a.g.inv_deg) k.in_vals = a.g.val_inv_deg;
-    if (per_entry && a.in_scale == a.g.gcn_norm) k.in_vals = a.g.val_gcn_norm;
-  }
   k.out_scale = a.out_scale;
   k.self_loop = a.self_loop;
   k.ld_relu = a.ld_relu;
@@ -753,6 +742,19 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
       sliced = false;
     }
     if (v == 8) sliced = sliceable;
+  }
+
+  // Per-source factors of a large graph are read per entry: the per-node vector no longer stays in L2 there, and
+  // every neighbour's factor would cost a memory access of its own beside the row it scales (28M-node partition,
+  // 256-wide bfloat16 launch: 16.7 ms with the per-node gather, 15.9 ms with the per-entry stream; no difference
+  // at 1.9M nodes), and so are those of column slices, where each of a row's eight wavefronts would gather the factors again
+  // (115k nodes, 3.5M entries, 256-wide float32: with the gather a four-layer training step took 5.36 ms, with the stream 5.07).  COFREE_AGG_ENTRY_SCALE = 0 / 1 forces one or the other.
+  k.in_vals = nullptr;
+  if (a.in_scale) {
+    bool per_entry = sliced || a.g.n >= AGG_ENTRY_SCALE_MIN_NODES;
+    if (const char* env = getenv("COFREE_AGG_ENTRY_SCALE")) per_entry = atoi(env) != 0;
+    if (per_entry && a.in_scale == a.g.inv_deg) k.in_vals = a.g.val_inv_deg;
+    if (per_entry && a.in_scale == a.g.gcn_norm) k.in_vals = a.g.val_gcn_norm;
   }
 
   // 1. hub rows
