@@ -14,6 +14,12 @@
 // behind them, so that the stores are not waited for (8 waves do not hide that); whole 128-byte lines of C per store
 // instruction; a row factor that arrives with the rows; no register spilled (a scratch frame costs 20 %).
 //
+// Parameters beyond 128 KB are cut by columns into two to four parts, each resident in its own workgroups.  The workgroups
+// of one group of rows lie next to each other on one XCD and walk the rows alike, so the rows come from memory once and
+// from that XCD's L2 for the others.  Measured, 1.88M rows to 256 columns, against the tiled
+// kernel: K = 356 684 -> 598 us, 303 649 -> 481, 512 714 -> 726 and, with two parameter matrices, 717 -> 711 (the tiled kernel
+// also needs one or two launches of 5 us that convert its parameters).
+
 // The first matrix operand is the parameter block, the second the rows: a lane then holds four consecutive columns of
 // one row at a time, and passes 32 x 32 results through 4 KB of LDS of its wavefront (float32, 16-byte pieces permuted
 // by row so that both directions are free of bank conflicts) to hold eight consecutive columns.
@@ -43,6 +49,8 @@ struct ResidentK {
   bf16_t* C;
   int64_t ldc, M;
   int32_t N;
+  int32_t parts;  // column parts
+  int64_t teams;  // groups of `parts` workgroups that share their rows
   const float* bias;
   int32_t relu;
   const float* row_scale;
@@ -62,7 +70,7 @@ __device__ inline u32x4u shift_halves(const u32x4u& w, int halves) {
   return u32x4u{(uint32_t)rl, (uint32_t)(rl >> 32), (uint32_t)rh, (uint32_t)(rh >> 32)};
 }
 
-// NB: 32-column blocks, 32 (NB - 1) < N <= 32 NB (two for N = 32); NCH: pieces of 64 k over both segments.
+// NB: 32-column blocks of a part, 32 (NB - 1) <= its columns <= 32 NB (two for 32 columns); NCH: pieces of 64 k over both segments.
 // LDS parameters: [k-group of 8][column][8 bfloat16]: a matrix operand is 512 contiguous bytes per half wavefront.
 // EXTRAS: the result is gated by another matrix or accumulated.
 template <int NB, int NCH, bool EXTRAS>
@@ -75,10 +83,18 @@ __global__ __launch_bounds__(64 * RES_WAVES) __attribute__((amdgpu_waves_per_eu(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 5, r = lane & 31;
 
-  // Block b of 32 result columns starts at column 32 b, the last one at N - 32: where N is no
-  // multiple of 32 the columns that two blocks share are computed twice, alike, so that every lane writes eight
+  // the workgroup's columns n0 .. n1 - 1 and its group of rows (uniform over the block)
+  int team = blockIdx.x, n0 = 0, n1 = p.N;
+  if (p.parts > 1) {
+    const int on_xcd = blockIdx.x >> 3, part = on_xcd % p.parts;
+    team = (on_xcd / p.parts) * 8 + (blockIdx.x & 7);
+    n0 = part * p.N / p.parts;
+    n1 = (part + 1) * p.N / p.parts;
+  }
+  // Block b of 32 result columns starts at column n0 + 32 b, the last one at n1 - 32: where the columns are no
+  // multiple of 32 those that two blocks share are computed twice, alike, so that every lane writes eight
   // existing columns.  column_of: the column at place m of the parameters in LDS.
-  const auto block_col = [&](int b) { return 32 * b < p.N - 32 ? 32 * b : p.N - 32; };
+  const auto block_col = [&](int b) { return n0 + 32 * b < n1 - 32 ? n0 + 32 * b : n1 - 32; };
   const auto column_of = [&](int m) { return (int64_t)(block_col(m >> 5) + (m & 31)); };
 
   // ---- parameters: 8 columns x 8 k-groups per wavefront and step, four steps requested at a time
@@ -117,11 +133,11 @@ __global__ __launch_bounds__(64 * RES_WAVES) __attribute__((amdgpu_waves_per_eu(
   }
   __syncthreads();
 
-  // ---- rows: wavefront w of workgroup b takes the 32-row tiles w * workgroups + b, then every 8 * workgroups-th.
+  // ---- rows: wavefront w of team b takes the 32-row tiles w * teams + b, then every 8 * teams-th.
   // The last tile ends with the matrix: the rows it shares with the tile before are computed twice, alike (not where
   // results are added to C, see below).
-  const int64_t tiles = (p.M + 31) / 32, stride = (int64_t)RES_WAVES * gridDim.x;
-  int64_t t = (int64_t)__builtin_amdgcn_readfirstlane(wave) * gridDim.x + blockIdx.x;
+  const int64_t tiles = (p.M + 31) / 32, stride = (int64_t)RES_WAVES * p.teams;
+  int64_t t = (int64_t)__builtin_amdgcn_readfirstlane(wave) * p.teams + team;
   if (t >= tiles) return;
   const unsigned char* const bs = smem + (g * COLS + r) * 16;
   float* const st = reinterpret_cast<float*>(smem + B_BYTES + wave * 4096);

@@ -1,4 +1,5 @@
 // Launch of the products whose parameters fit LDS, and their instances for at most 128 columns.
+#include <algorithm>
 #include <cstdio>
 
 #include "gemm_bf16_resident.h"
@@ -17,11 +18,21 @@ bool launch_resident_narrow(int nb, int nch, bool extras, dim3 grid, hipStream_t
 static int pieces(int32_t K) { return (K + 63) / 64; }
 static int col_blocks(int32_t N) { return N <= 64 ? 2 : (N <= 256 ? (N + 31) / 32 : 0); }
 
-// Parameters of at most 128 KB in LDS (and at most 512 k), segments of at least eight k.
+// Column parts of at most 128 KB of parameters each: the fewest, up to four (0: they do not fit).
+static int column_parts(int32_t N, int nch) {
+  for (int parts = 1; parts <= 4; ++parts) {
+    const int nb = col_blocks((N + parts - 1) / parts);
+    if (nb > 0 && nb * nch <= 32) return parts;
+  }
+  return 0;
+}
+
+// At most 512 k, segments of at least eight, and parameters of at most four column parts.
 bool gemm_resident_fits(const GemmArgs& a) {
-  const int nb = col_blocks(a.N), nch = pieces(a.K1) + (a.K2 > 0 ? pieces(a.K2) : 0);
+  const int nch = pieces(a.K1) + (a.K2 > 0 ? pieces(a.K2) : 0);
   const int64_t strides = a.lda1 | a.lda2 | a.ldc | a.ldg;  // 32-bit offsets inside a tile of 32 rows
-  return nb > 0 && a.N >= 32 && a.M >= 32 && strides < ((int64_t)1 << 26) && a.K1 >= 8 && (a.K2 == 0 || a.K2 >= 8) && nch <= 8 && nb * nch <= 32;
+  return a.N >= 32 && a.M >= 32 && strides < ((int64_t)1 << 26) && a.K1 >= 8 && (a.K2 == 0 || a.K2 >= 8) && nch <= 8 &&
+         column_parts(a.N, nch) > 0;
 }
 
 int32_t launch_gemm_resident(const GemmArgs& a, hipStream_t stream) {
@@ -51,9 +62,14 @@ int32_t launch_gemm_resident(const GemmArgs& a, hipStream_t stream) {
   p.relu_last = a.relu_last;
   p.gate_last = a.gate_last;
   p.gate_scale = a.gate ? a.gate_scale : 1.f;
-  const int nb = col_blocks(a.N), nch = pieces(a.K1) + (a.K2 > 0 ? pieces(a.K2) : 0);
+  const int nch = pieces(a.K1) + (a.K2 > 0 ? pieces(a.K2) : 0);
   const int64_t K = (int64_t)a.K1 + a.K2, tiles = (a.M + 31) / 32;
-  const dim3 grid((unsigned)(tiles < RES_CUS ? tiles : RES_CUS));
+  p.parts = column_parts(a.N, nch);
+  const int nb = col_blocks((a.N + p.parts - 1) / p.parts);
+  // a workgroup per CU; with several parts the teams come eight at a time, one on each XCD
+  p.teams = tiles < RES_CUS ? tiles : RES_CUS;
+  if (p.parts > 1) p.teams = 8 * std::min<int64_t>((tiles + 7) / 8, RES_CUS / 8 / p.parts);
+  const dim3 grid((unsigned)(p.teams * p.parts));
   char pname[96] = "";
   if (profiling()) snprintf(pname, sizeof(pname), "gemm_bf16_resident_kernel<%d,%d> N=%d K=%d", nb, nch, (int)a.N, (int)K);
   ProfScope prof(pname, stream, 2.0 * ((double)a.M * K + (double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1)),
