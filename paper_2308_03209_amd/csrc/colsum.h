@@ -40,9 +40,9 @@ __device__ inline float colsum_ld1(const bf16_t* p) { return bf16_to_f32(*p); }
 // 4 * 64 / LPR row groups of the workgroup take rows in turn, eight requested before the first is added (one dependent
 // load per iteration leaves the loop waiting on memory), and are added in order through LDS (sm: 1024 floats).
 template <typename T>
-__device__ inline void colsum_block(const ColsumK& p, int64_t b, float* sm) {
+__device__ inline void colsum_block(const ColsumK& p, int64_t b, float* sm, int tid) {
   const int lpr = p.N <= 64 ? 16 : (p.N <= 128 ? 32 : 64), groups = 256 / lpr;
-  const int quad = threadIdx.x % lpr, grp = threadIdx.x / lpr;
+  const int quad = tid % lpr, grp = tid / lpr;
   const int64_t split = b / p.panels;
   const int32_t c0 = (int32_t)(b % p.panels) * 256;
   const int64_t r0 = split * p.rows_per_split;
@@ -71,7 +71,7 @@ __device__ inline void colsum_block(const ColsumK& p, int64_t b, float* sm) {
   }
   *reinterpret_cast<float4*>(sm + (grp * lpr + quad) * 4) = make_float4(acc[0], acc[1], acc[2], acc[3]);
   __syncthreads();
-  const int c = threadIdx.x;
+  const int c = tid;
   if (c < 4 * lpr && c0 + c < p.N) {
     float t = sm[c];
     for (int g = 1; g < groups; ++g) t += sm[g * lpr * 4 + c];

@@ -355,7 +355,7 @@ struct WgradArgs {
   float* colsum_workspace = nullptr;
 };
 int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
-size_t wgrad_workspace_floats(int32_t N1, int32_t N2, int64_t M);
+size_t wgrad_workspace_floats(int32_t N1, int32_t N2, int64_t M, int32_t N2b = 0);
 size_t colsum_workspace_floats(int32_t N);
 // shared by the kernels; resident = workgroups of the kernel the chip holds at once (float32: three per CU; bfloat16:
 // two; float32 on the bfloat16 matrix cores: 256x128 tiles at two per CU, 128x128 at three)
@@ -374,6 +374,10 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream);
 bool gemm_resident_fits(const GemmArgs& a);
 int32_t launch_gemm_resident(const GemmArgs& a, hipStream_t stream);
 int32_t launch_wgrad_bf16(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
+// bfloat16 weight gradients of at least eight rows and columns (wgrad_bf16.hip); narrower ones stay in gemm_bf16.hip
+bool wgrad_bf16_fits(int32_t N1, int32_t N2, int32_t N2b);
+size_t wgrad_bf16_workspace_floats(int32_t N1, int32_t N2, int32_t N2b, int64_t M);
+int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
 
 // dst[r,c] = src[r,c] * [gate[r,c] > 0 if gate] * keep(r,c)/(1-q) if q > 0   (`dtype`, contiguous [M,N];
 // dst may be src)

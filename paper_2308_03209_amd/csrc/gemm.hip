@@ -340,7 +340,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
     const int64_t L = blockIdx.x;
     if constexpr (A_KMAJOR) {
       if (L >= (int64_t)gridDim.x - p.extra.blocks) {
-        colsum_block<float>(p.extra, L - ((int64_t)gridDim.x - p.extra.blocks), smem);
+        colsum_block<float>(p.extra, L - ((int64_t)gridDim.x - p.extra.blocks), smem, threadIdx.x);
         return;
       }
     }
@@ -725,20 +725,24 @@ int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident, int32_
 }
 
 // enough for either storage type
-size_t wgrad_workspace_floats(int32_t N1, int32_t N2, int64_t M) {
+size_t wgrad_workspace_floats(int32_t N1, int32_t first, int64_t M, int32_t N2b) {
+  const int32_t N2 = first + N2b;
   const int32_t s32 = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_F32), s16 = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_BF16);
   const int32_t tall = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_SPLIT_TALL, 256);
-  return (size_t)std::max(std::max(s32, s16), tall) * ((size_t)N1 * (size_t)N2 + (size_t)N1);
+  return std::max((size_t)std::max(std::max(s32, s16), tall) * ((size_t)N1 * (size_t)N2 + (size_t)N1),
+                  wgrad_bf16_workspace_floats(N1, first, N2b, M));
 }
 
 int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
   COFREE_REQUIRE(a.A && a.B && a.C && a.workspace, "wgrad: NULL operand");
   COFREE_REQUIRE(a.N1 >= 1 && a.N2 >= 1 && a.M >= 0, "wgrad: bad shape");
-  COFREE_REQUIRE(!a.B2 || (a.N2b >= 1 && a.N2 % BN == 0 && a.ldb2 >= a.N2b), "wgrad: bad second matrix");
+  const bool bf16_rows = a.dtype == COFREE_BF16 && wgrad_bf16_fits(a.N1, a.N2, a.B2 ? a.N2b : 0);
+  COFREE_REQUIRE(!a.B2 || (a.N2b >= 1 && (a.N2 % BN == 0 || bf16_rows) && a.ldb2 >= a.N2b), "wgrad: bad second matrix");
   const int32_t N1 = a.N1, N2 = a.N2 + (a.B2 ? a.N2b : 0);  // rows and columns of the result
   const int64_t M = a.M;
   COFREE_REQUIRE(a.lda >= N1 && a.ldb >= a.N2 && a.ldc >= N2, "wgrad: leading dimension too small");
-  if (a.dtype == COFREE_BF16) return launch_wgrad_bf16(a, sums, stream);
+  if (a.dtype == COFREE_BF16)
+    return bf16_rows ? launch_wgrad_bf16_rows(a, sums, stream) : launch_wgrad_bf16(a, sums, stream);
   COFREE_REQUIRE(a.dtype == COFREE_F32, "wgrad: unknown dtype");
   if (wgrad_split_fits(a)) return launch_wgrad_split(a, sums, stream);
   const int32_t S = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_F32);

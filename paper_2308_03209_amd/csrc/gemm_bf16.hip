@@ -415,7 +415,7 @@ __global__ __launch_bounds__(64 * WM * WN)
     const int64_t L = blockIdx.x;
     if constexpr (WGRAD) {
       if (L >= (int64_t)gridDim.x - p.extra.blocks) {
-        colsum_block<bf16_t>(p.extra, L - ((int64_t)gridDim.x - p.extra.blocks), reinterpret_cast<float*>(smem));
+        colsum_block<bf16_t>(p.extra, L - ((int64_t)gridDim.x - p.extra.blocks), reinterpret_cast<float*>(smem), threadIdx.x);
         return;
       }
     }

@@ -360,7 +360,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
     const int64_t L = blockIdx.x;
     if constexpr (A_KMAJOR) {
       if (L >= (int64_t)gridDim.x - p.extra.blocks) {
-        colsum_block<float>(p.extra, L - ((int64_t)gridDim.x - p.extra.blocks), reinterpret_cast<float*>(smem));
+        colsum_block<float>(p.extra, L - ((int64_t)gridDim.x - p.extra.blocks), reinterpret_cast<float*>(smem), threadIdx.x);
         return;
       }
     }

@@ -99,13 +99,18 @@ static bool conv_gathers_grad(const cofree_layer_desc& d) { return d.d_out <= d.
 static bool sage_combine_first(const cofree_layer_desc& d) { return d.d_out < d.d_msg; }
 
 // Two weight gradients of a layer that share the incoming gradient are one launch when both blocks are whole numbers of
-// 128-column tiles: the incoming gradient is read once (the products are memory bound in bf16; 256x512 over 1.9M nodes
-// 0.72 ms against 2 x 0.40; with a ragged second block the merged launch measured slower).
+// 128-column tiles, or in bfloat16 when they fit one tile: the incoming gradient is read once (the products are memory
+// bound in bf16; 256x512 over 1.9M nodes 0.72 ms against 2 x 0.40; with a ragged second block in a tile of its own the
+// merged launch measured slower; 128x(100+100) 379 -> 243 us).
+static bool merged_widths(const cofree_layer_desc& d, int32_t first, int32_t second) {
+  if (first % 128 == 0 && second % 128 == 0) return true;
+  return d.dtype == COFREE_BF16 && wgrad_bf16_fits(d.d_out, first, second) && (first + 7) / 8 + (second + 7) / 8 <= 32;
+}
 static bool sage_merged(const cofree_layer_desc& d) {
-  return !sage_combine_first(d) && d.d_msg % 128 == 0 && d.d_in % 128 == 0;
+  return !sage_combine_first(d) && merged_widths(d, d.d_msg, d.d_in);
 }
 static bool conv_merged(const cofree_layer_desc& d) {
-  return d.kind == COFREE_SAGE_CONV && !conv_transform_first(d) && d.d_in % 128 == 0;
+  return d.kind == COFREE_SAGE_CONV && !conv_transform_first(d) && merged_widths(d, d.d_in, d.d_in);
 }
 
 static size_t max2(size_t a, size_t b) { return a > b ? a : b; }
@@ -157,7 +162,7 @@ static BwdPlan plan_bwd(const cofree_layer_desc& d, int64_t n, void* ws) {
     p.dA = c.take(N * d.d_msg * es);
     p.dZ = c.take(N * d.d_msg * es);
     if (sage_merged(d)) {
-      p.wg[0] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_msg + d.d_in, n));
+      p.wg[0] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_msg, n, d.d_in));
     } else {
       p.wg[0] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
       p.wg[1] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_msg, n));
@@ -167,7 +172,7 @@ static BwdPlan plan_bwd(const cofree_layer_desc& d, int64_t n, void* ws) {
     if (d.dropout_q > 0.f || d.act) p.dP = c.take(N * d.d_out * es);
     // transform first: T = Ahat dPre [n, d_out]; aggregate first: T = norm * (dPre W) [n, d_in]
     p.T = c.take(N * (gcn_transform_first(d) ? d.d_out : d.d_in) * es);
-    p.wg[0] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, conv_merged(d) ? 2 * d.d_in : d.d_in, n));
+    p.wg[0] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n, conv_merged(d) ? d.d_in : 0));
     if (d.kind == COFREE_SAGE_CONV && !conv_merged(d)) p.wg[1] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
     if (d.kind == COFREE_GCN && gcn_transform_first(d)) p.cs = (float*)c.take(4 * colsum_workspace_floats(d.d_out));
   }
