@@ -96,6 +96,27 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
 }
 __device__ inline bf16_t f32_to_bf16(float f) { return (bf16_t)(pack_bf16x2(f, 0.f) & 0xffffu); }
 
+// ---- inverted dropout of a layer's output ------------------------------------------------------
+// Element e of a contiguous matrix is kept where word e % 4 of the draw numbered e / 4 reaches `thr`, and scaled.
+struct DropoutK {
+  uint32_t thr = 0, epoch = 0, stream = 0;
+  float scale = 0.f;  // 1 / (1 - q); 0: no dropout
+  uint64_t seed = 0;
+};
+// four elements, the first of them a multiple of four
+__device__ inline void drop4(const DropoutK& d, uint64_t first, float* x) {
+  const u32x4 w = draw4(d.seed, d.stream, first >> 2, d.epoch);
+  x[0] = w.x >= d.thr ? x[0] * d.scale : 0.f;
+  x[1] = w.y >= d.thr ? x[1] * d.scale : 0.f;
+  x[2] = w.z >= d.thr ? x[2] * d.scale : 0.f;
+  x[3] = w.w >= d.thr ? x[3] * d.scale : 0.f;
+}
+__device__ inline float drop1(const DropoutK& d, uint64_t e, float x) {
+  const u32x4 w = draw4(d.seed, d.stream, e >> 2, d.epoch);
+  const uint32_t word = (e & 2) ? ((e & 1) ? w.w : w.z) : ((e & 1) ? w.y : w.x);
+  return word >= d.thr ? x * d.scale : 0.f;
+}
+
 // ---- graph views ------------------------------------------------------------------------
 // One CSR on the device with its per-node normalisation vectors.
 struct DeviceGraph {
@@ -245,6 +266,17 @@ struct DropoutArgs {
   uint32_t epoch = 0;
   uint32_t layer_id = 0;
 };
+inline DropoutK dropout_k(const DropoutArgs& d) {
+  DropoutK k;
+  if (d.q > 0.f) {
+    k.thr = prob_threshold((double)d.q);
+    k.epoch = d.epoch;
+    k.stream = STREAM_DROPOUT + 256u * d.layer_id;
+    k.scale = 1.0f / (1.0f - d.q);
+    k.seed = d.seed;
+  }
+  return k;
+}
 
 struct AggArgs {
   DeviceGraph g;
@@ -262,8 +294,10 @@ struct AggArgs {
   // applied after out_scale, in this order: + bias[c], ReLU
   const float* bias = nullptr;
   int32_t relu_out = 0;
+  DropoutArgs dropout;  // of the finished rows, where aggregate_drops() allows it
 };
 int32_t launch_aggregate(const AggArgs& a, hipStream_t stream);
+bool aggregate_drops(const AggArgs& a);
 // Allocates and fills the processing-order copy of g (g.order and the per-node vectors must be set).
 int32_t build_slot_csr(const DeviceGraph& g, SlotCsr* out, hipStream_t stream);
 // val_inv_deg[e] = inv_deg[col[e]], val_gcn_norm[e] = gcn_norm[col[e]] for e < nnz
@@ -303,10 +337,13 @@ struct GemmArgs {
   int32_t relu_last = 0;             // ReLU after the accumulation
   int32_t gate_last = 0;             // apply `gate` after the accumulation instead of before it
   float gate_scale = 1.f;            // factor on the elements that pass `gate`
+  DropoutArgs dropout;               // of the finished result, where gemm_drops() says that the product applies it
   // bfloat16 only: scratch for the parameters converted to bfloat16, gemm_param_scratch_bytes(N, K1+K2)
   void* param_scratch = nullptr;
 };
 int32_t launch_gemm(const GemmArgs& a, hipStream_t stream);
+// whether the product that launch_gemm takes can apply dropout to its result
+bool gemm_drops(const GemmArgs& a);
 size_t gemm_param_scratch_bytes(int32_t N, int64_t K);
 
 // Sums of partial results in a fixed order: C[i, j] (+)= sum over z of part[z * stride + i * cols + j].  The weight and
@@ -372,6 +409,7 @@ int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stre
 int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream);
 // bfloat16 products whose parameters fit LDS (gemm_bf16_resident.hip)
 bool gemm_resident_fits(const GemmArgs& a);
+bool gemm_resident_drops(const GemmArgs& a);
 int32_t launch_gemm_resident(const GemmArgs& a, hipStream_t stream);
 int32_t launch_wgrad_bf16(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
 // bfloat16 weight gradients of at least eight rows and columns (wgrad_bf16.hip); narrower ones stay in gemm_bf16.hip

@@ -629,6 +629,12 @@ static int32_t check_grid(int64_t blocks) {
   return COFREE_OK;
 }
 
+bool gemm_drops(const GemmArgs& a) {
+  // rows of whole draws, so that the four elements of a draw belong to one lane
+  if (a.b_kmajor || a.N % 4 != 0 || a.ldc != a.N) return false;
+  return a.dtype == COFREE_F32 ? gemm_split_fits(a) : gemm_resident_drops(a);
+}
+
 int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(a.A1 && a.B && a.C, "dense: NULL operand");
   if (a.dtype == COFREE_BF16) return launch_gemm_bf16(a, stream);

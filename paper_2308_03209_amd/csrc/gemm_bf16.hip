@@ -642,7 +642,7 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
                    "dense: ldb too small");
   else
     COFREE_REQUIRE(a.b_kmajor ? a.ldb >= a.N : a.ldb >= K, "dense: ldb too small");
-  if (gemm_resident_fits(a) && !getenv("COFREE_BF16_TILE")) return launch_gemm_resident(a, stream);
+  if (gemm_resident_fits(a)) return launch_gemm_resident(a, stream);
   const int64_t ldd = pad8(K);
   bf16_t* Wb = (bf16_t*)a.param_scratch;
   {

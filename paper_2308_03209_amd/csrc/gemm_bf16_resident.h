@@ -58,6 +58,7 @@ struct ResidentK {
   int64_t ldg;
   int32_t accumulate, relu_last, gate_last;
   float gate_scale;
+  DropoutK drop;
 };
 
 // 128-bit value >> 16 * halves (0 .. 8), without branches
@@ -72,10 +73,13 @@ __device__ inline u32x4u shift_halves(const u32x4u& w, int halves) {
 
 // NB: 32-column blocks of a part, 32 (NB - 1) <= its columns <= 32 NB (two for 32 columns); NCH: pieces of 64 k over both segments.
 // LDS parameters: [k-group of 8][column][8 bfloat16]: a matrix operand is 512 contiguous bytes per half wavefront.
-// EXTRAS: the result is gated by another matrix or accumulated.
-template <int NB, int NCH, bool EXTRAS>
+// END: RES_EXTRAS - the result is gated by another matrix or accumulated; RES_DROP - dropout of the result
+// (1.88M x 128: the pass of its own took 203 us, a step with two of them is 300 us shorter without).
+constexpr int RES_PLAIN = 0, RES_EXTRAS = 1, RES_DROP = 2;
+template <int NB, int NCH, int END>
 __global__ __launch_bounds__(64 * RES_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void gemm_bf16_resident_kernel(
     const ResidentK p) {
+  constexpr bool EXTRAS = END == RES_EXTRAS;
   constexpr int COLS = 32 * NB;
   constexpr int B_BYTES = NCH * 8 * COLS * 16;
   constexpr int STORES = 2 * NB;  // of one tile
@@ -269,6 +273,11 @@ __global__ __launch_bounds__(64 * RES_WAVES) __attribute__((amdgpu_waves_per_eu(
           }
           if (p.relu_last) x[c] = fmaxf(x[c], 0.f);
         }
+        if constexpr (END == RES_DROP) {
+          const uint64_t first = (uint64_t)(i0 + row) * (uint32_t)p.N + (uint32_t)(block_col(b) + ec);
+          drop4(p.drop, first, x);
+          drop4(p.drop, first + 4, x + 4);
+        }
 #pragma unroll
         for (int c = 0; c < 4; ++c) packed[b & 1][h][c] = pack_bf16x2(x[2 * c], x[2 * c + 1]);
       }
@@ -312,20 +321,21 @@ __global__ __launch_bounds__(64 * RES_WAVES) __attribute__((amdgpu_waves_per_eu(
 }
 
 // Launches the instance for NB column blocks and nch pieces; false if there is none.
-bool launch_resident_narrow(int nb, int nch, bool extras, dim3 grid, hipStream_t stream, const ResidentK& p);  // 2 .. 4
-bool launch_resident_wide(int nb, int nch, bool extras, dim3 grid, hipStream_t stream, const ResidentK& p);    // 5 .. 8
+bool launch_resident_narrow(int nb, int nch, int end, dim3 grid, hipStream_t stream, const ResidentK& p);  // 2 .. 4
+bool launch_resident_wide(int nb, int nch, int end, dim3 grid, hipStream_t stream, const ResidentK& p);    // 5 .. 8
 
 template <int NB, int NCH>
-inline bool launch_resident_instance(bool extras, dim3 grid, hipStream_t stream, const ResidentK& p) {
-  if (extras) gemm_bf16_resident_kernel<NB, NCH, true><<<grid, 64 * RES_WAVES, 0, stream>>>(p);
-  else gemm_bf16_resident_kernel<NB, NCH, false><<<grid, 64 * RES_WAVES, 0, stream>>>(p);
+inline bool launch_resident_instance(int end, dim3 grid, hipStream_t stream, const ResidentK& p) {
+  if (end == RES_EXTRAS) gemm_bf16_resident_kernel<NB, NCH, RES_EXTRAS><<<grid, 64 * RES_WAVES, 0, stream>>>(p);
+  else if (end == RES_DROP) gemm_bf16_resident_kernel<NB, NCH, RES_DROP><<<grid, 64 * RES_WAVES, 0, stream>>>(p);
+  else gemm_bf16_resident_kernel<NB, NCH, RES_PLAIN><<<grid, 64 * RES_WAVES, 0, stream>>>(p);
   return true;
 }
 // nch counted down from the most that 128 KB of parameters allow
 template <int NB, int NCH>
-inline bool launch_resident_pieces(int nch, bool extras, dim3 grid, hipStream_t stream, const ResidentK& p) {
-  if (nch == NCH) return launch_resident_instance<NB, NCH>(extras, grid, stream, p);
-  if constexpr (NCH > 1) return launch_resident_pieces<NB, NCH - 1>(nch, extras, grid, stream, p);
+inline bool launch_resident_pieces(int nch, int end, dim3 grid, hipStream_t stream, const ResidentK& p) {
+  if (nch == NCH) return launch_resident_instance<NB, NCH>(end, grid, stream, p);
+  if constexpr (NCH > 1) return launch_resident_pieces<NB, NCH - 1>(nch, end, grid, stream, p);
   return false;
 }
 

@@ -3,12 +3,12 @@
 
 namespace cofree {
 
-bool launch_resident_wide(int nb, int nch, bool extras, dim3 grid, hipStream_t stream, const ResidentK& p) {
+bool launch_resident_wide(int nb, int nch, int end, dim3 grid, hipStream_t stream, const ResidentK& p) {
   switch (nb) {
-    case 5: return launch_resident_pieces<5, 6>(nch, extras, grid, stream, p);
-    case 6: return launch_resident_pieces<6, 5>(nch, extras, grid, stream, p);
-    case 7: return launch_resident_pieces<7, 4>(nch, extras, grid, stream, p);
-    case 8: return launch_resident_pieces<8, 4>(nch, extras, grid, stream, p);
+    case 5: return launch_resident_pieces<5, 6>(nch, end, grid, stream, p);
+    case 6: return launch_resident_pieces<6, 5>(nch, end, grid, stream, p);
+    case 7: return launch_resident_pieces<7, 4>(nch, end, grid, stream, p);
+    case 8: return launch_resident_pieces<8, 4>(nch, end, grid, stream, p);
     default: return false;
   }
 }

@@ -71,6 +71,7 @@ struct SplitK {
   int64_t ldg;
   int32_t accumulate, relu_last, gate_last;
   float gate_scale;
+  DropoutK drop;
 };
 
 template <int ROWS>
@@ -342,7 +343,10 @@ __device__ inline void run_plain(const float* A, int64_t sia, int64_t ska, const
 }
 
 // A_KMAJOR: weight gradient C = A^T B over graph nodes, float32 partials per chunk; else C = sum of segments A op(B).
-template <bool A_KMAJOR, bool B_KMAJOR, int RM, int RN>
+// DROP: dropout of the result, in rows of a multiple of four contiguous columns (529k x 512 with K = 1024: a pass of its own
+// took 353 us, a training step with three of them is 760 us shorter without).  Its generator runs beside the matrix
+// instructions of the CU's other workgroup, where a pass of its own reads and writes the result once more.
+template <bool A_KMAJOR, bool B_KMAJOR, int RM, int RN, bool DROP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 ? 2 : 3))) void gemm_split_kernel(
     const SplitK p) {
   constexpr int TM = 64 * RM, TN = 64 * RN;
@@ -475,6 +479,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
             if (p.accumulate) y += *dst;
             if (p.gate_last) y = shut ? 0.f : y * p.gate_scale;
             if (p.relu_last) y = fmaxf(y, 0.f);
+            if constexpr (DROP) y = drop1(p.drop, (uint64_t)i * (uint32_t)p.N + (uint32_t)j, y);
           }
           *dst = y;
         }
@@ -564,6 +569,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
 #pragma unroll
             for (int c = 0; c < 4; ++c) x[c] = fmaxf(x[c], 0.f);
           }
+          if constexpr (DROP) drop4(p.drop, (uint64_t)i * (uint32_t)p.N + (uint32_t)jv, x);
           float4u out;
 #pragma unroll
           for (int c = 0; c < 4; ++c) out[c] = x[c];
@@ -658,6 +664,7 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   p.relu_last = a.relu_last;
   p.gate_last = a.gate_last;
   p.gate_scale = a.gate ? a.gate_scale : 1.f;
+  p.drop = dropout_k(a.dropout);
   const int64_t K = (int64_t)a.K1 + a.K2;
   // 128x256 tiles where they fit the columns as well as 128x128 ones and give every CU its two workgroups (half
   // the reads of operand A; the rates are equal within 4 %), else 128x128 (20k x 256 x 256: 27.5 against 30.9 us)
@@ -673,12 +680,15 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + (double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1)),
                  2.0 * (double)a.M * a.N * (double)K);
   const dim3 grid((unsigned)blocks);
+  const bool drop = p.drop.scale != 0.f;  // forward products only
   if (wide) {
-    if (a.b_kmajor) gemm_split_kernel<false, true, 2, 4><<<grid, 256, 0, stream>>>(p);
-    else gemm_split_kernel<false, false, 2, 4><<<grid, 256, 0, stream>>>(p);
+    if (a.b_kmajor) gemm_split_kernel<false, true, 2, 4, false><<<grid, 256, 0, stream>>>(p);
+    else if (drop) gemm_split_kernel<false, false, 2, 4, true><<<grid, 256, 0, stream>>>(p);
+    else gemm_split_kernel<false, false, 2, 4, false><<<grid, 256, 0, stream>>>(p);
   } else {
-    if (a.b_kmajor) gemm_split_kernel<false, true, 2, 2><<<grid, 256, 0, stream>>>(p);
-    else gemm_split_kernel<false, false, 2, 2><<<grid, 256, 0, stream>>>(p);
+    if (a.b_kmajor) gemm_split_kernel<false, true, 2, 2, false><<<grid, 256, 0, stream>>>(p);
+    else if (drop) gemm_split_kernel<false, false, 2, 2, true><<<grid, 256, 0, stream>>>(p);
+    else gemm_split_kernel<false, false, 2, 2, false><<<grid, 256, 0, stream>>>(p);
   }
   COFREE_HIP_CHECK(hipGetLastError());
   return COFREE_OK;
@@ -723,8 +733,8 @@ int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stre
     if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<true,true,%d,2> N=%dx%d", tall ? 4 : 2, (int)N1, (int)N2);
     ProfScope prof(pname, stream, 4.0 * ((double)a.M * N1 * (p.extra.X ? 2 : 1) + (double)a.M * N2 + (double)N1 * N2),
                    2.0 * (double)a.M * N1 * N2);
-    if (tall) gemm_split_kernel<true, true, 4, 2><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
-    else gemm_split_kernel<true, true, 2, 2><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
+    if (tall) gemm_split_kernel<true, true, 4, 2, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
+    else gemm_split_kernel<true, true, 2, 2, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
   }
   COFREE_HIP_CHECK(hipGetLastError());
   COFREE_TRY(add_split_sum(sums, a.workspace, p.c_split_stride, S, a.C, a.ldc, N1, N2));

@@ -252,6 +252,16 @@ int32_t cofree_layer_fwd(const cofree_partition* part, const cofree_masks* masks
     return a;
   };
 
+  // Inverted dropout of the layer's output (the same keep decisions are recomputed in backward) is applied by the launch
+  // that finishes H_out where its kernel can, else in place by a launch of its own (which wants H_out aligned)
+  bool dropped = false;
+  auto with_dropout = [&](auto& last, bool can) {
+    if (d.dropout_q > 0.f && can && ((uintptr_t)H_out & 15u) == 0) {
+      last.dropout = dropout_of(d);
+      dropped = true;
+    }
+  };
+
   if (d.kind == COFREE_SAGE_MEAN) {
     COFREE_REQUIRE(params->U && params->bU, "layer_fwd: U / bU is NULL");
     COFREE_REQUIRE(saved->Z && saved->A, "layer_fwd: saved.Z / saved.A is NULL");
@@ -281,6 +291,7 @@ int32_t cofree_layer_fwd(const cofree_partition* part, const cofree_masks* masks
       c.B = params->U + d.d_msg; c.ldb = ldu;
       c.C = H_out; c.ldc = d.d_out; c.N = d.d_out;
       c.bias = params->bU; c.accumulate = 1;
+      with_dropout(c, gemm_drops(c));
       COFREE_TRY(launch_gemm(c, s));
     } else {
       // neighbourhood mean, then combine: H' = [A | H] U^T + bU
@@ -294,6 +305,7 @@ int32_t cofree_layer_fwd(const cofree_partition* part, const cofree_masks* masks
       c.B = params->U; c.ldb = ldu;
       c.C = H_out; c.ldc = d.d_out; c.N = d.d_out;
       c.bias = params->bU;
+      with_dropout(c, gemm_drops(c));
       COFREE_TRY(launch_gemm(c, s));
     }
   } else if (d.kind == COFREE_SAGE_CONV) {
@@ -314,6 +326,7 @@ int32_t cofree_layer_fwd(const cofree_partition* part, const cofree_masks* masks
       c.B = params->W; c.ldb = ldw;
       c.C = H_out; c.ldc = d.d_out; c.N = d.d_out;
       c.bias = params->bW; c.accumulate = 1; c.relu_last = d.act;
+      with_dropout(c, gemm_drops(c));
       COFREE_TRY(launch_gemm(c, s));
     } else {
       COFREE_REQUIRE(saved->A, "layer_fwd: saved.A is NULL");
@@ -328,6 +341,7 @@ int32_t cofree_layer_fwd(const cofree_partition* part, const cofree_masks* masks
       c.B = params->W; c.ldb = ldw;
       c.C = H_out; c.ldc = d.d_out; c.N = d.d_out;
       c.bias = params->bW; c.relu = d.act;
+      with_dropout(c, gemm_drops(c));
       COFREE_TRY(launch_gemm(c, s));
     }
   } else if (gcn_transform_first(d)) {
@@ -342,6 +356,7 @@ int32_t cofree_layer_fwd(const cofree_partition* part, const cofree_masks* masks
     a.X = fp.T; a.Y = H_out; a.width = d.d_out; a.ldx = a.ldy = d.d_out;
     a.out_scale = g.gcn_norm; a.self_loop = 1;  // sources are already scaled
     a.bias = params->bW; a.relu_out = d.act;
+    with_dropout(a, aggregate_drops(a));
     COFREE_TRY(launch_aggregate(a, s));
   } else {
     COFREE_REQUIRE(saved->A, "layer_fwd: saved.A is NULL");
@@ -355,10 +370,10 @@ int32_t cofree_layer_fwd(const cofree_partition* part, const cofree_masks* masks
     t.B = params->W; t.ldb = d.d_in;
     t.C = H_out; t.ldc = d.d_out; t.N = d.d_out;
     t.bias = params->bW; t.relu = d.act;
+    with_dropout(t, gemm_drops(t));
     COFREE_TRY(launch_gemm(t, s));
   }
-  // inverted dropout on the layer output, in place (the same keep decisions are recomputed in backward)
-  if (d.dropout_q > 0.f) COFREE_TRY(launch_mask_grad(dt, H_out, nullptr, H_out, n, d.d_out, dropout_of(d), s));
+  if (d.dropout_q > 0.f && !dropped) COFREE_TRY(launch_mask_grad(dt, H_out, nullptr, H_out, n, d.d_out, dropout_of(d), s));
   return COFREE_OK;
 }
 

@@ -171,6 +171,7 @@ struct AggK {
   const float* bias;
   int relu_out;
   int col0;  // first column of this launch in the full matrix (bias index)
+  DropoutK drop;  // after everything else (DROP instances; ldy is the width of the full matrix there)
 };
 
 // A lane owns VEC consecutive columns starting at a multiple of VEC.  When the last lane's columns
@@ -227,7 +228,9 @@ struct RowTail {
   }
 };
 
-template <typename T, int VEC, bool TINY>
+// DROP: dropout of the finished row, in rows of a multiple of four columns (100k rows of 128 bfloat16: a launch of its own took
+// 15 us).
+template <typename T, int VEC, bool TINY, bool DROP>
 __device__ inline void finish_row(const AggK<T>& p, int64_t row, int c0, int first, int avail, float (&acc)[VEC],
                                   const RowTail<T, VEC, TINY>& t) {
   if constexpr (TINY) {
@@ -279,6 +282,10 @@ __device__ inline void finish_row(const AggK<T>& p, int64_t row, int c0, int fir
   if (p.relu_out) {
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] = fmaxf(acc[i], 0.f);
+  }
+  if constexpr (DROP) {
+#pragma unroll
+    for (int q = 0; q < VEC / 4; ++q) drop4(p.drop, (uint64_t)row * (uint64_t)p.ldy + (uint32_t)(p.col0 + c0 + 4 * q), acc + 4 * q);
   }
   if (first == 0) {
     if constexpr (TINY) {
@@ -385,7 +392,7 @@ __device__ inline void gather_row(const AggK<T>& p, int64_t beg, int64_t end, in
 
 // TINY: rows narrower than one 16-byte access (element accesses; LPS = 1).
 // Rows need only element alignment (see LaneCols for the ragged end of a row).
-template <typename T, int TL, int LPS, int NCH, bool TINY>
+template <typename T, int TL, int LPS, int NCH, bool TINY, bool DROP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4 : (sizeof(T) == 4 ? 8 : 7)))) void aggregate_kernel(const AggK<T> p) {
   constexpr int VEC = RowIO<T>::WIDE;
   constexpr int RPW = 64 / TL;  // short rows per wavefront
@@ -453,7 +460,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4
   if ((lane % (team == 0 ? TL : 64)) >= LPS) return;  // the first neighbour group of the team writes
 #pragma unroll
   for (int c = 0; c < NCH; ++c)
-    if (lc[c].avail > 0) finish_row<T, VEC, TINY>(p, row, lc[c].c0, lc[c].first, lc[c].avail, acc[c], tail[c]);
+    if (lc[c].avail > 0) finish_row<T, VEC, TINY, DROP>(p, row, lc[c].c0, lc[c].first, lc[c].avail, acc[c], tail[c]);
 }
 
 // ---- XCD-affine column slices ---------------------------------------------------------------------
@@ -461,7 +468,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4
 // slice of LPS lanes x 16 bytes).  Workgroups are dealt round-robin to the 8 XCDs, so workgroup b works on column
 // slice b % 8 of row group b / 8, and each XCD's L2 only ever holds one eighth of every row - eight times as many
 // (hot) rows.  The launcher sends only widths that divide into eight slices.
-template <typename T, int LPS>
+template <typename T, int LPS, bool DROP>
 __global__ __launch_bounds__(256) void aggregate_sliced_kernel(const AggK<T> p) {
   constexpr int VEC = RowIO<T>::WIDE;
   constexpr int NG = 64 / LPS;
@@ -517,7 +524,7 @@ __global__ __launch_bounds__(256) void aggregate_sliced_kernel(const AggK<T> p) 
     for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
   }
   if (grp != 0) return;
-  finish_row<T, VEC, false>(p, row, c0, 0, VEC, acc, tail);
+  finish_row<T, VEC, false, DROP>(p, row, c0, 0, VEC, acc, tail);
 }
 
 // ---- hub rows -----------------------------------------------------------------------------------
@@ -527,7 +534,7 @@ __global__ __launch_bounds__(256) void aggregate_sliced_kernel(const AggK<T> p) 
 // instruction.  The groups of a wavefront are added by the same butterfly, then wavefront w > 0 writes its
 // partial panel to LDS and wavefront 0 adds the partials in ascending w: a fixed order.
 constexpr int HUB_WAVES = 16;
-template <typename T, int LPS>
+template <typename T, int LPS, bool DROP>
 __global__ __launch_bounds__(HUB_WAVES * 64) void aggregate_hub_kernel(const AggK<T> p) {
   constexpr int VEC = RowIO<T>::WIDE;
   constexpr int NG = 64 / LPS;
@@ -588,7 +595,7 @@ __global__ __launch_bounds__(HUB_WAVES * 64) void aggregate_hub_kernel(const Agg
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] += partial[w][sub * VEC + i];
   }
-  finish_row<T, VEC, false>(p, row, c0, lc.first, avail, acc, tail);
+  finish_row<T, VEC, false, DROP>(p, row, c0, lc.first, avail, acc, tail);
 }
 
 // ---- host side ------------------------------------------------------------------------------------
@@ -619,7 +626,7 @@ struct LaunchCost {
 // four to a wavefront, where the columns leave that many lanes: with more rows, narrow rows measured slower (8 rows
 // of 6 pieces: 0.50 ms, 4 rows 0.41 ms on 1.9M rows of 47 bfloat16); lanes that the columns leave free fetch further
 // neighbours of the row.
-template <typename T>
+template <typename T, bool DROP>
 static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
   constexpr int WIDE = RowIO<T>::WIDE;
   const int chunks = (k.width + WIDE - 1) / WIDE;
@@ -636,19 +643,19 @@ static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCos
            tiny ? "true" : "false", (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   const dim3 grid((unsigned)blocks);
-  if (tiny) aggregate_kernel<T, 16, 1, 1, true><<<grid, 256, 0, stream>>>(k);
-  else if (lps == 1) aggregate_kernel<T, 16, 1, 1, false><<<grid, 256, 0, stream>>>(k);
-  else if (lps == 2) aggregate_kernel<T, 16, 2, 1, false><<<grid, 256, 0, stream>>>(k);
-  else if (lps == 4) aggregate_kernel<T, 16, 4, 1, false><<<grid, 256, 0, stream>>>(k);
-  else if (lps == 8) aggregate_kernel<T, 16, 8, 1, false><<<grid, 256, 0, stream>>>(k);
-  else if (lps == 16) aggregate_kernel<T, 16, 16, 1, false><<<grid, 256, 0, stream>>>(k);
-  else if (lps == 32) aggregate_kernel<T, 32, 32, 1, false><<<grid, 256, 0, stream>>>(k);
-  else if (nch == 1) aggregate_kernel<T, 64, 64, 1, false><<<grid, 256, 0, stream>>>(k);
-  else aggregate_kernel<T, 64, 64, 2, false><<<grid, 256, 0, stream>>>(k);
+  if (tiny) aggregate_kernel<T, 16, 1, 1, true, false><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 1) aggregate_kernel<T, 16, 1, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 2) aggregate_kernel<T, 16, 2, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 4) aggregate_kernel<T, 16, 4, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 8) aggregate_kernel<T, 16, 8, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 16) aggregate_kernel<T, 16, 16, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 32) aggregate_kernel<T, 32, 32, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
+  else if (nch == 1) aggregate_kernel<T, 64, 64, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
+  else aggregate_kernel<T, 64, 64, 2, false, DROP><<<grid, 256, 0, stream>>>(k);
   return COFREE_OK;
 }
 
-template <typename T>
+template <typename T, bool DROP>
 static int32_t launch_sliced(const AggK<T>& k, int lps, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
   const int64_t blocks = ((k.n + 3) / 4) * 8;
   COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
@@ -657,17 +664,17 @@ static int32_t launch_sliced(const AggK<T>& k, int lps, hipStream_t stream, cons
   if (profiling()) snprintf(pname, sizeof(pname), "aggregate_sliced_kernel<%s,%d> width=%d", type_name<T>(), lps, (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   switch (lps) {
-    case 8: aggregate_sliced_kernel<T, 8><<<grid, 256, 0, stream>>>(k); break;
-    case 16: aggregate_sliced_kernel<T, 16><<<grid, 256, 0, stream>>>(k); break;
-    case 32: aggregate_sliced_kernel<T, 32><<<grid, 256, 0, stream>>>(k); break;
-    case 64: aggregate_sliced_kernel<T, 64><<<grid, 256, 0, stream>>>(k); break;
+    case 8: aggregate_sliced_kernel<T, 8, DROP><<<grid, 256, 0, stream>>>(k); break;
+    case 16: aggregate_sliced_kernel<T, 16, DROP><<<grid, 256, 0, stream>>>(k); break;
+    case 32: aggregate_sliced_kernel<T, 32, DROP><<<grid, 256, 0, stream>>>(k); break;
+    case 64: aggregate_sliced_kernel<T, 64, DROP><<<grid, 256, 0, stream>>>(k); break;
     default: return fail(COFREE_EINVAL, "internal: bad lanes-per-slice");
   }
   return COFREE_OK;
 }
 
 // hub rows: order[0 .. n_hub), one workgroup per (row, panel of lps lanes x 16 bytes)
-template <typename T>
+template <typename T, bool DROP>
 static int32_t launch_hub(const AggK<T>& k, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
   constexpr int WIDE = RowIO<T>::WIDE;
   int lps = 1;
@@ -679,18 +686,18 @@ static int32_t launch_hub(const AggK<T>& k, hipStream_t stream, const LaunchCost
   if (profiling()) snprintf(pname, sizeof(pname), "aggregate_hub_kernel<%s,%d> width=%d", type_name<T>(), lps, (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   switch (lps) {
-    case 1: aggregate_hub_kernel<T, 1><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
-    case 2: aggregate_hub_kernel<T, 2><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
-    case 4: aggregate_hub_kernel<T, 4><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
-    case 8: aggregate_hub_kernel<T, 8><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
-    case 16: aggregate_hub_kernel<T, 16><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
-    case 32: aggregate_hub_kernel<T, 32><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
-    default: aggregate_hub_kernel<T, 64><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
+    case 1: aggregate_hub_kernel<T, 1, DROP><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
+    case 2: aggregate_hub_kernel<T, 2, DROP><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
+    case 4: aggregate_hub_kernel<T, 4, DROP><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
+    case 8: aggregate_hub_kernel<T, 8, DROP><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
+    case 16: aggregate_hub_kernel<T, 16, DROP><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
+    case 32: aggregate_hub_kernel<T, 32, DROP><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
+    default: aggregate_hub_kernel<T, 64, DROP><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;
   }
   return COFREE_OK;
 }
 
-template <typename T>
+template <typename T, bool DROP>
 static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   constexpr int WIDE = RowIO<T>::WIDE;
   const T* X = (const T*)a.X;
@@ -708,6 +715,7 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   k.gate_scale = a.gate_scale;
   k.bias = a.bias;
   k.relu_out = a.relu_out;
+  k.drop = dropout_k(a.dropout);
   k.width = a.width;
   k.col0 = 0;
   k.X = X;
@@ -762,7 +770,7 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
     k.order = a.g.order;
     k.slot0 = 0;
     k.n = n_hub;
-    COFREE_TRY(launch_hub<T>(k, stream, cost, a.g.nnz_hub));
+    COFREE_TRY((launch_hub<T, DROP>(k, stream, cost, a.g.nnz_hub)));
   }
   if constexpr (sizeof(T) == 4) {
     if (sliced) {
@@ -771,7 +779,7 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
       k.slot0 = 0;
       k.n = a.g.n;
       k.skip_from = n_hub > 0 ? AGG_HUB_MIN : INT64_MAX;
-      COFREE_TRY(launch_sliced<T>(k, a.width / slice_unit, stream, cost, a.g.nnz - hub_nnz));
+      COFREE_TRY((launch_sliced<T, DROP>(k, a.width / slice_unit, stream, cost, a.g.nnz - hub_nnz)));
       COFREE_HIP_CHECK(hipGetLastError());
       return COFREE_OK;
     }
@@ -807,10 +815,15 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
     k.X = X + c0;
     k.Y = Y + c0;
     k.relu_src = R ? R + c0 : nullptr;
-    COFREE_TRY(launch_rows<T>(k, stream, cost, a.g.nnz - hub_nnz));
+    COFREE_TRY((launch_rows<T, DROP>(k, stream, cost, a.g.nnz - hub_nnz)));
   }
   COFREE_HIP_CHECK(hipGetLastError());
   return COFREE_OK;
+}
+
+// whole draws per lane: rows of a multiple of four contiguous columns, and of at least one wide access
+bool aggregate_drops(const AggArgs& a) {
+  return a.width % 4 == 0 && a.ldy == a.width && a.width >= (a.dtype == COFREE_F32 ? 4 : 8);
 }
 
 int32_t launch_aggregate(const AggArgs& a, hipStream_t stream) {
@@ -820,8 +833,9 @@ int32_t launch_aggregate(const AggArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(a.ldx >= a.width && a.ldy >= a.width, "aggregate: leading dimension smaller than width");
   COFREE_REQUIRE(a.g.n < ((int64_t)1 << 31), "aggregate: too many rows");
   if (a.g.n == 0) return COFREE_OK;
-  if (a.dtype == COFREE_F32) return launch_typed<float>(a, stream);
-  return launch_typed<bf16_t>(a, stream);
+  const bool drop = a.dropout.q > 0.f;
+  if (a.dtype == COFREE_F32) return drop ? launch_typed<float, true>(a, stream) : launch_typed<float, false>(a, stream);
+  return drop ? launch_typed<bf16_t, true>(a, stream) : launch_typed<bf16_t, false>(a, stream);
 }
 
 }  // namespace cofree

@@ -1,0 +1,63 @@
+"""Dropout applied by the launch that finishes a layer's output: every kernel that does so, at widths around its limits,
+against the same layer without dropout times the oracle's keep decisions."""
+import numpy as np
+import pytest
+
+from oracle.layers import dropout_keep
+from test_gpu_bf16 import G  # noqa: F401  (the fixture)
+
+pytestmark = pytest.mark.gpu
+
+# widths and the kernel that ends the layer (f32 / bf16)
+SHAPES = [("sage_conv", 72, 132),   # aggregate first: split / resident product, ragged column block
+          ("sage_conv", 256, 128),  # transform first: accumulating split product / a launch of its own
+          ("sage_conv", 40, 94),    # no multiple of four columns: a launch of its own
+          ("gcn", 256, 512),        # widest split tiles / column parts of the resident product
+          ("gcn", 72, 300),         # column parts that are no multiple of four columns where there are three
+          ("gcn", 128, 36),         # transform first: the aggregation
+          ("gcn", 700, 640),        # aggregation in two panels / with two pieces per lane
+          ("gcn", 80, 12),          # rows of few lanes, one window moved left
+          ("sage", 100, 260), ("sage", 64, 36)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("kind,d_in,d_out", SHAPES)
+def test_against_keep_decisions(G, kind, d_in, d_out, dtype):  # noqa: F811
+    B, torch = G["B"], G["torch"]
+    print(f"[case] fused dropout {kind} {d_in} -> {d_out} {dtype}", flush=True)
+    n, q = 5003, 0.3
+    rng = np.random.default_rng(1)
+    hub = np.arange(1, 4401, dtype=np.int64)  # node 0: a hub row; nodes 1 .. 200: rows of a wavefront or a workgroup
+    src = np.concatenate([np.zeros_like(hub), rng.integers(1, 200, 20_000), np.arange(n, dtype=np.int64)])
+    dst = np.concatenate([hub, rng.integers(200, n, 20_000), (np.arange(n, dtype=np.int64) + 1) % n])
+    lo, hi = np.minimum(src, dst), np.maximum(src, dst)
+    pair = np.unique(lo * n + hi)
+    P = B.build_partition(n, pair // n, pair % n, 1, 0, 3)
+    assert P.num_nodes == n
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    code = {"gcn": B.GCN, "sage": B.SAGE_MEAN, "sage_conv": B.SAGE_CONV}[kind]
+    d_msg = 72 if kind == "sage" else 0
+    gen = torch.Generator(device="cuda").manual_seed(5)
+
+    def rand(*shape):
+        return torch.randn(*shape, generator=gen, device="cuda")
+    H = rand(n, d_in).to(td)
+    prm = {"W": rand(d_msg or d_out, d_in * (2 if kind == "sage_conv" else 1)) / d_in ** 0.5, "bW": rand(d_msg or d_out)}
+    if kind == "sage":
+        prm.update(U=rand(d_out, d_msg + d_in) / d_in ** 0.5, bU=rand(d_out))
+    saved = {"Z": torch.empty(n, max(d_msg, 1), dtype=td, device="cuda"),
+             "A": torch.empty(n, max(d_msg, d_in, d_out), dtype=td, device="cuda")}
+    out = []
+    for rate in (0.0, q):
+        d = B.layer_desc(code, d_in, d_msg, d_out, act=0 if kind == "sage" else 1, dropout_q=rate, layer_id=3, seed=2 ** 40 + 9,
+                         epoch=6, dtype=B.F32 if dtype == "f32" else B.BF16)
+        y = torch.full((n, d_out), float("nan"), device="cuda", dtype=td)
+        B.layer_fwd(P, None, 0, d, H, prm, y, saved, torch.empty(B.layer_workspace_bytes(d, n, False), dtype=torch.uint8, device="cuda"))
+        out.append(y.float().cpu().numpy())
+    keep = dropout_keep(n, d_out, q, 2 ** 40 + 9, 6, 3)
+    want = np.where(keep, out[0] * np.float32(1.0 / (1.0 - np.float32(q))), np.float32(0.0))
+    assert np.all(out[1][~keep] == 0.0)
+    if dtype == "f32":  # the same sums and one more product
+        np.testing.assert_allclose(out[1], want, rtol=2e-7, atol=0)
+    else:  # the plain run rounds once more, by 2^-9 of its value
+        np.testing.assert_allclose(out[1], want, rtol=2.0 ** -7, atol=0)
