@@ -79,11 +79,11 @@ int32_t launch_gemm_resident(const GemmArgs& a, hipStream_t stream) {
   p.teams = tiles < RES_CUS ? tiles : RES_CUS;
   if (p.parts > 1) p.teams = 8 * std::min<int64_t>((tiles + 7) / 8, RES_CUS / 8 / p.parts);
   const dim3 grid((unsigned)(p.teams * p.parts));
+  const int end = a.gate || a.accumulate ? RES_EXTRAS : (p.drop.scale != 0.f ? RES_DROP : RES_PLAIN);
   char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "gemm_bf16_resident_kernel<%d,%d> N=%d K=%d", nb, nch, (int)a.N, (int)K);
+  if (profiling()) snprintf(pname, sizeof(pname), "gemm_bf16_resident_kernel<%d,%d,%d> N=%d K=%d", nb, nch, end, (int)a.N, (int)K);
   ProfScope prof(pname, stream, 2.0 * ((double)a.M * K + (double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1)),
                  2.0 * (double)a.M * a.N * (double)K);
-  const int end = a.gate || a.accumulate ? RES_EXTRAS : (p.drop.scale != 0.f ? RES_DROP : RES_PLAIN);
   const bool ok = nb <= 4 ? launch_resident_narrow(nb, nch, end, grid, stream, p) : launch_resident_wide(nb, nch, end, grid, stream, p);
   if (!ok) return fail(COFREE_EINVAL, "internal: no resident product of this shape");
   COFREE_HIP_CHECK(hipGetLastError());

@@ -674,13 +674,13 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   p.tiles_n = wide ? tiles128 / 2 : tiles128;
   const int64_t blocks = ((p.n_groups + 7) / 8) * 8 * p.tiles_n;
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "dense: grid too large");
+  const bool drop = p.drop.scale != 0.f;  // forward products only
   char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<false,%s,2,%d> N=%d K=%d", a.b_kmajor ? "true" : "false", wide ? 4 : 2,
-           (int)a.N, (int)K);
+  if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<false,%s,2,%d,%s> N=%d K=%d", a.b_kmajor ? "true" : "false", wide ? 4 : 2,
+           drop && !a.b_kmajor ? "true" : "false", (int)a.N, (int)K);
   ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + (double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1)),
                  2.0 * (double)a.M * a.N * (double)K);
   const dim3 grid((unsigned)blocks);
-  const bool drop = p.drop.scale != 0.f;  // forward products only
   if (wide) {
     if (a.b_kmajor) gemm_split_kernel<false, true, 2, 4, false><<<grid, 256, 0, stream>>>(p);
     else if (drop) gemm_split_kernel<false, false, 2, 4, true><<<grid, 256, 0, stream>>>(p);
@@ -730,7 +730,7 @@ int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stre
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "wgrad: grid too large");
   {
     char pname[96] = "";
-    if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<true,true,%d,2> N=%dx%d", tall ? 4 : 2, (int)N1, (int)N2);
+    if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<true,true,%d,2,false> N=%dx%d", tall ? 4 : 2, (int)N1, (int)N2);
     ProfScope prof(pname, stream, 4.0 * ((double)a.M * N1 * (p.extra.X ? 2 : 1) + (double)a.M * N2 + (double)N1 * N2),
                    2.0 * (double)a.M * N1 * N2);
     if (tall) gemm_split_kernel<true, true, 4, 2, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);

@@ -639,8 +639,8 @@ static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCos
   const int64_t blocks = k.n_block + (k.n_wave + 3) / 4 + (short_rows + per_block - 1) / per_block;
   COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
   char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_kernel<%s,%d,%d,%d,%s> width=%d", type_name<T>(), tl, lps, nch,
-           tiny ? "true" : "false", (int)cost.a.width);
+  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_kernel<%s,%d,%d,%d,%s,%s> width=%d", type_name<T>(), tl, lps, nch,
+           tiny ? "true" : "false", DROP && !tiny ? "true" : "false", (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   const dim3 grid((unsigned)blocks);
   if (tiny) aggregate_kernel<T, 16, 1, 1, true, false><<<grid, 256, 0, stream>>>(k);
@@ -661,7 +661,8 @@ static int32_t launch_sliced(const AggK<T>& k, int lps, hipStream_t stream, cons
   COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
   const dim3 grid((unsigned)blocks);
   char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_sliced_kernel<%s,%d> width=%d", type_name<T>(), lps, (int)cost.a.width);
+  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_sliced_kernel<%s,%d,%s> width=%d", type_name<T>(), lps, DROP ? "true" : "false",
+           (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   switch (lps) {
     case 8: aggregate_sliced_kernel<T, 8, DROP><<<grid, 256, 0, stream>>>(k); break;
@@ -683,7 +684,8 @@ static int32_t launch_hub(const AggK<T>& k, hipStream_t stream, const LaunchCost
   COFREE_REQUIRE(k.n < ((int64_t)1 << 31) && panels < 65536, "aggregate: hub grid too large");
   const dim3 grid((unsigned)k.n, (unsigned)panels);
   char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_hub_kernel<%s,%d> width=%d", type_name<T>(), lps, (int)cost.a.width);
+  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_hub_kernel<%s,%d,%s> width=%d", type_name<T>(), lps, DROP ? "true" : "false",
+           (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   switch (lps) {
     case 1: aggregate_hub_kernel<T, 1, DROP><<<grid, HUB_WAVES * 64, 0, stream>>>(k); break;

@@ -295,7 +295,9 @@ int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t 
   const int32_t th = tile_rows(8 * pieces_of(p.N1)), tw = tile_cols(8 * (pieces_of(p.N2) + pieces_of(p.N2b)));
   {
     char pname[96] = "";
-    if (profiling()) snprintf(pname, sizeof(pname), "wgrad_bf16_kernel<%d,%d> N=%dx%d", (int)th, (int)tw, (int)a.N1, (int)N2);
+    const char* rest = tw == 256 ? (th == 256 ? "32,3,2,4" : (th == 128 ? "32,4,2,4" : "64,2,1,8"))
+                                 : (th == 256 ? "32,4,4,2" : (th == 128 ? "32,6,2,4" : "64,4,2,4"));
+    if (profiling()) snprintf(pname, sizeof(pname), "wgrad_bf16_kernel<%d,%d,%s> N=%dx%d", (int)th, (int)tw, rest, (int)a.N1, (int)N2);
     ProfScope prof(pname, stream, 2.0 * ((double)a.M * a.N1 * (p.extra.X ? 2 : 1) + (double)a.M * N2) + 4.0 * (double)a.N1 * N2,
                    2.0 * (double)a.M * a.N1 * N2);
     const dim3 grid((unsigned)blocks);
