@@ -626,11 +626,13 @@ struct LaunchCost {
 // four to a wavefront, where the columns leave that many lanes: with more rows, narrow rows measured slower (8 rows
 // of 6 pieces: 0.50 ms, 4 rows 0.41 ms on 1.9M rows of 47 bfloat16); lanes that the columns leave free fetch further
 // neighbours of the row.
+constexpr int ROW_PIECES = 128;  // wider rows take several launches
 template <typename T, bool DROP>
 static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
   constexpr int WIDE = RowIO<T>::WIDE;
   const int chunks = (k.width + WIDE - 1) / WIDE;
   const bool tiny = k.width < WIDE;
+  if (DROP && tiny) return fail(COFREE_EINVAL, "internal: no dropout in rows of less than one access");
   int lps = 1;
   while (lps < chunks && lps < 64) lps *= 2;
   const int tl = lps < 16 ? 16 : lps;
@@ -640,7 +642,7 @@ static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCos
   COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
   char pname[96] = "";
   if (profiling()) snprintf(pname, sizeof(pname), "aggregate_kernel<%s,%d,%d,%d,%s,%s> width=%d", type_name<T>(), tl, lps, nch,
-           tiny ? "true" : "false", DROP && !tiny ? "true" : "false", (int)cost.a.width);
+           tiny ? "true" : "false", DROP ? "true" : "false", (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   const dim3 grid((unsigned)blocks);
   if (tiny) aggregate_kernel<T, 16, 1, 1, true, false><<<grid, 256, 0, stream>>>(k);
@@ -810,7 +812,7 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
     if (a.out_scale == a.g.inv_deg) k.out_scale_slot = a.g.s_inv_deg;
     if (a.out_scale == a.g.gcn_norm) k.out_scale_slot = a.g.s_gcn_norm;
   }
-  const int panel = 128 * WIDE;  // columns one launch covers
+  const int panel = ROW_PIECES * WIDE;  // columns one launch covers
   for (int c0 = 0; c0 < a.width; c0 += panel) {
     k.width = a.width - c0 < panel ? a.width - c0 : panel;
     k.col0 = c0;
@@ -823,9 +825,12 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   return COFREE_OK;
 }
 
-// whole draws per lane: rows of a multiple of four contiguous columns, and of at least one wide access
+// whole draws per lane: rows of a multiple of four contiguous columns, and of at least one wide access in every launch
+// (1028 bfloat16 columns leave four to the second)
 bool aggregate_drops(const AggArgs& a) {
-  return a.width % 4 == 0 && a.ldy == a.width && a.width >= (a.dtype == COFREE_F32 ? 4 : 8);
+  const int wide = a.dtype == COFREE_F32 ? RowIO<float>::WIDE : RowIO<bf16_t>::WIDE;
+  const int last = a.width % (ROW_PIECES * wide);
+  return a.width % 4 == 0 && a.ldy == a.width && (last == 0 || last >= wide);
 }
 
 int32_t launch_aggregate(const AggArgs& a, hipStream_t stream) {

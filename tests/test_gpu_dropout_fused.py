@@ -16,6 +16,7 @@ SHAPES = [("sage_conv", 72, 132),   # aggregate first: split / resident product,
           ("gcn", 72, 300),         # column parts that are no multiple of four columns where there are three
           ("gcn", 128, 36),         # transform first: the aggregation
           ("gcn", 700, 640),        # aggregation in two panels / with two pieces per lane
+          ("gcn", 1100, 1028),      # last panel of a bfloat16 row narrower than one access
           ("gcn", 80, 12),          # rows of few lanes, one window moved left
           ("sage", 100, 260), ("sage", 64, 36)]
 
