@@ -395,10 +395,9 @@ int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
 size_t wgrad_workspace_floats(int32_t N1, int32_t N2, int64_t M, int32_t N2b = 0);
 size_t colsum_workspace_floats(int32_t N);
 // shared by the kernels; resident = workgroups of the kernel the chip holds at once (float32: three per CU; bfloat16:
-// two; float32 on the bfloat16 matrix cores: 256x128 tiles at two per CU, 128x128 at three)
-constexpr int32_t WGRAD_RESIDENT_F32 = 768, WGRAD_RESIDENT_BF16 = 512;
-constexpr int32_t WGRAD_RESIDENT_SPLIT_TALL = 512, WGRAD_RESIDENT_SPLIT = 768;
-int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident, int32_t tile_rows = 128);
+// two; float32 on the bfloat16 matrix cores: two, of which two rounds, so that no sum is longer than on the float32 ones)
+constexpr int32_t WGRAD_RESIDENT_F32 = 768, WGRAD_RESIDENT_BF16 = 512, WGRAD_RESIDENT_SPLIT = 1024;
+int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident);
 struct ColsumK;
 int32_t plan_colsum(const WgradArgs& a, ColsumK* k, SplitSums* sums);  // extra workgroups of a launch, if any
 // float32 products on the bfloat16 matrix cores (gemm_split.hip): which shapes they take, and their launchers

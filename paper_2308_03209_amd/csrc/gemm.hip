@@ -710,8 +710,8 @@ int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
 // CU, 77 chunks x 10 tiles = 770 workgroups ran 1.5 rounds in the time of 2); and as many rounds as it takes
 // to have at least 128 chunks, since few long chunks measured slower (256x602 over 230k nodes: 51 chunks
 // 73 TFLOP/s, 102 chunks 91, 153 chunks 98).  At least 512 reduction steps per chunk, at most 512 chunks.
-int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident, int32_t tile_rows) {
-  const int64_t tiles = (int64_t)((N1 + tile_rows - 1) / tile_rows) * ((N2 + BN - 1) / BN);
+int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident) {
+  const int64_t tiles = (int64_t)((N1 + BM - 1) / BM) * ((N2 + BN - 1) / BN);
   int64_t rounds = 1;
   while (rounds < 8 && resident * rounds / tiles < 128) ++rounds;
   int64_t s = resident * rounds / tiles;
@@ -734,8 +734,8 @@ int32_t wgrad_splits(int32_t N1, int32_t N2, int64_t M, int32_t resident, int32_
 size_t wgrad_workspace_floats(int32_t N1, int32_t first, int64_t M, int32_t N2b) {
   const int32_t N2 = first + N2b;
   const int32_t s32 = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_F32), s16 = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_BF16);
-  const int32_t tall = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_SPLIT_TALL, 256);
-  return std::max((size_t)std::max(std::max(s32, s16), tall) * ((size_t)N1 * (size_t)N2 + (size_t)N1),
+  const int32_t split = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_SPLIT);
+  return std::max((size_t)std::max(std::max(s32, s16), split) * ((size_t)N1 * (size_t)N2 + (size_t)N1),
                   wgrad_bf16_workspace_floats(N1, first, N2b, M));
 }
 

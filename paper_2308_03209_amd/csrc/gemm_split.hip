@@ -1,30 +1,37 @@
 // Float32 products of the layers on the bfloat16 matrix cores, with float32 operands, sums and results.
 //
-// A float32 has 24 significant bits and a bfloat16 eight, over the same exponent range, so every float32 is the
-// exact sum of three bfloat16: x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m (both differences are
-// exact in float32, and the second has at most eight bits left).  A product of two float32 is then nine products
-// of bfloat16, each exact in float32; the six that reach 2^-24 of it (l h, h l, m m, m h, h m, h h) are accumulated
-// in float32, smallest first - the three-way split of Henry, Tang and Heinecke ("Leveraging the bfloat16 artificial
-// intelligence datatype for higher-precision computations", ARITH 2019).  What is left out is below 2^-23 of a
-// product at worst and around 2^-27 of it on average, less than the rounding of the running sum.
+// A float32 has 24 significant bits and a bfloat16 eight, so a float32 is the sum of three bfloat16: x = h + m + l with
+// h = bf16(x), m = bf16(x - h), l = x - h - m (both differences are exact in float32, and the second has at most eight
+// bits left).  A product of two float32 is then nine products of bfloat16, each exact in float32; the six that reach
+// 2^-24 of it (l h, h l, m m, m h, h m, h h) are summed in float32 - the three-way split of Henry, Tang and Heinecke
+// ("Leveraging the bfloat16 artificial intelligence datatype for higher-precision computations", ARITH 2019).  What is
+// left out is below 2^-23 of a product at worst and around 2^-27 of it on average, less than the rounding of the
+// running sum.
 //
 // Which shapes: results of more than 64 columns (weight gradients: more than 64 rows and columns) and ranges of at
 // least eight k.  Narrower ones are bound by their bytes and stay on the float32 instructions (gemm.hip).
 //
+// Rounding: every matrix instruction rounds its accumulator once.  h h has one of its own and the five products below it
+// another, which is about 2^-8 of the first, so that its rounding does not show; the two are added at the end.  The sum
+// is then rounded once per 16 k, where the float32 instructions round it once per pair of k - but only for pairs that
+// are not zero: features and gated gradients may be sparse, and with all six products in one accumulator results came
+// out up to twice as far from float64 as with float32 instructions.  Error against float64 relative to the result,
+// float32 instructions / one accumulator / two: 88k x 512 x 512 4.0e-7 / 3.4e-7 / 1.3e-7, with half of operand A zero
+// 2.9e-7 / 3.3e-7 / 9.8e-8, with nine tenths zero 1.3e-7 / 2.3e-7 / 5.2e-8; weight gradients of the same operands
+// 4.6e-7 / 4.1e-7 / 1.8e-7, 2.4e-7 / 3.6e-7 / 1.3e-7 and 1.1e-7 / 1.4e-7 / 1.0e-7.
+//
 // What bounds it: a 32x32x16 bfloat16 matrix instruction takes 32 cycles, eight 32x32x2 float32 ones 512, so six of
 // the former could be 2.7 times as fast; but a loop of nothing but matrix instructions on random data already lowers
-// the shader clock from 2.4 to 1.8 GHz (1,860 TFLOP/s in bfloat16), and this kernel runs at about 1.6 GHz with the
-// matrix units 65 % busy: power, not issue slots, is the limit (128x128 tiles with half the reuse are only 4 %
-// slower).  Measured against the float32 instructions, in TFLOP/s of the product: 470k x 512 x 512 125 -> 206 (A B^T),
-// 122 -> 188 (A B), 124 -> 214 (A^T B); 529k x 512 x 1024 132 -> 220 and 128 -> 239; 230k x 256 x 602 112 -> 158 and
-// 99 -> 155.  The error against float64 is below that of the float32 instructions (230k-node and 529k-node sums:
-// 6.3e-8 against 7.6e-8; K = 602: 3.7e-7 against 4.4e-7) because the running sum is rounded six times per 16 k
-// instead of eight.
+// the shader clock from 2.4 to 1.8 GHz (1,860 TFLOP/s in bfloat16): power, not issue slots, is the limit, with LDS at
+// three quarters of its rate behind it.  Measured against the float32 instructions, in TFLOP/s of the product: 470k x
+// 512 x 512 127 -> 169 (A B^T); 529k x 512 x 1024 134 -> 187; 230k x 256 x 602 118 -> 148; 115k x 256 x 512 112 -> 158.
 //
-// Tiling: four wavefronts 2x2 per workgroup, each 32 RM x 32 RN of the result (64x128 or 128x64: 18 operand reads
-// from LDS per 48 matrix instructions), two workgroups per CU; see run_split for the pipeline.
+// Tiling: 128x128 of the result per workgroup, four wavefronts 2x2 of 64x64 each (128 accumulators: two sets of four
+// 32x32 blocks), two workgroups per CU; see run_split for the pipeline.  One set of accumulators leaves room for
+// 128x256 tiles (189 TFLOP/s at 470k x 512 x 512, where two sets give 169); two sets in such tiles measured 163 with
+// one wavefront per SIMD and 168 with eight wavefronts in one workgroup.
 //
-// LDS plane of an operand of R rows: [k-group of 8][row][8 bfloat16].  A matrix operand - 8 consecutive k of 32
+// LDS plane of an operand of 128 rows: [k-group of 8][row][8 bfloat16].  A matrix operand - 8 consecutive k of 32
 // consecutive rows per half wavefront - is then 512 contiguous bytes.  Neighbouring rows are swapped in every other
 // group of eight and the second k-group is 64 bytes further than its rows take, so that all ways of filling a plane
 // (eight lanes = four rows of both k-groups, every row or every other row of one) write 128 distinct bytes: no bank
@@ -74,12 +81,10 @@ struct SplitK {
   DropoutK drop;
 };
 
-template <int ROWS>
-struct Plane {
-  static constexpr int KG = ROWS * 16 + 64;  // bytes of a k-group
-  static constexpr int SIZE = 2 * KG;        // bytes of a plane (16 k)
-  static constexpr int BYTES = 3 * SIZE;     // the three planes of an operand
-};
+constexpr int TILE = 128;                 // rows and columns of a workgroup's result
+constexpr int PLANE_KG = TILE * 16 + 64;  // bytes of a k-group
+constexpr int PLANE = 2 * PLANE_KG;       // bytes of a plane (16 k)
+constexpr int OPERAND = 3 * PLANE;        // the three planes of an operand
 __device__ inline int plane_row(int row) { return (row ^ ((row >> 3) & 1)) * 16; }
 
 // x0, x1 -> their high, middle and low parts, packed (x0 in the low half of each dword)
@@ -92,7 +97,6 @@ __device__ inline void split_pair(float x0, float x1, uint32_t& h, uint32_t& m, 
 }
 
 // eight consecutive k of one row, split and written to the three planes at d
-template <int ROWS>
 __device__ inline void store_group(unsigned char* d, const float (&x)[8]) {
   uint4 h, m, l;
   split_pair(x[0], x[1], h.x, m.x, l.x);
@@ -100,49 +104,43 @@ __device__ inline void store_group(unsigned char* d, const float (&x)[8]) {
   split_pair(x[4], x[5], h.z, m.z, l.z);
   split_pair(x[6], x[7], h.w, m.w, l.w);
   *reinterpret_cast<uint4*>(d) = h;
-  *reinterpret_cast<uint4*>(d + Plane<ROWS>::SIZE) = m;
-  *reinterpret_cast<uint4*>(d + 2 * Plane<ROWS>::SIZE) = l;
+  *reinterpret_cast<uint4*>(d + PLANE) = m;
+  *reinterpret_cast<uint4*>(d + 2 * PLANE) = l;
 }
 
-// ---- operand movers: ROWS rows x 16 k of an operand from memory to registers to LDS ---------------------------
-// A thread's share is UNITS groups of eight consecutive k of one row.  Loads are unconditional vector loads at a
-// block-uniform base plus 32-bit offsets.  Rows past the matrix edge repeat its last row (they feed results that are
-// never stored); k past the end of the range are read inside it and become zero on the way to LDS.
+// ---- operand movers: 128 rows x 16 k of an operand from memory to registers to LDS -----------------------------
+// A thread's share is eight consecutive k of one row.  Loads are unconditional vector loads at a block-uniform base plus
+// 32-bit offsets.  Rows past the matrix edge repeat its last row (they feed results that are never stored); k past the
+// end of the range are read inside it and become zero on the way to LDS.
 
-// k-contiguous source: thread t holds k-group t%2 of rows t/2 + 128 u.  The range has at least eight k: a group that
-// would cross its end is read eight from the end and moved into place (three select stages).
-template <int ROWS>
+// k-contiguous source: thread t holds k-group t%2 of row t/2.  The range has at least eight k: a group that would cross
+// its end is read eight from the end and moved into place (three select stages).
 struct SplitKContig {
-  static constexpr int UNITS = ROWS / 128;
   struct Raw {
-    float4u x[UNITS][2];
+    float4u x[2];
   };
   const float* base;
-  uint32_t off[UNITS];
+  uint32_t off;
   int kq, k_len;
   __device__ void init(const float* P, int64_t ld, int64_t extent, int64_t i0, int64_t k_len_, int tid) {
     base = P + i0 * ld;
     kq = (tid & 1) * 8;
     k_len = (int)k_len_;
-    const int64_t last = extent - 1 - i0;
-#pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-      const int64_t r = (tid >> 1) + 128 * u;
-      off[u] = (uint32_t)((r < last ? r : last) * ld);
-    }
+    const int64_t last = extent - 1 - i0, r = tid >> 1;
+    off = (uint32_t)((r < last ? r : last) * ld);
   }
   __device__ void load(int k0, Raw& w) const {
     const int k = k0 + kq < k_len - 8 ? k0 + kq : k_len - 8;
-#pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-      w.x[u][0] = *reinterpret_cast<const float4u*>(base + (off[u] + (uint32_t)k));
-      w.x[u][1] = *reinterpret_cast<const float4u*>(base + (off[u] + (uint32_t)k + 4));
-    }
+    w.x[0] = *reinterpret_cast<const float4u*>(base + (off + (uint32_t)k));
+    w.x[1] = *reinterpret_cast<const float4u*>(base + (off + (uint32_t)k + 4));
   }
-  __device__ void store(unsigned char* lds, int tid, int k0, int u, const Raw& w, float) const {
+  // ODD: with the other sign in odd rows
+  template <bool ODD>
+  __device__ void store(unsigned char* lds, int tid, int k0, const Raw& w, float) const {
+    const uint32_t flip = ODD ? (uint32_t)tid << 30 & 0x80000000u : 0u;
     float e[8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) e[c] = w.x[u][c >> 2][c & 3];
+    for (int c = 0; c < 8; ++c) e[c] = __uint_as_float(__float_as_uint(w.x[c >> 2][c & 3]) ^ flip);
     if (k0 + SBK > k_len) {  // uniform: the last step of a ragged range
       const int sh = k0 + kq - (k_len - 8);  // how far the group was moved; eight and more: nothing of it exists
       if (sh > 0) {
@@ -155,105 +153,85 @@ struct SplitKContig {
         for (int c = 0; c < 8; ++c) e[c] = sh > 7 ? 0.f : e[c];
       }
     }
-    store_group<ROWS>(lds + (tid & 1) * Plane<ROWS>::KG + plane_row((tid >> 1) + 128 * u), e);
+    store_group(lds + (tid & 1) * PLANE_KG + plane_row(tid >> 1), e);
   }
-  __device__ void add_rows(int, const Raw&, float (&)[2]) const {}
+  __device__ float sum(int, const Raw&) const { return 0.f; }
 };
 
-// k-major source (element (i, k) at P[k ld + i]): thread t holds UNITS consecutive columns of the eight k of group
-// t / 128 (the same for a whole wavefront, so rows are addressed with scalars), one or two elements per load.  A pair
-// that would cross the matrix edge is read one column further left; the matrix has at least UNITS columns.
-template <int ROWS>
+// k-major source (element (i, k) at P[k ld + i]): thread t holds column t%128 of the eight k of group t/128 (the same for
+// a whole wavefront, so rows are addressed with scalars).
 struct SplitKMajor {
-  static constexpr int UNITS = ROWS / 128, T = 128;  // T threads per k-group
   struct Raw {
-    float x[8][UNITS];
+    float x[8];
   };
   const float* base;
   int64_t ld;
-  uint32_t off;   // first column of the thread
+  uint32_t off;   // the thread's column
   int kq, k_len;  // kq: first k of the thread's group
-  bool moved;     // the thread's pair was moved left: its first column is the pair's second
   __device__ void init(const float* P, int64_t ld_, int64_t extent, int64_t i0, int64_t k_len_, int tid) {
     base = P;
     ld = ld_;
-    kq = __builtin_amdgcn_readfirstlane((tid / T) * 8);
+    kq = __builtin_amdgcn_readfirstlane((tid / TILE) * 8);
     k_len = (int)k_len_;
-    const int64_t i = i0 + (tid % T) * UNITS;
-    const int64_t start = i < extent - UNITS ? i : extent - UNITS;
-    moved = UNITS == 2 && start < i;
-    off = (uint32_t)start;
+    const int64_t i = i0 + tid % TILE;
+    off = (uint32_t)(i < extent - 1 ? i : extent - 1);
   }
   __device__ void load(int k0, Raw& w) const {
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       const int k = k0 + kq + c < k_len ? k0 + kq + c : k_len - 1;
       const float* const row = base + k * ld;
-      if constexpr (UNITS == 2) {
-        typedef float float2u __attribute__((ext_vector_type(2), aligned(4)));
-        const float2u t = *reinterpret_cast<const float2u*>(row + off);
-        w.x[c][0] = t[0];
-        w.x[c][1] = t[1];
-      } else {
-        w.x[c][0] = row[off];
-      }
+      w.x[c] = row[off];
     }
   }
-  __device__ float value(int k0, int c, int u, const Raw& w) const {
-    const float v = moved ? w.x[c][UNITS - 1] : w.x[c][u];
-    return k0 + kq + c < k_len ? v : 0.f;
-  }
+  __device__ float value(int k0, int c, const Raw& w) const { return k0 + kq + c < k_len ? w.x[c] : 0.f; }
   // sign: 1 or -1 on every element
-  __device__ void store(unsigned char* lds, int tid, int k0, int u, const Raw& w, float sign) const {
+  template <bool>
+  __device__ void store(unsigned char* lds, int tid, int k0, const Raw& w, float sign) const {
     float e[8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) e[c] = sign * value(k0, c, u, w);
-    store_group<ROWS>(lds + (tid / T) * Plane<ROWS>::KG + plane_row((tid % T) * UNITS + u), e);
+    for (int c = 0; c < 8; ++c) e[c] = sign * value(k0, c, w);
+    store_group(lds + (tid / TILE) * PLANE_KG + plane_row(tid % TILE), e);
   }
-  // s[u] += the thread's eight k of its column u (weight gradients: column sums of operand A)
-  __device__ void add_rows(int k0, const Raw& w, float (&s)[2]) const {
+  // sum of the thread's eight k (weight gradients: column sums of operand A)
+  __device__ float sum(int k0, const Raw& w) const {
+    float t = 0.f;
 #pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-      float t = 0.f;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) t += value(k0, c, u, w);
-      s[u] += t;
-    }
+    for (int c = 0; c < 8; ++c) t += value(k0, c, w);
+    return t;
   }
 };
 
-// 16 k of a wavefront's RM x RN blocks: 6 RM RN matrix instructions.  The operand with fewer blocks stays in
-// registers, the other one streams; between(o) is called in front of the o-th of its blocks.
-template <int TM, int TN, int RM, int RN, typename F>
-__device__ inline void multiply_step(const unsigned char* as, const unsigned char* bs, floatx16 (&acc)[RM][RN],
-                                     F between) {
-  constexpr bool STREAM_A = RM > RN;
-  constexpr int RK = STREAM_A ? RN : RM, RS = STREAM_A ? RM : RN;  // kept, streamed
-  const unsigned char* const kp = STREAM_A ? bs : as;
-  const unsigned char* const sp = STREAM_A ? as : bs;
-  constexpr int KS = Plane<STREAM_A ? TN : TM>::SIZE, SS = Plane<STREAM_A ? TM : TN>::SIZE;
-  bf16x8 kept[3][RK], st[2][3];
+// The accumulators of a wavefront's 2x2 blocks of 32x32: of h h, and of the five smaller products.
+struct Sums {
+  floatx16 hh[2][2], rest[2][2];
+};
+
+// 16 k of a wavefront's blocks: 24 matrix instructions.  Operand A stays in registers, B streams; between(o) is called in
+// front of the o-th block column.
+template <typename F>
+__device__ inline void multiply_step(const unsigned char* as, const unsigned char* bs, Sums& acc, F between) {
+  bf16x8 a[3][2], b[2][3];
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
 #pragma unroll
-    for (int m = 0; m < RK; ++m) kept[p][m] = *reinterpret_cast<const bf16x8*>(kp + p * KS + m * 512);
-    st[0][p] = *reinterpret_cast<const bf16x8*>(sp + p * SS);
+    for (int m = 0; m < 2; ++m) a[p][m] = *reinterpret_cast<const bf16x8*>(as + p * PLANE + m * 512);
+    b[0][p] = *reinterpret_cast<const bf16x8*>(bs + p * PLANE);
   }
 #pragma unroll
-  for (int o = 0; o < RS; ++o) {
-    if (o + 1 < RS) {
+  for (int o = 0; o < 2; ++o) {
+    if (o == 0) {
 #pragma unroll
-      for (int p = 0; p < 3; ++p) st[(o + 1) & 1][p] = *reinterpret_cast<const bf16x8*>(sp + p * SS + (o + 1) * 512);
+      for (int p = 0; p < 3; ++p) b[1][p] = *reinterpret_cast<const bf16x8*>(bs + p * PLANE + 512);
     }
     between(o);
-    constexpr int PK[6] = {2, 0, 1, 1, 0, 0}, PS[6] = {0, 2, 1, 0, 1, 0};
+    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};  // smallest products first
 #pragma unroll
     for (int q = 0; q < 6; ++q)
 #pragma unroll
-      for (int m = 0; m < RK; ++m) {
-        floatx16& c = STREAM_A ? acc[o][m] : acc[m][o];
-        c = STREAM_A ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(st[o & 1][PS[q]], kept[PK[q]][m], c, 0, 0, 0)
-                     : __builtin_amdgcn_mfma_f32_32x32x16_bf16(kept[PK[q]][m], st[o & 1][PS[q]], c, 0, 0, 0);
+      for (int m = 0; m < 2; ++m) {
+        floatx16& c = q < 5 ? acc.rest[m][o] : acc.hh[m][o];
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]][m], b[o][PB[q]], c, 0, 0, 0);
       }
   }
 }
@@ -264,35 +242,32 @@ __device__ inline void multiply_step(const unsigned char* as, const unsigned cha
 // half in between the matrix instructions (a wavefront's vector instructions issue while its matrix instructions
 // run), and step t+2 is requested from memory into the registers that this frees.
 //
-// FLIP (weight gradients: thousands of k in one sum, partial sums added over many chunks): the matrix instructions cut
-// off (towards minus infinity) what of a small product lies far below the running sum, which over 2.7k k of one sign
-// comes to 6e-8 of the result - little, but it does not average out over the chunks.  So the sign of the sum and of
-// operand B changes every FLIP_STEPS steps, and what is cut off cancels.
+// The matrix instructions cut off (towards minus infinity) what of a small product lies far below the running sum.  In
+// one result that is little, but it does not average out where results are added up: over neighbours, over all nodes in
+// a bias gradient, over the chunks of a weight gradient (115k nodes, 256 wide: bias gradients three layers down were
+// 4.7e-7 off, with float32 instructions 7.4e-8).  So half of the sums are formed with the other sign, and what is cut off
+// cancels: results in odd rows of a product (on operand A, taken back when they are written); in weight gradients every
+// FLIP_STEPS steps of a sum (FLIP, on operand B), starting with the other sign in odd chunks (phase).
 constexpr int FLIP_STEPS = 16;
-template <int TM, int TN, int RM, int RN, bool FLIP, typename MA, typename MB>
+template <bool FLIP, typename MA, typename MB>
 __device__ inline void run_split(const MA& ma, const MB& mb, int k_len, unsigned char* smem, int a_off, int b_off,
-                                 floatx16 (&acc)[RM][RN], int tid, bool colsum, float (&csum)[2]) {
-  constexpr int HALF = Plane<TM>::BYTES + Plane<TN>::BYTES;  // bytes of one step's operands
-  constexpr int RS = RM > RN ? RM : RN;
+                                 Sums& acc, int tid, int phase, bool colsum, float& csum) {
   const int n = (k_len + SBK - 1) / SBK;
   typename MA::Raw ra;
   typename MB::Raw rb;
-  auto put = [&](int t, int u) {  // unit u of the thread's share of step t
-    unsigned char* const d = smem + (t & 1) * HALF;
-    const int k0 = t * SBK;
-    if (u < MA::UNITS) {
-      ma.store(d, tid, k0, u, ra, 1.f);
-      if (u == 0 && colsum) ma.add_rows(k0, ra, csum);
-    } else {
-      mb.store(d + Plane<TM>::BYTES, tid, k0, u - MA::UNITS, rb, FLIP && (t / FLIP_STEPS) % 2 ? -1.f : 1.f);
-    }
+  auto put_a = [&](int t) {  // the thread's share of step t
+    ma.template store<!FLIP>(smem + (t & 1) * 2 * OPERAND, tid, t * SBK, ra, 1.f);
+    if (colsum) csum += ma.sum(t * SBK, ra);
   };
-  constexpr int UNITS = MA::UNITS + MB::UNITS;
+  auto put_b = [&](int t) {
+    mb.template store<false>(smem + (t & 1) * 2 * OPERAND + OPERAND, tid, t * SBK, rb,
+                             FLIP && (t / FLIP_STEPS + phase) % 2 ? -1.f : 1.f);
+  };
   ma.load(0, ra);
   mb.load(0, rb);
   __syncthreads();  // whoever used the LDS before is done
-#pragma unroll
-  for (int u = 0; u < UNITS; ++u) put(0, u);
+  put_a(0);
+  put_b(0);
   if (n > 1) {
     ma.load(SBK, ra);
     mb.load(SBK, rb);
@@ -300,21 +275,21 @@ __device__ inline void run_split(const MA& ma, const MB& mb, int k_len, unsigned
   __syncthreads();
   auto flip = [&]() {
 #pragma unroll
-    for (int m = 0; m < RM; ++m)
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int q = 0; q < RN; ++q)
+      for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[m][q][v] = -acc[m][q][v];
+        for (int v = 0; v < 16; ++v) acc.hh[m][q][v] = -acc.hh[m][q][v], acc.rest[m][q][v] = -acc.rest[m][q][v];
   };
 #pragma nounroll
   for (int t = 0; t + 1 < n; ++t) {
     if (FLIP && t > 0 && t % FLIP_STEPS == 0) flip();
-    const unsigned char* const d = smem + (t & 1) * HALF;
-    multiply_step<TM, TN, RM, RN>(d + a_off, d + Plane<TM>::BYTES + b_off, acc, [&](int o) {
-#pragma unroll
-      for (int u = 0; u < UNITS; ++u)
-        if (u % RS == o) put(t + 1, u);
-      if (o == RS - 1) {
+    const unsigned char* const d = smem + (t & 1) * 2 * OPERAND;
+    multiply_step(d + a_off, d + OPERAND + b_off, acc, [&](int o) {
+      if (o == 0) {
+        put_a(t + 1);
+      } else {
+        put_b(t + 1);
         const int t2 = t + 2 < n ? t + 2 : n - 1;
         ma.load(t2 * SBK, ra);
         mb.load(t2 * SBK, rb);
@@ -323,9 +298,9 @@ __device__ inline void run_split(const MA& ma, const MB& mb, int k_len, unsigned
     __syncthreads();
   }
   if (FLIP && n > 1 && (n - 1) % FLIP_STEPS == 0) flip();
-  const unsigned char* const d = smem + ((n - 1) & 1) * HALF;
-  multiply_step<TM, TN, RM, RN>(d + a_off, d + Plane<TM>::BYTES + b_off, acc, [](int) {});
-  if (FLIP && ((n - 1) / FLIP_STEPS) % 2) flip();
+  const unsigned char* const d = smem + ((n - 1) & 1) * 2 * OPERAND;
+  multiply_step(d + a_off, d + OPERAND + b_off, acc, [](int) {});
+  if (FLIP && ((n - 1) / FLIP_STEPS + phase) % 2) flip();
 }
 
 // One 32x32 block of the result over the same range on the float32 matrix instructions, operands straight from
@@ -346,14 +321,12 @@ __device__ inline void run_plain(const float* A, int64_t sia, int64_t ska, const
 // DROP: dropout of the result, in rows of a multiple of four contiguous columns (529k x 512 with K = 1024: a pass of its own
 // took 353 us, a training step with three of them is 760 us shorter without).  Its generator runs beside the matrix
 // instructions of the CU's other workgroup, where a pass of its own reads and writes the result once more.
-template <bool A_KMAJOR, bool B_KMAJOR, int RM, int RN, bool DROP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 ? 2 : 3))) void gemm_split_kernel(
+template <bool A_KMAJOR, bool B_KMAJOR, bool DROP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(
     const SplitK p) {
-  constexpr int TM = 64 * RM, TN = 64 * RN;
-  constexpr int STAGE_LD = 32 * RN + 4, STAGE_WAVE = 32 * STAGE_LD;  // result staging: floats
-  constexpr int OPERANDS = 2 * (Plane<TM>::BYTES + Plane<TN>::BYTES);
-  constexpr int STAGING = A_KMAJOR ? 0 : 4 * STAGE_WAVE * 4;
-  __shared__ __attribute__((aligned(128))) unsigned char smem[OPERANDS > STAGING ? OPERANDS : STAGING];
+  constexpr int STAGE_LD = 68, STAGE_WAVE = 32 * STAGE_LD;  // result staging: floats
+  __shared__ __attribute__((aligned(128))) unsigned char smem[4 * OPERAND];
+  static_assert(4 * OPERAND >= 4 * STAGE_WAVE * 4, "results are staged where the operands were");
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -374,22 +347,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
     if (group >= p.n_groups) return;  // padding of the last group octet (uniform over the block)
     if constexpr (A_KMAJOR) {
       z = group;
-      i0 = (member / p.tiles_n) * TM;
-      j0 = (member % p.tiles_n) * TN;
+      i0 = (member / p.tiles_n) * TILE;
+      j0 = (member % p.tiles_n) * TILE;
     } else {
-      i0 = group * TM;
-      j0 = member * TN;
+      i0 = group * TILE;
+      j0 = member * TILE;
     }
   }
-  const int a_off = g * Plane<TM>::KG + wm * RM * 512 + plane_row(r);
-  const int b_off = g * Plane<TN>::KG + wn * RN * 512 + plane_row(r);
-  floatx16 acc[RM][RN];
+  const int a_off = g * PLANE_KG + wm * 1024 + plane_row(r);
+  const int b_off = g * PLANE_KG + wn * 1024 + plane_row(r);
+  Sums sums;
 #pragma unroll
-  for (int m = 0; m < RM; ++m)
+  for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int n = 0; n < RN; ++n)
+    for (int n = 0; n < 2; ++n)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[m][n][v] = 0.f;
+      for (int v = 0; v < 16; ++v) sums.hh[m][n][v] = sums.rest[m][n][v] = 0.f;
 
   // weight gradients: this block's chunk of nodes and its matrix of operand B
   int64_t k_beg = 0, k_len = 0;
@@ -408,47 +381,53 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
     }
   }
   const int n_seg = !A_KMAJOR && p.K2 > 0 ? 2 : 1;
-  float csum[2] = {0.f, 0.f};
+  float csum = 0.f;
   if constexpr (A_KMAJOR) {
     if (k_len > 0) {
-      SplitKMajor<TM> ma;
-      SplitKMajor<TN> mb;
+      SplitKMajor ma;
+      SplitKMajor mb;
       ma.init(p.A1 + k_beg * p.lda1, p.lda1, p.M, i0, k_len, tid);
       mb.init(Bw + k_beg * ldbw, ldbw, extent_b, jw, k_len, tid);
-      run_split<TM, TN, RM, RN, true>(ma, mb, (int)k_len, smem, a_off, b_off, acc, tid, p.colsum_part != nullptr && j0 == 0,
-                                csum);
+      run_split<true>(ma, mb, (int)k_len, smem, a_off, b_off, sums, tid, (int)(z & 1), p.colsum_part != nullptr && j0 == 0, csum);
     }
   } else {
     // one loop body for both segments (two inlined copies would each claim their own accumulators)
 #pragma nounroll
     for (int seg = 0; seg < n_seg; ++seg) {
       const int k_seg = (int)(seg ? p.K2 : p.K1);
-      SplitKContig<TM> ma;
+      SplitKContig ma;
       ma.init(seg ? p.A2 : p.A1, seg ? p.lda2 : p.lda1, p.M, i0, k_seg, tid);
       if constexpr (B_KMAJOR) {
-        SplitKMajor<TN> mb;
+        SplitKMajor mb;
         mb.init(seg ? p.B2 : p.B1, seg ? p.ldb2 : p.ldb1, p.N, j0, k_seg, tid);
-        run_split<TM, TN, RM, RN, false>(ma, mb, k_seg, smem, a_off, b_off, acc, tid, false, csum);
+        run_split<false>(ma, mb, k_seg, smem, a_off, b_off, sums, tid, 0, false, csum);
       } else {
-        SplitKContig<TN> mb;
+        SplitKContig mb;
         mb.init(seg ? p.B2 : p.B1, seg ? p.ldb2 : p.ldb1, p.N, j0, k_seg, tid);
-        run_split<TM, TN, RM, RN, false>(ma, mb, k_seg, smem, a_off, b_off, acc, tid, false, csum);
+        run_split<false>(ma, mb, k_seg, smem, a_off, b_off, sums, tid, 0, false, csum);
       }
     }
   }
+  floatx16(&acc)[2][2] = sums.hh;
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[m][n][v] += sums.rest[m][n][v];
   bool tile_done = false;  // uniform over the block
   {
     float bad = 0.f;  // stays zero while every result is finite
 #pragma unroll
-    for (int m = 0; m < RM; ++m)
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int n = 0; n < RN; ++n)
+      for (int n = 0; n < 2; ++n)
 #pragma unroll
         for (int v = 0; v < 16; ++v) bad = fmaf(acc[m][n][v], 0.f, bad);
     if (__syncthreads_or(!(bad == 0.f))) {
 #pragma nounroll
-      for (int blk = 0; blk < RM * RN; ++blk) {
-        const int64_t ib = i0 + (wm * RM + blk / RN) * 32, jb = (wn * RN + blk % RN) * 32;
+      for (int blk = 0; blk < 4; ++blk) {
+        const int64_t ib = i0 + (wm * 2 + blk / 2) * 32, jb = (wn * 2 + blk % 2) * 32;
         const int64_t ia = ib + r < p.M ? ib + r : p.M - 1, ja = jw + jb + r < extent_b ? jw + jb + r : extent_b - 1;
         floatx16 c;
 #pragma unroll
@@ -494,13 +473,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
     float* Cz = p.C + z * p.c_split_stride;
     if (!tile_done) {
 #pragma unroll
-      for (int m = 0; m < RM; ++m) {
+      for (int m = 0; m < 2; ++m) {
 #pragma unroll
-        for (int n = 0; n < RN; ++n) {
-          const int64_t j = j0 + wn * (32 * RN) + n * 32 + r;
+        for (int n = 0; n < 2; ++n) {
+          const int64_t j = j0 + wn * 64 + n * 32 + r;
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
-            const int64_t i = i0 + wm * (32 * RM) + m * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
+            const int64_t i = i0 + wm * 64 + m * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
             if (j < p.N && i < p.M) Cz[i * p.ldc + j] = acc[m][n][v];
           }
         }
@@ -508,27 +487,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
     }
     if (p.colsum_part != nullptr && j0 == 0) {
       // the two k-groups of a column are added in order through LDS
-      using MA = SplitKMajor<TM>;
       float* const red = reinterpret_cast<float*>(smem);
       __syncthreads();
-#pragma unroll
-      for (int u = 0; u < MA::UNITS; ++u) red[(tid / MA::T) * TM + (tid % MA::T) * MA::UNITS + u] = csum[u];
+      red[tid] = csum;
       __syncthreads();
-      if (tid < TM && i0 + tid < p.M) {
-        p.colsum_part[z * p.M + i0 + tid] = red[tid] + red[TM + tid];
-      }
+      if (tid < TILE && i0 + tid < p.M) p.colsum_part[z * p.M + i0 + tid] = red[tid] + red[TILE + tid];
     }
   } else {
     // Each wavefront passes its result through LDS in 32-row blocks, after which a lane holds four consecutive
     // columns of one row: gate and accumulate operands are read, and the result is written, 16 bytes at a time.
     // Those operands and the row scales do not depend on the product, so they are requested for four passes at a
     // time, unconditionally at clamped addresses, the first four of a block before its staging barriers.
-    constexpr int LPR = 8 * RN;       // lanes per staged row
+    constexpr int LPR = 16;           // lanes per staged row
     constexpr int RPP = 64 / LPR;     // rows per pass
     constexpr int PASSES = 32 / RPP;  // passes per 32-row block
     float* const st = reinterpret_cast<float*>(smem) + wave * STAGE_WAVE;
     const int er = lane / LPR, ec = (lane % LPR) * 4;
-    const int64_t jv = j0 + wn * (32 * RN) + ec;
+    const int64_t jv = j0 + wn * 64 + ec;
     const bool wide_lane = jv + 4 <= p.N;   // the lane's four columns all exist
     const int64_t jl = wide_lane ? jv : 0;  // where its 16-byte operand loads go (in range: N >= 4)
     const bool extras = p.gate || p.accumulate || p.row_scale;  // uniform over the launch
@@ -537,7 +512,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
       float rs;
     };
     auto request = [&](int m, int s, Extra& e) {
-      int64_t il = i0 + wm * (32 * RM) + m * 32 + s * RPP + er;
+      int64_t il = i0 + wm * 64 + m * 32 + s * RPP + er;
       if (il > p.M - 1) il = p.M - 1;
       e.g = float4u{1.f, 1.f, 1.f, 1.f};
       e.c = float4u{0.f, 0.f, 0.f, 0.f};
@@ -548,7 +523,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
     };
     auto pass = [&](int m, int s, bool have, const Extra& e) {
       const int row = s * RPP + er;
-      const int64_t i = i0 + wm * (32 * RM) + m * 32 + row;
+      const int64_t i = i0 + wm * 64 + m * 32 + row;
       if (i < p.M && jv < p.N) {
         const float4 t = *reinterpret_cast<const float4*>(st + row * STAGE_LD + ec);
         float x[4] = {t.x, t.y, t.z, t.w};
@@ -592,7 +567,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
       }
     };
 #pragma unroll
-    for (int m = 0; m < RM; ++m) {
+    for (int m = 0; m < 2; ++m) {
       Extra e[4] = {};
       if (extras) {
 #pragma unroll
@@ -600,12 +575,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
       }
       __syncthreads();  // operand planes (m = 0) / previous block no longer read
 #pragma unroll
-      for (int n = 0; n < RN; ++n) {
-        const int64_t j = j0 + wn * (32 * RN) + n * 32 + r;
+      for (int n = 0; n < 2; ++n) {
+        const int64_t j = j0 + wn * 64 + n * 32 + r;
         const float bj = (p.bias && j < p.N) ? p.bias[j] : 0.f;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          float x = acc[m][n][v] + bj;
+          float x = (v & 1 ? -acc[m][n][v] : acc[m][n][v]) + bj;  // odd rows were summed with the other sign
           if (p.relu) x = fmaxf(x, 0.f);
           st[(8 * (v >> 2) + 4 * g + (v & 3)) * STAGE_LD + n * 32 + r] = x;
         }
@@ -631,7 +606,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM* RN > 4 
   }
 }
 
-// 32-bit element offsets inside a tile: 256 rows of a k-contiguous operand, 32 k-rows of a k-major one
+// 32-bit element offsets inside a tile: 128 rows of a k-contiguous operand
 static bool split_strides_ok(int64_t lda, int64_t ldb) { return lda < ((int64_t)1 << 22) && ldb < ((int64_t)1 << 22); }
 
 bool gemm_split_fits(const GemmArgs& a) {
@@ -666,30 +641,20 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   p.gate_scale = a.gate ? a.gate_scale : 1.f;
   p.drop = dropout_k(a.dropout);
   const int64_t K = (int64_t)a.K1 + a.K2;
-  // 128x256 tiles where they fit the columns as well as 128x128 ones and give every CU its two workgroups (half
-  // the reads of operand A; the rates are equal within 4 %), else 128x128 (20k x 256 x 256: 27.5 against 30.9 us)
-  p.n_groups = (a.M + 127) / 128;
-  const int32_t tiles128 = (a.N + 127) / 128;
-  const bool wide = tiles128 % 2 == 0 && p.n_groups * (tiles128 / 2) >= 512;
-  p.tiles_n = wide ? tiles128 / 2 : tiles128;
+  p.n_groups = (a.M + TILE - 1) / TILE;
+  p.tiles_n = (a.N + TILE - 1) / TILE;
   const int64_t blocks = ((p.n_groups + 7) / 8) * 8 * p.tiles_n;
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "dense: grid too large");
   const bool drop = p.drop.scale != 0.f;  // forward products only
   char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<false,%s,2,%d,%s> N=%d K=%d", a.b_kmajor ? "true" : "false", wide ? 4 : 2,
+  if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<false,%s,%s> N=%d K=%d", a.b_kmajor ? "true" : "false",
            drop && !a.b_kmajor ? "true" : "false", (int)a.N, (int)K);
   ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + (double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1)),
                  2.0 * (double)a.M * a.N * (double)K);
   const dim3 grid((unsigned)blocks);
-  if (wide) {
-    if (a.b_kmajor) gemm_split_kernel<false, true, 2, 4, false><<<grid, 256, 0, stream>>>(p);
-    else if (drop) gemm_split_kernel<false, false, 2, 4, true><<<grid, 256, 0, stream>>>(p);
-    else gemm_split_kernel<false, false, 2, 4, false><<<grid, 256, 0, stream>>>(p);
-  } else {
-    if (a.b_kmajor) gemm_split_kernel<false, true, 2, 2, false><<<grid, 256, 0, stream>>>(p);
-    else if (drop) gemm_split_kernel<false, false, 2, 2, true><<<grid, 256, 0, stream>>>(p);
-    else gemm_split_kernel<false, false, 2, 2, false><<<grid, 256, 0, stream>>>(p);
-  }
+  if (a.b_kmajor) gemm_split_kernel<false, true, false><<<grid, 256, 0, stream>>>(p);
+  else if (drop) gemm_split_kernel<false, false, true><<<grid, 256, 0, stream>>>(p);
+  else gemm_split_kernel<false, false, false><<<grid, 256, 0, stream>>>(p);
   COFREE_HIP_CHECK(hipGetLastError());
   return COFREE_OK;
 }
@@ -701,8 +666,7 @@ bool wgrad_split_fits(const WgradArgs& a) {
 
 int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
   const int32_t N1 = a.N1, N2 = a.N2 + (a.B2 ? a.N2b : 0);
-  const bool tall = ((N1 + 127) / 128) % 2 == 0;  // 256x128 tiles where they fit the rows as well as 128x128 ones
-  const int32_t S = wgrad_splits(N1, N2, a.M, tall ? WGRAD_RESIDENT_SPLIT_TALL : WGRAD_RESIDENT_SPLIT, tall ? 256 : 128);
+  const int32_t S = wgrad_splits(N1, N2, a.M, WGRAD_RESIDENT_SPLIT);
   SplitK p{};
   p.A1 = (const float*)a.A;
   p.lda1 = a.lda;
@@ -720,8 +684,8 @@ int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stre
   p.k_chunk = ((chunk + SBK - 1) / SBK) * SBK;
   if (p.k_chunk < SBK) p.k_chunk = SBK;
   p.c_split_stride = (int64_t)N1 * N2;
-  p.tiles_m = (N1 + (tall ? 255 : 127)) / (tall ? 256 : 128);
-  p.tiles_n = (N2 + 127) / 128;
+  p.tiles_m = (N1 + TILE - 1) / TILE;
+  p.tiles_n = (N2 + TILE - 1) / TILE;
   p.n_groups = S;
   float* colsum_part = a.workspace + (size_t)S * N1 * N2;
   p.colsum_part = a.colsum_out && !a.colsum_src ? colsum_part : nullptr;
@@ -730,11 +694,10 @@ int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stre
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "wgrad: grid too large");
   {
     char pname[96] = "";
-    if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<true,true,%d,2,false> N=%dx%d", tall ? 4 : 2, (int)N1, (int)N2);
+    if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<true,true,false> N=%dx%d", (int)N1, (int)N2);
     ProfScope prof(pname, stream, 4.0 * ((double)a.M * N1 * (p.extra.X ? 2 : 1) + (double)a.M * N2 + (double)N1 * N2),
                    2.0 * (double)a.M * N1 * N2);
-    if (tall) gemm_split_kernel<true, true, 4, 2, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
-    else gemm_split_kernel<true, true, 2, 2, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
+    gemm_split_kernel<true, true, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
   }
   COFREE_HIP_CHECK(hipGetLastError());
   COFREE_TRY(add_split_sum(sums, a.workspace, p.c_split_stride, S, a.C, a.ldc, N1, N2));

@@ -533,12 +533,12 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
         COFREE_TRY(launch_wgrad(wgrad(p.T, d.d_out, H_in, d.d_in, grads->W + d.d_in, ldw, p.wg[1]), &sums, s));
       if (dH_in) {
         GemmArgs h = gemm();
-        // W_self and W_neigh are column blocks of W: dH = dPre W_self + dT W_neigh is one product over the
-        // two k-segments [dPre | dT], each with its own block
-        h.A1 = dPre; h.lda1 = d.d_out; h.K1 = d.d_out;
-        h.B = params->W; h.ldb = ldw; h.b_kmajor = 1;
-        h.A2 = p.T; h.lda2 = d.d_out; h.K2 = d.d_out;
-        h.B2 = params->W + d.d_in; h.ldb2 = ldw;
+        // W_self and W_neigh are column blocks of W: dH = dT W_neigh + dPre W_self is one product over the
+        // two k-segments [dT | dPre], each with its own block; the means first, which are the smaller terms
+        h.A1 = p.T; h.lda1 = d.d_out; h.K1 = d.d_out;
+        h.B = params->W + d.d_in; h.ldb = ldw; h.b_kmajor = 1;
+        h.A2 = dPre; h.lda2 = d.d_out; h.K2 = d.d_out;
+        h.B2 = params->W; h.ldb2 = ldw;
         h.C = dH_in; h.ldc = d.d_in; h.N = d.d_in;
         h.gate = in_gate; h.ldg = d.d_in; h.gate_scale = in_scale;
         COFREE_TRY(launch_gemm(h, s));

@@ -87,3 +87,72 @@ def test_weight_and_input_gradients(env, d_in, d_out):
     ref, mag = o_layers.gcn_aggregate(full, h @ w), o_layers.gcn_aggregate(full, np.abs(h) @ np.abs(w))
     # on top of the product: three roundings of scales and a sum over at most max-degree neighbours
     assert_rounding(dX.cpu().numpy(), ref, mag, d_out + 4 + int(np.max(np.diff(O["rowptr"]))), "dH_in")
+
+
+def ring(env, n):
+    src = np.arange(n, dtype=np.int64)
+    return env["B"].build_partition(n, src, (src + 1) % n, 1, 0, 3)
+
+
+def assert_no_lean(err, what):
+    """Errors that lean to neither side: a sum of m of them is about sqrt(m) times one, and eight times that is beyond
+    the largest of the few hundred sums looked at.  (Downstream such sums over all nodes are the bias gradients.)"""
+    m = err.shape[0]
+    lean = float(err.sum(0).abs().max() / (m ** 0.5 * err.square().mean().sqrt()))
+    assert lean <= 8.0, f"{what}: column sums of the errors {lean:.1f} times those of independent errors"
+
+
+@pytest.mark.parametrize("M,N,K", [(65_600, 128, 512), (40_000, 512, 96), (65_600, 256, 40)])
+def test_product_errors_do_not_lean(env, M, N, K):
+    B, torch = env["B"], env["torch"]
+    print(f"[case] split product, sums of errors M={M} N={N} K={K}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    A, W = (torch.randn(*s, generator=gen, device="cuda") for s in ((M, K), (N, K)))
+    C = torch.full((M, N), float("nan"), device="cuda")
+    B.dense_nt_f32(A, W, None, C, False)
+    assert_no_lean(C.double() - A.double() @ W.double().T, "product")
+
+
+@pytest.mark.parametrize("nonzero", [1.0, 0.1])
+def test_one_rounding_per_step(env, nonzero):
+    """The sum of a product is rounded once per 16 k, by a random part of at most half a unit: relative to the result
+    2^-24 sqrt(K / 16 / 3) at most, also where most operands are zero (and float32 instructions round less often)."""
+    B, torch = env["B"], env["torch"]
+    print(f"[case] split product, nonzero {nonzero}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    A, W = (torch.randn(*s, generator=gen, device="cuda") for s in ((20_000, 512), (512, 512)))
+    A = A * (torch.rand(A.shape, generator=gen, device="cuda") < nonzero)
+    C = torch.full((20_000, 512), float("nan"), device="cuda")
+    B.dense_nt_f32(A, W, None, C, False)
+    ref = A.double() @ W.double().T
+    assert float((C.double() - ref).norm() / ref.norm()) <= 2.0 ** -24 * (512 / 16 / 3) ** 0.5
+
+
+# 16-node steps of a chunk: 17, 33, 39 and 33 - the sign of the running sum changes every 16
+@pytest.mark.parametrize("n,d_in,d_out", [(15_000, 257, 300), (117_003, 257, 300), (140_003, 257, 300), (88_001, 257, 512)])
+def test_gradients_of_long_chunks(env, n, d_in, d_out):
+    """dW, db and dH_in of an aggregate-first GCN layer on a ring, where Ahat is the mean over a node and its two
+    neighbours.  A chunk's sum is rounded once per step and the sum of the chunks once for each, every time by at most
+    half a unit of a sum that is no larger than about the result: 2^-24 sqrt(roundings) of its norm."""
+    B, torch = env["B"], env["torch"]
+    print(f"[case] split gradients of long chunks n={n} {d_in} -> {d_out}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    A, dH, W = (torch.randn(*s, generator=gen, device="cuda") for s in ((n, d_in), (n, d_out), (d_out, d_in)))
+    d = B.layer_desc(B.GCN, d_in, 0, d_out)
+    ws = torch.empty(B.layer_workspace_bytes(d, n, True), dtype=torch.uint8, device="cuda")
+    g = {"W": torch.full_like(W, float("nan")), "bW": torch.full((d_out,), float("nan"), device="cuda")}
+    dX = torch.full((n, d_in), float("nan"), device="cuda")
+    B.layer_bwd(ring(env, n), None, 0, d, A, dH, {"W": W, "bW": torch.zeros(d_out, device="cuda")}, {"A": A}, dH, dX, g, False, ws)
+
+    def rel(got, ref):
+        return float((got.double() - ref).norm() / ref.norm())
+    h = dH.double()
+    roundings = 39 + 227
+    dW = h.T @ A.double()
+    assert rel(g["W"], dW) <= 2.0 ** -24 * roundings ** 0.5
+    assert_no_lean(g["W"].double().flatten()[:, None] - dW.flatten()[:, None], "dW")
+    assert rel(g["bW"], h.sum(0)) <= 2.0 ** -24 * roundings ** 0.5
+    t = h @ W.double()
+    ref = (t + t.roll(1, 0) + t.roll(-1, 0)) / 3.0
+    assert rel(dX, ref) <= 2.0 ** -24 * ((d_out + 15) // 16) ** 0.5 + 4 * 2.0 ** -24
+    assert_no_lean(dX.double() - ref, "dH_in")
