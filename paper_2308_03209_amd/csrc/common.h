@@ -111,11 +111,6 @@ __device__ inline void drop4(const DropoutK& d, uint64_t first, float* x) {
   x[2] = w.z >= d.thr ? x[2] * d.scale : 0.f;
   x[3] = w.w >= d.thr ? x[3] * d.scale : 0.f;
 }
-__device__ inline float drop1(const DropoutK& d, uint64_t e, float x) {
-  const u32x4 w = draw4(d.seed, d.stream, e >> 2, d.epoch);
-  const uint32_t word = (e & 2) ? ((e & 1) ? w.w : w.z) : ((e & 1) ? w.y : w.x);
-  return word >= d.thr ? x * d.scale : 0.f;
-}
 
 // ---- graph views ------------------------------------------------------------------------
 // One CSR on the device with its per-node normalisation vectors.

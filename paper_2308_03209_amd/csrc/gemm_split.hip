@@ -38,8 +38,13 @@
 // conflicts by the counter.
 //
 // Non-finite values: an infinity (or a magnitude that rounds to one in bfloat16) makes x - h, and with it every
-// result it reaches, NaN.  A workgroup that finds a non-finite result computes its tile again with float32 matrix
-// instructions, which treat infinities and NaN as IEEE arithmetic does.
+// result it reaches, NaN.  A wavefront that finds a non-finite result in a 32x32 block computes the block again with
+// float32 matrix instructions, which treat infinities and NaN as IEEE arithmetic does.
+// Small values: bfloat16 ends at 2^-133, so a float32 below 2^-110 is not the sum of three.  What is lost is below 2^-134
+// and does not matter beside larger values; a workgroup that finds a row of an operand all below 2^-95 (in a thread's
+// share of it), and not zero, computes its whole tile again.
+// Both cost time where they happen: 230k x 256 x 602 0.57 ms in turn with others of its kind, with a NaN in one column of
+// B 1.13, with one in every tile of A 1.18 (float32 instructions 0.68 and 0.77).  Looking for small rows costs 1-2 %.
 #include <cstdio>
 
 #include "colsum.h"
@@ -113,6 +118,15 @@ __device__ inline void store_group(unsigned char* d, const float (&x)[8]) {
 // 32-bit offsets.  Rows past the matrix edge repeat its last row (they feed results that are never stored); k past the
 // end of the range are read inside it and become zero on the way to LDS.
 
+// the bits that are set in any of four values
+template <typename V>
+__device__ inline uint32_t any_bit(const V& x) {
+  return __float_as_uint(x[0]) | __float_as_uint(x[1]) | __float_as_uint(x[2]) | __float_as_uint(x[3]);
+}
+// From the bits set in any of them: values that are below 2^-95, all of them, and not all zero (2^-95 has the lowest
+// exponent with one of its three upper bits set).
+__device__ inline bool all_small(uint32_t bits) { return (bits & 0x70000000u) == 0u && (bits & 0x7fffffffu) != 0u; }
+
 // k-contiguous source: thread t holds k-group t%2 of row t/2.  The range has at least eight k: a group that would cross
 // its end is read eight from the end and moved into place (three select stages).
 struct SplitKContig {
@@ -156,6 +170,7 @@ struct SplitKContig {
     store_group(lds + (tid & 1) * PLANE_KG + plane_row(tid >> 1), e);
   }
   __device__ float sum(int, const Raw&) const { return 0.f; }
+  __device__ static uint32_t bits(const Raw& w) { return any_bit(w.x[0]) | any_bit(w.x[1]); }
 };
 
 // k-major source (element (i, k) at P[k ld + i]): thread t holds column t%128 of the eight k of group t/128 (the same for
@@ -200,6 +215,7 @@ struct SplitKMajor {
     for (int c = 0; c < 8; ++c) t += value(k0, c, w);
     return t;
   }
+  __device__ static uint32_t bits(const Raw& w) { return any_bit(w.x) | any_bit(w.x + 4); }
 };
 
 // The accumulators of a wavefront's 2x2 blocks of 32x32: of h h, and of the five smaller products.
@@ -236,7 +252,8 @@ __device__ inline void multiply_step(const unsigned char* as, const unsigned cha
   }
 }
 
-// One k-range of length k_len >= 1.  csum: column sums of operand A (only where the caller wants them).
+// One k-range of length k_len >= 1.  csum: column sums of operand A (only where the caller wants them).  small: set where
+// the thread's share of either operand is all small.
 //
 // LDS holds two steps, one barrier per step: while step t is multiplied, step t+1 is split and written to the other
 // half in between the matrix instructions (a wavefront's vector instructions issue while its matrix instructions
@@ -251,15 +268,18 @@ __device__ inline void multiply_step(const unsigned char* as, const unsigned cha
 constexpr int FLIP_STEPS = 16;
 template <bool FLIP, typename MA, typename MB>
 __device__ inline void run_split(const MA& ma, const MB& mb, int k_len, unsigned char* smem, int a_off, int b_off,
-                                 Sums& acc, int tid, int phase, bool colsum, float& csum) {
+                                 Sums& acc, int tid, int phase, bool colsum, float& csum, bool& small) {
   const int n = (k_len + SBK - 1) / SBK;
   typename MA::Raw ra;
   typename MB::Raw rb;
+  uint32_t bits_a = 0, bits_b = 0;
   auto put_a = [&](int t) {  // the thread's share of step t
+    bits_a |= MA::bits(ra);
     ma.template store<!FLIP>(smem + (t & 1) * 2 * OPERAND, tid, t * SBK, ra, 1.f);
     if (colsum) csum += ma.sum(t * SBK, ra);
   };
   auto put_b = [&](int t) {
+    bits_b |= MB::bits(rb);
     mb.template store<false>(smem + (t & 1) * 2 * OPERAND + OPERAND, tid, t * SBK, rb,
                              FLIP && (t / FLIP_STEPS + phase) % 2 ? -1.f : 1.f);
   };
@@ -301,19 +321,35 @@ __device__ inline void run_split(const MA& ma, const MB& mb, int k_len, unsigned
   const unsigned char* const d = smem + ((n - 1) & 1) * 2 * OPERAND;
   multiply_step(d + a_off, d + OPERAND + b_off, acc, [](int) {});
   if (FLIP && ((n - 1) / FLIP_STEPS + phase) % 2) flip();
+  small |= all_small(bits_a) || all_small(bits_b);
 }
 
-// One 32x32 block of the result over the same range on the float32 matrix instructions, operands straight from
-// memory (tiles with non-finite results).  Element (i, k) of an operand is at P[i si + k sk]; i, j: this lane's row of
-// each, inside the matrix.
-__device__ inline void run_plain(const float* A, int64_t sia, int64_t ska, const float* B, int64_t sib, int64_t skb,
-                                 int64_t i, int64_t j, int64_t k_len, int g, floatx16& acc) {
+// One 32x32 block of the result over the same range on the float32 matrix instructions, operands straight from memory.
+// Element k of the lane's row of an operand is at P[k sk]; half wavefront g takes the g-th eight of 16 k, the next of
+// which are requested while one is multiplied.
+__device__ inline void run_plain(const float* A, int64_t ska, const float* B, int64_t skb, int64_t k_len, int g, floatx16& acc) {
+  struct Eight {
+    float a[8], b[8];
+  } now, next;
+  auto load = [&](int64_t k0, Eight& w) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int64_t k = k0 + 8 * g + s < k_len ? k0 + 8 * g + s : k_len - 1;
+      w.a[s] = A[k * ska];
+      w.b[s] = B[k * skb];
+    }
+  };
+  if (k_len <= 0) return;
+  load(0, now);
 #pragma nounroll
-  for (int64_t k0 = 0; k0 < k_len; k0 += 2) {
-    const bool in = k0 + g < k_len;
-    const int64_t k = in ? k0 + g : k_len - 1;
-    const float a = A[i * sia + k * ska], b = B[j * sib + k * skb];
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? a : 0.f, in ? b : 0.f, acc, 0, 0, 0);
+  for (int64_t k0 = 0; k0 < k_len; k0 += 16) {
+    load(k0 + 16, next);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const bool in = k0 + 8 * g + s < k_len;
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? now.a[s] : 0.f, in ? now.b[s] : 0.f, acc, 0, 0, 0);
+    }
+    now = next;
   }
 }
 
@@ -382,13 +418,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
   }
   const int n_seg = !A_KMAJOR && p.K2 > 0 ? 2 : 1;
   float csum = 0.f;
+  bool small = false;
   if constexpr (A_KMAJOR) {
     if (k_len > 0) {
       SplitKMajor ma;
       SplitKMajor mb;
       ma.init(p.A1 + k_beg * p.lda1, p.lda1, p.M, i0, k_len, tid);
       mb.init(Bw + k_beg * ldbw, ldbw, extent_b, jw, k_len, tid);
-      run_split<true>(ma, mb, (int)k_len, smem, a_off, b_off, sums, tid, (int)(z & 1), p.colsum_part != nullptr && j0 == 0, csum);
+      run_split<true>(ma, mb, (int)k_len, smem, a_off, b_off, sums, tid, (int)(z & 1), p.colsum_part != nullptr && j0 == 0, csum,
+                      small);
     }
   } else {
     // one loop body for both segments (two inlined copies would each claim their own accumulators)
@@ -400,11 +438,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
       if constexpr (B_KMAJOR) {
         SplitKMajor mb;
         mb.init(seg ? p.B2 : p.B1, seg ? p.ldb2 : p.ldb1, p.N, j0, k_seg, tid);
-        run_split<false>(ma, mb, k_seg, smem, a_off, b_off, sums, tid, 0, false, csum);
+        run_split<false>(ma, mb, k_seg, smem, a_off, b_off, sums, tid, 0, false, csum, small);
       } else {
         SplitKContig mb;
         mb.init(seg ? p.B2 : p.B1, seg ? p.ldb2 : p.ldb1, p.N, j0, k_seg, tid);
-        run_split<false>(ma, mb, k_seg, smem, a_off, b_off, sums, tid, 0, false, csum);
+        run_split<false>(ma, mb, k_seg, smem, a_off, b_off, sums, tid, 0, false, csum, small);
       }
     }
   }
@@ -415,73 +453,52 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
     for (int n = 0; n < 2; ++n)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[m][n][v] += sums.rest[m][n][v];
-  bool tile_done = false;  // uniform over the block
-  {
+  // blocks that the split does not get right (see above) are computed again
+  int again = __syncthreads_or(small) ? 15 : 0;
+#pragma unroll
+  for (int blk = 0; blk < 4; ++blk) {
     float bad = 0.f;  // stays zero while every result is finite
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int n = 0; n < 2; ++n)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) bad = fmaf(acc[m][n][v], 0.f, bad);
-    if (__syncthreads_or(!(bad == 0.f))) {
+    for (int v = 0; v < 16; ++v) bad = fmaf(acc[blk / 2][blk % 2][v], 0.f, bad);
+    if (__any(!(bad == 0.f))) again |= 1 << blk;
+  }
 #pragma nounroll
-      for (int blk = 0; blk < 4; ++blk) {
-        const int64_t ib = i0 + (wm * 2 + blk / 2) * 32, jb = (wn * 2 + blk % 2) * 32;
-        const int64_t ia = ib + r < p.M ? ib + r : p.M - 1, ja = jw + jb + r < extent_b ? jw + jb + r : extent_b - 1;
-        floatx16 c;
+  for (int blk = 0; again >> blk != 0; ++blk) {
+    if (!(again >> blk & 1)) continue;
+    const int64_t ib = i0 + wm * 64 + blk / 2 * 32 + r, jb = jw + wn * 64 + blk % 2 * 32 + r;
+    const int64_t ia = ib < p.M ? ib : p.M - 1, ja = jb < extent_b ? jb : extent_b - 1;
+    floatx16 c;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) c[v] = 0.f;
-        if constexpr (A_KMAJOR) {
-          run_plain(p.A1 + k_beg * p.lda1, 1, p.lda1, Bw + k_beg * ldbw, 1, ldbw, ia, ja, k_len, g, c);
-        } else {
+    for (int v = 0; v < 16; ++v) c[v] = 0.f;
+    if constexpr (A_KMAJOR) {
+      run_plain(p.A1 + k_beg * p.lda1 + ia, p.lda1, Bw + k_beg * ldbw + ja, ldbw, k_len, g, c);
+    } else {
 #pragma nounroll
-          for (int seg = 0; seg < n_seg; ++seg) {
-            const int64_t ldb = seg ? p.ldb2 : p.ldb1;
-            run_plain(seg ? p.A2 : p.A1, seg ? p.lda2 : p.lda1, 1, seg ? p.B2 : p.B1, B_KMAJOR ? 1 : ldb,
-                      B_KMAJOR ? ldb : 1, ia, ja, seg ? p.K2 : p.K1, g, c);
-          }
-        }
-        const int64_t j = j0 + jb + r;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int64_t i = ib + 8 * (v >> 2) + 4 * g + (v & 3);
-          if (i >= p.M || j >= p.N) continue;
-          float* dst = p.C + z * p.c_split_stride + i * p.ldc + j;
-          float y = c[v];
-          if constexpr (!A_KMAJOR) {
-            if (p.bias) y += p.bias[j];
-            if (p.relu) y = fmaxf(y, 0.f);
-            if (p.row_scale) y *= p.row_scale[i];
-            const bool shut = p.gate && !(p.gate[i * p.ldg + j] > 0.f);
-            if (!p.gate_last) y = shut ? 0.f : y * p.gate_scale;
-            if (p.accumulate) y += *dst;
-            if (p.gate_last) y = shut ? 0.f : y * p.gate_scale;
-            if (p.relu_last) y = fmaxf(y, 0.f);
-            if constexpr (DROP) y = drop1(p.drop, (uint64_t)i * (uint32_t)p.N + (uint32_t)j, y);
-          }
-          *dst = y;
-        }
+      for (int seg = 0; seg < n_seg; ++seg) {
+        const int64_t ldb = seg ? p.ldb2 : p.ldb1;
+        run_plain((seg ? p.A2 : p.A1) + ia * (seg ? p.lda2 : p.lda1), 1, (seg ? p.B2 : p.B1) + ja * (B_KMAJOR ? 1 : ldb),
+                  B_KMAJOR ? ldb : 1, seg ? p.K2 : p.K1, g, c);
       }
-      if (!A_KMAJOR) return;
-      tile_done = true;
+#pragma unroll
+      for (int v = 1; v < 16; v += 2) c[v] = -c[v];  // odd rows with the other sign, as the split leaves them
     }
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      if (b == blk) acc[b / 2][b % 2] = c;
   }
 
   // accumulator register v of lane (g, r) is element [8 (v/4) + 4 g + v%4][r] of its 32x32 block
   if constexpr (A_KMAJOR) {
     float* Cz = p.C + z * p.c_split_stride;
-    if (!tile_done) {
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
+    for (int m = 0; m < 2; ++m) {
 #pragma unroll
-        for (int n = 0; n < 2; ++n) {
-          const int64_t j = j0 + wn * 64 + n * 32 + r;
+      for (int n = 0; n < 2; ++n) {
+        const int64_t j = j0 + wn * 64 + n * 32 + r;
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int64_t i = i0 + wm * 64 + m * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-            if (j < p.N && i < p.M) Cz[i * p.ldc + j] = acc[m][n][v];
-          }
+        for (int v = 0; v < 16; ++v) {
+          const int64_t i = i0 + wm * 64 + m * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
+          if (j < p.N && i < p.M) Cz[i * p.ldc + j] = acc[m][n][v];
         }
       }
     }

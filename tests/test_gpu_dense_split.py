@@ -113,6 +113,48 @@ def test_product_errors_do_not_lean(env, M, N, K):
     assert_no_lean(C.double() - A.double() @ W.double().T, "product")
 
 
+@pytest.mark.parametrize("row,col", [(-118, 100), (-130, 110), (100, -118), (-118, 0), (-94, 90), (-112, -20)])
+def test_small_operands(env, row, col):
+    """Rows and columns of magnitudes at which three bfloat16 do not hold a float32 (below 2^-110), beside ordinary ones."""
+    B, torch = env["B"], env["torch"]
+    print(f"[case] split product of 2^{row} by 2^{col}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    A, W = (torch.randn(*s, generator=gen, device="cuda") for s in ((300, 41), (200, 41)))
+    A[::3], W[::5] = torch.ldexp(A[::3], torch.tensor(row)), torch.ldexp(W[::5], torch.tensor(col))
+    A[5], W[7] = 0.0, 0.0
+    C = torch.full((300, 200), float("nan"), device="cuda")
+    B.dense_nt_f32(A, W, None, C, False)
+    ref, mag = A.double() @ W.double().T, A.double().abs() @ W.double().abs().T
+    # float32 itself has steps of 2^-149
+    assert bool(((C.double() - ref).abs() <= (41 + 4.0) * 2.0 ** -24 * mag + 41 * 2.0 ** -149).all())
+
+
+def test_small_gradients(env):
+    """The same in weight and input gradients: columns and rows of dH."""
+    B, torch = env["B"], env["torch"]
+    n, d_in, d_out = 5_000, 70, 140
+    print("[case] split gradients of small values", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    A, dH, W = (torch.randn(*s, generator=gen, device="cuda") for s in ((n, d_in), (n, d_out), (d_out, d_in)))
+    dH[:, ::3], dH[17::40] = torch.ldexp(dH[:, ::3], torch.tensor(-118)), torch.ldexp(dH[17::40], torch.tensor(-118))
+    d = B.layer_desc(B.GCN, d_in, 0, d_out)
+    ws = torch.empty(B.layer_workspace_bytes(d, n, True), dtype=torch.uint8, device="cuda")
+    g = {"W": torch.full_like(W, float("nan")), "bW": torch.full((d_out,), float("nan"), device="cuda")}
+    dX = torch.full((n, d_in), float("nan"), device="cuda")
+    src = np.arange(0, n, 2, dtype=np.int64)  # pairs: Ahat is the mean of a node and its partner
+    P = B.build_partition(n, src, src + 1, 1, 0, 3)
+    B.layer_bwd(P, None, 0, d, A, dH, {"W": W, "bW": torch.zeros(d_out, device="cuda")}, {"A": A}, dH, dX, g, False, ws)
+    h = dH.double()
+    assert bool(((g["W"].double() - h.T @ A.double()).abs() <= (n + 4.0) * 2.0 ** -24 * (h.abs().T @ A.double().abs())
+                 + n * 2.0 ** -149).all())
+    assert bool(((g["W"].double() - h.T @ A.double()).norm(dim=1) <= 2.0 ** -20 * (h.T @ A.double()).norm(dim=1)).all())
+
+    def pairs(t):
+        return (t + t.view(-1, 2, t.shape[1]).flip(1).reshape(t.shape)) / 2.0
+    ref, mag = pairs(h @ W.double()), pairs(h.abs() @ W.double().abs())
+    assert bool(((dX.double() - ref).abs() <= (d_out + 8.0) * 2.0 ** -24 * mag + d_out * 2.0 ** -149).all())
+
+
 @pytest.mark.parametrize("nonzero", [1.0, 0.1])
 def test_one_rounding_per_step(env, nonzero):
     """The sum of a product is rounded once per 16 k, by a random part of at most half a unit: relative to the result
