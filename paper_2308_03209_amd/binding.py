@@ -358,13 +358,13 @@ def layer_bwd(part: Partition, masks: Optional[Masks], mask_id: int, desc: Layer
 
 def layers_fwd(part: Partition, masks: Optional[Masks], mask_id: int, calls, workspace) -> None:
     """calls: a ctypes array of LayerCall, one per layer."""
-    _check(lib.cofree_layers_fwd(part.handle, _mh(masks), mask_id, calls, len(calls), workspace.data_ptr(),
+    _check(lib.cofree_layers_fwd(part.handle, _mh(masks), mask_id, calls, len(calls), _ptr(workspace),
                                  workspace.nbytes, _stream()))
 
 
 def layers_bwd(part: Partition, masks: Optional[Masks], mask_id: int, calls, accumulate: bool, workspace) -> None:
     _check(lib.cofree_layers_bwd(part.handle, _mh(masks), mask_id, calls, len(calls), 1 if accumulate else 0,
-                                 workspace.data_ptr(), workspace.nbytes, _stream()))
+                                 _ptr(workspace), workspace.nbytes, _stream()))
 
 
 def loss_workspace_bytes() -> int:

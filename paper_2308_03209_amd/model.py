@@ -46,6 +46,7 @@ class Model:
                 n_pad = (n + 63) // 64 * 64          # keep every tensor 256-byte aligned
                 sl[name] = (total, n, layer[name])
                 total += n_pad
+                self.total = sl[name][0] + n         # elements that a flat buffer has to have
             self.slices.append(sl)
         self.theta = torch.zeros(total, dtype=torch.float32, device=device)
         self.grad = torch.zeros(total, dtype=torch.float32, device=device)
@@ -57,6 +58,12 @@ class Model:
 
     def _views(self, flat) -> List[Dict[str, torch.Tensor]]:
         return [{k: flat[o:o + n].view(shape) for k, (o, n, shape) in sl.items()} for sl in self.slices]
+
+    def flat_ptr(self, flat: torch.Tensor) -> int:
+        """Address of `theta` or `grad`, which a program may have put in its place: it has to hold every tensor."""
+        if flat.numel() < self.total:
+            raise ValueError(f"flat buffer of {flat.numel()} elements for {self.total}")
+        return B._ptr(flat)
 
     @property
     def params(self):
@@ -175,17 +182,17 @@ class PartitionRunner:
             self._calls_for = settings
         return self._calls
 
-    def _fill(self, c: B.LayerCall, l: int, epoch: int) -> None:
+    def _fill(self, c: B.LayerCall, l: int, epoch: int, theta: int) -> None:
         """Addresses of layer l's buffers and parameters, taken anew for every call."""
         c.desc.epoch = epoch
-        c.H_in, c.H_out = self.H[l].data_ptr(), self.H[l + 1].data_ptr()
+        c.H_in, c.H_out = B._ptr(self.H[l]), B._ptr(self.H[l + 1])
         saved = self.saved[l]
         if "Z" in saved:
-            c.saved.Z = saved["Z"].data_ptr()
+            c.saved.Z = B._ptr(saved["Z"])
         if "A" in saved:
-            c.saved.A = saved["A"].data_ptr()
+            c.saved.A = B._ptr(saved["A"])
         W, bW, U, bU = self.model.offsets[l]
-        theta, p = self.model.theta.data_ptr(), c.params
+        p = c.params
         p.W, p.bW = theta + W, theta + bW
         if U is not None:
             p.U, p.bU = theta + U, theta + bU
@@ -193,12 +200,10 @@ class PartitionRunner:
     def forward(self, X: torch.Tensor, mask_id: int = 0, epoch: int = 0) -> torch.Tensor:
         if X.dtype != self.torch_dtype:
             raise ValueError(f"features must be {self.torch_dtype}")
-        if not X.is_contiguous():
-            raise ValueError("tensor must be contiguous")
         self.H[0] = X
-        calls = self._layer_calls()
+        calls, theta = self._layer_calls(), self.model.flat_ptr(self.model.theta)
         for l, c in enumerate(calls):
-            self._fill(c, l, epoch)
+            self._fill(c, l, epoch, theta)
         B.layers_fwd(self.part, self.masks, mask_id, calls, self.workspace)
         return self.H[-1]
 
@@ -209,14 +214,14 @@ class PartitionRunner:
         loss_fn = B.loss_weighted if self.loss_kind == "softmax_ce" else B.loss_bce_weighted
         loss_fn(self.part, weight_kind, custom_w, self.H[-1], labels, train_mask, C, scale_c, self.loss,
                 self.dlogits, self.workspace, self.dtype_code)
-        grad = self.model.grad.data_ptr()
-        d_out = self.dlogits.data_ptr()
+        theta, grad = self.model.flat_ptr(self.model.theta), self.model.flat_ptr(self.model.grad)
+        d_out = B._ptr(self.dlogits)
         calls = self._layer_calls()
         for l in range(len(calls) - 1, -1, -1):
             c = calls[l]
-            self._fill(c, l, epoch)
+            self._fill(c, l, epoch, theta)
             c.dH_out = d_out
-            c.dH_in = d_out = self.dH[l].data_ptr() if l > 0 else None
+            c.dH_in = d_out = B._ptr(self.dH[l])
             W, bW, U, bU = self.model.offsets[l]
             g = c.grads
             g.W, g.bW = grad + W, grad + bW
