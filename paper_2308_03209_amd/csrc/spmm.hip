@@ -115,29 +115,21 @@ struct RowIO<bf16_t> {
 // VEC elements starting at p, of which only the first `avail` exist (avail >= VEC: one wide access)
 template <typename T, int VEC>
 __device__ inline void load_elems(const T* p, int avail, float (&v)[VEC]) {
-  if constexpr (VEC == 1) {
-    v[0] = RowIO<T>::load1(p);
+  if (avail >= VEC) {
+    RowIO<T>::load_wide(p, v);
   } else {
-    if (avail >= VEC) {
-      RowIO<T>::load_wide(p, v);
-    } else {
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) v[i] = i < avail ? RowIO<T>::load1(p + i) : 0.f;
-    }
+    for (int i = 0; i < VEC; ++i) v[i] = i < avail ? RowIO<T>::load1(p + i) : 0.f;
   }
 }
 template <typename T, int VEC>
 __device__ inline void store_elems(T* p, int avail, const float (&v)[VEC]) {
-  if constexpr (VEC == 1) {
-    RowIO<T>::store1(p, v[0]);
+  if (avail >= VEC) {
+    RowIO<T>::store_wide(p, v);
   } else {
-    if (avail >= VEC) {
-      RowIO<T>::store_wide(p, v);
-    } else {
 #pragma unroll
-      for (int i = 0; i < VEC; ++i)
-        if (i < avail) RowIO<T>::store1(p + i, v[i]);
-    }
+    for (int i = 0; i < VEC; ++i)
+      if (i < avail) RowIO<T>::store1(p + i, v[i]);
   }
 }
 
@@ -313,8 +305,8 @@ __device__ inline void finish_row(const AggK<T>& p, int64_t row, int c0, int fir
 // float32 470 -> 350 us.  It is one launch because launches of their own for the long rows cost more than they saved.
 // The lines (32 and 128 neighbours, common.h) are flat: 16 to 64 and 64 to 512 measured within 4 % on every workload,
 // the smaller workgroup line ahead on 20k nodes (14 -> 11 us a launch).  At most 64 registers in float32 and 72 in
-// bfloat16 are what the occupancy of the gather needs: 73 and 76 cost 3-8 % of every large launch, and bfloat16 in 64
-// goes to scratch memory (30 % slower).
+// bfloat16 (64 where a row takes a whole wavefront's lanes) are what the occupancy of the gather needs: 73, 76 and 66 cost
+// 3-8 % of every large launch; fewer in bfloat16 go to scratch memory (30 % slower).
 template <int LANES>
 __device__ inline int team_read_i(int x, int base, int j) {
   if constexpr (LANES == 64) return __builtin_amdgcn_readlane(x, j);
@@ -327,10 +319,9 @@ __device__ inline float team_read_f(float x, int base, int j) {
 }
 
 // Adds the neighbours of a row that fall to this wavefront (entries first .. of every `stride`, TL of them at a time).
-template <typename T, int TL, int LPS, int NCH, bool TINY>
+template <typename T, int TL, int LPS, int NCH, int TINY>
 __device__ inline void gather_row(const AggK<T>& p, int64_t beg, int64_t end, int64_t first, int64_t stride, int lane,
-                                  const LaneCols (&lc)[NCH], const int (&cread)[NCH],
-                                  float (&acc)[NCH][RowIO<T>::WIDE]) {
+                                  const int (&cread)[NCH], float (&acc)[NCH][RowIO<T>::WIDE]) {
   constexpr int VEC = RowIO<T>::WIDE, NG = TL / LPS;
   constexpr int UNR = 4;
   const int32_t* __restrict__ col = p.col;
@@ -361,11 +352,13 @@ __device__ inline void gather_row(const AggK<T>& p, int64_t beg, int64_t end, in
       if constexpr (TINY) {
         float v[UNR][VEC];
 #pragma unroll
-        for (int t = 0; t < UNR; ++t) load_elems<T, VEC>(X + (int64_t)u[t] * p.ldx, p.width, v[t]);
+        for (int t = 0; t < UNR; ++t)
+#pragma unroll
+          for (int i = 0; i < TINY; ++i) v[t][i] = RowIO<T>::load1(X + (int64_t)u[t] * p.ldx + i);
 #pragma unroll
         for (int t = 0; t < UNR; ++t)
 #pragma unroll
-          for (int i = 0; i < VEC; ++i) acc[0][i] = ok[t] ? fmaf(s[t], v[t][i], acc[0][i]) : acc[0][i];
+          for (int i = 0; i < TINY; ++i) acc[0][i] = ok[t] ? fmaf(s[t], v[t][i], acc[0][i]) : acc[0][i];
       } else {
         typename RowIO<T>::Raw v[UNR][NCH];
 #pragma unroll
@@ -390,10 +383,81 @@ __device__ inline void gather_row(const AggK<T>& p, int64_t beg, int64_t end, in
   }
 }
 
-// TINY: rows narrower than one 16-byte access (element accesses; LPS = 1).
+// The same for a whole wavefront of at least eight neighbour groups (narrow rows), `wave` of `waves` that share the row: the
+// groups read their neighbours' ids themselves, which are consecutive.  Ids handed out 64 at a time leave most loads of so
+// many groups without a neighbour.  Rows of less than one access have an instance for every width: element loads under a
+// condition on the width wait for each other (bfloat16, 230k nodes, 14M entries: 3 columns 302 -> 108 us, 8 columns 183 -> 136;
+// 30k nodes, 14M entries: 3 columns 162 -> 44, 8 columns 95 -> 50).
+template <typename T, int LPS, int TINY>
+__device__ inline void gather_narrow(const AggK<T>& p, int64_t beg, int64_t end, int wave, int waves, int lane, int cread,
+                                     float (&acc)[RowIO<T>::WIDE]) {
+  constexpr int VEC = RowIO<T>::WIDE, NG = 64 / LPS;
+  constexpr int UNR = 4;
+  const int32_t* __restrict__ col = p.col;
+  const float* __restrict__ in_scale = p.in_scale;
+  const float* __restrict__ in_vals = p.in_vals;
+  const T* __restrict__ X = p.X + (TINY ? 0 : cread);
+  const int64_t last = end - 1, e0 = beg + wave * (NG * UNR) + lane / LPS, step = (int64_t)waves * (NG * UNR);
+  // scale_mode: 0 no per-source factor, 1 gathered from the per-node vector, 2 per entry
+  auto gather = [&](auto scale_mode) {
+    constexpr int MODE = decltype(scale_mode)::value;
+    for (int64_t e = e0; e < end; e += step) {
+      int u[UNR];
+      float s[UNR];
+      if constexpr (TINY) {
+        // 64 neighbours a slot: the element loads of slots that no lane has are passed over
+        float v[UNR][TINY];
+#pragma unroll
+        for (int t = 0; t < UNR; ++t) u[t] = e + t * NG < end ? col[e + t * NG] : -1;
+#pragma unroll
+        for (int t = 0; t < UNR; ++t) {
+          s[t] = 1.f;
+#pragma unroll
+          for (int i = 0; i < TINY; ++i) v[t][i] = 0.f;
+          if (u[t] >= 0) {
+            if constexpr (MODE == 2) s[t] = in_vals[e + t * NG];
+            if constexpr (MODE == 1) s[t] = in_scale[u[t]];
+#pragma unroll
+            for (int i = 0; i < TINY; ++i) v[t][i] = RowIO<T>::load1(X + (int64_t)u[t] * p.ldx + i);
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < UNR; ++t)
+#pragma unroll
+          for (int i = 0; i < TINY; ++i) acc[i] = fmaf(s[t], v[t][i], acc[i]);
+      } else {
+        typename RowIO<T>::Raw v[UNR];
+#pragma unroll
+        for (int t = 0; t < UNR; ++t) {
+          const int64_t ec = e + t * NG < last ? e + t * NG : last;  // past the end: the last one, left out (see RowIO)
+          u[t] = col[ec];
+          if constexpr (MODE == 2) s[t] = in_vals[ec];
+        }
+#pragma unroll
+        for (int t = 0; t < UNR; ++t) {
+          if constexpr (MODE == 1) s[t] = in_scale[u[t]];
+          if constexpr (MODE == 0) s[t] = 1.f;
+          v[t] = RowIO<T>::load_raw(X + (int64_t)u[t] * p.ldx);
+        }
+#pragma unroll
+        for (int t = 0; t < UNR; ++t) RowIO<T>::fma_raw(acc, s[t], RowIO<T>::keep_if(e + t * NG < end, v[t]));
+      }
+    }
+  };
+  if (in_vals) gather(std::integral_constant<int, 2>{});
+  else if (in_scale) gather(std::integral_constant<int, 1>{});
+  else gather(std::integral_constant<int, 0>{});
+#pragma unroll
+  for (int off = LPS; off < 64; off <<= 1) {
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
+  }
+}
+
+// TINY: the columns of rows narrower than one 16-byte access (element accesses; LPS = 1), else 0.
 // Rows need only element alignment (see LaneCols for the ragged end of a row).
-template <typename T, int TL, int LPS, int NCH, bool TINY, bool DROP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4 : (sizeof(T) == 4 ? 8 : 7)))) void aggregate_kernel(const AggK<T> p) {
+template <typename T, int TL, int LPS, int NCH, int TINY, bool DROP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4 : (sizeof(T) == 4 || TL == 64 ? 8 : 7)))) void aggregate_kernel(const AggK<T> p) {
   constexpr int VEC = RowIO<T>::WIDE;
   constexpr int RPW = 64 / TL;  // short rows per wavefront
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -431,14 +495,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[c][i] = 0.f;
   }
-  RowTail<T, VEC, TINY> tail[NCH];
+  RowTail<T, VEC, TINY != 0> tail[NCH];
 #pragma unroll
   for (int c = 0; c < NCH; ++c) tail[c].request(p, row, s, cread[c]);
 
-  if (team == 0) {
-    gather_row<T, TL, LPS, NCH, TINY>(p, beg, end, 0, TL, lane, lc, cread, acc);
+  if (TL < 64 && team == 0) {
+    gather_row<T, TL, LPS, NCH, TINY>(p, beg, end, 0, TL, lane, cread, acc);
   } else {
-    gather_row<T, 64, LPS, NCH, TINY>(p, beg, end, team == 2 ? wave * 64 : 0, team == 2 ? 256 : 64, lane, lc, cread, acc);
+    if constexpr (LPS <= 8) gather_narrow<T, LPS, TINY>(p, beg, end, team == 2 ? wave : 0, team == 2 ? 4 : 1, lane, cread[0], acc[0]);
+    else gather_row<T, 64, LPS, NCH, TINY>(p, beg, end, team == 2 ? wave * 64 : 0, team == 2 ? 256 : 64, lane, cread, acc);
     if (team == 2) {
       __shared__ float partial[3][NCH * LPS * VEC];
       if (wave > 0 && lane < LPS) {
@@ -460,7 +525,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4
   if ((lane % (team == 0 ? TL : 64)) >= LPS) return;  // the first neighbour group of the team writes
 #pragma unroll
   for (int c = 0; c < NCH; ++c)
-    if (lc[c].avail > 0) finish_row<T, VEC, TINY, DROP>(p, row, lc[c].c0, lc[c].first, lc[c].avail, acc[c], tail[c]);
+    if (lc[c].avail > 0) finish_row<T, VEC, TINY != 0, DROP>(p, row, lc[c].c0, lc[c].first, lc[c].avail, acc[c], tail[c]);
 }
 
 // ---- XCD-affine column slices ---------------------------------------------------------------------
@@ -626,6 +691,15 @@ struct LaunchCost {
 // four to a wavefront, where the columns leave that many lanes: with more rows, narrow rows measured slower (8 rows
 // of 6 pieces: 0.50 ms, 4 rows 0.41 ms on 1.9M rows of 47 bfloat16); lanes that the columns leave free fetch further
 // neighbours of the row.
+template <typename T, int WIDTH = RowIO<T>::WIDE - 1>
+static void launch_tiny(const AggK<T>& k, dim3 grid, hipStream_t stream) {
+  if (k.width == WIDTH) {
+    aggregate_kernel<T, 16, 1, 1, WIDTH, false><<<grid, 256, 0, stream>>>(k);
+  } else {
+    if constexpr (WIDTH > 1) launch_tiny<T, WIDTH - 1>(k, grid, stream);
+  }
+}
+
 constexpr int ROW_PIECES = 128;  // wider rows take several launches
 template <typename T, bool DROP>
 static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
@@ -641,19 +715,19 @@ static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCos
   const int64_t blocks = k.n_block + (k.n_wave + 3) / 4 + (short_rows + per_block - 1) / per_block;
   COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
   char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_kernel<%s,%d,%d,%d,%s,%s> width=%d", type_name<T>(), tl, lps, nch,
-           tiny ? "true" : "false", DROP ? "true" : "false", (int)cost.a.width);
+  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_kernel<%s,%d,%d,%d,%d,%s> width=%d", type_name<T>(), tl, lps, nch,
+           tiny ? (int)k.width : 0, DROP ? "true" : "false", (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   const dim3 grid((unsigned)blocks);
-  if (tiny) aggregate_kernel<T, 16, 1, 1, true, false><<<grid, 256, 0, stream>>>(k);
-  else if (lps == 1) aggregate_kernel<T, 16, 1, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
-  else if (lps == 2) aggregate_kernel<T, 16, 2, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
-  else if (lps == 4) aggregate_kernel<T, 16, 4, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
-  else if (lps == 8) aggregate_kernel<T, 16, 8, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
-  else if (lps == 16) aggregate_kernel<T, 16, 16, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
-  else if (lps == 32) aggregate_kernel<T, 32, 32, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
-  else if (nch == 1) aggregate_kernel<T, 64, 64, 1, false, DROP><<<grid, 256, 0, stream>>>(k);
-  else aggregate_kernel<T, 64, 64, 2, false, DROP><<<grid, 256, 0, stream>>>(k);
+  if (tiny) launch_tiny<T>(k, grid, stream);
+  else if (lps == 1) aggregate_kernel<T, 16, 1, 1, 0, DROP><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 2) aggregate_kernel<T, 16, 2, 1, 0, DROP><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 4) aggregate_kernel<T, 16, 4, 1, 0, DROP><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 8) aggregate_kernel<T, 16, 8, 1, 0, DROP><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 16) aggregate_kernel<T, 16, 16, 1, 0, DROP><<<grid, 256, 0, stream>>>(k);
+  else if (lps == 32) aggregate_kernel<T, 32, 32, 1, 0, DROP><<<grid, 256, 0, stream>>>(k);
+  else if (nch == 1) aggregate_kernel<T, 64, 64, 1, 0, DROP><<<grid, 256, 0, stream>>>(k);
+  else aggregate_kernel<T, 64, 64, 2, 0, DROP><<<grid, 256, 0, stream>>>(k);
   return COFREE_OK;
 }
 
@@ -796,7 +870,13 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   k.order = a.g.order;
   k.slot0 = n_hub;
   k.n = a.g.n - n_hub;
-  k.n_block = buckets ? a.g.n_block - n_hub : 0;
+  // Graphs of high average degree leave their long rows to a wavefront each where the rows are narrow, so that four
+  // wavefronts would find too little to share (115k nodes, 7M entries, 8 bfloat16 columns 1.10 -> 0.99 of the time with a
+  // wavefront for every row), and where most rows are long, so that the chip is full without (30k nodes, 14M entries, 300
+  // float32 columns 1.09 -> 1.00).  Elsewhere the shared rows are what a launch waits for (60k nodes, 2M entries, 128
+  // bfloat16 columns 0.61 of that time, 0.81 without).
+  const bool share = !waves || (a.width > 8 * WIDE && 2 * a.g.n_block <= a.g.n);
+  k.n_block = buckets && share ? a.g.n_block - n_hub : 0;
   k.n_wave = waves ? k.n - k.n_block : (buckets ? a.g.n_wave - a.g.n_block : 0);
   // The row kernel walks the processing-order copy of the graph (1.9M-node partition, 512-wide float32: 3.00 ms
   // by row id, 2.8 ms in natural order with its worse balance).  COFREE_AGG_SLOTS = 0 reads by row id.

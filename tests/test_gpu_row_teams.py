@@ -25,10 +25,21 @@ def env():
 
 
 # columns per 16-byte piece: 4 in float32, 8 in bfloat16; lane layouts change at 1, 2, 4, ... 64 and 128 pieces
-@pytest.mark.parametrize("dtype,width", [("f32", w) for w in (1, 4, 7, 13, 31, 41, 100, 255, 300, 514)] +
-                         [("bf16", w) for w in (3, 8, 15, 30, 47, 128, 172, 500, 1000)])
+@pytest.mark.parametrize("dtype,width", [("f32", w) for w in (1, 2, 3, 4, 7, 13, 31, 41, 100, 255, 300, 514)] +
+                         [("bf16", w) for w in (1, 2, 3, 4, 5, 6, 7, 8, 15, 30, 47, 128, 172, 500, 1000)])
 @pytest.mark.parametrize("masked", [False, True])
 def test_rows_at_the_team_limits(env, dtype, width, masked):
+    check(env, dtype, width, masked)
+
+
+@pytest.mark.parametrize("dtype,width", [("f32", w) for w in (2, 8, 31, 41, 300)] + [("bf16", w) for w in (5, 8, 64, 128, 500)])
+def test_a_wavefront_for_every_row(env, dtype, width, monkeypatch):
+    """As in graphs of high average degree, where narrow rows are not shared by a workgroup's wavefronts."""
+    monkeypatch.setenv("COFREE_AGG_SLICES", "1")
+    check(env, dtype, width, False)
+
+
+def check(env, dtype, width, masked):
     B, torch, P, O = env["B"], env["torch"], env["P"], env["O"]
     print(f"[case] row teams dtype={dtype} width={width} masked={masked}", flush=True)
     g = o_dropedge.full_graph(O)
