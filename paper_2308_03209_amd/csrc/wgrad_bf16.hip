@@ -242,13 +242,34 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
 }
 
 static int32_t pieces_of(int32_t N) { return (N + 7) / 8; }
-static int32_t tile_rows(int32_t N1) { return N1 <= 64 ? 64 : (N1 <= 128 ? 128 : 256); }
-static int32_t tile_cols(int32_t columns) { return columns <= 128 ? 128 : 256; }
+
+// Tile of the result (rows x columns, and how many).  The larger it is the less is read, but a workgroup per CU then means
+// more and shorter chunks, each with a ramp, a barrier per step that no other workgroup hides and a partial result of its
+// own (256 x 256 over 20k nodes: 256 chunks of 78 nodes and 64 MB of partials).  So small graphs take 128 x 128, as long as
+// the operands are not read too often for it, and results of up to 256 x 256 over middling ones 128 x 256.  Measured in
+// us of the layer's two launches, 128 x 128 / 128 x 256 / 256 x 256 (and 128 x 128 of four wavefronts, gemm_bf16.hip):
+// 256 x 256 over 20k nodes 19 / 21 / 30 (21), 100k 30 / 33 / 41 (36), 400k 92 / 92 / 109 (102), 800k 182 / 163 / 175 (186),
+// 1.6M 353 / 316 / 307 (375); 512 x 300 over 20k 30 / 28 / 31 (38), 50k 54 / 44 / 44 (57), 100k 94 / 74 / 69 (89).
+struct WgradTile {
+  int32_t h, w, m, n;
+};
+static WgradTile wgrad_tile(int32_t N1, int32_t N2, int32_t N2b, int64_t M) {
+  const int32_t rows = 8 * pieces_of(N1), columns = 8 * (pieces_of(N2) + pieces_of(N2b));
+  const int32_t small = ((rows + 127) / 128) * ((columns + 127) / 128);  // tiles of 128 x 128
+  const bool narrow = M < (1 << 17) && (small <= 10 || M < (1 << 15)), middling = small <= 4 && M < (1 << 20);
+  WgradTile t;
+  t.h = rows <= 64 ? 64 : (rows <= 128 || narrow || middling ? 128 : 256);
+  t.w = columns <= 128 || narrow ? 128 : 256;
+  t.m = (rows + t.h - 1) / t.h;
+  t.n = (columns + t.w - 1) / t.w;
+  return t;
+}
 
 // Chunks of nodes: a whole number of rounds of a workgroup per CU, enough of them for walks of at most about 16k nodes
 // (over longer ones the tiles of a chunk drift apart and each fetches its rows from memory), chunks of at least 64.
+// A chunk's tiles are on one XCD, which has 32 CUs: three tiles and 85 chunks were 33 workgroups on some.
 static int32_t wgrad_chunks(int32_t tiles, int64_t M) {
-  const int64_t per_round = std::max(1, WG_CUS / tiles);
+  const int64_t per_round = tiles <= WG_CUS / 8 ? 8 * (WG_CUS / 8 / tiles) : std::max(1, WG_CUS / tiles);
   const int64_t walks = std::min<int64_t>((M + 16383) / 16384, 2048);
   int64_t s = per_round * std::max<int64_t>(1, (walks + per_round - 1) / per_round);
   s = std::min<int64_t>(s, (M + 63) / 64);
@@ -257,17 +278,9 @@ static int32_t wgrad_chunks(int32_t tiles, int64_t M) {
 
 bool wgrad_bf16_fits(int32_t N1, int32_t N2, int32_t N2b) { return N1 >= 8 && N2 >= 8 && (N2b == 0 || N2b >= 8); }
 
-static int32_t wgrad_tiles(int32_t N1, int32_t N2, int32_t N2b, int32_t* tm, int32_t* tn) {
-  const int32_t columns = 8 * (pieces_of(N2) + pieces_of(N2b));
-  const int32_t rows = 8 * pieces_of(N1), h = tile_rows(rows), w = tile_cols(columns);
-  *tm = (rows + h - 1) / h;
-  *tn = (columns + w - 1) / w;
-  return *tm * *tn;
-}
-
 size_t wgrad_bf16_workspace_floats(int32_t N1, int32_t N2, int32_t N2b, int64_t M) {
-  int32_t tm, tn;
-  return (size_t)wgrad_chunks(wgrad_tiles(N1, N2, N2b, &tm, &tn), M) * ((size_t)N1 * ((size_t)N2 + N2b) + (size_t)N1);
+  const WgradTile t = wgrad_tile(N1, N2, N2b, M);
+  return (size_t)wgrad_chunks(t.m * t.n, M) * ((size_t)N1 * ((size_t)N2 + N2b) + (size_t)N1);
 }
 
 int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
@@ -283,7 +296,10 @@ int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t 
   p.N2b = a.B2 ? a.N2b : 0;
   p.M = a.M;
   const int32_t N2 = p.N2 + p.N2b;
-  const int32_t S = wgrad_chunks(wgrad_tiles(p.N1, p.N2, p.N2b, &p.tiles_m, &p.tiles_n), a.M);
+  const WgradTile tile = wgrad_tile(p.N1, p.N2, p.N2b, a.M);
+  p.tiles_m = tile.m;
+  p.tiles_n = tile.n;
+  const int32_t S = wgrad_chunks(tile.m * tile.n, a.M);
   p.n_chunks = S;
   p.chunk = std::max<int64_t>(1, (((a.M + S - 1) / S) + 31) / 32 * 32);
   p.C = a.workspace;
@@ -292,7 +308,7 @@ int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t 
   COFREE_TRY(plan_colsum(a, &p.extra, sums));
   const int64_t blocks = ((p.n_chunks + 7) / 8) * 8 * p.tiles_m * p.tiles_n + (p.extra.blocks + 1) / 2;
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31) && p.chunk < ((int64_t)1 << 31), "wgrad: grid too large");
-  const int32_t th = tile_rows(8 * pieces_of(p.N1)), tw = tile_cols(8 * (pieces_of(p.N2) + pieces_of(p.N2b)));
+  const int32_t th = tile.h, tw = tile.w;
   {
     char pname[96] = "";
     const char* rest = tw == 256 ? (th == 256 ? "32,3,2,4" : (th == 128 ? "32,4,2,4" : "64,2,1,8"))

@@ -72,3 +72,30 @@ def test_sums_of_another_matrix(env, n, d_in, d_out):
     t = (h + h.roll(1, 0) + h.roll(-1, 0)) / 3.0  # rounded to bfloat16 before the product: 2^-9 of every element
     ref, mag = t.T @ H.double(), t.abs().T @ H.double().abs()
     assert bool(((g["W"].double() - ref).abs() <= (2.0 ** -8 + n * 2.0 ** -24) * mag).all())
+
+
+# nodes and widths that reach each tile of the kernel with more steps than its ring of loads holds twice, ragged at the end
+@pytest.mark.parametrize("n,d_in,d_out,tile", [(100_002, 200, 200, "128x128"), (300_002, 100, 40, "64x128"), (300_002, 256, 256, "128x256"),
+                                               (300_002, 256, 40, "64x256"), (140_002, 100, 600, "256x128"),
+                                               (140_002, 300, 512, "256x256"), (1_100_002, 256, 256, "256x256"),
+                                               (20_002, 602, 256, "128x128"), (140_002, 602, 256, "256x256")])
+def test_exact_sums(env, n, d_in, d_out, tile):
+    """Small whole numbers, whose sums are exact in float32: a row left out or taken twice shows.  Nodes in pairs, so that
+    the aggregated gradient of a transform-first layer, the mean of two even numbers, is whole too."""
+    B, torch = env["B"], env["torch"]
+    print(f"[case] bfloat16 weight gradient, exact sums n={n} {d_in} -> {d_out} ({tile})", flush=True)
+    assert 12 * n < 2 ** 24 and n % 2 == 0
+    gen = torch.Generator(device="cuda").manual_seed(n + d_in)
+    A = torch.randint(-3, 4, (n, d_in), generator=gen, device="cuda").bfloat16()
+    dH = (2 * torch.randint(-2, 3, (n, d_out), generator=gen, device="cuda")).bfloat16()
+    src = np.arange(0, n, 2, dtype=np.int64)
+    P = B.build_partition(n, src, src + 1, 1, 0, 3)
+    W = torch.zeros(d_out, d_in, device="cuda")
+    d = B.layer_desc(B.GCN, d_in, 0, d_out, dtype=B.BF16)
+    ws = torch.empty(B.layer_workspace_bytes(d, n, True), dtype=torch.uint8, device="cuda")
+    g = {"W": torch.full_like(W, float("nan")), "bW": torch.full((d_out,), float("nan"), device="cuda")}
+    B.layer_bwd(P, None, 0, d, A, dH, {"W": W, "bW": torch.zeros(d_out, device="cuda")}, {"A": A}, dH, None, g, False, ws)
+    h = dH.double()
+    t = h if d_in <= d_out else (h + h.view(-1, 2, d_out).flip(1).reshape(n, d_out)) / 2
+    assert torch.equal(g["W"].double(), t.T @ A.double())
+    assert torch.equal(g["bW"].double(), h.sum(0))
