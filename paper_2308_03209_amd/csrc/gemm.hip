@@ -648,6 +648,7 @@ int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
                  "dense: ldb too small");
   if (a.M == 0) return COFREE_OK;
   if (gemm_split_fits(a)) return launch_gemm_split(a, stream);
+  if (a.dropout.q > 0.f) return fail(COFREE_EINVAL, "internal: no dropout in narrow products");
   GemmK p{};
   p.A1 = (const float*)a.A1;
   p.lda1 = a.lda1;

@@ -643,6 +643,7 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
   else
     COFREE_REQUIRE(a.b_kmajor ? a.ldb >= a.N : a.ldb >= K, "dense: ldb too small");
   if (gemm_resident_fits(a)) return launch_gemm_resident(a, stream);
+  if (a.dropout.q > 0.f) return fail(COFREE_EINVAL, "internal: no dropout in tiled products");
   const int64_t ldd = pad8(K);
   bf16_t* Wb = (bf16_t*)a.param_scratch;
   {

@@ -28,18 +28,43 @@ static int column_parts(int32_t N, int nch) {
   return 0;
 }
 
-// COFREE_BF16_TILE sends every product to the tiled kernel.
-// At most 512 k, segments of at least eight, and parameters of at most four column parts.
-bool gemm_resident_fits(const GemmArgs& a) {
+// Rows from which the resident kernel is the faster one.  Every workgroup first converts its parameters, row by row the
+// slower (A B^T), while the tiled kernel (gemm_bf16.hip) has 128 or 256 columns in a tile, empty or not.  us of a launch
+// and the aggregation beside it, tiled / resident: A B^T of 256 x 256 (columns x k) over 20k rows 23 / 36, 100k 57 / 69, 200k 127 / 123,
+// 800k 452 / 431; 128 x 128 20k 15 / 17, 100k 34 / 34, 200k 54 / 51; 128 x 400 200k 88 / 90, 400k 195 / 183; 172 x 256 20k 28 / 31,
+// 50k 46 / 42, 200k 137 / 101; 47 x 256 2k 16 / 12, 100k 45 / 40; 512 k everywhere slower: 512 x 512 200k 281 / 284, 1.6M
+// 2012 / 2074.  A B (with the launches of the weight gradient): 128 x 128 20k 35 / 32, 100k 56 / 50; 172 x 256 20k 54 / 52, 100k
+// 105 / 93; 256 x 256 20k 54 / 58, 100k 106 / 104, 200k 229 / 203; 256 x 172 100k 99 / 103, 200k 190 / 180; 512 x 512 20k 74 / 80, 100k
+// 231 / 225; 130 x 129, where a quarter of the k is padding, 100k 110 / 116, 200k 184 / 176.  Dropout would be a pass of its own
+// beside the tiled kernel (100k x 128: 15 us).
+static int64_t resident_min_rows(int32_t N, int32_t K, int nch, bool kmajor, bool drop) {
+  const int param = (N + 31) / 32 * nch;  // of 32 columns x 64 k
+  const bool tiles_empty = N <= 64 || 4 * (int64_t)((N + 127) / 128 * 128) >= 5 * (int64_t)N;
+  if (kmajor) return param <= 8 || (tiles_empty && 4 * 64 * nch <= 5 * K) ? 0 : 1 << 17;
+  if (drop) return param <= 8 ? 0 : 1 << 15;
+  if (nch >= 8) return INT64_MAX;
+  if (tiles_empty) return N <= 64 ? 0 : 1 << 15;
+  return param <= 24 ? 1 << 17 : 1 << 18;
+}
+
+// At most 512 k, segments of at least eight, parameters of at most four column parts, and rows as above.
+// COFREE_BF16_TILE = 0 takes every product that fits, = 128 or 256 none.
+static bool resident_fits(const GemmArgs& a, bool drop) {
   const int nch = pieces(a.K1) + (a.K2 > 0 ? pieces(a.K2) : 0);
   const int64_t strides = a.lda1 | a.lda2 | a.ldc | a.ldg;  // 32-bit offsets inside a tile of 32 rows
-  return !getenv("COFREE_BF16_TILE") && a.N >= 32 && a.M >= 32 && strides < ((int64_t)1 << 26) && a.K1 >= 8 && (a.K2 == 0 || a.K2 >= 8) && nch <= 8 &&
+  int64_t rows = resident_min_rows(a.N, a.K1 + a.K2, nch, a.b_kmajor != 0, drop);
+  if (const char* e = getenv("COFREE_BF16_TILE")) {
+    if (atoi(e) != 0) return false;
+    rows = 0;
+  }
+  return a.N >= 32 && a.M >= 32 && a.M >= rows && strides < ((int64_t)1 << 26) && a.K1 >= 8 && (a.K2 == 0 || a.K2 >= 8) && nch <= 8 &&
          column_parts(a.N, nch) > 0;
 }
+bool gemm_resident_fits(const GemmArgs& a) { return resident_fits(a, a.dropout.q > 0.f); }
 
 // Dropout needs a lane's eight columns to start at a whole draw in every part, and a product that only writes.
 bool gemm_resident_drops(const GemmArgs& a) {
-  if (!gemm_resident_fits(a) || a.gate || a.accumulate) return false;
+  if (!resident_fits(a, true) || a.gate || a.accumulate) return false;
   return a.N % (4 * column_parts(a.N, pieces(a.K1) + (a.K2 > 0 ? pieces(a.K2) : 0))) == 0;
 }
 

@@ -8,6 +8,12 @@ from test_gpu_bf16 import G, check_single_layer_bf16  # noqa: F401  (G is the fi
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(autouse=True)
+def resident(monkeypatch):
+    """Also for as few rows as these, where the tiled kernel would be taken."""
+    monkeypatch.setenv("COFREE_BF16_TILE", "0")
+
+
 # forward N = d_out (or d_msg), K = d_in; backward N = d_in; sums of two segments K = d_out + d_msg (sage), 2 d_out
 @pytest.mark.parametrize("kind,dims", [("gcn", (8, 8, 32)), ("gcn", (33, 8, 65)), ("gcn", (64, 8, 96)), ("gcn", (128, 8, 129)),
                                        ("gcn", (172, 8, 256)), ("gcn", (256, 8, 224)), ("gcn", (500, 8, 64)),

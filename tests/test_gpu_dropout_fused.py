@@ -21,10 +21,13 @@ SHAPES = [("sage_conv", 72, 132),   # aggregate first: split / resident product,
           ("sage", 100, 260), ("sage", 64, 36)]
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dtype,products", [("f32", None), ("bf16", "0"), ("bf16", None)])
 @pytest.mark.parametrize("kind,d_in,d_out", SHAPES)
-def test_against_keep_decisions(G, kind, d_in, d_out, dtype):  # noqa: F811
+def test_against_keep_decisions(G, kind, d_in, d_out, dtype, products, monkeypatch):  # noqa: F811
+    """products: resident ones wherever they fit ("0"), or as many rows as here take (mostly tiled ones)."""
     B, torch = G["B"], G["torch"]
+    if products is not None:
+        monkeypatch.setenv("COFREE_BF16_TILE", products)
     print(f"[case] fused dropout {kind} {d_in} -> {d_out} {dtype}", flush=True)
     n, q = 5003, 0.3
     rng = np.random.default_rng(1)
