@@ -363,7 +363,7 @@ int32_t launch_split_sums(SplitSums sums, hipStream_t stream);
 
 // Weight gradient C[N1, N2 + N2b] = A^T [B | B2] with A [M, N1], B [M, N2], B2 [M, N2b] of `dtype`, C float32: reduction
 // over the long dimension M in fixed-order split chunks, whose partials go to `workspace`
-// (wgrad_workspace_floats(N1, N2 + N2b, M)) and are added to the sums.
+// (wgrad_workspace_floats(N1, N2, M, N2b)) and are added to the sums.
 struct WgradArgs {
   int32_t dtype = COFREE_F32;
   int64_t M = 0;
@@ -373,7 +373,8 @@ struct WgradArgs {
   const void* B = nullptr;
   int64_t ldb = 0;
   int32_t N2 = 0;
-  // optional second matrix (N2 must be a multiple of 128): two weight gradients that share A read it once
+  // optional second matrix (N2 must be a multiple of 128, or in bfloat16 wgrad_bf16_fits(N1, N2, N2b)): two weight
+  // gradients that share A read it once
   const void* B2 = nullptr;
   int64_t ldb2 = 0;
   int32_t N2b = 0;

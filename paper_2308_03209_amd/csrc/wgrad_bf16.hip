@@ -1,8 +1,9 @@
 // Weight gradients of bfloat16 activations, C[N1, N2 + N2b] = A^T [B | B2] over the graph nodes, float32 partials per
 // chunk of nodes.
 //
-// Bound by the bytes of A and B, so the tile of the result is as large as a CU's registers hold - 256 x 256 in eight
-// wavefronts, 128 accumulators each - and every operand row is read once per launch where the result fits a tile.
+// Bound by the bytes of A and B, so on large graphs the tile of the result is as large as a CU's registers hold - 256 x 256
+// in eight wavefronts, 128 accumulators each - and every operand row is read once per launch where the result fits a tile
+// (wgrad_tile has the rule for smaller ones).
 // A workgroup per CU streams its chunk in steps of 32 or 64 nodes: 16-byte pieces of rows go through a ring of registers
 // (80 to 96 KB in flight per CU) into LDS as they lie in memory, [node][column], double-buffered with one barrier per
 // step.  The matrix instructions want eight consecutive nodes of one column per lane: the transposing LDS read
