@@ -875,9 +875,10 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   // wavefront for every row), and where most rows are long, so that the chip is full without (30k nodes, 14M entries, 300
   // float32 columns 1.09 -> 1.00).  Elsewhere the shared rows are what a launch waits for (60k nodes, 2M entries, 128
   // bfloat16 columns 0.61 of that time, 0.81 without).
-  const bool share = !waves || (a.width > 8 * WIDE && 2 * a.g.n_block <= a.g.n);
+  // (A launch has less than 2^32 work-items: eight million long rows do not need a workgroup each either.)
+  const bool share = a.g.n_block < (1 << 23) && (!waves || (a.width > 8 * WIDE && 2 * a.g.n_block <= a.g.n));
   k.n_block = buckets && share ? a.g.n_block - n_hub : 0;
-  k.n_wave = waves ? k.n - k.n_block : (buckets ? a.g.n_wave - a.g.n_block : 0);
+  k.n_wave = waves ? k.n - k.n_block : (buckets ? a.g.n_wave - n_hub - k.n_block : 0);
   // The row kernel walks the processing-order copy of the graph (1.9M-node partition, 512-wide float32: 3.00 ms
   // by row id, 2.8 ms in natural order with its worse balance).  COFREE_AGG_SLOTS = 0 reads by row id.
   bool slots = a.g.order != nullptr && a.g.s_rowptr != nullptr;
