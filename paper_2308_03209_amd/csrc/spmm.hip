@@ -872,11 +872,12 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   k.n = a.g.n - n_hub;
   // Graphs of high average degree leave their long rows to a wavefront each where the rows are narrow, so that four
   // wavefronts would find too little to share (115k nodes, 7M entries, 8 bfloat16 columns 1.10 -> 0.99 of the time with a
-  // wavefront for every row), and where most rows are long, so that the chip is full without (30k nodes, 14M entries, 300
-  // float32 columns 1.09 -> 1.00).  Elsewhere the shared rows are what a launch waits for (60k nodes, 2M entries, 128
-  // bfloat16 columns 0.61 of that time, 0.81 without).
+  // wavefront for every row), and from eight million entries on, where a launch outlasts a row of 4095 neighbours anyway
+  // (230k nodes, 14M entries, 41 float32 columns: shared 437 us, a wavefront each 409; 30k nodes, 14M entries, 300 columns 1.09
+  // -> 1.00).  Elsewhere the shared rows are what a launch waits for (60k nodes, 2M entries, 128 bfloat16 columns 0.61
+  // of that time, 0.81 without; 115k nodes, 7M entries, 41 float32 columns 0.77 and 0.86).
   // (A launch has less than 2^32 work-items: eight million long rows do not need a workgroup each either.)
-  const bool share = a.g.n_block < (1 << 23) && (!waves || (a.width > 8 * WIDE && 2 * a.g.n_block <= a.g.n));
+  const bool share = a.g.n_block < (1 << 23) && (!waves || (a.width > 8 * WIDE && a.g.nnz < (1 << 23)));
   k.n_block = buckets && share ? a.g.n_block - n_hub : 0;
   k.n_wave = waves ? k.n - k.n_block : (buckets ? a.g.n_wave - n_hub - k.n_block : 0);
   // The row kernel walks the processing-order copy of the graph (1.9M-node partition, 512-wide float32: 3.00 ms
