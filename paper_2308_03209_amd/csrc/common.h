@@ -398,6 +398,7 @@ struct ColsumK;
 int32_t plan_colsum(const WgradArgs& a, ColsumK* k, SplitSums* sums);  // extra workgroups of a launch, if any
 // float32 products on the bfloat16 matrix cores (gemm_split.hip): which shapes they take, and their launchers
 bool gemm_split_fits(const GemmArgs& a);
+size_t split_param_bytes(int32_t N, int64_t K1, int64_t K2);  // scratch for the parameters of a product split beforehand
 int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream);
 bool wgrad_split_fits(const WgradArgs& a);
 int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stream);

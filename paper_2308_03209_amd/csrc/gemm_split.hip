@@ -22,14 +22,17 @@
 //
 // What bounds it: a 32x32x16 bfloat16 matrix instruction takes 32 cycles, eight 32x32x2 float32 ones 512, so six of
 // the former could be 2.7 times as fast; but a loop of nothing but matrix instructions on random data already lowers
-// the shader clock from 2.4 to 1.8 GHz (1,860 TFLOP/s in bfloat16): power, not issue slots, is the limit, with LDS at
-// three quarters of its rate behind it.  Measured against the float32 instructions, in TFLOP/s of the product: 470k x
-// 512 x 512 127 -> 169 (A B^T); 529k x 512 x 1024 134 -> 187; 230k x 256 x 602 118 -> 148; 115k x 256 x 512 112 -> 158.
+// the shader clock from 2.4 to 1.7 GHz (1,760 TFLOP/s in bfloat16, 1,500 with the vector instructions of a split in
+// between): power, not issue slots, is the limit.  Here it runs at 1.8 GHz with the matrix units busy 59 % of the time (55 %
+// in weight gradients); the rest is mostly the first steps and the end of a tile.  In TFLOP/s of the product, float32
+// instructions / the steps read from LDS behind each barrier / now: 470k x 512 x 512 127 / 169 / 189 (A B^T), 529k x 512 x 1024
+// 134 / 187 / 200, 230k x 256 x 602 118 / 131 / 152; weight gradients 512 x 512 over 470k nodes - / 165 / 186.
 //
 // Tiling: 128x128 of the result per workgroup, four wavefronts 2x2 of 64x64 each (128 accumulators: two sets of four
 // 32x32 blocks), two workgroups per CU; see run_split for the pipeline.  One set of accumulators leaves room for
-// 128x256 tiles (189 TFLOP/s at 470k x 512 x 512, where two sets give 169); two sets in such tiles measured 163 with
-// one wavefront per SIMD and 168 with eight wavefronts in one workgroup.
+// 128x256 tiles, but rounds more often; two sets in such tiles were no faster with one wavefront per SIMD or with eight
+// wavefronts in one workgroup.  Nor were 512 workgroups that take tiles in turn and request the next one's first step before
+// they write the last (470k x 512 x 512 1285 -> 1400 us).
 //
 // LDS plane of an operand of 128 rows: [k-group of 8][row][8 bfloat16].  A matrix operand - 8 consecutive k of 32
 // consecutive rows per half wavefront - is then 512 contiguous bytes.  Neighbouring rows are swapped in every other
@@ -46,6 +49,7 @@
 // Both cost time where they happen: 230k x 256 x 602 0.57 ms in turn with others of its kind, with a NaN in one column of
 // B 1.13, with one in every tile of A 1.18 (float32 instructions 0.68 and 0.77).  Looking for small rows costs 1-2 %.
 #include <cstdio>
+#include <type_traits>
 
 #include "colsum.h"
 #include "common.h"
@@ -55,6 +59,7 @@ namespace cofree {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int SBK = 16;  // k per step: one matrix instruction deep
 
@@ -84,12 +89,16 @@ struct SplitK {
   int32_t accumulate, relu_last, gate_last;
   float gate_scale;
   DropoutK drop;
+  const unsigned char* planes;  // parameters split beforehand: [column tile][step][STEP_IMAGE]
+  const uint32_t* small_params; // [column tile][step]: they are to be computed again (see below)
 };
 
 constexpr int TILE = 128;                 // rows and columns of a workgroup's result
 constexpr int PLANE_KG = TILE * 16 + 64;  // bytes of a k-group
 constexpr int PLANE = 2 * PLANE_KG;       // bytes of a plane (16 k)
 constexpr int OPERAND = 3 * PLANE;        // the three planes of an operand
+constexpr int STAGE = 2 * OPERAND;        // a step of both operands
+constexpr int STEP_IMAGE = 3 * TILE * 32;  // a step of parameters split beforehand: three planes of [k-group][row][8]
 __device__ inline int plane_row(int row) { return (row ^ ((row >> 3) & 1)) * 16; }
 
 // x0, x1 -> their high, middle and low parts, packed (x0 in the low half of each dword)
@@ -101,76 +110,95 @@ __device__ inline void split_pair(float x0, float x1, uint32_t& h, uint32_t& m, 
   l = pack_bf16x2(s0, s1);
 }
 
-// eight consecutive k of one row, split and written to the three planes at d
-__device__ inline void store_group(unsigned char* d, const float (&x)[8]) {
-  uint4 h, m, l;
-  split_pair(x[0], x[1], h.x, m.x, l.x);
-  split_pair(x[2], x[3], h.y, m.y, l.y);
-  split_pair(x[4], x[5], h.z, m.z, l.z);
-  split_pair(x[6], x[7], h.w, m.w, l.w);
-  *reinterpret_cast<uint4*>(d) = h;
-  *reinterpret_cast<uint4*>(d + PLANE) = m;
-  *reinterpret_cast<uint4*>(d + 2 * PLANE) = l;
-}
+// Eight consecutive k of one row, split: a thread's share of a step on its way to LDS.
+struct Group {
+  uint32x4 h, m, l;
+  __device__ void pair(int q, float x0, float x1) {
+    uint32_t a, b, c;
+    split_pair(x0, x1, a, b, c);
+    h[q] = a, m[q] = b, l[q] = c;
+  }
+  __device__ void write(unsigned char* d, int plane) const {
+    *reinterpret_cast<uint32x4*>(d) = h;
+    *reinterpret_cast<uint32x4*>(d + plane) = m;
+    *reinterpret_cast<uint32x4*>(d + 2 * plane) = l;
+  }
+};
 
 // ---- operand movers: 128 rows x 16 k of an operand from memory to registers to LDS -----------------------------
-// A thread's share is eight consecutive k of one row.  Loads are unconditional vector loads at a block-uniform base plus
-// 32-bit offsets.  Rows past the matrix edge repeat its last row (they feed results that are never stored); k past the
-// end of the range are read inside it and become zero on the way to LDS.
+// A thread's share is eight consecutive k of one row.  Loads are unconditional vector loads at a block-uniform base plus a
+// constant 32-bit offset per thread.  Rows past the matrix edge repeat its last row (they feed results that are never
+// stored).  A range that is not whole steps ends with the window of its last 16 k, of which the ones that the step before
+// had are zero on the way to LDS (ONLY_PART); a range of less than one step is read at clamped k, element by element.
+
+// the k of a step's window that count: lo <= k < hi
+struct Window {
+  int start, lo, hi;
+};
+__device__ inline Window window_of(int t, int k_len) {
+  const int k0 = t * SBK, last = k_len - SBK;
+  if (last < 0) return Window{0, 0, k_len};
+  const int start = k0 < last ? k0 : last;
+  return Window{start, k0 - start, SBK};
+}
 
 // the bits that are set in any of four values
-template <typename V>
-__device__ inline uint32_t any_bit(const V& x) {
-  return __float_as_uint(x[0]) | __float_as_uint(x[1]) | __float_as_uint(x[2]) | __float_as_uint(x[3]);
+__device__ inline uint32_t any_bit(float a, float b, float c, float d) {
+  return __float_as_uint(a) | __float_as_uint(b) | __float_as_uint(c) | __float_as_uint(d);
 }
 // From the bits set in any of them: values that are below 2^-95, all of them, and not all zero (2^-95 has the lowest
 // exponent with one of its three upper bits set).
 __device__ inline bool all_small(uint32_t bits) { return (bits & 0x70000000u) == 0u && (bits & 0x7fffffffu) != 0u; }
 
-// k-contiguous source: thread t holds k-group t%2 of row t/2.  The range has at least eight k: a group that would cross
-// its end is read eight from the end and moved into place (three select stages).
+// k-contiguous source: thread t holds k-group t%2 of row t/2
 struct SplitKContig {
   struct Raw {
     float4u x[2];
   };
-  const float* base;
-  uint32_t off;
+  const char* base;
+  uint32_t off;  // bytes to the thread's group of the first step
   int kq, k_len;
   __device__ void init(const float* P, int64_t ld, int64_t extent, int64_t i0, int64_t k_len_, int tid) {
-    base = P + i0 * ld;
+    base = reinterpret_cast<const char*>(P + i0 * ld);
     kq = (tid & 1) * 8;
     k_len = (int)k_len_;
     const int64_t last = extent - 1 - i0, r = tid >> 1;
-    off = (uint32_t)((r < last ? r : last) * ld);
+    off = (uint32_t)(r < last ? r : last) * (uint32_t)ld * 4u + (k_len < SBK ? 0u : (uint32_t)kq * 4u);
   }
-  __device__ void load(int k0, Raw& w) const {
-    const int k = k0 + kq < k_len - 8 ? k0 + kq : k_len - 8;
-    w.x[0] = *reinterpret_cast<const float4u*>(base + (off + (uint32_t)k));
-    w.x[1] = *reinterpret_cast<const float4u*>(base + (off + (uint32_t)k + 4));
+  __device__ void load(int t, Raw& w) const {
+    const char* const p = base + (int64_t)window_of(t, k_len).start * 4;
+    w.x[0] = *reinterpret_cast<const float4u*>(p + off);
+    w.x[1] = *reinterpret_cast<const float4u*>(p + off + 16u);
   }
-  // ODD: with the other sign in odd rows
-  template <bool ODD>
-  __device__ void store(unsigned char* lds, int tid, int k0, const Raw& w, float) const {
-    const uint32_t flip = ODD ? (uint32_t)tid << 30 & 0x80000000u : 0u;
-    float e[8];
+  __device__ void load_short(Raw& w) const {  // k_len < 16
 #pragma unroll
-    for (int c = 0; c < 8; ++c) e[c] = __uint_as_float(__float_as_uint(w.x[c >> 2][c & 3]) ^ flip);
-    if (k0 + SBK > k_len) {  // uniform: the last step of a ragged range
-      const int sh = k0 + kq - (k_len - 8);  // how far the group was moved; eight and more: nothing of it exists
-      if (sh > 0) {
-#pragma unroll
-        for (int s = 4; s > 0; s >>= 1) {
-#pragma unroll
-          for (int c = 0; c < 8; ++c) e[c] = (sh & s) ? (c + s < 8 ? e[c + s < 8 ? c + s : 7] : 0.f) : e[c];
-        }
-#pragma unroll
-        for (int c = 0; c < 8; ++c) e[c] = sh > 7 ? 0.f : e[c];
-      }
+    for (int c = 0; c < 8; ++c) {
+      const int k = kq + c < k_len ? kq + c : k_len - 1;
+      w.x[c >> 2][c & 3] = *reinterpret_cast<const float*>(base + (off + (uint32_t)k * 4u));
     }
-    store_group(lds + (tid & 1) * PLANE_KG + plane_row(tid >> 1), e);
   }
-  __device__ float sum(int, const Raw&) const { return 0.f; }
-  __device__ static uint32_t bits(const Raw& w) { return any_bit(w.x[0]) | any_bit(w.x[1]); }
+  __device__ float value(const Window& in, int c, const Raw& w) const {
+    return kq + c >= in.lo && kq + c < in.hi ? w.x[c >> 2][c & 3] : 0.f;
+  }
+  // the q-th pair of the share; ODD: with the other sign in odd rows
+  template <bool ODD, bool ONLY_PART>
+  __device__ void pair(int q, int tid, int t, const Raw& w, uint32_t, Group& g) const {
+    const uint32_t flip = ODD ? (uint32_t)tid << 30 & 0x80000000u : 0u;
+    const Window in = window_of(t, k_len);
+    float e[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int c = 2 * q + i;
+      e[i] = __uint_as_float(__float_as_uint(ONLY_PART ? value(in, c, w) : w.x[c >> 2][c & 3]) ^ flip);
+    }
+    g.pair(q, e[0], e[1]);
+  }
+  __device__ static void write(unsigned char* lds, int tid, const Raw&, const Group& g) {
+    g.write(lds + (tid & 1) * PLANE_KG + plane_row(tid >> 1), PLANE);
+  }
+  __device__ static uint32_t bits(const Raw& w) {
+    return any_bit(w.x[0][0], w.x[0][1], w.x[0][2], w.x[0][3]) | any_bit(w.x[1][0], w.x[1][1], w.x[1][2], w.x[1][3]);
+  }
 };
 
 // k-major source (element (i, k) at P[k ld + i]): thread t holds column t%128 of the eight k of group t/128 (the same for
@@ -181,7 +209,7 @@ struct SplitKMajor {
   };
   const float* base;
   int64_t ld;
-  uint32_t off;   // the thread's column
+  uint32_t off;   // bytes to the thread's column
   int kq, k_len;  // kq: first k of the thread's group
   __device__ void init(const float* P, int64_t ld_, int64_t extent, int64_t i0, int64_t k_len_, int tid) {
     base = P;
@@ -189,33 +217,75 @@ struct SplitKMajor {
     kq = __builtin_amdgcn_readfirstlane((tid / TILE) * 8);
     k_len = (int)k_len_;
     const int64_t i = i0 + tid % TILE;
-    off = (uint32_t)(i < extent - 1 ? i : extent - 1);
+    off = (uint32_t)(i < extent - 1 ? i : extent - 1) * 4u;
   }
-  __device__ void load(int k0, Raw& w) const {
+  __device__ void load(int t, Raw& w) const {
+    const float* row = base + (int64_t)(window_of(t, k_len).start + kq) * ld;
+#pragma unroll
+    for (int c = 0; c < 8; ++c, row += ld) w.x[c] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + off);
+  }
+  __device__ void load_short(Raw& w) const {
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-      const int k = k0 + kq + c < k_len ? k0 + kq + c : k_len - 1;
-      const float* const row = base + k * ld;
-      w.x[c] = row[off];
+      const float* const row = base + (int64_t)(kq + c < k_len ? kq + c : k_len - 1) * ld;
+      w.x[c] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + off);
     }
   }
-  __device__ float value(int k0, int c, const Raw& w) const { return k0 + kq + c < k_len ? w.x[c] : 0.f; }
-  // sign: 1 or -1 on every element
-  template <bool>
-  __device__ void store(unsigned char* lds, int tid, int k0, const Raw& w, float sign) const {
-    float e[8];
+  __device__ float value(const Window& in, int c, const Raw& w) const { return kq + c >= in.lo && kq + c < in.hi ? w.x[c] : 0.f; }
+  // sign: 0 or the sign bit, on every element
+  template <bool, bool ONLY_PART>
+  __device__ void pair(int q, int, int t, const Raw& w, uint32_t sign, Group& g) const {
+    const Window in = window_of(t, k_len);
+    float e[2];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) e[c] = sign * value(k0, c, w);
-    store_group(lds + (tid / TILE) * PLANE_KG + plane_row(tid % TILE), e);
+    for (int i = 0; i < 2; ++i) {
+      const int c = 2 * q + i;
+      e[i] = __uint_as_float(__float_as_uint(ONLY_PART ? value(in, c, w) : w.x[c]) ^ sign);
+    }
+    g.pair(q, e[0], e[1]);
+  }
+  __device__ static void write(unsigned char* lds, int tid, const Raw&, const Group& g) {
+    g.write(lds + (tid / TILE) * PLANE_KG + plane_row(tid % TILE), PLANE);
   }
   // sum of the thread's eight k (weight gradients: column sums of operand A)
-  __device__ float sum(int k0, const Raw& w) const {
-    float t = 0.f;
+  template <bool ONLY_PART>
+  __device__ float sum(int t, const Raw& w) const {
+    const Window in = window_of(t, k_len);
+    float s = 0.f;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) t += value(k0, c, w);
-    return t;
+    for (int c = 0; c < 8; ++c) s += ONLY_PART ? value(in, c, w) : w.x[c];
+    return s;
   }
-  __device__ static uint32_t bits(const Raw& w) { return any_bit(w.x) | any_bit(w.x + 4); }
+  __device__ static uint32_t bits(const Raw& w) {
+    return any_bit(w.x[0], w.x[1], w.x[2], w.x[3]) | any_bit(w.x[4], w.x[5], w.x[6], w.x[7]);
+  }
+};
+
+// Parameters that split_params_kernel has split: the three planes of a step, 16 bytes (eight k of a row) after another
+struct SplitPlanes {
+  struct Raw {
+    uint32x4 x[3];
+  };
+  const unsigned char* base;  // the column tile's first step
+  uint32_t off;
+  __device__ void init(const unsigned char* P, int tid) {
+    base = P;
+    off = (uint32_t)tid * 16u;
+  }
+  __device__ void load(int t, Raw& w) const {
+    const unsigned char* const p = base + (int64_t)t * STEP_IMAGE;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) w.x[q] = *reinterpret_cast<const uint32x4*>(p + q * (STEP_IMAGE / 3) + off);
+  }
+  __device__ void load_short(Raw& w) const { load(0, w); }
+  template <bool, bool>
+  __device__ void pair(int, int, int, const Raw&, uint32_t, Group&) const {}
+  __device__ static void write(unsigned char* lds, int tid, const Raw& w, const Group&) {
+    unsigned char* const d = lds + (tid / TILE) * PLANE_KG + plane_row(tid % TILE);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<uint32x4*>(d + q * PLANE) = w.x[q];
+  }
+  __device__ static uint32_t bits(const Raw&) { return 0u; }
 };
 
 // The accumulators of a wavefront's 2x2 blocks of 32x32: of h h, and of the five smaller products.
@@ -223,41 +293,53 @@ struct Sums {
   floatx16 hh[2][2], rest[2][2];
 };
 
-// 16 k of a wavefront's blocks: 24 matrix instructions.  Operand A stays in registers, B streams; between(o) is called in
-// front of the o-th block column.
-template <typename F>
-__device__ inline void multiply_step(const unsigned char* as, const unsigned char* bs, Sums& acc, F between) {
+// A wavefront's operands of a step: planes h, m, l of two row blocks of A and two column blocks of B.
+struct Operands {
   bf16x8 a[3][2], b[2][3];
-#pragma unroll
-  for (int p = 0; p < 3; ++p) {
+  __device__ void read_a(const unsigned char* as, int p) {
 #pragma unroll
     for (int m = 0; m < 2; ++m) a[p][m] = *reinterpret_cast<const bf16x8*>(as + p * PLANE + m * 512);
-    b[0][p] = *reinterpret_cast<const bf16x8*>(bs + p * PLANE);
   }
+  __device__ void read_b(const unsigned char* bs, int o) {
 #pragma unroll
-  for (int o = 0; o < 2; ++o) {
-    if (o == 0) {
+    for (int p = 0; p < 3; ++p) b[o][p] = *reinterpret_cast<const bf16x8*>(bs + p * PLANE + o * 512);
+  }
+};
+
+// 16 k of a wavefront's blocks: 24 matrix instructions, in twelve slots of two with work(slot) in front of each.  Nothing
+// moves from one slot to another: left alone, the compiler gathers the LDS reads in front of the barrier.  The operands that
+// the first slots need (planes m and l of A, the first column block of B) were read during the step before, and here those
+// of the step after (NEXT, at as_next and bs_next) as soon as their registers are free: read behind the barrier, they had
+// the matrix units wait for LDS in every step (half of the time, by the counters).
+constexpr int SLOTS = 12;
+template <bool NEXT, typename F>
+__device__ inline void multiply_step(const unsigned char* as, const unsigned char* bs, const unsigned char* as_next,
+                                     const unsigned char* bs_next, Operands& x, Sums& acc, F work) {
+  constexpr int PA[6] = {2, 1, 1, 0, 0, 0}, PB[6] = {0, 1, 0, 2, 1, 0};
 #pragma unroll
-      for (int p = 0; p < 3; ++p) b[1][p] = *reinterpret_cast<const bf16x8*>(bs + p * PLANE + 512);
+  for (int s = 0; s < SLOTS; ++s) {
+    const int o = s / 6, pa = PA[s % 6], pb = PB[s % 6];
+    if (s == 0) x.read_a(as, 0);
+    if (s == 1) x.read_b(bs, 1);
+    if (NEXT && s == 6) x.read_b(bs_next, 0);
+    if (NEXT && s == 7) x.read_a(as_next, 2);
+    if (NEXT && s == 9) x.read_a(as_next, 1);
+    work(s);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      floatx16& c = pa + pb > 0 ? acc.rest[m][o] : acc.hh[m][o];
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.a[pa][m], x.b[o][pb], c, 0, 0, 0);
     }
-    between(o);
-    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};  // smallest products first
-#pragma unroll
-    for (int q = 0; q < 6; ++q)
-#pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        floatx16& c = q < 5 ? acc.rest[m][o] : acc.hh[m][o];
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]][m], b[o][PB[q]], c, 0, 0, 0);
-      }
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
 // One k-range of length k_len >= 1.  csum: column sums of operand A (only where the caller wants them).  small: set where
 // the thread's share of either operand is all small.
 //
-// LDS holds two steps, one barrier per step: while step t is multiplied, step t+1 is split and written to the other
-// half in between the matrix instructions (a wavefront's vector instructions issue while its matrix instructions
-// run), and step t+2 is requested from memory into the registers that this frees.
+// LDS holds three steps, one barrier per step: while step t is multiplied, step t+2 is split and written in between the
+// matrix instructions (a wavefront's vector instructions issue while its matrix instructions run), step t+3 is requested
+// from memory into the registers that this frees, and the operands of step t+1 are read.
 //
 // The matrix instructions cut off (towards minus infinity) what of a small product lies far below the running sum.  In
 // one result that is little, but it does not average out where results are added up: over neighbours, over all nodes in
@@ -272,28 +354,31 @@ __device__ inline void run_split(const MA& ma, const MB& mb, int k_len, unsigned
   const int n = (k_len + SBK - 1) / SBK;
   typename MA::Raw ra;
   typename MB::Raw rb;
+  Group ga, gb;
   uint32_t bits_a = 0, bits_b = 0;
-  auto put_a = [&](int t) {  // the thread's share of step t
+  // the thread's share of step t: four pairs, then (q = 4) on to LDS
+  auto put_a = [&](int q, int t, unsigned char* d, auto part) {
+    if (q < 4) return ma.template pair<!FLIP, decltype(part)::value>(q, tid, t, ra, 0u, ga);
     bits_a |= MA::bits(ra);
-    ma.template store<!FLIP>(smem + (t & 1) * 2 * OPERAND, tid, t * SBK, ra, 1.f);
-    if (colsum) csum += ma.sum(t * SBK, ra);
+    ma.write(d, tid, ra, ga);
   };
-  auto put_b = [&](int t) {
+  auto put_b = [&](int q, int t, unsigned char* d, auto part) {
+    const uint32_t sign = FLIP && (t / FLIP_STEPS + phase) % 2 ? 0x80000000u : 0u;
+    if (q < 4) return mb.template pair<false, decltype(part)::value>(q, tid, t, rb, sign, gb);
     bits_b |= MB::bits(rb);
-    mb.template store<false>(smem + (t & 1) * 2 * OPERAND + OPERAND, tid, t * SBK, rb,
-                             FLIP && (t / FLIP_STEPS + phase) % 2 ? -1.f : 1.f);
+    mb.write(d + OPERAND, tid, rb, gb);
   };
-  ma.load(0, ra);
-  mb.load(0, rb);
-  __syncthreads();  // whoever used the LDS before is done
-  put_a(0);
-  put_b(0);
-  if (n > 1) {
-    ma.load(SBK, ra);
-    mb.load(SBK, rb);
-  }
-  __syncthreads();
-  auto flip = [&]() {
+  auto put = [&](int t, unsigned char* d, auto part) {
+#pragma unroll
+    for (int q = 0; q < 5; ++q) put_a(q, t, d, part), put_b(q, t, d, part);
+  };
+  auto add_csum = [&](int t, auto part) {
+    if constexpr (FLIP) {
+      if (colsum) csum += ma.template sum<decltype(part)::value>(t, ra);
+    }
+  };
+  auto flip = [&](int t) {
+    if (!FLIP || t == 0 || t % FLIP_STEPS != 0) return;
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
@@ -301,27 +386,122 @@ __device__ inline void run_split(const MA& ma, const MB& mb, int k_len, unsigned
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc.hh[m][q][v] = -acc.hh[m][q][v], acc.rest[m][q][v] = -acc.rest[m][q][v];
   };
+  const std::true_type part{};
+  const std::false_type whole{};
+  typename MA::Raw ra1;
+  typename MB::Raw rb1;
+  if (k_len < SBK) {
+    ma.load_short(ra);
+    mb.load_short(rb);
+    ra1 = ra, rb1 = rb;
+  } else {
+    const int t = n > 1 ? 1 : 0;
+    ma.load(0, ra);
+    mb.load(0, rb);
+    ma.load(t, ra1);
+    mb.load(t, rb1);
+  }
+  __syncthreads();  // whoever used the LDS before is done
+  unsigned char *d0 = smem, *d1 = smem + STAGE, *d2 = smem + 2 * STAGE;  // steps t, t + 1, t + 2
+  add_csum(0, part);
+  put(0, d0, part);
+  if (n > 1) {
+    ra = ra1, rb = rb1;
+    add_csum(1, part);
+    put(1, d1, part);
+  }
+  if (n > 2) {
+    ma.load(2, ra);
+    mb.load(2, rb);
+  }
+  __syncthreads();
+  Operands x;
+  x.read_a(d0 + a_off, 2);
+  x.read_a(d0 + a_off, 1);
+  x.read_b(d0 + OPERAND + b_off, 0);
+  int t = 0;
 #pragma nounroll
-  for (int t = 0; t + 1 < n; ++t) {
-    if (FLIP && t > 0 && t % FLIP_STEPS == 0) flip();
-    const unsigned char* const d = smem + (t & 1) * 2 * OPERAND;
-    multiply_step(d + a_off, d + OPERAND + b_off, acc, [&](int o) {
-      if (o == 0) {
-        put_a(t + 1);
-      } else {
-        put_b(t + 1);
-        const int t2 = t + 2 < n ? t + 2 : n - 1;
-        ma.load(t2 * SBK, ra);
-        mb.load(t2 * SBK, rb);
-      }
+  for (; t + 3 < n; ++t) {
+    add_csum(t + 2, whole);
+    flip(t);
+    multiply_step<true>(d0 + a_off, d0 + OPERAND + b_off, d1 + a_off, d1 + OPERAND + b_off, x, acc, [&](int s) {
+      if (s >= 1 && s < 6) put_a(s - 1, t + 2, d2, whole);
+      if (s == 5) ma.load(t + 3, ra);
+      if (s >= 6 && s < 11) put_b(s - 6, t + 2, d2, whole);
+      if (s == 10) mb.load(t + 3, rb);
     });
     __syncthreads();
+    unsigned char* const d = d0;
+    d0 = d1;
+    d1 = d2;
+    d2 = d;
   }
-  if (FLIP && n > 1 && (n - 1) % FLIP_STEPS == 0) flip();
-  const unsigned char* const d = smem + ((n - 1) & 1) * 2 * OPERAND;
-  multiply_step(d + a_off, d + OPERAND + b_off, acc, [](int) {});
-  if (FLIP && ((n - 1) / FLIP_STEPS + phase) % 2) flip();
+  if (n > 2) {  // the last step to be written
+    add_csum(t + 2, part);
+    flip(t);
+    multiply_step<true>(d0 + a_off, d0 + OPERAND + b_off, d1 + a_off, d1 + OPERAND + b_off, x, acc, [&](int s) {
+      if (s >= 1 && s < 6) put_a(s - 1, t + 2, d2, part);
+      if (s >= 6 && s < 11) put_b(s - 6, t + 2, d2, part);
+    });
+    __syncthreads();
+    unsigned char* const d = d0;
+    d0 = d1;
+    d1 = d2;
+    d2 = d;
+    ++t;
+  }
+  if (n > 1) {
+    flip(t);
+    multiply_step<true>(d0 + a_off, d0 + OPERAND + b_off, d1 + a_off, d1 + OPERAND + b_off, x, acc, [](int) {});
+    d0 = d1;
+    ++t;
+  }
+  flip(t);
+  multiply_step<false>(d0 + a_off, d0 + OPERAND + b_off, d0, d0, x, acc, [](int) {});
+  if (FLIP && ((n - 1) / FLIP_STEPS + phase) % 2) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc.hh[m][q][v] = -acc.hh[m][q][v], acc.rest[m][q][v] = -acc.rest[m][q][v];
+  }
   small |= all_small(bits_a) || all_small(bits_b);
+}
+
+// The float32 parameters of a product, split for SplitPlanes: a workgroup writes the image of one step of one column tile
+// and says in flags whether a row's eight k are all small (see above).
+struct SplitParamsK {
+  const float* B[2];
+  int64_t ldb[2];
+  int32_t k_len[2], steps[2];
+  int32_t N, k_major;
+  unsigned char* image;
+  uint32_t* flags;
+};
+__global__ __launch_bounds__(256) void split_params_kernel(const SplitParamsK p) {
+  const int tid = threadIdx.x, steps = p.steps[0] + p.steps[1];
+  const int tile = (int)blockIdx.x / steps, step = (int)blockIdx.x % steps;
+  const int seg = step >= p.steps[0], t = step - (seg ? p.steps[0] : 0);
+  // k-contiguous sources: neighbouring threads read the two halves of a row
+  const int kg = p.k_major ? tid / TILE : tid & 1, row = p.k_major ? tid % TILE : tid >> 1;
+  const Window in = window_of(t, p.k_len[seg]);
+  const int64_t j = (int64_t)tile * TILE + row, ldb = p.ldb[seg];
+  const float* const B = p.B[seg];
+  float e[8];
+  uint32_t bits = 0;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const int kw = kg * 8 + c, k = in.start + kw;
+    e[c] = j < p.N && kw >= in.lo && kw < in.hi ? (p.k_major ? B[k * ldb + j] : B[j * ldb + k]) : 0.f;
+    bits |= __float_as_uint(e[c]);
+  }
+  Group g;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) g.pair(q, e[2 * q], e[2 * q + 1]);
+  g.write(p.image + (int64_t)blockIdx.x * STEP_IMAGE + (kg * TILE + row) * 16, STEP_IMAGE / 3);
+  const int any = __syncthreads_or(all_small(bits));
+  if (tid == 0) p.flags[blockIdx.x] = any ? 1u : 0u;
 }
 
 // One 32x32 block of the result over the same range on the float32 matrix instructions, operands straight from memory.
@@ -357,12 +537,12 @@ __device__ inline void run_plain(const float* A, int64_t ska, const float* B, in
 // DROP: dropout of the result, in rows of a multiple of four contiguous columns (529k x 512 with K = 1024: a pass of its own
 // took 353 us, a training step with three of them is 760 us shorter without).  Its generator runs beside the matrix
 // instructions of the CU's other workgroup, where a pass of its own reads and writes the result once more.
-template <bool A_KMAJOR, bool B_KMAJOR, bool DROP>
+template <bool A_KMAJOR, bool B_KMAJOR, bool PLANES, bool DROP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(
     const SplitK p) {
   constexpr int STAGE_LD = 68, STAGE_WAVE = 32 * STAGE_LD;  // result staging: floats
-  __shared__ __attribute__((aligned(128))) unsigned char smem[4 * OPERAND];
-  static_assert(4 * OPERAND >= 4 * STAGE_WAVE * 4, "results are staged where the operands were");
+  __shared__ __attribute__((aligned(128))) unsigned char smem[3 * STAGE];
+  static_assert(3 * STAGE >= 4 * STAGE_WAVE * 4, "results are staged where the operands were");
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -435,7 +615,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
       const int k_seg = (int)(seg ? p.K2 : p.K1);
       SplitKContig ma;
       ma.init(seg ? p.A2 : p.A1, seg ? p.lda2 : p.lda1, p.M, i0, k_seg, tid);
-      if constexpr (B_KMAJOR) {
+      if constexpr (PLANES) {
+        const int steps1 = (int)((p.K1 + SBK - 1) / SBK), steps = steps1 + (int)((p.K2 + SBK - 1) / SBK);
+        const int64_t first = (j0 / TILE) * steps + (seg ? steps1 : 0);
+        SplitPlanes mb;
+        mb.init(p.planes + first * STEP_IMAGE, tid);
+        const int n = (k_seg + SBK - 1) / SBK;
+        uint32_t again = p.small_params[first + (tid < n ? tid : 0)];
+        for (int t = tid + 256; t < n; t += 256) again |= p.small_params[first + t];
+        run_split<false>(ma, mb, k_seg, smem, a_off, b_off, sums, tid, 0, false, csum, small);
+        small |= again != 0u;
+      } else if constexpr (B_KMAJOR) {
         SplitKMajor mb;
         mb.init(seg ? p.B2 : p.B1, seg ? p.ldb2 : p.ldb1, p.N, j0, k_seg, tid);
         run_split<false>(ma, mb, k_seg, smem, a_off, b_off, sums, tid, 0, false, csum, small);
@@ -528,6 +718,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
       float4u g, c;
       float rs;
     };
+    if constexpr (!DROP) {
+      if (!extras && !p.relu_last && i0 + TILE <= p.M) {
+        // Nothing but bias and ReLU: a register of a block is two rows of a whole line of 128 bytes and is stored as it lies
+        // (470k x 512 x 512 1330 -> 1281 us, 60k x 256 x 256 58 -> 53; with gates or row factors, element by element like
+        // this, products took up to 11 % longer than through LDS).
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          const int64_t j = j0 + wn * 64 + n * 32 + r;
+          if (j < p.N) {
+            const float bj = p.bias ? p.bias[j] : 0.f;
+            float* const dst = p.C + (i0 + wm * 64 + 4 * g) * p.ldc + j;
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+              for (int v = 0; v < 16; ++v) {
+                float x = (v & 1 ? -acc[m][n][v] : acc[m][n][v]) + bj;  // odd rows were summed with the other sign
+                if (p.relu) x = fmaxf(x, 0.f);
+                dst[(int64_t)(m * 32 + 8 * (v >> 2) + (v & 3)) * p.ldc] = x;
+              }
+          }
+        }
+        return;
+      }
+    }
     auto request = [&](int m, int s, Extra& e) {
       int64_t il = i0 + wm * 64 + m * 32 + s * RPP + er;
       if (il > p.M - 1) il = p.M - 1;
@@ -631,6 +845,19 @@ bool gemm_split_fits(const GemmArgs& a) {
          (a.K2 == 0 || split_strides_ok(a.lda2, a.B2 ? a.ldb2 : 0));
 }
 
+size_t split_param_bytes(int32_t N, int64_t K1, int64_t K2) {
+  if (N <= 64) return 0;
+  const size_t images = (size_t)((N + TILE - 1) / TILE) * (size_t)((K1 + SBK - 1) / SBK + (K2 + SBK - 1) / SBK);
+  return images * (STEP_IMAGE + 4);
+}
+
+// Whether the parameters are split by a launch of their own, of 6 us, where every workgroup would split them again: from
+// 20 billion operand pairs on (230k x 256 x 256: 231 -> 225 us and the launch; 230k x 256 x 602 496 -> 467, 470k x 512 x 512
+// 1374 -> 1330, gated 1465 -> 1359; 60k x 256 x 256 59.7 -> 58.1).
+static bool split_params_first(const GemmArgs& a) {
+  return a.param_scratch != nullptr && (double)a.M * a.N * ((double)a.K1 + a.K2) >= 2e10;
+}
+
 int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   SplitK p{};
   p.A1 = (const float*)a.A1;
@@ -663,15 +890,34 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   const int64_t blocks = ((p.n_groups + 7) / 8) * 8 * p.tiles_n;
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "dense: grid too large");
   const bool drop = p.drop.scale != 0.f;  // forward products only
+  const bool planes = split_params_first(a);
+  if (planes) {
+    SplitParamsK q{};
+    q.B[0] = p.B1, q.B[1] = p.B2;
+    q.ldb[0] = p.ldb1, q.ldb[1] = p.ldb2;
+    q.k_len[0] = a.K1, q.k_len[1] = a.K2;
+    q.steps[0] = (a.K1 + SBK - 1) / SBK, q.steps[1] = (a.K2 + SBK - 1) / SBK;
+    q.N = a.N, q.k_major = a.b_kmajor;
+    const int steps = q.steps[0] + q.steps[1];
+    q.image = (unsigned char*)a.param_scratch;
+    q.flags = (uint32_t*)(q.image + (size_t)p.tiles_n * steps * STEP_IMAGE);
+    ProfScope prof("split_params_kernel", stream, 10.0 * (double)a.N * K, 0.0);
+    split_params_kernel<<<dim3((unsigned)(p.tiles_n * steps)), 256, 0, stream>>>(q);
+    p.planes = q.image;
+    p.small_params = q.flags;
+  }
   char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<false,%s,%s> N=%d K=%d", a.b_kmajor ? "true" : "false",
-           drop && !a.b_kmajor ? "true" : "false", (int)a.N, (int)K);
+  if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<false,%s,%s,%s> N=%d K=%d", a.b_kmajor ? "true" : "false",
+           planes ? "true" : "false", drop && !a.b_kmajor ? "true" : "false", (int)a.N, (int)K);
   ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + (double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1)),
                  2.0 * (double)a.M * a.N * (double)K);
   const dim3 grid((unsigned)blocks);
-  if (a.b_kmajor) gemm_split_kernel<false, true, false><<<grid, 256, 0, stream>>>(p);
-  else if (drop) gemm_split_kernel<false, false, true><<<grid, 256, 0, stream>>>(p);
-  else gemm_split_kernel<false, false, false><<<grid, 256, 0, stream>>>(p);
+  if (planes && a.b_kmajor) gemm_split_kernel<false, true, true, false><<<grid, 256, 0, stream>>>(p);
+  else if (planes && drop) gemm_split_kernel<false, false, true, true><<<grid, 256, 0, stream>>>(p);
+  else if (planes) gemm_split_kernel<false, false, true, false><<<grid, 256, 0, stream>>>(p);
+  else if (a.b_kmajor) gemm_split_kernel<false, true, false, false><<<grid, 256, 0, stream>>>(p);
+  else if (drop) gemm_split_kernel<false, false, false, true><<<grid, 256, 0, stream>>>(p);
+  else gemm_split_kernel<false, false, false, false><<<grid, 256, 0, stream>>>(p);
   COFREE_HIP_CHECK(hipGetLastError());
   return COFREE_OK;
 }
@@ -711,10 +957,10 @@ int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stre
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "wgrad: grid too large");
   {
     char pname[96] = "";
-    if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<true,true,false> N=%dx%d", (int)N1, (int)N2);
+    if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<true,true,false,false> N=%dx%d", (int)N1, (int)N2);
     ProfScope prof(pname, stream, 4.0 * ((double)a.M * N1 * (p.extra.X ? 2 : 1) + (double)a.M * N2 + (double)N1 * N2),
                    2.0 * (double)a.M * N1 * N2);
-    gemm_split_kernel<true, true, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
+    gemm_split_kernel<true, true, false, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
   }
   COFREE_HIP_CHECK(hipGetLastError());
   COFREE_TRY(add_split_sum(sums, a.workspace, p.c_split_stride, S, a.C, a.ldc, N1, N2));

@@ -116,9 +116,16 @@ static bool conv_merged(const cofree_layer_desc& d) {
 static size_t max2(size_t a, size_t b) { return a > b ? a : b; }
 static size_t max3(size_t a, size_t b, size_t c) { return max2(a, max2(b, c)); }
 
-// largest bf16 copy of a parameter matrix any product of the layer needs
+// largest copy of a parameter matrix - in bfloat16, or split into three of them - that any product of the layer needs
 static size_t param_scratch_bytes(const cofree_layer_desc& d) {
-  if (d.dtype != COFREE_BF16) return 0;
+  if (d.dtype != COFREE_BF16) {
+    if (d.kind == COFREE_SAGE_MEAN)
+      return max3(split_param_bytes(d.d_msg, d.d_in, 0), split_param_bytes(d.d_out, d.d_msg, d.d_in),
+                  max2(split_param_bytes(d.d_msg, d.d_out, 0), split_param_bytes(d.d_in, d.d_out, d.d_msg)));
+    if (d.kind == COFREE_SAGE_CONV)
+      return max2(split_param_bytes(d.d_out, d.d_in, d.d_in), split_param_bytes(d.d_in, d.d_out, d.d_out));
+    return max2(split_param_bytes(d.d_out, d.d_in, 0), split_param_bytes(d.d_in, d.d_out, 0));
+  }
   if (d.kind == COFREE_SAGE_MEAN)
     return max3(gemm_param_scratch_bytes(d.d_msg, d.d_in),
                 gemm_param_scratch_bytes(d.d_out, (int64_t)d.d_msg + d.d_in),
@@ -141,7 +148,7 @@ static FwdPlan plan_fwd(const cofree_layer_desc& d, int64_t n, void* ws) {
   FwdPlan p;
   if ((d.kind == COFREE_GCN && gcn_transform_first(d)) || (d.kind == COFREE_SAGE_CONV && conv_transform_first(d)))
     p.T = c.take((size_t)n * d.d_out * elem_size(d.dtype));
-  if (d.dtype == COFREE_BF16) p.params = c.take(param_scratch_bytes(d));
+  p.params = c.take(param_scratch_bytes(d));
   p.bytes = c.used;
   return p;
 }
@@ -176,7 +183,7 @@ static BwdPlan plan_bwd(const cofree_layer_desc& d, int64_t n, void* ws) {
     if (d.kind == COFREE_SAGE_CONV && !conv_merged(d)) p.wg[1] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
     if (d.kind == COFREE_GCN && gcn_transform_first(d)) p.cs = (float*)c.take(4 * colsum_workspace_floats(d.d_out));
   }
-  if (d.dtype == COFREE_BF16) p.params = c.take(param_scratch_bytes(d));
+  p.params = c.take(param_scratch_bytes(d));
   p.bytes = c.used;
   return p;
 }

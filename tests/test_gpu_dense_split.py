@@ -198,3 +198,39 @@ def test_gradients_of_long_chunks(env, n, d_in, d_out):
     ref = (t + t.roll(1, 0) + t.roll(-1, 0)) / 3.0
     assert rel(dX, ref) <= 2.0 ** -24 * ((d_out + 15) // 16) ** 0.5 + 4 * 2.0 ** -24
     assert_no_lean(dX.double() - ref, "dH_in")
+
+
+@pytest.mark.parametrize("special", ["none", "small", "infinite"])
+def test_parameters_split_beforehand(env, special):
+    """Both directions of a square conventional GraphSAGE layer large enough that its parameters are split by a launch of
+    their own: two ranges of 417 k, a ragged column tile and row tile; some rows of parameters at magnitudes that three
+    bfloat16 do not hold, or with an infinity.  On a ring the mean is over two neighbours: one rounding."""
+    B, torch = env["B"], env["torch"]
+    n, d = 60_001, 417
+    print(f"[case] parameters split beforehand, {special}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(17)
+    H, dH, W = (torch.randn(*s, generator=gen, device="cuda") for s in ((n, d), (n, d), (d, 2 * d)))
+    if special == "small":
+        W[::3], W[:, 5::7] = torch.ldexp(W[::3], torch.tensor(-118)), torch.ldexp(W[:, 5::7], torch.tensor(-118))
+    if special == "infinite":
+        H, dH = H.abs() + 0.1, dH.abs() + 0.1  # no sum of opposite infinities
+        W[400, 416] = float("inf")
+    b = torch.randn(d, generator=gen, device="cuda")
+    P, desc = ring(env, n), B.layer_desc(B.SAGE_CONV, d, 0, d)
+    ws = torch.empty(max(B.layer_workspace_bytes(desc, n, x) for x in (False, True)), dtype=torch.uint8, device="cuda")
+    prm, sv = {"W": W, "bW": b}, {"A": torch.empty(n, d, device="cuda")}
+    Y, dX, g = torch.full_like(H, float("nan")), torch.full_like(H, float("nan")), {k: torch.empty_like(v) for k, v in prm.items()}
+    B.layer_fwd(P, None, 0, desc, H, prm, Y, sv, ws)
+    B.layer_bwd(P, None, 0, desc, H, Y, prm, sv, dH, dX, g, False, ws)
+
+    def mean(t):
+        return (t.roll(1, 0) + t.roll(-1, 0)) / 2.0
+    h, gr, w = H.double(), dH.double(), W.double()
+    for what, got, ref, mag in (
+            ("forward", Y, h @ w[:, :d].T + mean(h) @ w[:, d:].T + b.double(),
+             h.abs() @ w[:, :d].abs().T + mean(h.abs()) @ w[:, d:].abs().T + b.double().abs()),
+            ("dH_in", dX, gr @ w[:, :d] + mean(gr) @ w[:, d:], gr.abs() @ w[:, :d].abs() + mean(gr.abs()) @ w[:, d:].abs())):
+        finite = torch.isfinite(ref)
+        assert bool((got[~finite] == ref[~finite]).all()) and bool(torch.isfinite(got[finite]).all()), what
+        bound = (2 * d + 8.0) * 2.0 ** -24 * mag + 2 * d * 2.0 ** -149
+        assert bool(((got.double() - ref).abs()[finite] <= bound[finite]).all()), what
