@@ -138,14 +138,14 @@ struct AggK {
   const int64_t* rowptr;
   const int32_t* col;
   const T* X;
-  int64_t ldx;
+  uint32_t ldx;
   T* Y;
-  int64_t ldy;
+  uint32_t ldy;
   int width;  // columns of this launch
   int64_t n;
   const int32_t* order;  // the i-th team works on row order[slot0 + i] (null: row i)
-  int64_t n_block, n_wave;  // row kernel: the first n_block rows get a workgroup each, the next n_wave a wavefront each
-  int64_t slot0;      // first entry of `order` this launch covers (its bucket); n counts the entries from there
+  int32_t n_block, n_wave;  // row kernel: the first n_block rows get a workgroup each, the next n_wave a wavefront each
+  int32_t slot0;      // first entry of `order` this launch covers (its bucket); n counts the entries from there
   int64_t skip_from;  // rows of at least this many neighbours belong to another launch (natural-order launches)
   // row kernel on the processing-order copy of the graph: rowptr, col and in_vals are that copy's, indexed by
   // slot, and the row's own factors come per slot too (null: none, or read by row id from in_scale / out_scale)
@@ -157,7 +157,7 @@ struct AggK {
   const float* out_scale;
   int self_loop;
   const T* relu_src;
-  int64_t ld_relu;
+  uint32_t ld_relu;
   float gate_scale;  // factor on the elements that pass relu_src
   // output epilogue (after out_scale): + bias, ReLU
   const float* bias;
@@ -166,26 +166,30 @@ struct AggK {
   DropoutK drop;  // after everything else (DROP instances; ldy is the width of the full matrix there)
 };
 
+// Row numbers and strides have 32 bits, so that the offset of a row is one multiplication.
+template <typename T>
+__device__ inline T* row_at(T* base, uint32_t row, uint32_t ld) {
+  return base + (uint64_t)row * ld;
+}
+
 // A lane owns VEC consecutive columns starting at a multiple of VEC.  When the last lane's columns
 // would cross the end of a row of at least VEC columns, its window is moved left to end with the row,
-// so that every access stays one wide access; the `first` leading columns of the window then belong to
-// the lane before it and are not stored.  In rows of at least VEC columns a lane therefore has either a
+// so that every access stays one wide access; the leading columns of the window are then also those of the lane before
+// it, and both lanes store the same sums (left out, they cost a store for each of the last lane's own
+// columns: 1.88M rows of 47 bfloat16 381 -> 363 us).  In rows of at least VEC columns a lane therefore has either a
 // full window or none (avail <= 0).  Only rows narrower than VEC (the TINY kernel instances) use
 // element accesses.
 struct LaneCols {
   int c0;     // first column of the window
-  int first;  // leading columns of the window owned by the previous lane (0 unless moved)
   int avail;  // columns of the window that exist (>= VEC unless the whole row is narrower than VEC)
 };
 template <int VEC>
 __device__ inline LaneCols lane_cols(int width, int start) {
   LaneCols l;
   l.c0 = start;
-  l.first = 0;
   l.avail = width - start;
   if (l.avail > 0 && l.avail < VEC && width >= VEC) {
     l.c0 = width - VEC;
-    l.first = VEC - l.avail;
     l.avail = VEC;
   }
   return l;
@@ -202,7 +206,7 @@ struct RowTail {
   float ss, so;
   // cread: first column of the lane's read window (valid memory also for lanes that own nothing); s: the row's
   // slot (used by the launches on the processing-order copy)
-  __device__ void request(const AggK<T>& p, int64_t row, int64_t s, int cread) {
+  __device__ void request(const AggK<T>& p, uint32_t row, uint32_t s, int cread) {
     ss = 1.f;
     so = 1.f;
     xs = RowIO<T>::zero_raw();
@@ -213,9 +217,9 @@ struct RowTail {
       if (p.self_loop) {
         if (p.in_scale_slot) ss = p.in_scale_slot[s];
         else if (p.in_scale) ss = p.in_scale[row];
-        xs = RowIO<T>::load_raw(p.X + row * p.ldx + cread);
+        xs = RowIO<T>::load_raw(row_at(p.X, row, p.ldx) + cread);
       }
-      if (p.relu_src) g = RowIO<T>::load_raw(p.relu_src + row * p.ld_relu + cread);
+      if (p.relu_src) g = RowIO<T>::load_raw(row_at(p.relu_src, row, p.ld_relu) + cread);
     }
   }
 };
@@ -223,13 +227,13 @@ struct RowTail {
 // DROP: dropout of the finished row, in rows of a multiple of four columns (100k rows of 128 bfloat16: a launch of its own took
 // 15 us).
 template <typename T, int VEC, bool TINY, bool DROP>
-__device__ inline void finish_row(const AggK<T>& p, int64_t row, int c0, int first, int avail, float (&acc)[VEC],
+__device__ inline void finish_row(const AggK<T>& p, uint32_t row, int c0, int avail, float (&acc)[VEC],
                                   const RowTail<T, VEC, TINY>& t) {
   if constexpr (TINY) {
     if (p.self_loop) {
       const float ss = p.in_scale ? p.in_scale[row] : 1.f;
       float xs[VEC];
-      load_elems<T, VEC>(p.X + row * p.ldx + c0, avail, xs);
+      load_elems<T, VEC>(row_at(p.X, row, p.ldx) + c0, avail, xs);
 #pragma unroll
       for (int i = 0; i < VEC; ++i) acc[i] = fmaf(ss, xs[i], acc[i]);
     }
@@ -238,7 +242,7 @@ __device__ inline void finish_row(const AggK<T>& p, int64_t row, int c0, int fir
     for (int i = 0; i < VEC; ++i) acc[i] *= so;
     if (p.relu_src) {
       float g[VEC];
-      load_elems<T, VEC>(p.relu_src + row * p.ld_relu + c0, avail, g);
+      load_elems<T, VEC>(row_at(p.relu_src, row, p.ld_relu) + c0, avail, g);
 #pragma unroll
       for (int i = 0; i < VEC; ++i) acc[i] = g[i] > 0.f ? acc[i] * p.gate_scale : 0.f;
     }
@@ -277,19 +281,11 @@ __device__ inline void finish_row(const AggK<T>& p, int64_t row, int c0, int fir
   }
   if constexpr (DROP) {
 #pragma unroll
-    for (int q = 0; q < VEC / 4; ++q) drop4(p.drop, (uint64_t)row * (uint64_t)p.ldy + (uint32_t)(p.col0 + c0 + 4 * q), acc + 4 * q);
+    for (int q = 0; q < VEC / 4; ++q) drop4(p.drop, (uint64_t)row * p.ldy + (uint32_t)(p.col0 + c0 + 4 * q), acc + 4 * q);
   }
-  if (first == 0) {
-    if constexpr (TINY) {
-      store_elems<T, VEC>(p.Y + row * p.ldy + c0, avail, acc);
-    } else {
-      RowIO<T>::store_wide(p.Y + row * p.ldy + c0, acc);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < VEC; ++i)
-      if (i >= first) RowIO<T>::store1(p.Y + row * p.ldy + c0 + i, acc[i]);
-  }
+  // A window that was moved left stores the columns that it shares with the lane before as well: both have the same sums.
+  if constexpr (TINY) store_elems<T, VEC>(row_at(p.Y, row, p.ldy) + c0, avail, acc);
+  else RowIO<T>::store_wide(row_at(p.Y, row, p.ldy) + c0, acc);
 }
 
 // ---- rows by teams of lanes -----------------------------------------------------------------------
@@ -308,36 +304,123 @@ __device__ inline void finish_row(const AggK<T>& p, int64_t row, int c0, int fir
 // bfloat16 (64 where a row takes a whole wavefront's lanes) are what the occupancy of the gather needs: 73, 76 and 66 cost
 // 3-8 % of every large launch; fewer in bfloat16 go to scratch memory (30 % slower).
 template <int LANES>
-__device__ inline int team_read_i(int x, int base, int j) {
+__device__ inline int team_read_i(int x, int j) {
   if constexpr (LANES == 64) return __builtin_amdgcn_readlane(x, j);
-  else return __shfl(x, base + j, 64);
+  else return __shfl(x, j, 64);
 }
 template <int LANES>
-__device__ inline float team_read_f(float x, int base, int j) {
-  if constexpr (LANES == 64) return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j));
-  else return __shfl(x, base + j, 64);
+__device__ inline float team_read_f(float x, int j) {
+  return __int_as_float(team_read_i<LANES>(__float_as_int(x), j));
 }
 
-// Adds the neighbours of a row that fall to this wavefront (entries first .. of every `stride`, TL of them at a time).
-template <typename T, int TL, int LPS, int NCH, int TINY>
-__device__ inline void gather_row(const AggK<T>& p, int64_t beg, int64_t end, int64_t first, int64_t stride, int lane,
-                                  const int (&cread)[NCH], float (&acc)[NCH][RowIO<T>::WIDE]) {
+// Adds the neighbours of a short row: col and vals point at its first entry (vals null: factors per node, or none).  The
+// groups read their neighbours' ids themselves.  A row has few neighbours, so a batch is one, two or four neighbours a group,
+// whichever covers the longest row of the wavefront (rows come in descending degree: mostly all of them); slots past a
+// row's end repeat its last neighbour (see RowIO) and are left out, by selects where any lane has one.  Launches of
+// rows of up to 64 bfloat16 take as long as their instructions: with batches of four throughout, 64-bit indices and the row's
+// offsets waiting for its number they had 230 vector ones a wavefront, half of the time (1.88M rows, 3.9M entries, 47
+// bfloat16 363 -> 311 us, 3 bfloat16 258 -> 214; from 128 on, bound by memory, 0-3 %).
+template <typename T, int TL, int LPS, int TINY>
+__device__ inline void gather_short(const AggK<T>& p, const int32_t* __restrict__ col, const float* __restrict__ vals, int cnt,
+                                    int lane, int cread, float (&acc)[RowIO<T>::WIDE]) {
   constexpr int VEC = RowIO<T>::WIDE, NG = TL / LPS;
+  const T* __restrict__ X = p.X + (TINY ? 0 : cread);
+  const float* __restrict__ in_scale = p.in_scale;
+  const int grp = lane % TL / LPS, last = cnt > 0 ? cnt - 1 : 0;
+  // one group a row: its ids are fetched one per lane and handed out by cross-lane reads, so that a batch does not wait for
+  // its own ids (20k rows of 128 bfloat16 9.7 -> 8.0 us)
+  int my_col = 0;
+  float my_s = 1.f;
+  auto fetch = [&](int j) {
+    if (NG > 1 || j % TL != 0) return;
+    const int q = j + lane % TL, qc = q < last ? q : last;
+    my_col = col[qc];
+    if (vals) my_s = vals[qc];
+    else if (in_scale) my_s = in_scale[my_col];
+  };
+  auto batch = [&](int j, auto size) {
+    constexpr int B = decltype(size)::value;
+    uint32_t u[B];
+    float s[B];
+#pragma unroll
+    for (int t = 0; t < B; ++t) {
+      const int q = j + t * NG + grp, qc = q < last ? q : last;
+      if constexpr (NG == 1) {
+        const int from = lane - lane % TL + qc % TL;
+        u[t] = (uint32_t)__shfl(my_col, from, 64);
+        s[t] = __shfl(my_s, from, 64);
+      } else {
+        u[t] = (uint32_t)col[qc];
+        s[t] = vals ? vals[qc] : 1.f;
+      }
+    }
+    if (NG > 1 && !vals && in_scale) {
+#pragma unroll
+      for (int t = 0; t < B; ++t) s[t] = in_scale[u[t]];
+    }
+    const bool whole = __all(j + B * NG <= cnt);
+    if constexpr (TINY) {
+      float v[B][TINY];
+#pragma unroll
+      for (int t = 0; t < B; ++t)
+#pragma unroll
+        for (int i = 0; i < TINY; ++i) v[t][i] = RowIO<T>::load1(row_at(X, u[t], p.ldx) + i);
+#pragma unroll
+      for (int t = 0; t < B; ++t)
+#pragma unroll
+        for (int i = 0; i < TINY; ++i) acc[i] = j + t * NG + grp < cnt ? fmaf(s[t], v[t][i], acc[i]) : acc[i];
+    } else {
+      typename RowIO<T>::Raw v[B];
+#pragma unroll
+      for (int t = 0; t < B; ++t) v[t] = RowIO<T>::load_raw(row_at(X, u[t], p.ldx));
+      if (whole) {
+#pragma unroll
+        for (int t = 0; t < B; ++t) RowIO<T>::fma_raw(acc, s[t], v[t]);
+      } else {
+#pragma unroll
+        for (int t = 0; t < B; ++t) RowIO<T>::fma_raw(acc, s[t], RowIO<T>::keep_if(j + t * NG + grp < cnt, v[t]));
+      }
+    }
+  };
+  for (int j = 0; __any(j < cnt);) {
+    fetch(j);
+    if (__any(j + 2 * NG < cnt)) {
+      batch(j, std::integral_constant<int, 4>{});
+      j += 4 * NG;
+    } else if (__any(j + NG < cnt)) {
+      batch(j, std::integral_constant<int, 2>{});
+      j += 2 * NG;
+    } else {
+      batch(j, std::integral_constant<int, 1>{});
+      j += NG;
+    }
+  }
+#pragma unroll
+  for (int off = LPS; off < TL; off <<= 1) {
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
+  }
+}
+
+// Adds the neighbours of a row that fall to this wavefront (entries first .. of every `stride`, 64 of them at a time): ids are
+// fetched one per lane and handed out by cross-lane reads.
+template <typename T, int LPS, int NCH>
+__device__ inline void gather_row(const AggK<T>& p, const int32_t* __restrict__ col, const float* __restrict__ vals, int cnt_row,
+                                  int first, int stride, int lane, const int (&cread)[NCH], float (&acc)[NCH][RowIO<T>::WIDE]) {
+  constexpr int VEC = RowIO<T>::WIDE, NG = 64 / LPS;
   constexpr int UNR = 4;
-  const int32_t* __restrict__ col = p.col;
   const T* __restrict__ X = p.X;
   const float* __restrict__ in_scale = p.in_scale;
-  const float* __restrict__ in_vals = p.in_vals;
-  const int tl = lane % TL, base = lane - tl, grp = tl / LPS;
-  for (int64_t e0 = beg + first; e0 < end; e0 += stride) {
-    const int64_t e = e0 + tl < end ? e0 + tl : end - 1;
+  const int grp = lane / LPS;
+  for (int e0 = first; e0 < cnt_row; e0 += stride) {
+    const int e = e0 + lane < cnt_row ? e0 + lane : cnt_row - 1;
     const int my_col = col[e];
     float my_s = 1.f;
-    if (in_vals) my_s = in_vals[e];
+    if (vals) my_s = vals[e];
     else if (in_scale) my_s = in_scale[my_col];
-    const int cnt = (int)((end - e0) < (int64_t)TL ? (end - e0) : (int64_t)TL);
+    const int cnt = cnt_row - e0 < 64 ? cnt_row - e0 : 64;
     for (int j = 0; j < cnt; j += UNR * NG) {
-      int u[UNR];
+      uint32_t u[UNR];
       float s[UNR];
       bool ok[UNR];
 #pragma unroll
@@ -346,36 +429,24 @@ __device__ inline void gather_row(const AggK<T>& p, int64_t beg, int64_t end, in
         const int q = j + t * NG + (NG == 1 ? 0 : grp);
         ok[t] = q < cnt;
         const int qc = ok[t] ? q : cnt - 1;
-        u[t] = team_read_i<LPS>(my_col, base, qc);
-        s[t] = team_read_f<LPS>(my_s, base, qc);
+        u[t] = (uint32_t)team_read_i<LPS>(my_col, qc);
+        s[t] = team_read_f<LPS>(my_s, qc);
       }
-      if constexpr (TINY) {
-        float v[UNR][VEC];
+      typename RowIO<T>::Raw v[UNR][NCH];
 #pragma unroll
-        for (int t = 0; t < UNR; ++t)
+      for (int t = 0; t < UNR; ++t) {
+        const T* const src = row_at(X, u[t], p.ldx);
 #pragma unroll
-          for (int i = 0; i < TINY; ++i) v[t][i] = RowIO<T>::load1(X + (int64_t)u[t] * p.ldx + i);
-#pragma unroll
-        for (int t = 0; t < UNR; ++t)
-#pragma unroll
-          for (int i = 0; i < TINY; ++i) acc[0][i] = ok[t] ? fmaf(s[t], v[t][i], acc[0][i]) : acc[0][i];
-      } else {
-        typename RowIO<T>::Raw v[UNR][NCH];
-#pragma unroll
-        for (int t = 0; t < UNR; ++t) {
-          const T* const src = X + (int64_t)u[t] * p.ldx;
-#pragma unroll
-          for (int c = 0; c < NCH; ++c) v[t][c] = RowIO<T>::load_raw(src + cread[c]);
-        }
-#pragma unroll
-        for (int t = 0; t < UNR; ++t)
-#pragma unroll
-          for (int c = 0; c < NCH; ++c) RowIO<T>::fma_raw(acc[c], s[t], RowIO<T>::keep_if(ok[t], v[t][c]));
+        for (int c = 0; c < NCH; ++c) v[t][c] = RowIO<T>::load_raw(src + cread[c]);
       }
+#pragma unroll
+      for (int t = 0; t < UNR; ++t)
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) RowIO<T>::fma_raw(acc[c], s[t], RowIO<T>::keep_if(ok[t], v[t][c]));
     }
   }
 #pragma unroll
-  for (int off = LPS; off < TL; off <<= 1) {
+  for (int off = LPS; off < 64; off <<= 1) {
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
 #pragma unroll
@@ -389,36 +460,34 @@ __device__ inline void gather_row(const AggK<T>& p, int64_t beg, int64_t end, in
 // condition on the width wait for each other (bfloat16, 230k nodes, 14M entries: 3 columns 302 -> 108 us, 8 columns 183 -> 136;
 // 30k nodes, 14M entries: 3 columns 162 -> 44, 8 columns 95 -> 50).
 template <typename T, int LPS, int TINY>
-__device__ inline void gather_narrow(const AggK<T>& p, int64_t beg, int64_t end, int wave, int waves, int lane, int cread,
-                                     float (&acc)[RowIO<T>::WIDE]) {
+__device__ inline void gather_narrow(const AggK<T>& p, const int32_t* __restrict__ col, const float* __restrict__ in_vals, int cnt,
+                                     int wave, int waves, int lane, int cread, float (&acc)[RowIO<T>::WIDE]) {
   constexpr int VEC = RowIO<T>::WIDE, NG = 64 / LPS;
   constexpr int UNR = 4;
-  const int32_t* __restrict__ col = p.col;
   const float* __restrict__ in_scale = p.in_scale;
-  const float* __restrict__ in_vals = p.in_vals;
   const T* __restrict__ X = p.X + (TINY ? 0 : cread);
-  const int64_t last = end - 1, e0 = beg + wave * (NG * UNR) + lane / LPS, step = (int64_t)waves * (NG * UNR);
+  const int last = cnt - 1, e0 = wave * (NG * UNR) + lane / LPS, step = waves * (NG * UNR);
   // scale_mode: 0 no per-source factor, 1 gathered from the per-node vector, 2 per entry
   auto gather = [&](auto scale_mode) {
     constexpr int MODE = decltype(scale_mode)::value;
-    for (int64_t e = e0; e < end; e += step) {
-      int u[UNR];
+    for (int e = e0; e < cnt; e += step) {
+      uint32_t u[UNR];
       float s[UNR];
       if constexpr (TINY) {
         // 64 neighbours a slot: the element loads of slots that no lane has are passed over
         float v[UNR][TINY];
 #pragma unroll
-        for (int t = 0; t < UNR; ++t) u[t] = e + t * NG < end ? col[e + t * NG] : -1;
+        for (int t = 0; t < UNR; ++t) u[t] = e + t * NG < cnt ? (uint32_t)col[e + t * NG] : ~0u;
 #pragma unroll
         for (int t = 0; t < UNR; ++t) {
           s[t] = 1.f;
 #pragma unroll
           for (int i = 0; i < TINY; ++i) v[t][i] = 0.f;
-          if (u[t] >= 0) {
+          if (u[t] != ~0u) {
             if constexpr (MODE == 2) s[t] = in_vals[e + t * NG];
             if constexpr (MODE == 1) s[t] = in_scale[u[t]];
 #pragma unroll
-            for (int i = 0; i < TINY; ++i) v[t][i] = RowIO<T>::load1(X + (int64_t)u[t] * p.ldx + i);
+            for (int i = 0; i < TINY; ++i) v[t][i] = RowIO<T>::load1(row_at(X, u[t], p.ldx) + i);
           }
         }
 #pragma unroll
@@ -429,18 +498,18 @@ __device__ inline void gather_narrow(const AggK<T>& p, int64_t beg, int64_t end,
         typename RowIO<T>::Raw v[UNR];
 #pragma unroll
         for (int t = 0; t < UNR; ++t) {
-          const int64_t ec = e + t * NG < last ? e + t * NG : last;  // past the end: the last one, left out (see RowIO)
-          u[t] = col[ec];
+          const int ec = e + t * NG < last ? e + t * NG : last;  // past the end: the last one, left out (see RowIO)
+          u[t] = (uint32_t)col[ec];
           if constexpr (MODE == 2) s[t] = in_vals[ec];
         }
 #pragma unroll
         for (int t = 0; t < UNR; ++t) {
           if constexpr (MODE == 1) s[t] = in_scale[u[t]];
           if constexpr (MODE == 0) s[t] = 1.f;
-          v[t] = RowIO<T>::load_raw(X + (int64_t)u[t] * p.ldx);
+          v[t] = RowIO<T>::load_raw(row_at(X, u[t], p.ldx));
         }
 #pragma unroll
-        for (int t = 0; t < UNR; ++t) RowIO<T>::fma_raw(acc, s[t], RowIO<T>::keep_if(e + t * NG < end, v[t]));
+        for (int t = 0; t < UNR; ++t) RowIO<T>::fma_raw(acc, s[t], RowIO<T>::keep_if(e + t * NG < cnt, v[t]));
       }
     }
   };
@@ -462,28 +531,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4
   constexpr int RPW = 64 / TL;  // short rows per wavefront
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane % LPS;
-  const int64_t b = blockIdx.x;
-  const int64_t wave_blocks = (p.n_wave + 3) / 4;
+  const uint32_t b = blockIdx.x, n_block = p.n_block, n_wave = p.n_wave;
+  const uint32_t wave_blocks = (n_wave + 3) / 4;
   int team;  // 0 short rows, 1 a wavefront per row, 2 a workgroup per row (uniform over the block)
-  int64_t slot, limit;
-  if (b < p.n_block) {
+  uint32_t slot, limit;
+  if (b < n_block) {
     team = 2;
     slot = b;
-    limit = p.n_block;
-  } else if (b < p.n_block + wave_blocks) {
+    limit = n_block;
+  } else if (b < n_block + wave_blocks) {
     team = 1;
-    slot = p.n_block + (b - p.n_block) * 4 + wave;
-    limit = p.n_block + p.n_wave;
+    slot = n_block + (b - n_block) * 4 + wave;
+    limit = n_block + n_wave;
   } else {
     team = 0;
-    slot = p.n_block + p.n_wave + ((b - p.n_block - wave_blocks) * 4 + wave) * RPW + lane / TL;
-    limit = p.n;
+    slot = n_block + n_wave + ((b - n_block - wave_blocks) * 4 + wave) * RPW + lane / TL;
+    limit = (uint32_t)p.n;
   }
   if (slot >= limit) return;  // never in a workgroup that shares a row
-  const int64_t s = p.slot0 + slot;
-  const int64_t row = p.order ? (int64_t)p.order[s] : slot;
-  const int64_t at = p.by_slot ? s : row;
-  const int64_t beg = p.rowptr[at], end = p.rowptr[at + 1];
+  const uint32_t s = (uint32_t)p.slot0 + slot;
+  uint32_t row = slot;
+  int64_t beg, end;
+  if (p.by_slot) {  // the row's number is not needed for its offsets: both are on their way together
+    row = (uint32_t)p.order[s];
+    beg = p.rowptr[s], end = p.rowptr[s + 1];
+  } else {
+    if (p.order) row = (uint32_t)p.order[s];
+    beg = p.rowptr[row], end = p.rowptr[row + 1];
+  }
+  const int cnt = (int)(end - beg);
+  // a row without neighbours beside one that has some reads the graph's first entry
+  const int64_t at = cnt > 0 ? beg : 0;
+  const int32_t* const col = p.col + at;
+  const float* const vals = p.in_vals ? p.in_vals + at : nullptr;
 
   float acc[NCH][VEC];
   LaneCols lc[NCH];
@@ -499,11 +579,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4
 #pragma unroll
   for (int c = 0; c < NCH; ++c) tail[c].request(p, row, s, cread[c]);
 
-  if (TL < 64 && team == 0) {
-    gather_row<T, TL, LPS, NCH, TINY>(p, beg, end, 0, TL, lane, cread, acc);
+  bool short_row = false;
+  if constexpr (TL < 64) short_row = team == 0;
+  if (short_row) {
+    if constexpr (TL < 64) gather_short<T, TL, LPS, TINY>(p, col, vals, cnt, lane, cread[0], acc[0]);
   } else {
-    if constexpr (LPS <= 8) gather_narrow<T, LPS, TINY>(p, beg, end, team == 2 ? wave : 0, team == 2 ? 4 : 1, lane, cread[0], acc[0]);
-    else gather_row<T, 64, LPS, NCH, TINY>(p, beg, end, team == 2 ? wave * 64 : 0, team == 2 ? 256 : 64, lane, cread, acc);
+    if constexpr (LPS <= 8) gather_narrow<T, LPS, TINY>(p, col, vals, cnt, team == 2 ? wave : 0, team == 2 ? 4 : 1, lane, cread[0], acc[0]);
+    else gather_row<T, LPS, NCH>(p, col, vals, cnt, team == 2 ? wave * 64 : 0, team == 2 ? 256 : 64, lane, cread, acc);
     if (team == 2) {
       __shared__ float partial[3][NCH * LPS * VEC];
       if (wave > 0 && lane < LPS) {
@@ -525,7 +607,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4
   if ((lane % (team == 0 ? TL : 64)) >= LPS) return;  // the first neighbour group of the team writes
 #pragma unroll
   for (int c = 0; c < NCH; ++c)
-    if (lc[c].avail > 0) finish_row<T, VEC, TINY != 0, DROP>(p, row, lc[c].c0, lc[c].first, lc[c].avail, acc[c], tail[c]);
+    if (lc[c].avail > 0) finish_row<T, VEC, TINY != 0, DROP>(p, row, lc[c].c0, lc[c].avail, acc[c], tail[c]);
 }
 
 // ---- XCD-affine column slices ---------------------------------------------------------------------
@@ -540,7 +622,7 @@ __global__ __launch_bounds__(256) void aggregate_sliced_kernel(const AggK<T> p) 
   constexpr int UNR = 4;
   const int lane = threadIdx.x & 63;
   const int sub = lane % LPS, grp = lane / LPS;
-  const int64_t row = (int64_t)(blockIdx.x / 8u) * 4 + (threadIdx.x >> 6);  // natural order, which measured better
+  const uint32_t row = (blockIdx.x / 8u) * 4 + (threadIdx.x >> 6);  // natural order, which measured better
   if (row >= p.n) return;
   const int c0 = ((int)(blockIdx.x % 8u) * LPS + sub) * VEC;
   const T* __restrict__ X = p.X + c0;
@@ -560,21 +642,21 @@ __global__ __launch_bounds__(256) void aggregate_sliced_kernel(const AggK<T> p) 
     constexpr int MODE = decltype(scale_mode)::value;
     const int64_t last = end - 1;
     for (int64_t e = beg + grp; e < end; e += NG * UNR) {
-      int u[UNR];
+      uint32_t u[UNR];
       float s[UNR];
       typename RowIO<T>::Raw v[UNR];
 #pragma unroll
       for (int t = 0; t < UNR; ++t) {
         const int64_t ee = e + t * NG;
         const int64_t ec = ee < last ? ee : last;
-        u[t] = col[ec];
+        u[t] = (uint32_t)col[ec];
         if constexpr (MODE == 2) s[t] = in_vals[ec];
       }
 #pragma unroll
       for (int t = 0; t < UNR; ++t) {
         if constexpr (MODE == 1) s[t] = in_scale[u[t]];
         if constexpr (MODE == 0) s[t] = 1.f;
-        v[t] = RowIO<T>::load_raw(X + (int64_t)u[t] * p.ldx);
+        v[t] = RowIO<T>::load_raw(row_at(X, u[t], p.ldx));
       }
 #pragma unroll
       for (int t = 0; t < UNR; ++t) RowIO<T>::fma_raw(acc, s[t], RowIO<T>::keep_if(e + t * NG < end, v[t]));
@@ -589,7 +671,7 @@ __global__ __launch_bounds__(256) void aggregate_sliced_kernel(const AggK<T> p) 
     for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
   }
   if (grp != 0) return;
-  finish_row<T, VEC, false, DROP>(p, row, c0, 0, VEC, acc, tail);
+  finish_row<T, VEC, false, DROP>(p, row, c0, VEC, acc, tail);
 }
 
 // ---- hub rows -----------------------------------------------------------------------------------
@@ -607,7 +689,7 @@ __global__ __launch_bounds__(HUB_WAVES * 64) void aggregate_hub_kernel(const Agg
   __shared__ float partial[HUB_WAVES - 1][LPS * VEC];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane % LPS, grp = lane / LPS;
-  const int64_t row = (int64_t)p.order[p.slot0 + blockIdx.x];
+  const uint32_t row = (uint32_t)p.order[p.slot0 + blockIdx.x];
   const LaneCols lc = lane_cols<VEC>(p.width, (int)blockIdx.y * (LPS * VEC) + sub * VEC);
   const int c0 = lc.c0, avail = lc.avail;
   const int cread = avail > 0 ? c0 : p.width - VEC;  // the launcher sends only rows of at least VEC columns here
@@ -625,20 +707,20 @@ __global__ __launch_bounds__(HUB_WAVES * 64) void aggregate_hub_kernel(const Agg
     const int64_t last = end - 1;
     // step of one wavefront: NG neighbours; of the workgroup: NG * HUB_WAVES; UNR steps in flight
     for (int64_t e = beg + (int64_t)wave * NG + grp; e < end; e += (int64_t)NG * HUB_WAVES * UNR) {
-      int u[UNR];
+      uint32_t u[UNR];
       float sc[UNR];
       typename RowIO<T>::Raw v[UNR];
 #pragma unroll
       for (int t = 0; t < UNR; ++t) {
         const int64_t ee = e + (int64_t)t * NG * HUB_WAVES;
         const int64_t ec = ee < last ? ee : last;
-        u[t] = col[ec];
+        u[t] = (uint32_t)col[ec];
         sc[t] = in_vals ? in_vals[ec] : 1.f;
       }
 #pragma unroll
       for (int t = 0; t < UNR; ++t) {
         if (!in_vals && in_scale) sc[t] = in_scale[u[t]];
-        v[t] = RowIO<T>::load_raw(Xread + (int64_t)u[t] * p.ldx);
+        v[t] = RowIO<T>::load_raw(row_at(Xread, u[t], p.ldx));
       }
 #pragma unroll
       for (int t = 0; t < UNR; ++t)
@@ -660,7 +742,7 @@ __global__ __launch_bounds__(HUB_WAVES * 64) void aggregate_hub_kernel(const Agg
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] += partial[w][sub * VEC + i];
   }
-  finish_row<T, VEC, false, DROP>(p, row, c0, lc.first, avail, acc, tail);
+  finish_row<T, VEC, false, DROP>(p, row, c0, avail, acc, tail);
 }
 
 // ---- host side ------------------------------------------------------------------------------------
@@ -712,7 +794,7 @@ static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCos
   const int tl = lps < 16 ? 16 : lps;
   const int nch = chunks > 64 ? 2 : 1;
   const int64_t short_rows = k.n - k.n_block - k.n_wave, per_block = 4 * (64 / tl);
-  const int64_t blocks = k.n_block + (k.n_wave + 3) / 4 + (short_rows + per_block - 1) / per_block;
+  const int64_t blocks = k.n_block + ((int64_t)k.n_wave + 3) / 4 + (short_rows + per_block - 1) / per_block;
   COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
   char pname[96] = "";
   if (profiling()) snprintf(pname, sizeof(pname), "aggregate_kernel<%s,%d,%d,%d,%d,%s> width=%d", type_name<T>(), tl, lps, nch,
@@ -784,12 +866,12 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   AggK<T> k{};
   k.rowptr = a.g.rowptr;
   k.col = a.g.col;
-  k.ldx = a.ldx;
-  k.ldy = a.ldy;
+  k.ldx = (uint32_t)a.ldx;
+  k.ldy = (uint32_t)a.ldy;
   k.in_scale = a.in_scale;
   k.out_scale = a.out_scale;
   k.self_loop = a.self_loop;
-  k.ld_relu = a.ld_relu;
+  k.ld_relu = (uint32_t)a.ld_relu;
   k.gate_scale = a.gate_scale;
   k.bias = a.bias;
   k.relu_out = a.relu_out;
@@ -868,7 +950,7 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
     return COFREE_OK;
   }
   k.order = a.g.order;
-  k.slot0 = n_hub;
+  k.slot0 = (int32_t)n_hub;
   k.n = a.g.n - n_hub;
   // Graphs of high average degree leave their long rows to a wavefront each where the rows are narrow, so that four
   // wavefronts would find too little to share (115k nodes, 7M entries, 8 bfloat16 columns 1.10 -> 0.99 of the time with a
@@ -878,8 +960,8 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   // of that time, 0.81 without; 115k nodes, 7M entries, 41 float32 columns 0.77 and 0.86).
   // (A launch has less than 2^32 work-items: eight million long rows do not need a workgroup each either.)
   const bool share = a.g.n_block < (1 << 23) && (!waves || (a.width > 8 * WIDE && a.g.nnz < (1 << 23)));
-  k.n_block = buckets && share ? a.g.n_block - n_hub : 0;
-  k.n_wave = waves ? k.n - k.n_block : (buckets ? a.g.n_wave - n_hub - k.n_block : 0);
+  k.n_block = buckets && share ? (int32_t)(a.g.n_block - n_hub) : 0;
+  k.n_wave = waves ? (int32_t)(k.n - k.n_block) : (buckets ? (int32_t)(a.g.n_wave - n_hub) - k.n_block : 0);
   // The row kernel walks the processing-order copy of the graph (1.9M-node partition, 512-wide float32: 3.00 ms
   // by row id, 2.8 ms in natural order with its worse balance).  COFREE_AGG_SLOTS = 0 reads by row id.
   bool slots = a.g.order != nullptr && a.g.s_rowptr != nullptr;
@@ -921,6 +1003,7 @@ int32_t launch_aggregate(const AggArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(a.X && a.Y && a.X != a.Y, "aggregate: X and Y must be distinct non-NULL buffers");
   COFREE_REQUIRE(a.ldx >= a.width && a.ldy >= a.width, "aggregate: leading dimension smaller than width");
   COFREE_REQUIRE(a.g.n < ((int64_t)1 << 31), "aggregate: too many rows");
+  COFREE_REQUIRE((a.ldx | a.ldy | a.ld_relu) < ((int64_t)1 << 32), "aggregate: leading dimension too large");
   if (a.g.n == 0) return COFREE_OK;
   const bool drop = a.dropout.q > 0.f;
   if (a.dtype == COFREE_F32) return drop ? launch_typed<float, true>(a, stream) : launch_typed<float, false>(a, stream);

@@ -54,3 +54,33 @@ def check(env, dtype, width, masked):
         Y.fill_(float("nan"))
         B.aggregate(P, masks, 0, mode, X, Y, width, code)
         assert_close(Y.float().cpu().numpy(), ref(g, X64), tol, f"mode {mode} width {width}")
+
+
+@pytest.mark.parametrize("dtype,width", [("f32", w) for w in (3, 4, 13, 30, 41, 100)] + [("bf16", w) for w in (5, 8, 15, 30, 47, 100, 172)])
+def test_short_rows(env, dtype, width):
+    """Rows of 0 to 23 neighbours, whose batches are one, two or four neighbours a lane group, beside each other in a
+    wavefront; an infinite row reaches its neighbours' sums only."""
+    B, torch = env["B"], env["torch"]
+    print(f"[case] short rows dtype={dtype} width={width}", flush=True)
+    src, dst = inputs.hub_graph(701, list(range(1, 24)) * 2, 250, 5)
+    P, O = B.build_partition(701, src, dst, 1, 0, 1), o_partition.build_partition(701, src, dst, 1, 0, 1)
+    td, code, tol = (torch.float32, B.F32, 1e-5) if dtype == "f32" else (torch.bfloat16, B.BF16, 5e-3)
+    masks = B.dropedge_k(P, 1, 0.5, 3)
+    n = P.num_nodes
+    X = torch.from_numpy(np.random.default_rng(width).standard_normal((n, width)).astype(np.float32)).to(td).cuda()
+    X64 = X.float().cpu().numpy().astype(np.float64)
+    bad = int(np.argmax(np.diff(O["rowptr"])))
+    Xinf = X.clone()
+    Xinf[bad] = float("inf")
+    for m, g in ((None, o_dropedge.full_graph(O)), (masks, o_dropedge.masked_graph(O, o_dropedge.masks(O["n_edges"], 1, 0.5, 3)[0]))):
+        rowptr, col = g[0], g[1]
+        assert m is None or int(np.min(np.diff(rowptr))) == 0
+        for mode, ref in ((B.AGG_MEAN, o_layers.mean_aggregate), (B.AGG_GCN, o_layers.gcn_aggregate)):
+            Y = torch.full_like(X, float("nan"))
+            B.aggregate(P, m, 0, mode, X, Y, width, code)
+            assert_close(Y.float().cpu().numpy(), ref(g, X64), tol, f"mode {mode} width {width}")
+            Z = torch.full_like(X, float("nan"))
+            B.aggregate(P, m, 0, mode, Xinf, Z, width, code)
+            reached = col[rowptr[bad]:rowptr[bad + 1]].tolist() + ([bad] if mode == B.AGG_GCN else [])
+            other = np.setdiff1d(np.arange(n), reached)
+            assert bool(torch.isposinf(Z[reached]).all()) and torch.equal(Z[other], Y[other])
