@@ -280,7 +280,8 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
 
 /* The layers of a model in one call (Algorithm 1 line 10), for callers whose iteration is bound by the host: the same
  * work as n_layers calls of cofree_layer_fwd in ascending order, or of cofree_layer_bwd in descending order, on one
- * workspace that is large enough for each of them.  A layer's H_in is normally the H_out of the layer before, its dH_in
+ * workspace that is large enough for each of them; with one of cofree_layers_workspace_bytes the backward call sums the
+ * gradients of small graphs in one launch for all layers.  A layer's H_in is normally the H_out of the layer before, its dH_in
  * the dH_out of the layer before.  The forward call does not read dH_out, dH_in and grads.  An error of one layer ends the
  * call; what was enqueued before it runs. */
 typedef struct cofree_layer_call {
@@ -293,6 +294,7 @@ typedef struct cofree_layer_call {
   void* dH_in;
   cofree_layer_grads grads;
 } cofree_layer_call;
+size_t cofree_layers_workspace_bytes(const cofree_layer_desc* descs, int32_t n_layers, int64_t n_nodes);
 int32_t cofree_layers_fwd(const cofree_partition* part, const cofree_masks* masks, int32_t mask_id,
                           const cofree_layer_call* layers, int32_t n_layers, void* workspace, size_t workspace_bytes,
                           void* stream);

@@ -43,6 +43,7 @@ EXPORTS = [
     "cofree_masks_host_graph", "cofree_dropedge_pick",
     "cofree_aggregate",
     "cofree_layer_workspace_bytes", "cofree_layer_fwd", "cofree_layer_bwd", "cofree_layers_fwd", "cofree_layers_bwd",
+    "cofree_layers_workspace_bytes",
     "cofree_loss_workspace_bytes", "cofree_loss_weighted", "cofree_loss_weighted_static", "cofree_loss_bce_weighted",
     "cofree_grad_gap", "cofree_step", "cofree_dense_nt_f32",
     "cofree_profile_enable", "cofree_profile_read",
@@ -115,6 +116,7 @@ def _load() -> C.CDLL:
         "cofree_dropedge_pick": (i32, [u64, u64, i32, P(i32)]),
         "cofree_aggregate": (i32, [vp, vp, i32, i32, vp, vp, i32, i32, vp]),
         "cofree_layer_workspace_bytes": (sz, [P(LayerDesc), i64, i32]),
+        "cofree_layers_workspace_bytes": (sz, [P(LayerDesc), i32, i64]),
         "cofree_layer_fwd": (i32, [vp, vp, i32, P(LayerDesc), vp, P(LayerParams), vp, P(LayerSaved), vp, sz, vp]),
         "cofree_layer_bwd": (i32, [vp, vp, i32, P(LayerDesc), vp, vp, P(LayerParams), P(LayerSaved), vp, vp,
                                    P(LayerGrads), i32, vp, sz, vp]),
@@ -330,6 +332,12 @@ def layer_desc(kind: int, d_in: int, d_msg: int, d_out: int, act: int = 0, dropo
 
 def layer_workspace_bytes(desc: LayerDesc, n_nodes: int, backward: bool) -> int:
     return int(lib.cofree_layer_workspace_bytes(C.byref(desc), n_nodes, 1 if backward else 0))
+
+
+def layers_workspace_bytes(descs, n_nodes: int) -> int:
+    """Scratch of both directions of a list of layers, with room for all their gradients' partials where that is faster."""
+    arr = (LayerDesc * len(descs))(*descs)
+    return int(lib.cofree_layers_workspace_bytes(arr, len(descs), n_nodes))
 
 
 def _params(p: dict, cls):

@@ -342,7 +342,7 @@ bool gemm_drops(const GemmArgs& a);
 size_t gemm_param_scratch_bytes(int32_t N, int64_t K);
 
 // Sums of partial results in a fixed order: C[i, j] (+)= sum over z of part[z * stride + i * cols + j].  The weight and
-// bias gradients of a layer leave partials behind and are summed by one launch at its end.
+// bias gradients of a layer leave partials behind and are summed by one launch at its end, or at the end of all layers.
 struct SplitSum {
   const float* part;
   int64_t stride;
@@ -352,7 +352,7 @@ struct SplitSum {
   int32_t block0;  // first workgroup of this job (set by the launcher)
 };
 struct SplitSums {
-  static constexpr int MAX = 8;
+  static constexpr int MAX = 24, PER_LAYER = 5;  // a layer leaves at most three weight and two bias gradients
   SplitSum job[MAX];
   int32_t n = 0;
   int32_t accumulate = 0;

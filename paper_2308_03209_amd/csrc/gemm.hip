@@ -16,6 +16,7 @@
 // A may consist of two k-segments taken from different matrices: this is the CONCAT of the
 // layer definition, evaluated without materialising the concatenated matrix.
 #include <algorithm>
+#include <climits>
 #include <cstdio>
 
 #include "colsum.h"
@@ -556,8 +557,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
 constexpr int SR_IDX = 32, SR_ZG = 8;
 __global__ __launch_bounds__(256) void split_sums_kernel(const SplitSums p) {
   __shared__ float red[SR_ZG][SR_IDX];
-  int q = 0;  // this block's job (uniform)
-  while (q + 1 < p.n && (int)blockIdx.x >= p.job[q + 1].block0) ++q;
+  // this block's job (uniform): the last one that starts at or before it
+  static_assert(SplitSums::MAX <= 64, "one lane a job");
+  const int at = threadIdx.x & 63;
+  const int first = at < p.n ? p.job[at].block0 : INT_MAX;
+  const int q = __builtin_amdgcn_readfirstlane(__popcll(__ballot(first <= (int)blockIdx.x)) - 1);
   const SplitSum& jb = p.job[q];
   const int ii = threadIdx.x % SR_IDX, zg = threadIdx.x / SR_IDX;
   const int64_t idx = (int64_t)((int)blockIdx.x - jb.block0) * SR_IDX + ii;

@@ -155,13 +155,12 @@ static FwdPlan plan_fwd(const cofree_layer_desc& d, int64_t n, void* ws) {
 
 struct BwdPlan {
   void *dP = nullptr, *dA = nullptr, *dZ = nullptr, *T = nullptr, *params = nullptr;
-  // partials of up to three weight gradients (they stay until the layer's last launch sums them), of one bias gradient
+  // partials of up to three weight gradients (they stay until they are summed), of one bias gradient
   float *wg[3] = {nullptr, nullptr, nullptr}, *cs = nullptr;
-  size_t bytes = 0;
 };
 
-static BwdPlan plan_bwd(const cofree_layer_desc& d, int64_t n, void* ws) {
-  Carver c(ws);
+// c: what is dead when the layer is done; part: the partials (the same carver where a layer sums its own)
+static BwdPlan plan_bwd(const cofree_layer_desc& d, int64_t n, Carver& c, Carver& part) {
   BwdPlan p;
   const size_t N = (size_t)n, es = elem_size(d.dtype);
   if (d.kind == COFREE_SAGE_MEAN) {
@@ -169,23 +168,49 @@ static BwdPlan plan_bwd(const cofree_layer_desc& d, int64_t n, void* ws) {
     p.dA = c.take(N * d.d_msg * es);
     p.dZ = c.take(N * d.d_msg * es);
     if (sage_merged(d)) {
-      p.wg[0] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_msg, n, d.d_in));
+      p.wg[0] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_msg, n, d.d_in));
     } else {
-      p.wg[0] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
-      p.wg[1] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_msg, n));
+      p.wg[0] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
+      p.wg[1] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_msg, n));
     }
-    p.wg[2] = (float*)c.take(4 * wgrad_workspace_floats(d.d_msg, d.d_in, n));
+    p.wg[2] = (float*)part.take(4 * wgrad_workspace_floats(d.d_msg, d.d_in, n));
   } else {
     if (d.dropout_q > 0.f || d.act) p.dP = c.take(N * d.d_out * es);
     // transform first: T = Ahat dPre [n, d_out]; aggregate first: T = norm * (dPre W) [n, d_in]
     p.T = c.take(N * (gcn_transform_first(d) ? d.d_out : d.d_in) * es);
-    p.wg[0] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n, conv_merged(d) ? d.d_in : 0));
-    if (d.kind == COFREE_SAGE_CONV && !conv_merged(d)) p.wg[1] = (float*)c.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
-    if (d.kind == COFREE_GCN && gcn_transform_first(d)) p.cs = (float*)c.take(4 * colsum_workspace_floats(d.d_out));
+    p.wg[0] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n, conv_merged(d) ? d.d_in : 0));
+    if (d.kind == COFREE_SAGE_CONV && !conv_merged(d)) p.wg[1] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
+    if (d.kind == COFREE_GCN && gcn_transform_first(d)) p.cs = (float*)part.take(4 * colsum_workspace_floats(d.d_out));
   }
   p.params = c.take(param_scratch_bytes(d));
-  p.bytes = c.used;
   return p;
+}
+
+static size_t bwd_bytes(const cofree_layer_desc& d, int64_t n) {
+  Carver c(nullptr);
+  plan_bwd(d, n, c, c);
+  return c.used;
+}
+
+// The layers of a backward pass may leave their partials until one launch sums all of them: a launch less per layer, which
+// is what small graphs wait for (2,000 nodes, two layers 69.4 -> 66.5 us a training step).  Beyond DEFER_MAX bytes of partials the sums of a layer take
+// longer than a launch does, and every layer uses the same part of the workspace.
+constexpr size_t DEFER_MAX = (size_t)32 << 20;
+struct Deferral {
+  size_t scratch = 0, partials = 0;  // bytes: shared by the layers in turn; of all layers
+  bool worth = false;
+};
+template <typename Desc>
+static Deferral plan_deferral(int32_t n_layers, int64_t n, const Desc& desc) {
+  Deferral f;
+  for (int32_t l = 0; l < n_layers; ++l) {
+    Carver c(nullptr), part(nullptr);
+    plan_bwd(desc(l), n, c, part);
+    f.scratch = max2(f.scratch, c.used);
+    f.partials += part.used;
+  }
+  f.worth = n_layers > 1 && f.partials <= DEFER_MAX;
+  return f;
 }
 
 static int32_t check_desc(const cofree_layer_desc* d) {
@@ -225,7 +250,7 @@ size_t cofree_layer_desc_size(void) { return sizeof(cofree_layer_desc); }
 
 size_t cofree_layer_workspace_bytes(const cofree_layer_desc* desc, int64_t n_nodes, int32_t backward) {
   if (!desc || n_nodes < 0) return 0;
-  const size_t b = backward ? plan_bwd(*desc, n_nodes, nullptr).bytes : plan_fwd(*desc, n_nodes, nullptr).bytes;
+  const size_t b = backward ? bwd_bytes(*desc, n_nodes) : plan_fwd(*desc, n_nodes, nullptr).bytes;
   return b < 256 ? 256 : b;
 }
 
@@ -384,11 +409,31 @@ int32_t cofree_layer_fwd(const cofree_partition* part, const cofree_masks* masks
   return COFREE_OK;
 }
 
-int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks, int32_t mask_id,
+}  // extern "C"
+
+// Launches the first `before` sums by themselves where one of the others goes to the same memory.
+static int32_t sums_of_one_launch(SplitSums* sums, int32_t before, hipStream_t s) {
+  auto last = [](const SplitSum& j) { return j.C + (int64_t)(j.rows - 1) * j.ldc + j.cols; };
+  bool meet = false;
+  for (int32_t a = 0; a < before; ++a)
+    for (int32_t b = before; b < sums->n; ++b)
+      meet = meet || (sums->job[a].C < last(sums->job[b]) && sums->job[b].C < last(sums->job[a]));
+  if (!meet) return COFREE_OK;
+  SplitSums first = *sums;
+  first.n = before;
+  COFREE_TRY(launch_split_sums(first, s));
+  for (int32_t b = before; b < sums->n; ++b) sums->job[b - before] = sums->job[b];
+  sums->n -= before;
+  return COFREE_OK;
+}
+
+// One layer's backward pass, which leaves its weight and bias gradients as partials in `sums`.  partials: the part of the
+// workspace that they go to, null where they follow the layer's scratch.
+static int32_t layer_bwd(const cofree_partition* part, const cofree_masks* masks, int32_t mask_id,
                          const cofree_layer_desc* desc, const void* H_in, const void* H_out,
                          const cofree_layer_params* params, const cofree_layer_saved* saved, const void* dH_out,
-                         void* dH_in, const cofree_layer_grads* grads, int32_t accumulate, void* workspace,
-                         size_t workspace_bytes, void* stream) {
+                         void* dH_in, const cofree_layer_grads* grads, void* workspace, size_t workspace_bytes,
+                         Carver* partials, SplitSums* sums, hipStream_t s) {
   COFREE_TRY(check_desc(desc));
   const cofree_layer_desc& d = *desc;
   DeviceGraph g;
@@ -396,9 +441,9 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
   COFREE_REQUIRE(H_in && H_out && params && saved && dH_out && grads && workspace, "layer_bwd: NULL argument");
   COFREE_REQUIRE(params->W && grads->W && grads->bW, "layer_bwd: W / grads.W / grads.bW is NULL");
   const int64_t n = g.n;
-  const BwdPlan p = plan_bwd(d, n, workspace);
-  if (workspace_bytes < p.bytes) return fail(COFREE_ENOMEM, "layer_bwd: workspace too small");
-  hipStream_t s = (hipStream_t)stream;
+  Carver scratch(workspace);
+  const BwdPlan p = plan_bwd(d, n, scratch, partials ? *partials : scratch);
+  if (workspace_bytes < scratch.used) return fail(COFREE_ENOMEM, "layer_bwd: workspace too small");
   const int32_t dt = d.dtype;
   auto gemm = [&]() {
     GemmArgs a;
@@ -413,9 +458,6 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
     a.dtype = dt;
     return a;
   };
-  // the weight and bias gradients leave partials, which the layer's last launch sums
-  SplitSums sums;
-  sums.accumulate = accumulate ? 1 : 0;
   auto wgrad = [&](const void* A, int32_t N1, const void* B, int32_t N2, float* C, int64_t ldc, float* ws) {
     WgradArgs a;
     a.dtype = dt;
@@ -449,7 +491,7 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
                             : wgrad(dP, d.d_out, H_in, d.d_in, grads->U + d.d_msg, ldu, p.wg[0]);
     if (merged_dU) u.B2 = H_in, u.ldb2 = u.N2b = d.d_in;
     u.colsum_out = grads->bU;
-    COFREE_TRY(launch_wgrad(u, &sums, s2));
+    COFREE_TRY(launch_wgrad(u, sums, s2));
     if (sage_combine_first(d)) {
       // forward was mean(Z U_a^T): dT = mean^T(dP) on d_out columns, dU_a = dT^T Z,
       // dZ = [Z > 0] * (dT U_a)
@@ -457,7 +499,7 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
       t.X = dP; t.Y = p.dA; t.width = d.d_out; t.ldx = t.ldy = d.d_out;
       t.in_scale = g.inv_deg;
       COFREE_TRY(launch_aggregate(t, s));
-      COFREE_TRY(launch_wgrad(wgrad(p.dA, d.d_out, Z, d.d_msg, grads->U, ldu, p.wg[1]), &sums, s));
+      COFREE_TRY(launch_wgrad(wgrad(p.dA, d.d_out, Z, d.d_msg, grads->U, ldu, p.wg[1]), sums, s));
       GemmArgs z = gemm();
       z.A1 = p.dA; z.lda1 = d.d_out; z.K1 = d.d_out;
       z.B = params->U; z.ldb = ldu; z.b_kmajor = 1;
@@ -467,7 +509,7 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
     } else {
       // dU_a = dP^T A (side stream as well)
       if (!merged_dU)
-        COFREE_TRY(launch_wgrad(wgrad(dP, d.d_out, A, d.d_msg, grads->U, ldu, p.wg[1]), &sums, s2));
+        COFREE_TRY(launch_wgrad(wgrad(dP, d.d_out, A, d.d_msg, grads->U, ldu, p.wg[1]), sums, s2));
       // dA / deg = (dP U_a) scaled per destination row, so that the transposed mean is a plain pull
       GemmArgs a = gemm();
       a.A1 = dP; a.lda1 = d.d_out; a.K1 = d.d_out;
@@ -484,7 +526,7 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
     // dW = dZ^T H, dbW = column sums of dZ
     WgradArgs w = wgrad(p.dZ, d.d_msg, H_in, d.d_in, grads->W, d.d_in, p.wg[2]);
     w.colsum_out = grads->bW;
-    COFREE_TRY(launch_wgrad(w, &sums, s));
+    COFREE_TRY(launch_wgrad(w, sums, s));
     if (dH_in) {
       // dH = dP U_s + dZ W: one product over the two k-segments [dP | dZ], each with its own parameters
       GemmArgs h = gemm();
@@ -495,8 +537,7 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
       h.C = dH_in; h.ldc = d.d_in; h.N = d.d_in;
       COFREE_TRY(launch_gemm(h, s));
     }
-    COFREE_TRY(joiner.finish());
-    return launch_split_sums(sums, s);
+    return joiner.finish();
   }
 
   // GCN and conventional GraphSAGE: dPre = dH_out gated by the activation and the dropout mask
@@ -524,12 +565,12 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
       w.B2 = saved->A, w.ldb2 = w.N2b = d.d_in;
     }
     w.colsum_out = grads->bW;
-    COFREE_TRY(launch_wgrad(w, &sums, s2));
+    COFREE_TRY(launch_wgrad(w, sums, s2));
     const bool transform_first = conv_transform_first(d);
     if (!transform_first) COFREE_REQUIRE(saved->A, "layer_bwd: saved.A is NULL");
     // dW_neigh = dPre^T M where the forward pass has kept M = mean(H) (side stream as well)
     if (!transform_first && !merged_dW)
-      COFREE_TRY(launch_wgrad(wgrad(dPre, d.d_out, saved->A, d.d_in, grads->W + d.d_in, ldw, p.wg[1]), &sums, s2));
+      COFREE_TRY(launch_wgrad(wgrad(dPre, d.d_out, saved->A, d.d_in, grads->W + d.d_in, ldw, p.wg[1]), sums, s2));
     if (transform_first || (dH_in && conv_gathers_grad(d))) {
       AggArgs t = agg();  // dT = mean^T(dPre)
       t.X = dPre; t.Y = p.T; t.width = d.d_out; t.ldx = t.ldy = d.d_out;
@@ -537,7 +578,7 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
       COFREE_TRY(launch_aggregate(t, s));
       // forward was mean(H W_neigh^T): dW_neigh = dT^T H
       if (transform_first)
-        COFREE_TRY(launch_wgrad(wgrad(p.T, d.d_out, H_in, d.d_in, grads->W + d.d_in, ldw, p.wg[1]), &sums, s));
+        COFREE_TRY(launch_wgrad(wgrad(p.T, d.d_out, H_in, d.d_in, grads->W + d.d_in, ldw, p.wg[1]), sums, s));
       if (dH_in) {
         GemmArgs h = gemm();
         // W_self and W_neigh are column blocks of W: dH = dT W_neigh + dPre W_self is one product over the
@@ -569,8 +610,7 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
       self.gate = in_gate; self.ldg = d.d_in; self.gate_last = 1; self.gate_scale = in_scale;
       COFREE_TRY(launch_gemm(self, s));
     }
-    COFREE_TRY(joiner.finish());
-    return launch_split_sums(sums, s);
+    return joiner.finish();
   }
   if (gcn_transform_first(d)) {
     // forward was Ahat (H W^T): dT = Ahat dPre, dW = dT^T H, dH = dT W
@@ -582,7 +622,7 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
     w.colsum_out = grads->bW;  // db = column sums of dPre, which dW does not read
     w.colsum_src = dPre;
     w.colsum_workspace = p.cs;
-    COFREE_TRY(launch_wgrad(w, &sums, s));
+    COFREE_TRY(launch_wgrad(w, sums, s));
     if (dH_in) {
       GemmArgs h = gemm();
       h.A1 = p.T; h.lda1 = d.d_out; h.K1 = d.d_out;
@@ -596,7 +636,7 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
     COFREE_REQUIRE(saved->A, "layer_bwd: saved.A is NULL");
     WgradArgs w = wgrad(dPre, d.d_out, saved->A, d.d_in, grads->W, d.d_in, p.wg[0]);
     w.colsum_out = grads->bW;
-    COFREE_TRY(launch_wgrad(w, &sums, s2));
+    COFREE_TRY(launch_wgrad(w, sums, s2));
     if (dH_in) {
       GemmArgs h = gemm();
       h.A1 = dPre; h.lda1 = d.d_out; h.K1 = d.d_out;
@@ -611,8 +651,30 @@ int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks
       COFREE_TRY(launch_aggregate(a, s));
     }
   }
-  COFREE_TRY(joiner.finish());
-  return launch_split_sums(sums, s);
+  return joiner.finish();
+}
+
+extern "C" {
+
+int32_t cofree_layer_bwd(const cofree_partition* part, const cofree_masks* masks, int32_t mask_id,
+                         const cofree_layer_desc* desc, const void* H_in, const void* H_out,
+                         const cofree_layer_params* params, const cofree_layer_saved* saved, const void* dH_out,
+                         void* dH_in, const cofree_layer_grads* grads, int32_t accumulate, void* workspace,
+                         size_t workspace_bytes, void* stream) {
+  SplitSums sums;
+  sums.accumulate = accumulate ? 1 : 0;
+  COFREE_TRY(layer_bwd(part, masks, mask_id, desc, H_in, H_out, params, saved, dH_out, dH_in, grads, workspace, workspace_bytes,
+                       nullptr, &sums, (hipStream_t)stream));
+  return launch_split_sums(sums, (hipStream_t)stream);
+}
+
+size_t cofree_layers_workspace_bytes(const cofree_layer_desc* descs, int32_t n_layers, int64_t n_nodes) {
+  if (!descs || n_layers < 1 || n_nodes < 0) return 0;
+  size_t b = 256;
+  for (int32_t l = 0; l < n_layers; ++l)
+    b = max3(b, plan_fwd(descs[l], n_nodes, nullptr).bytes, bwd_bytes(descs[l], n_nodes));
+  const Deferral f = plan_deferral(n_layers, n_nodes, [&](int32_t l) { return descs[l]; });
+  return f.worth ? max2(b, f.scratch + f.partials) : b;
 }
 
 int32_t cofree_layers_fwd(const cofree_partition* part, const cofree_masks* masks, int32_t mask_id,
@@ -631,12 +693,29 @@ int32_t cofree_layers_bwd(const cofree_partition* part, const cofree_masks* mask
                           const cofree_layer_call* layers, int32_t n_layers, int32_t accumulate, void* workspace,
                           size_t workspace_bytes, void* stream) {
   COFREE_REQUIRE(n_layers >= 0 && (n_layers == 0 || layers), "layers_bwd: bad layer list");
-  for (int32_t l = n_layers - 1; l >= 0; --l) {
+  if (n_layers == 0) return COFREE_OK;
+  hipStream_t s = (hipStream_t)stream;
+  for (int32_t l = 0; l < n_layers; ++l) COFREE_TRY(check_desc(&layers[l].desc));
+  DeviceGraph g;
+  COFREE_TRY(select_graph(part, masks, mask_id, &g));
+  const Deferral f = plan_deferral(n_layers, g.n, [&](int32_t l) { return layers[l].desc; });
+  const bool defer = f.worth && workspace && workspace_bytes >= f.scratch + f.partials;
+  Carver partials(defer ? (char*)workspace + f.scratch : nullptr);
+  SplitSums sums;
+  sums.accumulate = accumulate ? 1 : 0;
+  int32_t rc = COFREE_OK;
+  for (int32_t l = n_layers - 1; l >= 0 && rc == COFREE_OK; --l) {
     const cofree_layer_call& c = layers[l];
-    COFREE_TRY(cofree_layer_bwd(part, masks, mask_id, &c.desc, c.H_in, c.H_out, &c.params, &c.saved, c.dH_out, c.dH_in,
-                                &c.grads, accumulate, workspace, workspace_bytes, stream));
+    const int32_t before = sums.n;
+    rc = layer_bwd(part, masks, mask_id, &c.desc, c.H_in, c.H_out, &c.params, &c.saved, c.dH_out, c.dH_in, &c.grads, workspace,
+                   workspace_bytes, defer ? &partials : nullptr, &sums, s);
+    if (rc != COFREE_OK) sums.n = before;
+    COFREE_TRY(sums_of_one_launch(&sums, before, s));  // layers that share a gradient are summed one after the other
+    if (defer && l > 0 && rc == COFREE_OK && sums.n + SplitSums::PER_LAYER <= SplitSums::MAX) continue;
+    COFREE_TRY(launch_split_sums(sums, s));
+    sums.n = 0;
   }
-  return COFREE_OK;
+  return rc;
 }
 
 }  // extern "C"

@@ -152,10 +152,7 @@ class PartitionRunner:
         self._calls = (B.LayerCall * L)()
         self._calls_for = None   # settings the descriptors in _calls were made from
         self.loss = torch.zeros(1, dtype=torch.float32, device=device)
-        ws = B.loss_workspace_bytes()
-        for l in range(L):
-            d = self.desc(l, 0)
-            ws = max(ws, B.layer_workspace_bytes(d, n, False), B.layer_workspace_bytes(d, n, True))
+        ws = max(B.loss_workspace_bytes(), B.layers_workspace_bytes([self.desc(l, 0) for l in range(L)], n))
         self.workspace = pool.raw("workspace", ws) if pool is not None else torch.empty(ws, dtype=torch.uint8,
                                                                                         device=device)
 
