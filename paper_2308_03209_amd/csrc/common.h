@@ -402,6 +402,12 @@ size_t split_param_bytes(int32_t N, int64_t K1, int64_t K2);  // scratch for the
 int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream);
 bool wgrad_split_fits(const WgradArgs& a);
 int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
+// float32 products of at most 64 columns, weight gradients of at most 64 rows or columns (gemm_narrow.hip)
+bool gemm_narrow_fits(const GemmArgs& a);
+int32_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream);
+bool wgrad_narrow_fits(int32_t N1, int32_t N2, int32_t N2b);
+size_t wgrad_narrow_workspace_floats(int32_t N1, int32_t N2, int32_t N2b, int64_t M);
+int32_t launch_wgrad_narrow(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
 int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream);
 // bfloat16 products whose parameters fit LDS (gemm_bf16_resident.hip)
 bool gemm_resident_fits(const GemmArgs& a);

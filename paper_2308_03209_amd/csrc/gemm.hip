@@ -1,6 +1,6 @@
 // Dense feature transforms of the layers (the W and U products of the GraphSAGE layer in
-// Section 3 and their gradients) on the fp32 matrix cores of gfx950: results of at most 64 columns (weight
-// gradients: 64 rows or columns) and the shapes that gemm_split.hip leaves out.
+// Section 3 and their gradients) on the fp32 matrix cores of gfx950: the shapes that gemm_split.hip and gemm_narrow.hip
+// leave out (a range of fewer than eight k, operands with rows gigabytes apart).
 //
 // One kernel computes a 128x128 tile of  C = sum_k Aop(i,k) * Bop(j,k)  per 256-thread block:
 // four 64-wide wavefronts in a 2x2 grid, each holding a 64x64 sub-tile as 2x2 blocks of
@@ -28,6 +28,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int BM = 128, BN = 128, BK = 16, LDS_LD = 132;  // 132 = 128 + 4 words of padding
+constexpr int AM = 2, AN = 2;  // 32x32 blocks of a wavefront's sub-tile
 
 struct GemmK {
   const float* A1;
@@ -142,15 +143,12 @@ struct MoverKContig {
 // four columns may cross the end of the row: its load window is moved left to end with the row - if
 // need be into the columns of the tile before - so the loop issues one vector load per row on every
 // path, and store() moves the elements back to their positions; columns past the edge receive
-// arbitrary finite values.  TINY is for matrices with fewer than four columns in all, where no such
-// window exists: scalar loads of clamped columns.
-template <bool TINY>
-struct MoverKMajorT {
+// arbitrary finite values.
+struct MoverKMajor {
   const float* base;  // &P[(t>>5) * ld + i0]
   int64_t ld;
   int32_t start;   // first column of the load window relative to i0 (negative: reaches into the tile before)
   int32_t shift;   // the thread's column c is element c + shift of the window (0 unless moved)
-  int32_t ic[4];   // TINY: clamped column of each element
   bool edge;
   __device__ void init(const float* P, int64_t ld_, int64_t extent, int64_t i0, int tid) {
     ld = ld_;
@@ -162,19 +160,8 @@ struct MoverKMajorT {
     if (start > last - 3) start = last - 3;
     shift = i - start;
     if (shift > 3) shift = 0;  // all four columns are past the edge
-#pragma unroll
-    for (int c = 0; c < 4; ++c) ic[c] = i + c < last ? i + c : last;
   }
-  __device__ void load_row(const float* row, float4u& x) const {
-    if constexpr (TINY) {
-      x[0] = row[ic[0]];
-      x[1] = row[ic[1]];
-      x[2] = row[ic[2]];
-      x[3] = row[ic[3]];
-    } else {
-      x = *reinterpret_cast<const float4u*>(row + start);
-    }
-  }
+  __device__ void load_row(const float* row, float4u& x) const { x = *reinterpret_cast<const float4u*>(row + start); }
   __device__ void load(int64_t k0, float4u& x0, float4u& x1) const {
     const float* r = base + k0 * ld;
     load_row(r, x0);
@@ -192,12 +179,10 @@ struct MoverKMajorT {
   }
   __device__ float4 unshift(const float4u& w) const {
     float4 x = make_float4(w[0], w[1], w[2], w[3]);
-    if constexpr (!TINY) {
-      if (edge) {
-        if (shift == 1) x = make_float4(w[1], w[2], w[3], w[3]);
-        if (shift == 2) x = make_float4(w[2], w[3], w[3], w[3]);
-        if (shift == 3) x = make_float4(w[3], w[3], w[3], w[3]);
-      }
+    if (edge) {
+      if (shift == 1) x = make_float4(w[1], w[2], w[3], w[3]);
+      if (shift == 2) x = make_float4(w[2], w[3], w[3], w[3]);
+      if (shift == 3) x = make_float4(w[3], w[3], w[3], w[3]);
     }
     return x;
   }
@@ -208,8 +193,7 @@ struct MoverKMajorT {
   }
 };
 
-// 16 k-steps of one LDS tile pair on a wavefront's sub-tile of AM x AN blocks of 32x32 (2x2: 32 MFMAs).
-template <int AM, int AN>
+// 16 k-steps of one LDS tile pair on a wavefront's sub-tile of AM x AN blocks of 32x32 (32 MFMAs).
 __device__ inline void compute_tile(const float* __restrict__ as, const float* __restrict__ bs,
                                     floatx16 (&acc)[AM][AN], int g) {
 #pragma unroll
@@ -243,7 +227,7 @@ __device__ inline void compute_tile(const float* __restrict__ as, const float* _
 // a store waits for its own slot only.  LDS is double-buffered with one barrier per tile: tile t is stored,
 // the barrier passes, tile t is multiplied, and the store of tile t+1 goes to the other buffer, which
 // every wavefront stopped reading before that barrier.
-template <int D, int AM, int AN, typename MA, typename MB>
+template <int D, typename MA, typename MB>
 __device__ inline void run_range_deep(const MA& ma, const MB& mb, int64_t k_len, float (&As)[2][BK * LDS_LD],
                                       float (&Bs)[2][BK * LDS_LD], floatx16 (&acc)[AM][AN], int tid,
                                       bool do_colsum, float& colsum) {
@@ -274,7 +258,7 @@ __device__ inline void run_range_deep(const MA& ma, const MB& mb, int64_t k_len,
         mb.load(tn * BK, rb[s][0], rb[s][1]);
       }
       __syncthreads();
-      compute_tile<AM, AN>(at + a_off, bt + b_off, acc, g);
+      compute_tile(at + a_off, bt + b_off, acc, g);
       add_colsum(at);
     };
 #pragma unroll
@@ -300,7 +284,7 @@ __device__ inline void run_range_deep(const MA& ma, const MB& mb, int64_t k_len,
     ma.store(at, tid, ra[0][0], ra[0][1]);
     mb.store(bt, tid, rb[0][0], rb[0][1]);
     __syncthreads();
-    compute_tile<AM, AN>(at + a_off, bt + b_off, acc, g);
+    compute_tile(at + a_off, bt + b_off, acc, g);
     add_colsum(at);
   }
 }
@@ -310,16 +294,9 @@ __device__ inline void run_range_deep(const MA& ma, const MB& mb, int64_t k_len,
 constexpr int WGRAD_DEPTH = 2;
 constexpr int NT_DEPTH = 2;
 
-// TINY: a k-major operand has fewer than four columns (see MoverKMajorT).
-// NARROW: 0 = 128x128 block tile (wavefronts 2x2, each 64x64); 1 = 128x64 for outputs of at most 64 columns
-// (each wavefront 64x32); 2 = 64x128 for at most 64 rows (each 32x64).  The narrow forms move the same
-// 128-wide operand tiles - the clamped rows past the matrix edge repeat its last row - and only skip the
-// MFMAs of the half that would never be stored (a 41-column product otherwise spends two thirds of its
-// matrix instructions on padding).
-template <bool A_KMAJOR, bool B_KMAJOR, bool TINY, int NARROW>
+template <bool A_KMAJOR, bool B_KMAJOR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void gemm_kernel(const GemmK p) {
-  constexpr int AM = NARROW == 2 ? 1 : 2, AN = NARROW == 1 ? 1 : 2;  // 32x32 blocks per wavefront
-  constexpr int TM = 64 * AM, TN = 64 * AN;                          // block tile
+  constexpr int TM = BM, TN = BN;  // block tile
   // operand tiles during the k loop; afterwards the same memory stages the result tile
   constexpr int STAGE_LD = 68;  // floats per staged row: 64 + 4 of padding
   constexpr int SMEM_FLOATS = 4 * BK * LDS_LD > 4 * 32 * STAGE_LD ? 4 * BK * LDS_LD : 4 * 32 * STAGE_LD;
@@ -378,11 +355,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
       if constexpr (!B_KMAJOR) {
         MoverKContig mb;
         mb.init(B, ldb, p.N, j0, tid);
-        run_range_deep<NT_DEPTH, AM, AN>(ma, mb, k_len, As, Bs, acc, tid, false, no_colsum);
+        run_range_deep<NT_DEPTH>(ma, mb, k_len, As, Bs, acc, tid, false, no_colsum);
       } else {
-        MoverKMajorT<TINY> mb;
+        MoverKMajor mb;
         mb.init(B, ldb, p.N, j0, tid);
-        run_range_deep<NT_DEPTH, AM, AN>(ma, mb, k_len, As, Bs, acc, tid, false, no_colsum);
+        run_range_deep<NT_DEPTH>(ma, mb, k_len, As, Bs, acc, tid, false, no_colsum);
       }
     };
     // one loop body for both K-segments (two inlined copies would each claim their own accumulators)
@@ -408,7 +385,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
     const int64_t k_len = k_end > k_beg ? k_end - k_beg : 0;
     const float* A = p.A1 + k_beg * p.lda1;
     if (k_len > 0) {
-      MoverKMajorT<TINY> ma, mb;
+      MoverKMajor ma, mb;
       ma.init(A, p.lda1, p.M, i0, tid);
       if (p.n_split > 0 && j0 >= p.n_split)  // a column tile of the second matrix (uniform over the block)
         mb.init(p.B2 + k_beg * p.ldb2, p.ldb2, p.N - p.n_split, j0 - p.n_split, tid);
@@ -416,7 +393,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
         mb.init(p.B + k_beg * p.ldb, p.ldb, p.n_split > 0 ? p.n_split : p.N, j0, tid);
       float csum = 0.f;
       const bool do_colsum = p.colsum_part != nullptr && j0 == 0;
-      run_range_deep<WGRAD_DEPTH, AM, AN>(ma, mb, k_len, As, Bs, acc, tid, do_colsum, csum);
+      run_range_deep<WGRAD_DEPTH>(ma, mb, k_len, As, Bs, acc, tid, do_colsum, csum);
       if (do_colsum && tid < TM && i0 + tid < p.M) p.colsum_part[z * p.M + i0 + tid] = csum;
     } else if (p.colsum_part != nullptr && j0 == 0 && tid < TM && i0 + tid < p.M) {
       p.colsum_part[z * p.M + i0 + tid] = 0.f;
@@ -652,7 +629,8 @@ int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
                  "dense: ldb too small");
   if (a.M == 0) return COFREE_OK;
   if (gemm_split_fits(a)) return launch_gemm_split(a, stream);
-  if (a.dropout.q > 0.f) return fail(COFREE_EINVAL, "internal: no dropout in narrow products");
+  if (a.dropout.q > 0.f) return fail(COFREE_EINVAL, "internal: no dropout in these products");
+  if (gemm_narrow_fits(a)) return launch_gemm_narrow(a, stream);
   GemmK p{};
   p.A1 = (const float*)a.A1;
   p.lda1 = a.lda1;
@@ -680,8 +658,7 @@ int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
   p.relu_last = a.relu_last;
   p.gate_last = a.gate_last;
   p.gate_scale = a.gate ? a.gate_scale : 1.f;
-  const bool narrow = a.N <= 64;  // one 128x64 tile per row panel
-  p.tiles_n = narrow ? 1 : (a.N + BN - 1) / BN;
+  p.tiles_n = (a.N + BN - 1) / BN;
   p.tiles_m = 1;
   p.n_groups = (a.M + BM - 1) / BM;
   const int64_t blocks = ((p.n_groups + 7) / 8) * 8 * p.tiles_n;
@@ -689,22 +666,13 @@ int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
   const double flops = 2.0 * (double)a.M * a.N * (double)p.K;
   const double bytes = 4.0 * ((double)a.M * p.K + (double)a.N * p.K + (double)a.M * a.N * (a.accumulate ? 2 : 1));
   char pname[96] = "";  // the template instance launched below, then the shape
-  if (profiling()) snprintf(pname, sizeof(pname), "gemm_kernel<false,%s,%s,%d> N=%d K=%d", a.b_kmajor ? "true" : "false",
-           a.b_kmajor && a.N < 4 ? "true" : "false", (a.b_kmajor && a.N < 4) || narrow ? 1 : 0, (int)a.N, (int)p.K);
+  if (profiling()) snprintf(pname, sizeof(pname), "gemm_kernel<false,%s> N=%d K=%d", a.b_kmajor ? "true" : "false", (int)a.N,
+                            (int)p.K);
   ProfScope prof(pname, stream, bytes, flops);
-  if (a.b_kmajor) {
-    if (a.N < 4)
-      gemm_kernel<false, true, true, 1><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
-    else if (narrow)
-      gemm_kernel<false, true, false, 1><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
-    else
-      gemm_kernel<false, true, false, 0><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
-  } else {
-    if (narrow)
-      gemm_kernel<false, false, false, 1><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
-    else
-      gemm_kernel<false, false, false, 0><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
-  }
+  if (a.b_kmajor)
+    gemm_kernel<false, true><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
+  else
+    gemm_kernel<false, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
   COFREE_HIP_CHECK(hipGetLastError());
   return COFREE_OK;
 }
@@ -741,7 +709,7 @@ size_t wgrad_workspace_floats(int32_t N1, int32_t first, int64_t M, int32_t N2b)
   const int32_t s32 = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_F32), s16 = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_BF16);
   const int32_t split = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_SPLIT);
   return std::max((size_t)std::max(std::max(s32, s16), split) * ((size_t)N1 * (size_t)N2 + (size_t)N1),
-                  wgrad_bf16_workspace_floats(N1, first, N2b, M));
+                  std::max(wgrad_narrow_workspace_floats(N1, first, N2b, M), wgrad_bf16_workspace_floats(N1, first, N2b, M)));
 }
 
 int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
@@ -756,6 +724,7 @@ int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
     return bf16_rows ? launch_wgrad_bf16_rows(a, sums, stream) : launch_wgrad_bf16(a, sums, stream);
   COFREE_REQUIRE(a.dtype == COFREE_F32, "wgrad: unknown dtype");
   if (wgrad_split_fits(a)) return launch_wgrad_split(a, sums, stream);
+  if (wgrad_narrow_fits(N1, a.N2, a.B2 ? a.N2b : 0)) return launch_wgrad_narrow(a, sums, stream);
   const int32_t S = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_F32);
   GemmK p{};
   p.A1 = (const float*)a.A;
@@ -776,10 +745,8 @@ int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
   if (chunk < BK) chunk = BK;
   p.k_chunk = chunk;
   p.c_split_stride = (int64_t)N1 * N2;
-  // narrow outputs: 64x128 tiles for at most 64 rows, else 128x64 for at most 64 columns
-  const int narrow = N1 <= 64 ? 2 : (N2 <= 64 ? 1 : 0);
-  p.tiles_n = narrow == 1 ? 1 : (N2 + BN - 1) / BN;
-  p.tiles_m = narrow == 2 ? 1 : (N1 + BM - 1) / BM;
+  p.tiles_n = (N2 + BN - 1) / BN;
+  p.tiles_m = (N1 + BM - 1) / BM;
   p.n_groups = S;
   float* colsum_part = a.workspace + (size_t)S * N1 * N2;
   p.colsum_part = a.colsum_out && !a.colsum_src ? colsum_part : nullptr;
@@ -787,22 +754,11 @@ int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
   const int64_t blocks = (int64_t)((S + 7) / 8) * 8 * p.tiles_m * p.tiles_n + p.extra.blocks;
   COFREE_TRY(check_grid(blocks));
   {
-    const bool tiny = N1 < 4 || (a.B2 ? a.N2b < 4 : N2 < 4);
     char pname[96] = "";
-    if (profiling()) snprintf(pname, sizeof(pname), "gemm_kernel<true,true,%s,%d> N=%dx%d", tiny && narrow ? "true" : "false", narrow,
-             (int)N1, (int)N2);
+    if (profiling()) snprintf(pname, sizeof(pname), "gemm_kernel<true,true> N=%dx%d", (int)N1, (int)N2);
     ProfScope prof(pname, stream, 4.0 * ((double)M * N1 * (p.extra.X ? 2 : 1) + (double)M * N2 + (double)N1 * N2),
                    2.0 * (double)M * N1 * N2);
-    const dim3 grid((unsigned)blocks);
-    if (narrow == 2) {
-      if (tiny) gemm_kernel<true, true, true, 2><<<grid, 256, 0, stream>>>(p);
-      else gemm_kernel<true, true, false, 2><<<grid, 256, 0, stream>>>(p);
-    } else if (narrow == 1) {
-      if (tiny) gemm_kernel<true, true, true, 1><<<grid, 256, 0, stream>>>(p);
-      else gemm_kernel<true, true, false, 1><<<grid, 256, 0, stream>>>(p);
-    } else {
-      gemm_kernel<true, true, false, 0><<<grid, 256, 0, stream>>>(p);
-    }
+    gemm_kernel<true, true><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
   }
   COFREE_HIP_CHECK(hipGetLastError());
   COFREE_TRY(add_split_sum(sums, a.workspace, p.c_split_stride, S, a.C, a.ldc, N1, N2));

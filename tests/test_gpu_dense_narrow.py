@@ -1,0 +1,105 @@
+"""Float32 products of at most 64 columns and weight gradients of at most 64 rows or columns against float64: edges of
+blocks and windows, ranges of less than one step, two segments, everything the epilogue can do, parameters beyond LDS."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2308_03209_amd import binding as B
+    return dict(B=B, torch=torch)
+
+
+def ring(B, n):
+    src = np.arange(n, dtype=np.int64)
+    return B.build_partition(n, src, (src + 1) % n, 1, 0, 3)
+
+
+def within_rounding(got, ref, mag, terms, what):
+    """A float32 sum of `terms` products: terms 2^-24 of the sum of magnitudes, and the result's own rounding."""
+    err, bound = (got.double() - ref).abs(), (terms + 4.0) * 2.0 ** -24 * mag
+    assert bool((err <= bound).all()), f"{what}: error {float((err / bound.clamp_min(1e-300)).max()):.2f} of its bound"
+
+
+# rows: less than a tile, ragged, several rounds of all workgroups; columns: windows of 1 .. 3, moved, whole; k: short,
+# one window, moved windows, whole steps, more steps than LDS holds
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (15, 2, 3), (17, 3, 15), (33, 4, 16), (1000, 5, 17), (2049, 16, 31), (300, 17, 602),
+                                   (19_717, 33, 500), (40_001, 47, 128), (5_000, 49, 129), (70_003, 64, 40), (66_000, 63, 7),
+                                   (3_000, 64, 1433), (2_100, 48, 900), (515, 9, 2600), (35_000, 20, 70), (50_000, 7, 33)])
+@pytest.mark.parametrize("relu", [False, True])
+def test_products(env, M, N, K, relu):
+    B, torch = env["B"], env["torch"]
+    print(f"[case] narrow product M={M} N={N} K={K}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, W, b = (torch.randn(*s, generator=gen, device="cuda") for s in ((M, K), (N, K), (N,)))
+    C = torch.full((M + 1, N), float("nan"), device="cuda")
+    B.dense_nt_f32(A, W, b, C[:M], relu)
+    ref = A.double() @ W.double().T + b.double()
+    within_rounding(C[:M], ref.clamp_min(0.0) if relu else ref, A.double().abs() @ W.double().abs().T + b.double().abs(), K + 1, "product")
+    assert bool(torch.isnan(C[M]).all())  # nothing behind the result
+
+
+def test_non_finite_operands_stay_in_their_rows_and_columns(env):
+    B, torch = env["B"], env["torch"]
+    print("[case] narrow product of non-finite operands", flush=True)
+    A, W = torch.rand(100, 37, device="cuda") + 0.1, torch.rand(43, 37, device="cuda") + 0.1
+    A[3, 20], A[5, 36], A[6, 0] = float("inf"), float("nan"), -float("inf")
+    W[42, 36] = float("inf")
+    C = torch.empty(100, 43, device="cuda")
+    B.dense_nt_f32(A, W, torch.zeros(43, device="cuda"), C, False)
+    ref = A.double() @ W.double().T
+    bad = ~torch.isfinite(ref)
+    assert bool((torch.isnan(C) == torch.isnan(ref)).all()) and bool((C.double() == ref)[bad & ~torch.isnan(ref)].all())
+    assert bool(torch.isfinite(C[~bad]).all())
+
+
+# Both directions of a layer on a ring, whose aggregation is a mean over neighbours: products of either order with every
+# epilogue (conventional GraphSAGE accumulates where it transforms first) and weight gradients of either narrow side.
+# The printed layer's inner ReLU cannot be switched off, so it runs where no pre-activation is within rounding of zero.
+@pytest.mark.parametrize("kind,n,d_in,d_msg,d_out",
+                         [(k, n, *d) for k in ("gcn", "sage", "sage_conv")
+                          for n, *d in [(129, 3, 2, 2), (2_000, 64, 16, 16), (5_003, 41, 33, 7), (33_000, 100, 64, 47),
+                                        (20_011, 130, 48, 63), (9_001, 12, 5, 200), (40_000, 256, 40, 1)]
+                          if k != "sage" or n <= 10_000] + [("sage", 4_001, 128, 256, 50)])
+def test_layers(env, kind, n, d_in, d_msg, d_out):
+    from oracle import dropedge as o_dropedge
+    from oracle import layers as o_layers
+    from oracle import partition as o_partition
+    from paper_2308_03209_amd import inputs
+    from util import assert_close
+    B, torch = env["B"], env["torch"]
+    print(f"[case] narrow {kind} n={n} {d_in} -> {d_msg} -> {d_out}", flush=True)
+    code = {"gcn": B.GCN, "sage": B.SAGE_MEAN, "sage_conv": B.SAGE_CONV}[kind]
+    prm = inputs.model_params(kind, [(d_in, d_msg, d_out)], random_bias=True)[0]
+    src = np.arange(n, dtype=np.int64)
+    O = o_dropedge.full_graph(o_partition.build_partition(n, src, (src + 1) % n, 1, 0, 3))
+    rng = np.random.default_rng(n + d_in)
+    H, dY = rng.standard_normal((n, d_in)).astype(np.float32), rng.standard_normal((n, d_out)).astype(np.float32)
+    desc = B.layer_desc(code, d_in, d_msg, d_out)
+    ws = torch.empty(max(B.layer_workspace_bytes(desc, n, x) for x in (False, True)), dtype=torch.uint8, device="cuda")
+    p = {k: torch.from_numpy(v).cuda() for k, v in prm.items()}
+    h, dy = torch.from_numpy(H).cuda(), torch.from_numpy(dY).cuda()
+    Y, dX = torch.full((n, d_out), float("nan"), device="cuda"), torch.full((n, d_in), float("nan"), device="cuda")
+    saved = {"Z": torch.empty((n, d_msg), device="cuda"), "A": torch.empty((n, max(d_msg, d_in)), device="cuda")}
+    g = {k: torch.full_like(v, float("nan")) for k, v in p.items()}
+    P = ring(B, n)
+    B.layer_fwd(P, None, 0, desc, h, p, Y, saved, ws)
+    B.layer_bwd(P, None, 0, desc, h, Y, p, saved, dy, dX, g, False, ws)
+    p64 = {k: v.astype(np.float64) for k, v in prm.items()}
+    if kind == "sage":
+        ref, sv = o_layers.sage_fwd(O, H, p64)
+        ref_dX, ref_g = o_layers.sage_bwd(O, p64, sv, dY)
+    elif kind == "sage_conv":
+        ref, sv = o_layers.sage_conv_fwd(O, H, p64, False)
+        ref_dX, ref_g = o_layers.sage_conv_bwd(O, p64, sv, dY)
+    else:
+        ref, sv = o_layers.gcn_fwd(O, H, p64, False)
+        ref_dX, ref_g = o_layers.gcn_bwd(O, p64, sv, dY)
+    assert_close(Y.cpu().numpy(), ref, what="H_out")
+    assert_close(dX.cpu().numpy(), ref_dX, what="dH_in")
+    for k in ref_g:
+        assert_close(g[k].cpu().numpy(), ref_g[k], what=f"d{k}")
