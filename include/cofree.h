@@ -21,8 +21,8 @@
  *    one host thread at a time.  Without it (the default) everything is enqueued on `stream`.
  *  - More environment variables override launch choices that the library otherwise makes from the
  *    shapes; results are the same to rounding order, they exist for tuning and so that tests can send small
- *    inputs through every kernel: COFREE_AGG_SLICES = 0 | 1 | 8 (aggregation: teams of lanes by the row's
- *    degree, a wavefront for every row, the same in 8 column slices), COFREE_AGG_BUCKETS = 0 (aggregation: no degree
+ *    inputs through every kernel: COFREE_AGG_SLICES = 0 | 1 | 2 | 8 (aggregation: teams of lanes by the row's
+ *    degree, a wavefront for every row, teams of a few lanes, the same in up to 8 column slices), COFREE_AGG_BUCKETS = 0 (aggregation: no degree
  *    buckets - no row is split over a workgroup and the average degree alone chooses the teams),
  *    COFREE_AGG_ENTRY_SCALE = 0 | 1 (aggregation: per-source factors gathered from the per-node vector, or read
  *    per adjacency entry next to the neighbour ids), COFREE_AGG_SLOTS = 0 (aggregation: the row kernel reads

@@ -15,9 +15,9 @@
 //    the cut, Theorem 2): a workgroup of sixteen wavefronts per (row, column panel); every wavefront sums a
 //    strided share of the neighbours, the sixteen partial rows are staged in LDS and added in wavefront order.
 //    A launch of its own over the head of the order, when the graph has such rows.
-//  * aggregate_sliced_kernel (high average degree, wide float32 rows): a wavefront per (row, column slice), slices
-//    bound to XCDs.
+//  * aggregate_sliced_kernel (high average degree): a team of lanes per row or per (row, column slice), slices bound to XCDs.
 // Which wavefront sums which neighbours is fixed by the launch shape, so results are run-to-run identical.
+#include <algorithm>
 #include <climits>
 #include <cstdio>
 #include <cstdlib>
@@ -146,7 +146,6 @@ struct AggK {
   const int32_t* order;  // the i-th team works on row order[slot0 + i] (null: row i)
   int32_t n_block, n_wave;  // row kernel: the first n_block rows get a workgroup each, the next n_wave a wavefront each
   int32_t slot0;      // first entry of `order` this launch covers (its bucket); n counts the entries from there
-  int64_t skip_from;  // rows of at least this many neighbours belong to another launch (natural-order launches)
   // row kernel on the processing-order copy of the graph: rowptr, col and in_vals are that copy's, indexed by
   // slot, and the row's own factors come per slot too (null: none, or read by row id from in_scale / out_scale)
   int by_slot;
@@ -611,66 +610,149 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4
 }
 
 // ---- XCD-affine column slices ---------------------------------------------------------------------
-// For graphs of high average degree whose matrix is far larger than one XCD's 4 MB L2: one wavefront per (row, column
-// slice of LPS lanes x 16 bytes).  Workgroups are dealt round-robin to the 8 XCDs, so workgroup b works on column
-// slice b % 8 of row group b / 8, and each XCD's L2 only ever holds one eighth of every row - eight times as many
-// (hot) rows.  The launcher sends only widths that divide into eight slices.
+// For graphs of high average degree whose matrix is far larger than one XCD's 4 MB L2.  Workgroups are dealt round-robin to
+// the 8 XCDs, so workgroup b works on column slice b % 8 (with fewer slices on slice b % slices, where the XCDs of a slice
+// share its rows), and each XCD's L2 only ever holds that part of every row - as many more (hot) rows.
+// Rows of up to AGG_BLOCK_MIN neighbours belong to LPS lanes each, so that a wavefront works on 64 / LPS rows of nearly equal
+// degree (processing order) without adding groups up at the end: a wavefront for every row and slice spent about half of its
+// instructions outside the gather (256 float32: 115k nodes, 3.5M entries 510 -> 342 us, 230k nodes, 14M entries 1645 -> 1515,
+// 9.4 TB/s of gathered rows; 256 bfloat16, which had no slices: 230k nodes 875 -> 690, 600k nodes, 15M entries 1026 -> 952).
+// Longer rows take a wavefront.  Rows that are no whole lines, or narrow ones, take the same teams without slices.
+
+// lane n of each team of LPS lanes, to all of the team (n < 8)
+template <int LPS, int N>
+__device__ inline int team_share(int x) {
+  return __builtin_amdgcn_ds_swizzle(x, (N << 5) | (LPS < 32 ? 32 - LPS : 0));
+}
+
+// Adds the neighbours of the team's row, eight at a time: a lane holds the id (and factor) of one.  In float32 each of the
+// eight has a sum of its own, added pairwise at the end, so that sums are rounded as often as with a wavefront per row (one sum
+// per two: 2-4 % faster, 2-3 % further from float64).  bfloat16 results are rounded to 2^-9 anyway and registers are dearer.
+template <typename T, int LPS, int MODE>
+__device__ inline void gather_teams(const AggK<T>& p, const T* __restrict__ X, const int32_t* __restrict__ col,
+                                    const float* __restrict__ vals, int cnt, int lane, float (&out)[RowIO<T>::WIDE]) {
+  constexpr int VEC = RowIO<T>::WIDE, UNR = 8, SUMS = VEC == 4 ? 8 : 2;
+  const int most = __builtin_amdgcn_readlane(cnt, 0), least = __builtin_amdgcn_readlane(cnt, 63);  // descending degree
+  const int last = cnt > 0 ? cnt - 1 : 0, k = lane & 7;
+  float acc[SUMS][VEC];
+#pragma unroll
+  for (int t = 0; t < SUMS; ++t)
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[t][i] = out[i] = 0.f;
+  if (most == 0) return;  // the graph may have no entry to read
+  int id = col[k < last ? k : last];
+  float f = 1.f;
+  if constexpr (MODE == 2) f = vals[k < last ? k : last];
+  for (int e = 0; e < most; e += UNR) {
+    if constexpr (MODE == 1) f = p.in_scale[id];
+    uint32_t u[UNR];
+    u[0] = team_share<LPS, 0>(id), u[1] = team_share<LPS, 1>(id), u[2] = team_share<LPS, 2>(id), u[3] = team_share<LPS, 3>(id);
+    u[4] = team_share<LPS, 4>(id), u[5] = team_share<LPS, 5>(id), u[6] = team_share<LPS, 6>(id), u[7] = team_share<LPS, 7>(id);
+    float w[UNR];
+    if constexpr (MODE != 0) {
+      const int fi = __float_as_int(f);
+      w[0] = __int_as_float(team_share<LPS, 0>(fi)), w[1] = __int_as_float(team_share<LPS, 1>(fi));
+      w[2] = __int_as_float(team_share<LPS, 2>(fi)), w[3] = __int_as_float(team_share<LPS, 3>(fi));
+      w[4] = __int_as_float(team_share<LPS, 4>(fi)), w[5] = __int_as_float(team_share<LPS, 5>(fi));
+      w[6] = __int_as_float(team_share<LPS, 6>(fi)), w[7] = __int_as_float(team_share<LPS, 7>(fi));
+    }
+    typename RowIO<T>::Raw v[UNR];
+#pragma unroll
+    for (int t = 0; t < UNR; ++t) v[t] = RowIO<T>::load_raw(row_at(X, u[t], p.ldx));
+    const int n = e + UNR + k < last ? e + UNR + k : last;  // the next batch's
+    id = col[n];
+    if constexpr (MODE == 2) f = vals[n];
+    if (e + UNR > least) {
+#pragma unroll
+      for (int t = 0; t < UNR; ++t) v[t] = RowIO<T>::keep_if(e + t < cnt, v[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < SUMS; ++t) {
+      if constexpr (SUMS == UNR) {
+        RowIO<T>::fma_raw(acc[t], MODE == 0 ? 1.f : w[t], v[t]);
+      } else {
+        float x[VEC] = {};
+#pragma unroll
+        for (int q = t; q < UNR; q += SUMS) RowIO<T>::fma_raw(x, MODE == 0 ? 1.f : w[q], v[q]);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[t][i] += x[i];
+      }
+    }
+  }
+#pragma unroll
+  for (int d = SUMS / 2; d > 0; d >>= 1)
+#pragma unroll
+    for (int t = 0; t < d; ++t)
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) acc[t][i] += acc[t + d][i];
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) out[i] = acc[0][i];
+}
+
 template <typename T, int LPS, bool DROP>
-__global__ __launch_bounds__(256) void aggregate_sliced_kernel(const AggK<T> p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 5))) void aggregate_sliced_kernel(const AggK<T> p, int slice_bits, uint32_t long_units) {
   constexpr int VEC = RowIO<T>::WIDE;
   constexpr int NG = 64 / LPS;
   constexpr int UNR = 4;
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane % LPS, grp = lane / LPS;
-  const uint32_t row = (blockIdx.x / 8u) * 4 + (threadIdx.x >> 6);  // natural order, which measured better
-  if (row >= p.n) return;
-  const int c0 = ((int)(blockIdx.x % 8u) * LPS + sub) * VEC;
+  const uint32_t xcd = blockIdx.x & 7u, unit = ((blockIdx.x >> 3) << (3 - slice_bits)) + (xcd >> slice_bits);
+  // a lane's columns: whole lines of a slice, or any row that is not cut (the last window moved, lanes past the end idle)
+  const LaneCols lc = lane_cols<VEC>(p.width, ((int)(xcd & ((1u << slice_bits) - 1u)) * LPS + sub) * VEC);
+  const int c0 = lc.avail > 0 ? lc.c0 : p.width - VEC;
   const T* __restrict__ X = p.X + c0;
-  const int32_t* __restrict__ col = p.col;
-  const float* __restrict__ in_scale = p.in_scale;
-  const float* __restrict__ in_vals = p.in_vals;
-  const int64_t beg = p.rowptr[row], end = p.rowptr[row + 1];
-  if (end - beg >= p.skip_from) return;  // a hub row: the hub launch owns it
-  float acc[VEC];
-#pragma unroll
-  for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+  const bool is_long = unit < long_units;  // uniform over the block
+  const uint32_t limit = is_long ? (uint32_t)p.n_wave : (uint32_t)p.n;
+  const uint32_t first = is_long ? unit * 4 + wave : (uint32_t)p.n_wave + ((unit - long_units) * 4 + wave) * NG;
+  if (first >= limit) return;
+  const uint32_t slot = is_long ? first : first + grp;
+  const bool has = slot < limit;
+  const uint32_t s = (uint32_t)p.slot0 + (has ? slot : limit - 1);
+  const uint32_t row = (uint32_t)p.order[s];
+  const uint32_t at = p.by_slot ? s : row;
+  const int64_t beg = p.rowptr[at];
+  const int cnt = has ? (int)(p.rowptr[at + 1] - beg) : 0;
+  const int32_t* __restrict__ col = p.col + (cnt > 0 ? beg : 0);
+  const float* __restrict__ vals = p.in_vals ? p.in_vals + (cnt > 0 ? beg : 0) : nullptr;
   RowTail<T, VEC, false> tail;
-  tail.request(p, row, 0, c0);
-  // every load of the loop is unconditional (see RowIO): ids past the end of the row repeat its last id and are
-  // zeroed after the load.  scale_mode: 0 no per-source factor, 1 gathered from the per-node vector, 2 per entry
-  auto gather = [&](auto scale_mode) {
-    constexpr int MODE = decltype(scale_mode)::value;
-    const int64_t last = end - 1;
-    for (int64_t e = beg + grp; e < end; e += NG * UNR) {
+  tail.request(p, row, s, c0);
+  float acc[VEC];
+  if (!is_long) {
+    if (vals) gather_teams<T, LPS, 2>(p, X, col, vals, cnt, lane, acc);
+    else if (p.in_scale) gather_teams<T, LPS, 1>(p, X, col, vals, cnt, lane, acc);
+    else gather_teams<T, LPS, 0>(p, X, col, vals, cnt, lane, acc);
+    if (!has || lc.avail <= 0) return;
+  } else {
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+    // every load of the loop is unconditional (see RowIO): ids past the end of the row repeat its last id and are
+    // zeroed after the load
+    for (int e = grp; e < cnt; e += NG * UNR) {
       uint32_t u[UNR];
-      float s[UNR];
+      float f[UNR];
       typename RowIO<T>::Raw v[UNR];
 #pragma unroll
       for (int t = 0; t < UNR; ++t) {
-        const int64_t ee = e + t * NG;
-        const int64_t ec = ee < last ? ee : last;
+        const int ec = e + t * NG < cnt ? e + t * NG : cnt - 1;
         u[t] = (uint32_t)col[ec];
-        if constexpr (MODE == 2) s[t] = in_vals[ec];
+        f[t] = 1.f;
+        if (vals) f[t] = vals[ec];
       }
 #pragma unroll
       for (int t = 0; t < UNR; ++t) {
-        if constexpr (MODE == 1) s[t] = in_scale[u[t]];
-        if constexpr (MODE == 0) s[t] = 1.f;
+        if (!vals && p.in_scale) f[t] = p.in_scale[u[t]];
         v[t] = RowIO<T>::load_raw(row_at(X, u[t], p.ldx));
       }
 #pragma unroll
-      for (int t = 0; t < UNR; ++t) RowIO<T>::fma_raw(acc, s[t], RowIO<T>::keep_if(e + t * NG < end, v[t]));
+      for (int t = 0; t < UNR; ++t) RowIO<T>::fma_raw(acc, f[t], RowIO<T>::keep_if(e + t * NG < cnt, v[t]));
     }
-  };
-  if (in_vals) gather(std::integral_constant<int, 2>{});
-  else if (in_scale) gather(std::integral_constant<int, 1>{});
-  else gather(std::integral_constant<int, 0>{});
 #pragma unroll
-  for (int off = LPS; off < 64; off <<= 1) {
+    for (int off = LPS; off < 64; off <<= 1) {
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
+      for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
+    }
+    if (grp != 0 || lc.avail <= 0) return;
   }
-  if (grp != 0) return;
   finish_row<T, VEC, false, DROP>(p, row, c0, VEC, acc, tail);
 }
 
@@ -814,8 +896,10 @@ static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCos
 }
 
 template <typename T, bool DROP>
-static int32_t launch_sliced(const AggK<T>& k, int lps, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
-  const int64_t blocks = ((k.n + 3) / 4) * 8;
+static int32_t launch_sliced(const AggK<T>& k, int lps, int slice_bits, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
+  const int64_t long_units = (k.n_wave + 3) / 4, rows = 4 * (64 / lps), parts = 8 >> slice_bits;
+  const int64_t units = long_units + (k.n - k.n_wave + rows - 1) / rows;
+  const int64_t blocks = (units + parts - 1) / parts * 8;
   COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
   const dim3 grid((unsigned)blocks);
   char pname[96] = "";
@@ -823,10 +907,10 @@ static int32_t launch_sliced(const AggK<T>& k, int lps, hipStream_t stream, cons
            (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   switch (lps) {
-    case 8: aggregate_sliced_kernel<T, 8, DROP><<<grid, 256, 0, stream>>>(k); break;
-    case 16: aggregate_sliced_kernel<T, 16, DROP><<<grid, 256, 0, stream>>>(k); break;
-    case 32: aggregate_sliced_kernel<T, 32, DROP><<<grid, 256, 0, stream>>>(k); break;
-    case 64: aggregate_sliced_kernel<T, 64, DROP><<<grid, 256, 0, stream>>>(k); break;
+    case 8: aggregate_sliced_kernel<T, 8, DROP><<<grid, 256, 0, stream>>>(k, slice_bits, (uint32_t)long_units); break;
+    case 16: aggregate_sliced_kernel<T, 16, DROP><<<grid, 256, 0, stream>>>(k, slice_bits, (uint32_t)long_units); break;
+    case 32: aggregate_sliced_kernel<T, 32, DROP><<<grid, 256, 0, stream>>>(k, slice_bits, (uint32_t)long_units); break;
+    case 64: aggregate_sliced_kernel<T, 64, DROP><<<grid, 256, 0, stream>>>(k, slice_bits, (uint32_t)long_units); break;
     default: return fail(COFREE_EINVAL, "internal: bad lanes-per-slice");
   }
   return COFREE_OK;
@@ -881,7 +965,6 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   k.X = X;
   k.Y = Y;
   k.relu_src = R;
-  k.skip_from = INT64_MAX;
   const LaunchCost<T> cost{a, R};
 
   // Hub rows (the head of the sorted row order) get a launch of their own.  COFREE_AGG_BUCKETS = 0 leaves them - and
@@ -891,35 +974,48 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   const int64_t n_hub = buckets && a.width >= WIDE ? a.g.n_hub : 0;
   const int64_t hub_nnz = n_hub > 0 ? a.g.nnz_hub : 0;
 
-  // High average degree: a wavefront for every row.  Additionally cut into 8 XCD-affine column slices when the
-  // matrix is far larger than one XCD's 4 MB L2 and the width divides evenly into slices of at least one 128-byte
-  // cache line of float32: a gather costs a compute unit about the same per line request whatever part of the line
-  // is used, so narrower slices only multiply the requests (230k x 128 float32, average degree 61: 1.35 ms in
-  // 64-byte slices, 0.87 ms unsliced), and for bfloat16 rows the unsliced kernel measured faster at every width
-  // (512 wide: 1.73 against 2.13 ms).
-  const int slice_unit = 8 * WIDE;  // 8 slices of at least one 16-byte lane each
+  // High average degree: teams of lanes per row in wavefronts of rows of nearly equal degree (aggregate_sliced_kernel), cut into
+  // up to 8 XCD-affine column slices of whole 128-byte lines, two at least; else a wavefront for every row.
+  //  * Slices, of rows of four lines and more from a matrix of one XCD's 4 MB L2 on (8k nodes, 300k entries, 256 float32 30 -> 22 us;
+  //    115k nodes, 3.5M entries 472 -> 344; 230k nodes, 14M entries 1870 -> 1519), of two lines from 12 MB on (60k nodes, 2M
+  //    entries, 128 bfloat16 60 -> 52; at 7.7 MB 27 -> 30), up to 350 MB: beyond the memory-side cache their pieces of rows cost
+  //    more than the hits are worth (600k nodes, 15M entries, 128 float32, 307 MB: 946 against 986; 256 float32 2219 against 2131).
+  //  * Without slices, rows of up to 16 pieces of 16 bytes that are no whole lines or lie beyond that: a team walks a row alone, so
+  //    a launch has to outlast 128 neighbours - up to eight pieces from two million entries on (115k nodes, 3.5M entries, 47
+  //    bfloat16 112 -> 70; 600k nodes, 15M entries 547 -> 360; 60k nodes, 2M entries 64 -> 60; 20k nodes, 1.2M entries, 8
+  //    float32 16.7 -> 20.6), wider rows from eight million on (230k nodes, 14M entries, 41 float32 435 -> 397; 300k nodes, 9M
+  //    entries 330 -> 312; 115k nodes, 7M entries 175 -> 180).  Wider still, a wavefront has two rows and gains nothing (100
+  //    float32: 230k nodes, 14M entries 865 -> 803, 300k nodes, 9M entries 628 -> 643).
+  // Below an average of 16 neighbours neither is faster than the row kernel (600k nodes, 7M entries: 1.00 to 1.15 of its time).
   const bool dense_rows = a.g.nnz / a.g.n >= AGG_LONG_MIN;
-  const bool sliceable = sizeof(T) == 4 && a.width % slice_unit == 0 && a.width / slice_unit <= 64 &&
-                         ((a.width / slice_unit) & (a.width / slice_unit - 1)) == 0 && a.width / slice_unit >= 8;
+  const int64_t row_bytes = a.width * (int64_t)sizeof(T), lines = row_bytes / 128;
+  const double matrix = (double)a.g.n * row_bytes;
+  const int pieces = (a.width + WIDE - 1) / WIDE;
+  const bool sliceable = a.g.order != nullptr && lines * 128 == row_bytes && lines >= 2 && lines <= 64 && (lines & (lines - 1)) == 0;
+  const bool teamable = a.g.order != nullptr && a.width >= WIDE && pieces <= 32;
   bool waves = dense_rows;
-  bool sliced = dense_rows && sliceable && (double)a.g.n * a.width * sizeof(T) > 32e6;
-  if (const char* env = getenv("COFREE_AGG_SLICES")) {  // 0 = teams by degree, 1 = a wavefront per row, 8 = sliced
+  bool sliced = dense_rows && sliceable && matrix >= (lines >= 4 ? 4e6 : 12e6) && matrix <= 350e6;
+  bool teams = dense_rows && teamable && !sliced && pieces <= 16 && a.g.nnz >= (pieces <= 8 ? 1 << 21 : 1 << 23);
+  if (const char* env = getenv("COFREE_AGG_SLICES")) {  // 0 = by degree, 1 = a wavefront per row, 2 = teams, 8 = sliced
     const int v = atoi(env);
-    if (v == 0 || v == 1) {
-      waves = v == 1;
-      sliced = false;
-    }
-    if (v == 8) sliced = sliceable;
+    if (v == 0 || v == 1) waves = v == 1, sliced = teams = false;
+    if (v == 2) sliced = false, teams = teamable;
+    if (v == 8) sliced = sliceable, teams = false;
+  }
+  int slice_bits = lines >= 8 ? 3 : lines == 4 ? 2 : 1, team_lanes = (int)(lines * 8 >> slice_bits);
+  if (teams) {
+    slice_bits = 0, team_lanes = 8;
+    while (team_lanes < pieces) team_lanes *= 2;
   }
 
   // Per-source factors of a large graph are read per entry: the per-node vector no longer stays in L2 there, and
   // every neighbour's factor would cost a memory access of its own beside the row it scales (28M-node partition,
   // 256-wide bfloat16 launch: 16.7 ms with the per-node gather, 15.9 ms with the per-entry stream; no difference
-  // at 1.9M nodes), and so are those of column slices, where each of a row's eight wavefronts would gather the factors again
+  // at 1.9M nodes), and so are those of teams, which read them with the ids, and of slices, each of which would gather them again
   // (115k nodes, 3.5M entries, 256-wide float32: with the gather a four-layer training step took 5.36 ms, with the stream 5.07).  COFREE_AGG_ENTRY_SCALE = 0 / 1 forces one or the other.
   k.in_vals = nullptr;
   if (a.in_scale) {
-    bool per_entry = sliced || a.g.n >= AGG_ENTRY_SCALE_MIN_NODES;
+    bool per_entry = sliced || teams || a.g.n >= AGG_ENTRY_SCALE_MIN_NODES;
     if (const char* env = getenv("COFREE_AGG_ENTRY_SCALE")) per_entry = atoi(env) != 0;
     if (per_entry && a.in_scale == a.g.inv_deg) k.in_vals = a.g.val_inv_deg;
     if (per_entry && a.in_scale == a.g.gcn_norm) k.in_vals = a.g.val_gcn_norm;
@@ -931,18 +1027,6 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
     k.slot0 = 0;
     k.n = n_hub;
     COFREE_TRY((launch_hub<T, DROP>(k, stream, cost, a.g.nnz_hub)));
-  }
-  if constexpr (sizeof(T) == 4) {
-    if (sliced) {
-      // 2a. every other row in natural order: hub rows are met and skipped
-      k.order = nullptr;
-      k.slot0 = 0;
-      k.n = a.g.n;
-      k.skip_from = n_hub > 0 ? AGG_HUB_MIN : INT64_MAX;
-      COFREE_TRY((launch_sliced<T, DROP>(k, a.width / slice_unit, stream, cost, a.g.nnz - hub_nnz)));
-      COFREE_HIP_CHECK(hipGetLastError());
-      return COFREE_OK;
-    }
   }
   // 2b. every other row, order[n_hub ..)
   if (n_hub == a.g.n) {
@@ -975,6 +1059,13 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
     if (a.in_scale == a.g.gcn_norm) k.in_scale_slot = a.g.s_gcn_norm;
     if (a.out_scale == a.g.inv_deg) k.out_scale_slot = a.g.s_inv_deg;
     if (a.out_scale == a.g.gcn_norm) k.out_scale_slot = a.g.s_gcn_norm;
+  }
+  if (sliced || teams) {
+    k.n_block = 0;
+    k.n_wave = (int32_t)(std::max(a.g.n_block, n_hub) - n_hub);  // longer rows are never left to a team
+    COFREE_TRY((launch_sliced<T, DROP>(k, team_lanes, slice_bits, stream, cost, a.g.nnz - hub_nnz)));
+    COFREE_HIP_CHECK(hipGetLastError());
+    return COFREE_OK;
   }
   const int panel = ROW_PIECES * WIDE;  // columns one launch covers
   for (int c0 = 0; c0 < a.width; c0 += panel) {

@@ -39,6 +39,30 @@ def test_a_wavefront_for_every_row(env, dtype, width, monkeypatch):
     check(env, dtype, width, False)
 
 
+# without slices any width of 1 to 32 pieces, with slices 2 to 64 whole lines of 128 bytes (other widths take another kernel)
+@pytest.mark.parametrize("launch,dtype,width",
+                         [("2", "f32", w) for w in (4, 5, 31, 32, 33, 64, 100, 128)] + [("2", "bf16", w) for w in (8, 9, 47, 64, 100, 172, 256)] +
+                         [("8", "f32", w) for w in (64, 128, 256, 512, 1024, 2048)] + [("8", "bf16", w) for w in (128, 256, 512, 1024, 4096)])
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("slots", ["0", "1"])
+def test_teams_of_equal_rows_and_column_slices(env, launch, dtype, width, masked, slots, monkeypatch):
+    """As in graphs of high average degree; the last wavefront has lanes without a row and rows without neighbours."""
+    monkeypatch.setenv("COFREE_AGG_SLICES", launch)
+    monkeypatch.setenv("COFREE_AGG_SLOTS", slots)
+    check(env, dtype, width, masked)
+
+
+@pytest.mark.parametrize("launch", ["2", "8"])
+def test_teams_on_a_mask_that_drops_everything(env, launch, monkeypatch):
+    B, torch = env["B"], env["torch"]
+    monkeypatch.setenv("COFREE_AGG_SLICES", launch)
+    masks = B.dropedge_k(env["P"], 1, 1.0 - 2.0 ** -31, 3)
+    assert len(masks.host_graph(0)[1]) == 0
+    X, Y = torch.ones(env["P"].num_nodes, 128, device="cuda"), torch.full((env["P"].num_nodes, 128), float("nan"), device="cuda")
+    B.aggregate(env["P"], masks, 0, B.AGG_GCN, X, Y, 128, B.F32)
+    assert torch.equal(Y, X)
+
+
 def check(env, dtype, width, masked):
     B, torch, P, O = env["B"], env["torch"], env["P"], env["O"]
     print(f"[case] row teams dtype={dtype} width={width} masked={masked}", flush=True)
