@@ -388,6 +388,7 @@ struct WgradArgs {
   float* colsum_workspace = nullptr;
 };
 int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
+int32_t launch_wgrads(const WgradArgs& a, const WgradArgs& b, SplitSums* sums, hipStream_t stream);  // one after the other, or paired
 size_t wgrad_workspace_floats(int32_t N1, int32_t N2, int64_t M, int32_t N2b = 0);
 size_t colsum_workspace_floats(int32_t N);
 // shared by the kernels; resident = workgroups of the kernel the chip holds at once (float32: three per CU; bfloat16:
@@ -407,7 +408,8 @@ bool gemm_narrow_fits(const GemmArgs& a);
 int32_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream);
 bool wgrad_narrow_fits(int32_t N1, int32_t N2, int32_t N2b);
 size_t wgrad_narrow_workspace_floats(int32_t N1, int32_t N2, int32_t N2b, int64_t M);
-int32_t launch_wgrad_narrow(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
+int32_t launch_wgrad_narrow(const WgradArgs& a, const WgradArgs* b, SplitSums* sums, hipStream_t stream);  // b: or null
+bool wgrads_pair(const WgradArgs& a, const WgradArgs& b);  // whether both can be one launch of that
 int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream);
 // bfloat16 products whose parameters fit LDS (gemm_bf16_resident.hip)
 bool gemm_resident_fits(const GemmArgs& a);

@@ -712,19 +712,34 @@ size_t wgrad_workspace_floats(int32_t N1, int32_t first, int64_t M, int32_t N2b)
                   std::max(wgrad_narrow_workspace_floats(N1, first, N2b, M), wgrad_bf16_workspace_floats(N1, first, N2b, M)));
 }
 
-int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
+static int32_t check_wgrad(const WgradArgs& a) {
   COFREE_REQUIRE(a.A && a.B && a.C && a.workspace, "wgrad: NULL operand");
   COFREE_REQUIRE(a.N1 >= 1 && a.N2 >= 1 && a.M >= 0, "wgrad: bad shape");
   const bool bf16_rows = a.dtype == COFREE_BF16 && wgrad_bf16_fits(a.N1, a.N2, a.B2 ? a.N2b : 0);
   COFREE_REQUIRE(!a.B2 || (a.N2b >= 1 && (a.N2 % BN == 0 || bf16_rows) && a.ldb2 >= a.N2b), "wgrad: bad second matrix");
+  COFREE_REQUIRE(a.lda >= a.N1 && a.ldb >= a.N2 && a.ldc >= a.N2 + (a.B2 ? a.N2b : 0), "wgrad: leading dimension too small");
+  return COFREE_OK;
+}
+
+int32_t launch_wgrads(const WgradArgs& a, const WgradArgs& b, SplitSums* sums, hipStream_t stream) {
+  if (wgrads_pair(a, b)) {
+    COFREE_TRY(check_wgrad(a));
+    COFREE_TRY(check_wgrad(b));
+    return launch_wgrad_narrow(a, &b, sums, stream);
+  }
+  COFREE_TRY(launch_wgrad(a, sums, stream));
+  return launch_wgrad(b, sums, stream);
+}
+
+int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
+  COFREE_TRY(check_wgrad(a));
   const int32_t N1 = a.N1, N2 = a.N2 + (a.B2 ? a.N2b : 0);  // rows and columns of the result
   const int64_t M = a.M;
-  COFREE_REQUIRE(a.lda >= N1 && a.ldb >= a.N2 && a.ldc >= N2, "wgrad: leading dimension too small");
   if (a.dtype == COFREE_BF16)
-    return bf16_rows ? launch_wgrad_bf16_rows(a, sums, stream) : launch_wgrad_bf16(a, sums, stream);
+    return wgrad_bf16_fits(a.N1, a.N2, a.B2 ? a.N2b : 0) ? launch_wgrad_bf16_rows(a, sums, stream) : launch_wgrad_bf16(a, sums, stream);
   COFREE_REQUIRE(a.dtype == COFREE_F32, "wgrad: unknown dtype");
   if (wgrad_split_fits(a)) return launch_wgrad_split(a, sums, stream);
-  if (wgrad_narrow_fits(N1, a.N2, a.B2 ? a.N2b : 0)) return launch_wgrad_narrow(a, sums, stream);
+  if (wgrad_narrow_fits(N1, a.N2, a.B2 ? a.N2b : 0)) return launch_wgrad_narrow(a, nullptr, sums, stream);
   const int32_t S = wgrad_splits(N1, N2, M, WGRAD_RESIDENT_F32);
   GemmK p{};
   p.A1 = (const float*)a.A;

@@ -364,6 +364,14 @@ struct NarrowWgradK {
   ColsumK extra;
 };
 
+// Two weight gradients of one kernel instance in one launch, the second's workgroups behind the first's: a launch less, and the
+// first's last round is filled (19,717 nodes, two of 33 x 500: 43 -> 37 us, two of 3 x 33 9.5 -> 6.0; 230k nodes, two of 41 x
+// 256: 139 -> 127).
+struct NarrowPairK {
+  NarrowWgradK job[2];
+  uint32_t first_blocks;
+};
+
 template <int N>
 struct Cols {
   float v[N];
@@ -394,13 +402,16 @@ __device__ inline int window(int first, int i, int n) {
 // sums are added in wavefront order through LDS.
 constexpr int WSTEPS = 8, WGROUP = 4 * WSTEPS;
 template <int NA, int NB>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB == 4 ? 2 : 3))) void narrow_wgrad_kernel(const NarrowWgradK p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB == 4 ? 2 : 3))) void narrow_wgrad_kernel(const NarrowPairK two) {
   __shared__ __attribute__((aligned(16))) float sums[4][NA * 16 * NB * 16];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t L = blockIdx.x;
-  if (L >= (int64_t)gridDim.x - p.extra.blocks) {
-    colsum_block<float>(p.extra, L - ((int64_t)gridDim.x - p.extra.blocks), &sums[0][0], tid);
+  const int which = blockIdx.x >= two.first_blocks;
+  const NarrowWgradK& p = two.job[which];
+  const int64_t L = blockIdx.x - (which ? two.first_blocks : 0u), 
+                blocks = which ? gridDim.x - two.first_blocks : two.first_blocks;
+  if (L >= blocks - p.extra.blocks) {
+    colsum_block<float>(p.extra, L - (blocks - p.extra.blocks), &sums[0][0], tid);
     return;
   }
   // the panels of a chunk are neighbours on one XCD (ids congruent mod 8), whose L2 then holds the narrow side's rows
@@ -541,15 +552,14 @@ size_t wgrad_narrow_workspace_floats(int32_t N1, int32_t first, int32_t N2b, int
 }
 
 template <int NA, int NB>
-static int32_t launch_narrow_wgrad(const NarrowWgradK& p, int64_t blocks, hipStream_t stream) {
+static int32_t launch_narrow_wgrad(const NarrowPairK& p, int64_t blocks, hipStream_t stream) {
   narrow_wgrad_kernel<NA, NB><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
   COFREE_HIP_CHECK(hipGetLastError());
   return COFREE_OK;
 }
 
-int32_t launch_wgrad_narrow(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
+static int32_t fill_narrow(const WgradArgs& a, const NarrowPlan& q, NarrowWgradK* job, int64_t* blocks, SplitSums* sums) {
   const int32_t N2b = a.B2 ? a.N2b : 0, N1 = a.N1, N2 = a.N2 + N2b;
-  const NarrowPlan q = plan_narrow(N1, a.N2, N2b, a.M);
   NarrowWgradK p{};
   p.rows_narrow = q.rows_narrow;
   p.narrow = (const float*)(q.rows_narrow ? a.A : a.B);
@@ -570,27 +580,50 @@ int32_t launch_wgrad_narrow(const WgradArgs& a, SplitSums* sums, hipStream_t str
   float* const colsum_part = a.workspace + (size_t)q.chunks * N1 * N2;
   p.colsum_part = a.colsum_out && !a.colsum_src ? colsum_part : nullptr;
   COFREE_TRY(plan_colsum(a, &p.extra, sums));
-  const int64_t blocks = (q.chunks + 7) / 8 * 8 * q.panels + p.extra.blocks;
-  COFREE_REQUIRE(q.chunk < INT_MAX - WGROUP * 8 && blocks < INT_MAX, "wgrad: too many rows");
-  char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "narrow_wgrad_kernel<%d,%d> N=%dx%d", q.na, q.nb, (int)N1, (int)N2);
-  ProfScope prof(pname, stream, 4.0 * ((double)a.M * N1 * (p.extra.X ? 2 : 1) + (double)a.M * N2 + (double)N1 * N2),
-                 2.0 * (double)a.M * N1 * N2);
-  int32_t rc;
-  switch (q.na * 8 + q.nb) {
-    case 9: rc = launch_narrow_wgrad<1, 1>(p, blocks, stream); break;
-    case 10: rc = launch_narrow_wgrad<1, 2>(p, blocks, stream); break;
-    case 11: rc = launch_narrow_wgrad<1, 3>(p, blocks, stream); break;
-    case 12: rc = launch_narrow_wgrad<1, 4>(p, blocks, stream); break;
-    case 33: rc = launch_narrow_wgrad<4, 1>(p, blocks, stream); break;
-    case 34: rc = launch_narrow_wgrad<4, 2>(p, blocks, stream); break;
-    case 35: rc = launch_narrow_wgrad<4, 3>(p, blocks, stream); break;
-    default: rc = launch_narrow_wgrad<4, 4>(p, blocks, stream); break;
-  }
-  COFREE_TRY(rc);
+  *blocks = (q.chunks + 7) / 8 * 8 * q.panels + p.extra.blocks;
+  COFREE_REQUIRE(q.chunk < INT_MAX - WGROUP * 8 && *blocks < INT_MAX / 2, "wgrad: too many rows");
+  *job = p;
   COFREE_TRY(add_split_sum(sums, a.workspace, (int64_t)N1 * N2, (int32_t)q.chunks, a.C, a.ldc, N1, N2));
   if (p.colsum_part) COFREE_TRY(add_split_sum(sums, colsum_part, N1, (int32_t)q.chunks, a.colsum_out, N1, 1, N1));
   return COFREE_OK;
+}
+
+static bool narrow_wgrad(const WgradArgs& a) {
+  return a.dtype == COFREE_F32 && wgrad_narrow_fits(a.N1, a.N2, a.B2 ? a.N2b : 0);
+}
+bool wgrads_pair(const WgradArgs& a, const WgradArgs& b) {
+  if (!narrow_wgrad(a) || !narrow_wgrad(b) || a.M != b.M) return false;
+  const NarrowPlan q = plan_narrow(a.N1, a.N2, a.B2 ? a.N2b : 0, a.M), r = plan_narrow(b.N1, b.N2, b.B2 ? b.N2b : 0, b.M);
+  return q.na == r.na && q.nb == r.nb;
+}
+
+int32_t launch_wgrad_narrow(const WgradArgs& a, const WgradArgs* b, SplitSums* sums, hipStream_t stream) {
+  const NarrowPlan q = plan_narrow(a.N1, a.N2, a.B2 ? a.N2b : 0, a.M);
+  NarrowPairK p{};
+  int64_t first = 0, second = 0;
+  COFREE_TRY(fill_narrow(a, q, &p.job[0], &first, sums));
+  if (b) COFREE_TRY(fill_narrow(*b, plan_narrow(b->N1, b->N2, b->B2 ? b->N2b : 0, b->M), &p.job[1], &second, sums));
+  p.first_blocks = (uint32_t)first;
+  const int64_t blocks = first + second;
+  auto bytes = [](const WgradArgs& w, const NarrowWgradK& j) {
+    const double N1 = w.N1, N2 = (double)w.N2 + (w.B2 ? w.N2b : 0), M = (double)w.M;
+    return 4.0 * (M * N1 * (j.extra.X ? 2 : 1) + M * N2 + N1 * N2);
+  };
+  auto flops = [](const WgradArgs& w) { return 2.0 * (double)w.M * w.N1 * ((double)w.N2 + (w.B2 ? w.N2b : 0)); };
+  char pname[96] = "";
+  if (profiling()) snprintf(pname, sizeof(pname), "narrow_wgrad_kernel<%d,%d> N=%dx%d%s", q.na, q.nb, (int)a.N1,
+                            (int)(a.N2 + (a.B2 ? a.N2b : 0)), b ? " and another" : "");
+  ProfScope prof(pname, stream, bytes(a, p.job[0]) + (b ? bytes(*b, p.job[1]) : 0.0), flops(a) + (b ? flops(*b) : 0.0));
+  switch (q.na * 8 + q.nb) {
+    case 9: return launch_narrow_wgrad<1, 1>(p, blocks, stream);
+    case 10: return launch_narrow_wgrad<1, 2>(p, blocks, stream);
+    case 11: return launch_narrow_wgrad<1, 3>(p, blocks, stream);
+    case 12: return launch_narrow_wgrad<1, 4>(p, blocks, stream);
+    case 33: return launch_narrow_wgrad<4, 1>(p, blocks, stream);
+    case 34: return launch_narrow_wgrad<4, 2>(p, blocks, stream);
+    case 35: return launch_narrow_wgrad<4, 3>(p, blocks, stream);
+    default: return launch_narrow_wgrad<4, 4>(p, blocks, stream);
+  }
 }
 
 }  // namespace cofree

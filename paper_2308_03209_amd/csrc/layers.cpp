@@ -491,15 +491,17 @@ static int32_t layer_bwd(const cofree_partition* part, const cofree_masks* masks
                             : wgrad(dP, d.d_out, H_in, d.d_in, grads->U + d.d_msg, ldu, p.wg[0]);
     if (merged_dU) u.B2 = H_in, u.ldb2 = u.N2b = d.d_in;
     u.colsum_out = grads->bU;
-    COFREE_TRY(launch_wgrad(u, sums, s2));
     if (sage_combine_first(d)) {
+      const WgradArgs ua = wgrad(p.dA, d.d_out, Z, d.d_msg, grads->U, ldu, p.wg[1]);
+      const bool together = !side && wgrads_pair(u, ua);  // one launch instead of two
+      if (!together) COFREE_TRY(launch_wgrad(u, sums, s2));
       // forward was mean(Z U_a^T): dT = mean^T(dP) on d_out columns, dU_a = dT^T Z,
       // dZ = [Z > 0] * (dT U_a)
       AggArgs t = agg();
       t.X = dP; t.Y = p.dA; t.width = d.d_out; t.ldx = t.ldy = d.d_out;
       t.in_scale = g.inv_deg;
       COFREE_TRY(launch_aggregate(t, s));
-      COFREE_TRY(launch_wgrad(wgrad(p.dA, d.d_out, Z, d.d_msg, grads->U, ldu, p.wg[1]), sums, s));
+      COFREE_TRY(together ? launch_wgrads(u, ua, sums, s) : launch_wgrad(ua, sums, s));
       GemmArgs z = gemm();
       z.A1 = p.dA; z.lda1 = d.d_out; z.K1 = d.d_out;
       z.B = params->U; z.ldb = ldu; z.b_kmajor = 1;
@@ -508,8 +510,8 @@ static int32_t layer_bwd(const cofree_partition* part, const cofree_masks* masks
       COFREE_TRY(launch_gemm(z, s));
     } else {
       // dU_a = dP^T A (side stream as well)
-      if (!merged_dU)
-        COFREE_TRY(launch_wgrad(wgrad(dP, d.d_out, A, d.d_msg, grads->U, ldu, p.wg[1]), sums, s2));
+      COFREE_TRY(merged_dU ? launch_wgrad(u, sums, s2)
+                           : launch_wgrads(u, wgrad(dP, d.d_out, A, d.d_msg, grads->U, ldu, p.wg[1]), sums, s2));
       // dA / deg = (dP U_a) scaled per destination row, so that the transposed mean is a plain pull
       GemmArgs a = gemm();
       a.A1 = dP; a.lda1 = d.d_out; a.K1 = d.d_out;
@@ -565,20 +567,22 @@ static int32_t layer_bwd(const cofree_partition* part, const cofree_masks* masks
       w.B2 = saved->A, w.ldb2 = w.N2b = d.d_in;
     }
     w.colsum_out = grads->bW;
-    COFREE_TRY(launch_wgrad(w, sums, s2));
     const bool transform_first = conv_transform_first(d);
     if (!transform_first) COFREE_REQUIRE(saved->A, "layer_bwd: saved.A is NULL");
+    // dW_neigh = dT^T H where the forward pass was mean(H W_neigh^T), in the launch of dW_self where both can be
+    const WgradArgs wn = transform_first ? wgrad(p.T, d.d_out, H_in, d.d_in, grads->W + d.d_in, ldw, p.wg[1]) : WgradArgs{};
+    const bool together = transform_first && !side && wgrads_pair(w, wn);
     // dW_neigh = dPre^T M where the forward pass has kept M = mean(H) (side stream as well)
     if (!transform_first && !merged_dW)
-      COFREE_TRY(launch_wgrad(wgrad(dPre, d.d_out, saved->A, d.d_in, grads->W + d.d_in, ldw, p.wg[1]), sums, s2));
+      COFREE_TRY(launch_wgrads(w, wgrad(dPre, d.d_out, saved->A, d.d_in, grads->W + d.d_in, ldw, p.wg[1]), sums, s2));
+    else if (!together)
+      COFREE_TRY(launch_wgrad(w, sums, s2));
     if (transform_first || (dH_in && conv_gathers_grad(d))) {
       AggArgs t = agg();  // dT = mean^T(dPre)
       t.X = dPre; t.Y = p.T; t.width = d.d_out; t.ldx = t.ldy = d.d_out;
       t.in_scale = g.inv_deg;
       COFREE_TRY(launch_aggregate(t, s));
-      // forward was mean(H W_neigh^T): dW_neigh = dT^T H
-      if (transform_first)
-        COFREE_TRY(launch_wgrad(wgrad(p.T, d.d_out, H_in, d.d_in, grads->W + d.d_in, ldw, p.wg[1]), sums, s));
+      if (transform_first) COFREE_TRY(together ? launch_wgrads(w, wn, sums, s) : launch_wgrad(wn, sums, s));
       if (dH_in) {
         GemmArgs h = gemm();
         // W_self and W_neigh are column blocks of W: dH = dT W_neigh + dPre W_self is one product over the

@@ -103,3 +103,29 @@ def test_layers(env, kind, n, d_in, d_msg, d_out):
     assert_close(dX.cpu().numpy(), ref_dX, what="dH_in")
     for k in ref_g:
         assert_close(g[k].cpu().numpy(), ref_g[k], what=f"d{k}")
+
+
+@pytest.mark.parametrize("kind,d_in,d_msg,d_out", [("sage_conv", 100, 0, 33), ("sage_conv", 40, 0, 64), ("sage", 48, 70, 20), ("sage", 30, 24, 40),
+                                                   ("sage", 8, 100, 40)])
+def test_two_weight_gradients_in_one_launch(env, kind, d_in, d_msg, d_out, monkeypatch):
+    """The two weight gradients of a layer from one launch, or (as the second stream wants them) from two: the same bits."""
+    B, torch = env["B"], env["torch"]
+    n = 3_001
+    print(f"[case] paired weight gradients {kind} {d_in} -> {d_msg} -> {d_out}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(d_in)
+    rand = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    desc = B.layer_desc({"sage": B.SAGE_MEAN, "sage_conv": B.SAGE_CONV}[kind], d_in, d_msg, d_out)
+    p = {"W": rand(d_msg, d_in), "bW": rand(d_msg), "U": rand(d_out, d_msg + d_in), "bU": rand(d_out)} if kind == "sage" else \
+        {"W": rand(d_out, 2 * d_in), "bW": rand(d_out)}
+    ws = torch.empty(max(B.layer_workspace_bytes(desc, n, x) for x in (False, True)), dtype=torch.uint8, device="cuda")
+    H, dY, Y, dX = rand(n, d_in), rand(n, d_out), torch.empty(n, d_out, device="cuda"), torch.empty(n, d_in, device="cuda")
+    saved = {"Z": torch.empty(n, max(d_msg, 1), device="cuda"), "A": torch.empty(n, max(d_msg, d_in, d_out), device="cuda")}
+    P, got = ring(B, n), []
+    B.layer_fwd(P, None, 0, desc, H, p, Y, saved, ws)
+    for overlap in ("0", "1"):
+        monkeypatch.setenv("COFREE_OVERLAP", overlap)
+        g = {k: torch.full_like(v, float("nan")) for k, v in p.items()}
+        B.layer_bwd(P, None, 0, desc, H, Y, p, saved, dY, dX, g, False, ws)
+        got.append(g)
+    for k in p:
+        assert bool(torch.isfinite(got[0][k]).all()) and torch.equal(got[0][k], got[1][k]), k
