@@ -146,7 +146,7 @@ struct DeviceGraph {
 // million-row graph (0.4-0.5 ms), below that the descending-degree order of the launches hides it.
 // AGG_ENTRY_SCALE_MIN_NODES: from this many nodes on (a per-node vector of 2 MB, half of one XCD's L2) the
 // per-source factors of an aggregation are read per adjacency entry instead of gathered per neighbour.
-// AGG_LONG_MIN: graphs of at least this average degree give every row a wavefront.
+// AGG_LONG_MIN: graphs of at least this average degree give rows teams or slices, or every row a wavefront (spmm.hip).
 // AGG_BLOCK_MIN, AGG_WAVE_MIN: rows that the row kernel gives to a workgroup / a wavefront (measured in spmm.hip).
 constexpr int64_t AGG_HUB_MIN = 4096, AGG_LONG_MIN = 16, AGG_ENTRY_SCALE_MIN_NODES = 1 << 19;
 constexpr int64_t AGG_BLOCK_MIN = 128, AGG_WAVE_MIN = 32;

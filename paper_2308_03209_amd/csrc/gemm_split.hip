@@ -9,7 +9,7 @@
 // running sum.
 //
 // Which shapes: results of more than 64 columns (weight gradients: more than 64 rows and columns) and ranges of at
-// least eight k.  Narrower ones are bound by their bytes and stay on the float32 instructions (gemm.hip).
+// least eight k.  Narrower ones are bound by their bytes and stay on the float32 instructions (gemm_narrow.hip).
 //
 // Rounding: every matrix instruction rounds its accumulator once.  h h has one of its own and the five products below it
 // another, which is about 2^-8 of the first, so that its rounding does not show; the two are added at the end.  The sum
