@@ -403,7 +403,9 @@ __device__ inline int window(int first, int i, int n) {
 constexpr int WSTEPS = 8, WGROUP = 4 * WSTEPS;
 template <int NA, int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB == 4 ? 2 : 3))) void narrow_wgrad_kernel(const NarrowPairK two) {
-  __shared__ __attribute__((aligned(16))) float sums[4][NA * 16 * NB * 16];
+  // padded: lanes read down a column of it, with 16 * NB from as few as one bank (64 x 64 over 2,000 nodes 16.6 -> 10.3 us)
+  constexpr int LD = 16 * NB + 4;
+  __shared__ __attribute__((aligned(16))) float sums[4][NA * 16 * LD];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int which = blockIdx.x >= two.first_blocks;
@@ -485,23 +487,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB == 4 ? 2
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) sums[wave][((4 * g + v) * NA + a) * (16 * NB) + r * NB + b] = acc[a][b][v];
+      for (int v = 0; v < 4; ++v) sums[wave][((4 * g + v) * NA + a) * LD + r * NB + b] = acc[a][b][v];
   __syncthreads();
-  auto place = [](int n, int first, int c, int N) {  // where column c of a row of n columns lies among the windows
-    const int i = (c - first) / N;
-    const int s = first + N * i < n - N ? first + N * i : n - N;
-    return i * N + (c - s);
+  // the column that element `place` of the windows holds, or -1 where the lane before has it
+  auto column = [](int n, int first, int place, int N) {
+    const int own = first + place / N * N, c = (own < n - N ? own : n - N) + place % N;
+    return c >= own ? c : -1;
   };
-  const int here = n_wide - c0 < 16 * NA ? n_wide - c0 : 16 * NA;  // columns of this panel
-  const int n_all = p.n_wide1 + p.n_wide2, at = second ? p.n_wide1 + c0 : c0;
+  const int n_all = p.n_wide1 + p.n_wide2, at = second ? p.n_wide1 : 0;
   float* const part = p.part + z * (int64_t)n_all * p.n_narrow;
-  const int inner = p.rows_narrow ? here : p.n_narrow;
-  for (int q = tid; q < here * p.n_narrow; q += 256) {
-    const int o = q / inner, i = q - o * inner;
-    const int cw = p.rows_narrow ? i : o, cn = p.rows_narrow ? o : i;
-    const int e = place(n_wide, c0, c0 + cw, NA) * (16 * NB) + place(p.n_narrow, 0, cn, NB);
-    const float t = ((sums[0][e] + sums[1][e]) + sums[2][e]) + sums[3][e];
-    part[p.rows_narrow ? (int64_t)cn * n_all + at + cw : (int64_t)(at + cw) * p.n_narrow + cn] = t;
+  // The partial sums of the four wavefronts, by lanes along the rows of the result.
+  if (p.rows_narrow) {
+    const int cw = lane < 16 * NA ? column(n_wide, c0, lane, NA) : -1;
+    if (cw >= 0) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int e = 4 * (4 * j + wave);
+        floatx4 t = *reinterpret_cast<const floatx4*>(&sums[0][lane * LD + e]);
+#pragma unroll
+        for (int s = 1; s < 4; ++s) t += *reinterpret_cast<const floatx4*>(&sums[s][lane * LD + e]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int cn = column(p.n_narrow, 0, e + c, NB);
+          if (cn >= 0) part[(int64_t)cn * n_all + at + cw] = t[c];
+        }
+      }
+    }
+  } else {
+    constexpr int ROWS = 64 / (16 * NB);  // of the result, a wavefront at a time
+    const int cn = lane < ROWS * 16 * NB ? column(p.n_narrow, 0, lane % (16 * NB), NB) : -1;
+    if (cn >= 0) {
+#pragma unroll
+      for (int j = 0; j < 16 * NA / (4 * ROWS); ++j) {
+        const int o = (4 * j + wave) * ROWS + lane / (16 * NB), e = o * LD + lane % (16 * NB);
+        const int cw = column(n_wide, c0, o, NA);
+        if (cw >= 0) part[(int64_t)(at + cw) * p.n_narrow + cn] = ((sums[0][e] + sums[1][e]) + sums[2][e]) + sums[3][e];
+      }
+    }
   }
   if (do_colsum) {
     __syncthreads();
@@ -511,12 +533,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB == 4 ? 2
     for (int c = 0; c < CS; ++c)
       if (c < N) lds[(wave * 4 + g) * 16 * N + r * N + c] = csum[c];
     __syncthreads();
-    const int cols = p.rows_narrow ? p.n_narrow : here;
-    if (tid < cols) {
-      const int e = p.rows_narrow ? place(p.n_narrow, 0, tid, NB) : place(n_wide, c0, c0 + tid, NA);
+    const int N_all = 16 * N;
+    if (tid < N_all) {
+      const int c = p.rows_narrow ? column(p.n_narrow, 0, tid, NB) : column(n_wide, c0, tid, NA);
       float t = 0.f;
-      for (int s = 0; s < 16; ++s) t += lds[s * 16 * N + e];
-      p.colsum_part[z * (p.rows_narrow ? p.n_narrow : n_all) + (p.rows_narrow ? tid : at + tid)] = t;
+      for (int s = 0; s < 16; ++s) t += lds[s * N_all + tid];
+      if (c >= 0) p.colsum_part[z * (p.rows_narrow ? p.n_narrow : n_all) + (p.rows_narrow ? c : at + c)] = t;
     }
   }
 }
@@ -536,10 +558,13 @@ static NarrowPlan plan_narrow(int32_t N1, int32_t first, int32_t N2b, int64_t M)
   q.nb = (narrow + 15) / 16;
   q.panels1 = (wide + 16 * q.na - 1) / (16 * q.na);
   q.panels = q.panels1 + (N2b + 16 * q.na - 1) / (16 * q.na);
-  // One round of the workgroups that the chip holds, at least a group of nodes for every wavefront.  Long reductions get
-  // more, shorter chunks, so that the panels of a chunk do not drift apart.
-  const int64_t resident = CUS * (q.nb == 4 ? 2 : 3);
-  const int64_t s = std::max<int64_t>(std::max<int64_t>(1, resident / q.panels), std::min<int64_t>(M / 16384, 2048));
+  // One round of the workgroups that the chip holds, at least a group of nodes for every wavefront.  Panels that read the same
+  // narrow rows drift apart on a long walk and read them again: with four blocks of columns and more than four panels, chunks of
+  // more than 768 nodes are cut up to four times (64 x 602 over 150,000 nodes 163 -> 134 us, 64 x 300 88 -> 68; not where chunks are
+  // short, 64 x 602 over 20,000 29 -> 32, nor with three blocks, 33 x 500 over 300,000 167 -> 179), and long reductions get more chunks.
+  const int64_t resident = CUS * (q.nb == 4 ? 2 : 3), one = std::max<int64_t>(1, resident / q.panels);
+  const int64_t rounds = q.nb == 4 && q.panels > 4 ? std::min<int64_t>(std::max<int64_t>((M + 768 * one - 1) / (768 * one), 1), 4) : 1;
+  const int64_t s = std::max<int64_t>(std::max<int64_t>(1, resident * rounds / q.panels), std::min<int64_t>(M / 16384, 2048));
   const int64_t whole = 4 * WGROUP;
   q.chunk = std::max<int64_t>(1, ((M + s - 1) / s + whole - 1) / whole) * whole;
   q.chunks = std::max<int64_t>(1, (M + q.chunk - 1) / q.chunk);

@@ -64,7 +64,9 @@ def test_non_finite_operands_stay_in_their_rows_and_columns(env):
                          [(k, n, *d) for k in ("gcn", "sage", "sage_conv")
                           for n, *d in [(129, 3, 2, 2), (2_000, 64, 16, 16), (5_003, 41, 33, 7), (33_000, 100, 64, 47),
                                         (20_011, 130, 48, 63), (9_001, 12, 5, 200), (40_000, 256, 40, 1)]
-                          if k != "sage" or n <= 10_000] + [("sage", 4_001, 128, 256, 50)])
+                          if k != "sage" or n <= 10_000] + [("sage", 4_001, 128, 256, 50)] +
+                         # weight gradients of 50 and 64 rows or columns whose chunks are cut in two and in three
+                         [("gcn", 45_001, 601, 2, 50), ("gcn", 90_001, 50, 2, 320), ("sage_conv", 130_003, 512, 2, 64)])
 def test_layers(env, kind, n, d_in, d_msg, d_out):
     from oracle import dropedge as o_dropedge
     from oracle import layers as o_layers
