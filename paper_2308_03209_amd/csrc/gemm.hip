@@ -1,6 +1,6 @@
 // Dense feature transforms of the layers (the W and U products of the GraphSAGE layer in
 // Section 3 and their gradients) on the fp32 matrix cores of gfx950: the shapes that gemm_split.hip and gemm_narrow.hip
-// leave out (a range of fewer than eight k, operands with rows gigabytes apart).
+// leave out (a range of fewer than eight k, operands of four million columns and more, some results of 33 to 64 columns).
 //
 // One kernel computes a 128x128 tile of  C = sum_k Aop(i,k) * Bop(j,k)  per 256-thread block:
 // four 64-wide wavefronts in a 2x2 grid, each holding a 64x64 sub-tile as 2x2 blocks of
@@ -28,7 +28,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int BM = 128, BN = 128, BK = 16, LDS_LD = 132;  // 132 = 128 + 4 words of padding
-constexpr int AM = 2, AN = 2;  // 32x32 blocks of a wavefront's sub-tile
+constexpr int AM = 2;  // rows of 32x32 blocks of a wavefront's sub-tile
 
 struct GemmK {
   const float* A1;
@@ -193,7 +193,8 @@ struct MoverKMajor {
   }
 };
 
-// 16 k-steps of one LDS tile pair on a wavefront's sub-tile of AM x AN blocks of 32x32 (32 MFMAs).
+// 16 k-steps of one LDS tile pair on a wavefront's sub-tile of AM x AN blocks of 32x32 (2x2: 32 MFMAs).
+template <int AN>
 __device__ inline void compute_tile(const float* __restrict__ as, const float* __restrict__ bs,
                                     floatx16 (&acc)[AM][AN], int g) {
 #pragma unroll
@@ -227,7 +228,7 @@ __device__ inline void compute_tile(const float* __restrict__ as, const float* _
 // a store waits for its own slot only.  LDS is double-buffered with one barrier per tile: tile t is stored,
 // the barrier passes, tile t is multiplied, and the store of tile t+1 goes to the other buffer, which
 // every wavefront stopped reading before that barrier.
-template <int D, typename MA, typename MB>
+template <int D, int AN, typename MA, typename MB>
 __device__ inline void run_range_deep(const MA& ma, const MB& mb, int64_t k_len, float (&As)[2][BK * LDS_LD],
                                       float (&Bs)[2][BK * LDS_LD], floatx16 (&acc)[AM][AN], int tid,
                                       bool do_colsum, float& colsum) {
@@ -258,7 +259,7 @@ __device__ inline void run_range_deep(const MA& ma, const MB& mb, int64_t k_len,
         mb.load(tn * BK, rb[s][0], rb[s][1]);
       }
       __syncthreads();
-      compute_tile(at + a_off, bt + b_off, acc, g);
+      compute_tile<AN>(at + a_off, bt + b_off, acc, g);
       add_colsum(at);
     };
 #pragma unroll
@@ -284,7 +285,7 @@ __device__ inline void run_range_deep(const MA& ma, const MB& mb, int64_t k_len,
     ma.store(at, tid, ra[0][0], ra[0][1]);
     mb.store(bt, tid, rb[0][0], rb[0][1]);
     __syncthreads();
-    compute_tile(at + a_off, bt + b_off, acc, g);
+    compute_tile<AN>(at + a_off, bt + b_off, acc, g);
     add_colsum(at);
   }
 }
@@ -294,9 +295,11 @@ __device__ inline void run_range_deep(const MA& ma, const MB& mb, int64_t k_len,
 constexpr int WGRAD_DEPTH = 2;
 constexpr int NT_DEPTH = 2;
 
-template <bool A_KMAJOR, bool B_KMAJOR>
+// AN: 32x32 blocks of a wavefront's row of blocks, two in 128x128 tiles, one in the 128x64 tiles of results of at most 64
+// columns, which move the same 128-wide operand tiles and only skip the matrix instructions of the half that is never stored.
+template <bool A_KMAJOR, bool B_KMAJOR, int AN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void gemm_kernel(const GemmK p) {
-  constexpr int TM = BM, TN = BN;  // block tile
+  constexpr int TM = BM, TN = 64 * AN;  // block tile
   // operand tiles during the k loop; afterwards the same memory stages the result tile
   constexpr int STAGE_LD = 68;  // floats per staged row: 64 + 4 of padding
   constexpr int SMEM_FLOATS = 4 * BK * LDS_LD > 4 * 32 * STAGE_LD ? 4 * BK * LDS_LD : 4 * 32 * STAGE_LD;
@@ -355,11 +358,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
       if constexpr (!B_KMAJOR) {
         MoverKContig mb;
         mb.init(B, ldb, p.N, j0, tid);
-        run_range_deep<NT_DEPTH>(ma, mb, k_len, As, Bs, acc, tid, false, no_colsum);
+        run_range_deep<NT_DEPTH, AN>(ma, mb, k_len, As, Bs, acc, tid, false, no_colsum);
       } else {
         MoverKMajor mb;
         mb.init(B, ldb, p.N, j0, tid);
-        run_range_deep<NT_DEPTH>(ma, mb, k_len, As, Bs, acc, tid, false, no_colsum);
+        run_range_deep<NT_DEPTH, AN>(ma, mb, k_len, As, Bs, acc, tid, false, no_colsum);
       }
     };
     // one loop body for both K-segments (two inlined copies would each claim their own accumulators)
@@ -393,7 +396,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
         mb.init(p.B + k_beg * p.ldb, p.ldb, p.n_split > 0 ? p.n_split : p.N, j0, tid);
       float csum = 0.f;
       const bool do_colsum = p.colsum_part != nullptr && j0 == 0;
-      run_range_deep<WGRAD_DEPTH>(ma, mb, k_len, As, Bs, acc, tid, do_colsum, csum);
+      run_range_deep<WGRAD_DEPTH, AN>(ma, mb, k_len, As, Bs, acc, tid, do_colsum, csum);
       if (do_colsum && tid < TM && i0 + tid < p.M) p.colsum_part[z * p.M + i0 + tid] = csum;
     } else if (p.colsum_part != nullptr && j0 == 0 && tid < TM && i0 + tid < p.M) {
       p.colsum_part[z * p.M + i0 + tid] = 0.f;
@@ -658,7 +661,8 @@ int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
   p.relu_last = a.relu_last;
   p.gate_last = a.gate_last;
   p.gate_scale = a.gate ? a.gate_scale : 1.f;
-  p.tiles_n = (a.N + BN - 1) / BN;
+  const bool narrow = a.N <= 64;  // one 128x64 tile per row panel
+  p.tiles_n = narrow ? 1 : (a.N + BN - 1) / BN;
   p.tiles_m = 1;
   p.n_groups = (a.M + BM - 1) / BM;
   const int64_t blocks = ((p.n_groups + 7) / 8) * 8 * p.tiles_n;
@@ -666,13 +670,14 @@ int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
   const double flops = 2.0 * (double)a.M * a.N * (double)p.K;
   const double bytes = 4.0 * ((double)a.M * p.K + (double)a.N * p.K + (double)a.M * a.N * (a.accumulate ? 2 : 1));
   char pname[96] = "";  // the template instance launched below, then the shape
-  if (profiling()) snprintf(pname, sizeof(pname), "gemm_kernel<false,%s> N=%d K=%d", a.b_kmajor ? "true" : "false", (int)a.N,
-                            (int)p.K);
+  if (profiling()) snprintf(pname, sizeof(pname), "gemm_kernel<false,%s,%d> N=%d K=%d", a.b_kmajor ? "true" : "false", narrow ? 1 : 2,
+                            (int)a.N, (int)p.K);
   ProfScope prof(pname, stream, bytes, flops);
-  if (a.b_kmajor)
-    gemm_kernel<false, true><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
-  else
-    gemm_kernel<false, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
+  const dim3 grid((unsigned)blocks);
+  if (a.b_kmajor && narrow) gemm_kernel<false, true, 1><<<grid, 256, 0, stream>>>(p);
+  else if (a.b_kmajor) gemm_kernel<false, true, 2><<<grid, 256, 0, stream>>>(p);
+  else if (narrow) gemm_kernel<false, false, 1><<<grid, 256, 0, stream>>>(p);
+  else gemm_kernel<false, false, 2><<<grid, 256, 0, stream>>>(p);
   COFREE_HIP_CHECK(hipGetLastError());
   return COFREE_OK;
 }
@@ -770,10 +775,10 @@ int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
   COFREE_TRY(check_grid(blocks));
   {
     char pname[96] = "";
-    if (profiling()) snprintf(pname, sizeof(pname), "gemm_kernel<true,true> N=%dx%d", (int)N1, (int)N2);
+    if (profiling()) snprintf(pname, sizeof(pname), "gemm_kernel<true,true,2> N=%dx%d", (int)N1, (int)N2);
     ProfScope prof(pname, stream, 4.0 * ((double)M * N1 * (p.extra.X ? 2 : 1) + (double)M * N2 + (double)N1 * N2),
                    2.0 * (double)M * N1 * N2);
-    gemm_kernel<true, true><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
+    gemm_kernel<true, true, 2><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
   }
   COFREE_HIP_CHECK(hipGetLastError());
   COFREE_TRY(add_split_sum(sums, a.workspace, p.c_split_stride, S, a.C, a.ldc, N1, N2));

@@ -14,8 +14,8 @@
 // that it shares with the lane before are computed twice, with the same result.
 //
 // Before, these shapes went through LDS in tiles of 128 x 128, of which a narrow product used half, with two steps of 16 k in
-// flight.  470k x 47 x 512: 326 -> 254 us (4.1 TB/s), weight gradient 327 -> 274; 230k x 41 x 256: 91 -> 69 and 86 -> 69; 19,717 x
-// 33 x 500: 31 -> 23; 2,000 x 16 x 64: 9.4 -> 5.5.
+// flight (gemm.hip).  470k x 47 x 512: 326 -> 254 us (4.1 TB/s), weight gradient 327 -> 274; 300k x 41 x 256: 107 -> 82 and 106 -> 84;
+// 20,000 x 33 x 500: 28 -> 20 and 25 -> 22; 64 x 64 over 20,000 nodes 18 -> 12; 2,000 x 16 x 64: 6.6 -> 3.6.
 #include <algorithm>
 #include <climits>
 #include <cstdio>
@@ -52,42 +52,44 @@ struct NarrowK {
   float gate_scale;
 };
 
-// Steps of 16 k that a wavefront has in flight (DEPTH of the kernel): eight, or two where a segment has fewer than 16 k, which
-// also says that it is read element by element (2,000 rows of 8 k: 12.0 us with eight, most of them repeating the only
-// step, 6.1 with two).  Sixteen, and loads of four steps issued together, were no faster.
-constexpr int DEPTH_SHORT = 2, DEPTH_WIDE = 8;
+// Steps of 16 k that a wavefront has in flight (DEPTH of the kernel): eight, or about as many as the product has, because a
+// ring that is too long repeats the last step (33,000 rows x 64 x 64: 9.4 -> 8.1 us with four, 60,000 x 48 x 8 10.7 -> 6.1 with
+// two).  Sixteen, and loads of four steps issued together, were no faster.  One says that a segment has fewer than 4 k and is
+// read element by element.
 
-// A step's k: segment, window of 16 and how many of the window's first k the step before had.  A segment that is no whole
-// number of steps ends with the window of its last 16 k.  SHORT: a segment has fewer than 16 k, windows start every 16.
-template <bool SHORT>
+// A step's k: segment and first k.  A lane has the four from 4 g on, g its group of 16; where they would cross the end of the
+// segment, its last four, of which those that the group before has are zero.
+template <bool ELEMENTS>
 struct Step {
   bool second;
-  int32_t start, skip, len;
+  int32_t start, len;
   __device__ Step(int t, int n1, int32_t K1, int32_t K2) {
     second = t >= n1;
-    const int32_t k0 = (second ? t - n1 : t) * 16;
+    start = (second ? t - n1 : t) * 16;
     len = second ? K2 : K1;
-    start = SHORT || k0 < len - 16 ? k0 : len - 16;
-    skip = k0 - start;
   }
-  __device__ bool whole() const { return SHORT ? start + 16 <= len : skip == 0; }
-  __device__ bool has(int32_t k) const { return SHORT ? start + k < len : k >= skip; }  // k counted from start
-  __device__ int32_t at(int32_t k) const { return SHORT && start + k > len - 1 ? len - 1 : start + k; }
+  __device__ bool whole() const { return start + 16 <= len; }
+  __device__ int32_t first(int g) const {
+    const int32_t k = start + 4 * g;
+    return ELEMENTS || k < len - 4 ? k : len - 4;
+  }
+  __device__ bool has(int g, int c) const { return ELEMENTS ? start + 4 * g + c < len : first(g) + c >= start + 4 * g; }
+  __device__ int32_t at(int g, int c) const { return ELEMENTS && start + 4 * g + c > len - 1 ? len - 1 : first(g) + c; }
 };
 
-// A wavefront computes NB blocks of 16 columns of a tile of 16 rows; several may share a tile (NB = 1).  A workgroup keeps
+// A wavefront computes NB blocks of 16 columns of a tile of 16 rows; several may share a tile (SHARE).  A workgroup keeps
 // all parameters in LDS where they fit and walks the row tiles; where they do not, it walks the parts of k for every round
 // of tiles.
-template <int NB, bool B_KMAJOR, int DEPTH, bool EXTRAS>
+template <int NB, bool SHARE, bool B_KMAJOR, int DEPTH, bool EXTRAS>
 __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
-  constexpr bool SHORT = DEPTH == DEPTH_SHORT;
-  const int col_waves = NB == 1 ? p.col_waves : 1, nb = NB * col_waves;
+  constexpr bool ELEMENTS = DEPTH == 1;
+  const int col_waves = SHARE ? p.col_waves : 1, nb = NB * col_waves;
   float* const bias = lds;              // [nb][16], in the order of `column`
   float* const params = lds + nb * 16;  // [step][nb][lane][4]
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int b0 = wave % col_waves, row_wave = wave / col_waves, row_waves = (int)(blockDim.x >> 6) / col_waves;
+  const int b0 = wave % col_waves * NB, row_wave = wave / col_waves, row_waves = (int)(blockDim.x >> 6) / col_waves;
   const int n1 = (p.K1 + 15) / 16, n = n1 + (p.K2 + 15) / 16;
 
   struct Rows {
@@ -100,13 +102,13 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
     return Rows{p.A1 + i * p.lda1, p.K2 ? p.A2 + i * p.lda2 : nullptr};
   };
   auto load = [&](const Rows& rows, int t, float4u& x) {
-    const Step<SHORT> s(t < n ? t : n - 1, n1, p.K1, p.K2);
+    const Step<ELEMENTS> s(t < n ? t : n - 1, n1, p.K1, p.K2);
     const float* const a = s.second ? rows.a2 : rows.a1;
-    if constexpr (SHORT) {
+    if constexpr (ELEMENTS) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) x[c] = a[s.at(4 * g + c)];
+      for (int c = 0; c < 4; ++c) x[c] = a[s.at(g, c)];
     } else {
-      x = *reinterpret_cast<const float4u*>(a + s.start + 4 * g);
+      x = *reinterpret_cast<const float4u*>(a + s.first(g));
     }
   };
   // output column of row i of the instruction's first operand in block b
@@ -118,30 +120,30 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
   auto fill = [&](int t0, int t1) {  // parameters of steps t0 .. t1 - 1; a wavefront takes steps of one block of columns
     const int b = wave % nb, every = (int)(blockDim.x >> 6) / nb;
     const int64_t j = column(b, r);
-    constexpr int BATCH = 8;
+    constexpr int BATCH = DEPTH;
     for (int base = t0 + wave / nb; base < t1 && wave < every * nb; base += BATCH * every) {
       float4u v[BATCH];
 #pragma unroll
       for (int u = 0; u < BATCH; ++u) {
         const int t = base + u * every;
-        const Step<SHORT> s(t < t1 ? t : t1 - 1, n1, p.K1, p.K2);
+        const Step<ELEMENTS> s(t < t1 ? t : t1 - 1, n1, p.K1, p.K2);
         const float* const B = s.second ? p.B2 : p.B1;
         const int64_t ldb = s.second ? p.ldb2 : p.ldb1;
-        if constexpr (!B_KMAJOR && !SHORT) {
-          v[u] = *reinterpret_cast<const float4u*>(B + j * ldb + s.start + 4 * g);
+        if constexpr (!B_KMAJOR && !ELEMENTS) {
+          v[u] = *reinterpret_cast<const float4u*>(B + j * ldb + s.first(g));
         } else {
 #pragma unroll
-          for (int c = 0; c < 4; ++c) v[u][c] = B[B_KMAJOR ? s.at(4 * g + c) * ldb + j : j * ldb + s.at(4 * g + c)];
+          for (int c = 0; c < 4; ++c) v[u][c] = B[B_KMAJOR ? s.at(g, c) * ldb + j : j * ldb + s.at(g, c)];
         }
       }
 #pragma unroll
       for (int u = 0; u < BATCH; ++u) {
         const int t = base + u * every;
         if (t >= t1) break;
-        const Step<SHORT> s(t, n1, p.K1, p.K2);
+        const Step<ELEMENTS> s(t, n1, p.K1, p.K2);
         float4 w;
-        w.x = s.has(4 * g) ? v[u][0] : 0.f, w.y = s.has(4 * g + 1) ? v[u][1] : 0.f;
-        w.z = s.has(4 * g + 2) ? v[u][2] : 0.f, w.w = s.has(4 * g + 3) ? v[u][3] : 0.f;
+        w.x = s.has(g, 0) ? v[u][0] : 0.f, w.y = s.has(g, 1) ? v[u][1] : 0.f;
+        w.z = s.has(g, 2) ? v[u][2] : 0.f, w.w = s.has(g, 3) ? v[u][3] : 0.f;
         *reinterpret_cast<float4*>(params + (((t - t0) * nb + b) * 64 + lane) * 4) = w;
       }
     }
@@ -174,10 +176,10 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
       const int t = t0 + s;
       float4u& x = ring[s];
       if (t < n) {  // uniform
-        const Step<SHORT> st(t, n1, p.K1, p.K2);
+        const Step<ELEMENTS> st(t, n1, p.K1, p.K2);
         if (!st.whole()) {
 #pragma unroll
-          for (int c = 0; c < 4; ++c) x[c] = st.has(4 * g + c) ? x[c] : 0.f;
+          for (int c = 0; c < 4; ++c) x[c] = st.has(g, c) ? x[c] : 0.f;
         }
         const float4* const b = reinterpret_cast<const float4*>(params) + ((t - part0) * nb + b0) * 64 + lane;
         float4 w[NB];
@@ -197,7 +199,9 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
   bool filled = false;
   for (int round = 0; round < p.rounds; ++round) {
     const int64_t i = tile_of(round) * 16 + r;
-    const Rows next = rows_of(round + 1 < p.rounds ? round + 1 : round);
+    // after the last round the loads go on, from one row for all lanes (left out by a condition, every chunk waits longer: 45,000 rows
+    // x 64 x 300 24.6 -> 29.0 us)
+    const Rows next = round + 1 < p.rounds ? rows_of(round + 1) : Rows{p.A1, p.A2};
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = floatx4{0.f, 0.f, 0.f, 0.f};
     for (int part0 = 0; part0 < n; part0 += p.part_steps) {
@@ -264,14 +268,41 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
   }
 }
 
-bool gemm_narrow_fits(const GemmArgs& a) { return a.N <= 64; }
+struct NarrowShape {
+  int nb;            // blocks of 16 columns
+  int64_t steps;     // of 16 k
+  int64_t most;      // steps whose parameters LDS holds
+  int64_t cu_tiles;  // row tiles of a CU
+};
+static NarrowShape narrow_shape(const GemmArgs& a) {
+  NarrowShape s;
+  s.nb = (a.N + 15) / 16;
+  s.steps = ((int64_t)a.K1 + 15) / 16 + ((int64_t)a.K2 + 15) / 16;
+  s.most = (LDS_BYTES - s.nb * 64) / (s.nb * 1024);
+  s.cu_tiles = (a.M + 16 * CUS - 1) / (16 * CUS);
+  return s;
+}
 
-template <int NB, bool B_KMAJOR, int DEPTH, bool EXTRAS>
+// At most 64 columns, except, in the tiles of gemm.hip,
+//  * parameters beyond LDS by several rounds of row tiles, each of which reads them again: more than 48 columns (90,000 x 64 x 1433
+//    222 us here, 185 there; 150,000 332 and 304; in one round, 60,000, 118 and 123), and 33 to 48 in two rounds (90,000 x 41 x 900
+//    120 and 111; 150,000 179 and 184)
+//  * 49 to 64 columns by 113 to 320 k in one round or little more, where filling LDS and multiplying follow one another
+//    (60,000 x 64 x 256 28.4 and 25.5, x 128 17.7 and 16.3; 45,000 x 256 22.8 and 24.9; 150,000 54.2 and 52.5)
+bool gemm_narrow_fits(const GemmArgs& a) {
+  if (a.N > 64) return false;
+  const NarrowShape s = narrow_shape(a);
+  if (s.steps > s.most && s.cu_tiles > 16 && (s.nb == 4 || (s.nb == 3 && s.cu_tiles <= 32))) return false;
+  return !(s.nb == 4 && s.cu_tiles >= 14 && s.cu_tiles <= 24 && s.steps >= 8 && s.steps <= 20);
+}
+
+template <int NB, bool SHARE, bool B_KMAJOR, int DEPTH, bool EXTRAS>
 static int32_t launch_narrow(const NarrowK& p, int64_t blocks, int threads, size_t lds, hipStream_t stream) {
+  const auto kernel = narrow_gemm_kernel<NB, SHARE, B_KMAJOR, DEPTH, EXTRAS>;
   if (lds > 64 * 1024)
-    COFREE_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(narrow_gemm_kernel<NB, B_KMAJOR, DEPTH, EXTRAS>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES));
-  narrow_gemm_kernel<NB, B_KMAJOR, DEPTH, EXTRAS><<<dim3((unsigned)blocks), threads, lds, stream>>>(p);
+    COFREE_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         LDS_BYTES));
+  kernel<<<dim3((unsigned)blocks), threads, lds, stream>>>(p);
   COFREE_HIP_CHECK(hipGetLastError());
   return COFREE_OK;
 }
@@ -304,20 +335,17 @@ int32_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream) {
   p.gate_last = a.gate_last;
   p.gate_scale = a.gate ? a.gate_scale : 1.f;
   p.tiles = (a.M + 15) / 16;
-  const int nb = (a.N + 15) / 16;
-  const int64_t steps = ((int64_t)a.K1 + 15) / 16 + ((int64_t)a.K2 + 15) / 16;
-  const bool is_short = a.K1 < 16 || (a.K2 > 0 && a.K2 < 16);
-  const int64_t most = (LDS_BYTES - nb * 64) / (nb * 1024);
-  const bool spread = p.tiles <= 8 * CUS;
-  const int depth = is_short ? DEPTH_SHORT : DEPTH_WIDE;
+  const auto [nb, steps, most, cu_tiles] = narrow_shape(a);
+  const int depth = a.K1 < 4 || (a.K2 > 0 && a.K2 < 4) ? 1 : steps <= 2 ? 2 : steps <= 4 ? 4 : 8;
   p.part_steps = (int32_t)(steps <= most ? steps : most / depth * depth);
   const size_t lds = (size_t)p.part_steps * nb * 1024 + nb * 64;
-  // Up to eight tiles per CU the chain of matrix instructions on one tile is what a launch waits for: a wavefront per block of
-  // columns, and workgroups so small that every CU has one (19,717 rows: 66 columns of 8 k 10.6 -> 7.5 us, 33 of 500 k no
-  // difference).  Beyond that a
-  // wavefront takes all columns, and workgroups have as many as the registers of a CU hold.
-  p.col_waves = spread ? nb : 1;
-  const int row_waves = spread ? std::min((int)std::max<int64_t>((p.tiles + CUS - 1) / CUS, (3 + nb) / nb), 16 / nb) : 16;
+  // A wavefront takes all columns of a row tile, workgroups as many row tiles as their CU has, up to 16.  With so few tiles that
+  // every block of columns can have a wavefront of its own it gets one: the chain of matrix instructions on one tile is what
+  // the launch waits for.  Five and six tiles of four blocks, which would lie unevenly on four SIMDs, are cut in two (20,000 x 64 x
+  // 602: 38 us in five wavefronts, 30 in ten).  Always 16 tiles left CUs without a workgroup (33,000 x 48 x 64 11.7 -> 8.3 us).
+  p.col_waves = cu_tiles * nb <= 16 ? nb : nb == 4 && cu_tiles <= 6 && depth == 8 ? 2 : 1;
+  const int cols = nb / p.col_waves;  // blocks of columns a wavefront
+  const int row_waves = (int)std::min<int64_t>(std::max<int64_t>(cu_tiles, (3 + p.col_waves) / p.col_waves), 16 / p.col_waves);
   const int waves = row_waves * p.col_waves;
   const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(16 / waves, (int64_t)(LDS_BYTES / lds)));
   const int64_t blocks = std::min<int64_t>((p.tiles + row_waves - 1) / row_waves, CUS * per_cu);
@@ -327,26 +355,39 @@ int32_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream) {
   const bool extras = a.gate || a.accumulate || a.row_scale || a.relu_last;
   const double K = (double)a.K1 + a.K2;
   char pname[96] = "";  // the template instance launched below, then the shape
-  if (profiling()) snprintf(pname, sizeof(pname), "narrow_gemm_kernel<%d,%s,%d,%s> N=%d K=%lld", spread ? 1 : nb, a.b_kmajor ? "true" : "false",
+  if (profiling()) snprintf(pname, sizeof(pname), "narrow_gemm_kernel<%d,%s,%s,%d,%s> N=%d K=%lld", cols, cols == 1 || p.col_waves > 1 ? "true" : "false", a.b_kmajor ? "true" : "false",
                             depth, extras ? "true" : "false", (int)a.N, (long long)K);
   ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + (double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1)),
                  2.0 * (double)a.M * a.N * K);
-  auto by_depth = [&](auto n, auto kmajor) {
+  auto by_depth = [&](auto n, auto share, auto kmajor) {
     constexpr int NB = decltype(n)::value;
-    constexpr bool BK = decltype(kmajor)::value;
-    auto go = [&](auto depth) {
-      constexpr int D = decltype(depth)::value;
-      return extras ? launch_narrow<NB, BK, D, true>(p, blocks, 64 * waves, lds, stream)
-                    : launch_narrow<NB, BK, D, false>(p, blocks, 64 * waves, lds, stream);
+    constexpr bool SHARE = decltype(share)::value, KMAJOR = decltype(kmajor)::value;
+    auto go = [&](auto d) {
+      constexpr int DEPTH = decltype(d)::value;
+      return extras ? launch_narrow<NB, SHARE, KMAJOR, DEPTH, true>(p, blocks, 64 * waves, lds, stream)
+                    : launch_narrow<NB, SHARE, KMAJOR, DEPTH, false>(p, blocks, 64 * waves, lds, stream);
     };
-    return is_short ? go(std::integral_constant<int, DEPTH_SHORT>{}) : go(std::integral_constant<int, DEPTH_WIDE>{});
+    if constexpr (NB == 2 && SHARE) {
+      return go(std::integral_constant<int, 8>{});
+    } else {
+      switch (depth) {
+        case 1: return go(std::integral_constant<int, 1>{});
+        case 2: return go(std::integral_constant<int, 2>{});
+        case 4: return go(std::integral_constant<int, 4>{});
+        default: return go(std::integral_constant<int, 8>{});
+      }
+    }
   };
-  auto by_order = [&](auto n) { return a.b_kmajor ? by_depth(n, std::true_type{}) : by_depth(n, std::false_type{}); };
-  switch (spread ? 1 : nb) {
-    case 1: return by_order(std::integral_constant<int, 1>{});
-    case 2: return by_order(std::integral_constant<int, 2>{});
-    case 3: return by_order(std::integral_constant<int, 3>{});
-    default: return by_order(std::integral_constant<int, 4>{});
+  auto by_order = [&](auto n, auto share) {
+    return a.b_kmajor ? by_depth(n, share, std::true_type{}) : by_depth(n, share, std::false_type{});
+  };
+  const std::true_type shared{};
+  const std::false_type alone{};
+  switch (cols) {
+    case 1: return by_order(std::integral_constant<int, 1>{}, shared);
+    case 2: return p.col_waves == 2 ? by_order(std::integral_constant<int, 2>{}, shared) : by_order(std::integral_constant<int, 2>{}, alone);
+    case 3: return by_order(std::integral_constant<int, 3>{}, alone);
+    default: return by_order(std::integral_constant<int, 4>{}, alone);
   }
 }
 

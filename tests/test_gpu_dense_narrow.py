@@ -29,7 +29,15 @@ def within_rounding(got, ref, mag, terms, what):
 # one window, moved windows, whole steps, more steps than LDS holds
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (15, 2, 3), (17, 3, 15), (33, 4, 16), (1000, 5, 17), (2049, 16, 31), (300, 17, 602),
                                    (19_717, 33, 500), (40_001, 47, 128), (5_000, 49, 129), (70_003, 64, 40), (66_000, 63, 7),
-                                   (3_000, 64, 1433), (2_100, 48, 900), (515, 9, 2600), (35_000, 20, 70), (50_000, 7, 33)])
+                                   (3_000, 64, 1433), (2_100, 48, 900), (515, 9, 2600), (35_000, 20, 70), (50_000, 7, 33),
+                                   # the last four k of a segment, element by element below four, rings of one, two and four steps
+                                   (5_000, 33, 5), (50, 60, 2), (140_000, 20, 3), (100_003, 64, 6), (300_001, 16, 9), (65_537, 30, 64),
+                                   # two wavefronts of 32 columns a row tile, with parameters beyond LDS in the first
+                                   (20_003, 50, 1433), (24_001, 64, 77), (17_003, 49, 602),
+                                   # parameters beyond LDS in two parts, read again by two (66,003 and 70,003 rows) and three rounds
+                                   (66_003, 9, 2600), (70_003, 17, 1300), (140_001, 41, 900),
+                                   # tiles of 128 x 64
+                                   (90_001, 41, 900), (70_003, 64, 1433), (60_001, 50, 130), (60_001, 64, 256)])
 @pytest.mark.parametrize("relu", [False, True])
 def test_products(env, M, N, K, relu):
     B, torch = env["B"], env["torch"]
@@ -41,6 +49,24 @@ def test_products(env, M, N, K, relu):
     ref = A.double() @ W.double().T + b.double()
     within_rounding(C[:M], ref.clamp_min(0.0) if relu else ref, A.double().abs() @ W.double().abs().T + b.double().abs(), K + 1, "product")
     assert bool(torch.isnan(C[M]).all())  # nothing behind the result
+
+
+@pytest.mark.parametrize("M,N,K,tiled", [(65_536, 64, 1433, False), (65_537, 64, 1433, True), (131_072, 33, 900, True), (131_073, 33, 900, False),
+                                         (70_000, 32, 1300, False), (65_537, 64, 600, False), (53_249, 49, 113, True), (53_248, 49, 113, False),
+                                         (98_304, 64, 320, True), (98_305, 64, 320, False), (60_000, 64, 112, False), (60_000, 64, 321, False),
+                                         (60_000, 48, 128, False)])
+def test_which_kernel(env, M, N, K, tiled):
+    """Parameters beyond LDS read again every round, and a round and a bit of 49 to 64 columns, go to the tiles."""
+    B, torch = env["B"], env["torch"]
+    print(f"[case] kernel of the product M={M} N={N} K={K}", flush=True)
+    A, W = torch.ones(M, K, device="cuda"), torch.ones(N, K, device="cuda")
+    C = torch.empty(M, N, device="cuda")
+    B.profile_enable(True)
+    B.dense_nt_f32(A, W, torch.zeros(N, device="cuda"), C, False)
+    names = list(B.profile_read())
+    B.profile_enable(False)
+    assert len(names) == 1 and names[0].startswith("gemm_kernel<false,false,1>" if tiled else "narrow_gemm_kernel<"), names
+    assert bool((C == K).all())
 
 
 def test_non_finite_operands_stay_in_their_rows_and_columns(env):
@@ -66,7 +92,11 @@ def test_non_finite_operands_stay_in_their_rows_and_columns(env):
                                         (20_011, 130, 48, 63), (9_001, 12, 5, 200), (40_000, 256, 40, 1)]
                           if k != "sage" or n <= 10_000] + [("sage", 4_001, 128, 256, 50)] +
                          # weight gradients of 50 and 64 rows or columns whose chunks are cut in two and in three
-                         [("gcn", 45_001, 601, 2, 50), ("gcn", 90_001, 50, 2, 320), ("sage_conv", 130_003, 512, 2, 64)])
+                         [("gcn", 45_001, 601, 2, 50), ("gcn", 90_001, 50, 2, 320), ("sage_conv", 130_003, 512, 2, 64)] +
+                         # k-major parameters in two segments beyond LDS, in one round and in two; a short segment before a long one;
+                         # tiles in both orders and accumulating
+                         [("sage_conv", 5_003, 48, 2, 600), ("sage_conv", 70_003, 20, 2, 700), ("sage", 3_001, 40, 100, 2),
+                          ("sage_conv", 60_001, 50, 2, 130), ("sage_conv", 60_001, 150, 2, 50)])
 def test_layers(env, kind, n, d_in, d_msg, d_out):
     from oracle import dropedge as o_dropedge
     from oracle import layers as o_layers
