@@ -333,8 +333,10 @@ struct GemmArgs {
   int32_t gate_last = 0;             // apply `gate` after the accumulation instead of before it
   float gate_scale = 1.f;            // factor on the elements that pass `gate`
   DropoutArgs dropout;               // of the finished result, where gemm_drops() says that the product applies it
-  // bfloat16 only: scratch for the parameters converted to bfloat16, gemm_param_scratch_bytes(N, K1+K2)
+  // scratch for the parameters: in bfloat16 for their conversion, at least gemm_param_scratch_bytes(N, K1+K2); in float32 to
+  // split them beforehand, which is done where split_param_bytes(M, N, K1, K2) is not zero and there are as many bytes
   void* param_scratch = nullptr;
+  size_t param_scratch_bytes = 0;
 };
 int32_t launch_gemm(const GemmArgs& a, hipStream_t stream);
 // whether the product that launch_gemm takes can apply dropout to its result
@@ -399,7 +401,7 @@ struct ColsumK;
 int32_t plan_colsum(const WgradArgs& a, ColsumK* k, SplitSums* sums);  // extra workgroups of a launch, if any
 // float32 products on the bfloat16 matrix cores (gemm_split.hip): which shapes they take, and their launchers
 bool gemm_split_fits(const GemmArgs& a);
-size_t split_param_bytes(int32_t N, int64_t K1, int64_t K2);  // scratch for the parameters of a product split beforehand
+size_t split_param_bytes(int64_t M, int32_t N, int64_t K1, int64_t K2);  // see GemmArgs::param_scratch
 int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream);
 bool wgrad_split_fits(const WgradArgs& a);
 int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stream);

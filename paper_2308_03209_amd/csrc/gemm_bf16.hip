@@ -633,7 +633,8 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(a.K2 == 0 || a.A2, "dense: second segment is NULL");
   COFREE_REQUIRE(a.lda1 >= a.K1 && (a.K2 == 0 || a.lda2 >= a.K2), "dense: lda too small");
   COFREE_REQUIRE(a.ldc >= a.N, "dense: ldc too small");
-  COFREE_REQUIRE(a.param_scratch != nullptr, "dense: bf16 products need param_scratch");
+  COFREE_REQUIRE(a.param_scratch && a.param_scratch_bytes >= gemm_param_scratch_bytes(a.N, (int64_t)a.K1 + a.K2),
+                 "dense: bf16 products need param_scratch");
   if (a.M == 0) return COFREE_OK;
   const int64_t K = (int64_t)a.K1 + a.K2;
   const bool two = a.K2 > 0 && a.B2;  // the second segment has its own parameter matrix

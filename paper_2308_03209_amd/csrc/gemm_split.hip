@@ -845,17 +845,18 @@ bool gemm_split_fits(const GemmArgs& a) {
          (a.K2 == 0 || split_strides_ok(a.lda2, a.B2 ? a.ldb2 : 0));
 }
 
-size_t split_param_bytes(int32_t N, int64_t K1, int64_t K2) {
-  if (N <= 64) return 0;
+// The parameters are split by a launch of their own, of 6 us, where every workgroup would split them again: from 20 billion
+// operand pairs on (230k x 256 x 256: 231 -> 225 us and the launch; 230k x 256 x 602 496 -> 467, 470k x 512 x 512 1374 -> 1330, gated
+// 1465 -> 1359; 60k x 256 x 256 59.7 -> 58.1).
+size_t split_param_bytes(int64_t M, int32_t N, int64_t K1, int64_t K2) {
+  if (N <= 64 || (double)M * N * ((double)K1 + K2) < 2e10) return 0;
   const size_t images = (size_t)((N + TILE - 1) / TILE) * (size_t)((K1 + SBK - 1) / SBK + (K2 + SBK - 1) / SBK);
   return images * (STEP_IMAGE + 4);
 }
 
-// Whether the parameters are split by a launch of their own, of 6 us, where every workgroup would split them again: from
-// 20 billion operand pairs on (230k x 256 x 256: 231 -> 225 us and the launch; 230k x 256 x 602 496 -> 467, 470k x 512 x 512
-// 1374 -> 1330, gated 1465 -> 1359; 60k x 256 x 256 59.7 -> 58.1).
 static bool split_params_first(const GemmArgs& a) {
-  return a.param_scratch != nullptr && (double)a.M * a.N * ((double)a.K1 + a.K2) >= 2e10;
+  const size_t bytes = split_param_bytes(a.M, a.N, a.K1, a.K2);
+  return bytes > 0 && a.param_scratch && a.param_scratch_bytes >= bytes;
 }
 
 int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {

@@ -116,15 +116,16 @@ static bool conv_merged(const cofree_layer_desc& d) {
 static size_t max2(size_t a, size_t b) { return a > b ? a : b; }
 static size_t max3(size_t a, size_t b, size_t c) { return max2(a, max2(b, c)); }
 
-// largest copy of a parameter matrix - in bfloat16, or split into three of them - that any product of the layer needs
-static size_t param_scratch_bytes(const cofree_layer_desc& d) {
+// largest copy of a parameter matrix - in bfloat16, or split into three of them - that any product of the layer makes.  In
+// float32 it only saves time: a call whose workspace has no room for it does without.
+static size_t param_scratch_bytes(const cofree_layer_desc& d, int64_t n) {
   if (d.dtype != COFREE_BF16) {
     if (d.kind == COFREE_SAGE_MEAN)
-      return max3(split_param_bytes(d.d_msg, d.d_in, 0), split_param_bytes(d.d_out, d.d_msg, d.d_in),
-                  max2(split_param_bytes(d.d_msg, d.d_out, 0), split_param_bytes(d.d_in, d.d_out, d.d_msg)));
+      return max3(split_param_bytes(n, d.d_msg, d.d_in, 0), split_param_bytes(n, d.d_out, d.d_msg, d.d_in),
+                  max2(split_param_bytes(n, d.d_msg, d.d_out, 0), split_param_bytes(n, d.d_in, d.d_out, d.d_msg)));
     if (d.kind == COFREE_SAGE_CONV)
-      return max2(split_param_bytes(d.d_out, d.d_in, d.d_in), split_param_bytes(d.d_in, d.d_out, d.d_out));
-    return max2(split_param_bytes(d.d_out, d.d_in, 0), split_param_bytes(d.d_in, d.d_out, 0));
+      return max2(split_param_bytes(n, d.d_out, d.d_in, d.d_in), split_param_bytes(n, d.d_in, d.d_out, d.d_out));
+    return max2(split_param_bytes(n, d.d_out, d.d_in, 0), split_param_bytes(n, d.d_in, d.d_out, 0));
   }
   if (d.kind == COFREE_SAGE_MEAN)
     return max3(gemm_param_scratch_bytes(d.d_msg, d.d_in),
@@ -139,8 +140,9 @@ static size_t param_scratch_bytes(const cofree_layer_desc& d) {
 
 struct FwdPlan {
   void* T = nullptr;       // transform-first: norm * (H W^T) (GCN), H W_neigh^T (conventional GraphSAGE)
-  void* params = nullptr;  // bf16 copy of a parameter matrix
-  size_t bytes = 0;
+  void* params = nullptr;  // copy of a parameter matrix
+  size_t params_bytes = 0;
+  size_t bytes = 0, needed = 0;  // in all; of which a call cannot do without
 };
 
 static FwdPlan plan_fwd(const cofree_layer_desc& d, int64_t n, void* ws) {
@@ -148,8 +150,11 @@ static FwdPlan plan_fwd(const cofree_layer_desc& d, int64_t n, void* ws) {
   FwdPlan p;
   if ((d.kind == COFREE_GCN && gcn_transform_first(d)) || (d.kind == COFREE_SAGE_CONV && conv_transform_first(d)))
     p.T = c.take((size_t)n * d.d_out * elem_size(d.dtype));
-  p.params = c.take(param_scratch_bytes(d));
+  p.needed = c.used;
+  p.params_bytes = param_scratch_bytes(d, n);
+  p.params = c.take(p.params_bytes);
   p.bytes = c.used;
+  if (d.dtype == COFREE_BF16) p.needed = p.bytes;
   return p;
 }
 
@@ -157,6 +162,8 @@ struct BwdPlan {
   void *dP = nullptr, *dA = nullptr, *dZ = nullptr, *T = nullptr, *params = nullptr;
   // partials of up to three weight gradients (they stay until they are summed), of one bias gradient
   float *wg[3] = {nullptr, nullptr, nullptr}, *cs = nullptr;
+  size_t params_bytes = 0;
+  size_t needed = 0;  // bytes of the layer's own workspace that a call cannot do without
 };
 
 // c: what is dead when the layer is done; part: the partials (the same carver where a layer sums its own)
@@ -182,7 +189,10 @@ static BwdPlan plan_bwd(const cofree_layer_desc& d, int64_t n, Carver& c, Carver
     if (d.kind == COFREE_SAGE_CONV && !conv_merged(d)) p.wg[1] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
     if (d.kind == COFREE_GCN && gcn_transform_first(d)) p.cs = (float*)part.take(4 * colsum_workspace_floats(d.d_out));
   }
-  p.params = c.take(param_scratch_bytes(d));
+  p.needed = c.used;
+  p.params_bytes = param_scratch_bytes(d, n);
+  p.params = c.take(p.params_bytes);
+  if (d.dtype == COFREE_BF16) p.needed = c.used;
   return p;
 }
 
@@ -265,15 +275,16 @@ int32_t cofree_layer_fwd(const cofree_partition* part, const cofree_masks* masks
   COFREE_REQUIRE(H_in && H_out && params && saved, "layer_fwd: NULL argument");
   COFREE_REQUIRE(params->W && params->bW, "layer_fwd: W / bW is NULL");
   const FwdPlan fp = plan_fwd(d, g.n, workspace);
-  if (fp.bytes > 0 && (workspace == nullptr || workspace_bytes < fp.bytes))
+  if (fp.needed > 0 && (workspace == nullptr || workspace_bytes < fp.needed))
     return fail(COFREE_ENOMEM, "layer_fwd: workspace too small");
+  const bool copies = workspace != nullptr && workspace_bytes >= fp.bytes;
   hipStream_t s = (hipStream_t)stream;
   const int64_t n = g.n;
   const int32_t dt = d.dtype;
   auto gemm = [&]() {
     GemmArgs a;
     a.dtype = dt;
-    a.param_scratch = fp.params;
+    if (copies) a.param_scratch = fp.params, a.param_scratch_bytes = fp.params_bytes;
     a.M = n;
     return a;
   };
@@ -443,12 +454,13 @@ static int32_t layer_bwd(const cofree_partition* part, const cofree_masks* masks
   const int64_t n = g.n;
   Carver scratch(workspace);
   const BwdPlan p = plan_bwd(d, n, scratch, partials ? *partials : scratch);
-  if (workspace_bytes < scratch.used) return fail(COFREE_ENOMEM, "layer_bwd: workspace too small");
+  if (workspace_bytes < p.needed) return fail(COFREE_ENOMEM, "layer_bwd: workspace too small");
+  const bool copies = workspace_bytes >= scratch.used;
   const int32_t dt = d.dtype;
   auto gemm = [&]() {
     GemmArgs a;
     a.dtype = dt;
-    a.param_scratch = p.params;
+    if (copies) a.param_scratch = p.params, a.param_scratch_bytes = p.params_bytes;
     a.M = n;
     return a;
   };
