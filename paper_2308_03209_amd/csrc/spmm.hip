@@ -617,7 +617,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4
 // degree (processing order) without adding groups up at the end: a wavefront for every row and slice spent about half of its
 // instructions outside the gather (256 float32: 115k nodes, 3.5M entries 510 -> 342 us, 230k nodes, 14M entries 1645 -> 1515,
 // 9.4 TB/s of gathered rows; 256 bfloat16, which had no slices: 230k nodes 875 -> 690, 600k nodes, 15M entries 1026 -> 952).
-// Longer rows take a wavefront.  Rows that are no whole lines, or narrow ones, take the same teams without slices.
+// Longer rows take a wavefront, in which a neighbour has as many lanes as a row has pieces, or a slice, and float32 has a sum for
+// every load in flight: eight lanes whatever the row and one sum were up to 2.1 times as far from float64 as the row kernel is
+// (230k nodes, 14M entries, 4 float32: relative error of a mean over hubs 9.0e-8, now 4.4e-8, row kernel 4.4e-8) and slower where
+// most rows are long (60k nodes, 9M entries, 8 bfloat16 68 -> 48 us; 230k nodes 101 -> 86).
+// Rows that are no whole lines, or narrow ones, take the same teams without slices.
 
 // lane n of each team of LPS lanes, to all of the team (n < 8)
 template <int LPS, int N>
@@ -690,18 +694,20 @@ __device__ inline void gather_teams(const AggK<T>& p, const T* __restrict__ X, c
 }
 
 template <typename T, int LPS, bool DROP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 5))) void aggregate_sliced_kernel(const AggK<T> p, int slice_bits, uint32_t long_units) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 5))) void aggregate_sliced_kernel(
+    const AggK<T> p, int slice_bits, uint32_t long_units, int long_bits) {
   constexpr int VEC = RowIO<T>::WIDE;
   constexpr int NG = 64 / LPS;
   constexpr int UNR = 4;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int sub = lane % LPS, grp = lane / LPS;
   const uint32_t xcd = blockIdx.x & 7u, unit = ((blockIdx.x >> 3) << (3 - slice_bits)) + (xcd >> slice_bits);
+  const bool is_long = unit < long_units;  // uniform over the block
+  const int bits = is_long ? long_bits : LPS == 8 ? 3 : LPS == 16 ? 4 : LPS == 32 ? 5 : 6;  // 2^bits lanes share a neighbour
+  const int sub = lane & ((1 << bits) - 1), grp = lane >> bits;
   // a lane's columns: whole lines of a slice, or any row that is not cut (the last window moved, lanes past the end idle)
   const LaneCols lc = lane_cols<VEC>(p.width, ((int)(xcd & ((1u << slice_bits) - 1u)) * LPS + sub) * VEC);
   const int c0 = lc.avail > 0 ? lc.c0 : p.width - VEC;
   const T* __restrict__ X = p.X + c0;
-  const bool is_long = unit < long_units;  // uniform over the block
   const uint32_t limit = is_long ? (uint32_t)p.n_wave : (uint32_t)p.n;
   const uint32_t first = is_long ? unit * 4 + wave : (uint32_t)p.n_wave + ((unit - long_units) * 4 + wave) * NG;
   if (first >= limit) return;
@@ -723,17 +729,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     else gather_teams<T, LPS, 0>(p, X, col, vals, cnt, lane, acc);
     if (!has || lc.avail <= 0) return;
   } else {
+    constexpr int SUMS = VEC == 4 ? UNR : 1;
+    float part[SUMS][VEC];
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+    for (int t = 0; t < SUMS; ++t)
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) part[t][i] = 0.f;
     // every load of the loop is unconditional (see RowIO): ids past the end of the row repeat its last id and are
     // zeroed after the load
-    for (int e = grp; e < cnt; e += NG * UNR) {
+    const int ng = 64 >> bits;
+    for (int e = grp; e < cnt; e += ng * UNR) {
       uint32_t u[UNR];
       float f[UNR];
       typename RowIO<T>::Raw v[UNR];
 #pragma unroll
       for (int t = 0; t < UNR; ++t) {
-        const int ec = e + t * NG < cnt ? e + t * NG : cnt - 1;
+        const int ec = e + t * ng < cnt ? e + t * ng : cnt - 1;
         u[t] = (uint32_t)col[ec];
         f[t] = 1.f;
         if (vals) f[t] = vals[ec];
@@ -744,10 +755,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
         v[t] = RowIO<T>::load_raw(row_at(X, u[t], p.ldx));
       }
 #pragma unroll
-      for (int t = 0; t < UNR; ++t) RowIO<T>::fma_raw(acc, f[t], RowIO<T>::keep_if(e + t * NG < cnt, v[t]));
+      for (int t = 0; t < UNR; ++t) RowIO<T>::fma_raw(part[t % SUMS], f[t], RowIO<T>::keep_if(e + t * ng < cnt, v[t]));
     }
 #pragma unroll
-    for (int off = LPS; off < 64; off <<= 1) {
+    for (int i = 0; i < VEC; ++i) {
+      if constexpr (SUMS == 4) acc[i] = (part[0][i] + part[1][i]) + (part[2][i] + part[3][i]);
+      else acc[i] = part[0][i];
+    }
+    for (int off = 1 << bits; off < 64; off <<= 1) {
 #pragma unroll
       for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
     }
@@ -896,7 +911,7 @@ static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCos
 }
 
 template <typename T, bool DROP>
-static int32_t launch_sliced(const AggK<T>& k, int lps, int slice_bits, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
+static int32_t launch_sliced(const AggK<T>& k, int lps, int long_bits, int slice_bits, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
   const int64_t long_units = (k.n_wave + 3) / 4, rows = 4 * (64 / lps), parts = 8 >> slice_bits;
   const int64_t units = long_units + (k.n - k.n_wave + rows - 1) / rows;
   const int64_t blocks = (units + parts - 1) / parts * 8;
@@ -907,10 +922,10 @@ static int32_t launch_sliced(const AggK<T>& k, int lps, int slice_bits, hipStrea
            (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   switch (lps) {
-    case 8: aggregate_sliced_kernel<T, 8, DROP><<<grid, 256, 0, stream>>>(k, slice_bits, (uint32_t)long_units); break;
-    case 16: aggregate_sliced_kernel<T, 16, DROP><<<grid, 256, 0, stream>>>(k, slice_bits, (uint32_t)long_units); break;
-    case 32: aggregate_sliced_kernel<T, 32, DROP><<<grid, 256, 0, stream>>>(k, slice_bits, (uint32_t)long_units); break;
-    case 64: aggregate_sliced_kernel<T, 64, DROP><<<grid, 256, 0, stream>>>(k, slice_bits, (uint32_t)long_units); break;
+    case 8: aggregate_sliced_kernel<T, 8, DROP><<<grid, 256, 0, stream>>>(k, slice_bits, (uint32_t)long_units, long_bits); break;
+    case 16: aggregate_sliced_kernel<T, 16, DROP><<<grid, 256, 0, stream>>>(k, slice_bits, (uint32_t)long_units, long_bits); break;
+    case 32: aggregate_sliced_kernel<T, 32, DROP><<<grid, 256, 0, stream>>>(k, slice_bits, (uint32_t)long_units, long_bits); break;
+    case 64: aggregate_sliced_kernel<T, 64, DROP><<<grid, 256, 0, stream>>>(k, slice_bits, (uint32_t)long_units, long_bits); break;
     default: return fail(COFREE_EINVAL, "internal: bad lanes-per-slice");
   }
   return COFREE_OK;
@@ -1007,6 +1022,8 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
     slice_bits = 0, team_lanes = 8;
     while (team_lanes < pieces) team_lanes *= 2;
   }
+  int long_bits = 0;  // a neighbour of a long row takes as many lanes as the row has pieces, but a whole slice
+  while ((1 << long_bits) < (teams ? pieces : team_lanes)) ++long_bits;
 
   // Per-source factors of a large graph are read per entry: the per-node vector no longer stays in L2 there, and
   // every neighbour's factor would cost a memory access of its own beside the row it scales (28M-node partition,
@@ -1063,7 +1080,7 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   if (sliced || teams) {
     k.n_block = 0;
     k.n_wave = (int32_t)(std::max(a.g.n_block, n_hub) - n_hub);  // longer rows are never left to a team
-    COFREE_TRY((launch_sliced<T, DROP>(k, team_lanes, slice_bits, stream, cost, a.g.nnz - hub_nnz)));
+    COFREE_TRY((launch_sliced<T, DROP>(k, team_lanes, long_bits, slice_bits, stream, cost, a.g.nnz - hub_nnz)));
     COFREE_HIP_CHECK(hipGetLastError());
     return COFREE_OK;
   }

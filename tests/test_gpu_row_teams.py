@@ -52,6 +52,23 @@ def test_teams_of_equal_rows_and_column_slices(env, launch, dtype, width, masked
     check(env, dtype, width, masked)
 
 
+@pytest.mark.parametrize("launch,width", [("2", w) for w in (4, 8, 16, 31, 64)] + [("8", w) for w in (64, 128, 256, 512)])
+def test_float32_sums_of_long_rows_are_short(env, launch, width, monkeypatch):
+    """4000 neighbours of 1 + 0.45 2^-15: a chain of additions loses the fraction from 256 on (6e-6 of the sum in eight chains of
+    500), one of up to 250 loses at most 1.3e-6."""
+    B, torch = env["B"], env["torch"]
+    monkeypatch.setenv("COFREE_AGG_SLICES", launch)
+    print(f"[case] long row in float32, launch {launch}, {width} columns", flush=True)
+    n = 4_100
+    spokes = np.arange(1, 4_001, dtype=np.int64)
+    ring = np.arange(4_000, n - 1, dtype=np.int64)
+    P = B.build_partition(n, np.concatenate([np.zeros_like(spokes), ring]), np.concatenate([spokes, ring + 1]), 1, 0, 3)
+    X = torch.full((n, width), 1.0 + 0.45 * 2.0 ** -15, device="cuda")
+    Y = torch.empty_like(X)
+    B.aggregate(P, None, 0, B.AGG_MEAN, X, Y, width, B.F32)
+    assert float((Y[0].double() / X[0].double() - 1.0).abs().max()) < 2e-6
+
+
 @pytest.mark.parametrize("launch", ["2", "8"])
 def test_teams_on_a_mask_that_drops_everything(env, launch, monkeypatch):
     B, torch = env["B"], env["torch"]
