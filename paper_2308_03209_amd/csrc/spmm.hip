@@ -456,8 +456,7 @@ __device__ inline void gather_row(const AggK<T>& p, const int32_t* __restrict__ 
 // The same for a whole wavefront of at least eight neighbour groups (narrow rows), `wave` of `waves` that share the row: the
 // groups read their neighbours' ids themselves, which are consecutive.  Ids handed out 64 at a time leave most loads of so
 // many groups without a neighbour.  Rows of less than one access have an instance for every width: element loads under a
-// condition on the width wait for each other (bfloat16, 230k nodes, 14M entries: 3 columns 302 -> 108 us, 8 columns 183 -> 136;
-// 30k nodes, 14M entries: 3 columns 162 -> 44, 8 columns 95 -> 50).
+// condition on the width wait for each other (3 bfloat16 columns: 230k nodes, 14M entries 302 -> 108 us, 30k nodes 162 -> 44).
 template <typename T, int LPS, int TINY>
 __device__ inline void gather_narrow(const AggK<T>& p, const int32_t* __restrict__ col, const float* __restrict__ in_vals, int cnt,
                                      int wave, int waves, int lane, int cread, float (&acc)[RowIO<T>::WIDE]) {
@@ -991,16 +990,25 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
 
   // High average degree: teams of lanes per row in wavefronts of rows of nearly equal degree (aggregate_sliced_kernel), cut into
   // up to 8 XCD-affine column slices of whole 128-byte lines, two at least; else a wavefront for every row.
-  //  * Slices, of rows of four lines and more from a matrix of one XCD's 4 MB L2 on (8k nodes, 300k entries, 256 float32 30 -> 22 us;
-  //    115k nodes, 3.5M entries 472 -> 344; 230k nodes, 14M entries 1870 -> 1519), of two lines from 12 MB on (60k nodes, 2M
-  //    entries, 128 bfloat16 60 -> 52; at 7.7 MB 27 -> 30), up to 350 MB: beyond the memory-side cache their pieces of rows cost
-  //    more than the hits are worth (600k nodes, 15M entries, 128 float32, 307 MB: 946 against 986; 256 float32 2219 against 2131).
+  //  * Slices, of rows of four lines and more from a matrix of one XCD's 4 MB L2 on (8k nodes, 300k entries, 256 float32 30 -> 21 us;
+  //    115k nodes, 3.5M entries 472 -> 344; 230k nodes, 14M entries 1805 -> 1455), of two lines from 12 MB on (60k nodes, 2.2M entries,
+  //    128 bfloat16 59 -> 52; 8 MB 36 -> 38).  Up to 420 MB in float32, 500 MB in bfloat16: the rows that are gathered most stay in
+  //    the memory-side cache of 256 MB, beyond that pieces of one line cost more than the hits are worth (20 to 40 entries a node;
+  //    128 float32 358 MB 1.00 and 0.98 of the time of a wavefront for every row, 410 MB 1.00 and 0.97, 435 MB 1.02 and 0.99, 512 MB
+  //    1.03 and 1.00; 256 bfloat16 410 MB 0.95 and 0.91, 512 MB 0.96 and 0.93; 512 bfloat16 410 MB 0.89 and 0.90, 461 MB 0.97 and
+  //    1.01, 614 MB 1.07 and 1.03, 1024 MB 1.16 and 1.13; GCN and mean).
+  //  * float32 rows of eight lines and more are cut whatever their number: a wavefront for every row sums all of a neighbour
+  //    list in one chain, up to 6.8 times as far from float64 (600k nodes, 15M entries, 256 float32: relative error of a mean over
+  //    hubs 6.1e-7 and 0.9e-7).  256 float32 461 MB 1.02 of the time, 614 MB 1.12, 1024 MB 1.16; 512 float32, in slices of two
+  //    lines, 471 MB 0.76, 1229 MB 0.92, 1638 MB 1.00, 2048 MB 1.08.
   //  * Without slices, rows of up to 16 pieces of 16 bytes that are no whole lines or lie beyond that: a team walks a row alone, so
-  //    a launch has to outlast 128 neighbours - up to eight pieces from two million entries on (115k nodes, 3.5M entries, 47
-  //    bfloat16 112 -> 70; 600k nodes, 15M entries 547 -> 360; 60k nodes, 2M entries 64 -> 60; 20k nodes, 1.2M entries, 8
-  //    float32 16.7 -> 20.6), wider rows from eight million on (230k nodes, 14M entries, 41 float32 435 -> 397; 300k nodes, 9M
-  //    entries 330 -> 312; 115k nodes, 7M entries 175 -> 180).  Wider still, a wavefront has two rows and gains nothing (100
-  //    float32: 230k nodes, 14M entries 865 -> 803, 300k nodes, 9M entries 628 -> 643).
+  //    a launch has to outlast 128 neighbours - up to four pieces from 2^21 entries on (60k nodes, 2.2M entries, 16 float32 36 -> 28
+  //    us; 115k nodes, 3.5M entries, 8 bfloat16 72 -> 31; 600k nodes, 15M entries 337 -> 149), up to eight from 3 * 2^20 on (115k
+  //    nodes, 3.5M entries, 47 bfloat16 104 -> 78, 40 bfloat16 77 -> 67; 60k nodes, 2.2M entries 47 -> 50), wider rows from 2^23
+  //    on (230k nodes, 14M entries, 41 float32 435 -> 397; 300k nodes, 9M entries 330 -> 312; 115k nodes, 7M entries 175 -> 180), and
+  //    where no factors are read beside the ids, below an average of 48 neighbours (33 float32: 300k nodes, 9M entries 232 -> 228;
+  //    230k nodes, 14M entries 299 -> 308; 60k nodes, 9M entries 136 -> 147).  Wider still, a wavefront has two rows and gains nothing
+  //    (100 float32: 230k nodes, 14M entries 865 -> 803, 300k nodes, 9M entries 628 -> 643).
   // Below an average of 16 neighbours neither is faster than the row kernel (600k nodes, 7M entries: 1.00 to 1.15 of its time).
   const bool dense_rows = a.g.nnz / a.g.n >= AGG_LONG_MIN;
   const int64_t row_bytes = a.width * (int64_t)sizeof(T), lines = row_bytes / 128;
@@ -1009,8 +1017,10 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   const bool sliceable = a.g.order != nullptr && lines * 128 == row_bytes && lines >= 2 && lines <= 64 && (lines & (lines - 1)) == 0;
   const bool teamable = a.g.order != nullptr && a.width >= WIDE && pieces <= 32;
   bool waves = dense_rows;
-  bool sliced = dense_rows && sliceable && matrix >= (lines >= 4 ? 4e6 : 12e6) && matrix <= 350e6;
-  bool teams = dense_rows && teamable && !sliced && pieces <= 16 && a.g.nnz >= (pieces <= 8 ? 1 << 21 : 1 << 23);
+  bool sliced = dense_rows && sliceable && matrix >= (lines >= 4 ? 4e6 : 12e6) &&
+                (sizeof(T) == 4 ? lines >= 8 || matrix <= 420e6 : matrix <= 500e6);
+  bool teams = dense_rows && teamable && !sliced && pieces <= 16 && a.g.nnz >= (pieces <= 4 ? 1 << 21 : pieces <= 8 ? 3 << 20 : 1 << 23) &&
+               (pieces <= 8 || a.in_scale || a.g.nnz / a.g.n < 48);
   if (const char* env = getenv("COFREE_AGG_SLICES")) {  // 0 = by degree, 1 = a wavefront per row, 2 = teams, 8 = sliced
     const int v = atoi(env);
     if (v == 0 || v == 1) waves = v == 1, sliced = teams = false;

@@ -69,6 +69,47 @@ def test_float32_sums_of_long_rows_are_short(env, launch, width, monkeypatch):
     assert float((Y[0].double() / X[0].double() - 1.0).abs().max()) < 2e-6
 
 
+@pytest.fixture(scope="module")
+def circulants(env):
+    """Graphs in which node i is joined to the k nodes on either side of it: 2 k n entries."""
+    made = {}
+
+    def get(n, k):
+        if (n, k) not in made:
+            i = np.repeat(np.arange(n, dtype=np.int64), k)
+            made.clear()
+            made[n, k] = env["B"].build_partition(n, i, (i + np.tile(np.arange(1, k + 1, dtype=np.int64), n)) % n, 1, 0, 3)
+        return made[n, k]
+    return get
+
+
+# launches: "rows" the row kernel, a number: lanes of a team, or of a slice
+@pytest.mark.parametrize("n,k,dtype,width,mean,gcn",
+                         [(65_535, 16, "f32", 4, "rows", "rows"), (65_536, 16, "f32", 4, 8, 8), (65_536, 16, "f32", 16, 8, 8),
+                          (65_536, 16, "bf16", 8, 8, 8), (65_536, 16, "f32", 17, "rows", "rows"), (65_535, 24, "f32", 17, "rows", "rows"),
+                          (65_536, 24, "f32", 17, 8, 8), (65_536, 24, "bf16", 64, 8, 8), (65_536, 24, "f32", 33, "rows", "rows"),
+                          (262_144, 16, "f32", 33, 16, 16), (131_072, 32, "f32", 33, "rows", 16), (131_072, 32, "bf16", 72, "rows", 16),
+                          (7_812, 8, "f32", 128, "rows", "rows"), (7_813, 8, "f32", 128, 8, 8), (7_813, 7, "f32", 128, "rows", "rows"),
+                          (46_874, 8, "f32", 64, "rows", "rows"), (46_875, 8, "f32", 64, 8, 8), (46_875, 8, "f32", 96, "rows", "rows"),
+                          (60_000, 8, "f32", 2048, 64, 64), (60_000, 8, "bf16", 4096, 64, 64), (62_000, 8, "bf16", 4096, "rows", "rows")])
+def test_which_launch_of_dense_graphs(env, circulants, n, k, dtype, width, mean, gcn):
+    """The launch on either side of the limits in entries, bytes and pieces; float32 rows of eight lines are cut at any size."""
+    B, torch = env["B"], env["torch"]
+    print(f"[case] launch for {n} nodes of {2 * k} neighbours, {width} {dtype} columns", flush=True)
+    P = circulants(n, k)
+    td, code = (torch.float32, B.F32) if dtype == "f32" else (torch.bfloat16, B.BF16)
+    X = torch.ones(n, width, device="cuda", dtype=td)
+    for mode, want in ((B.AGG_MEAN, mean), (B.AGG_GCN, gcn)):
+        Y = torch.zeros_like(X)
+        B.profile_enable(True)
+        B.aggregate(P, None, 0, mode, X, Y, width, code)
+        names = list(B.profile_read())
+        B.profile_enable(False)
+        assert all(name.startswith("aggregate_kernel<" if want == "rows" else "aggregate_sliced_kernel<") for name in names), names
+        assert want == "rows" or f",{want}," in names[0], names
+        assert float((Y.float() - 1).abs().max()) <= (2e-6 if dtype == "f32" else 2.0 ** -8)
+
+
 @pytest.mark.parametrize("launch", ["2", "8"])
 def test_teams_on_a_mask_that_drops_everything(env, launch, monkeypatch):
     B, torch = env["B"], env["torch"]
