@@ -137,7 +137,7 @@ def test_aggregate_hub_rows_split_over_a_workgroup(env, hubs, dtype, width, mask
 @pytest.mark.parametrize("launch", ["0", "1", "8"])
 def test_aggregate_hub_rows_with_forced_launches_and_without_buckets(env, hubs, launch, monkeypatch):
     """The hub launch beside each forced kernel choice for the other rows (row kernel, neighbour-group kernel,
-    its XCD-sliced form, where hub rows are met in natural order and skipped), and the bucket-free launches."""
+    its XCD-sliced form, which starts behind the hub rows), and the bucket-free launches."""
     B, torch = env["B"], env["torch"]
     P, O = hubs["P"], hubs["O"]
     g = o_dropedge.full_graph(O)

@@ -69,6 +69,43 @@ def test_float32_sums_of_long_rows_are_short(env, launch, width, monkeypatch):
     assert float((Y[0].double() / X[0].double() - 1.0).abs().max()) < 2e-6
 
 
+@pytest.mark.parametrize("launch,dtype,width",
+                         [("2", "f32", w) for w in (4, 5, 12, 33, 36, 47, 64)] + [("2", "bf16", w) for w in (8, 12, 44, 47, 64, 100, 172)] +
+                         [("8", "f32", w) for w in (64, 128, 256, 512)] + [("8", "bf16", w) for w in (128, 256, 512, 1024)])
+def test_what_follows_a_sum_in_teams_and_slices(env, launch, dtype, width, monkeypatch):
+    """Bias, ReLU and dropout of a layer that transforms first, the gate of the layer below in the backward pass of one that
+    aggregates first: as in the row kernel, which other tests hold against the oracle, up to the order of the sums."""
+    B, torch, P = env["B"], env["torch"], env["P"]
+    print(f"[case] epilogue of launch {launch}, {width} {dtype} columns", flush=True)
+    n, q = P.num_nodes, 0.3
+    td, code, tol = (torch.float32, B.F32, 1e-5) if dtype == "f32" else (torch.bfloat16, B.BF16, 2.0 ** -7)
+    gen = torch.Generator(device="cuda").manual_seed(width)
+    rand = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    first = B.layer_desc(B.GCN, width + 8, 0, width, 1, q, 2, 77, 5, code)
+    H, W, b = rand(n, width + 8).to(td), rand(width, width + 8) / width ** 0.5, rand(width)
+    last = B.layer_desc(B.GCN, width, 0, width + 4, 0, 0.0, 3, 77, 5, code, B.GRAD_IN_GATED, q)
+    gate, dY = rand(n, width).clamp_min(0.0).to(td), rand(n, width + 4).to(td)
+    W2, A = rand(width + 4, width) / width ** 0.5, rand(n, width).to(td)
+    ws = torch.empty(max(B.layer_workspace_bytes(first, n, False), B.layer_workspace_bytes(last, n, True)), dtype=torch.uint8, device="cuda")
+    g = {"W": torch.empty_like(W2), "bW": torch.empty(width + 4, device="cuda")}
+    got = []
+    for env_launch in ("0", launch):
+        monkeypatch.setenv("COFREE_AGG_SLICES", env_launch)
+        Y, dX = torch.full((n, width), float("nan"), device="cuda", dtype=td), torch.full((n, width), float("nan"), device="cuda", dtype=td)
+        B.profile_enable(True)
+        B.layer_fwd(P, None, 0, first, H, {"W": W, "bW": b}, Y, {}, ws)
+        B.layer_bwd(P, None, 0, last, gate, dY, {"W": W2, "bW": g["bW"]}, {"A": A}, dY, dX, g, False, ws)
+        names = [x for x in B.profile_read() if x.startswith("aggregate")]
+        B.profile_enable(False)
+        assert any(x.startswith("aggregate_sliced_kernel") for x in names) == (env_launch != "0"), names
+        got.append((Y.float(), dX.float()))
+    for (a, c), what in zip(zip(*got), ("output", "gradient")):
+        assert bool(torch.isfinite(a).all()) and bool(torch.isfinite(c).all()), what
+        assert float(((a == 0) != (c == 0)).float().mean()) <= 1e-5, what  # but for sums within rounding of zero
+        assert float((a == 0).float().mean()) > 0.4, what  # ReLU and dropout, or the gate, were there
+        assert float((a - c).norm()) <= tol * float(a.norm()) and float((a - c).abs().max()) <= 4 * tol * float(a.abs().max()), what
+
+
 @pytest.fixture(scope="module")
 def circulants(env):
     """Graphs in which node i is joined to the k nodes on either side of it: 2 k n entries."""
