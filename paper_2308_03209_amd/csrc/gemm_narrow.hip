@@ -494,6 +494,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB == 4 ? 2
       __builtin_amdgcn_sched_barrier(0);
     }
     for (; k0 < len; k0 += 4 * WGROUP) {
+      float group[CS] = {};  // column sums of this group, so that csum is rounded once for it
 #pragma unroll
       for (int s = 0; s < WSTEPS; ++s) {
         Cols<NA>& u = w[s];
@@ -512,14 +513,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB == 4 ? 2
         if (do_colsum) {
           if (p.rows_narrow) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b) csum[b] += v.v[b];
+            for (int b = 0; b < NB; ++b) group[b] += v.v[b];
           } else {
 #pragma unroll
-            for (int a = 0; a < NA; ++a) csum[a] += u.v[a];
+            for (int a = 0; a < NA; ++a) group[a] += u.v[a];
           }
         }
         load(k0 + 4 * WGROUP, s);  // into the registers just used
       }
+#pragma unroll
+      for (int c = 0; c < CS; ++c) csum[c] += group[c];
     }
   }
   // register v of lane (g, r) is row 4 g + v, column r of its block

@@ -161,3 +161,22 @@ def test_two_weight_gradients_in_one_launch(env, kind, d_in, d_msg, d_out, monke
         got.append(g)
     for k in p:
         assert bool(torch.isfinite(got[0][k]).all()) and torch.equal(got[0][k], got[1][k]), k
+
+
+def test_bias_gradients_are_rounded_once_a_group_of_nodes(env):
+    """Column sums beside a weight gradient, over 24 draws of 100,000 x 47: relative error 1.75e-7 where 16 nodes at a time were added
+    to a sum, 2.0e-7 where every node is (3 % of it is the spread of the estimate)."""
+    B, torch = env["B"], env["torch"]
+    n, d_in, d_out = 100_000, 512, 47
+    print("[case] bias gradients of a narrow layer", flush=True)
+    P, desc = ring(B, n), B.layer_desc(B.SAGE_CONV, d_in, 0, d_out)
+    ws = torch.empty(B.layer_workspace_bytes(desc, n, True), dtype=torch.uint8, device="cuda")
+    H, Y = torch.zeros(n, d_in, device="cuda"), torch.zeros(n, d_out, device="cuda")
+    p = {"W": torch.zeros(d_out, 2 * d_in, device="cuda"), "bW": torch.zeros(d_out, device="cuda")}
+    g, err, size = {k: torch.empty_like(v) for k, v in p.items()}, 0.0, 0.0
+    for seed in range(24):
+        dY = torch.randn(n, d_out, generator=torch.Generator(device="cuda").manual_seed(seed), device="cuda")
+        B.layer_bwd(P, None, 0, desc, H, Y, p, {}, dY, None, g, False, ws)
+        ref = dY.double().sum(0)
+        err, size = err + float((g["bW"].double() - ref).square().sum()), size + float(ref.square().sum())
+    assert (err / size) ** 0.5 < 1.85e-7
