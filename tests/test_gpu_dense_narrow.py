@@ -96,7 +96,10 @@ def test_non_finite_operands_stay_in_their_rows_and_columns(env):
                          # k-major parameters in two segments beyond LDS, in one round and in two; a short segment before a long one;
                          # tiles in both orders and accumulating
                          [("sage_conv", 5_003, 48, 2, 600), ("sage_conv", 70_003, 20, 2, 700), ("sage", 3_001, 40, 100, 2),
-                          ("sage_conv", 60_001, 50, 2, 130), ("sage_conv", 60_001, 150, 2, 50)])
+                          ("sage_conv", 60_001, 50, 2, 130), ("sage_conv", 60_001, 150, 2, 50)] +
+                         # wide input gradients from 8 to 15 k, wide weight gradients over 5 to 13 nodes (gemm_split.hip)
+                         [("gcn", 3_001, 100, 2, 8), ("sage_conv", 3_001, 130, 2, 13), ("gcn", 257, 70, 2, 15), ("gcn", 300, 80, 2, 16),
+                          ("gcn", 5, 65, 2, 66), ("gcn", 9, 65, 2, 66), ("gcn", 13, 65, 2, 130)])
 def test_layers(env, kind, n, d_in, d_msg, d_out):
     from oracle import dropedge as o_dropedge
     from oracle import layers as o_layers
