@@ -132,24 +132,18 @@ struct Group {
 // had are zero on the way to LDS (ONLY_PART).  In a range of less than one step the second group of eight is the range's last
 // eight, of which the ones that the first group has are zero; fewer than eight k are read at clamped places.
 
-// first k of a step's window (k_len >= 16)
-__device__ inline int window_start(int t, int k_len) {
-  const int last = k_len - SBK;
-  return t * SBK < last ? t * SBK : last;
-}
-// a thread's eight k of step t: the first, and the k from which on they count (up to k_len)
-struct Share {
-  int first, from;
-  __device__ Share(int t, int k_len, int kq) {
-    if (k_len >= SBK) {
-      first = window_start(t, k_len) + kq;
-      from = t * SBK;
-    } else {
-      first = k_len >= 8 && kq > k_len - 8 ? k_len - 8 : kq;
-      from = kq;
-    }
-  }
+// Of the eight places from kq on that a thread has in a step's window, those that count: lo <= place < hi.  start: the k of
+// place 0, but in short ranges the thread's places start at short_first.
+struct Window {
+  int start, lo, hi;
 };
+__device__ inline Window window_of(int t, int k_len, int kq) {
+  const int k0 = t * SBK, last = k_len - SBK;
+  if (last < 0) return k_len < 8 ? Window{0, 0, k_len} : Window{0, kq == 0 ? 0 : 24 - k_len, SBK};
+  const int start = k0 < last ? k0 : last;
+  return Window{start, k0 - start, SBK};
+}
+__device__ inline int short_first(int k_len, int kq) { return k_len >= 8 && kq > k_len - 8 ? k_len - 8 : kq; }
 
 // the bits that are set in any of four values
 __device__ inline uint32_t any_bit(float a, float b, float c, float d) {
@@ -175,23 +169,23 @@ struct SplitKContig {
     off = (uint32_t)(r < last ? r : last) * (uint32_t)ld * 4u + (k_len < SBK ? 0u : (uint32_t)kq * 4u);
   }
   __device__ void load(int t, Raw& w) const {
-    const char* const p = base + (int64_t)window_start(t, k_len) * 4;
+    const char* const p = base + (int64_t)window_of(t, k_len, 0).start * 4;
     w.x[0] = *reinterpret_cast<const float4u*>(p + off);
     w.x[1] = *reinterpret_cast<const float4u*>(p + off + 16u);
   }
   __device__ void load_short(Raw& w) const {  // 8 <= k_len < 16
-    const char* const p = base + (off + (uint32_t)Share(0, k_len, kq).first * 4u);
+    const char* const p = base + (off + (uint32_t)short_first(k_len, kq) * 4u);
     w.x[0] = *reinterpret_cast<const float4u*>(p);
     w.x[1] = *reinterpret_cast<const float4u*>(p + 16);
   }
-  __device__ float value(const Share& in, int c, const Raw& w) const {
-    return in.first + c >= in.from && in.first + c < k_len ? w.x[c >> 2][c & 3] : 0.f;
+  __device__ float value(const Window& in, int c, const Raw& w) const {
+    return kq + c >= in.lo && kq + c < in.hi ? w.x[c >> 2][c & 3] : 0.f;
   }
   // the q-th pair of the share; ODD: with the other sign in odd rows
   template <bool ODD, bool ONLY_PART>
   __device__ void pair(int q, int tid, int t, const Raw& w, uint32_t, Group& g) const {
     const uint32_t flip = ODD ? (uint32_t)tid << 30 & 0x80000000u : 0u;
-    const Share in(t, k_len, kq);
+    const Window in = window_of(t, k_len, kq);
     float e[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -227,25 +221,23 @@ struct SplitKMajor {
     off = (uint32_t)(i < extent - 1 ? i : extent - 1) * 4u;
   }
   __device__ void load(int t, Raw& w) const {
-    const float* row = base + (int64_t)(window_start(t, k_len) + kq) * ld;
+    const float* row = base + (int64_t)(window_of(t, k_len, 0).start + kq) * ld;
 #pragma unroll
     for (int c = 0; c < 8; ++c, row += ld) w.x[c] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + off);
   }
   __device__ void load_short(Raw& w) const {  // k_len < 16
-    const int first = Share(0, k_len, kq).first;
+    const int first = short_first(k_len, kq);
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       const float* const row = base + (int64_t)(first + c < k_len ? first + c : k_len - 1) * ld;
       w.x[c] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + off);
     }
   }
-  __device__ float value(const Share& in, int c, const Raw& w) const {
-    return in.first + c >= in.from && in.first + c < k_len ? w.x[c] : 0.f;
-  }
+  __device__ float value(const Window& in, int c, const Raw& w) const { return kq + c >= in.lo && kq + c < in.hi ? w.x[c] : 0.f; }
   // sign: 0 or the sign bit, on every element
   template <bool, bool ONLY_PART>
   __device__ void pair(int q, int, int t, const Raw& w, uint32_t sign, Group& g) const {
-    const Share in(t, k_len, kq);
+    const Window in = window_of(t, k_len, kq);
     float e[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -260,7 +252,7 @@ struct SplitKMajor {
   // sum of the thread's eight k (weight gradients: column sums of operand A)
   template <bool ONLY_PART>
   __device__ float sum(int t, const Raw& w) const {
-    const Share in(t, k_len, kq);
+    const Window in = window_of(t, k_len, kq);
     float s = 0.f;
 #pragma unroll
     for (int c = 0; c < 8; ++c) s += ONLY_PART ? value(in, c, w) : w.x[c];
@@ -403,13 +395,13 @@ __device__ inline void run_split(const MA& ma, const MB& mb, int k_len, unsigned
   if (k_len < SBK) {
     ma.load_short(ra);
     mb.load_short(rb);
+    ra1 = ra, rb1 = rb;
   } else {
+    const int t = n > 1 ? 1 : 0;  // the only step twice: under a condition, step 0 would wait for step 1 (gradients 1-2 % slower)
     ma.load(0, ra);
     mb.load(0, rb);
-  }
-  if (n > 1) {
-    ma.load(1, ra1);
-    mb.load(1, rb1);
+    ma.load(t, ra1);
+    mb.load(t, rb1);
   }
   __syncthreads();  // whoever used the LDS before is done
   unsigned char *d0 = smem, *d1 = smem + STAGE, *d2 = smem + 2 * STAGE;  // steps t, t + 1, t + 2
@@ -495,15 +487,17 @@ __global__ __launch_bounds__(256) void split_params_kernel(const SplitParamsK p)
   const int seg = step >= p.steps[0], t = step - (seg ? p.steps[0] : 0);
   // k-contiguous sources: neighbouring threads read the two halves of a row
   const int kg = p.k_major ? tid / TILE : tid & 1, row = p.k_major ? tid % TILE : tid >> 1;
-  const Share in(t, p.k_len[seg], kg * 8);
+  const int k_len = p.k_len[seg];
+  const Window in = window_of(t, k_len, kg * 8);
+  const int first = k_len < SBK ? short_first(k_len, kg * 8) : in.start + kg * 8;
   const int64_t j = (int64_t)tile * TILE + row, ldb = p.ldb[seg];
   const float* const B = p.B[seg];
   float e[8];
   uint32_t bits = 0;
 #pragma unroll
   for (int c = 0; c < 8; ++c) {
-    const int k = in.first + c;
-    e[c] = j < p.N && k >= in.from && k < p.k_len[seg] ? (p.k_major ? B[k * ldb + j] : B[j * ldb + k]) : 0.f;
+    const int k = first + c, place = kg * 8 + c;
+    e[c] = j < p.N && place >= in.lo && place < in.hi ? (p.k_major ? B[k * ldb + j] : B[j * ldb + k]) : 0.f;
     bits |= __float_as_uint(e[c]);
   }
   Group g;
