@@ -96,6 +96,23 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
 }
 __device__ inline bf16_t f32_to_bf16(float f) { return (bf16_t)(pack_bf16x2(f, 0.f) & 0xffffu); }
 
+// ---- results past the caches --------------------------------------------------------------------
+// A result that does not fit the memory-side cache (256 MB) beside the operands of its launch only pushes them out.
+constexpr double STREAM_RESULT_MIN = 160e6;  // bytes
+inline bool stream_result(double bytes) { return bytes >= STREAM_RESULT_MIN; }
+// One store, past the caches where `stream` (uniform).  The assembler comments keep the compiler from moving the two stores
+// together in front of or behind the branch, which loses the hint.  (A macro: a template would drop the type's alignment.)
+#define COFREE_STORE_PIECE(p, x, stream)    \
+  do {                                      \
+    if (stream) {                           \
+      asm volatile("; past the caches");    \
+      __builtin_nontemporal_store((x), (p)); \
+      asm volatile("; end");                \
+    } else {                                \
+      *(p) = (x);                           \
+    }                                       \
+  } while (0)
+
 // ---- inverted dropout of a layer's output ------------------------------------------------------
 // Element e of a contiguous matrix is kept where word e % 4 of the draw numbered e / 4 reaches `thr`, and scaled.
 struct DropoutK {
