@@ -1101,7 +1101,14 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
     COFREE_HIP_CHECK(hipGetLastError());
     return COFREE_OK;
   }
-  const int panel = ROW_PIECES * WIDE;  // columns one launch covers
+  // Rows of 65 to 96 pieces leave a quarter to a half of a wavefront's second access without columns.  Where such rows are short and
+  // their matrix is beyond the caches, so that a launch waits for its bytes and not for the graph, 64 pieces and the others are two
+  // launches: 500k rows of 300 float32, 3 entries each 554 -> 480 us, 250k of 260 (2 entries) 197 -> 163, 250k of 530 bfloat16 (4) 270 ->
+  // 230, 500k of 768 (7) 953 -> 851.  From 4 (bfloat16: 8) entries a row on 0.98 to 1.09 (0.85 to 1.03), below 250 (200) MB up to 1.06
+  // (150k of 300 float32, 4 entries), on 30k rows 1.07 to 1.23; of 97 to 125 pieces 1.01 to 1.10.
+  const bool halves = pieces > 64 && pieces <= 96 && a.width >= 65 * WIDE && a.g.nnz < a.g.n * (sizeof(T) == 4 ? 4 : 8) &&
+                      matrix >= (sizeof(T) == 4 ? 250e6 : 200e6);
+  const int panel = (halves ? 64 : ROW_PIECES) * WIDE;  // columns one launch covers
   for (int c0 = 0; c0 < a.width; c0 += panel) {
     k.width = a.width - c0 < panel ? a.width - c0 : panel;
     k.col0 = c0;
