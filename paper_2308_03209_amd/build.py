@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcofree.so")
 GATHER_CEILING = os.path.join(HERE, "gather_ceiling")   # stand-alone micro-benchmark (csrc/gather_ceiling.hip)
-SOURCES = ["partition.cpp", "dropedge.hip", "spmm.hip", "gemm.hip", "gemm_split.hip", "gemm_narrow.hip", "gemm_bf16.hip", "gemm_bf16_resident.hip", "gemm_bf16_resident_wide.hip", "wgrad_bf16.hip", "loss_step.hip", "layers.cpp", "profile.cpp"]
+SOURCES = ["partition.cpp", "dropedge.hip", "spmm.hip", "gemm.hip", "gemm_split.hip", "gemm_narrow.hip", "gemm_bf16.hip", "gemm_bf16_resident.hip", "gemm_bf16_resident_wide.hip", "gemm_bf16_pinned.hip", "wgrad_bf16.hip", "loss_step.hip", "layers.cpp", "profile.cpp"]
 HEADERS = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "colsum.h"), os.path.join(CSRC, "gemm_bf16_resident.h"),
            os.path.join(HERE, "..", "include", "cofree.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",

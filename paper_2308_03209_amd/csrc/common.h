@@ -434,6 +434,10 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream);
 bool gemm_resident_fits(const GemmArgs& a);
 bool gemm_resident_drops(const GemmArgs& a);
 int32_t launch_gemm_resident(const GemmArgs& a, hipStream_t stream);
+// ... or registers (gemm_bf16_pinned.hip); Wb: bfloat16 copy [N][ldwb] of the parameters, the second segment's behind the first's
+bool gemm_pinned_fits(const GemmArgs& a);
+bool gemm_pinned_drops(const GemmArgs& a);
+int32_t launch_gemm_pinned(const GemmArgs& a, const bf16_t* Wb, int64_t ldwb, hipStream_t stream);
 int32_t launch_wgrad_bf16(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
 // bfloat16 weight gradients of at least eight rows and columns (wgrad_bf16.hip); narrower ones stay in gemm_bf16.hip
 bool wgrad_bf16_fits(int32_t N1, int32_t N2, int32_t N2b);

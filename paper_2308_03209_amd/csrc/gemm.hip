@@ -616,7 +616,8 @@ static int32_t check_grid(int64_t blocks) {
 bool gemm_drops(const GemmArgs& a) {
   // rows of whole draws, so that the four elements of a draw belong to one lane
   if (a.b_kmajor || a.N % 4 != 0 || a.ldc != a.N) return false;
-  return a.dtype == COFREE_F32 ? gemm_split_fits(a) : gemm_resident_drops(a);
+  if (a.dtype == COFREE_F32) return gemm_split_fits(a);
+  return gemm_pinned_fits(a) ? gemm_pinned_drops(a) : gemm_resident_drops(a);
 }
 
 int32_t launch_gemm(const GemmArgs& a, hipStream_t stream) {

@@ -643,8 +643,9 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
                    "dense: ldb too small");
   else
     COFREE_REQUIRE(a.b_kmajor ? a.ldb >= a.N : a.ldb >= K, "dense: ldb too small");
-  if (gemm_resident_fits(a)) return launch_gemm_resident(a, stream);
-  if (a.dropout.q > 0.f) return fail(COFREE_EINVAL, "internal: no dropout in tiled products");
+  const bool pinned = gemm_pinned_fits(a);
+  if (!pinned && gemm_resident_fits(a)) return launch_gemm_resident(a, stream);
+  if (!pinned && a.dropout.q > 0.f) return fail(COFREE_EINVAL, "internal: no dropout in tiled products");
   const int64_t ldd = pad8(K);
   bf16_t* Wb = (bf16_t*)a.param_scratch;
   {
@@ -660,6 +661,7 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
                                                                                         a.K2, Wb, ldd, a.K1, a.K2);
     }
   }
+  if (pinned) return launch_gemm_pinned(a, Wb, ldd, stream);
   GemmHK p{};
   p.A1 = (const bf16_t*)a.A1;
   p.lda1 = a.lda1;
