@@ -303,7 +303,9 @@ struct AggArgs {
   const void* relu_src = nullptr;    // if set: Y[v,c] = 0 where relu_src[v,c] <= 0 (same dtype, ld = ld_relu)
   int64_t ld_relu = 0;
   float gate_scale = 1.f;            // factor on the elements that pass relu_src
-  // applied after out_scale, in this order: + bias[c], ReLU
+  const void* add = nullptr;         // added to Y (same dtype, ld = ld_add); not together with relu_src
+  int64_t ld_add = 0;
+  // applied after out_scale, in this order: + add[v,c], + bias[c], ReLU
   const float* bias = nullptr;
   int32_t relu_out = 0;
   DropoutArgs dropout;  // of the finished rows, where aggregate_drops() allows it
@@ -335,6 +337,10 @@ struct GemmArgs {
   // the k-range K1.. of B - for sums of two products with different parameters, C = A1 op(B) + A2 op(B2)
   const float* B2 = nullptr;
   int64_t ldb2 = 0;
+  // optional, where gemm_two_fits() and nothing but the product is asked for: a second result C_second = A B_second^T of as many
+  // columns, with the same leading dimensions
+  const float* B_second = nullptr;
+  void* C_second = nullptr;
   void* C = nullptr;
   int64_t ldc = 0;
   int64_t M = 0;
@@ -424,6 +430,7 @@ bool wgrad_split_fits(const WgradArgs& a);
 int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
 // float32 products of at most 64 columns, weight gradients of at most 64 rows or columns (gemm_narrow.hip)
 bool gemm_narrow_fits(const GemmArgs& a);
+bool gemm_two_fits(int32_t d_out, int32_t d_in, int64_t M);  // two results of d_out columns from one float32 matrix, see GemmArgs::C_second
 int32_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream);
 bool wgrad_narrow_fits(int32_t N1, int32_t N2, int32_t N2b);
 size_t wgrad_narrow_workspace_floats(int32_t N1, int32_t N2, int32_t N2b, int64_t M);

@@ -36,6 +36,9 @@ struct NarrowK {
   const float *A1, *A2, *B1, *B2;
   int64_t lda1, lda2, ldb1, ldb2;
   int32_t K1, K2;  // K2 = 0: one segment
+  const float* B_second;  // second result, of the blocks of columns from `half` on (INT_MAX: none)
+  float* C_second;
+  int32_t half;
   float* C;
   int64_t ldc, M;
   int32_t N;
@@ -89,7 +92,11 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
   float* const params = lds + nb * 16;  // [step][nb][lane][4]
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int b0 = wave % col_waves * NB, row_wave = wave / col_waves, row_waves = (int)(blockDim.x >> 6) / col_waves;
+  const int b0 = wave % col_waves * NB;  // the wavefront's blocks, all of one result
+  const bool second_result = SHARE && b0 >= p.half;
+  const int own_b0 = second_result ? b0 - p.half : b0;
+  float* const C = second_result ? p.C_second : p.C;
+  const int row_wave = wave / col_waves, row_waves = (int)(blockDim.x >> 6) / col_waves;
   const int n1 = (p.K1 + 15) / 16, n = n1 + (p.K2 + 15) / 16;
 
   struct Rows {
@@ -119,7 +126,9 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
   };
   auto fill = [&](int t0, int t1) {  // parameters of steps t0 .. t1 - 1; a wavefront takes steps of one block of columns
     const int b = wave % nb, every = (int)(blockDim.x >> 6) / nb;
-    const int64_t j = column(b, r);
+    const bool of_second = SHARE && b >= p.half;
+    const int64_t j = column(of_second ? b - p.half : b, r);
+    const float* const first_B = of_second ? p.B_second : p.B1;
     constexpr int BATCH = DEPTH;
     for (int base = t0 + wave / nb; base < t1 && wave < every * nb; base += BATCH * every) {
       float4u v[BATCH];
@@ -127,7 +136,7 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
       for (int u = 0; u < BATCH; ++u) {
         const int t = base + u * every;
         const Step<ELEMENTS> s(t < t1 ? t : t1 - 1, n1, p.K1, p.K2);
-        const float* const B = s.second ? p.B2 : p.B1;
+        const float* const B = s.second ? p.B2 : first_B;
         const int64_t ldb = s.second ? p.ldb2 : p.ldb1;
         if constexpr (!B_KMAJOR && !ELEMENTS) {
           v[u] = *reinterpret_cast<const float4u*>(B + j * ldb + s.first(g));
@@ -153,7 +162,7 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
   int32_t col[NB], own[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const int first = 16 * (b0 + b) + 4 * g;
+    const int first = 16 * (own_b0 + b) + 4 * g;
     col[b] = p.N < 4 || first < p.N - 4 ? first : p.N - 4;
     own[b] = first - col[b];
   }
@@ -234,7 +243,7 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
     };
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      if (16 * (b0 + b) + 4 * g >= p.N) continue;
+      if (16 * (own_b0 + b) + 4 * g >= p.N) continue;
       floatx4 y = acc[b] + *reinterpret_cast<const floatx4*>(bias + 16 * (b0 + b) + 4 * g);
       if (p.relu) {
 #pragma unroll
@@ -243,7 +252,7 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
       if constexpr (EXTRAS) {
         float4u gate = {1.f, 1.f, 1.f, 1.f}, sum = {0.f, 0.f, 0.f, 0.f};
         if (p.gate) gate = read(p.gate + i * p.ldg, b);
-        if (p.accumulate) sum = read(p.C + i * p.ldc, b);
+        if (p.accumulate) sum = read(C + i * p.ldc, b);
         const float rs = p.row_scale ? p.row_scale[i] : 1.f;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -255,7 +264,7 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
           y[c] = p.relu_last ? fmaxf(x, 0.f) : x;
         }
       }
-      float* const dst = p.C + i * p.ldc + col[b];
+      float* const dst = C + i * p.ldc + col[b];
       // An element that the launch reads too (accumulated, or its own gate) is written by one lane only.
       if (p.N >= 4 && (own[b] == 0 || !EXTRAS)) {
         *reinterpret_cast<float4u*>(dst) = float4u{y[0], y[1], y[2], y[3]};
@@ -276,7 +285,7 @@ struct NarrowShape {
 };
 static NarrowShape narrow_shape(const GemmArgs& a) {
   NarrowShape s;
-  s.nb = (a.N + 15) / 16;
+  s.nb = (a.N + 15) / 16 * (a.C_second ? 2 : 1);
   s.steps = ((int64_t)a.K1 + 15) / 16 + ((int64_t)a.K2 + 15) / 16;
   s.most = (LDS_BYTES - s.nb * 64) / (s.nb * 1024);
   s.cu_tiles = (a.M + 16 * CUS - 1) / (16 * CUS);
@@ -334,8 +343,11 @@ int32_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream) {
   p.relu_last = a.relu_last;
   p.gate_last = a.gate_last;
   p.gate_scale = a.gate ? a.gate_scale : 1.f;
+  p.B_second = a.B_second;
+  p.C_second = (float*)a.C_second;
   p.tiles = (a.M + 15) / 16;
   const auto [nb, steps, most, cu_tiles] = narrow_shape(a);
+  p.half = a.C_second ? nb / 2 : INT_MAX;
   const int depth = a.K1 < 4 || (a.K2 > 0 && a.K2 < 4) ? 1 : steps <= 2 ? 2 : steps <= 4 ? 4 : 8;
   p.part_steps = (int32_t)(steps <= most ? steps : most / depth * depth);
   const size_t lds = (size_t)p.part_steps * nb * 1024 + nb * 64;
@@ -343,7 +355,8 @@ int32_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream) {
   // every block of columns can have a wavefront of its own it gets one: the chain of matrix instructions on one tile is what
   // the launch waits for.  Five and six tiles of four blocks, which would lie unevenly on four SIMDs, are cut in two (20,000 x 64 x
   // 602: 38 us in five wavefronts, 30 in ten).  Always 16 tiles left CUs without a workgroup (33,000 x 48 x 64 11.7 -> 8.3 us).
-  p.col_waves = cu_tiles * nb <= 16 ? nb : nb == 4 && cu_tiles <= 6 && depth == 8 ? 2 : 1;
+  // Two results are two wavefronts' at least.
+  p.col_waves = cu_tiles * nb <= 16 ? nb : a.C_second || (nb == 4 && cu_tiles <= 6 && depth == 8) ? 2 : 1;
   const int cols = nb / p.col_waves;  // blocks of columns a wavefront
   const int row_waves = (int)std::min<int64_t>(std::max<int64_t>(cu_tiles, (3 + p.col_waves) / p.col_waves), 16 / p.col_waves);
   const int waves = row_waves * p.col_waves;
@@ -353,12 +366,12 @@ int32_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(rounds < INT_MAX, "dense: too many rows");
   p.rounds = (int32_t)rounds;
   const bool extras = a.gate || a.accumulate || a.row_scale || a.relu_last;
-  const double K = (double)a.K1 + a.K2;
+  const double K = (double)a.K1 + a.K2, results = a.C_second ? 2.0 : 1.0;
   char pname[96] = "";  // the template instance launched below, then the shape
   if (profiling()) snprintf(pname, sizeof(pname), "narrow_gemm_kernel<%d,%s,%s,%d,%s> N=%d K=%lld", cols, cols == 1 || p.col_waves > 1 ? "true" : "false", a.b_kmajor ? "true" : "false",
                             depth, extras ? "true" : "false", (int)a.N, (long long)K);
-  ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + (double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1)),
-                 2.0 * (double)a.M * a.N * K);
+  ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + results * ((double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1))),
+                 2.0 * results * (double)a.M * a.N * K);
   auto by_depth = [&](auto n, auto share, auto kmajor) {
     constexpr int NB = decltype(n)::value;
     constexpr bool SHARE = decltype(share)::value, KMAJOR = decltype(kmajor)::value;
@@ -367,7 +380,7 @@ int32_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream) {
       return extras ? launch_narrow<NB, SHARE, KMAJOR, DEPTH, true>(p, blocks, 64 * waves, lds, stream)
                     : launch_narrow<NB, SHARE, KMAJOR, DEPTH, false>(p, blocks, 64 * waves, lds, stream);
     };
-    if constexpr (NB == 2 && SHARE) {
+    if constexpr (NB == 2 && SHARE && KMAJOR) {
       return go(std::integral_constant<int, 8>{});
     } else {
       switch (depth) {

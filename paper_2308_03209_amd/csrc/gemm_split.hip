@@ -48,6 +48,7 @@
 // share of it), and not zero, computes its whole tile again.
 // Both cost time where they happen: 230k x 256 x 602 0.57 ms in turn with others of its kind, with a NaN in one column of
 // B 1.13, with one in every tile of A 1.18 (float32 instructions 0.68 and 0.77).  Looking for small rows costs 1-2 %.
+#include <climits>
 #include <cstdio>
 #include <type_traits>
 
@@ -91,6 +92,11 @@ struct SplitK {
   DropoutK drop;
   const unsigned char* planes;  // parameters split beforehand: [column tile][step][STEP_IMAGE]
   const uint32_t* small_params; // [column tile][step]: they are to be computed again (see below)
+  // second result (TWO): the columns from `half` on are those of A B_second^T, B1 = B_second + b_offset, stored at C_second
+  const float* B_second;
+  float* C_second;
+  int64_t b_offset;
+  int32_t half;
 };
 
 constexpr int TILE = 128;                 // rows and columns of a workgroup's result
@@ -167,6 +173,14 @@ struct SplitKContig {
     k_len = (int)k_len_;
     const int64_t last = extent - 1 - i0, r = tid >> 1;
     off = (uint32_t)(r < last ? r : last) * (uint32_t)ld * 4u + (k_len < SBK ? 0u : (uint32_t)kq * 4u);
+  }
+  // rows of two matrices: the first `half` begin at P + offset, the others at P
+  __device__ void init_two(const float* P, int64_t offset, int32_t half, int64_t ld, int64_t extent, int64_t i0, int64_t k_len_, int tid) {
+    base = reinterpret_cast<const char*>(P);
+    kq = (tid & 1) * 8;
+    k_len = (int)k_len_;
+    const int64_t last = extent - 1, r = i0 + (tid >> 1) < last ? i0 + (tid >> 1) : last;
+    off = (uint32_t)((r < half ? offset + r * ld : (r - half) * ld) * 4) + (k_len < SBK ? 0u : (uint32_t)kq * 4u);
   }
   __device__ void load(int t, Raw& w) const {
     const char* const p = base + (int64_t)window_of(t, k_len, 0).start * 4;
@@ -478,6 +492,8 @@ struct SplitParamsK {
   int64_t ldb[2];
   int32_t k_len[2], steps[2];
   int32_t N, k_major;
+  const float* B_second;  // rows from `half` on (see SplitK)
+  int32_t half;
   unsigned char* image;
   uint32_t* flags;
 };
@@ -491,7 +507,8 @@ __global__ __launch_bounds__(256) void split_params_kernel(const SplitParamsK p)
   const Window in = window_of(t, k_len, kg * 8);
   const int first = k_len < SBK ? short_first(k_len, kg * 8) : in.start + kg * 8;
   const int64_t j = (int64_t)tile * TILE + row, ldb = p.ldb[seg];
-  const float* const B = p.B[seg];
+  const bool of_second = j >= p.half;
+  const float* const B = of_second ? p.B_second - p.half * ldb : p.B[seg];
   float e[8];
   uint32_t bits = 0;
 #pragma unroll
@@ -541,7 +558,8 @@ __device__ inline void run_plain(const float* A, int64_t ska, const float* B, in
 // DROP: dropout of the result, in rows of a multiple of four contiguous columns (529k x 512 with K = 1024: a pass of its own
 // took 353 us, a training step with three of them is 760 us shorter without).  Its generator runs beside the matrix
 // instructions of the CU's other workgroup, where a pass of its own reads and writes the result once more.
-template <bool A_KMAJOR, bool B_KMAJOR, bool PLANES, bool DROP>
+// TWO: two results of one matrix A, whose columns follow one another and are stored apart, without an epilogue.
+template <bool A_KMAJOR, bool B_KMAJOR, bool PLANES, bool DROP, bool TWO = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(
     const SplitK p) {
   constexpr int STAGE_LD = 68, STAGE_WAVE = 32 * STAGE_LD;  // result staging: floats
@@ -635,7 +653,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
         run_split<false>(ma, mb, k_seg, smem, a_off, b_off, sums, tid, 0, false, csum, small);
       } else {
         SplitKContig mb;
-        mb.init(seg ? p.B2 : p.B1, seg ? p.ldb2 : p.ldb1, p.N, j0, k_seg, tid);
+        if constexpr (TWO) mb.init_two(p.B_second, p.b_offset, p.half, p.ldb1, p.N, j0, k_seg, tid);
+        else mb.init(seg ? p.B2 : p.B1, seg ? p.ldb2 : p.ldb1, p.N, j0, k_seg, tid);
         run_split<false>(ma, mb, k_seg, smem, a_off, b_off, sums, tid, 0, false, csum, small);
       }
     }
@@ -670,7 +689,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
 #pragma nounroll
       for (int seg = 0; seg < n_seg; ++seg) {
         const int64_t ldb = seg ? p.ldb2 : p.ldb1;
-        run_plain((seg ? p.A2 : p.A1) + ia * (seg ? p.lda2 : p.lda1), 1, (seg ? p.B2 : p.B1) + ja * (B_KMAJOR ? 1 : ldb),
+        const float* B = (seg ? p.B2 : p.B1) + ja * (B_KMAJOR ? 1 : ldb);
+        if (TWO && ja >= p.half) B = p.B_second + (ja - p.half) * ldb;
+        run_plain((seg ? p.A2 : p.A1) + ia * (seg ? p.lda2 : p.lda1), 1, B,
                   B_KMAJOR ? ldb : 1, seg ? p.K2 : p.K1, g, c);
       }
 #pragma unroll
@@ -722,6 +743,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
       float4u g, c;
       float rs;
     };
+    if constexpr (TWO) {
+      const bool whole = i0 + TILE <= p.M;
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        const int64_t j = j0 + wn * 64 + n * 32 + r;
+        if (j < p.N) {
+          float* const dst = (j < p.half ? p.C + j : p.C_second + (j - p.half)) + (i0 + wm * 64 + 4 * g) * p.ldc;
+#pragma unroll
+          for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              const int row = m * 32 + 8 * (v >> 2) + (v & 3);
+              if (whole || i0 + wm * 64 + 4 * g + row < p.M) dst[(int64_t)row * p.ldc] = v & 1 ? -acc[m][n][v] : acc[m][n][v];
+            }
+        }
+      }
+      return;
+    }
     if constexpr (!DROP) {
       if (!extras && !p.relu_last && i0 + TILE <= p.M) {
         // Nothing but bias and ReLU: a register of a block is two rows of a whole line of 128 bytes and is stored as it lies
@@ -859,7 +898,7 @@ size_t split_param_bytes(int64_t M, int32_t N, int64_t K1, int64_t K2) {
 }
 
 static bool split_params_first(const GemmArgs& a) {
-  const size_t bytes = split_param_bytes(a.M, a.N, a.K1, a.K2);
+  const size_t bytes = split_param_bytes(a.M, a.C_second ? 2 * a.N : a.N, a.K1, a.K2);
   return bytes > 0 && a.param_scratch && a.param_scratch_bytes >= bytes;
 }
 
@@ -878,7 +917,12 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   p.C = (float*)a.C;
   p.ldc = a.ldc;
   p.M = a.M;
-  p.N = a.N;
+  const int32_t N = a.C_second ? 2 * a.N : a.N;
+  p.N = N;
+  p.B_second = a.B_second;
+  p.C_second = (float*)a.C_second;
+  p.b_offset = a.C_second ? a.B - a.B_second : 0;
+  p.half = a.C_second ? a.N : INT_MAX;
   p.bias = a.bias;
   p.relu = a.relu;
   p.row_scale = a.row_scale;
@@ -891,7 +935,7 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   p.drop = dropout_k(a.dropout);
   const int64_t K = (int64_t)a.K1 + a.K2;
   p.n_groups = (a.M + TILE - 1) / TILE;
-  p.tiles_n = (a.N + TILE - 1) / TILE;
+  p.tiles_n = (N + TILE - 1) / TILE;
   const int64_t blocks = ((p.n_groups + 7) / 8) * 8 * p.tiles_n;
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "dense: grid too large");
   const bool drop = p.drop.scale != 0.f;  // forward products only
@@ -902,22 +946,25 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
     q.ldb[0] = p.ldb1, q.ldb[1] = p.ldb2;
     q.k_len[0] = a.K1, q.k_len[1] = a.K2;
     q.steps[0] = (a.K1 + SBK - 1) / SBK, q.steps[1] = (a.K2 + SBK - 1) / SBK;
-    q.N = a.N, q.k_major = a.b_kmajor;
+    q.N = N, q.k_major = a.b_kmajor;
+    q.B_second = a.B_second, q.half = p.half;
     const int steps = q.steps[0] + q.steps[1];
     q.image = (unsigned char*)a.param_scratch;
     q.flags = (uint32_t*)(q.image + (size_t)p.tiles_n * steps * STEP_IMAGE);
-    ProfScope prof("split_params_kernel", stream, 10.0 * (double)a.N * K, 0.0);
+    ProfScope prof("split_params_kernel", stream, 10.0 * (double)N * K, 0.0);
     split_params_kernel<<<dim3((unsigned)(p.tiles_n * steps)), 256, 0, stream>>>(q);
     p.planes = q.image;
     p.small_params = q.flags;
   }
   char pname[96] = "";
   if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<false,%s,%s,%s> N=%d K=%d", a.b_kmajor ? "true" : "false",
-           planes ? "true" : "false", drop && !a.b_kmajor ? "true" : "false", (int)a.N, (int)K);
-  ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + (double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1)),
-                 2.0 * (double)a.M * a.N * (double)K);
+           planes ? "true" : "false", drop && !a.b_kmajor ? "true" : "false", (int)N, (int)K);
+  ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + (double)N * K + (double)a.M * N * (a.accumulate ? 2 : 1)),
+                 2.0 * (double)a.M * N * (double)K);
   const dim3 grid((unsigned)blocks);
-  if (planes && a.b_kmajor) gemm_split_kernel<false, true, true, false><<<grid, 256, 0, stream>>>(p);
+  if (a.C_second && planes) gemm_split_kernel<false, false, true, false, true><<<grid, 256, 0, stream>>>(p);
+  else if (a.C_second) gemm_split_kernel<false, false, false, false, true><<<grid, 256, 0, stream>>>(p);
+  else if (planes && a.b_kmajor) gemm_split_kernel<false, true, true, false><<<grid, 256, 0, stream>>>(p);
   else if (planes && drop) gemm_split_kernel<false, false, true, true><<<grid, 256, 0, stream>>>(p);
   else if (planes) gemm_split_kernel<false, false, true, false><<<grid, 256, 0, stream>>>(p);
   else if (a.b_kmajor) gemm_split_kernel<false, true, false, false><<<grid, 256, 0, stream>>>(p);

@@ -1,5 +1,6 @@
 // Composition of one GNN layer, forward and backward, from the aggregation and dense kernels
 // (layer definition of Section 3; gradient flow as in the proof of Theorem 3).
+#include <cstdint>
 #include <cstdlib>
 #include <mutex>
 
@@ -116,6 +117,12 @@ static bool conv_merged(const cofree_layer_desc& d) {
 static size_t max2(size_t a, size_t b) { return a > b ? a : b; }
 static size_t max3(size_t a, size_t b, size_t c) { return max2(a, max2(b, c)); }
 
+// Conventional GraphSAGE, transform first: both products of H are one launch, and the self part is added by the
+// aggregation - H is read once, and a launch falls away.
+static bool conv_two(const cofree_layer_desc& d, int64_t n) {
+  return d.kind == COFREE_SAGE_CONV && d.dtype == COFREE_F32 && conv_transform_first(d) && gemm_two_fits(d.d_out, d.d_in, n);
+}
+
 // largest copy of a parameter matrix - in bfloat16, or split into three of them - that any product of the layer makes.  In
 // float32 it only saves time: a call whose workspace has no room for it does without.
 static size_t param_scratch_bytes(const cofree_layer_desc& d, int64_t n) {
@@ -124,7 +131,8 @@ static size_t param_scratch_bytes(const cofree_layer_desc& d, int64_t n) {
       return max3(split_param_bytes(n, d.d_msg, d.d_in, 0), split_param_bytes(n, d.d_out, d.d_msg, d.d_in),
                   max2(split_param_bytes(n, d.d_msg, d.d_out, 0), split_param_bytes(n, d.d_in, d.d_out, d.d_msg)));
     if (d.kind == COFREE_SAGE_CONV)
-      return max2(split_param_bytes(n, d.d_out, d.d_in, d.d_in), split_param_bytes(n, d.d_in, d.d_out, d.d_out));
+      return max3(split_param_bytes(n, d.d_out, d.d_in, d.d_in), split_param_bytes(n, d.d_in, d.d_out, d.d_out),
+                  conv_two(d, n) ? split_param_bytes(n, 2 * d.d_out, d.d_in, 0) : 0);
     return max2(split_param_bytes(n, d.d_out, d.d_in, 0), split_param_bytes(n, d.d_in, d.d_out, 0));
   }
   if (d.kind == COFREE_SAGE_MEAN)
@@ -140,16 +148,19 @@ static size_t param_scratch_bytes(const cofree_layer_desc& d, int64_t n) {
 
 struct FwdPlan {
   void* T = nullptr;       // transform-first: norm * (H W^T) (GCN), H W_neigh^T (conventional GraphSAGE)
+  void* S = nullptr;       // H W_self^T where both products are one launch
   void* params = nullptr;  // copy of a parameter matrix
   size_t params_bytes = 0;
   size_t bytes = 0, needed = 0;  // in all; of which a call cannot do without
 };
 
-static FwdPlan plan_fwd(const cofree_layer_desc& d, int64_t n, void* ws) {
+// room: bytes of the workspace (two results only where they find room)
+static FwdPlan plan_fwd(const cofree_layer_desc& d, int64_t n, void* ws, size_t room) {
   Carver c(ws);
   FwdPlan p;
-  if ((d.kind == COFREE_GCN && gcn_transform_first(d)) || (d.kind == COFREE_SAGE_CONV && conv_transform_first(d)))
-    p.T = c.take((size_t)n * d.d_out * elem_size(d.dtype));
+  const size_t T = (size_t)n * d.d_out * elem_size(d.dtype);
+  if ((d.kind == COFREE_GCN && gcn_transform_first(d)) || (d.kind == COFREE_SAGE_CONV && conv_transform_first(d))) p.T = c.take(T);
+  if (conv_two(d, n) && room >= c.used + align256(T)) p.S = c.take(T);
   p.needed = c.used;
   p.params_bytes = param_scratch_bytes(d, n);
   p.params = c.take(p.params_bytes);
@@ -260,7 +271,7 @@ size_t cofree_layer_desc_size(void) { return sizeof(cofree_layer_desc); }
 
 size_t cofree_layer_workspace_bytes(const cofree_layer_desc* desc, int64_t n_nodes, int32_t backward) {
   if (!desc || n_nodes < 0) return 0;
-  const size_t b = backward ? bwd_bytes(*desc, n_nodes) : plan_fwd(*desc, n_nodes, nullptr).bytes;
+  const size_t b = backward ? bwd_bytes(*desc, n_nodes) : plan_fwd(*desc, n_nodes, nullptr, SIZE_MAX).bytes;
   return b < 256 ? 256 : b;
 }
 
@@ -274,7 +285,7 @@ int32_t cofree_layer_fwd(const cofree_partition* part, const cofree_masks* masks
   COFREE_TRY(select_graph(part, masks, mask_id, &g));
   COFREE_REQUIRE(H_in && H_out && params && saved, "layer_fwd: NULL argument");
   COFREE_REQUIRE(params->W && params->bW, "layer_fwd: W / bW is NULL");
-  const FwdPlan fp = plan_fwd(d, g.n, workspace);
+  const FwdPlan fp = plan_fwd(d, g.n, workspace, workspace ? workspace_bytes : 0);
   if (fp.needed > 0 && (workspace == nullptr || workspace_bytes < fp.needed))
     return fail(COFREE_ENOMEM, "layer_fwd: workspace too small");
   const bool copies = workspace != nullptr && workspace_bytes >= fp.bytes;
@@ -353,7 +364,22 @@ int32_t cofree_layer_fwd(const cofree_partition* part, const cofree_masks* masks
     }
   } else if (d.kind == COFREE_SAGE_CONV) {
     const int64_t ldw = 2 * (int64_t)d.d_in;  // W = [W_self | W_neigh]
-    if (conv_transform_first(d)) {
+    if (fp.S) {
+      // T = H W_neigh^T, S = H W_self^T; H' = act(mean(T) + S + b)
+      GemmArgs t = gemm();
+      t.A1 = H_in; t.lda1 = d.d_in; t.K1 = d.d_in;
+      t.B = params->W + d.d_in; t.ldb = ldw;
+      t.C = fp.T; t.ldc = d.d_out; t.N = d.d_out;
+      t.B_second = params->W; t.C_second = fp.S;
+      COFREE_TRY(launch_gemm(t, s));
+      AggArgs a = agg();
+      a.X = fp.T; a.Y = H_out; a.width = d.d_out; a.ldx = a.ldy = d.d_out;
+      a.out_scale = g.inv_deg;
+      a.add = fp.S; a.ld_add = d.d_out;
+      a.bias = params->bW; a.relu_out = d.act;
+      with_dropout(a, aggregate_drops(a));
+      COFREE_TRY(launch_aggregate(a, s));
+    } else if (conv_transform_first(d)) {
       // T = H W_neigh^T; H' = mean(T); H' = act(H' + H W_self^T + b)
       GemmArgs t = gemm();
       t.A1 = H_in; t.lda1 = d.d_in; t.K1 = d.d_in;
@@ -688,7 +714,7 @@ size_t cofree_layers_workspace_bytes(const cofree_layer_desc* descs, int32_t n_l
   if (!descs || n_layers < 1 || n_nodes < 0) return 0;
   size_t b = 256;
   for (int32_t l = 0; l < n_layers; ++l)
-    b = max3(b, plan_fwd(descs[l], n_nodes, nullptr).bytes, bwd_bytes(descs[l], n_nodes));
+    b = max3(b, plan_fwd(descs[l], n_nodes, nullptr, SIZE_MAX).bytes, bwd_bytes(descs[l], n_nodes));
   const Deferral f = plan_deferral(n_layers, n_nodes, [&](int32_t l) { return descs[l]; });
   return f.worth ? max2(b, f.scratch + f.partials) : b;
 }

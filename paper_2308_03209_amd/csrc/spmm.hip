@@ -155,8 +155,9 @@ struct AggK {
   const float* in_vals;   // the same factor per adjacency entry (in_vals[e] = in_scale[col[e]]), or null
   const float* out_scale;
   int self_loop;
-  const T* relu_src;
+  const T* relu_src;  // the row's other operand: gates the result, or is added to it (add_src)
   uint32_t ld_relu;
+  int add_src;
   float gate_scale;  // factor on the elements that pass relu_src
   // output epilogue (after out_scale): + bias, ReLU
   const float* bias;
@@ -195,7 +196,7 @@ __device__ inline LaneCols lane_cols(int width, int start) {
   return l;
 }
 
-// Shared tail of both kernels: self term, destination scale, gate, bias, ReLU, store.
+// Shared tail of the kernels: self term, destination scale, gate or added row, bias, ReLU, store.
 // The operands of the tail that depend on the row alone - its own X row, its gate row, its two scales -
 // are requested together as soon as the row is known (RowTail::request, all loads back to back, nothing
 // uses them yet) and applied after the neighbour sum: fetched one after the other at the end, each with
@@ -244,7 +245,7 @@ __device__ inline void finish_row(const AggK<T>& p, uint32_t row, int c0, int av
       float g[VEC];
       load_elems<T, VEC>(row_at(p.relu_src, row, p.ld_relu) + c0, avail, g);
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) acc[i] = g[i] > 0.f ? acc[i] * p.gate_scale : 0.f;
+      for (int i = 0; i < VEC; ++i) acc[i] = p.add_src ? acc[i] + g[i] : (g[i] > 0.f ? acc[i] * p.gate_scale : 0.f);
     }
   } else {
     if (p.self_loop) RowIO<T>::fma_raw(acc, t.ss, t.xs);
@@ -254,7 +255,7 @@ __device__ inline void finish_row(const AggK<T>& p, uint32_t row, int c0, int av
       float g[VEC];
       RowIO<T>::unpack(t.g, g);
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) acc[i] = g[i] > 0.f ? acc[i] * p.gate_scale : 0.f;
+      for (int i = 0; i < VEC; ++i) acc[i] = p.add_src ? acc[i] + g[i] : (g[i] > 0.f ? acc[i] * p.gate_scale : 0.f);
     }
   }
   if (p.bias) {
@@ -961,7 +962,7 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   constexpr int WIDE = RowIO<T>::WIDE;
   const T* X = (const T*)a.X;
   T* Y = (T*)a.Y;
-  const T* R = (const T*)a.relu_src;
+  const T* R = (const T*)(a.add ? a.add : a.relu_src);
   AggK<T> k{};
   k.rowptr = a.g.rowptr;
   k.col = a.g.col;
@@ -970,7 +971,8 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   k.in_scale = a.in_scale;
   k.out_scale = a.out_scale;
   k.self_loop = a.self_loop;
-  k.ld_relu = (uint32_t)a.ld_relu;
+  k.ld_relu = (uint32_t)(a.add ? a.ld_add : a.ld_relu);
+  k.add_src = a.add != nullptr;
   k.gate_scale = a.gate_scale;
   k.bias = a.bias;
   k.relu_out = a.relu_out;
@@ -1135,7 +1137,8 @@ int32_t launch_aggregate(const AggArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(a.X && a.Y && a.X != a.Y, "aggregate: X and Y must be distinct non-NULL buffers");
   COFREE_REQUIRE(a.ldx >= a.width && a.ldy >= a.width, "aggregate: leading dimension smaller than width");
   COFREE_REQUIRE(a.g.n < ((int64_t)1 << 31), "aggregate: too many rows");
-  COFREE_REQUIRE((a.ldx | a.ldy | a.ld_relu) < ((int64_t)1 << 32), "aggregate: leading dimension too large");
+  COFREE_REQUIRE(!a.add || !a.relu_src, "aggregate: gated and added to");
+  COFREE_REQUIRE((a.ldx | a.ldy | a.ld_relu | a.ld_add) < ((int64_t)1 << 32), "aggregate: leading dimension too large");
   if (a.g.n == 0) return COFREE_OK;
   const bool drop = a.dropout.q > 0.f;
   if (a.dtype == COFREE_F32) return drop ? launch_typed<float, true>(a, stream) : launch_typed<float, false>(a, stream);
