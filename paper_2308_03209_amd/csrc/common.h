@@ -129,6 +129,23 @@ __device__ inline void drop4(const DropoutK& d, uint64_t first, float* x) {
   x[3] = w.w >= d.thr ? x[3] * d.scale : 0.f;
 }
 
+// N consecutive elements, N a multiple of four, that may begin inside a draw: one draw more, whose words are moved into place.
+template <int N>
+__device__ inline void drop_span(const DropoutK& d, uint64_t first, float* x) {
+  u32x4 w = draw4(d.seed, d.stream, first >> 2, d.epoch);
+#pragma unroll
+  for (int q = 0; q < N; q += 4) {
+    const u32x4 v = draw4(d.seed, d.stream, (first >> 2) + (q / 4 + 1), d.epoch);
+    const bool two = (first & 2u) != 0, one = (first & 1u) != 0;
+    const uint32_t t0 = two ? w.z : w.x, t1 = two ? w.w : w.y, t2 = two ? v.x : w.z, t3 = two ? v.y : w.w, t4 = two ? v.z : v.x;
+    x[q] = (one ? t1 : t0) >= d.thr ? x[q] * d.scale : 0.f;
+    x[q + 1] = (one ? t2 : t1) >= d.thr ? x[q + 1] * d.scale : 0.f;
+    x[q + 2] = (one ? t3 : t2) >= d.thr ? x[q + 2] * d.scale : 0.f;
+    x[q + 3] = (one ? t4 : t3) >= d.thr ? x[q + 3] * d.scale : 0.f;
+    w = v;
+  }
+}
+
 // ---- graph views ------------------------------------------------------------------------
 // One CSR on the device with its per-node normalisation vectors.
 struct DeviceGraph {

@@ -225,9 +225,10 @@ struct RowTail {
   }
 };
 
-// DROP: dropout of the finished row, in rows of a multiple of four columns (100k rows of 128 bfloat16: a launch of its own took
-// 15 us).
-template <typename T, int VEC, bool TINY, bool DROP>
+// DROP: dropout of the finished row, 1 in rows of a multiple of four columns (100k rows of 128 bfloat16: a launch of its own took
+// 15 us), 2 in any, where lanes begin inside draws and have one draw more (20k rows of 33 float32: 5 us; one instance for both
+// cost the former 3 us of 30).
+template <typename T, int VEC, bool TINY, int DROP>
 __device__ inline void finish_row(const AggK<T>& p, uint32_t row, int c0, int avail, float (&acc)[VEC],
                                   const RowTail<T, VEC, TINY>& t) {
   if constexpr (TINY) {
@@ -281,8 +282,13 @@ __device__ inline void finish_row(const AggK<T>& p, uint32_t row, int c0, int av
     for (int i = 0; i < VEC; ++i) acc[i] = fmaxf(acc[i], 0.f);
   }
   if constexpr (DROP) {
+    const uint64_t first = (uint64_t)row * p.ldy + (uint32_t)(p.col0 + c0);
+    if constexpr (DROP == 2) {
+      drop_span<VEC>(p.drop, first, acc);
+    } else {
 #pragma unroll
-    for (int q = 0; q < VEC / 4; ++q) drop4(p.drop, (uint64_t)row * p.ldy + (uint32_t)(p.col0 + c0 + 4 * q), acc + 4 * q);
+      for (int q = 0; q < VEC; q += 4) drop4(p.drop, first + q, acc + q);
+    }
   }
   // A window that was moved left stores the columns that it shares with the lane before as well: both have the same sums.
   if constexpr (TINY) store_elems<T, VEC>(row_at(p.Y, row, p.ldy) + c0, avail, acc);
@@ -525,7 +531,7 @@ __device__ inline void gather_narrow(const AggK<T>& p, const int32_t* __restrict
 
 // TINY: the columns of rows narrower than one 16-byte access (element accesses; LPS = 1), else 0.
 // Rows need only element alignment (see LaneCols for the ragged end of a row).
-template <typename T, int TL, int LPS, int NCH, int TINY, bool DROP>
+template <typename T, int TL, int LPS, int NCH, int TINY, int DROP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NCH > 1 ? 4 : (sizeof(T) == 4 || TL == 64 ? 8 : 7)))) void aggregate_kernel(const AggK<T> p) {
   constexpr int VEC = RowIO<T>::WIDE;
   constexpr int RPW = 64 / TL;  // short rows per wavefront
@@ -694,7 +700,7 @@ __device__ inline void gather_teams(const AggK<T>& p, const T* __restrict__ X, c
   for (int i = 0; i < VEC; ++i) out[i] = acc[0][i];
 }
 
-template <typename T, int LPS, bool DROP>
+template <typename T, int LPS, int DROP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 5))) void aggregate_sliced_kernel(
     const AggK<T> p, int slice_bits, uint32_t long_units, int long_bits) {
   constexpr int VEC = RowIO<T>::WIDE;
@@ -779,7 +785,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 // instruction.  The groups of a wavefront are added by the same butterfly, then wavefront w > 0 writes its
 // partial panel to LDS and wavefront 0 adds the partials in ascending w: a fixed order.
 constexpr int HUB_WAVES = 16;
-template <typename T, int LPS, bool DROP>
+template <typename T, int LPS, int DROP>
 __global__ __launch_bounds__(HUB_WAVES * 64) void aggregate_hub_kernel(const AggK<T> p) {
   constexpr int VEC = RowIO<T>::WIDE;
   constexpr int NG = 64 / LPS;
@@ -874,14 +880,14 @@ struct LaunchCost {
 template <typename T, int WIDTH = RowIO<T>::WIDE - 1>
 static void launch_tiny(const AggK<T>& k, dim3 grid, hipStream_t stream) {
   if (k.width == WIDTH) {
-    aggregate_kernel<T, 16, 1, 1, WIDTH, false><<<grid, 256, 0, stream>>>(k);
+    aggregate_kernel<T, 16, 1, 1, WIDTH, 0><<<grid, 256, 0, stream>>>(k);
   } else {
     if constexpr (WIDTH > 1) launch_tiny<T, WIDTH - 1>(k, grid, stream);
   }
 }
 
 constexpr int ROW_PIECES = 128;  // wider rows take several launches
-template <typename T, bool DROP>
+template <typename T, int DROP>
 static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
   constexpr int WIDE = RowIO<T>::WIDE;
   const int chunks = (k.width + WIDE - 1) / WIDE;
@@ -895,8 +901,8 @@ static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCos
   const int64_t blocks = k.n_block + ((int64_t)k.n_wave + 3) / 4 + (short_rows + per_block - 1) / per_block;
   COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
   char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_kernel<%s,%d,%d,%d,%d,%s> width=%d", type_name<T>(), tl, lps, nch,
-           tiny ? (int)k.width : 0, DROP ? "true" : "false", (int)cost.a.width);
+  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_kernel<%s,%d,%d,%d,%d,%d> width=%d", type_name<T>(), tl, lps, nch,
+           tiny ? (int)k.width : 0, DROP, (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   const dim3 grid((unsigned)blocks);
   if (tiny) launch_tiny<T>(k, grid, stream);
@@ -911,7 +917,7 @@ static int32_t launch_rows(const AggK<T>& k, hipStream_t stream, const LaunchCos
   return COFREE_OK;
 }
 
-template <typename T, bool DROP>
+template <typename T, int DROP>
 static int32_t launch_sliced(const AggK<T>& k, int lps, int long_bits, int slice_bits, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
   const int64_t long_units = (k.n_wave + 3) / 4, rows = 4 * (64 / lps), parts = 8 >> slice_bits;
   const int64_t units = long_units + (k.n - k.n_wave + rows - 1) / rows;
@@ -919,7 +925,7 @@ static int32_t launch_sliced(const AggK<T>& k, int lps, int long_bits, int slice
   COFREE_REQUIRE(blocks < ((int64_t)1 << 31), "aggregate: grid too large");
   const dim3 grid((unsigned)blocks);
   char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_sliced_kernel<%s,%d,%s> width=%d", type_name<T>(), lps, DROP ? "true" : "false",
+  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_sliced_kernel<%s,%d,%d> width=%d", type_name<T>(), lps, DROP,
            (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   switch (lps) {
@@ -933,7 +939,7 @@ static int32_t launch_sliced(const AggK<T>& k, int lps, int long_bits, int slice
 }
 
 // hub rows: order[0 .. n_hub), one workgroup per (row, panel of lps lanes x 16 bytes)
-template <typename T, bool DROP>
+template <typename T, int DROP>
 static int32_t launch_hub(const AggK<T>& k, hipStream_t stream, const LaunchCost<T>& cost, int64_t nnz) {
   constexpr int WIDE = RowIO<T>::WIDE;
   int lps = 1;
@@ -942,7 +948,7 @@ static int32_t launch_hub(const AggK<T>& k, hipStream_t stream, const LaunchCost
   COFREE_REQUIRE(k.n < ((int64_t)1 << 31) && panels < 65536, "aggregate: hub grid too large");
   const dim3 grid((unsigned)k.n, (unsigned)panels);
   char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_hub_kernel<%s,%d,%s> width=%d", type_name<T>(), lps, DROP ? "true" : "false",
+  if (profiling()) snprintf(pname, sizeof(pname), "aggregate_hub_kernel<%s,%d,%d> width=%d", type_name<T>(), lps, DROP,
            (int)cost.a.width);
   ProfScope prof(pname, stream, cost.bytes(k.n, nnz), cost.flops(nnz));
   switch (lps) {
@@ -957,7 +963,7 @@ static int32_t launch_hub(const AggK<T>& k, hipStream_t stream, const LaunchCost
   return COFREE_OK;
 }
 
-template <typename T, bool DROP>
+template <typename T, int DROP>
 static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   constexpr int WIDE = RowIO<T>::WIDE;
   const T* X = (const T*)a.X;
@@ -1123,12 +1129,11 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
   return COFREE_OK;
 }
 
-// whole draws per lane: rows of a multiple of four contiguous columns, and of at least one wide access in every launch
-// (1028 bfloat16 columns leave four to the second)
+// contiguous rows of at least one wide access in every launch (1028 bfloat16 columns leave four to the second)
 bool aggregate_drops(const AggArgs& a) {
   const int wide = a.dtype == COFREE_F32 ? RowIO<float>::WIDE : RowIO<bf16_t>::WIDE;
   const int last = a.width % (ROW_PIECES * wide);
-  return a.width % 4 == 0 && a.ldy == a.width && (last == 0 || last >= wide);
+  return a.width >= wide && a.ldy == a.width && (last == 0 || last >= wide);
 }
 
 int32_t launch_aggregate(const AggArgs& a, hipStream_t stream) {
@@ -1140,9 +1145,11 @@ int32_t launch_aggregate(const AggArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(!a.add || !a.relu_src, "aggregate: gated and added to");
   COFREE_REQUIRE((a.ldx | a.ldy | a.ld_relu | a.ld_add) < ((int64_t)1 << 32), "aggregate: leading dimension too large");
   if (a.g.n == 0) return COFREE_OK;
-  const bool drop = a.dropout.q > 0.f;
-  if (a.dtype == COFREE_F32) return drop ? launch_typed<float, true>(a, stream) : launch_typed<float, false>(a, stream);
-  return drop ? launch_typed<bf16_t, true>(a, stream) : launch_typed<bf16_t, false>(a, stream);
+  auto typed = [&](auto drop) {
+    return a.dtype == COFREE_F32 ? launch_typed<float, decltype(drop)::value>(a, stream) : launch_typed<bf16_t, decltype(drop)::value>(a, stream);
+  };
+  if (!(a.dropout.q > 0.f)) return typed(std::integral_constant<int, 0>{});
+  return a.width % 4 == 0 ? typed(std::integral_constant<int, 1>{}) : typed(std::integral_constant<int, 2>{});
 }
 
 }  // namespace cofree

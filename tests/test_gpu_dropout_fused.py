@@ -18,6 +18,7 @@ SHAPES = [("sage_conv", 72, 132),   # aggregate first: split / resident product,
           ("gcn", 700, 640),        # aggregation in two panels / with two pieces per lane
           ("gcn", 1100, 1028),      # last panel of a bfloat16 row narrower than one access
           ("gcn", 80, 12),          # rows of few lanes, one window moved left
+          ("gcn", 128, 37), ("gcn", 128, 39), ("gcn", 700, 641), ("sage_conv", 200, 33), ("sage_conv", 90, 9), ("gcn", 1100, 1037),  # lanes that begin inside draws
           ("sage", 100, 260), ("sage", 64, 36)]
 
 
