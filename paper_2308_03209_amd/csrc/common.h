@@ -412,6 +412,10 @@ struct WgradArgs {
   const void* A = nullptr;
   int64_t lda = 0;
   int32_t N1 = 0;
+  // optional, where wgrad_two_fits(): a second matrix of the same shape and leading dimension, whose gradient A2^T B goes to C2
+  // (leading dimension ldc) from the same launch; the workspace is that of 2 N1 rows
+  const void* A2 = nullptr;
+  float* C2 = nullptr;
   const void* B = nullptr;
   int64_t ldb = 0;
   int32_t N2 = 0;
@@ -432,6 +436,7 @@ struct WgradArgs {
 int32_t launch_wgrad(const WgradArgs& a, SplitSums* sums, hipStream_t stream);
 int32_t launch_wgrads(const WgradArgs& a, const WgradArgs& b, SplitSums* sums, hipStream_t stream);  // one after the other, or paired
 size_t wgrad_workspace_floats(int32_t N1, int32_t N2, int64_t M, int32_t N2b = 0);
+bool wgrad_two_fits(int32_t dtype, int32_t N1, int32_t N2, int64_t M);
 size_t colsum_workspace_floats(int32_t N);
 // shared by the kernels; resident = workgroups of the kernel the chip holds at once (float32: three per CU; bfloat16:
 // two; float32 on the bfloat16 matrix cores: two, of which two rounds, so that no sum is longer than on the float32 ones)

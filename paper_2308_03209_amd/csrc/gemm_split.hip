@@ -92,7 +92,8 @@ struct SplitK {
   DropoutK drop;
   const unsigned char* planes;  // parameters split beforehand: [column tile][step][STEP_IMAGE]
   const uint32_t* small_params; // [column tile][step]: they are to be computed again (see below)
-  // second result (TWO): the columns from `half` on are those of A B_second^T, B1 = B_second + b_offset, stored at C_second
+  // second result (TWO): the columns from `half` on are those of A B_second^T, B1 = B_second + b_offset, stored at C_second;
+  // second weight gradient: the rows from `half` on are those of A2^T B
   const float* B_second;
   float* C_second;
   int64_t b_offset;
@@ -217,8 +218,9 @@ struct SplitKContig {
 };
 
 // k-major source (element (i, k) at P[k ld + i]): thread t holds column t%128 of the eight k of group t/128 (the same for
-// a whole wavefront, so rows are addressed with scalars).
-struct SplitKMajor {
+// a whole wavefront, so rows are addressed with scalars).  TWO: columns of two matrices.
+template <bool TWO>
+struct SplitKMajorOf {
   struct Raw {
     float x[8];
   };
@@ -233,6 +235,13 @@ struct SplitKMajor {
     k_len = (int)k_len_;
     const int64_t i = i0 + tid % TILE;
     off = (uint32_t)(i < extent - 1 ? i : extent - 1) * 4u;
+  }
+  // the first `half` columns are those of P, the others of P2
+  __device__ void init_two(const float* P, const float* P2, int32_t half, int64_t ld_, int64_t extent, int64_t i0, int64_t k_len_, int tid) {
+    init(P, ld_, extent, i0, k_len_, tid);
+    const int64_t i = off / 4u;
+    base = i < half ? P + i : P2 + (i - half);
+    off = 0;
   }
   __device__ void load(int t, Raw& w) const {
     const float* row = base + (int64_t)(window_of(t, k_len, 0).start + kq) * ld;
@@ -276,6 +285,8 @@ struct SplitKMajor {
     return any_bit(w.x[0], w.x[1], w.x[2], w.x[3]) | any_bit(w.x[4], w.x[5], w.x[6], w.x[7]);
   }
 };
+
+typedef SplitKMajorOf<false> SplitKMajor;
 
 // Parameters that split_params_kernel has split: the three planes of a step, 16 bytes (eight k of a row) after another
 struct SplitPlanes {
@@ -558,7 +569,8 @@ __device__ inline void run_plain(const float* A, int64_t ska, const float* B, in
 // DROP: dropout of the result, in rows of a multiple of four contiguous columns (529k x 512 with K = 1024: a pass of its own
 // took 353 us, a training step with three of them is 760 us shorter without).  Its generator runs beside the matrix
 // instructions of the CU's other workgroup, where a pass of its own reads and writes the result once more.
-// TWO: two results of one matrix A, whose columns follow one another and are stored apart, without an epilogue.
+// TWO: two results of one matrix A, whose columns follow one another and are stored apart, without an epilogue; two weight
+// gradients of one matrix B, whose rows follow one another.
 template <bool A_KMAJOR, bool B_KMAJOR, bool PLANES, bool DROP, bool TWO = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(
     const SplitK p) {
@@ -623,9 +635,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
   bool small = false;
   if constexpr (A_KMAJOR) {
     if (k_len > 0) {
-      SplitKMajor ma;
+      SplitKMajorOf<TWO> ma;
       SplitKMajor mb;
-      ma.init(p.A1 + k_beg * p.lda1, p.lda1, p.M, i0, k_len, tid);
+      if constexpr (TWO) ma.init_two(p.A1 + k_beg * p.lda1, p.A2 + k_beg * p.lda1, p.half, p.lda1, p.M, i0, k_len, tid);
+      else ma.init(p.A1 + k_beg * p.lda1, p.lda1, p.M, i0, k_len, tid);
       mb.init(Bw + k_beg * ldbw, ldbw, extent_b, jw, k_len, tid);
       run_split<true>(ma, mb, (int)k_len, smem, a_off, b_off, sums, tid, (int)(z & 1), p.colsum_part != nullptr && j0 == 0, csum,
                       small);
@@ -684,7 +697,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
 #pragma unroll
     for (int v = 0; v < 16; ++v) c[v] = 0.f;
     if constexpr (A_KMAJOR) {
-      run_plain(p.A1 + k_beg * p.lda1 + ia, p.lda1, Bw + k_beg * ldbw + ja, ldbw, k_len, g, c);
+      const float* const A = TWO && ia >= p.half ? p.A2 + (ia - p.half) : p.A1 + ia;
+      run_plain(A + k_beg * p.lda1, p.lda1, Bw + k_beg * ldbw + ja, ldbw, k_len, g, c);
     } else {
 #pragma nounroll
       for (int seg = 0; seg < n_seg; ++seg) {
@@ -957,8 +971,8 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
     p.small_params = q.flags;
   }
   char pname[96] = "";
-  if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<false,%s,%s,%s> N=%d K=%d", a.b_kmajor ? "true" : "false",
-           planes ? "true" : "false", drop && !a.b_kmajor ? "true" : "false", (int)N, (int)K);
+  if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<false,%s,%s,%s,%s> N=%d K=%d", a.b_kmajor ? "true" : "false",
+           planes ? "true" : "false", drop && !a.b_kmajor ? "true" : "false", a.C_second ? "true" : "false", (int)N, (int)K);
   ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + (double)N * K + (double)a.M * N * (a.accumulate ? 2 : 1)),
                  2.0 * (double)a.M * N * (double)K);
   const dim3 grid((unsigned)blocks);
@@ -980,11 +994,13 @@ bool wgrad_split_fits(const WgradArgs& a) {
 }
 
 int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
-  const int32_t N1 = a.N1, N2 = a.N2 + (a.B2 ? a.N2b : 0);
+  const int32_t N1 = a.A2 ? 2 * a.N1 : a.N1, N2 = a.N2 + (a.B2 ? a.N2b : 0);
   const int32_t S = wgrad_splits(N1, N2, a.M, WGRAD_RESIDENT_SPLIT);
   SplitK p{};
   p.A1 = (const float*)a.A;
   p.lda1 = a.lda;
+  p.A2 = (const float*)a.A2;
+  p.half = a.A2 ? a.N1 : INT_MAX;
   p.B1 = (const float*)a.B;
   p.ldb1 = a.ldb;
   p.B2 = (const float*)a.B2;
@@ -1009,14 +1025,16 @@ int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stre
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "wgrad: grid too large");
   {
     char pname[96] = "";
-    if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<true,true,false,false> N=%dx%d", (int)N1, (int)N2);
+    if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_kernel<true,true,false,false,%s> N=%dx%d", a.A2 ? "true" : "false", (int)N1, (int)N2);
     ProfScope prof(pname, stream, 4.0 * ((double)a.M * N1 * (p.extra.X ? 2 : 1) + (double)a.M * N2 + (double)N1 * N2),
                    2.0 * (double)a.M * N1 * N2);
-    gemm_split_kernel<true, true, false, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
+    if (a.A2) gemm_split_kernel<true, true, false, false, true><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
+    else gemm_split_kernel<true, true, false, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
   }
   COFREE_HIP_CHECK(hipGetLastError());
-  COFREE_TRY(add_split_sum(sums, a.workspace, p.c_split_stride, S, a.C, a.ldc, N1, N2));
-  if (p.colsum_part) COFREE_TRY(add_split_sum(sums, colsum_part, N1, S, a.colsum_out, N1, 1, N1));
+  COFREE_TRY(add_split_sum(sums, a.workspace, p.c_split_stride, S, a.C, a.ldc, a.N1, N2));
+  if (a.A2) COFREE_TRY(add_split_sum(sums, a.workspace + (size_t)a.N1 * N2, p.c_split_stride, S, a.C2, a.ldc, a.N1, N2));
+  if (p.colsum_part) COFREE_TRY(add_split_sum(sums, colsum_part, N1, S, a.colsum_out, a.N1, 1, a.N1));
   return COFREE_OK;
 }
 

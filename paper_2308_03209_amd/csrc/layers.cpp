@@ -146,6 +146,11 @@ static size_t param_scratch_bytes(const cofree_layer_desc& d, int64_t n) {
   return max2(gemm_param_scratch_bytes(d.d_out, d.d_in), gemm_param_scratch_bytes(d.d_in, d.d_out));
 }
 
+// ... and both weight gradients, of dPre and mean^T(dPre), which read H too.
+static bool conv_two_wgrads(const cofree_layer_desc& d, int64_t n) {
+  return d.kind == COFREE_SAGE_CONV && conv_transform_first(d) && wgrad_two_fits(d.dtype, d.d_out, d.d_in, n);
+}
+
 struct FwdPlan {
   void* T = nullptr;       // transform-first: norm * (H W^T) (GCN), H W_neigh^T (conventional GraphSAGE)
   void* S = nullptr;       // H W_self^T where both products are one launch
@@ -196,8 +201,8 @@ static BwdPlan plan_bwd(const cofree_layer_desc& d, int64_t n, Carver& c, Carver
     if (d.dropout_q > 0.f || d.act) p.dP = c.take(N * d.d_out * es);
     // transform first: T = Ahat dPre [n, d_out]; aggregate first: T = norm * (dPre W) [n, d_in]
     p.T = c.take(N * (gcn_transform_first(d) ? d.d_out : d.d_in) * es);
-    p.wg[0] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n, conv_merged(d) ? d.d_in : 0));
-    if (d.kind == COFREE_SAGE_CONV && !conv_merged(d)) p.wg[1] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
+    p.wg[0] = (float*)part.take(4 * wgrad_workspace_floats(conv_two_wgrads(d, n) ? 2 * d.d_out : d.d_out, d.d_in, n, conv_merged(d) ? d.d_in : 0));
+    if (d.kind == COFREE_SAGE_CONV && !conv_merged(d) && !conv_two_wgrads(d, n)) p.wg[1] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
     if (d.kind == COFREE_GCN && gcn_transform_first(d)) p.cs = (float*)part.take(4 * colsum_workspace_floats(d.d_out));
   }
   p.needed = c.used;
@@ -609,18 +614,20 @@ static int32_t layer_bwd(const cofree_partition* part, const cofree_masks* masks
     if (!transform_first) COFREE_REQUIRE(saved->A, "layer_bwd: saved.A is NULL");
     // dW_neigh = dT^T H where the forward pass was mean(H W_neigh^T), in the launch of dW_self where both can be
     const WgradArgs wn = transform_first ? wgrad(p.T, d.d_out, H_in, d.d_in, grads->W + d.d_in, ldw, p.wg[1]) : WgradArgs{};
-    const bool together = transform_first && !side && wgrads_pair(w, wn);
+    const bool both = conv_two_wgrads(d, n);  // as two results of one product
+    if (both) w.A2 = p.T, w.C2 = grads->W + d.d_in;
+    const bool together = transform_first && !both && !side && wgrads_pair(w, wn);
     // dW_neigh = dPre^T M where the forward pass has kept M = mean(H) (side stream as well)
     if (!transform_first && !merged_dW)
       COFREE_TRY(launch_wgrads(w, wgrad(dPre, d.d_out, saved->A, d.d_in, grads->W + d.d_in, ldw, p.wg[1]), sums, s2));
-    else if (!together)
+    else if (!together && !both)
       COFREE_TRY(launch_wgrad(w, sums, s2));
     if (transform_first || (dH_in && conv_gathers_grad(d))) {
       AggArgs t = agg();  // dT = mean^T(dPre)
       t.X = dPre; t.Y = p.T; t.width = d.d_out; t.ldx = t.ldy = d.d_out;
       t.in_scale = g.inv_deg;
       COFREE_TRY(launch_aggregate(t, s));
-      if (transform_first) COFREE_TRY(together ? launch_wgrads(w, wn, sums, s) : launch_wgrad(wn, sums, s));
+      if (transform_first) COFREE_TRY(both ? launch_wgrad(w, sums, s) : together ? launch_wgrads(w, wn, sums, s) : launch_wgrad(wn, sums, s));
       if (dH_in) {
         GemmArgs h = gemm();
         // W_self and W_neigh are column blocks of W: dH = dT W_neigh + dPre W_self is one product over the

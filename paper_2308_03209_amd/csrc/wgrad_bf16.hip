@@ -31,12 +31,13 @@ constexpr int WG_WAVES = 8, WG_CUS = 256;
 
 struct WgradK {
   const bf16_t* A;
+  const bf16_t* A2;  // a second matrix like A, or null
   const bf16_t* B;
   const bf16_t* B2;
   int64_t lda, ldb, ldb2;
-  int32_t N1, N2, N2b;  // columns of the three matrices (N2b = 0: no second one)
+  int32_t N1, N1b, N2, N2b;  // columns of the four matrices (N1b, N2b = 0: no second one)
   int64_t M, chunk;
-  float* C;  // partials: [chunks][N1][N2 + N2b]
+  float* C;  // partials: [chunks][N1 + N1b][N2 + N2b]
   int32_t tiles_m, tiles_n;
   int64_t n_chunks;
   float* colsum_part;  // [chunks][N1] partial column sums of A, or null
@@ -44,11 +45,11 @@ struct WgradK {
 };
 
 // Places of operand columns: pieces of eight, the last piece of a matrix moved left to end with its rows (the columns it
-// shares with the piece before are computed twice and stored once), the pieces of B2 behind those of B.
+// shares with the piece before are computed twice and stored once), the pieces of a second matrix behind those of the first.
 struct Piece {
   int32_t col;    // first column inside its matrix
   int32_t first;  // columns of it that belong to the piece before
-  bool second;    // a piece of B2
+  bool second;    // a piece of the second matrix
   bool exists;
 };
 __device__ inline Piece piece_of(int q, int32_t N, int32_t Nb) {
@@ -111,9 +112,9 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
   // thread t moves piece t % Q of rows t / Q + (T / Q) j of a step; rows past the chunk repeat its last one (and become
   // zero on the way to LDS)
   const int ra = tid / QA, rb = tid / QB;
-  const Piece xa = piece_of(qm + tid % QA, p.N1, 0), xb = piece_of(qn + tid % QB, p.N2, p.N2b);
+  const Piece xa = piece_of(qm + tid % QA, p.N1, p.N1b), xb = piece_of(qn + tid % QB, p.N2, p.N2b);
   const int64_t ldb = xb.second ? p.ldb2 : p.ldb;
-  const bf16_t* const pa = p.A + k_beg * p.lda + xa.col;
+  const bf16_t* const pa = (xa.second ? p.A2 : p.A) + k_beg * p.lda + xa.col;
   const bf16_t* const pb = (xb.second ? p.B2 : p.B) + k_beg * ldb + xb.col;
   struct Raw {
     u32x4u a[JA], b[JB];
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
   // accumulator register v of lane (g, r) is element [8 (v / 4) + 4 g + v % 4][r] of its 32 x 32 block
   const int g = lane >> 5, r = lane & 31;
   const int64_t ldc = (int64_t)p.N2 + p.N2b;
-  float* const Cz = p.C + z * p.N1 * ldc;
+  float* const Cz = p.C + z * (p.N1 + p.N1b) * ldc;
 #pragma unroll
   for (int q = 0; q < RN; ++q) {
     const int place = (wn * RN + q) * 32 + r;
@@ -220,10 +221,11 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
     for (int m = 0; m < RM; ++m)
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
-        const Piece xr = piece_of(qm + (wm * RM + m) * 4 + h, p.N1, 0);
+        const Piece xr = piece_of(qm + (wm * RM + m) * 4 + h, p.N1, p.N1b);
+        const int32_t row = (xr.second ? p.N1 : 0) + xr.col + 4 * g;
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          if (xr.exists && 4 * g + v >= xr.first) Cz[(int64_t)(xr.col + 4 * g + v) * ldc + j] = acc[m][q][4 * h + v];
+          if (xr.exists && 4 * g + v >= xr.first) Cz[(int64_t)(row + v) * ldc + j] = acc[m][q][4 * h + v];
       }
   }
   if (colsum) {
@@ -236,8 +238,8 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
     if (tid < TM) {
       float t = 0.f;
       for (int h = 0; h < T / QA; ++h) t += red[h * TM + tid];
-      const Piece xr = piece_of(qm + (tid >> 3), p.N1, 0);
-      if (xr.exists && (tid & 7) >= xr.first) p.colsum_part[z * p.N1 + xr.col + (tid & 7)] = t;
+      const Piece xr = piece_of(qm + (tid >> 3), p.N1, p.N1b);
+      if (xr.exists && !xr.second && (tid & 7) >= xr.first) p.colsum_part[z * p.N1 + xr.col + (tid & 7)] = t;
     }
   }
 }
@@ -254,8 +256,8 @@ static int32_t pieces_of(int32_t N) { return (N + 7) / 8; }
 struct WgradTile {
   int32_t h, w, m, n;
 };
-static WgradTile wgrad_tile(int32_t N1, int32_t N2, int32_t N2b, int64_t M) {
-  const int32_t rows = 8 * pieces_of(N1), columns = 8 * (pieces_of(N2) + pieces_of(N2b));
+// rows, columns: in whole pieces
+static WgradTile wgrad_tile(int32_t rows, int32_t columns, int64_t M) {
   const int32_t small = ((rows + 127) / 128) * ((columns + 127) / 128);  // tiles of 128 x 128
   const bool narrow = M < (1 << 17) && (small <= 10 || M < (1 << 15)), middling = small <= 4 && M < (1 << 20);
   WgradTile t;
@@ -280,7 +282,7 @@ static int32_t wgrad_chunks(int32_t tiles, int64_t M) {
 bool wgrad_bf16_fits(int32_t N1, int32_t N2, int32_t N2b) { return N1 >= 8 && N2 >= 8 && (N2b == 0 || N2b >= 8); }
 
 size_t wgrad_bf16_workspace_floats(int32_t N1, int32_t N2, int32_t N2b, int64_t M) {
-  const WgradTile t = wgrad_tile(N1, N2, N2b, M);
+  const WgradTile t = wgrad_tile(8 * pieces_of(N1), 8 * (pieces_of(N2) + pieces_of(N2b)), M);
   return (size_t)wgrad_chunks(t.m * t.n, M) * ((size_t)N1 * ((size_t)N2 + N2b) + (size_t)N1);
 }
 
@@ -293,18 +295,21 @@ int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t 
   p.B2 = (const bf16_t*)a.B2;
   p.ldb2 = a.ldb2;
   p.N1 = a.N1;
+  p.A2 = (const bf16_t*)a.A2;
+  p.N1b = a.A2 ? a.N1 : 0;
   p.N2 = a.N2;
   p.N2b = a.B2 ? a.N2b : 0;
   p.M = a.M;
   const int32_t N2 = p.N2 + p.N2b;
-  const WgradTile tile = wgrad_tile(p.N1, p.N2, p.N2b, a.M);
+  const WgradTile tile = wgrad_tile(8 * (pieces_of(p.N1) + pieces_of(p.N1b)), 8 * (pieces_of(p.N2) + pieces_of(p.N2b)), a.M);
   p.tiles_m = tile.m;
   p.tiles_n = tile.n;
   const int32_t S = wgrad_chunks(tile.m * tile.n, a.M);
   p.n_chunks = S;
   p.chunk = std::max<int64_t>(1, (((a.M + S - 1) / S) + 31) / 32 * 32);
   p.C = a.workspace;
-  float* const colsum_part = a.workspace + (size_t)S * a.N1 * N2;
+  const int32_t N1 = p.N1 + p.N1b;
+  float* const colsum_part = a.workspace + (size_t)S * N1 * N2;
   p.colsum_part = a.colsum_out && !a.colsum_src ? colsum_part : nullptr;
   COFREE_TRY(plan_colsum(a, &p.extra, sums));
   const int64_t blocks = ((p.n_chunks + 7) / 8) * 8 * p.tiles_m * p.tiles_n + (p.extra.blocks + 1) / 2;
@@ -314,9 +319,9 @@ int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t 
     char pname[96] = "";
     const char* rest = tw == 256 ? (th == 256 ? "32,3,2,4" : (th == 128 ? "32,4,2,4" : "64,2,1,8"))
                                  : (th == 256 ? "32,4,4,2" : (th == 128 ? "32,6,2,4" : "64,4,2,4"));
-    if (profiling()) snprintf(pname, sizeof(pname), "wgrad_bf16_kernel<%d,%d,%s> N=%dx%d", (int)th, (int)tw, rest, (int)a.N1, (int)N2);
-    ProfScope prof(pname, stream, 2.0 * ((double)a.M * a.N1 * (p.extra.X ? 2 : 1) + (double)a.M * N2) + 4.0 * (double)a.N1 * N2,
-                   2.0 * (double)a.M * a.N1 * N2);
+    if (profiling()) snprintf(pname, sizeof(pname), "wgrad_bf16_kernel<%d,%d,%s> N=%dx%d", (int)th, (int)tw, rest, (int)N1, (int)N2);
+    ProfScope prof(pname, stream, 2.0 * ((double)a.M * N1 * (p.extra.X ? 2 : 1) + (double)a.M * N2) + 4.0 * (double)N1 * N2,
+                   2.0 * (double)a.M * N1 * N2);
     const dim3 grid((unsigned)blocks);
     if (tw == 256) {
       if (th == 256) wgrad_bf16_kernel<256, 256, 32, 3, 2, 4><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
@@ -329,7 +334,8 @@ int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t 
     }
   }
   COFREE_HIP_CHECK(hipGetLastError());
-  COFREE_TRY(add_split_sum(sums, a.workspace, (int64_t)a.N1 * N2, S, a.C, a.ldc, a.N1, N2));
+  COFREE_TRY(add_split_sum(sums, a.workspace, (int64_t)N1 * N2, S, a.C, a.ldc, a.N1, N2));
+  if (a.A2) COFREE_TRY(add_split_sum(sums, a.workspace + (size_t)a.N1 * N2, (int64_t)N1 * N2, S, a.C2, a.ldc, a.N1, N2));
   if (p.colsum_part) COFREE_TRY(add_split_sum(sums, colsum_part, a.N1, S, a.colsum_out, a.N1, 1, a.N1));
   return COFREE_OK;
 }
