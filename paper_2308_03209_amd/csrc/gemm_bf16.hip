@@ -11,6 +11,7 @@
 // them into the [i][k] LDS layout.
 #include <cstdio>
 #include <cstdlib>
+#include <type_traits>
 
 #include "colsum.h"
 #include "common.h"
@@ -37,6 +38,8 @@ struct GemmHK {
   int32_t K2;
   const bf16_t* B;
   int64_t ldb;
+  const float* W[2];  // parameters of the two segments, float32 (PARAMS_ROWS, PARAMS_COLUMNS)
+  int64_t ldw[2];
   void* C;
   int64_t ldc;
   int32_t c_f32;  // 1: C is float32 (weight-gradient partials), 0: bf16
@@ -147,6 +150,88 @@ struct HMoverKContig {
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
       *reinterpret_cast<uint4*>(d + RP * j * HLD) = make_uint4(w.x[j][0], w.x[j][1], w.x[j][2], w.x[j][3]);
+  }
+};
+
+// Parameters as they are, float32, converted on the way to LDS (PARAMS_ROWS: element (column j, k) at W[j ld + k], a thread's share as
+// above; PARAMS_COLUMNS: at W[k ld + j], thread t has column t % COLS, so that a wavefront reads whole lines, and 8 NJ of the 64 k).
+constexpr int PARAMS_COPY = 0, PARAMS_ROWS = 1, PARAMS_COLUMNS = 2;
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+template <int NJ, int PARAMS>
+struct HMoverParams {
+  static constexpr int COLS = 32 * NJ;
+  struct Raw {
+    float x[NJ][8];
+  };
+  const char* base;                                // the tile's first column, uniform
+  uint32_t off[PARAMS == PARAMS_ROWS ? NJ : 1];  // bytes from there to the thread's share of the first step
+  int64_t ld;
+  int kq;  // first k of that share
+  __device__ void init(const float* W, int64_t ld_, int64_t extent, int64_t j0, int tid) {
+    ld = ld_;
+    const int32_t last = (int32_t)(extent - 1 - j0);
+    if constexpr (PARAMS == PARAMS_ROWS) {
+      base = reinterpret_cast<const char*>(W + j0 * ld);
+      kq = (tid & 7) * 8;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int32_t r = (tid >> 3) + 32 * j;
+        off[j] = ((uint32_t)(r < last ? r : last) * (uint32_t)ld + (uint32_t)kq) * 4u;
+      }
+    } else {
+      base = reinterpret_cast<const char*>(W + j0);
+      kq = __builtin_amdgcn_readfirstlane(tid / COLS) * (8 * NJ);
+      off[0] = (uint32_t)(tid % COLS < last ? tid % COLS : last) * 4u;
+    }
+  }
+  // the thread's element k of the range (PARAMS_ROWS: of its row j)
+  __device__ const float* at(int j, int64_t k) const {
+    if constexpr (PARAMS == PARAMS_ROWS) return reinterpret_cast<const float*>(base + (k - kq) * 4 + off[j]);
+    else return reinterpret_cast<const float*>(base + k * ld * 4 + off[0]);
+  }
+  __device__ void load(int64_t k0, Raw& w) const {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      if constexpr (PARAMS == PARAMS_ROWS) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float4u v = *reinterpret_cast<const float4u*>(base + (k0 + 4 * h) * 4 + off[j]);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) w.x[j][4 * h + c] = v[c];
+        }
+      } else {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) w.x[j][c] = *at(j, k0 + kq + 8 * j + c);
+      }
+    }
+  }
+  // the last step of a range: clamped element loads, zero past the end
+  __device__ void load_ragged(int64_t k0, int64_t k_len, int, Raw& w) const {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const int64_t k = k0 + kq + (PARAMS == PARAMS_ROWS ? c : 8 * j + c), kc = k < k_len ? k : k_len - 1;
+        w.x[j][c] = *at(j, kc);
+      }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const int64_t k = k0 + kq + (PARAMS == PARAMS_ROWS ? c : 8 * j + c);
+        w.x[j][c] = k < k_len ? w.x[j][c] : 0.f;
+      }
+  }
+  __device__ void load_ragged_short(int64_t k0, int64_t k_len, int tid, Raw& w) const { load_ragged(k0, k_len, tid, w); }
+  __device__ void store(bf16_t* lds, int tid, const Raw& w) const {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int g8 = kq / 8 + (PARAMS == PARAMS_ROWS ? 0 : j);  // of the step's eight groups of eight k
+      const int row = PARAMS == PARAMS_ROWS ? (tid >> 3) + 32 * j : tid % COLS;
+      *reinterpret_cast<uint4*>(lds + (g8 >> 2) * HHALF + row * HLD + (g8 & 3) * 8) =
+          make_uint4(pack_bf16x2(w.x[j][0], w.x[j][1]), pack_bf16x2(w.x[j][2], w.x[j][3]), pack_bf16x2(w.x[j][4], w.x[j][5]),
+                     pack_bf16x2(w.x[j][6], w.x[j][7]));
+    }
   }
 };
 
@@ -392,7 +477,8 @@ constexpr size_t bf16_lds_bytes() {
   return operands > staging ? operands : staging;
 }
 
-template <bool WGRAD, bool SINGLE, bool NARROW, int WM = 2, int WN = 2>
+// PARAMS: parameters from their bfloat16 copy B, or float32 as they are.
+template <bool WGRAD, bool SINGLE, bool NARROW, int WM = 2, int WN = 2, int PARAMS = PARAMS_COPY>
 __global__ __launch_bounds__(64 * WM * WN)
     __attribute__((amdgpu_waves_per_eu(WGRAD ? 2 : (WM * WN > 4 ? 4 : 3)))) void gemm_bf16_kernel(const GemmHK p) {
   static_assert((WM == 2 && WN == 2) || (!WGRAD && !NARROW), "larger tiles: plain A B^T only");
@@ -447,9 +533,10 @@ __global__ __launch_bounds__(64 * WM * WN)
 #pragma nounroll
     for (int seg = 0; seg < n_seg; ++seg) {
       HMoverKContig<TM / RP, RP, HALF_A> ma;
-      HMoverKContig<TN / RP, RP, HALF_B> mb;
       ma.init(seg ? p.A2 : p.A1, seg ? p.lda2 : p.lda1, p.M, i0, tid);
-      mb.init(p.B + (seg ? p.K1 : 0), p.ldb, p.N, j0, tid);
+      typename std::conditional<PARAMS == PARAMS_COPY, HMoverKContig<TN / RP, RP, HALF_B>, HMoverParams<TN / 32, PARAMS>>::type mb;
+      if constexpr (PARAMS == PARAMS_COPY) mb.init(p.B + (seg ? p.K1 : 0), p.ldb, p.N, j0, tid);
+      else mb.init(p.W[seg], p.ldw[seg], p.N, j0, tid);
       run_steps_bf16<NARROW ? HDEPTH_NARROW : HDEPTH_NT, AN>(
           ma, mb, seg ? p.K2 : p.K1, As, Bs, ((wm * 64 + (lane & 31)) * HLD + (lane >> 5) * 8),
           ((wn * (32 * AN) + (lane & 31)) * HLD + (lane >> 5) * 8), HALF_A, HALF_B, acc, tid);
@@ -628,6 +715,23 @@ __global__ __launch_bounds__(256) void convert_params_kernel(const float* __rest
 static int64_t pad8(int64_t k) { return (k + 7) & ~(int64_t)7; }
 size_t gemm_param_scratch_bytes(int32_t N, int64_t K) { return (size_t)N * (size_t)pad8(K) * sizeof(bf16_t); }
 
+// Bfloat16 copy [N][ldd] of a product's parameters, the second segment's behind the first's, zeros up to ldd.
+static int32_t convert_params(const GemmArgs& a, bf16_t* Wb, int64_t ldd, hipStream_t stream) {
+  const int64_t K = (int64_t)a.K1 + a.K2;
+  const bool two = a.K2 > 0 && a.B2;  // the second segment has its own parameter matrix
+  const int64_t total = (int64_t)a.N * ldd;
+  ProfScope prof("convert_params_kernel", stream, 6.0 * (double)total, 0.0);
+  convert_params_kernel<<<dim3((unsigned)((total + 255) / 256)), 256, 0, stream>>>(a.B, a.ldb, a.b_kmajor, a.N, two ? a.K1 : K, Wb,
+                                                                                   ldd, 0, ldd);
+  if (two) {
+    const int64_t total2 = (int64_t)a.N * a.K2;
+    convert_params_kernel<<<dim3((unsigned)((total2 + 255) / 256)), 256, 0, stream>>>(a.B2, a.ldb2, a.b_kmajor, a.N, a.K2, Wb, ldd,
+                                                                                      a.K1, a.K2);
+  }
+  COFREE_HIP_CHECK(hipGetLastError());
+  return COFREE_OK;
+}
+
 int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(a.M >= 0 && a.N >= 1 && a.K1 >= 1 && a.K2 >= 0, "dense: bad shape");
   COFREE_REQUIRE(a.K2 == 0 || a.A2, "dense: second segment is NULL");
@@ -646,21 +750,23 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
   const bool pinned = gemm_pinned_fits(a);
   if (!pinned && gemm_resident_fits(a)) return launch_gemm_resident(a, stream);
   if (!pinned && a.dropout.q > 0.f) return fail(COFREE_EINVAL, "internal: no dropout in tiled products");
-  const int64_t ldd = pad8(K);
-  bf16_t* Wb = (bf16_t*)a.param_scratch;
-  {
-    // columns [0, K) of the copy from B (or [0, K1) from B and [K1, K) from B2), zeros up to ldd
-    const int64_t kb = two ? a.K1 : K;
-    const int64_t total = (int64_t)a.N * ldd;
-    ProfScope prof("convert_params_kernel", stream, 6.0 * (double)total, 0.0);
-    convert_params_kernel<<<dim3((unsigned)((total + 255) / 256)), 256, 0, stream>>>(a.B, a.ldb, a.b_kmajor, a.N, kb,
-                                                                                     Wb, ldd, 0, ldd);
-    if (two) {
-      const int64_t total2 = (int64_t)a.N * a.K2;
-      convert_params_kernel<<<dim3((unsigned)((total2 + 255) / 256)), 256, 0, stream>>>(a.B2, a.ldb2, a.b_kmajor, a.N,
-                                                                                        a.K2, Wb, ldd, a.K1, a.K2);
-    }
+  const bool narrow = a.N <= 64;  // one 128x64 tile per row panel
+  // 256x256 tiles once the matrix gives every CU more than one of them (one such block fills a CU, so small
+  // launches keep the 128x128 tile and its three blocks per CU).  COFREE_BF16_TILE = 256 / 128 forces a
+  // choice (tests run small shapes through the large tile with it).
+  bool big = !narrow && a.N > HBN && a.M >= (int64_t)2 * 256 * 256;
+  if (const char* e = getenv("COFREE_BF16_TILE")) {
+    if (atoi(e) == 256) big = !narrow && a.N > HBN;
+    if (atoi(e) == 128) big = false;
   }
+  // Narrow products of few rows read their parameters in float32, which saves the launch that converts them (us of a layer with / without
+  // it: 2,000 rows, GCN 128 -> 24 forward 11.5 / 9.7, printed GraphSAGE of 24 columns 16.6 / 14.5 forward, 32.4 / 28.6 backward; 30k rows
+  // 14.5 / 12.7, 19.5 / 17.3, 36.2 / 32.7; 100k 29.0 / 27.5, 33.6 / 34.0, 56.9 / 54.9; 500k 94 / 94, 100 / 109, 151 / 158).  In the tiles of 128
+  // columns that was no faster (256 -> 256 over 2,000 rows 26.7 / 25.2, 30k 43.7 / 43.7, 500 -> 500 over 30k 57 / 63).
+  const bool as_is = narrow && a.M < 1 << 16 && (a.ldb | a.ldb2) < 1 << 22;  // (32-bit offsets)
+  const int64_t ldd = pad8(K);
+  bf16_t* const Wb = (bf16_t*)a.param_scratch;
+  if (pinned || !as_is) COFREE_TRY(convert_params(a, Wb, ldd, stream));
   if (pinned) return launch_gemm_pinned(a, Wb, ldd, stream);
   GemmHK p{};
   p.A1 = (const bf16_t*)a.A1;
@@ -671,6 +777,10 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
   p.K2 = a.K2;
   p.B = Wb;
   p.ldb = ldd;
+  p.W[0] = a.B;
+  p.W[1] = a.B2 ? a.B2 : a.B + (a.b_kmajor ? (int64_t)a.K1 * a.ldb : (int64_t)a.K1);
+  p.ldw[0] = a.ldb;
+  p.ldw[1] = a.B2 ? a.ldb2 : a.ldb;
   p.C = a.C;
   p.ldc = a.ldc;
   p.c_f32 = 0;
@@ -687,7 +797,6 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
   p.relu_last = a.relu_last;
   p.gate_last = a.gate_last;
   p.gate_scale = a.gate ? a.gate_scale : 1.f;
-  const bool narrow = a.N <= 64;  // one 128x64 tile per row panel
   p.tiles_n = narrow ? 1 : (a.N + HBN - 1) / HBN;
   p.tiles_m = 1;
   p.n_groups = (a.M + HBM - 1) / HBM;
@@ -695,17 +804,9 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "dense: grid too large");
   const double flops = 2.0 * (double)a.M * a.N * (double)K;
   const double bytes = 2.0 * ((double)a.M * K + (double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1));
-  // 256x256 tiles once the matrix gives every CU more than one of them (one such block fills a CU, so small
-  // launches keep the 128x128 tile and its three blocks per CU).  COFREE_BF16_TILE = 256 / 128 forces a
-  // choice (tests run small shapes through the large tile with it).
-  bool big = !narrow && a.N > HBN && a.M >= (int64_t)2 * 256 * 256;
-  if (const char* e = getenv("COFREE_BF16_TILE")) {
-    if (atoi(e) == 256) big = !narrow && a.N > HBN;
-    if (atoi(e) == 128) big = false;
-  }
   char pname[96] = "";  // the template instance launched below, then the shape
-  if (profiling()) snprintf(pname, sizeof(pname), "gemm_bf16_kernel<false,false,%s> N=%d K=%d", big ? "false,4,4" : (narrow ? "true,2,2" : "false,2,2"),
-           (int)a.N, (int)K);
+  if (profiling()) snprintf(pname, sizeof(pname), "gemm_bf16_kernel<false,false,%s,%d> N=%d K=%d", big ? "false,4,4" : (narrow ? "true,2,2" : "false,2,2"),
+           !as_is ? PARAMS_COPY : (a.b_kmajor ? PARAMS_COLUMNS : PARAMS_ROWS), (int)a.N, (int)K);
   ProfScope prof(pname, stream, bytes, flops);
   if (big) {
     p.tiles_n = (a.N + 255) / 256;
@@ -713,10 +814,13 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
     const int64_t wblocks = ((p.n_groups + 7) / 8) * 8 * p.tiles_n;
     COFREE_REQUIRE(wblocks > 0 && wblocks < ((int64_t)1 << 31), "dense: grid too large");
     gemm_bf16_kernel<false, false, false, 4, 4><<<dim3((unsigned)wblocks), 1024, 0, stream>>>(p);
-  } else if (narrow)
-    gemm_bf16_kernel<false, false, true><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
-  else
-    gemm_bf16_kernel<false, false, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
+  } else {
+    const dim3 grid((unsigned)blocks);
+    if (as_is && a.b_kmajor) gemm_bf16_kernel<false, false, true, 2, 2, PARAMS_COLUMNS><<<grid, 256, 0, stream>>>(p);
+    else if (as_is) gemm_bf16_kernel<false, false, true, 2, 2, PARAMS_ROWS><<<grid, 256, 0, stream>>>(p);
+    else if (narrow) gemm_bf16_kernel<false, false, true><<<grid, 256, 0, stream>>>(p);
+    else gemm_bf16_kernel<false, false, false><<<grid, 256, 0, stream>>>(p);
+  }
   COFREE_HIP_CHECK(hipGetLastError());
   return COFREE_OK;
 }
@@ -755,7 +859,7 @@ int32_t launch_wgrad_bf16(const WgradArgs& a, SplitSums* sums, hipStream_t strea
   {
     const bool single = N1 % HBM == 1 || a.N2 % HBN == 1 || (a.B2 && a.N2b % HBN == 1);
     char pname[96] = "";
-    if (profiling()) snprintf(pname, sizeof(pname), "gemm_bf16_kernel<true,%s,false,2,2> N=%dx%d", single ? "true" : "false", (int)N1, (int)N2);
+    if (profiling()) snprintf(pname, sizeof(pname), "gemm_bf16_kernel<true,%s,false,2,2,0> N=%dx%d", single ? "true" : "false", (int)N1, (int)N2);
     ProfScope prof(pname, stream, 2.0 * ((double)M * N1 * (p.extra.X ? 2 : 1) + (double)M * N2) + 4.0 * (double)N1 * N2,
                    2.0 * (double)M * N1 * N2);
     if (single)
