@@ -57,10 +57,11 @@ def test_many_rows(G, n, d_in, d_out):  # noqa: F811
         assert float(err) <= 2e-2 and float(fro) <= 1e-2, (what, float(err), float(fro))
 
 
-@pytest.mark.parametrize("kind,dims", [("gcn", (1, 8, 3)), ("gcn", (7, 8, 64)), ("gcn", (8, 8, 31)), ("gcn", (63, 8, 17)), ("gcn", (64, 8, 1)),
+@pytest.mark.parametrize("kind,dims", [("gcn", (1, 8, 3)), ("gcn", (7, 8, 64)), ("gcn", (8, 8, 31)), ("gcn", (63, 8, 17)), ("gcn", (64, 8, 9)),
                                        ("gcn", (65, 8, 40)), ("gcn", (130, 8, 63)), ("sage", (5, 9, 64)), ("sage", (66, 33, 20)),
                                        ("sage", (64, 70, 48)), ("sage_conv", (130, 8, 24)), ("sage_conv", (20, 8, 50))])
 def test_narrow_products_of_few_rows(G, kind, dims, monkeypatch):  # noqa: F811
-    """Tiles of 64 columns, which read few rows' parameters as they are: edges of columns, steps of 64 k and of eight, both segments."""
+    """Tiles of 64 columns, which read few rows' parameters as they are: edges of columns, steps of 64 k and of eight, both segments.
+    (Not a single column: its one bias gradient is a sum that cancels, 2.7 % off with the converted copy and without, whose bits agree.)"""
     monkeypatch.setenv("COFREE_BF16_TILE", "128")
     check_single_layer_bf16(G, kind, dims)
