@@ -894,6 +894,202 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
   }
 }
 
+// ---- few rows ---------------------------------------------------------------------------------------------------
+// The same product in 64x64 tiles of the result, 32x32 a wavefront, for results of so few 128x128 tiles that most CUs would have no
+// workgroup.  There the time is the chain of one workgroup's steps: here a step has a quarter of the matrix instructions, and
+// four steps of loads are in flight.  Wavefronts 0 and 1 move operand A, the others B.  Sums are formed in the same order, so
+// results are those of the large tiles bit for bit.  No dropout: its four columns a draw lie in four lanes here.
+constexpr int FEW_TILE = 64, FEW_KG = FEW_TILE * 16 + 64, FEW_PLANE = 2 * FEW_KG, FEW_OPERAND = 3 * FEW_PLANE, FEW_STAGE = 2 * FEW_OPERAND;
+constexpr int FEW_RING = 4;
+template <bool B_KMAJOR, bool TWO>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void gemm_split_few_kernel(const SplitK p) {
+  __shared__ __attribute__((aligned(128))) unsigned char smem[3 * FEW_STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1, g = lane >> 5, r = lane & 31;
+  const bool of_b = wave >= 2;
+  // the column tiles of a row panel are neighbours on one XCD
+  const int64_t L = blockIdx.x, group = (L / (8 * p.tiles_n)) * 8 + (L & 7), member = (L >> 3) % p.tiles_n;
+  if (group >= p.n_groups) return;
+  const int64_t i0 = group * FEW_TILE, j0 = member * FEW_TILE;
+
+  // the thread's share of a step: eight k of one row, or (parameters [k][column]) of one column
+  const int lt = tid & 127;
+  const bool by_column = B_KMAJOR && of_b;  // uniform over the wavefront
+  const int row = by_column ? lt & 63 : lt >> 1, kq = by_column ? (wave & 1) * 8 : (lt & 1) * 8;
+  const int n1 = (int)((p.K1 + SBK - 1) / SBK), n = n1 + (int)((p.K2 + SBK - 1) / SBK);
+  const float *s1, *s2 = nullptr;  // element k of the row at s[k sk]
+  int64_t sk1 = 1, sk2 = 1;
+  if (of_b) {
+    const int64_t j = j0 + row < p.N - 1 ? j0 + row : p.N - 1;
+    if (TWO && j >= p.half) s1 = p.B_second + (j - p.half) * p.ldb1;
+    else s1 = p.B1 + (B_KMAJOR ? j : j * p.ldb1);
+    if (p.K2 > 0) s2 = p.B2 + (B_KMAJOR ? j : j * p.ldb2);
+    if (B_KMAJOR) sk1 = p.ldb1, sk2 = p.ldb2;
+  } else {
+    const int64_t i = i0 + row < p.M - 1 ? i0 + row : p.M - 1;
+    s1 = p.A1 + i * p.lda1;
+    if (p.K2 > 0) s2 = p.A2 + i * p.lda2;
+  }
+  const uint32_t flip = !of_b ? (uint32_t)row << 31 : 0u;  // odd rows are summed with the other sign
+
+  struct Raw {
+    float x[8];
+  } ring[FEW_RING];
+  auto load = [&](int q, Raw& w) __attribute__((always_inline)) {
+    if (q > n - 1) q = n - 1;
+    const bool second = q >= n1;
+    const int k_len = (int)(second ? p.K2 : p.K1), t = second ? q - n1 : q;
+    const int first = k_len < SBK ? short_first(k_len, kq) : window_of(t, k_len, kq).start + kq;
+    const float* const s = second ? s2 : s1;
+    if (by_column) {
+      const int64_t sk = second ? sk2 : sk1;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) w.x[c] = s[(first + c) * sk];
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float4u v = *reinterpret_cast<const float4u*>(s + first + 4 * h);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) w.x[4 * h + c] = v[c];
+      }
+    }
+  };
+  bool small = false;
+  uint32_t bits = 0;
+  auto put = [&](int q, const Raw& w, unsigned char* stage) __attribute__((always_inline)) {
+    const bool second = q >= n1;
+    const int k_len = (int)(second ? p.K2 : p.K1), t = second ? q - n1 : q;
+    if (q == n1) small |= all_small(bits), bits = 0;
+    bits |= any_bit(w.x[0], w.x[1], w.x[2], w.x[3]) | any_bit(w.x[4], w.x[5], w.x[6], w.x[7]);
+    float e[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) e[c] = __uint_as_float(__float_as_uint(w.x[c]) ^ flip);
+    if ((t + 1) * SBK > k_len) {  // uniform: the last step of a segment that is not whole steps
+      const Window in = window_of(t, k_len, kq);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) e[c] = kq + c >= in.lo && kq + c < in.hi ? e[c] : 0.f;
+    }
+    Group o;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) o.pair(c, e[2 * c], e[2 * c + 1]);
+    o.write(stage + (of_b ? FEW_OPERAND : 0) + (kq >> 3) * FEW_KG + plane_row(row), FEW_PLANE);
+  };
+  struct Planes {
+    bf16x8 a[3], b[3];
+  };
+  const int a_off = g * FEW_KG + wm * 512 + plane_row(r), b_off = FEW_OPERAND + g * FEW_KG + wn * 512 + plane_row(r);
+  auto take = [&](const unsigned char* stage, Planes& x) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      x.a[q] = *reinterpret_cast<const bf16x8*>(stage + a_off + q * FEW_PLANE);
+      x.b[q] = *reinterpret_cast<const bf16x8*>(stage + b_off + q * FEW_PLANE);
+    }
+  };
+  floatx16 hh, rest;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) hh[v] = rest[v] = 0.f;
+  auto multiply = [&](const Planes& x) __attribute__((always_inline)) {
+    constexpr int PA[6] = {2, 1, 1, 0, 0, 0}, PB[6] = {0, 1, 0, 2, 1, 0};
+#pragma unroll
+    for (int s = 0; s < 6; ++s) {
+      floatx16& c = s < 5 ? rest : hh;
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.a[PA[s]], x.b[PB[s]], c, 0, 0, 0);
+    }
+  };
+
+#pragma unroll
+  for (int q = 0; q < FEW_RING; ++q) load(q, ring[q]);
+  unsigned char *d0 = smem, *d1 = smem + FEW_STAGE, *d2 = smem + 2 * FEW_STAGE;  // steps t, t + 1, t + 2
+  put(0, ring[0], d0);
+  load(FEW_RING, ring[0]);
+  if (n > 1) put(1, ring[1], d1);
+  load(FEW_RING + 1, ring[1]);
+  __syncthreads();
+  // step t is multiplied, t + 2 written, t + 2 + FEW_RING requested
+#pragma nounroll
+  for (int t0 = 0; t0 < n; t0 += FEW_RING) {
+#pragma unroll
+    for (int s = 0; s < FEW_RING; ++s) {
+      const int t = t0 + s;
+      if (t < n) {  // uniform over the workgroup
+        Planes x;
+        take(d0, x);
+        Raw& w = ring[(s + 2) % FEW_RING];
+        if (t + 2 < n) put(t + 2, w, d2);
+        load(t + 2 + FEW_RING, w);
+        multiply(x);
+        __syncthreads();
+        unsigned char* const d = d0;
+        d0 = d1;
+        d1 = d2;
+        d2 = d;
+      }
+    }
+  }
+  small |= all_small(bits);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) hh[v] += rest[v];
+  // blocks that the split does not get right are computed again (see gemm_split_kernel)
+  bool again = __syncthreads_or(small);
+  float bad = 0.f;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) bad = fmaf(hh[v], 0.f, bad);
+  again |= __any(!(bad == 0.f)) != 0;
+  const int64_t jb = j0 + wn * 32 + r;
+  if (again) {
+    const int64_t ib = i0 + wm * 32 + r, ia = ib < p.M ? ib : p.M - 1, ja = jb < p.N ? jb : p.N - 1;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) hh[v] = 0.f;
+#pragma nounroll
+    for (int seg = 0; seg < (p.K2 > 0 ? 2 : 1); ++seg) {
+      const int64_t ldb = seg ? p.ldb2 : p.ldb1;
+      const float* B = (seg ? p.B2 : p.B1) + ja * (B_KMAJOR ? 1 : ldb);
+      if (TWO && ja >= p.half) B = p.B_second + (ja - p.half) * ldb;
+      run_plain((seg ? p.A2 : p.A1) + ia * (seg ? p.lda2 : p.lda1), 1, B, B_KMAJOR ? ldb : 1, seg ? p.K2 : p.K1, g, hh);
+    }
+#pragma unroll
+    for (int v = 1; v < 16; v += 2) hh[v] = -hh[v];
+  }
+  // register v of lane (g, r) is element [8 (v / 4) + 4 g + v % 4][r] of the block: a register is two rows of a whole line
+  if (jb >= p.N) return;
+  const int64_t first = i0 + wm * 32 + 4 * g;
+  float* const C = TWO && jb >= p.half ? p.C_second + (jb - p.half) : p.C + jb;
+  const float bj = !TWO && p.bias ? p.bias[jb] : 0.f;
+  float gate[16], sum[16], rs[16];
+  if constexpr (!TWO) {
+    auto at = [&](int v) {
+      const int64_t i = first + 8 * (v >> 2) + (v & 3);
+      return i < p.M ? i : p.M - 1;
+    };
+    if (p.gate) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) gate[v] = p.gate[at(v) * p.ldg + jb];
+    }
+    if (p.accumulate) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sum[v] = C[at(v) * p.ldc];
+    }
+    if (p.row_scale) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) rs[v] = p.row_scale[at(v)];
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int64_t i = first + 8 * (v >> 2) + (v & 3);
+    float x = (v & 1 ? -hh[v] : hh[v]) + bj;
+    if constexpr (!TWO) {
+      if (p.relu) x = fmaxf(x, 0.f);
+      if (p.row_scale) x *= rs[v];
+      if (p.gate && !p.gate_last) x = gate[v] > 0.f ? x * p.gate_scale : 0.f;
+      if (p.accumulate) x += sum[v];
+      if (p.gate && p.gate_last) x = gate[v] > 0.f ? x * p.gate_scale : 0.f;
+      if (p.relu_last) x = fmaxf(x, 0.f);
+    }
+    if (i < p.M) C[i * p.ldc] = x;
+  }
+}
+
 // 32-bit element offsets inside a tile: 128 rows of a k-contiguous operand
 static bool split_strides_ok(int64_t lda, int64_t ldb) { return lda < ((int64_t)1 << 22) && ldb < ((int64_t)1 << 22); }
 
@@ -915,6 +1111,11 @@ static bool split_params_first(const GemmArgs& a) {
   const size_t bytes = split_param_bytes(a.M, a.C_second ? 2 * a.N : a.N, a.K1, a.K2);
   return bytes > 0 && a.param_scratch && a.param_scratch_bytes >= bytes;
 }
+
+// Results of at most 64 tiles of 128x128 are computed in tiles of a quarter of that: the line is where those are one for each CU.
+// Microseconds, large tiles / small ones: 4 tiles (500 x 128 x 512) 24.7 / 19.9, 16 (2k x 66 x 500) 26.5 / 20.0, 40 (5k x 128 x 512)
+// 24.0 / 20.4, 64 (2k x 512 x 512) 25.1 / 20.9; above, 79 (10k x 128 x 512) 24.1 / 24.2, 158 (10k x 256 x 256) 16.2 / 19.3.
+static bool few_tiles(int64_t large_tiles) { return large_tiles <= 64; }
 
 int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   SplitK p{};
@@ -954,6 +1155,21 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "dense: grid too large");
   const bool drop = p.drop.scale != 0.f;  // forward products only
   const bool planes = split_params_first(a);
+  if (!planes && !drop && few_tiles(p.n_groups * p.tiles_n)) {
+    p.n_groups = (a.M + FEW_TILE - 1) / FEW_TILE;
+    p.tiles_n = (N + FEW_TILE - 1) / FEW_TILE;
+    const int64_t few = (p.n_groups + 7) / 8 * 8 * p.tiles_n;
+    char pname[96] = "";
+    if (profiling()) snprintf(pname, sizeof(pname), "gemm_split_few_kernel<%s,%s> N=%d K=%d", a.b_kmajor ? "true" : "false",
+             a.C_second ? "true" : "false", (int)N, (int)K);
+    ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + (double)N * K + (double)a.M * N * (a.accumulate ? 2 : 1)),
+                   2.0 * (double)a.M * N * (double)K);
+    if (a.C_second) gemm_split_few_kernel<false, true><<<dim3((unsigned)few), 256, 0, stream>>>(p);
+    else if (a.b_kmajor) gemm_split_few_kernel<true, false><<<dim3((unsigned)few), 256, 0, stream>>>(p);
+    else gemm_split_few_kernel<false, false><<<dim3((unsigned)few), 256, 0, stream>>>(p);
+    COFREE_HIP_CHECK(hipGetLastError());
+    return COFREE_OK;
+  }
   if (planes) {
     SplitParamsK q{};
     q.B[0] = p.B1, q.B[1] = p.B2;

@@ -234,3 +234,70 @@ def test_parameters_split_beforehand(env, special):
         assert bool((got[~finite] == ref[~finite]).all()) and bool(torch.isfinite(got[finite]).all()), what
         bound = (2 * d + 8.0) * 2.0 ** -24 * mag + 2 * d * 2.0 ** -149
         assert bool(((got.double() - ref).abs()[finite] <= bound[finite]).all()), what
+
+
+# few rows: 64 x 64 tiles; eleven to forty times as many: more than 64 tiles of 128 x 128
+@pytest.mark.parametrize("M,N,K", [(1, 65, 8), (63, 66, 31), (64, 128, 16), (65, 129, 17), (129, 100, 500), (700, 300, 90), (1_000, 512, 15)])
+def test_few_rows_give_the_same_bits(env, M, N, K):
+    """A result of few tiles is computed in smaller ones; its sums are formed in the same order."""
+    B, torch = env["B"], env["torch"]
+    print(f"[case] split product of few rows M={M} N={N} K={K}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    many = 65 * 128 + M
+    A, W, b = (torch.randn(*s, generator=gen, device="cuda") for s in ((many, K), (N, K), (N,)))
+    long, few = torch.full((many, N), float("nan"), device="cuda"), torch.full((M + 1, N), float("nan"), device="cuda")
+    B.dense_nt_f32(A, W, b, long, True)
+    B.dense_nt_f32(A[:M], W, b, few[:M], True)
+    assert torch.equal(few[:M], long[:M]) and bool(few[M].isnan().all())
+
+
+@pytest.mark.parametrize("row,value", [(7, float("inf")), (8_000, float("nan")), (7, 2.0 ** -118), (8_000, 2.0 ** -118)])
+def test_blocks_computed_again(env, row, value):
+    """What the split does not hold, in tiles of either size: the first 300 rows by themselves and among 10,000."""
+    B, torch = env["B"], env["torch"]
+    print(f"[case] split product, row {row} of {value}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    A, W = torch.rand(10_000, 41, generator=gen, device="cuda") + 0.1, torch.rand(200, 41, generator=gen, device="cuda") + 0.1
+    A[row] = value
+    for rows in (300, 10_000):
+        C = torch.full((rows, 200), 7.0, device="cuda")
+        B.dense_nt_f32(A[:rows], W, None, C, False)
+        ref = A[:rows].double() @ W.double().T
+        finite = torch.isfinite(ref)
+        assert torch.equal(C[~finite].double().nan_to_num(nan=-1.0), ref[~finite].nan_to_num(nan=-1.0)) and bool(torch.isfinite(C[finite]).all())
+        assert bool(((C.double() - ref).abs()[finite] <= (41 + 4.0) * 2.0 ** -24 * ref[finite]).all())
+
+
+@pytest.mark.parametrize("q", [0.0, 0.3])
+@pytest.mark.parametrize("kind,d_in,d_out", [("gcn", 100, 70), ("gcn", 70, 129), ("sage", 130, 90), ("sage", 70, 200), ("sage_conv", 70, 130),
+                                             ("sage_conv", 200, 66)])
+def test_layers_of_few_nodes_give_the_same_bits(env, kind, d_in, d_out, q):
+    """Both directions of a layer on one ring and on 30 copies of it: the first copy's rows are the same bits with products in
+    64 x 64 tiles and in 128 x 128 ones, through every gate, scale, second range and addition of the layers."""
+    B, torch = env["B"], env["torch"]
+    print(f"[case] split products of few nodes {kind} {d_in} -> {d_out} q={q}", flush=True)
+    one, copies, d_msg = 333, 30, 96 if kind == "sage" else 0
+    code = {"gcn": B.GCN, "sage": B.SAGE_MEAN, "sage_conv": B.SAGE_CONV}[kind]
+    gen = torch.Generator(device="cuda").manual_seed(d_in)
+
+    def rand(*shape):
+        return torch.randn(*shape, generator=gen, device="cuda")
+    prm = {"W": rand(d_msg or d_out, d_in * (2 if kind == "sage_conv" else 1)) / d_in ** 0.5, "bW": rand(d_msg or d_out)}
+    if kind == "sage":
+        prm.update(U=rand(d_out, d_msg + d_in) / d_in ** 0.5, bU=rand(d_out))
+    X, G = rand(copies * one, d_in), rand(copies * one, d_out)
+    out = []
+    for c in (1, copies):
+        n = c * one
+        src = np.arange(n, dtype=np.int64)
+        P = B.build_partition(n, src, src // one * one + (src + 1) % one, 1, 0, 3)
+        d = B.layer_desc(code, d_in, d_msg, d_out, act=1, dropout_q=q, layer_id=2, seed=5, epoch=3)
+        ws = torch.empty(max(B.layer_workspace_bytes(d, n, x) for x in (False, True)), dtype=torch.uint8, device="cuda")
+        sv = {"Z": torch.empty(n, max(d_msg, 1), device="cuda"), "A": torch.empty(n, max(d_msg, d_in, d_out), device="cuda")}
+        H, dY = X[:n].clone(), G[:n].clone()
+        Y, dX = torch.full((n, d_out), float("nan"), device="cuda"), torch.full((n, d_in), float("nan"), device="cuda")
+        grads = {k: torch.empty_like(v) for k, v in prm.items()}
+        B.layer_fwd(P, None, 0, d, H, prm, Y, sv, ws)
+        B.layer_bwd(P, None, 0, d, H, Y, prm, sv, dY, dX, grads, False, ws)
+        out.append((Y[:one], dX[:one]))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
