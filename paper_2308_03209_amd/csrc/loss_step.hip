@@ -52,6 +52,17 @@ __device__ inline void ld4(const bf16_t* p, int avail, float (&v)[4], float fill
     for (int i = 0; i < 4; ++i) v[i] = i < avail ? bf16_to_f32(p[i]) : fill;
   }
 }
+__device__ inline void ld4(const uint8_t* p, int avail, uint32_t (&v)[4]) {
+  typedef uint32_t u32e __attribute__((aligned(1)));
+  if (avail >= 4) {
+    const uint32_t t = *reinterpret_cast<const u32e*>(p);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = (t >> (8 * i)) & 0xffu;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = i < avail ? p[i] : 0u;
+  }
+}
 __device__ inline void st4(float* p, int avail, const float (&v)[4]) {
   if (avail >= 4) {
     f32x4e t;
@@ -106,7 +117,10 @@ __device__ inline void st_n(bf16_t* p, int avail, const float (&v)[8]) {
   }
 }
 
-constexpr int LOSS_BLOCKS = 2048;  // partial sums; the final reduction runs over exactly this many
+constexpr int LOSS_BLOCKS = 2048;  // workgroups, and partial sums, at most
+// of loss_group_kernel: five a CU are resident (94 VGPRs), and a sixth would run behind them (2.4M x 172 bfloat16: 1,280
+// workgroups 378 us, 1,536 457, 2,048 395)
+constexpr int GROUP_BLOCKS = 5 * 256;
 
 // Partial sums of cofree_loss_weighted_static: device memory that exists from the moment the library is loaded
 // (one copy per GPU, 8 KiB, held until the process ends), so that the call never allocates.  In host code this
@@ -124,6 +138,15 @@ __device__ inline float wave_sum(float x) {
   return x;
 }
 
+// A workgroup's loss: its lanes' in a fixed order
+__device__ inline void store_partial(float my_loss, float* __restrict__ partial) {
+  __shared__ float wave_loss[4];
+  my_loss = wave_sum(my_loss);
+  if ((threadIdx.x & 63) == 0) wave_loss[threadIdx.x >> 6] = my_loss;
+  __syncthreads();
+  if (threadIdx.x == 0) partial[blockIdx.x] = (wave_loss[0] + wave_loss[1]) + (wave_loss[2] + wave_loss[3]);
+}
+
 // One wavefront per node: softmax over its C logits (lanes stride over classes), cross-entropy
 // against the label, times c * w_j; dlogits = c * w_j * (softmax - onehot).  Each block adds up
 // its wavefronts' losses in a fixed order into partial[blockIdx.x].
@@ -134,7 +157,6 @@ __global__ __launch_bounds__(256) void loss_kernel(const T* __restrict__ logits,
                                                    const uint8_t* __restrict__ train_mask, int64_t n, int32_t C,
                                                    float scale_c, T* __restrict__ dlogits,
                                                    float* __restrict__ partial) {
-  __shared__ float wave_loss[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float my_loss = 0.f;
   for (int64_t row = (int64_t)blockIdx.x * 4 + wave; row < n; row += (int64_t)gridDim.x * 4) {
@@ -161,9 +183,7 @@ __global__ __launch_bounds__(256) void loss_kernel(const T* __restrict__ logits,
     }
     if (lane == 0) my_loss += coef * (m + logf(se) - ld_elem(z + y));
   }
-  if (lane == 0) wave_loss[wave] = my_loss;
-  __syncthreads();
-  if (threadIdx.x == 0) partial[blockIdx.x] = (wave_loss[0] + wave_loss[1]) + (wave_loss[2] + wave_loss[3]);
+  store_partial(my_loss, partial);
 }
 
 // e^x for x <= 0.  bfloat16 logits: the hardware's 2^x on x log2(e) (relative error about |x| 2^-24, far below
@@ -176,180 +196,185 @@ __device__ inline float softmax_exp(float x) {
   else return expf(x);
 }
 
-// Same computation for C <= PER * LANES with a group of LANES lanes per node (LANES a power of two dividing
-// 64): lane l of the group owns the PER consecutive classes PER l .. PER l + PER - 1 - 16 bytes of them, four
-// float32 or eight bfloat16 - read and written with one wide access (narrower loads per lane are bound by
-// the rate of load instructions, not by bytes: 172 bfloat16 classes in 8-byte pieces, one node per
-// wavefront, ran at 2.3 TB/s); a wavefront works on 64/LANES nodes at once and on two of them per group and
-// iteration (four measured slower), so that the loads of independent rows overlap.
-// WIDE (C >= PER): a lane whose classes would cross the end of the row - or lie past it - reads the
-// window that ends with the row instead and ignores the `skip` leading classes that belong to the lane
-// before, so that every lane issues the same unconditional wide load and store in the loop (a per-lane
-// width branch around the loads made the loop wait for each row in turn); the overlapped classes are
-// written twice with identical values.
-template <typename T, int LANES, bool WIDE>
-__device__ inline void loss_group_rows(const T* __restrict__ logits, const int32_t* __restrict__ labels,
-                                       const float* __restrict__ w, const uint8_t* __restrict__ train_mask,
-                                       int64_t n, int32_t C, float scale_c, T* __restrict__ dlogits, float& my_loss) {
-  constexpr int GROUPS = 256 / LANES, R = 2, PER = 16 / (int)sizeof(T);
-  const int gl = threadIdx.x % LANES, grp = threadIdx.x / LANES;
-  int c0 = gl * PER, avail = C - c0, skip = 0;  // this lane's classes (avail <= 0: none)
-  if (WIDE && avail < PER) {
-    skip = avail > 0 ? PER - avail : PER;
-    c0 = C - PER;
-    avail = PER;
-  }
-  // a workgroup owns one contiguous run of rows and walks it front to back, GROUPS * R consecutive rows per
-  // iteration, so that rows sharing a cache line at their ends (rows are C elements long, any C) are handled
-  // by the same workgroup close in time (timing equal to a grid-strided walk at 28M rows of 172 bfloat16)
-  const int64_t per_block = (n + gridDim.x - 1) / gridDim.x;
-  const int64_t b0 = (int64_t)blockIdx.x * per_block, b1 = b0 + per_block < n ? b0 + per_block : n;
-  constexpr int64_t stride = GROUPS;
-  for (int64_t row0 = b0 + grp; row0 < b1; row0 += R * stride) {
-    float v[R][PER];
-    bool valid[R];
-    int64_t rows[R];
-    float wjs[R];
-    int32_t ys[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      valid[r] = row0 + r * stride < b1;
-      rows[r] = valid[r] ? row0 + r * stride : row0;  // a row past the end is computed on row0 and not stored
-      // label and weight are requested with the logits, not after the reductions
-      wjs[r] = w ? w[rows[r]] : 1.f;
-      if (train_mask && train_mask[rows[r]] == 0) wjs[r] = 0.f;
-      ys[r] = labels[rows[r]];
-      if (WIDE) {
-        ld_n(logits + rows[r] * C + c0, PER, v[r], -INFINITY);
-      } else if (avail > 0) {
-        ld_n(logits + rows[r] * C + c0, avail, v[r], -INFINITY);
-      } else {
-#pragma unroll
-        for (int k = 0; k < PER; ++k) v[r][k] = -INFINITY;
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      float m = -INFINITY;
-#pragma unroll
-      for (int k = 0; k < PER; ++k) m = fmaxf(m, k >= skip ? v[r][k] : -INFINITY);
-#pragma unroll
-      for (int o = LANES / 2; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-      // e[k] of a skipped class is the value its owner computes (same logit, same maximum); it only
-      // stays out of this lane's share of the sum
-      float e[PER], se = 0.f;
-#pragma unroll
-      for (int k = 0; k < PER; ++k) {
-        e[k] = k < avail ? softmax_exp<T>(v[r][k] - m) : 0.f;
-        se += k >= skip ? e[k] : 0.f;
-      }
-#pragma unroll
-      for (int o = LANES / 2; o > 0; o >>= 1) se += __shfl_xor(se, o, 64);
-      const int64_t row = rows[r];
-      float wj = wjs[r];
-      int32_t y = ys[r];
-      if ((uint32_t)y >= (uint32_t)C) {  // label outside [0, C): the node does not contribute
-        y = 0;
-        wj = 0.f;
-      }
-      const float coef = scale_c * wj;
-      const float inv = 1.f / se;
-      float zy = 0.f;
-      if (WIDE) {
-        // the label's logit is in a register of the lane that owns class y: element y - c0 of its window
-        const int owner = y / PER;                                   // same in every lane of the group
-        const int oc0 = C - owner * PER < PER ? C - PER : owner * PER;  // that lane's (possibly moved) window
-        const int k = y - oc0;
-        float mine = v[r][0];
-#pragma unroll
-        for (int i = 1; i < PER; ++i) mine = k == i ? v[r][i] : mine;
-        zy = __shfl(mine, (threadIdx.x & 63) - gl + owner, 64);
-      }
-      if (valid[r]) {
-        if (WIDE) {
-          float g[PER];
-#pragma unroll
-          for (int k = 0; k < PER; ++k) g[k] = coef * (e[k] * inv - (c0 + k == y ? 1.f : 0.f));
-          st_n(dlogits + row * C + c0, PER, g);
-        } else if (avail > 0) {
-          float g[PER];
-#pragma unroll
-          for (int k = 0; k < PER; ++k) g[k] = coef * (e[k] * inv - (c0 + k == y ? 1.f : 0.f));
-          st_n(dlogits + row * C + c0, avail, g);
-        }
-        if (gl == 0) my_loss += coef * (m + logf(se) - (WIDE ? zy : ld_elem(logits + row * C + y)));
-      }
-    }
-  }
-}
-
-template <typename T, int LANES>
+// Same computation with a group of LANES lanes per node, C <= LANES * PIECES * PER (LANES a power of two dividing 64): lane l
+// owns the PER consecutive classes - 16 bytes of them, four float32 or eight bfloat16 - from PER l on and, with two pieces, as
+// many from PER (LANES + l) on, each read and written with one wide access; a wavefront works on 64/LANES nodes at once and on
+// two of them per group and iteration, so that the loads of independent rows overlap.
+// WIDE (C >= PER): a last piece that would cross the end of the row - or lie past it - is the window that ends with the row
+// instead, with the `skip` leading classes that belong to the piece before left out of the sum, so that every lane issues the
+// same unconditional wide loads and stores (a per-lane width branch around the loads made the loop wait for each row in turn);
+// the overlapped classes are written twice with identical values.
+// What bounds it: vector instructions (about 120 for eight classes of a row, a third of them for the row as a whole: reductions, 1 / sum,
+// logarithm), hence two pieces a lane wherever the row has them, and no more lanes than it needs.  Microseconds with one piece
+// and at least eight lanes, the label's logit fetched from its lane, and now: 2.4M x 172 bfloat16 501 / 378 (4.4 TB/s), 2.4M x 47
+// bfloat16 148 / 120, 1.2M x 47 float32 119 / 108, 500k x 600 bfloat16 (then a wavefront a node) 946 / 291, 500k x 5 float32 25 / 9.
+template <typename T, int LANES, int PIECES>
 __global__ __launch_bounds__(256) void loss_group_kernel(const T* __restrict__ logits,
                                                          const int32_t* __restrict__ labels,
                                                          const float* __restrict__ w,
                                                          const uint8_t* __restrict__ train_mask, int64_t n, int32_t C,
                                                          float scale_c, T* __restrict__ dlogits,
                                                          float* __restrict__ partial) {
-  constexpr int GROUPS = 256 / LANES;
-  __shared__ float group_loss[GROUPS];
+  constexpr int GROUPS = 256 / LANES, R = 2, PER = 16 / (int)sizeof(T), LAST = PIECES - 1;
+  constexpr bool WIDE = LANES > 1 || PIECES > 1;
   const int gl = threadIdx.x % LANES, grp = threadIdx.x / LANES;
-  float my_loss = 0.f;
-  if (C >= 16 / (int)sizeof(T))
-    loss_group_rows<T, LANES, true>(logits, labels, w, train_mask, n, C, scale_c, dlogits, my_loss);
-  else
-    loss_group_rows<T, LANES, false>(logits, labels, w, train_mask, n, C, scale_c, dlogits, my_loss);
-  if (gl == 0) group_loss[grp] = my_loss;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float t = 0.f;
-    for (int i = 0; i < GROUPS; ++i) t += group_loss[i];
-    partial[blockIdx.x] = t;
+  int c0[PIECES], skip = 0;  // the pieces' first classes
+#pragma unroll
+  for (int q = 0; q < PIECES; ++q) c0[q] = (q * LANES + gl) * PER;
+  const int last = c0[LAST], avail = C - last;
+  if (WIDE && avail < PER) {
+    skip = avail > 0 ? PER - avail : PER;
+    c0[LAST] = C - PER;
   }
+  float own[PER];  // 0 for a class that the piece before adds to the sum
+#pragma unroll
+  for (int k = 0; k < PER; ++k) own[k] = k >= skip ? 1.f : 0.f;
+  // a workgroup owns one contiguous run of rows and walks it front to back, GROUPS * R consecutive rows per
+  // iteration, so that rows sharing a cache line at their ends (rows are C elements long, any C) are handled
+  // by the same workgroup close in time (timing equal to a grid-strided walk at 28M rows of 172 bfloat16)
+  const int64_t per_block = (n + gridDim.x - 1) / gridDim.x, b0 = (int64_t)blockIdx.x * per_block;
+  const int count = (int)(n - b0 < per_block ? n - b0 : per_block);
+  // the run's rows by 32-bit offsets: its elements take less than 4 GiB (a GPU's memory over LOSS_BLOCKS)
+  logits += b0 * C, dlogits += b0 * C, labels += b0;
+  if (w) w += b0;
+  if (train_mask) train_mask += b0;
+  float my_loss = 0.f;
+  for (int row0 = grp; row0 < count; row0 += R * GROUPS) {
+    float v[R][PIECES][PER];
+    bool valid[R];
+    uint32_t at[R];
+    float coefs[R];
+    int32_t ys[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      valid[r] = row0 + r * GROUPS < count;
+      const uint32_t row = valid[r] ? row0 + r * GROUPS : row0;  // a row past the end is computed on row0 and not stored
+      at[r] = row * (uint32_t)C;
+      // label and weight are requested with the logits, not after the reductions
+      coefs[r] = w ? w[row] : 1.f;
+      if (train_mask && train_mask[row] == 0) coefs[r] = 0.f;
+      ys[r] = labels[row];
+#pragma unroll
+      for (int q = 0; q < PIECES; ++q) ld_n(logits + (at[r] + c0[q]), WIDE ? PER : C, v[r][q], -INFINITY);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float m = v[r][0][0];
+#pragma unroll
+      for (int k = 1; k < PIECES * PER; ++k) m = fmaxf(m, v[r][k / PER][k % PER]);
+#pragma unroll
+      for (int o = LANES / 2; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+      // e of a skipped class is the value that its owner computes (same logit, same maximum); it only
+      // stays out of this piece's share of the sum
+      float e[PIECES][PER], se = 0.f;
+#pragma unroll
+      for (int q = 0; q < PIECES; ++q) {
+        float sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+          e[q][k] = softmax_exp<T>(v[r][q][k] - m);
+          if (WIDE) sum = q == LAST ? fmaf(e[q][k], own[k], sum) : sum + e[q][k];
+          else if (k < C) sum += e[q][k];
+        }
+        se += sum;
+      }
+#pragma unroll
+      for (int o = LANES / 2; o > 0; o >>= 1) se += __shfl_xor(se, o, 64);
+      const bool known = (uint32_t)ys[r] < (uint32_t)C;  // label outside [0, C): the node does not contribute
+      const int y = known ? ys[r] : 0;
+      const float coef = scale_c * (known ? coefs[r] : 0.f);
+      const float inv = 1.f / se;
+      float zy = v[r][0][0];
+#pragma unroll
+      for (int q = 0; q < PIECES; ++q) {
+        float g[PER];
+        const int mine = y - c0[q];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+          const bool hit = k == mine;
+          g[k] = coef * (e[q][k] * inv - (hit ? 1.f : 0.f));
+          zy = hit ? v[r][q][k] : zy;
+        }
+        if (valid[r]) st_n(dlogits + (at[r] + c0[q]), WIDE ? PER : C, g);
+      }
+      if (valid[r] && y / PER % LANES == gl) my_loss += coef * (m + logf(se) - zy);  // the lane that owns class y
+    }
+  }
+  store_partial(my_loss, partial);
 }
 
-// Multi-label loss (the sigmoid + binary cross-entropy of Theorem 3): one thread per (node, class)
-// element, grid-stride.  loss element = softplus(z) - y z with softplus(z) = max(z, 0) + log1p(e^-|z|);
+// Multi-label loss (the sigmoid + binary cross-entropy of Theorem 3): a thread takes four consecutive elements of the matrix
+// as one list, grid-stride.  loss element = softplus(z) - y z with softplus(z) = max(z, 0) + log1p(e^-|z|);
 // dlogits = c w_j (sigmoid(z) - y).  Per-thread sums in index order, then the fixed wavefront / block tree.
+// log1p(e) = log(u) + (e - (u - 1)) / u with u = 1 + e rounded (u - 1 is exact): what the rounding of u left out, to
+// first order.
+// What bounds it: vector instructions, 65 an element; one element a thread with its row by division and log1pf took 230.
+// 717k x 100 float32 292 -> 174 us, bfloat16 294 -> 162.
 template <typename T>
 __global__ __launch_bounds__(256) void bce_kernel(const T* __restrict__ logits, const uint8_t* __restrict__ targets,
                                                   const float* __restrict__ w,
                                                   const uint8_t* __restrict__ train_mask, int64_t n, int32_t C,
                                                   float scale_c, T* __restrict__ dlogits,
                                                   float* __restrict__ partial) {
-  __shared__ float wave_loss[4];
-  const int64_t total = n * C;
-  const int64_t stride = (int64_t)gridDim.x * 256;
+  const int64_t total = n * C, step = (int64_t)gridDim.x * 1024, step_rows = step / C;
+  const int32_t step_cols = (int32_t)(step - step_rows * C);
+  int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4, row = i / C;
+  int32_t col = (int32_t)(i - row * C);
   float my_loss = 0.f;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
-    const int64_t row = i / C;
-    float wj = w ? w[row] : 1.f;
-    if (train_mask && train_mask[row] == 0) wj = 0.f;
-    const float coef = scale_c * wj;
-    const float z = ld_elem(logits + i);
-    const float y = targets[i] != 0 ? 1.f : 0.f;
-    const float e = expf(-fabsf(z));
-    const float sig = (z >= 0.f ? 1.f : e) / (1.f + e);
-    st_elem(dlogits + i, coef * (sig - y));
-    my_loss += coef * (fmaxf(z, 0.f) + log1pf(e) - y * z);
+  auto weight = [&](int64_t r) {
+    const float x = w ? w[r] : 1.f;
+    return scale_c * (train_mask && train_mask[r] == 0 ? 0.f : x);
+  };
+  for (; i < total; i += step) {
+    const int avail = total - i < 4 ? (int)(total - i) : 4;
+    float z[4], g[4], coef[4];
+    uint32_t t[4];
+    ld4(logits + i, avail, z, 0.f);
+    ld4(targets + i, avail, t);
+    if (C >= 3) {  // two rows at most
+      const float first = weight(row), next = weight(row + 1 < n ? row + 1 : row);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) coef[k] = col + k < C ? first : next;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int64_t r = row + ((col + k) >> (C - 1));
+        coef[k] = weight(r < n ? r : n - 1);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float y = t[k] != 0 ? 1.f : 0.f;
+      const float e = expf(-fabsf(z[k])), u = 1.f + e;
+      g[k] = coef[k] * ((z[k] >= 0.f ? 1.f : e) / u - y);
+      const float log1p_e = logf(u) + (e - (u - 1.f)) / u;
+      if (k < avail) my_loss += coef[k] * (fmaxf(z[k], 0.f) + log1p_e - y * z[k]);
+    }
+    st4(dlogits + i, avail, g);
+    row += step_rows;
+    col += step_cols;
+    if (col >= C) col -= C, ++row;
   }
-  my_loss = wave_sum(my_loss);
-  if ((threadIdx.x & 63) == 0) wave_loss[threadIdx.x >> 6] = my_loss;
-  __syncthreads();
-  if (threadIdx.x == 0) partial[blockIdx.x] = (wave_loss[0] + wave_loss[1]) + (wave_loss[2] + wave_loss[3]);
+  store_partial(my_loss, partial);
 }
 
+// One workgroup: eight partial sums at most a thread, requested together
 __global__ __launch_bounds__(256) void loss_reduce_kernel(const float* __restrict__ partial, int32_t count,
                                                           float* __restrict__ out) {
-  __shared__ float s[256];
-  float acc = 0.f;
-  for (int i = threadIdx.x; i < count; i += 256) acc += partial[i];
-  s[threadIdx.x] = acc;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) s[threadIdx.x] += s[threadIdx.x + o];
-    __syncthreads();
+  static_assert(LOSS_BLOCKS == 8 * 256, "eight a thread");
+  __shared__ float s[4];
+  float x[8], acc = 0.f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int i = threadIdx.x + 256 * k;
+    x[k] = partial[i < count ? i : 0];
   }
-  if (threadIdx.x == 0) *out = s[0];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) acc += (int)threadIdx.x + 256 * k < count ? x[k] : 0.f;
+  acc = wave_sum(acc);
+  if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) *out = (s[0] + s[1]) + (s[2] + s[3]);
 }
 
 // partial[2b], partial[2b+1] = this block's sums of (a-b)^2 and a^2 (grid-stride, fixed order)
@@ -526,6 +551,12 @@ static int32_t loss_setup(const cofree_partition* part, int32_t weight_kind, con
   return COFREE_OK;
 }
 
+// Workgroups of a loss over `items`, `each` of which a workgroup takes at a time: no more than there is work for, and `most`
+static int loss_blocks(int64_t items, int64_t each, int most) {
+  const int64_t b = (items + each - 1) / each;
+  return b < 1 ? 1 : b < most ? (int)b : most;
+}
+
 // launches shared by cofree_loss_weighted and cofree_loss_weighted_static: `partial` holds LOSS_BLOCKS floats
 static int32_t enqueue_softmax_loss(const cofree_partition* part, const float* w, const void* logits, int32_t dtype,
                                     const int32_t* labels, const uint8_t* train_mask, int32_t n_classes,
@@ -536,21 +567,30 @@ static int32_t enqueue_softmax_loss(const cofree_partition* part, const float* w
 #define COFREE_LOSS_ARGS(T) \
   (const T*)logits, labels, w, train_mask, part->n_nodes, n_classes, scale_c, (T*)dlogits, partial
   const bool f32 = dtype == COFREE_F32;
-  const int per = f32 ? 4 : 8;  // classes per lane: 16 bytes
-#define COFREE_LOSS_GROUP(L)                                                              \
-  do {                                                                                    \
-    if (f32) loss_group_kernel<float, L><<<LOSS_BLOCKS, 256, 0, s>>>(COFREE_LOSS_ARGS(float)); \
-    else loss_group_kernel<bf16_t, L><<<LOSS_BLOCKS, 256, 0, s>>>(COFREE_LOSS_ARGS(bf16_t));   \
+  const int pieces = (n_classes + (f32 ? 3 : 7)) / (f32 ? 4 : 8);  // of 16 bytes
+  int blocks = 0;
+#define COFREE_LOSS_GROUP(L, Q)                                                                \
+  do {                                                                                         \
+    blocks = loss_blocks(part->n_nodes, 2 * 256 / L, GROUP_BLOCKS);                            \
+    if (f32) loss_group_kernel<float, L, Q><<<blocks, 256, 0, s>>>(COFREE_LOSS_ARGS(float));   \
+    else loss_group_kernel<bf16_t, L, Q><<<blocks, 256, 0, s>>>(COFREE_LOSS_ARGS(bf16_t));     \
   } while (0)
-  if (n_classes <= 8 * per) COFREE_LOSS_GROUP(8);
-  else if (n_classes <= 16 * per) COFREE_LOSS_GROUP(16);
-  else if (n_classes <= 32 * per) COFREE_LOSS_GROUP(32);
-  else if (n_classes <= 64 * per) COFREE_LOSS_GROUP(64);
-  else if (f32) loss_kernel<float><<<LOSS_BLOCKS, 256, 0, s>>>(COFREE_LOSS_ARGS(float));
-  else loss_kernel<bf16_t><<<LOSS_BLOCKS, 256, 0, s>>>(COFREE_LOSS_ARGS(bf16_t));
+  if (pieces <= 1) COFREE_LOSS_GROUP(1, 1);
+  else if (pieces <= 2) COFREE_LOSS_GROUP(1, 2);
+  else if (pieces <= 4) COFREE_LOSS_GROUP(2, 2);
+  else if (pieces <= 8) COFREE_LOSS_GROUP(4, 2);
+  else if (pieces <= 16) COFREE_LOSS_GROUP(8, 2);
+  else if (pieces <= 32) COFREE_LOSS_GROUP(16, 2);
+  else if (pieces <= 64) COFREE_LOSS_GROUP(32, 2);
+  else if (pieces <= 128) COFREE_LOSS_GROUP(64, 2);
+  else {
+    blocks = loss_blocks(part->n_nodes, 4, LOSS_BLOCKS);
+    if (f32) loss_kernel<float><<<blocks, 256, 0, s>>>(COFREE_LOSS_ARGS(float));
+    else loss_kernel<bf16_t><<<blocks, 256, 0, s>>>(COFREE_LOSS_ARGS(bf16_t));
+  }
 #undef COFREE_LOSS_GROUP
 #undef COFREE_LOSS_ARGS
-  loss_reduce_kernel<<<1, 256, 0, s>>>(partial, LOSS_BLOCKS, loss_out);
+  loss_reduce_kernel<<<1, 256, 0, s>>>(partial, blocks, loss_out);
   COFREE_HIP_CHECK(hipGetLastError());
   return COFREE_OK;
 }
@@ -599,7 +639,7 @@ int32_t cofree_loss_weighted_static(const cofree_partition* part, int32_t weight
   const float* w = nullptr;
   COFREE_TRY(loss_setup(part, weight_kind, custom_w, logits, dtype, labels, n_classes, loss_out, dlogits, partial,
                         cofree_loss_workspace_bytes(), &w));
-  // every one of the LOSS_BLOCKS partial sums is written by its workgroup (a workgroup without rows writes 0)
+  // every partial sum that the reduction reads is written by its workgroup (a workgroup without rows writes 0)
   // before the reduction reads it, so nothing of an earlier call's contents survives into this one
   return enqueue_softmax_loss(part, w, logits, dtype, labels, train_mask, n_classes, scale_c, loss_out, dlogits,
                               partial, (hipStream_t)stream);
@@ -617,13 +657,14 @@ int32_t cofree_loss_bce_weighted(const cofree_partition* part, int32_t weight_ki
   const double es = dtype == COFREE_F32 ? 4.0 : 2.0;
   ProfScope prof("loss_kernels", s, (double)part->n_nodes * ((2.0 * es + 1.0) * n_classes + 4.0),
                  12.0 * (double)part->n_nodes * n_classes);
+  const int blocks = loss_blocks(part->n_nodes * n_classes, 4 * 256, LOSS_BLOCKS);
   if (dtype == COFREE_F32)
-    bce_kernel<float><<<LOSS_BLOCKS, 256, 0, s>>>((const float*)logits, targets, w, train_mask, part->n_nodes,
+    bce_kernel<float><<<blocks, 256, 0, s>>>((const float*)logits, targets, w, train_mask, part->n_nodes,
                                                   n_classes, scale_c, (float*)dlogits, partial);
   else
-    bce_kernel<bf16_t><<<LOSS_BLOCKS, 256, 0, s>>>((const bf16_t*)logits, targets, w, train_mask, part->n_nodes,
+    bce_kernel<bf16_t><<<blocks, 256, 0, s>>>((const bf16_t*)logits, targets, w, train_mask, part->n_nodes,
                                                    n_classes, scale_c, (bf16_t*)dlogits, partial);
-  loss_reduce_kernel<<<1, 256, 0, s>>>(partial, LOSS_BLOCKS, loss_out);
+  loss_reduce_kernel<<<1, 256, 0, s>>>(partial, blocks, loss_out);
   COFREE_HIP_CHECK(hipGetLastError());
   return COFREE_OK;
 }
