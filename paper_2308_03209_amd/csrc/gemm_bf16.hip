@@ -732,6 +732,12 @@ static int32_t convert_params(const GemmArgs& a, bf16_t* Wb, int64_t ldd, hipStr
   return COFREE_OK;
 }
 
+// Tiles of 128x64 for results of up to 64 columns, and for those of at most 256 tiles of 128x128, one for each CU: twice as many workgroups
+// with half the chain of matrix instructions (us of a layer with tiles of 128 / 64 columns: GCN 500 -> 100 forward over 500 rows, 4 tiles of
+// 128, 21.4 / 13.8; 500 -> 500 over 2,000, 64, 20.6 / 15.0; 4,000, 128, 22.7 / 17.4; 8,000, 252, 26.6 / 25.1; 300 -> 200 over 16,000, 250,
+// 22.7 / 22.1; over 30k, 470, 30.4 / 33.2; 500 -> 500 over 16,000, 500, 34.9 / 38.2).
+bool gemm_bf16_few(int64_t M, int32_t N) { return (M + HBM - 1) / HBM * ((N + HBN - 1) / HBN) <= (N <= 64 ? 512 : 256); }
+
 int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(a.M >= 0 && a.N >= 1 && a.K1 >= 1 && a.K2 >= 0, "dense: bad shape");
   COFREE_REQUIRE(a.K2 == 0 || a.A2, "dense: second segment is NULL");
@@ -750,19 +756,23 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
   const bool pinned = gemm_pinned_fits(a);
   if (!pinned && gemm_resident_fits(a)) return launch_gemm_resident(a, stream);
   if (!pinned && a.dropout.q > 0.f) return fail(COFREE_EINVAL, "internal: no dropout in tiled products");
-  const bool narrow = a.N <= 64;  // one 128x64 tile per row panel
   // 256x256 tiles once the matrix gives every CU more than one of them (one such block fills a CU, so small
-  // launches keep the 128x128 tile and its three blocks per CU).  COFREE_BF16_TILE = 256 / 128 forces a
-  // choice (tests run small shapes through the large tile with it).
-  bool big = !narrow && a.N > HBN && a.M >= (int64_t)2 * 256 * 256;
+  // launches keep smaller tiles and their three blocks per CU).  COFREE_BF16_TILE = 256 / 128 / 64 forces a
+  // choice (tests run small shapes through the large tiles with it).
+  bool big = a.N > HBN && a.M >= (int64_t)2 * 256 * 256;
   if (const char* e = getenv("COFREE_BF16_TILE")) {
-    if (atoi(e) == 256) big = !narrow && a.N > HBN;
-    if (atoi(e) == 128) big = false;
+    if (atoi(e) == 256) big = a.N > HBN;
+    if (atoi(e) == 128 || atoi(e) == 64) big = false;
   }
-  // Narrow products of few rows read their parameters in float32, which saves the launch that converts them (us of a layer with / without
+  bool narrow = a.N <= 64 || (!big && gemm_bf16_few(a.M, a.N));
+  if (const char* e = getenv("COFREE_BF16_TILE")) {
+    if (atoi(e) >= 128) narrow = a.N <= 64;
+    if (atoi(e) == 64) narrow = true;
+  }
+  // They read their parameters in float32 where the rows are few, which saves the launch that converts them (us of a layer with / without
   // it: 2,000 rows, GCN 128 -> 24 forward 11.5 / 9.7, printed GraphSAGE of 24 columns 16.6 / 14.5 forward, 32.4 / 28.6 backward; 30k rows
   // 14.5 / 12.7, 19.5 / 17.3, 36.2 / 32.7; 100k 29.0 / 27.5, 33.6 / 34.0, 56.9 / 54.9; 500k 94 / 94, 100 / 109, 151 / 158).  In the tiles of 128
-  // columns that was no faster (256 -> 256 over 2,000 rows 26.7 / 25.2, 30k 43.7 / 43.7, 500 -> 500 over 30k 57 / 63).
+  // columns that was no faster (500 -> 500 over 30k 57 / 63).
   const bool as_is = narrow && a.M < 1 << 16 && (a.ldb | a.ldb2) < 1 << 22;  // (32-bit offsets)
   const int64_t ldd = pad8(K);
   bf16_t* const Wb = (bf16_t*)a.param_scratch;
@@ -797,7 +807,8 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
   p.relu_last = a.relu_last;
   p.gate_last = a.gate_last;
   p.gate_scale = a.gate ? a.gate_scale : 1.f;
-  p.tiles_n = narrow ? 1 : (a.N + HBN - 1) / HBN;
+  const int tile_n = narrow ? 64 : HBN;
+  p.tiles_n = (a.N + tile_n - 1) / tile_n;
   p.tiles_m = 1;
   p.n_groups = (a.M + HBM - 1) / HBM;
   const int64_t blocks = ((p.n_groups + 7) / 8) * 8 * p.tiles_n;

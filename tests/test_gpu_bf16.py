@@ -377,3 +377,41 @@ def test_cfg3_at_one_hundredth_scale_through_the_streamed_builder(G):
     for l, (got, ref) in enumerate(zip(model.grads, G_ref)):
         for name in ref:
             assert_close(got[name].cpu().numpy(), ref[name], TOL_BF16, f"layer {l} d{name}")
+
+
+@pytest.mark.parametrize("q", [0.0, 0.3])
+@pytest.mark.parametrize("kind,d_in,d_out", [("gcn", 65, 66), ("gcn", 130, 100), ("gcn", 8, 127), ("gcn", 193, 129), ("gcn", 300, 257), ("sage", 70, 192),
+                                             ("sage", 129, 65), ("sage_conv", 96, 193), ("sage_conv", 200, 70)])
+@pytest.mark.parametrize("n", [3, 129, 5_001])
+def test_tiles_of_64_columns_give_the_same_bits(kind, d_in, d_out, q, n, monkeypatch):
+    """Results of few tiles are taken 64 columns at a time, with parameters as they are or from their copy; sums are formed in
+    the same order, through every gate, scale, second range and addition of the layers in both directions."""
+    import torch
+    from paper_2308_03209_amd import binding as B
+    print(f"[case] bf16 tiles of 64 columns {kind} n={n} {d_in} -> {d_out} q={q}", flush=True)
+    d_msg = 104 if kind == "sage" else 0
+    code = {"gcn": B.GCN, "sage": B.SAGE_MEAN, "sage_conv": B.SAGE_CONV}[kind]
+    gen = torch.Generator(device="cuda").manual_seed(d_in)
+
+    def rand(*shape):
+        return torch.randn(*shape, generator=gen, device="cuda")
+    prm = {"W": rand(d_msg or d_out, d_in * (2 if kind == "sage_conv" else 1)) / d_in ** 0.5, "bW": rand(d_msg or d_out)}
+    if kind == "sage":
+        prm.update(U=rand(d_out, d_msg + d_in) / d_in ** 0.5, bU=rand(d_out))
+    H, dY = rand(n, d_in).bfloat16(), rand(n, d_out).bfloat16()
+    src = np.arange(n, dtype=np.int64)
+    P = B.build_partition(n, src, (src + 1) % n, 1, 0, 3)
+    d = B.layer_desc(code, d_in, d_msg, d_out, act=1, dropout_q=q, layer_id=2, seed=5, epoch=3, dtype=B.BF16)
+    ws = torch.empty(max(B.layer_workspace_bytes(d, n, x) for x in (False, True)), dtype=torch.uint8, device="cuda")
+    out = []
+    for tile in ("128", "64"):
+        monkeypatch.setenv("COFREE_BF16_TILE", tile)
+        sv = {"Z": torch.empty(n, max(d_msg, 1), device="cuda", dtype=torch.bfloat16),
+              "A": torch.empty(n, max(d_msg, d_in, d_out), device="cuda", dtype=torch.bfloat16)}
+        Y, dX = torch.full((n + 1, d_out), 7.0, device="cuda", dtype=torch.bfloat16), torch.full((n + 1, d_in), 7.0, device="cuda", dtype=torch.bfloat16)
+        grads = {k: torch.empty_like(v) for k, v in prm.items()}
+        B.layer_fwd(P, None, 0, d, H, prm, Y[:n], sv, ws)
+        B.layer_bwd(P, None, 0, d, H, Y[:n], prm, sv, dY.clone(), dX[:n], grads, False, ws)
+        assert bool((Y[n] == 7.0).all()) and bool((dX[n] == 7.0).all())
+        out.append((Y, dX, *grads.values()))
+    assert all(torch.equal(a, b) for a, b in zip(*out))
