@@ -27,8 +27,8 @@
  *    COFREE_AGG_ENTRY_SCALE = 0 | 1 (aggregation: per-source factors gathered from the per-node vector, or read
  *    per adjacency entry next to the neighbour ids), COFREE_AGG_SLOTS = 0 (aggregation: the row kernel reads
  *    the graph by row id instead of walking the copy stored in processing order) and
- *    COFREE_BF16_TILE = 0 | 128 | 256 (bfloat16 products with parameters: resident in LDS wherever they fit, or the tiled
- *    kernel with this block tile).  All are read at every launch.
+ *    COFREE_BF16_TILE = 0 | 1 | 64 | 128 | 256 (bfloat16 products with parameters: in LDS or in registers wherever they fit, or the
+ *    tiled kernel with blocks of so many columns).  All are read at every launch.
  *  - Parameters, gradients, norms, loss weights and the loss are float32.  Features and
  *    activations have the layer's dtype (COFREE_F32, or COFREE_BF16 with float32 accumulation).
  */

@@ -1,12 +1,13 @@
 // Dense feature transforms for bfloat16-stored activations: bf16 operands on the matrix cores
 // (v_mfma_f32_32x32x16_bf16), float32 accumulation, bf16 or float32 results.  Products with parameters over fewer rows
-// than gemm_bf16_resident.hip takes or over more k, and weight gradients of fewer than eight rows or columns.
+// than gemm_bf16_resident.hip and gemm_bf16_pinned.hip take or over more k, and weight gradients of fewer than eight rows or columns.
 //
 // Same tiling as the float32 kernel (128x128 block tile, four wavefronts 2x2, each 64x64 as 2x2
-// MFMA accumulators) with k-tiles of 32; large A B^T products (K > 512, or 512 in the forward pass) use a 256x256 tile of
-// sixteen wavefronts.  LDS tiles are stored row-major [i][k] with rows padded to 40 elements (80 bytes), so an MFMA operand (8 consecutive k of one row) is one conflict-free
-// ds_read_b128.  Float32 parameters are first converted to a bf16 [N][K] copy by a small kernel,
-// so that both products with parameters (C = A W^T and C = A W) read the same operand layout.
+// MFMA accumulators) with k-tiles of 32; large products of more than 512 k use a 256x256 tile of sixteen wavefronts, narrow ones and those
+// of few tiles 128x64 (gemm_bf16_few).  LDS tiles are stored row-major [i][k] with rows padded to 40 elements (80 bytes), so an MFMA operand
+// (8 consecutive k of one row) is one conflict-free ds_read_b128.  Float32 parameters are converted to a bf16 [N][K] copy by a small kernel
+// first, so that both products with parameters (C = A W^T and C = A W) read the same operand layout, or, in tiles of 64 columns over few
+// rows, on their way to LDS (HMoverParams).
 // Weight gradients (C = A^T B over the node dimension) read both operands node-major and scatter
 // them into the [i][k] LDS layout.
 #include <cstdio>

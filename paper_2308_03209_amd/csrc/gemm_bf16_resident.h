@@ -17,8 +17,8 @@
 // Parameters beyond 128 KB are cut by columns into two to four parts, each resident in its own workgroups.  The workgroups
 // of one group of rows lie next to each other on one XCD and walk the rows alike, so the rows come from memory once and
 // from that XCD's L2 for the others.  Measured, 1.88M rows to 256 columns, against the tiled
-// kernel: K = 356 684 -> 598 us, 303 649 -> 481; 512 with two parameter matrices of an input gradient 717 -> 711 (and two
-// launches of 5 us saved that convert parameters).  512 of a forward product, 714 -> 726, stays with the tiled kernel.
+// kernel: K = 356 684 -> 598 us, 303 649 -> 481, 512 717 -> 711.  Over many rows parameters of more than 256 k now lie in registers
+// (gemm_bf16_pinned.hip: 479, 427 and 587); parts remain for more than 256 columns of fewer k, fewer rows, and sums in place.
 
 // The first matrix operand is the parameter block, the second the rows: a lane then holds four consecutive columns of
 // one row at a time, and passes 32 x 32 results through 4 KB of LDS of its wavefront (float32, 16-byte pieces permuted

@@ -8,6 +8,7 @@
 //    4 * (lane / 16) on of its row, and element c of all lanes is one instruction.  Parameters lie in LDS in the order that
 //    the instructions read them.  They are the instruction's first operand, which leaves a lane four neighbouring columns
 //    of one row of the result: one 16-byte store, no staging.
+//    Two products of one matrix are the blocks of columns of one.
 //  * C = A^T B over nodes: a lane loads four neighbouring columns of node lane / 16, and element b of all lanes is the
 //    operand for the columns 4 i + b; the narrow side likewise, with as many columns per lane as it has blocks of 16.
 // Where the last lane's columns would cross the end of a row, its window is moved left to end with the row; the columns

@@ -9,7 +9,8 @@
 // running sum.
 //
 // Which shapes: results of more than 64 columns (weight gradients: more than 64 rows and columns) and ranges of at
-// least eight k.  Narrower ones are bound by their bytes and stay on the float32 instructions (gemm_narrow.hip).
+// least eight k; two products or weight gradients of one matrix as the columns or rows of one (TWO).  Narrower ones are bound by their
+// bytes and stay on the float32 instructions (gemm_narrow.hip).
 //
 // Rounding: every matrix instruction rounds its accumulator once.  h h has one of its own and the five products below it
 // another, which is about 2^-8 of the first, so that its rounding does not show; the two are added at the end.  The sum
@@ -32,7 +33,8 @@
 // 32x32 blocks), two workgroups per CU; see run_split for the pipeline.  One set of accumulators leaves room for
 // 128x256 tiles, but rounds more often; two sets in such tiles were no faster with one wavefront per SIMD or with eight
 // wavefronts in one workgroup.  Nor were 512 workgroups that take tiles in turn and request the next one's first step before
-// they write the last (470k x 512 x 512 1285 -> 1400 us).
+// they write the last (470k x 512 x 512 1285 -> 1400 us), nor a second step of a row operand in flight (0.97 to 1.09 of the time).
+// Results of few tiles: gemm_split_few_kernel.
 //
 // LDS plane of an operand of 128 rows: [k-group of 8][row][8 bfloat16].  A matrix operand - 8 consecutive k of 32
 // consecutive rows per half wavefront - is then 512 contiguous bytes.  Neighbouring rows are swapped in every other

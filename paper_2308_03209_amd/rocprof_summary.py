@@ -40,8 +40,8 @@ def kernel_source_hash() -> str:
 
 
 def instance_name(kernel: str) -> str:
-    """'void cofree::aggregate_sliced_kernel<float, 8, false>(cofree::AggK<float>)' ->
-    'aggregate_sliced_kernel<float,8,false>' (the form the library's own timing records use)."""
+    """'void cofree::aggregate_sliced_kernel<float, 8, 0>(cofree::AggK<float>)' ->
+    'aggregate_sliced_kernel<float,8,0>' (the form the library's own timing records use)."""
     k = re.sub(r"\(.*", "", kernel)
     k = k.replace("void ", "").replace("cofree::", "").replace("unsigned short", "bf16").replace(" ", "")
     return k
