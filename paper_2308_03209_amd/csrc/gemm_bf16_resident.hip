@@ -37,7 +37,7 @@ static int column_parts(int32_t N, int nch) {
 // and the aggregation beside it, tiled / resident: A B^T of 256 x 256 (columns x k) over 20k rows 23 / 36, 100k 57 / 69, 200k 127 / 123,
 // 800k 452 / 431; 128 x 128 20k 15 / 17, 100k 34 / 34, 200k 54 / 51; 128 x 400 200k 88 / 90, 400k 195 / 183; 172 x 256 20k 28 / 31,
 // 50k 46 / 42, 200k 137 / 101; 47 x 256 2k 16 / 12, 100k 45 / 40; 512 k everywhere slower: 512 x 512 200k 281 / 284, 1.6M
-// 2012 / 2074.  A B (with the launches of the weight gradient): 128 x 128 20k 35 / 32, 100k 56 / 50; 172 x 256 20k 54 / 52, 100k
+// 2012 / 2074; 380 x 276 140k 98 / 61.  A B (with the launches of the weight gradient): 128 x 128 20k 35 / 32, 100k 56 / 50; 172 x 256 20k 54 / 52, 100k
 // 105 / 93; 256 x 256 20k 54 / 58, 100k 106 / 104, 200k 229 / 203; 256 x 172 100k 99 / 103, 200k 190 / 180; 512 x 512 20k 74 / 80, 100k
 // 231 / 225; 130 x 129, where a quarter of the k is padding, 100k 110 / 116, 200k 184 / 176.  Dropout would be a pass of its own
 // beside the tiled kernel (100k x 128: 15 us).
@@ -48,7 +48,7 @@ static int64_t resident_min_rows(int32_t N, int32_t K, int nch, bool kmajor, boo
   if (drop) return param <= 8 ? 0 : 1 << 15;
   if (nch >= 8) return INT64_MAX;
   if (tiles_empty) return N <= 64 ? 0 : 1 << 15;
-  return param <= 24 ? 1 << 17 : 1 << 18;
+  return param <= 24 || (nch == 5 && N > 256 && N <= 384) ? 1 << 17 : 1 << 18;
 }
 
 // At most 512 k, segments of at least eight, parameters of at most four column parts, and rows as above.
