@@ -322,7 +322,7 @@ struct AggArgs {
   float gate_scale = 1.f;            // factor on the elements that pass relu_src
   const void* add = nullptr;         // added to Y (same dtype, ld = ld_add); not together with relu_src
   int64_t ld_add = 0;
-  // applied after out_scale, in this order: + add[v,c], + bias[c], ReLU
+  // applied after out_scale, in this order: + bias[c] (first to add[v,c], which is then added), ReLU
   const float* bias = nullptr;
   int32_t relu_out = 0;
   DropoutArgs dropout;  // of the finished rows, where aggregate_drops() allows it

@@ -370,7 +370,7 @@ int32_t cofree_layer_fwd(const cofree_partition* part, const cofree_masks* masks
   } else if (d.kind == COFREE_SAGE_CONV) {
     const int64_t ldw = 2 * (int64_t)d.d_in;  // W = [W_self | W_neigh]
     if (fp.S) {
-      // T = H W_neigh^T, S = H W_self^T; H' = act(mean(T) + S + b)
+      // T = H W_neigh^T, S = H W_self^T; H' = act(mean(T) + (S + b))
       GemmArgs t = gemm();
       t.A1 = H_in; t.lda1 = d.d_in; t.K1 = d.d_in;
       t.B = params->W + d.d_in; t.ldb = ldw;

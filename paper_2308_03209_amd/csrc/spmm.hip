@@ -231,6 +231,7 @@ struct RowTail {
 template <typename T, int VEC, bool TINY, int DROP>
 __device__ inline void finish_row(const AggK<T>& p, uint32_t row, int c0, int avail, float (&acc)[VEC],
                                   const RowTail<T, VEC, TINY>& t) {
+  float other[VEC];  // the row's other operand
   if constexpr (TINY) {
     if (p.self_loop) {
       const float ss = p.in_scale ? p.in_scale[row] : 1.f;
@@ -242,40 +243,44 @@ __device__ inline void finish_row(const AggK<T>& p, uint32_t row, int c0, int av
     const float so = p.out_scale ? p.out_scale[row] : 1.f;
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] *= so;
-    if (p.relu_src) {
-      float g[VEC];
-      load_elems<T, VEC>(row_at(p.relu_src, row, p.ld_relu) + c0, avail, g);
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) acc[i] = p.add_src ? acc[i] + g[i] : (g[i] > 0.f ? acc[i] * p.gate_scale : 0.f);
-    }
+    if (p.relu_src) load_elems<T, VEC>(row_at(p.relu_src, row, p.ld_relu) + c0, avail, other);
   } else {
     if (p.self_loop) RowIO<T>::fma_raw(acc, t.ss, t.xs);
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] *= t.so;
-    if (p.relu_src) {
-      float g[VEC];
-      RowIO<T>::unpack(t.g, g);
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) acc[i] = p.add_src ? acc[i] + g[i] : (g[i] > 0.f ? acc[i] * p.gate_scale : 0.f);
-    }
+    if (p.relu_src) RowIO<T>::unpack(t.g, other);
   }
-  if (p.bias) {
-    // A window of a row that is not TINY exists whole, so its biases are wide loads without a condition: eight
-    // conditional ones, each with its own wait, held a launch back by half (2.35M rows of 172 bfloat16 1615 -> 1222 us,
-    // 100k rows of 128 43.8 -> 27.0).
+  // A window of a row that is not TINY exists whole, so its biases are wide loads without a condition: eight
+  // conditional ones, each with its own wait, held a launch back by half (2.35M rows of 172 bfloat16 1615 -> 1222 us,
+  // 100k rows of 128 43.8 -> 27.0).
+  auto add_bias = [&](float (&x)[VEC]) __attribute__((always_inline)) {
     const float* const b = p.bias + (p.col0 + c0);
     if constexpr (TINY) {
 #pragma unroll
       for (int i = 0; i < VEC; ++i)
-        if (i < avail) acc[i] += b[i];
+        if (i < avail) x[i] += b[i];
     } else {
 #pragma unroll
       for (int q = 0; q < VEC / 4; ++q) {
         const f32x4u t = reinterpret_cast<const f32x4u*>(b)[q];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[4 * q + i] += t[i];
+        for (int i = 0; i < 4; ++i) x[4 * q + i] += t[i];
       }
     }
+  };
+  if (p.add_src) {
+    // (other + bias) + the scaled sum, each rounded: the bits of a product with its bias that is added to the sum.  Another
+    // order opens or closes the ReLU of elements within rounding of zero, and Adam's first steps make whole steps of that.
+#pragma clang fp contract(off)
+    if (p.bias) add_bias(other);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[i] = other[i] + acc[i];
+  } else {
+    if (p.relu_src) {
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) acc[i] = other[i] > 0.f ? acc[i] * p.gate_scale : 0.f;
+    }
+    if (p.bias) add_bias(acc);
   }
   if (p.relu_out) {
 #pragma unroll

@@ -1,5 +1,6 @@
 """Conventional GraphSAGE layers that transform first, in float32: both products of a layer's input in one launch (blocks of 16 columns
-up to 32 columns a result, tiles of 128 beyond), the self part added by the aggregation; against float64."""
+up to 32 columns a result, tiles of 128 beyond), the self part added by the aggregation; against float64, and bit for bit against the
+three launches that a workspace without room for a second result takes."""
 import numpy as np
 import pytest
 
@@ -73,6 +74,32 @@ def test_dropout_and_without_room(d_in, d_out):
     clear = (Y > 1e-3) | (Y == 0)  # away from zero both routes agree on the sign
     assert torch.equal(kept[clear], (Z != 0)[clear])
     assert float((D - Z).abs().max()) <= 1e-5
+
+
+# rows of every degree class, hubs among them; slices: the aggregation's launches (see COFREE_AGG_SLICES)
+@pytest.mark.parametrize("slices,widths", [("0", (66, 100, 128, 129)), ("1", (66, 128)), ("2", (68, 128)), ("8", (128, 256))])
+@pytest.mark.parametrize("q", [0.0, 0.3])
+def test_the_bits_of_three_launches(slices, widths, q, monkeypatch):
+    """Products of more than 64 columns are the same tiles in both forms, and mean + (self part + bias) is rounded alike: with
+    another order of these additions ReLUs within rounding of zero open or close."""
+    import torch
+    from paper_2308_03209_amd import binding as B
+    monkeypatch.setenv("COFREE_AGG_SLICES", slices)
+    src, dst = inputs.hub_graph(5_001, [4_097, 4_095, 1_000, 257, 255, 128, 65, 64, 33, 31, 17, 15], 6_000, 21)
+    P = B.build_partition(5_001, src, dst, 1, 0, 1)
+    n = P.num_nodes
+    for d_out in widths:
+        d_in = 2 * d_out + 3
+        print(f"[case] two results against three launches, slices {slices}, {d_in} -> {d_out}, dropout {q}", flush=True)
+        B.profile_enable(True)
+        _, _, _, Y = layer(B, torch, P, d_in, d_out, 1, q, n, d_out)
+        names = list(B.profile_read())
+        B.profile_enable(False)
+        assert sum("gemm" in x for x in names) == 1 and (slices != "0" or any(x.startswith("aggregate_hub_kernel") for x in names)), names
+        assert slices in "01" or any(x.startswith("aggregate_sliced_kernel") for x in names), names
+        _, _, _, Z = layer(B, torch, P, d_in, d_out, 1, q, n, d_out, room=(n * d_out * 4 + 255) // 256 * 256)
+        assert bool(torch.isfinite(Y).all()) and float((Y > 0).float().mean()) > 0.2
+        assert torch.equal(Y, Z)
 
 
 @pytest.mark.parametrize("d_in,d_out", [(70, 20), (70, 40)])
