@@ -202,7 +202,7 @@ static BwdPlan plan_bwd(const cofree_layer_desc& d, int64_t n, Carver& c, Carver
     // transform first: T = Ahat dPre [n, d_out]; aggregate first: T = norm * (dPre W) [n, d_in]
     p.T = c.take(N * (gcn_transform_first(d) ? d.d_out : d.d_in) * es);
     p.wg[0] = (float*)part.take(4 * wgrad_workspace_floats(conv_two_wgrads(d, n) ? 2 * d.d_out : d.d_out, d.d_in, n, conv_merged(d) ? d.d_in : 0));
-    if (d.kind == COFREE_SAGE_CONV && !conv_merged(d) && !conv_two_wgrads(d, n)) p.wg[1] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
+    if (d.kind == COFREE_SAGE_CONV && !conv_merged(d)) p.wg[1] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
     if (d.kind == COFREE_GCN && gcn_transform_first(d)) p.cs = (float*)part.take(4 * colsum_workspace_floats(d.d_out));
   }
   p.needed = c.used;
@@ -612,9 +612,10 @@ static int32_t layer_bwd(const cofree_partition* part, const cofree_masks* masks
     w.colsum_out = grads->bW;
     const bool transform_first = conv_transform_first(d);
     if (!transform_first) COFREE_REQUIRE(saved->A, "layer_bwd: saved.A is NULL");
-    // dW_neigh = dT^T H where the forward pass was mean(H W_neigh^T), in the launch of dW_self where both can be
+    // dW_neigh = dT^T H where the forward pass was mean(H W_neigh^T), in the launch of dW_self where both can be:
     const WgradArgs wn = transform_first ? wgrad(p.T, d.d_out, H_in, d.d_in, grads->W + d.d_in, ldw, p.wg[1]) : WgradArgs{};
-    const bool both = conv_two_wgrads(d, n);  // as two results of one product
+    // ... as two results of one product; with a second stream dW_self runs there beside the aggregation that dW_neigh waits for
+    const bool both = !side && conv_two_wgrads(d, n);
     if (both) w.A2 = p.T, w.C2 = grads->W + d.d_in;
     const bool together = transform_first && !both && !side && wgrads_pair(w, wn);
     // dW_neigh = dPre^T M where the forward pass has kept M = mean(H) (side stream as well)

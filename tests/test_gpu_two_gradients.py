@@ -36,3 +36,32 @@ def test_against_float64(dtype, d_in, d_out, n, accumulate):
     base = 1.0 if accumulate else 0.0
     assert bool(((g["W"].double() - base - ref).abs() <= (n + 8.0) * 2.0 ** -24 * (mag + base)).all())
     assert bool(((g["bW"].double() - base - z.sum(0)).abs() <= (n + 8.0) * 2.0 ** -24 * (z.abs().sum(0) + base)).all())
+
+
+@pytest.mark.parametrize("dtype,n,d_in,d_out", [("f32", 5_003, 200, 100), ("f32", 40_011, 129, 47), ("bf16", 5_003, 100, 47)])
+def test_a_second_stream_has_dW_self(dtype, n, d_in, d_out, monkeypatch):
+    """With COFREE_OVERLAP=1 dW_self, which does not wait for the aggregation, is a launch of its own on the second stream."""
+    import torch
+    from paper_2308_03209_amd import binding as B
+    print(f"[case] two gradients on two streams {dtype} n={n} {d_in} -> {d_out}", flush=True)
+    src = np.arange(n, dtype=np.int64)
+    P = B.build_partition(n, src, (src + 1) % n, 1, 0, 3)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    H = (torch.randint(-8, 9, (n, d_in), generator=gen, device="cuda") * 0.25).to(td)
+    # products are multiples of 1/32 of at most 4: every partial sum is exact
+    dO = (torch.randint(-8, 9, (n, d_out), generator=gen, device="cuda") * 0.25).to(td)
+    p = {"W": torch.zeros(d_out, 2 * d_in, device="cuda"), "bW": torch.zeros(d_out, device="cuda")}
+    d = B.layer_desc(B.SAGE_CONV, d_in, 0, d_out, dtype=B.F32 if dtype == "f32" else B.BF16)
+    ws = torch.empty(B.layer_workspace_bytes(d, n, True), dtype=torch.uint8, device="cuda")
+    got = []
+    for overlap, launches in (("0", 1), ("1", 2)):
+        monkeypatch.setenv("COFREE_OVERLAP", overlap)
+        g = {k: torch.full_like(v, float("nan")) for k, v in p.items()}
+        B.profile_enable(True)
+        B.layer_bwd(P, None, 0, d, H, dO, p, {}, dO, None, g, False, ws)
+        stats = B.profile_read()
+        B.profile_enable(False)
+        assert sum(v["launches"] for k, v in stats.items() if f"x{d_in}" in k) == launches, list(stats)
+        got.append(g)
+    assert all(torch.equal(got[0][k], got[1][k]) for k in p)
