@@ -413,7 +413,7 @@ struct WgradArgs {
   int64_t lda = 0;
   int32_t N1 = 0;
   // optional, where wgrad_two_fits(): a second matrix of the same shape and leading dimension, whose gradient A2^T B goes to C2
-  // (leading dimension ldc) from the same launch; the workspace is that of 2 N1 rows
+  // (leading dimension ldc) from the same launch; the workspace is twice that of one
   const void* A2 = nullptr;
   float* C2 = nullptr;
   const void* B = nullptr;

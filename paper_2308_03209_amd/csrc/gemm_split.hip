@@ -1213,7 +1213,7 @@ bool wgrad_split_fits(const WgradArgs& a) {
 
 int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
   const int32_t N1 = a.A2 ? 2 * a.N1 : a.N1, N2 = a.N2 + (a.B2 ? a.N2b : 0);
-  const int32_t S = wgrad_splits(N1, N2, a.M, WGRAD_RESIDENT_SPLIT);
+  const int32_t S = wgrad_splits(a.N1, N2, a.M, WGRAD_RESIDENT_SPLIT);  // also of two gradients, see wgrad_two_fits()
   SplitK p{};
   p.A1 = (const float*)a.A;
   p.lda1 = a.lda;

@@ -176,7 +176,7 @@ static FwdPlan plan_fwd(const cofree_layer_desc& d, int64_t n, void* ws, size_t 
 
 struct BwdPlan {
   void *dP = nullptr, *dA = nullptr, *dZ = nullptr, *T = nullptr, *params = nullptr;
-  // partials of up to three weight gradients (they stay until they are summed), of one bias gradient
+  // partials of up to three weight gradients (they stay until they are summed), one behind the other, of one bias gradient
   float *wg[3] = {nullptr, nullptr, nullptr}, *cs = nullptr;
   size_t params_bytes = 0;
   size_t needed = 0;  // bytes of the layer's own workspace that a call cannot do without
@@ -201,7 +201,7 @@ static BwdPlan plan_bwd(const cofree_layer_desc& d, int64_t n, Carver& c, Carver
     if (d.dropout_q > 0.f || d.act) p.dP = c.take(N * d.d_out * es);
     // transform first: T = Ahat dPre [n, d_out]; aggregate first: T = norm * (dPre W) [n, d_in]
     p.T = c.take(N * (gcn_transform_first(d) ? d.d_out : d.d_in) * es);
-    p.wg[0] = (float*)part.take(4 * wgrad_workspace_floats(conv_two_wgrads(d, n) ? 2 * d.d_out : d.d_out, d.d_in, n, conv_merged(d) ? d.d_in : 0));
+    p.wg[0] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n, conv_merged(d) ? d.d_in : 0));
     if (d.kind == COFREE_SAGE_CONV && !conv_merged(d)) p.wg[1] = (float*)part.take(4 * wgrad_workspace_floats(d.d_out, d.d_in, n));
     if (d.kind == COFREE_GCN && gcn_transform_first(d)) p.cs = (float*)part.take(4 * colsum_workspace_floats(d.d_out));
   }

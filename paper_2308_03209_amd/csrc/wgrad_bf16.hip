@@ -65,7 +65,9 @@ __device__ inline Piece piece_of(int q, int32_t N, int32_t Nb) {
 }
 
 // TM x TN: tile of the result; SN: nodes per step; D: steps in flight; WM x WN: wavefronts over the tile.
-template <int TM, int TN, int SN, int D, int WM, int WN>
+// PARTS: of a thread's column sums - two where two matrices A share a tile of twice the rows that one of them would take, in which a
+// thread has twice the nodes of a column.
+template <int TM, int TN, int SN, int D, int WM, int WN, int PARTS>
 __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void wgrad_bf16_kernel(
     const WgradK p) {
   static_assert(WM * WN == WG_WAVES, "eight wavefronts");
@@ -76,7 +78,8 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
   constexpr int JA = SN * QA / T, JB = SN * QB / T;      // pieces of a step that a thread moves
   static_assert(JA * T == SN * QA && JB * T == SN * QB, "whole pieces");
   constexpr int RM = TM / WM / 32, RN = TN / WN / 32;  // 32 x 32 blocks of a wavefront
-  constexpr int RED = (T / QA) * TM * 4;               // column sums: one row of the tile per thread group
+  static_assert(PARTS == 1 || JA == 2 || (JA == 1 && D % 2 == 0), "a part is a thread's piece of a step, or every other step");
+  constexpr int RED = PARTS * (T / QA) * TM * 4;       // column sums: one row of the tile per thread group and part
   __shared__ __attribute__((aligned(128))) unsigned char smem[2 * STEP > RED ? 2 * STEP : RED];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
@@ -106,7 +109,7 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
     for (int n = 0; n < RN; ++n)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[m][n][v] = 0.f;
-  float csum[8] = {};
+  float csum[PARTS][8] = {};
   const bool colsum = p.colsum_part != nullptr && qn == 0;
 
   // thread t moves piece t % Q of rows t / Q + (T / Q) j of a step; rows past the chunk repeat its last one (and become
@@ -132,7 +135,7 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
     }
   };
   const int to_a = ra * PA + (tid % QA) * 16, to_b = SN * PA + rb * PB + (tid % QB) * 16;
-  auto store = [&](int k0, unsigned char* d, Raw& w) {
+  auto store = [&](int k0, unsigned char* d, Raw& w, int s) __attribute__((always_inline)) {
     if (k0 + SN > k_len) {  // uniform: the chunk ends inside this step
 #pragma unroll
       for (int j = 0; j < JA; ++j)
@@ -147,10 +150,11 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
     for (int j = 0; j < JA; ++j) {
       *reinterpret_cast<uint4*>(d + to_a + (T / QA) * j * PA) = make_uint4(w.a[j][0], w.a[j][1], w.a[j][2], w.a[j][3]);
       if (colsum) {
+        float (&sum)[8] = csum[PARTS == 2 && (JA == 2 ? j : s & 1) == 1 ? PARTS - 1 : 0];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-          csum[2 * c] += __uint_as_float(w.a[j][c] << 16);
-          csum[2 * c + 1] += __uint_as_float(w.a[j][c] & 0xffff0000u);
+          sum[2 * c] += __uint_as_float(w.a[j][c] << 16);
+          sum[2 * c + 1] += __uint_as_float(w.a[j][c] & 0xffff0000u);
         }
       }
     }
@@ -189,7 +193,7 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
     // loads past the end repeat the last step, which keeps the count of loads in flight the same on every path
     auto step = [&](int t, int s, bool refill) {
       unsigned char* const d = smem + (t & 1) * STEP;
-      store(t * SN, d, ring[s]);
+      store(t * SN, d, ring[s], s);
       if (refill) load((t + D < n ? t + D : n - 1) * SN, ring[s]);
       __syncthreads();
       multiply(d);
@@ -233,11 +237,13 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
     float* const red = reinterpret_cast<float*>(smem);
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < 8; ++c) red[ra * TM + (tid % QA) * 8 + c] = csum[c];
+    for (int q = 0; q < PARTS; ++q)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) red[(q * (T / QA) + ra) * TM + (tid % QA) * 8 + c] = csum[q][c];
     __syncthreads();
     if (tid < TM) {
       float t = 0.f;
-      for (int h = 0; h < T / QA; ++h) t += red[h * TM + tid];
+      for (int h = 0; h < PARTS * (T / QA); ++h) t += red[h * TM + tid];
       const Piece xr = piece_of(qm + (tid >> 3), p.N1, p.N1b);
       if (xr.exists && !xr.second && (tid & 7) >= xr.first) p.colsum_part[z * p.N1 + xr.col + (tid & 7)] = t;
     }
@@ -281,9 +287,25 @@ static int32_t wgrad_chunks(int32_t tiles, int64_t M) {
 
 bool wgrad_bf16_fits(int32_t N1, int32_t N2, int32_t N2b) { return N1 >= 8 && N2 >= 8 && (N2b == 0 || N2b >= 8); }
 
+// Tile and chunks of the gradient of one matrix A.  A launch of two has larger tiles but the same chunks (see wgrad_two_fits()).
+static WgradTile tile_of_one(int32_t N1, int32_t N2, int32_t N2b, int64_t M) {
+  return wgrad_tile(8 * pieces_of(N1), 8 * (pieces_of(N2) + pieces_of(N2b)), M);
+}
+
 size_t wgrad_bf16_workspace_floats(int32_t N1, int32_t N2, int32_t N2b, int64_t M) {
-  const WgradTile t = wgrad_tile(8 * pieces_of(N1), 8 * (pieces_of(N2) + pieces_of(N2b)), M);
+  const WgradTile t = tile_of_one(N1, N2, N2b, M);
   return (size_t)wgrad_chunks(t.m * t.n, M) * ((size_t)N1 * ((size_t)N2 + N2b) + (size_t)N1);
+}
+
+template <int PARTS>
+static void launch_tile(int32_t th, int32_t tw, unsigned blocks, const WgradK& p, hipStream_t stream) {
+  const dim3 grid(blocks);
+  if (tw == 256 && th == 256) wgrad_bf16_kernel<256, 256, 32, 3, 2, 4, PARTS><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
+  else if (tw == 256 && th == 128) wgrad_bf16_kernel<128, 256, 32, 4, 2, 4, PARTS><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
+  else if (th == 256) wgrad_bf16_kernel<256, 128, 32, 4, 4, 2, PARTS><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
+  else if (th == 128) wgrad_bf16_kernel<128, 128, 32, 6, 2, 4, PARTS><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
+  else if (tw == 256) wgrad_bf16_kernel<64, 256, 64, 2, 1, 8, 1><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
+  else wgrad_bf16_kernel<64, 128, 64, 4, 2, 4, 1><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
 }
 
 int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
@@ -301,10 +323,16 @@ int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t 
   p.N2b = a.B2 ? a.N2b : 0;
   p.M = a.M;
   const int32_t N2 = p.N2 + p.N2b;
-  const WgradTile tile = wgrad_tile(8 * (pieces_of(p.N1) + pieces_of(p.N1b)), 8 * (pieces_of(p.N2) + pieces_of(p.N2b)), a.M);
+  const int32_t rows = 8 * (pieces_of(p.N1) + pieces_of(p.N1b));
+  WgradTile tile = wgrad_tile(rows, 8 * (pieces_of(p.N2) + pieces_of(p.N2b)), a.M);
+  // With the chunks of one gradient a tile of both is no workgroup more: 100 x 256 over 300,000 nodes 120 us in two tiles of 128 rows, 109 in
+  // one of 256 (but over 2,000, 16 chunks a tile, 15 and 17).
+  if (a.A2 && rows > 128 && a.M >= 1 << 17) tile.h = 256, tile.m = 1;
   p.tiles_m = tile.m;
   p.tiles_n = tile.n;
-  const int32_t S = wgrad_chunks(tile.m * tile.n, a.M);
+  const WgradTile one = tile_of_one(p.N1, p.N2, p.N2b, a.M);
+  const bool apart = one.h < tile.h;
+  const int32_t S = wgrad_chunks(one.m * one.n, a.M);
   p.n_chunks = S;
   p.chunk = std::max<int64_t>(1, (((a.M + S - 1) / S) + 31) / 32 * 32);
   p.C = a.workspace;
@@ -319,19 +347,11 @@ int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t 
     char pname[96] = "";
     const char* rest = tw == 256 ? (th == 256 ? "32,3,2,4" : (th == 128 ? "32,4,2,4" : "64,2,1,8"))
                                  : (th == 256 ? "32,4,4,2" : (th == 128 ? "32,6,2,4" : "64,4,2,4"));
-    if (profiling()) snprintf(pname, sizeof(pname), "wgrad_bf16_kernel<%d,%d,%s> N=%dx%d", (int)th, (int)tw, rest, (int)N1, (int)N2);
+    if (profiling()) snprintf(pname, sizeof(pname), "wgrad_bf16_kernel<%d,%d,%s,%d> N=%dx%d", (int)th, (int)tw, rest, apart ? 2 : 1, (int)N1, (int)N2);
     ProfScope prof(pname, stream, 2.0 * ((double)a.M * N1 * (p.extra.X ? 2 : 1) + (double)a.M * N2) + 4.0 * (double)N1 * N2,
                    2.0 * (double)a.M * N1 * N2);
-    const dim3 grid((unsigned)blocks);
-    if (tw == 256) {
-      if (th == 256) wgrad_bf16_kernel<256, 256, 32, 3, 2, 4><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
-      else if (th == 128) wgrad_bf16_kernel<128, 256, 32, 4, 2, 4><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
-      else wgrad_bf16_kernel<64, 256, 64, 2, 1, 8><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
-    } else {
-      if (th == 256) wgrad_bf16_kernel<256, 128, 32, 4, 4, 2><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
-      else if (th == 128) wgrad_bf16_kernel<128, 128, 32, 6, 2, 4><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
-      else wgrad_bf16_kernel<64, 128, 64, 4, 2, 4><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
-    }
+    if (apart) launch_tile<2>(th, tw, (unsigned)blocks, p, stream);
+    else launch_tile<1>(th, tw, (unsigned)blocks, p, stream);
   }
   COFREE_HIP_CHECK(hipGetLastError());
   COFREE_TRY(add_split_sum(sums, a.workspace, (int64_t)N1 * N2, S, a.C, a.ldc, a.N1, N2));

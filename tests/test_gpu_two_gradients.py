@@ -65,3 +65,31 @@ def test_a_second_stream_has_dW_self(dtype, n, d_in, d_out, monkeypatch):
         assert sum(v["launches"] for k, v in stats.items() if f"x{d_in}" in k) == launches, list(stats)
         got.append(g)
     assert all(torch.equal(got[0][k], got[1][k]) for k in p)
+
+
+# pairs of tiles that one gradient alone would cut into more chunks: tiles of 128 rows (float32), of up to 256 (bfloat16); 64 and less: the same tiles
+@pytest.mark.parametrize("dtype,n,d_in,d_out", [("f32", 115_001, 602, 256), ("f32", 150_001, 512, 100), ("f32", 40_003, 300, 128), ("f32", 9_001, 140, 66),
+                                                ("bf16", 150_001, 300, 128), ("bf16", 70_001, 256, 100), ("bf16", 300_001, 200, 64)])
+def test_sums_as_short_as_one_gradients(dtype, n, d_in, d_out, monkeypatch):
+    """Both gradients and the bias gradient have the bits of launches of their own (COFREE_OVERLAP=1): as many chunks of nodes."""
+    import torch
+    from paper_2308_03209_amd import binding as B
+    print(f"[case] sums of two gradients {dtype} n={n} {d_in} -> {d_out}", flush=True)
+    src = np.arange(n, dtype=np.int64)
+    P = B.build_partition(n, src, (src + 1) % n, 1, 0, 3)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    H = torch.randn(n, d_in, generator=gen, device="cuda").to(td)
+    dO = torch.randn(n, d_out, generator=gen, device="cuda").to(td)
+    p = {"W": torch.zeros(d_out, 2 * d_in, device="cuda"), "bW": torch.zeros(d_out, device="cuda")}
+    d = B.layer_desc(B.SAGE_CONV, d_in, 0, d_out, dtype=B.F32 if dtype == "f32" else B.BF16)
+    room = B.layer_workspace_bytes(d, n, True)
+    ws = torch.full((room + 4096,), 0xa5, dtype=torch.uint8, device="cuda")
+    got = []
+    for overlap in ("0", "1"):
+        monkeypatch.setenv("COFREE_OVERLAP", overlap)
+        g = {k: torch.full_like(v, float("nan")) for k, v in p.items()}
+        B.layer_bwd(P, None, 0, d, H, dO, p, {}, dO, None, g, False, ws[:room])
+        got.append(g)
+    assert bool((ws[room:] == 0xa5).all())
+    assert all(bool(torch.isfinite(got[0][k]).all()) and torch.equal(got[0][k], got[1][k]) for k in p)
