@@ -391,6 +391,7 @@ struct SplitSum {
   float* C;
   int64_t ldc;
   int32_t splits, rows, cols;
+  int32_t f64;     // added in float64 (but for the last eight terms)
   int32_t block0;  // first workgroup of this job (set by the launcher)
 };
 struct SplitSums {
@@ -400,7 +401,7 @@ struct SplitSums {
   int32_t accumulate = 0;
 };
 int32_t add_split_sum(SplitSums* sums, const float* part, int64_t stride, int32_t splits, float* C, int64_t ldc,
-                      int32_t rows, int32_t cols);
+                      int32_t rows, int32_t cols, bool f64 = false);
 int32_t launch_split_sums(SplitSums sums, hipStream_t stream);
 
 // Weight gradient C[N1, N2 + N2b] = A^T [B | B2] with A [M, N1], B [M, N2], B2 [M, N2b] of `dtype`, C float32: reduction

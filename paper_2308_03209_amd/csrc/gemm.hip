@@ -549,8 +549,15 @@ __global__ __launch_bounds__(256) void split_sums_kernel(const SplitSums p) {
   float s = 0.f;
   if (ok) {
     const float* part = jb.part + idx;
+    if (jb.f64) {  // uniform
+      double d = 0.0;
 #pragma unroll 8
-    for (int z = zg; z < jb.splits; z += SR_ZG) s += part[(int64_t)z * jb.stride];
+      for (int z = zg; z < jb.splits; z += SR_ZG) d += (double)part[(int64_t)z * jb.stride];
+      s = (float)d;
+    } else {
+#pragma unroll 8
+      for (int z = zg; z < jb.splits; z += SR_ZG) s += part[(int64_t)z * jb.stride];
+    }
   }
   red[zg][ii] = s;
   __syncthreads();
@@ -564,9 +571,9 @@ __global__ __launch_bounds__(256) void split_sums_kernel(const SplitSums p) {
 }
 
 int32_t add_split_sum(SplitSums* sums, const float* part, int64_t stride, int32_t splits, float* C, int64_t ldc,
-                      int32_t rows, int32_t cols) {
+                      int32_t rows, int32_t cols, bool f64) {
   if (sums->n >= SplitSums::MAX) return fail(COFREE_EINVAL, "internal: too many split sums");
-  sums->job[sums->n++] = SplitSum{part, stride, C, ldc, splits, rows, cols, 0};
+  sums->job[sums->n++] = SplitSum{part, stride, C, ldc, splits, rows, cols, f64, 0};
   return COFREE_OK;
 }
 

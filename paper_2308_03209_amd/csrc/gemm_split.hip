@@ -83,6 +83,7 @@ struct SplitK {
   int64_t n_groups;
   int32_t n_split;     // weight gradients: columns n_split .. of the result come from B2 (0: all from B1)
   float* colsum_part;  // weight gradients: [chunks][M] partial column sums of operand A, or null
+  int32_t colsum_f64;  // ... in float64 inside a chunk
   ColsumK extra;       // weight gradients: workgroups behind the others that sum columns of another matrix
   const float* bias;
   int32_t relu;
@@ -223,6 +224,7 @@ struct SplitKContig {
 // a whole wavefront, so rows are addressed with scalars).  TWO: columns of two matrices.
 template <bool TWO>
 struct SplitKMajorOf {
+  static constexpr bool OF_TWO = TWO;
   struct Raw {
     float x[8];
   };
@@ -363,6 +365,13 @@ __device__ inline void multiply_step(const unsigned char* as, const unsigned cha
   }
 }
 
+// A thread's share of a column sum, in float64 where a narrow matrix is (TWO, see launch_wgrad_split)
+struct ColumnSum {
+  float sum = 0.f;
+  double sum64 = 0.0;
+  bool f64 = false;
+};
+
 // One k-range of length k_len >= 1.  csum: column sums of operand A (only where the caller wants them).  small: set where
 // the thread's share of either operand is all small.
 //
@@ -379,7 +388,7 @@ __device__ inline void multiply_step(const unsigned char* as, const unsigned cha
 constexpr int FLIP_STEPS = 16;
 template <bool FLIP, typename MA, typename MB>
 __device__ inline void run_split(const MA& ma, const MB& mb, int k_len, unsigned char* smem, int a_off, int b_off,
-                                 Sums& acc, int tid, int phase, bool colsum, float& csum, bool& small) {
+                                 Sums& acc, int tid, int phase, bool colsum, ColumnSum& csum, bool& small) {
   const int n = (k_len + SBK - 1) / SBK;
   typename MA::Raw ra;
   typename MB::Raw rb;
@@ -403,7 +412,11 @@ __device__ inline void run_split(const MA& ma, const MB& mb, int k_len, unsigned
   };
   auto add_csum = [&](int t, auto part) {
     if constexpr (FLIP) {
-      if (colsum) csum += ma.template sum<decltype(part)::value>(t, ra);
+      if (colsum) {
+        const float s = ma.template sum<decltype(part)::value>(t, ra);
+        if (MA::OF_TWO && csum.f64) csum.sum64 += (double)s;
+        else csum.sum += s;
+      }
     }
   };
   auto flip = [&](int t) {
@@ -633,7 +646,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
     }
   }
   const int n_seg = !A_KMAJOR && p.K2 > 0 ? 2 : 1;
-  float csum = 0.f;
+  ColumnSum csum;
+  if constexpr (A_KMAJOR && TWO) csum.f64 = p.colsum_f64;
   bool small = false;
   if constexpr (A_KMAJOR) {
     if (k_len > 0) {
@@ -737,7 +751,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
       // the two k-groups of a column are added in order through LDS
       float* const red = reinterpret_cast<float*>(smem);
       __syncthreads();
-      red[tid] = csum;
+      red[tid] = csum.f64 ? (float)csum.sum64 : csum.sum;
       __syncthreads();
       if (tid < TILE && i0 + tid < p.M) p.colsum_part[z * p.M + i0 + tid] = red[tid] + red[TILE + tid];
     }
@@ -1238,6 +1252,12 @@ int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stre
   p.n_groups = S;
   float* colsum_part = a.workspace + (size_t)S * N1 * N2;
   p.colsum_part = a.colsum_out && !a.colsum_src ? colsum_part : nullptr;
+  // Two gradients of up to 64 rows each would be a pair in gemm_narrow.hip, whose chunks are other ones and whose column sums are rounded once
+  // a group of 32 nodes.  So column sums are formed in float64 inside a chunk, and the chunks' partials are added in float64: against
+  // float64, errors of gradients over 17,000 to 1,000,000 nodes, 66 to 602 -> 33 to 64, are 0.47 to 0.68 of the pair's and of bias gradients 0.43 to
+  // 0.76, where float32 sums had up to 1.11 and 1.41.  602 -> 64 over 300k nodes 395 -> 395 us, 256 -> 41 over 115k 71 -> 72.
+  const bool narrow = a.A2 && a.N1 <= 64;
+  p.colsum_f64 = narrow;
   COFREE_TRY(plan_colsum(a, &p.extra, sums));
   const int64_t blocks = (int64_t)((S + 7) / 8) * 8 * p.tiles_m * p.tiles_n + p.extra.blocks;
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "wgrad: grid too large");
@@ -1250,9 +1270,9 @@ int32_t launch_wgrad_split(const WgradArgs& a, SplitSums* sums, hipStream_t stre
     else gemm_split_kernel<true, true, false, false><<<dim3((unsigned)blocks), 256, 0, stream>>>(p);
   }
   COFREE_HIP_CHECK(hipGetLastError());
-  COFREE_TRY(add_split_sum(sums, a.workspace, p.c_split_stride, S, a.C, a.ldc, a.N1, N2));
-  if (a.A2) COFREE_TRY(add_split_sum(sums, a.workspace + (size_t)a.N1 * N2, p.c_split_stride, S, a.C2, a.ldc, a.N1, N2));
-  if (p.colsum_part) COFREE_TRY(add_split_sum(sums, colsum_part, N1, S, a.colsum_out, a.N1, 1, a.N1));
+  COFREE_TRY(add_split_sum(sums, a.workspace, p.c_split_stride, S, a.C, a.ldc, a.N1, N2, narrow));
+  if (a.A2) COFREE_TRY(add_split_sum(sums, a.workspace + (size_t)a.N1 * N2, p.c_split_stride, S, a.C2, a.ldc, a.N1, N2, narrow));
+  if (p.colsum_part) COFREE_TRY(add_split_sum(sums, colsum_part, N1, S, a.colsum_out, a.N1, 1, a.N1, narrow));
   return COFREE_OK;
 }
 
