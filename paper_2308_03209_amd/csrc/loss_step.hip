@@ -118,8 +118,9 @@ __device__ inline void st_n(bf16_t* p, int avail, const float (&v)[8]) {
 }
 
 constexpr int LOSS_BLOCKS = 2048;  // workgroups, and partial sums, at most
-// of loss_group_kernel: five a CU are resident (94 VGPRs), and a sixth would run behind them (2.4M x 172 bfloat16: 1,280
-// workgroups 378 us, 1,536 457, 2,048 395)
+// of loss_group_kernel: five a CU are resident in every bfloat16 instance of rows of several pieces (83 to 94 VGPRs), and a sixth would
+// run behind them (2.4M x 172: 1,280 workgroups 378 us, 1,536 457, 2,048 395).  Float32 instances (38 to 75) would hold six and
+// more, which was not measured.
 constexpr int GROUP_BLOCKS = 5 * 256;
 
 // Partial sums of cofree_loss_weighted_static: device memory that exists from the moment the library is loaded
