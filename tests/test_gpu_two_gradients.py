@@ -1,5 +1,5 @@
-"""Both weight gradients of a conventional GraphSAGE layer that transforms first, of dPre and mean^T(dPre), in one launch: against
-float64, at widths where the second gradient begins inside a tile or a piece of eight columns, with a ragged number of nodes."""
+"""Both weight gradients of a conventional GraphSAGE layer that transforms first, of dPre and mean^T(dPre), in one launch:
+exact where sums are, at widths where the second gradient begins inside a tile or a piece of eight columns, with a ragged number of nodes."""
 import numpy as np
 import pytest
 
@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
                                               ("bf16", 300, 128), ("bf16", 300, 129)])
 @pytest.mark.parametrize("n", [33, 2_005, 40_011])
 @pytest.mark.parametrize("accumulate", [False, True])
-def test_against_float64(dtype, d_in, d_out, n, accumulate):
+def test_exact_sums(dtype, d_in, d_out, n, accumulate):
     import torch
     from paper_2308_03209_amd import binding as B
     print(f"[case] two gradients {dtype} n={n} {d_in} -> {d_out}", flush=True)
@@ -19,7 +19,8 @@ def test_against_float64(dtype, d_in, d_out, n, accumulate):
     P = B.build_partition(n, src, (src + 1) % n, 1, 0, 3)
     gen = torch.Generator(device="cuda").manual_seed(d_in + n)
     td = torch.float32 if dtype == "f32" else torch.bfloat16
-    # multiples of 1/4: the mean of two neighbours is exact in bfloat16 too, and so are products; sums of n of them are not
+    # multiples of 1/4: the mean of two neighbours is exact in bfloat16 too, products are multiples of 1/32 of at most 4, and n of them
+    # stay below 2^24 / 32: every partial sum is exact, in any order
     H = (torch.randint(-8, 9, (n, d_in), generator=gen, device="cuda") * 0.25).to(td)
     dO = (torch.randint(-8, 9, (n, d_out), generator=gen, device="cuda") * 0.25).to(td)
     W = torch.zeros(d_out, 2 * d_in, device="cuda")
@@ -32,10 +33,9 @@ def test_against_float64(dtype, d_in, d_out, n, accumulate):
     h, z = H.double(), dO.double()
     t = 0.5 * (z.roll(1, 0) + z.roll(-1, 0))
     ref = torch.cat([z.T @ h, t.T @ h], 1)
-    mag = torch.cat([z.abs().T @ h.abs(), t.abs().T @ h.abs()], 1)
     base = 1.0 if accumulate else 0.0
-    assert bool(((g["W"].double() - base - ref).abs() <= (n + 8.0) * 2.0 ** -24 * (mag + base)).all())
-    assert bool(((g["bW"].double() - base - z.sum(0)).abs() <= (n + 8.0) * 2.0 ** -24 * (z.abs().sum(0) + base)).all())
+    assert torch.equal(g["W"].double(), base + ref)
+    assert torch.equal(g["bW"].double(), base + z.sum(0))
 
 
 @pytest.mark.parametrize("dtype,n,d_in,d_out", [("f32", 5_003, 200, 100), ("f32", 40_011, 129, 47), ("bf16", 5_003, 100, 47)])
