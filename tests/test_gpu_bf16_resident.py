@@ -62,6 +62,43 @@ def test_many_rows(G, n, d_in, d_out):  # noqa: F811
                                        ("sage", (64, 70, 48)), ("sage_conv", (130, 8, 24)), ("sage_conv", (20, 8, 50))])
 def test_narrow_products_of_few_rows(G, kind, dims, monkeypatch):  # noqa: F811
     """Tiles of 64 columns, which read few rows' parameters as they are: edges of columns, steps of 64 k and of eight, both segments.
-    (Not a single column: its one bias gradient is a sum that cancels, 2.7 % off with the converted copy and without, whose bits agree.)"""
+    (A single column: below.)"""
     monkeypatch.setenv("COFREE_BF16_TILE", "128")
     check_single_layer_bf16(G, kind, dims)
+
+
+@pytest.mark.parametrize("n", [1, 130, 2_003])
+@pytest.mark.parametrize("d_in", [9, 64, 130])
+def test_a_single_column(n, d_in, monkeypatch):
+    """Every column of the tile but one is the last one again.  Its bias gradient may cancel: judged by the size of its terms."""
+    import torch
+    from paper_2308_03209_amd import binding as B
+    monkeypatch.delenv("COFREE_BF16_TILE")
+    print(f"[case] a single column n={n} d_in={d_in}", flush=True)
+    src = np.arange(max(n, 3), dtype=np.int64)
+    n = len(src)
+    P = B.build_partition(n, src, (src + 1) % n, 1, 0, 3)
+    gen = torch.Generator(device="cuda").manual_seed(d_in + n)
+    H, dO = torch.randn(n, d_in, generator=gen, device="cuda").bfloat16(), torch.randn(n, 1, generator=gen, device="cuda").bfloat16()
+    p = {"W": torch.randn(1, d_in, generator=gen, device="cuda"), "bW": torch.randn(1, generator=gen, device="cuda")}
+    d = B.layer_desc(B.GCN, d_in, 0, 1, dtype=B.BF16)
+    ws = torch.empty(max(B.layer_workspace_bytes(d, n, x) for x in (False, True)), dtype=torch.uint8, device="cuda")
+    Y, dH = torch.full_like(dO, float("nan")), torch.full_like(H, float("nan"))
+    g = {k: torch.full_like(v, float("nan")) for k, v in p.items()}
+    B.profile_enable(True)
+    B.layer_fwd(P, None, 0, d, H, p, Y, {}, ws)
+    B.layer_bwd(P, None, 0, d, H, Y, p, {}, dO, dH, g, False, ws)
+    names = list(B.profile_read())
+    B.profile_enable(False)
+    assert any(x.startswith("gemm_bf16_kernel<false,false,true,2,2,1> N=1 ") for x in names), names
+
+    def ahat(x):  # every node has degree two
+        return (x.roll(1, 0) + x.roll(-1, 0) + x) / 3
+    h, w, z = H.double(), p["W"].double(), dO.double()
+    t = ahat(z)
+    # parameters, the stored intermediate and the result are rounded, each by at most 2^-8 of its value (eight significant bits)
+    for got, ref, mag, what in ((Y, ahat(h @ w.T) + p["bW"].double(), ahat(h.abs() @ w.abs().T) + p["bW"].double().abs(), "H_out"),
+                                (dH, t @ w, ahat(z.abs()) @ w.abs(), "dH_in"),
+                                (g["W"], t.T @ h, ahat(z.abs()).T @ h.abs(), "dW"),
+                                (g["bW"], z.sum(0), z.abs().sum(0), "dbW")):
+        assert bool(((got.double() - ref).abs() <= 3.05 * 2.0 ** -8 * mag).all()), what

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 # widths and the kernel that ends the layer (f32 / bf16)
 SHAPES = [("sage_conv", 72, 132),   # aggregate first: split / resident product, ragged column block
-          ("sage_conv", 256, 128),  # transform first: accumulating split product / a launch of its own
+          ("sage_conv", 256, 128),  # transform first: the aggregation, which adds the self part / a launch of its own
           ("sage_conv", 40, 94),    # no multiple of four columns: a launch of its own
           ("gcn", 256, 512),        # widest split tiles / column parts of the resident product
           ("gcn", 72, 300),         # column parts that are no multiple of four columns where there are three
