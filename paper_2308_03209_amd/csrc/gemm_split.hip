@@ -24,8 +24,11 @@
 // What bounds it: a 32x32x16 bfloat16 matrix instruction takes 32 cycles, eight 32x32x2 float32 ones 512, so six of
 // the former could be 2.7 times as fast; but a loop of nothing but matrix instructions on random data already lowers
 // the shader clock from 2.4 to 1.7 GHz (1,760 TFLOP/s in bfloat16, 1,500 with the vector instructions of a split in
-// between): power, not issue slots, is the limit.  Here it runs at 1.8 GHz with the matrix units busy 59 % of the time (55 %
-// in weight gradients); the rest is mostly the first steps and the end of a tile.  In TFLOP/s of the product, float32
+// between): for such a loop power, not issue slots, is the limit.  Here matrix units are busy 58 % of the cycles at 1.77 GHz in A B^T, 56 % at
+// 1.86 in weight gradients, 47 % at 1.91 in gated A B (512 x 512 over 1.87M rows): the clock is lowered, but matrix instructions take 1.03,
+// 1.04 and 0.90 of its 1.7 GHz, so something else is waited for too, most of all in A B.  Candidates, not measured apart: the first
+// steps and the end of a tile (A B asks for its gates there), 12 LDS reads for 24 matrix instructions, and the left operand's
+// split, which every column tile repeats.  In TFLOP/s of the product, float32
 // instructions / the steps read from LDS behind each barrier / now: 470k x 512 x 512 127 / 169 / 189 (A B^T), 529k x 512 x 1024
 // 134 / 187 / 200, 230k x 256 x 602 118 / 131 / 152; weight gradients 512 x 512 over 470k nodes - / 165 / 186.
 //
