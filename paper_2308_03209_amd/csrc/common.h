@@ -320,7 +320,7 @@ struct AggArgs {
   const void* relu_src = nullptr;    // if set: Y[v,c] = 0 where relu_src[v,c] <= 0 (same dtype, ld = ld_relu)
   int64_t ld_relu = 0;
   float gate_scale = 1.f;            // factor on the elements that pass relu_src
-  const void* add = nullptr;         // added to Y (same dtype, ld = ld_add); not together with relu_src
+  const void* add = nullptr;         // added to Y (float32, ld = ld_add); not together with relu_src
   int64_t ld_add = 0;
   // applied after out_scale, in this order: + bias[c] (first to add[v,c], which is then added), ReLU
   const float* bias = nullptr;
