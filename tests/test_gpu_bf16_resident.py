@@ -62,7 +62,7 @@ def test_many_rows(G, n, d_in, d_out):  # noqa: F811
                                        ("sage", (64, 70, 48)), ("sage_conv", (130, 8, 24)), ("sage_conv", (20, 8, 50))])
 def test_narrow_products_of_few_rows(G, kind, dims, monkeypatch):  # noqa: F811
     """Tiles of 64 columns, which read few rows' parameters as they are: edges of columns, steps of 64 k and of eight, both segments.
-    (A single column: below.)"""
+    (Not a single column: its one bias gradient is a sum that cancels, 2.7 % off with the converted copy and without, whose bits agree.)"""
     monkeypatch.setenv("COFREE_BF16_TILE", "128")
     check_single_layer_bf16(G, kind, dims)
 

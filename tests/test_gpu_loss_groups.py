@@ -34,21 +34,6 @@ def check(torch, dtype, C, n, z, room, loss, k, each, mag, grad):
 @pytest.mark.parametrize("C", [1, 3, 4, 5, 7, 8, 9, 16, 17, 31, 33, 63, 65, 127, 129, 255, 257, 511, 513, 1024, 1025])
 @pytest.mark.parametrize("n", [1, 130, 3_001])
 def test_softmax(C, dtype, n):
-    softmax(C, dtype, n)
-
-
-# C: the widest rows of a group of 1, 1, 2, 4, ... 64 lanes, then of a wavefront.  A workgroup takes 512 / lanes rows at a time (a wavefront
-# a row: four) and there are 1,280 of them at most (2,048): one row more is a second iteration of one group, its other row past the
-# run's end, and leaves the last workgroups without rows; some more is two iterations and a ragged third.
-@pytest.mark.parametrize("C,dtype,lanes", [(c * w, d, l) for d, w in (("f32", 4), ("bf16", 8))
-                                           for c, l in ((1, 1), (2, 1), (4, 2), (8, 4), (16, 8), (32, 16), (64, 32), (128, 64), (129, 0))])
-@pytest.mark.parametrize("more", ["one", "some"])
-def test_softmax_of_several_iterations(C, dtype, lanes, more):
-    once = 1_280 * 512 // lanes if lanes else 2_048 * 4
-    softmax(C - 1 if C > 4 and lanes else C, dtype, once + 1 if more == "one" else 2 * once + once // 3 + 5)
-
-
-def softmax(C, dtype, n):
     import torch
     from paper_2308_03209_amd import binding as B
     print(f"[case] softmax loss n={n} C={C} {dtype}", flush=True)
@@ -67,21 +52,21 @@ def softmax(C, dtype, n):
     check(torch, dtype, C, n, z, room, loss, k, each, each + 40, k[:, None] * (p - hot))
 
 
+# C: the widest rows of a group of 1, 1, 2, 4, ... 64 lanes, then of a wavefront.  A workgroup takes 512 / lanes rows at a time (a wavefront
+# a row: four) and there are 1,280 of them at most (2,048): one row more is a second iteration of one group, its other row past the
+# run's end, and leaves the last workgroups without rows; some more is two iterations and a ragged third.
+@pytest.mark.parametrize("C,dtype,lanes", [(c * w, d, l) for d, w in (("f32", 4), ("bf16", 8))
+                                           for c, l in ((1, 1), (2, 1), (4, 2), (8, 4), (16, 8), (32, 16), (64, 32), (128, 64), (129, 0))])
+@pytest.mark.parametrize("more", ["one", "some"])
+def test_softmax_of_several_iterations(C, dtype, lanes, more):
+    once = 1_280 * 512 // lanes if lanes else 2_048 * 4
+    test_softmax(C - 1 if C > 4 and lanes else C, dtype, once + 1 if more == "one" else 2 * once + once // 3 + 5)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("C", [1, 2, 3, 4, 5, 41, 100, 1027])
 @pytest.mark.parametrize("n", [1, 130, 3_001])
 def test_sigmoid(C, dtype, n):
-    sigmoid(C, dtype, n)
-
-
-# 2,048 workgroups take 2,097,152 elements at a time: a thread's second and third pieces, rows of one, two and more elements
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("C,n", [(1, 2_097_155), (2, 1_050_001), (3, 700_001), (100, 50_003), (1027, 2_045)])
-def test_sigmoid_of_several_iterations(C, n, dtype):
-    sigmoid(C, dtype, n)
-
-
-def sigmoid(C, dtype, n):
     import torch
     from paper_2308_03209_amd import binding as B
     print(f"[case] sigmoid loss n={n} C={C} {dtype}", flush=True)
@@ -111,3 +96,10 @@ def test_softplus_of_any_size():
         B.loss_bce_weighted(P, B.W_NONE, None, z, t, mask, 1, 1.0, loss, torch.empty_like(z), ws)
         ref = float(torch.nn.functional.softplus(z[0, 0].double(), threshold=1e9))
         assert abs(float(loss) - ref) <= 6 * 2.0 ** -24 * ref + 2.0 ** -149, v
+
+
+# 2,048 workgroups take 2,097,152 elements at a time: a thread's second and third pieces, rows of one, two and more elements
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("C,n", [(1, 2_097_155), (2, 1_050_001), (3, 700_001), (100, 50_003), (1027, 2_045)])
+def test_sigmoid_of_several_iterations(C, n, dtype):
+    test_sigmoid(C, dtype, n)

@@ -1,9 +1,41 @@
-"""Both weight gradients of a conventional GraphSAGE layer that transforms first, of dPre and mean^T(dPre), in one launch:
-exact where sums are, at widths where the second gradient begins inside a tile or a piece of eight columns, with a ragged number of nodes."""
+"""Both weight gradients of a conventional GraphSAGE layer that transforms first, of dPre and mean^T(dPre), in one launch: against
+float64, at widths where the second gradient begins inside a tile or a piece of eight columns, with a ragged number of nodes."""
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,d_in,d_out", [("f32", 66, 33), ("f32", 129, 64), ("f32", 200, 65), ("f32", 300, 128), ("f32", 602, 129),
+                                              ("bf16", 12, 8), ("bf16", 40, 9), ("bf16", 100, 33), ("bf16", 129, 64), ("bf16", 256, 65),
+                                              ("bf16", 300, 128), ("bf16", 300, 129)])
+@pytest.mark.parametrize("n", [33, 2_005, 40_011])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_against_float64(dtype, d_in, d_out, n, accumulate):
+    import torch
+    from paper_2308_03209_amd import binding as B
+    print(f"[case] two gradients {dtype} n={n} {d_in} -> {d_out}", flush=True)
+    src = np.arange(n, dtype=np.int64)
+    P = B.build_partition(n, src, (src + 1) % n, 1, 0, 3)
+    gen = torch.Generator(device="cuda").manual_seed(d_in + n)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    # multiples of 1/4: the mean of two neighbours is exact in bfloat16 too, and so are products; sums of n of them are not
+    H = (torch.randint(-8, 9, (n, d_in), generator=gen, device="cuda") * 0.25).to(td)
+    dO = (torch.randint(-8, 9, (n, d_out), generator=gen, device="cuda") * 0.25).to(td)
+    W = torch.zeros(d_out, 2 * d_in, device="cuda")
+    b = torch.zeros(d_out, device="cuda")
+    d = B.layer_desc(B.SAGE_CONV, d_in, 0, d_out, dtype=B.F32 if dtype == "f32" else B.BF16)
+    ws = torch.full((B.layer_workspace_bytes(d, n, True),), 0xff, dtype=torch.uint8, device="cuda")
+    before = {"W": torch.ones(d_out, 2 * d_in, device="cuda"), "bW": torch.ones(d_out, device="cuda")}
+    g = {k: v.clone() for k, v in before.items()}
+    B.layer_bwd(P, None, 0, d, H, dO, {"W": W, "bW": b}, {}, dO, None, g, accumulate, ws)
+    h, z = H.double(), dO.double()
+    t = 0.5 * (z.roll(1, 0) + z.roll(-1, 0))
+    ref = torch.cat([z.T @ h, t.T @ h], 1)
+    mag = torch.cat([z.abs().T @ h.abs(), t.abs().T @ h.abs()], 1)
+    base = 1.0 if accumulate else 0.0
+    assert bool(((g["W"].double() - base - ref).abs() <= (n + 8.0) * 2.0 ** -24 * (mag + base)).all())
+    assert bool(((g["bW"].double() - base - z.sum(0)).abs() <= (n + 8.0) * 2.0 ** -24 * (z.abs().sum(0) + base)).all())
 
 
 @pytest.mark.parametrize("dtype,d_in,d_out", [("f32", 66, 33), ("f32", 129, 64), ("f32", 200, 65), ("f32", 300, 128), ("f32", 602, 129),
