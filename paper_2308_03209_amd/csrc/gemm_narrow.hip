@@ -37,9 +37,6 @@ struct NarrowK {
   const float *A1, *A2, *B1, *B2;
   int64_t lda1, lda2, ldb1, ldb2;
   int32_t K1, K2;  // K2 = 0: one segment
-  const float* B_second;  // second result, of the blocks of columns from `half` on (INT_MAX: none)
-  float* C_second;
-  int32_t half;
   float* C;
   int64_t ldc, M;
   int32_t N;
@@ -54,6 +51,9 @@ struct NarrowK {
   int64_t ldg;
   int32_t accumulate, relu_last, gate_last;
   float gate_scale;
+  const float* B_second;  // TWO: the second result, of the blocks of columns from `half` on
+  float* C_second;
+  int32_t half;
 };
 
 // Steps of 16 k that a wavefront has in flight (DEPTH of the kernel): eight, or about as many as the product has, because a
@@ -83,8 +83,8 @@ struct Step {
 
 // A wavefront computes NB blocks of 16 columns of a tile of 16 rows; several may share a tile (SHARE).  A workgroup keeps
 // all parameters in LDS where they fit and walks the row tiles; where they do not, it walks the parts of k for every round
-// of tiles.
-template <int NB, bool SHARE, bool B_KMAJOR, int DEPTH, bool EXTRAS>
+// of tiles.  TWO: two results (an instance of its own: deciding by block cost every product of few rows 0.5 us, 4 % of a small layer).
+template <int NB, bool SHARE, bool B_KMAJOR, int DEPTH, bool EXTRAS, bool TWO>
 __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   constexpr bool ELEMENTS = DEPTH == 1;
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b0 = wave % col_waves * NB;  // the wavefront's blocks, all of one result
-  const bool second_result = SHARE && b0 >= p.half;
+  const bool second_result = TWO && b0 >= p.half;
   const int own_b0 = second_result ? b0 - p.half : b0;
   float* const C = second_result ? p.C_second : p.C;
   const int row_wave = wave / col_waves, row_waves = (int)(blockDim.x >> 6) / col_waves;
@@ -127,9 +127,9 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
   };
   auto fill = [&](int t0, int t1) {  // parameters of steps t0 .. t1 - 1; a wavefront takes steps of one block of columns
     const int b = wave % nb, every = (int)(blockDim.x >> 6) / nb;
-    const bool of_second = SHARE && b >= p.half;
+    const bool of_second = TWO && b >= p.half;
     const int64_t j = column(of_second ? b - p.half : b, r);
-    const float* const first_B = of_second ? p.B_second : p.B1;
+    const float* const only_B = of_second ? p.B_second : p.B1;  // (two results: of one segment)
     constexpr int BATCH = DEPTH;
     for (int base = t0 + wave / nb; base < t1 && wave < every * nb; base += BATCH * every) {
       float4u v[BATCH];
@@ -137,8 +137,8 @@ __global__ __launch_bounds__(1024) void narrow_gemm_kernel(const NarrowK p) {
       for (int u = 0; u < BATCH; ++u) {
         const int t = base + u * every;
         const Step<ELEMENTS> s(t < t1 ? t : t1 - 1, n1, p.K1, p.K2);
-        const float* const B = s.second ? p.B2 : first_B;
-        const int64_t ldb = s.second ? p.ldb2 : p.ldb1;
+        const float* const B = TWO ? only_B : s.second ? p.B2 : p.B1;
+        const int64_t ldb = !TWO && s.second ? p.ldb2 : p.ldb1;
         if constexpr (!B_KMAJOR && !ELEMENTS) {
           v[u] = *reinterpret_cast<const float4u*>(B + j * ldb + s.first(g));
         } else {
@@ -306,9 +306,9 @@ bool gemm_narrow_fits(const GemmArgs& a) {
   return !(s.nb == 4 && s.cu_tiles >= 14 && s.cu_tiles <= 24 && s.steps >= 8 && s.steps <= 20);
 }
 
-template <int NB, bool SHARE, bool B_KMAJOR, int DEPTH, bool EXTRAS>
+template <int NB, bool SHARE, bool B_KMAJOR, int DEPTH, bool EXTRAS, bool TWO>
 static int32_t launch_narrow(const NarrowK& p, int64_t blocks, int threads, size_t lds, hipStream_t stream) {
-  const auto kernel = narrow_gemm_kernel<NB, SHARE, B_KMAJOR, DEPTH, EXTRAS>;
+  const auto kernel = narrow_gemm_kernel<NB, SHARE, B_KMAJOR, DEPTH, EXTRAS, TWO>;
   if (lds > 64 * 1024)
     COFREE_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                          LDS_BYTES));
@@ -348,7 +348,7 @@ int32_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream) {
   p.C_second = (float*)a.C_second;
   p.tiles = (a.M + 15) / 16;
   const auto [nb, steps, most, cu_tiles] = narrow_shape(a);
-  p.half = a.C_second ? nb / 2 : INT_MAX;
+  p.half = nb / 2;
   const int depth = a.K1 < 4 || (a.K2 > 0 && a.K2 < 4) ? 1 : steps <= 2 ? 2 : steps <= 4 ? 4 : 8;
   p.part_steps = (int32_t)(steps <= most ? steps : most / depth * depth);
   const size_t lds = (size_t)p.part_steps * nb * 1024 + nb * 64;
@@ -369,8 +369,8 @@ int32_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream) {
   const bool extras = a.gate || a.accumulate || a.row_scale || a.relu_last;
   const double K = (double)a.K1 + a.K2, results = a.C_second ? 2.0 : 1.0;
   char pname[96] = "";  // the template instance launched below, then the shape
-  if (profiling()) snprintf(pname, sizeof(pname), "narrow_gemm_kernel<%d,%s,%s,%d,%s> N=%d K=%lld", cols, cols == 1 || p.col_waves > 1 ? "true" : "false", a.b_kmajor ? "true" : "false",
-                            depth, extras ? "true" : "false", (int)a.N, (long long)K);
+  if (profiling()) snprintf(pname, sizeof(pname), "narrow_gemm_kernel<%d,%s,%s,%d,%s,%s> N=%d K=%lld", cols, cols == 1 || p.col_waves > 1 ? "true" : "false", a.b_kmajor ? "true" : "false",
+                            depth, extras ? "true" : "false", a.C_second ? "true" : "false", (int)a.N, (long long)K);
   ProfScope prof(pname, stream, 4.0 * ((double)a.M * K + results * ((double)a.N * K + (double)a.M * a.N * (a.accumulate ? 2 : 1))),
                  2.0 * results * (double)a.M * a.N * K);
   auto by_depth = [&](auto n, auto share, auto kmajor) {
@@ -378,8 +378,12 @@ int32_t launch_gemm_narrow(const GemmArgs& a, hipStream_t stream) {
     constexpr bool SHARE = decltype(share)::value, KMAJOR = decltype(kmajor)::value;
     auto go = [&](auto d) {
       constexpr int DEPTH = decltype(d)::value;
-      return extras ? launch_narrow<NB, SHARE, KMAJOR, DEPTH, true>(p, blocks, 64 * waves, lds, stream)
-                    : launch_narrow<NB, SHARE, KMAJOR, DEPTH, false>(p, blocks, 64 * waves, lds, stream);
+      if constexpr (SHARE && !KMAJOR)
+        if (a.C_second) return launch_narrow<NB, SHARE, KMAJOR, DEPTH, false, true>(p, blocks, 64 * waves, lds, stream);
+      if constexpr (NB == 2 && SHARE && DEPTH < 8) return fail(COFREE_EINVAL, "internal: no narrow product of this shape");
+      else
+        return extras ? launch_narrow<NB, SHARE, KMAJOR, DEPTH, true, false>(p, blocks, 64 * waves, lds, stream)
+                      : launch_narrow<NB, SHARE, KMAJOR, DEPTH, false, false>(p, blocks, 64 * waves, lds, stream);
     };
     if constexpr (NB == 2 && SHARE && KMAJOR) {
       return go(std::integral_constant<int, 8>{});
