@@ -31,17 +31,18 @@ constexpr int WG_WAVES = 8, WG_CUS = 256;
 
 struct WgradK {
   const bf16_t* A;
-  const bf16_t* A2;  // a second matrix like A, or null
   const bf16_t* B;
   const bf16_t* B2;
   int64_t lda, ldb, ldb2;
-  int32_t N1, N1b, N2, N2b;  // columns of the four matrices (N1b, N2b = 0: no second one)
+  int32_t N1, N2, N2b;  // columns of the three matrices (N2b = 0: no second one)
   int64_t M, chunk;
-  float* C;  // partials: [chunks][N1 + N1b][N2 + N2b]
+  float* C;  // partials: [chunks][N1 (two: + N1b)][N2 + N2b]
   int32_t tiles_m, tiles_n;
   int64_t n_chunks;
   float* colsum_part;  // [chunks][N1] partial column sums of A, or null
   ColsumK extra;
+  const bf16_t* A2;  // TWO: a second matrix like A, of N1b columns
+  int32_t N1b;
 };
 
 // Places of operand columns: pieces of eight, the last piece of a matrix moved left to end with its rows (the columns it
@@ -66,8 +67,9 @@ __device__ inline Piece piece_of(int q, int32_t N, int32_t Nb) {
 
 // TM x TN: tile of the result; SN: nodes per step; D: steps in flight; WM x WN: wavefronts over the tile.
 // PARTS: of a thread's column sums - two where two matrices A share a tile of twice the rows that one of them would take, in which a
-// thread has twice the nodes of a column.
-template <int TM, int TN, int SN, int D, int WM, int WN, int PARTS>
+// thread has twice the nodes of a column.  TWO: of two matrices A (instances of their own: looking for the second one in every launch cost
+// 0.3 to 1.5 us: backward of 602 -> 33 over 20k nodes 45.7 -> 47.2, of 1000 -> 24 over 6,000 39.2 -> 40.3).
+template <int TM, int TN, int SN, int D, int WM, int WN, int PARTS, bool TWO>
 __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void wgrad_bf16_kernel(
     const WgradK p) {
   static_assert(WM * WN == WG_WAVES, "eight wavefronts");
@@ -97,6 +99,7 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
   const int64_t z = (L / (8 * per_chunk)) * 8 + (L & 7);
   const int member = (int)((L >> 3) % per_chunk);
   if (z >= p.n_chunks) return;  // padding of the last octet (uniform over the block)
+  const int32_t N1b = TWO ? p.N1b : 0;
   const int qm = (member / p.tiles_n) * QA, qn = (member % p.tiles_n) * QB;  // first pieces of the tile
   const int64_t k_beg = z * p.chunk;
   const int64_t k_end = k_beg + p.chunk < p.M ? k_beg + p.chunk : p.M;
@@ -115,9 +118,9 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
   // thread t moves piece t % Q of rows t / Q + (T / Q) j of a step; rows past the chunk repeat its last one (and become
   // zero on the way to LDS)
   const int ra = tid / QA, rb = tid / QB;
-  const Piece xa = piece_of(qm + tid % QA, p.N1, p.N1b), xb = piece_of(qn + tid % QB, p.N2, p.N2b);
+  const Piece xa = piece_of(qm + tid % QA, p.N1, N1b), xb = piece_of(qn + tid % QB, p.N2, p.N2b);
   const int64_t ldb = xb.second ? p.ldb2 : p.ldb;
-  const bf16_t* const pa = (xa.second ? p.A2 : p.A) + k_beg * p.lda + xa.col;
+  const bf16_t* const pa = (TWO && xa.second ? p.A2 : p.A) + k_beg * p.lda + xa.col;
   const bf16_t* const pb = (xb.second ? p.B2 : p.B) + k_beg * ldb + xb.col;
   struct Raw {
     u32x4u a[JA], b[JB];
@@ -214,7 +217,7 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
   // accumulator register v of lane (g, r) is element [8 (v / 4) + 4 g + v % 4][r] of its 32 x 32 block
   const int g = lane >> 5, r = lane & 31;
   const int64_t ldc = (int64_t)p.N2 + p.N2b;
-  float* const Cz = p.C + z * (p.N1 + p.N1b) * ldc;
+  float* const Cz = p.C + z * (p.N1 + N1b) * ldc;
 #pragma unroll
   for (int q = 0; q < RN; ++q) {
     const int place = (wn * RN + q) * 32 + r;
@@ -225,8 +228,8 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
     for (int m = 0; m < RM; ++m)
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
-        const Piece xr = piece_of(qm + (wm * RM + m) * 4 + h, p.N1, p.N1b);
-        const int32_t row = (xr.second ? p.N1 : 0) + xr.col + 4 * g;
+        const Piece xr = piece_of(qm + (wm * RM + m) * 4 + h, p.N1, N1b);
+        const int32_t row = (TWO && xr.second ? p.N1 : 0) + xr.col + 4 * g;
 #pragma unroll
         for (int v = 0; v < 4; ++v)
           if (xr.exists && 4 * g + v >= xr.first) Cz[(int64_t)(row + v) * ldc + j] = acc[m][q][4 * h + v];
@@ -244,8 +247,8 @@ __global__ __launch_bounds__(64 * WG_WAVES) __attribute__((amdgpu_waves_per_eu(2
     if (tid < TM) {
       float t = 0.f;
       for (int h = 0; h < PARTS * (T / QA); ++h) t += red[h * TM + tid];
-      const Piece xr = piece_of(qm + (tid >> 3), p.N1, p.N1b);
-      if (xr.exists && !xr.second && (tid & 7) >= xr.first) p.colsum_part[z * p.N1 + xr.col + (tid & 7)] = t;
+      const Piece xr = piece_of(qm + (tid >> 3), p.N1, N1b);
+      if (xr.exists && !(TWO && xr.second) && (tid & 7) >= xr.first) p.colsum_part[z * p.N1 + xr.col + (tid & 7)] = t;
     }
   }
 }
@@ -297,15 +300,15 @@ size_t wgrad_bf16_workspace_floats(int32_t N1, int32_t N2, int32_t N2b, int64_t 
   return (size_t)wgrad_chunks(t.m * t.n, M) * ((size_t)N1 * ((size_t)N2 + N2b) + (size_t)N1);
 }
 
-template <int PARTS>
+template <int PARTS, bool TWO>
 static void launch_tile(int32_t th, int32_t tw, unsigned blocks, const WgradK& p, hipStream_t stream) {
   const dim3 grid(blocks);
-  if (tw == 256 && th == 256) wgrad_bf16_kernel<256, 256, 32, 3, 2, 4, PARTS><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
-  else if (tw == 256 && th == 128) wgrad_bf16_kernel<128, 256, 32, 4, 2, 4, PARTS><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
-  else if (th == 256) wgrad_bf16_kernel<256, 128, 32, 4, 4, 2, PARTS><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
-  else if (th == 128) wgrad_bf16_kernel<128, 128, 32, 6, 2, 4, PARTS><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
-  else if (tw == 256) wgrad_bf16_kernel<64, 256, 64, 2, 1, 8, 1><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
-  else wgrad_bf16_kernel<64, 128, 64, 4, 2, 4, 1><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
+  if (tw == 256 && th == 256) wgrad_bf16_kernel<256, 256, 32, 3, 2, 4, PARTS, TWO><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
+  else if (tw == 256 && th == 128) wgrad_bf16_kernel<128, 256, 32, 4, 2, 4, PARTS, TWO><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
+  else if (th == 256) wgrad_bf16_kernel<256, 128, 32, 4, 4, 2, PARTS, TWO><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
+  else if (th == 128) wgrad_bf16_kernel<128, 128, 32, 6, 2, 4, PARTS, TWO><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
+  else if (tw == 256) wgrad_bf16_kernel<64, 256, 64, 2, 1, 8, 1, TWO><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
+  else wgrad_bf16_kernel<64, 128, 64, 4, 2, 4, 1, TWO><<<grid, 64 * WG_WAVES, 0, stream>>>(p);
 }
 
 int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t stream) {
@@ -347,11 +350,12 @@ int32_t launch_wgrad_bf16_rows(const WgradArgs& a, SplitSums* sums, hipStream_t 
     char pname[96] = "";
     const char* rest = tw == 256 ? (th == 256 ? "32,3,2,4" : (th == 128 ? "32,4,2,4" : "64,2,1,8"))
                                  : (th == 256 ? "32,4,4,2" : (th == 128 ? "32,6,2,4" : "64,4,2,4"));
-    if (profiling()) snprintf(pname, sizeof(pname), "wgrad_bf16_kernel<%d,%d,%s,%d> N=%dx%d", (int)th, (int)tw, rest, apart ? 2 : 1, (int)N1, (int)N2);
+    if (profiling()) snprintf(pname, sizeof(pname), "wgrad_bf16_kernel<%d,%d,%s,%d,%s> N=%dx%d", (int)th, (int)tw, rest, apart ? 2 : 1, a.A2 ? "true" : "false", (int)N1, (int)N2);
     ProfScope prof(pname, stream, 2.0 * ((double)a.M * N1 * (p.extra.X ? 2 : 1) + (double)a.M * N2) + 4.0 * (double)N1 * N2,
                    2.0 * (double)a.M * N1 * N2);
-    if (apart) launch_tile<2>(th, tw, (unsigned)blocks, p, stream);
-    else launch_tile<1>(th, tw, (unsigned)blocks, p, stream);
+    if (apart) launch_tile<2, true>(th, tw, (unsigned)blocks, p, stream);
+    else if (a.A2) launch_tile<1, true>(th, tw, (unsigned)blocks, p, stream);
+    else launch_tile<1, false>(th, tw, (unsigned)blocks, p, stream);
   }
   COFREE_HIP_CHECK(hipGetLastError());
   COFREE_TRY(add_split_sum(sums, a.workspace, (int64_t)N1 * N2, S, a.C, a.ldc, a.N1, N2));
