@@ -774,7 +774,10 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
   // it: 2,000 rows, GCN 128 -> 24 forward 11.5 / 9.7, printed GraphSAGE of 24 columns 16.6 / 14.5 forward, 32.4 / 28.6 backward; 30k rows
   // 14.5 / 12.7, 19.5 / 17.3, 36.2 / 32.7; 100k 29.0 / 27.5, 33.6 / 34.0, 56.9 / 54.9; 500k 94 / 94, 100 / 109, 151 / 158).  In the tiles of 128
   // columns that was no faster (500 -> 500 over 30k 57 / 63).
-  const bool as_is = narrow && a.M < 1 << 16 && (a.ldb | a.ldb2) < 1 << 22;  // (32-bit offsets)
+  // Nor where every CU has several workgroups that each convert more than 512 k for themselves (602 -> 128 over 20k rows 28.7 us as they are,
+  // 27.9 converted, 1000 -> 96 31.7 / 30.5, 602 -> 64 over 60k 37.5 / 36.6; but over 20k, 157 workgroups, 19.8 / 20.4).
+  const int64_t tiles_64 = (a.M + HBM - 1) / HBM * ((a.N + 63) / 64);
+  const bool as_is = narrow && a.M < 1 << 16 && (K <= 512 || tiles_64 <= 256) && (a.ldb | a.ldb2) < 1 << 22;  // (32-bit offsets)
   const int64_t ldd = pad8(K);
   bf16_t* const Wb = (bf16_t*)a.param_scratch;
   if (pinned || !as_is) COFREE_TRY(convert_params(a, Wb, ldd, stream));

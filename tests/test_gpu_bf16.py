@@ -415,3 +415,15 @@ def test_tiles_of_64_columns_give_the_same_bits(kind, d_in, d_out, q, n, monkeyp
         assert bool((Y[n] == 7.0).all()) and bool((dX[n] == 7.0).all())
         out.append((Y, dX, *grads.values()))
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+# more than 512 k over more workgroups than CUs: 157 panels of rows, two tiles of columns and more
+@pytest.mark.parametrize("kind,d_in,d_out", [("gcn", 602, 96), ("gcn", 96, 514), ("sage", 513, 129), ("sage_conv", 520, 70)])
+def test_tiles_of_64_columns_of_long_products(kind, d_in, d_out, monkeypatch):
+    """They read the copy of their parameters, which a launch of its own converts."""
+    from paper_2308_03209_amd import binding as B
+    B.profile_enable(True)
+    test_tiles_of_64_columns_give_the_same_bits(kind, d_in, d_out, 0.0, 20_001, monkeypatch)
+    names = list(B.profile_read())
+    B.profile_enable(False)
+    assert any(x.startswith("gemm_bf16_kernel<false,false,true,2,2,0> ") for x in names), names
