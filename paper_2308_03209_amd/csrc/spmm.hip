@@ -1136,7 +1136,11 @@ static int32_t launch_typed(const AggArgs& a, hipStream_t stream) {
 }
 
 // contiguous rows of at least one wide access in every launch (1028 bfloat16 columns leave four to the second)
+// Narrow rows of a width that is no multiple of four over many nodes: their lanes, with windows that overlap and a draw more
+// each, take longer than a launch that draws once an element (GCN forward, q = 0.3, there / here: bfloat16 10 columns over 400k nodes 99 / 117 us, 18
+// over 100k 38 / 42, 23 over 400k 0.99; float32 5 over 400k 76 / 81, 9 0.97; over 20k nodes 0.94 and 0.96).
 bool aggregate_drops(const AggArgs& a) {
+  if (a.width % 4 != 0 && a.g.n >= 1 << 16 && a.width < (a.dtype == COFREE_F32 ? 8 : 23)) return false;
   const int wide = a.dtype == COFREE_F32 ? RowIO<float>::WIDE : RowIO<bf16_t>::WIDE;
   const int last = a.width % (ROW_PIECES * wide);
   return a.width >= wide && a.ldy == a.width && (last == 0 || last >= wide);

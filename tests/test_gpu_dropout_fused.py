@@ -66,3 +66,33 @@ def test_against_keep_decisions(G, kind, d_in, d_out, dtype, products, monkeypat
         np.testing.assert_allclose(out[1], want, rtol=2e-7, atol=0)
     else:  # the plain run rounds once more, by 2^-9 of its value
         np.testing.assert_allclose(out[1], want, rtol=2.0 ** -7, atol=0)
+
+
+@pytest.mark.parametrize("dtype,width", [("f32", 5), ("f32", 7), ("bf16", 9), ("bf16", 22)])
+@pytest.mark.parametrize("n", [65_535, 65_536])
+def test_narrow_rows_over_many_nodes(dtype, width, n):
+    """A launch of its own from 65,536 nodes on, the aggregation's before."""
+    import torch
+    from paper_2308_03209_amd import binding as B
+    print(f"[case] dropout of narrow rows {dtype} {n} x {width}", flush=True)
+    src = np.arange(n, dtype=np.int64)
+    P = B.build_partition(n, src, (src + 1) % n, 1, 0, 3)
+    td, code = (torch.float32, B.F32) if dtype == "f32" else (torch.bfloat16, B.BF16)
+    gen = torch.Generator(device="cuda").manual_seed(width)
+    H = torch.randn(n, width + 7, generator=gen, device="cuda").to(td)
+    p = {"W": torch.randn(width, width + 7, generator=gen, device="cuda"), "bW": torch.randn(width, generator=gen, device="cuda")}
+    q, out = 0.3, []
+    for rate in (0.0, q):
+        d = B.layer_desc(B.GCN, width + 7, 0, width, act=1, dropout_q=rate, layer_id=3, seed=2 ** 40 + 9, epoch=6, dtype=code)
+        Y = torch.full((n, width), float("nan"), dtype=td, device="cuda")
+        B.profile_enable(True)
+        B.layer_fwd(P, None, 0, d, H, p, Y, {}, torch.empty(B.layer_workspace_bytes(d, n, False), dtype=torch.uint8, device="cuda"))
+        names = list(B.profile_read())
+        B.profile_enable(False)
+        assert any(x.startswith("mask_grad") for x in names) == (rate > 0 and n >= 65_536), names
+        out.append(Y.float().cpu().numpy())
+    keep = dropout_keep(n, width, q, 2 ** 40 + 9, 6, 3)
+    want = np.where(keep, out[0] * np.float32(1.0 / (1.0 - np.float32(q))), np.float32(0.0))
+    assert np.all(out[1][~keep] == 0.0)
+    # float32: one more product; bfloat16: both runs round once, by at most 2^-8
+    np.testing.assert_allclose(out[1], want, rtol=2e-7 if dtype == "f32" else 2.0 ** -7, atol=0)
