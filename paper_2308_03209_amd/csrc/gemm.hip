@@ -747,13 +747,15 @@ size_t wgrad_workspace_floats(int32_t N1, int32_t first, int64_t M, int32_t N2b)
 // GraphSAGE layer without input gradient, us, two launches (float32 of up to 64 rows: a pair in one, gemm_narrow.hip) / one: bfloat16 300k
 // nodes 602 -> 64 221 / 155, 60k 256 -> 41 38 / 30, 2,000 nodes 64 -> 16 14.9 / 12.3; float32 300k nodes 602 -> 64 528 / 401, 256 -> 100 391
 // / 358, 20k nodes 500 -> 33 45 / 37, 300 -> 128 62 / 60, 2,000 nodes 256 -> 100 30 / 21; but of up to 64 rows over few nodes the
-// pair: 2,000 nodes 602 -> 47 18 / 22, 20k 128 -> 47 26 / 30 (256 -> 41 34 / 30, 60k 128 -> 47 51 / 42).
+// pair: 2,000 nodes 602 -> 47 18 / 22, 20k 128 -> 47 26 / 30 (256 -> 41 34 / 30, 60k 128 -> 47 51 / 42), and of up
+// to 48 rows with three tiles of columns over many: 300 -> 33 60k nodes 119 / 126, 300 -> 41 250k 456 / 478 (256 -> 41 250k 0.96 of the pair, 436 -> 41 0.93).
 // The nodes are cut into as many chunks as for one gradient, so no sum is longer than in a launch of its own: with chunks for the tiles of
 // both (256 x 602 over 115,000 nodes 752 nodes a chunk for 564, 128 x 300 over 300,000 1,765 for 880) float32 gradients were 1.2 to 1.4 times as
 // far from float64.  It costs float32 602 -> 256 over 115k nodes 529 -> 551 us, 256 -> 100 over 60k 68 -> 76, bfloat16 256 -> 100 over 300k 103 -> 109.
 bool wgrad_two_fits(int32_t dtype, int32_t N1, int32_t N2, int64_t M) {
   if (dtype == COFREE_BF16) return wgrad_bf16_fits(N1, N2, 0) && N1 <= 128;
   if (N1 <= 32 || N2 <= 64 || N1 >= (1 << 21) || N2 >= (1 << 21)) return false;
+  if (N1 <= 48 && N2 > 256 && N2 <= 384 && M >= 50000) return false;
   return N1 > 64 || M >= 40000 || (M >= 16384 && N2 >= 256);
 }
 
