@@ -1134,7 +1134,11 @@ static bool split_params_first(const GemmArgs& a) {
 // Results of at most 64 tiles of 128x128 are computed in tiles of a quarter of that: the line is where those are one for each CU.
 // Microseconds, large tiles / small ones: 4 tiles (500 x 128 x 512) 24.7 / 19.9, 16 (2k x 66 x 500) 26.5 / 20.0, 40 (5k x 128 x 512)
 // 24.0 / 20.4, 64 (2k x 512 x 512) 25.1 / 20.9; above, 79 (10k x 128 x 512) 24.1 / 24.2, 158 (10k x 256 x 256) 16.2 / 19.3.
-static bool few_tiles(int64_t large_tiles) { return large_tiles <= 64; }
+// But not A B of up to three steps and more than 80 columns, where nothing but the ends of a tile is left (backward of 128 -> 8 over 4,000 nodes
+// 22.4 / 23.5, 256 -> 32 25.6 / 26.4, 200 -> 48 28.2 / 29.1; 66 -> 8 over 2,000 0.93 of the time in small ones, A B^T of 8 k 0.95).
+static bool few_tiles(const GemmArgs& a, int64_t K, int64_t large_tiles) {
+  return large_tiles <= 64 && !(a.b_kmajor && K <= 48 && a.N > 80);
+}
 
 int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   SplitK p{};
@@ -1174,7 +1178,7 @@ int32_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   COFREE_REQUIRE(blocks > 0 && blocks < ((int64_t)1 << 31), "dense: grid too large");
   const bool drop = p.drop.scale != 0.f;  // forward products only
   const bool planes = split_params_first(a);
-  if (!planes && !drop && few_tiles(p.n_groups * p.tiles_n)) {
+  if (!planes && !drop && few_tiles(a, K, p.n_groups * p.tiles_n)) {
     p.n_groups = (a.M + FEW_TILE - 1) / FEW_TILE;
     p.tiles_n = (N + FEW_TILE - 1) / FEW_TILE;
     const int64_t few = (p.n_groups + 7) / 8 * 8 * p.tiles_n;
