@@ -765,7 +765,9 @@ int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream) {
     if (atoi(e) == 256) big = a.N > HBN;
     if (atoi(e) == 128 || atoi(e) == 64) big = false;
   }
-  bool narrow = a.N <= 64 || (!big && gemm_bf16_few(a.M, a.N));
+  // (but not where rows of more than 32 MB, which the L2s do not hold for the next tile of columns, would be read once more: launches of 104
+  // columns x 842 k over 25,000 rows 19.2 / 22.6, a layer 1000 -> 128 over 20,000 31.3 / 32.4)
+  bool narrow = a.N <= 64 || (!big && gemm_bf16_few(a.M, a.N) && 2 * a.M * K <= 32 << 20);
   if (const char* e = getenv("COFREE_BF16_TILE")) {
     if (atoi(e) >= 128) narrow = a.N <= 64;
     if (atoi(e) == 64) narrow = true;
