@@ -282,10 +282,13 @@ static int pinned_pieces(const GemmArgs& a) { return (a.K1 + 63) / 64 + (a.K2 + 
 //    72 t, 78 / 62, 110k 50 t / 50, 50k 30 t / 34; 256 x 428 150k 73 / 60; 256 x 356 1.88M 579 / 479; 256 x 303 1.88M 472 / 427; 130 x
 //    320 400k 109 / 101, 150k 49 / 46), of more than 448 k and more than 256 columns, or columns that leave tiles empty, from 65536
 //    on (500 x 500 75k 81 t / 59, 50k 60 t / 45; 140 x 512 75k 43 t / 38; but 300 x 400 75k 56 / 53, 400 x 300 47 / 44).
-//    A second workgroup for few of the columns costs what a whole one does, so up to 307 columns only from 385 k on, up to 384 from 321 on, and of
-//    these least k not A B of fewer than 196608 rows (276 columns x 276 k 276k 115 / 128, 800k 302 / 347; 300 x 350 800k 373 / 388; 276 x 448 800k
+//    A second workgroup for few of the columns costs what a whole one does, so up to 307 columns only from 385 k on, up to 384 from 321 on, and
+//    fewer than 196608 rows not of 385 to 448 k by up to 307 columns, nor A B of up to 384 columns or of these least k (276 columns x 276 k 276k 115 / 128, 800k 302 / 347; 300 x 350 800k 373 / 388; 276 x 448 800k
 //    448 / 418, 140k 93 / 91, A B 276 x 420 78 / 92, 276k 167 / 161; 380 x 276 800k 342 / 350; 330 x 350 276k 168 / 144, A B 350 x 330 140k 81 / 84; 420 x 276
-//    276k 160 / 129).
+//    276k 160 / 129; layers of 135,000 rows: GCN 400 -> 260 forward 195 / 213, 290 -> 500 backward 387 / 407).
+//    Nor does it pay where two of the wavefronts have few columns or none: up to 160 columns only from 385 k on, and up to 192 columns of up to 448 k from
+//    262144 rows on (layers: conventional GraphSAGE 130 -> 130 over 200k forward 159 / 173, 400k 305 / 334; 150 -> 150 200k backward 299 / 310; GCN 130 -> 360 200k
+//    backward 308 / 328; 172 -> 360 200k 348 / 366, 400k 0.95, 900k 0.95).
 //  * 193 to 256 k of more than 160 columns that are no multiple of 64, from 131072 rows on (200 x 256 150k 57 / 41, 1.88M 441 / 359; 172 x
 //    256 150k 49 / 41, 400k 99 / 88, 1.88M 420 / 366; 160 x 256 400k 90 / 92; 256 x 256 1.88M 372 / 366), of whole ones where the
 //    tiled kernel would be taken (256 x 256 150k 55 t / 43, 200k 69 t / 53).
@@ -303,11 +306,17 @@ bool gemm_pinned_fits(const GemmArgs& a) {
     return a.N % 64 != 0 || (!a.b_kmajor && a.dropout.q == 0.f && a.M < 1 << 18);
   }
   const bool tiles_empty = 4 * (int64_t)((a.N + 127) / 128 * 128) >= 5 * (int64_t)a.N;
+  int64_t rows = nch == 8 && (a.N > 256 || tiles_empty) ? 1 << 16 : 1 << 17;
+  if (a.N <= 192 && nch < 8) {
+    if (a.N <= 160 && nch < 7) return false;
+    rows = 1 << 18;
+  }
   if (a.N > 256) {
     const int least = tiles_empty ? 7 : a.N <= 384 ? 6 : 5;
-    if (nch < least || (nch == least && a.b_kmajor && a.M < 3 << 16)) return false;
+    if (nch < least) return false;
+    if ((nch == least && (a.b_kmajor || tiles_empty)) || (a.b_kmajor && a.N <= 384)) rows = 3 << 16;
   }
-  return a.M >= (nch == 8 && (a.N > 256 || tiles_empty) ? 1 << 16 : 1 << 17);
+  return a.M >= rows;
 }
 bool gemm_pinned_drops(const GemmArgs& a) { return gemm_pinned_fits(a) && !a.gate && !a.accumulate && a.N % 4 == 0; }
 
