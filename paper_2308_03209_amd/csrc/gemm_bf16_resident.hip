@@ -32,10 +32,7 @@ static int column_parts(int32_t N, int nch) {
 // slower (A B^T), while the tiled kernel (gemm_bf16.hip) has 128 or 256 columns in a tile, empty or not, and where a result has few of them 64,
 // with parameters as they are: eight pieces of parameters (of 32 columns x 64 k) and more then take longer than the chain of a tile.  us of a
 // GCN layer, tiled / resident: forward 300 -> 64 over 500 rows 11.7 / 13.5, 60k 26.0 / 28.6, 400 -> 40 over 30k 16.6 / 21.9; backward 256 -> 64 over 2,000
-// 18.6 / 21.9, 30k 40.8 / 42.5, 128 -> 128 over 30k 35.4 / 36.4; but A B of 33 to 64 columns and 193 to 256 k, backward 33 -> 200 over 2,000
-// 25.4 / 24.2, 64 -> 256 over 6,000 29.1 / 28.7, 64 -> 200 over 20k 34.1 / 33.4, or sums in place (conventional GraphSAGE 256 -> 45 over 2,000
-// forward 24.9 / 23.2), and A B of 65 to 128 ragged columns, whose last tile is stored element by element (GCN backward 77 -> 181 over 2,000 30.1 / 27.8,
-// 86 -> 300 over 7,000 37.6 / 36.1, 117 -> 117 over 2,000 28.6 / 26.9; conventional GraphSAGE 93 -> 181 over 7,000 49.6 / 45.1); fewer pieces: forward 64 -> 64 over 2,000 9.6 / 8.9, backward 90 -> 90 over 30k 36.0 / 35.1;
+// 18.6 / 21.9, 30k 40.8 / 42.5, 128 -> 128 over 30k 35.4 / 36.4; fewer pieces: forward 64 -> 64 over 2,000 9.6 / 8.9, backward 90 -> 90 over 30k 36.0 / 35.1;
 // more tiles: backward 300 -> 64 over 60k 60.9 / 54.5.  us of a launch
 // and the aggregation beside it, tiled / resident: A B^T of 256 x 256 (columns x k) over 20k rows 23 / 36, 100k 57 / 69, 200k 127 / 123,
 // 800k 452 / 431; 128 x 128 20k 15 / 17, 100k 34 / 34, 200k 54 / 51; 128 x 400 200k 88 / 90, 400k 195 / 183; 172 x 256 20k 28 / 31,
@@ -54,15 +51,28 @@ static int64_t resident_min_rows(int32_t N, int32_t K, int nch, bool kmajor, boo
   return param <= 24 || (nch == 5 && N > 256 && N <= 384) ? 1 << 17 : 1 << 18;
 }
 
+// Where the rows are few, though, and there are eight pieces and more: tiles store the ragged end of a row element by element, and read
+// parameters [k][column] in single floats; the resident kernel reads rows of odd length slowly, which many rows show.  Layers, tiled / resident:
+// A B of up to 64 columns GCN backward 33 -> 200 over 2,000 25.4 / 24.2, 64 -> 200 over 20k 34.1 / 33.4, 64 -> 193 over 20k 0.87, 45 -> 500 over 2,000 32.2 / 30.1,
+// 63 -> 300 over 20k 41.3 / 39.7;
+// A B^T of 45 columns and 251 k over 2,000 1.22 (33 columns 1.01, 64 1.04, 45 over 20k 1.01), of 63 and 224 over 20k 20.8 / 19.4, conventional GraphSAGE 256 -> 45 over 2,000 forward 24.9 / 23.2;
+// A B of 65 to 128 GCN backward 77 -> 181 over 2,000 30.1 / 27.8, 86 -> 300 over 7,000 37.6 / 36.1, 117 -> 117 over 2,000 28.6 / 26.9 (96 -> 184 0.99, 104 -> 117
+// 0.98), conventional GraphSAGE 93 -> 181 over 7,000 49.6 / 45.1.
+static bool few_resident(const GemmArgs& a, int nch) {
+  const bool ragged = a.N % 8 > 1;
+  if (a.N > 64) return a.b_kmajor && ragged && nch <= (a.N <= 96 ? 6 : a.N <= 128 ? 3 : 0);
+  const bool few = a.M < 1 << 14, even = (a.K1 | a.K2) % 2 == 0;
+  if (!a.b_kmajor) return ragged && nch <= 4 && (few || even);
+  return few ? ragged || nch <= 4 : even && nch <= (ragged ? 5 : 4);
+}
+
 // At most 512 k, segments of at least eight, parameters of at most four column parts, and rows as above.
 // COFREE_BF16_TILE = 0 takes every product that fits, any other none.
 static bool resident_fits(const GemmArgs& a, bool drop) {
   const int nch = pieces(a.K1) + (a.K2 > 0 ? pieces(a.K2) : 0);
   const int64_t strides = a.lda1 | a.lda2 | a.ldc | a.ldg;  // 32-bit offsets inside a tile of 32 rows
   int64_t rows = resident_min_rows(a.N, a.K1 + a.K2, nch, a.b_kmajor != 0, drop);
-  const bool short_columns = a.N <= 64 ? nch <= 4 && (a.b_kmajor || a.accumulate)
-                                       : a.b_kmajor && a.N % 8 != 0 && nch <= (a.N <= 96 ? 6 : a.N <= 128 ? 3 : 0);
-  if (!drop && (a.N + 31) / 32 * nch >= 8 && !short_columns && gemm_bf16_few(a.M, a.N)) rows = INT64_MAX;
+  if (!drop && (a.N + 31) / 32 * nch >= 8 && gemm_bf16_few(a.M, a.N) && !few_resident(a, nch)) rows = INT64_MAX;
   if (const char* e = getenv("COFREE_BF16_TILE")) {
     if (atoi(e) != 0) return false;
     rows = 0;
