@@ -289,7 +289,7 @@ static int pinned_pieces(const GemmArgs& a) { return (a.K1 + 63) / 64 + (a.K2 + 
 //    Nor does it pay where two of the wavefronts have few columns or none: up to 160 columns only from 385 k on, and up to 192 columns of up to 448 k from
 //    262144 rows on (layers: conventional GraphSAGE 130 -> 130 over 200k forward 159 / 173, 400k 305 / 334; 150 -> 150 200k backward 299 / 310; GCN 130 -> 360 200k
 //    backward 308 / 328; 172 -> 360 200k 348 / 366, 400k 0.95, 900k 0.95).
-//  * 193 to 256 k of more than 160 columns that are no multiple of 64, from 131072 rows on (200 x 256 150k 57 / 41, 1.88M 441 / 359; 172 x
+//  * 193 to 256 k (not fewer, in two segments: 182 columns x 71 + 71 k over 200k 50 / 62) of more than 160 columns that are no multiple of 64, from 131072 rows on (200 x 256 150k 57 / 41, 1.88M 441 / 359; 172 x
 //    256 150k 49 / 41, 400k 99 / 88, 1.88M 420 / 366; 160 x 256 400k 90 / 92; 256 x 256 1.88M 372 / 366), of whole ones where the
 //    tiled kernel would be taken (256 x 256 150k 55 t / 43, 200k 69 t / 53).
 // Up to 128 columns half of the wavefronts would have none (128 x 256 1.88M 265 / 351).
@@ -302,7 +302,7 @@ bool gemm_pinned_fits(const GemmArgs& a) {
     return false;
   if (const char* e = getenv("COFREE_BF16_TILE")) return atoi(e) == 1;
   if (nch == 4) {
-    if (a.N <= 160 || a.N > 256 || a.M < 1 << 17) return false;
+    if (a.N <= 160 || a.N > 256 || a.M < 1 << 17 || a.K1 + a.K2 <= 192) return false;
     return a.N % 64 != 0 || (!a.b_kmajor && a.dropout.q == 0.f && a.M < 1 << 18);
   }
   const bool tiles_empty = 4 * (int64_t)((a.N + 127) / 128 * 128) >= 5 * (int64_t)a.N;
