@@ -460,7 +460,7 @@ size_t wgrad_narrow_workspace_floats(int32_t N1, int32_t N2, int32_t N2b, int64_
 int32_t launch_wgrad_narrow(const WgradArgs& a, const WgradArgs* b, SplitSums* sums, hipStream_t stream);  // b: or null
 bool wgrads_pair(const WgradArgs& a, const WgradArgs& b);  // whether both can be one launch of that
 int32_t launch_gemm_bf16(const GemmArgs& a, hipStream_t stream);
-bool gemm_bf16_few(int64_t M, int32_t N);  // results of so few tiles that they are taken 64 columns wide
+bool gemm_bf16_few(int64_t M, int32_t N);  // results of so few tiles that tiles of 64 columns can pay
 // bfloat16 products whose parameters fit LDS (gemm_bf16_resident.hip)
 bool gemm_resident_fits(const GemmArgs& a);
 bool gemm_resident_drops(const GemmArgs& a);
